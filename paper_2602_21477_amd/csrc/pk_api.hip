@@ -207,6 +207,7 @@ struct Plan {
     double avg_per_list; // queries per list on average (the largest over the handles of the call)
     uint32_t stride, ecap, tile_cap, span;
     uint64_t cbuf_entries; // entries of all emission regions together
+    uint32_t rescues;      // overflowed queries of the call that have a region to be scored again into (0: none can overflow)
     bool need_coarse, need_fine, f16;
     bool raw_queries; // the coarse step reads the caller's query rows directly (no preparation launch)
     bool wl_small;    // the second half of the work list is small enough for one workgroup (rides in the threshold launch)
@@ -328,6 +329,9 @@ const Tunables &tunables()
 
 // a tile of the threshold sample scores one query against one page of its first probed list
 constexpr int kSampleSlots = 1;
+
+// largest batch whose queries all get emission regions of 32768 entries (see emit_cap_for)
+constexpr int64_t kRoomyBatch = 128;
 
 int grid_for(const pk_index *ix, int row_bytes, int mq)
 {
@@ -492,6 +496,12 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     p.cbuf_entries = (uint64_t)nq * p.ecap;
     // a smaller batch has larger regions: none needs more in all than this
     if (worst) p.cbuf_entries = std::max<uint64_t>(p.cbuf_entries, std::min<uint64_t>(32768ull * (uint64_t)nq, 4ull << 20));
+    // A batch large enough that its regions are not the roomy ones (32768 entries) can have a query overflow in
+    // ordinary use (a query whose nearest list is a merged cluster: its sample's k-th best lets a tenth of all its
+    // rows through); the launch that scores such queries again, 3 us when there is none, then pays for itself.  Its
+    // regions are the sample's values, which nothing reads any more by then.
+    if (need_fine && nq > kRoomyBatch && (uint64_t)p.ecap < round_up(wmax, 16))
+        p.rescues = (uint32_t)std::min<uint64_t>((uint64_t)nq * p.span * 4 / (kRescueCap * 8), kRescueRegions);
     p.tile_cap = (uint32_t)tiles;
     carve(p, nullptr, own);
     return PK_OK;
@@ -816,6 +826,11 @@ int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, i
     f.qnorm = p.qn;
     f.out_ids = out_ids;
     f.out_dist = out_dist;
+    f.rkeys = reinterpret_cast<unsigned long long *>(p.svals);
+    f.rcnt = p.sslot_o;
+    f.rregions = p.rescues;
+    f.rcap = kRescueCap;
+    if (p.rescues > 0) PK_HIP(launch_rescue(f, m, p.nq, 2 * own->num_cu, s));
     PK_HIP(launch_select_final(f, m, p.nq, s));
     if (timed) PK_TRY(mark(own, s));
     return PK_OK;

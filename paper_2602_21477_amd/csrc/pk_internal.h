@@ -378,7 +378,15 @@ struct FinalArgs {
     const float *qnorm;               // [nq]
     int64_t *out_ids;
     float *out_dist;
+    // Queries whose region overflowed, scored again by many workgroups (launch_rescue): the first `rregions` of them,
+    // in query order, have a region of rcap keys each; rcnt[q] counts what query q got (more than rcap: overflowed again)
+    unsigned long long *rkeys;
+    uint32_t *rcnt;                   // [nq] zero before launch_rescue
+    uint32_t rregions, rcap;          // rregions 0: launch_rescue was not called
 };
+constexpr uint32_t kRescueCap = 4096;    // keys per rescue region: what the final selection takes in registers
+constexpr uint32_t kRescueRegions = 128; // most queries of a call that are rescued
+hipError_t launch_rescue(const FinalArgs &a, const MultiArgs &m, int64_t nq, int grid, hipStream_t s);
 hipError_t launch_select_final(const FinalArgs &a, const MultiArgs &m, int64_t nq, hipStream_t s);
 
 // Per-query bookkeeping of the coarse step, filled while the queries are prepared.
@@ -476,7 +484,7 @@ struct SampleArgs {
     uint32_t span;             // values per query = sp * rows per page (same for all handles)
     Tile *tiles;               // [nq * sp]
     uint32_t *slot_query;      // [nq] = q
-    uint32_t *slot_out;        // [nq] = q * span
+    uint32_t *slot_out;        // [nq] = q * span; once the threshold exists: 0 (the query's rescue counter)
     float *vals;               // [nq][span], pre-filled with the padding value by the kernel
     uint32_t *scalars;         // [0] ntiles [1] tile counter [2] grab size
     uint32_t *tau;             // [nq] out: k-th best sample key, or 0xffffffff

@@ -350,11 +350,32 @@ static uint32_t final_cap(int K)
     return c;
 }
 
+// One query (LDS: the row, then a row of zeros; qbase = the lane's part) against 32 rows of a page, 16 columns in
+// each accumulator: the MFMA sequence of the scan kernels (the query in MFMA row 0, zeros in the other rows), so the
+// values are bit-identical to the scan's.  Element 0 of lanes 0..15 holds the dot products.
+template <int STORAGE>
+__device__ __forceinline__ void score_32_rows(f32x4 &acc0, f32x4 &acc1, const char *qbase, gbytes p0, int row_bytes)
+{
+    const int nit = row_bytes / kIterBytes;
+    const gbytes p1 = p0 + (size_t)16 * row_bytes;
+    acc0 = f32x4{0.f, 0.f, 0.f, 0.f};
+    acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int it = 0; it < nit; ++it) {
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) {
+            const u32x4 qa = *reinterpret_cast<const u32x4 *>(qbase + (size_t)it * kIterBytes + s4 * 64);
+            const u32x4 x0 = *reinterpret_cast<gvec4>(p0 + (size_t)it * kIterBytes + s4 * 64);
+            const u32x4 x1 = *reinterpret_cast<gvec4>(p1 + (size_t)it * kIterBytes + s4 * 64);
+            mfma_step<STORAGE>(acc0, qa, x0);
+            mfma_step<STORAGE>(acc1, qa, x1);
+        }
+    }
+}
+
 // Exact pass over every row the query probes, for a query whose emission region overflowed
 // (more candidates passed the gate than the region holds: no usable threshold, or a tie group
-// larger than the region).  One workgroup walks the probed lists page by page; each wave
-// scores 32 rows against the one query with the MFMA sequence of the scan kernels (the query
-// in MFMA row 0, zeros in the other rows), so the values are bit-identical to the scan's.
+// larger than the region) and that launch_rescue did not select from (no region, or one that
+// overflowed as well).  One workgroup walks the probed lists page by page; each wave scores 32 rows.
 //   by_id false: every value goes to the selector as (value key, position)  -> best K
 //   by_id true:  the ids of the rows whose value key equals `tau` go to the selector
 //                (lowest ids of a tie group; several rows may carry one id)
@@ -366,7 +387,7 @@ __device__ void rescore_query(const FinalArgs &a, const MultiArgs &h, uint32_t q
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ln = lane & 15, lg = lane >> 4;
     const DevIndex &ix = *h.ix[a.qagent[q]];
-    const int row_bytes = a.row_bytes, nit = row_bytes / kIterBytes;
+    const int row_bytes = a.row_bytes;
     const uint32_t P = (uint32_t)ix.P;
     const float qn = a.qnorm[q];
     const uint32_t *po = a.pair_off + (size_t)q * (a.nprobe + 1);
@@ -387,19 +408,8 @@ __device__ void rescore_query(const FinalArgs &a, const MultiArgs &h, uint32_t q
                 if (rb >= nrows) continue; // the next reserve() is a barrier every wave reaches
                 // rows rb .. rb + 31 lie inside the page (its size is a multiple of 32); those past
                 // nrows hold stale bytes and their values are not used
-                const gbytes p0 = px + (size_t)(rb + ln) * row_bytes + lg * 16;
-                const gbytes p1 = p0 + (size_t)16 * row_bytes;
-                f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-                for (int it = 0; it < nit; ++it) {
-#pragma unroll
-                    for (int s4 = 0; s4 < 4; ++s4) {
-                        const u32x4 qa = *reinterpret_cast<const u32x4 *>(qbase + (size_t)it * kIterBytes + s4 * 64);
-                        const u32x4 x0 = *reinterpret_cast<gvec4>(p0 + (size_t)it * kIterBytes + s4 * 64);
-                        const u32x4 x1 = *reinterpret_cast<gvec4>(p1 + (size_t)it * kIterBytes + s4 * 64);
-                        mfma_step<STORAGE>(acc0, qa, x0);
-                        mfma_step<STORAGE>(acc1, qa, x1);
-                    }
-                }
+                f32x4 acc0, acc1;
+                score_32_rows<STORAGE>(acc0, acc1, qbase, px + (size_t)(rb + ln) * row_bytes + lg * 16, row_bytes);
                 if (lg == 0) { // accumulator element 0 of lanes 0..15: MFMA row 0 (the query) x column ln (the row)
 #pragma unroll
                     for (int nt = 0; nt < 2; ++nt) {
@@ -415,6 +425,119 @@ __device__ void rescore_query(const FinalArgs &a, const MultiArgs &h, uint32_t q
                         }
                     }
                 }
+            }
+        }
+    }
+}
+
+// Queries whose emission region overflowed, scored again by the whole chip.  The keys that a region did keep are
+// candidates of the query, so the k-th best of any k of them bounds the k-th best of all: with that as the threshold
+// (a few hundred rows pass it) every probed row is scored once more, and what passes goes to a region of its own.
+// Workgroup b serves overflowed query b % n (n of them, counted by every workgroup for itself) and takes every
+// n-th-workgroup's share of its pages.  Bound by latency: a query of 148 000 rows of 1536 bytes (228 MB) takes its
+// 1170 pages to 512 workgroups, where select_final's one workgroup (rescore_query) needed 15.4 ms for it: a batch of
+// 1024 over 10 M x 768 fp16 rows with one such query went from 18.1 to 2.96 ms, as long as one with none.
+template <int STORAGE>
+__global__ __launch_bounds__(kSelThreads) void rescue_kernel(FinalArgs a, MultiArgs h, uint32_t nq)
+{
+    extern __shared__ __align__(16) unsigned char s_dyn[];
+    __shared__ __align__(16) uint32_t hist[4][256];
+    __shared__ uint32_t s_wave[17];
+    __shared__ uint32_t s_over[kRescueRegions]; // the overflowed queries, ascending
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // the overflowed queries, in query order
+    uint32_t n = 0;
+    for (uint32_t q0 = 0; q0 < nq && n < a.rregions; q0 += kSelThreads) {
+        const uint32_t q = q0 + (uint32_t)tid;
+        const bool over = q < nq && a.qcnt[q] > a.ecap;
+        const unsigned long long m = __ballot(over);
+        __syncthreads(); // s_wave of the round before is no longer read
+        if (lane == 0) s_wave[wave] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint32_t at = n + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        for (int w = 0; w < 4; ++w) {
+            if (w < wave) at += s_wave[w];
+            n += s_wave[w];
+        }
+        if (over && at < a.rregions) s_over[at] = q;
+    }
+    n = n < a.rregions ? n : a.rregions;
+    if (n == 0) return;
+    __syncthreads();
+    const uint32_t region = blockIdx.x % n, part = blockIdx.x / n, parts = (gridDim.x - region + n - 1) / n;
+    const uint32_t q = s_over[region];
+    const DevIndex &ix = *h.ix[a.qagent[q]];
+    const uint32_t P = (uint32_t)ix.P, nprobe = (uint32_t)a.nprobe;
+    const int row_bytes = a.row_bytes, qstride = row_bytes + kQPadBytes;
+    char *s_q = reinterpret_cast<char *>(s_dyn);                          // the query row, then a row of zeros
+    uint32_t *s_len = reinterpret_cast<uint32_t *>(s_q + 2 * qstride);    // [nprobe] rows of each probed list
+    uint32_t *s_list = s_len + nprobe, *s_page0 = s_list + nprobe;        // [nprobe] the list; [nprobe] pages before it
+    for (int i = tid; i < 2 * qstride / 16; i += kSelThreads) {
+        u32x4 w = {0u, 0u, 0u, 0u};
+        if (i < row_bytes / 16) w = *reinterpret_cast<const u32x4 *>(a.qs + (size_t)q * row_bytes + (size_t)i * 16);
+        *reinterpret_cast<u32x4 *>(s_q + (size_t)i * 16) = w;
+    }
+    for (uint32_t r = (uint32_t)tid; r < nprobe; r += kSelThreads) {
+        const uint32_t l = (uint32_t)a.probes[(size_t)q * nprobe + r];
+        const uint32_t len = l < (uint32_t)ix.nlist ? ix.list_len[l] : 0u;
+        s_list[r] = l;
+        s_len[r] = len;
+        s_page0[r] = (len + P - 1) / P;
+    }
+    // threshold: the k-th best of the keys stored last (the gate tightened over time, so those are the best)
+    constexpr int VPT = (int)kRescueCap / kSelThreads;
+    const uint32_t used = a.ecap < kRescueCap ? a.ecap : kRescueCap; // >= k: a region holds at least k + 1 keys
+    const u64 *stored = a.keys + (size_t)q * a.ecap + (a.ecap - used);
+    uint32_t key[VPT];
+    bool live[VPT];
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+        const uint32_t p = (uint32_t)tid + (uint32_t)kSelThreads * j;
+        live[j] = p < used;
+        key[j] = live[j] ? (uint32_t)(stored[p] >> 32) : 0xffffffffu;
+    }
+    uint32_t left, ties;
+    const uint32_t tau = radix_kth<VPT>(key, live, (uint32_t)a.k, hist, left, ties); // its barriers publish the LDS arrays
+    const uint32_t pages = block_exscan(s_page0, s_page0, nprobe, s_wave);
+
+    const int ln = lane & 15, lg = lane >> 4;
+    const float qn = a.qnorm[q];
+    const char *qbase = s_q + (size_t)(ln == 0 ? 0 : 1) * qstride + lg * 16;
+    u64 *out = a.rkeys + (size_t)region * a.rcap;
+    for (uint32_t u = part; u < pages; u += parts) {
+        uint32_t lo = 0, hi = nprobe - 1; // the last list whose pages start at or before u (empty lists share a start: the last has them)
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) >> 1;
+            if (s_page0[mid] <= u) lo = mid;
+            else hi = mid - 1;
+        }
+        const uint32_t lp = u - s_page0[lo], len = s_len[lo];
+        const uint32_t pg = phys_page(ix, s_list[lo], lp);
+        const Arena &ar = arena_of(ix, pg);
+        const size_t local = (size_t)(pg - ar.first_page) * P;
+        const gbytes px = in_global(ar.vec + local * (size_t)row_bytes);
+        const uint32_t nrows = len - lp * P < P ? len - lp * P : P;
+        const uint32_t first = a.pair_off[(size_t)q * (nprobe + 1) + lo] + lp * P; // position of the page's first row
+        // rows rb .. rb + 31 lie inside the page (its size is a multiple of 32); those past nrows hold stale bytes
+        // and their values are not used
+        for (uint32_t rb = (uint32_t)wave * kRowBlock; rb < nrows; rb += 4 * kRowBlock) {
+            f32x4 acc0, acc1;
+            score_32_rows<STORAGE>(acc0, acc1, qbase, px + (size_t)(rb + ln) * row_bytes + lg * 16, row_bytes);
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                const uint32_t row = rb + (uint32_t)nt * 16u + (uint32_t)ln;
+                const bool mine = lg == 0 && row < nrows;
+                float v = nt == 0 ? acc0[0] : acc1[0];
+                if (a.metric == PK_METRIC_L2) v = l2_from_dot(mine ? ar.norm[local + row] : 0.f, v, qn);
+                const uint32_t bits = order_bits(v, a.metric);
+                const bool pass = mine && bits <= tau;
+                const uint32_t m = (uint32_t)__ballot(pass); // lanes 0..15
+                if (m == 0u) continue;
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&a.rcnt[q], (uint32_t)__popc(m));
+                base = __shfl(base, 0);
+                const uint32_t at = base + (uint32_t)__popc(m & ((1u << ln) - 1u));
+                if (pass && at < a.rcap) out[at] = ((u64)bits << 32) | (first + row);
             }
         }
     }
@@ -510,8 +633,8 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     // everything the usual path reads from global memory is requested at once: the count, the thread's key
     // of a short region (the entry exists whatever the count; it is used only if it is below it), the
     // query's rows of the candidate layout, its index
-    const uint32_t cnt_q = a.qcnt[q];
-    const u64 early = threadIdx.x < a.ecap ? a.keys[region + threadIdx.x] : kMaxKey;
+    uint32_t cnt_q = a.qcnt[q];
+    u64 early = threadIdx.x < a.ecap ? a.keys[region + threadIdx.x] : kMaxKey;
     for (int r = threadIdx.x; r <= a.nprobe; r += blockDim.x) {
         s_po[r] = a.pair_off[(size_t)q * (a.nprobe + 1) + r];
         if (r < a.nprobe) s_pr[r] = (uint32_t)a.probes[(size_t)q * a.nprobe + r];
@@ -533,16 +656,31 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     }
     Selector sel;
     sel.init(keys, &s_cnt, a.K, cap);
-    const bool overflow = cnt_q > a.ecap; // the region lost candidates: select by rescoring the query's rows
+    bool overflow = cnt_q > a.ecap; // the region lost candidates: select by rescoring the query's rows
+    const u64 *v = a.keys + region; // where the query's candidates are
+    if (overflow && a.rregions > 0) {
+        // ... unless they were scored again already: the query's region is its number among the overflowed queries
+        uint32_t before = 0;
+        for (uint32_t t = threadIdx.x; t < q; t += blockDim.x) before += a.qcnt[t] > a.ecap ? 1u : 0u;
+        for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+        if ((threadIdx.x & 63) == 0) s_redpos[threadIdx.x >> 6] = before;
+        __syncthreads();
+        before = s_redpos[0] + s_redpos[1] + s_redpos[2] + s_redpos[3];
+        const uint32_t got = a.rcnt[q];
+        if (before < a.rregions && got <= a.rcap) {
+            overflow = false;
+            v = a.rkeys + (size_t)before * a.rcap;
+            cnt_q = got;
+            early = threadIdx.x < got ? v[threadIdx.x] : kMaxKey;
+        }
+    }
     const bool in_registers = cnt_q <= 16u * kSelThreads && !overflow;
     if (in_registers) {
         uint32_t(*hist)[256] = reinterpret_cast<uint32_t(*)[256]>(s_q);
-        const u64 *v = a.keys + region;
         if (cnt_q <= (uint32_t)kSelThreads) final_by_radix<1>(v, cnt_q, (uint32_t)a.K, early, hist, keys, &s_cnt);
         else if (cnt_q <= 4u * kSelThreads) final_by_radix<4>(v, cnt_q, (uint32_t)a.K, early, hist, keys, &s_cnt);
         else final_by_radix<16>(v, cnt_q, (uint32_t)a.K, early, hist, keys, &s_cnt);
     } else if (!overflow) {
-        const u64 *v = a.keys + region;
         // short ranges go one key per thread and round, so the buffer that gets sorted stays small
         const uint32_t per = cnt_q <= 8192u ? 1u : (uint32_t)kSelVec;
         const uint32_t round = kSelThreads * per;
@@ -609,7 +747,7 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
             __syncthreads();
         } else {
         const uint32_t total = cnt_q;
-        const u64 *rk = a.keys + region;
+        const u64 *rk = v;
         // Members are taken in (id, position) order: several rows may carry one id, and each
         // of them is a candidate of its own.
         long long last_id = 0;
@@ -808,6 +946,22 @@ hipError_t launch_select_probes(const unsigned long long *partial, int nchunks, 
     if (nq <= 0) return hipSuccess;
     hipLaunchKernelGGL(select_probes_kernel, dim3((uint32_t)nq), dim3(kSelThreads), 0, s, partial, nchunks, K, nprobe,
                        probes);
+    return hipGetLastError();
+}
+
+// grid: workgroups (at least rregions)
+hipError_t launch_rescue(const FinalArgs &a, const MultiArgs &m, int64_t nq, int grid, hipStream_t s)
+{
+    if (nq <= 0) return hipSuccess;
+    static_assert(kRescueCap % kSelThreads == 0, "the threshold of a rescue comes out of registers");
+    if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || a.ecap < (uint32_t)a.K || a.rcap != kRescueCap ||
+        a.rregions < 1 || a.rregions > kRescueRegions || grid < (int)a.rregions)
+        return hipErrorInvalidValue;
+    const size_t lds = (size_t)2 * (a.row_bytes + kQPadBytes) + (size_t)3 * a.nprobe * sizeof(uint32_t);
+    if (a.storage == PK_F16)
+        hipLaunchKernelGGL(rescue_kernel<PK_F16>, dim3(grid), dim3(kSelThreads), lds, s, a, m, (uint32_t)nq);
+    else
+        hipLaunchKernelGGL(rescue_kernel<PK_F32>, dim3(grid), dim3(kSelThreads), lds, s, a, m, (uint32_t)nq);
     return hipGetLastError();
 }
 
