@@ -16,7 +16,9 @@ namespace {
 
 constexpr uint64_t kMagic = 0x70616e63616b6531ull;
 constexpr uint64_t kRegionBytes = 256ull << 20; // emission regions of one launch sequence (all queries together)
-constexpr int kBuildChunk = 16384;          // vectors assigned per coarse pass during the build
+constexpr int kFillChunk = 16384;           // vectors of a chunk that fills 128 tiles of 128 x 128 whatever the number of lists
+constexpr int kAssignChunk = 32768;         // vectors assigned per launch pair by the build and by k-means: 512 lists
+                                            // give every CU a 256 x 256 tile of scores
 constexpr int kInsertFast = 1024;           // most vectors of an insert call that takes the two-launch path
 
 #define PK_HIP(expr)                                   \
@@ -210,9 +212,12 @@ struct Plan {
     uint32_t rescues;      // overflowed queries of the call that have a region to be scored again into (0: none can overflow)
     bool need_coarse, need_fine, f16;
     bool raw_queries; // the coarse step reads the caller's query rows directly (no preparation launch)
+    bool split;       // the coarse scores come from the split-operand GEMM
     bool wl_small;    // the second half of the work list is small enough for one workgroup (rides in the threshold launch)
     // buffers
     char *qs32, *qs;
+    char *xs, *cs;    // split: query rows and centroid table as halfs,
+    float *xback, *cback; // and what undoes their rows' scales
     float *qn32, *qn, *S, *svals, *tlo, *tinv;
     uint32_t *cand_off, *cand_cnt, *lcnt, *lstart, *lfill, *ltile, *lhtile, *pair_off, *slot_q, *slot_o, *scalars,
         *tau, *tcur, *hist, *ccnt, *sslot_q, *sslot_o;
@@ -238,6 +243,12 @@ void carve(Plan &p, char *base, const pk_index *own)
     }
     p.qagent = c.take<uint16_t>(nq);
     p.scalars = c.take<uint32_t>(32);
+    if (p.split && !p.need_fine) { // nobody reads the queries in fp32 then
+        p.xs = p.qs32;
+        p.cs = c.take<char>((size_t)own->nlist_pad * own->rb32);
+        p.xback = c.take<float>(nq);
+        p.cback = c.take<float>(own->nlist_pad);
+    }
     p.probes = c.take<int32_t>(nq * p.nprobe);
     p.cand_off = c.take<uint32_t>(nq);
     p.cand_cnt = c.take<uint32_t>(nq);
@@ -268,6 +279,13 @@ void carve(Plan &p, char *base, const pk_index *own)
         p.stiles = c.take<Tile>(nq * p.sp + 1);
         p.svals = c.take<float>(nq * p.span + 16);
         p.cbuf = c.take<unsigned long long>((size_t)p.cbuf_entries + 16);
+        if (p.split) { // the emission regions are written after the coarse step is over
+            Carver o{reinterpret_cast<char *>(p.cbuf), 0};
+            p.xs = o.take<char>(nq * own->rb32);
+            p.cs = o.take<char>((size_t)own->nlist_pad * own->rb32);
+            p.xback = o.take<float>(nq);
+            p.cback = o.take<float>(own->nlist_pad);
+        }
     }
     p.bytes = round_up(c.off, 256);
 }
@@ -332,6 +350,13 @@ constexpr int kSampleSlots = 1;
 
 // largest batch whose queries all get emission regions of 32768 entries (see emit_cap_for)
 constexpr int64_t kRoomyBatch = 128;
+
+// bytes of the split operands of one handle's coarse step over nq queries
+size_t split_bytes(const pk_index *ix, int64_t nq)
+{
+    return round_up((size_t)nq * ix->rb32, 256) + round_up((size_t)ix->nlist_pad * ix->rb32, 256) +
+           round_up((size_t)nq * 4, 256) + round_up((size_t)ix->nlist_pad * 4, 256);
+}
 
 int grid_for(const pk_index *ix, int row_bytes, int mq)
 {
@@ -490,12 +515,16 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     p.raw_queries = need_coarse && !worst && own->cfg.metric == PK_METRIC_IP && own->cfg.d * 4 == own->rb32;
     for (int a = 0; a < nh && p.raw_queries; ++a)
         if (coarse_by_gemm(qlo[a + 1] - qlo[a], hs[a])) p.raw_queries = false;
-    // few lists, pairs and tiles: the threshold kernel's workgroups lay out slots and tiles as well (see wl_spread)
-    p.wl_small = (uint64_t)nh * (uint64_t)nlist_hi <= kWlSmallLists && (uint64_t)nq * (uint64_t)nprobe <= 16384 && tiles <= 65536;
     p.ecap = emit_cap_for(own, p.K, wmax, nq);
     p.cbuf_entries = (uint64_t)nq * p.ecap;
     // a smaller batch has larger regions: none needs more in all than this
     if (worst) p.cbuf_entries = std::max<uint64_t>(p.cbuf_entries, std::min<uint64_t>(32768ull * (uint64_t)nq, 4ull << 20));
+    // The split operands of a search lie where the emitted candidates will: only where they fit, so that no search
+    // needs a larger workspace for them (the fp32 GEMM takes the others, and calls over several handles).
+    p.split = need_coarse && nh == 1 && !worst && coarse_by_gemm(qlo[1] - qlo[0], own) &&
+              (!need_fine || split_bytes(own, nq) <= (size_t)p.cbuf_entries * sizeof(unsigned long long));
+    // few lists, pairs and tiles: the threshold kernel's workgroups lay out slots and tiles as well (see wl_spread)
+    p.wl_small = (uint64_t)nh * (uint64_t)nlist_hi <= kWlSmallLists && (uint64_t)nq * (uint64_t)nprobe <= 16384 && tiles <= 65536;
     // A batch large enough that its regions are not the roomy ones (32768 entries) can have a query overflow in
     // ordinary use (a query whose nearest list is a merged cluster: its sample's k-th best lets a tenth of all its
     // rows through); the launch that scores such queries again, 3 us when there is none, then pays for itself.  Its
@@ -509,11 +538,12 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
 
 // A query segment goes through the 128 x 128-tile MFMA GEMM when it has enough tiles to
 // occupy a good part of the chip; smaller segments take the finely cut centroid kernel.
-bool coarse_by_gemm(uint32_t nqa, const pk_index *ix)
+bool coarse_tiles(uint32_t nqa, int nlist_pad)
 {
-    const uint64_t wgs = (uint64_t)((nqa + 127) / 128) * (uint64_t)((ix->nlist_pad + 127) / 128);
+    const uint64_t wgs = (uint64_t)((nqa + 127) / 128) * (uint64_t)((nlist_pad + 127) / 128);
     return wgs >= (uint64_t)tunables().gemm_wgs;
 }
+bool coarse_by_gemm(uint32_t nqa, const pk_index *ix) { return coarse_tiles(nqa, ix->nlist_pad); }
 
 void fill_multi(MultiArgs &m, pk_index *const *hs, int nh, const uint32_t *qlo)
 {
@@ -602,7 +632,44 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
     qm.nclear = p.need_fine ? 2u * (uint32_t)p.nh * (uint32_t)p.nlist_max : 0u; // and the fill marks behind them
     // small segments: one launch of the centroid kernel for all of them
     CentroidArgs ca{};
-    if (p.raw_queries) {
+    if (p.split) {
+        SplitRowsArgs sr{};
+        sr.x = q;
+        sr.c = own->host.cent;
+        sr.m = (uint32_t)p.nq;
+        sr.n_c = (uint32_t)own->nlist_pad;
+        sr.d = own->cfg.d;
+        sr.ld = own->dpad32;
+        sr.xs = p.xs;
+        sr.cs = p.cs;
+        sr.x_back = p.xback;
+        sr.c_back = p.cback;
+        sr.qnorm = p.qn32;
+        if (p.need_fine && p.f16) { // what the scan reads, made in the same pass
+            sr.half_rows = p.qs;
+            sr.half_norm = p.qn;
+            sr.half_bytes = own->row_bytes;
+        } else if (p.need_fine) {
+            sr.copy = reinterpret_cast<float *>(p.qs32);
+        }
+        sr.meta = qm;
+        PK_HIP(launch_split_rows(sr, m, s));
+        SplitGemmArgs g{};
+        g.q = p.xs;
+        g.c = p.cs;
+        g.q_back = p.xback;
+        g.c_back = p.cback;
+        g.qnorm = p.qn32;
+        g.cnorm = own->host.cnorm;
+        g.out = p.S;
+        g.m = (int)p.nq;
+        g.n = own->cfg.nlist;
+        g.n_pad = own->nlist_pad;
+        g.ld = own->dpad32;
+        g.metric = own->cfg.metric;
+        g.stride = p.stride;
+        PK_HIP(launch_gemm_split(g, own->num_cu, s));
+    } else if (p.raw_queries) {
         // the caller's rows are usable as they are and no norms are needed: the centroid kernel does the bookkeeping
         ca.qs = reinterpret_cast<const char *>(q);
         ca.qnorm = nullptr;
@@ -612,52 +679,54 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
         ca.qs = p.qs32;
         ca.qnorm = p.qn32;
     }
-    ca.out = p.S;
-    ca.stride = p.stride;
-    ca.row_bytes = own->rb32;
-    ca.metric = own->cfg.metric;
-    uint32_t longest = 0;
-    for (int a = 0; a < m.n; ++a) {
-        const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
-        if (!coarse_by_gemm(nqa, hs[a])) longest = std::max(longest, nqa);
-    }
-    // Queries per workgroup: as many as one workgroup takes (64) when that still leaves a workgroup for every
-    // CU; fewer otherwise, since the kernel is a chain of dependent slices and a chip half empty gains nothing
-    // from the centroid rows a larger group shares.
-    ca.chunk = (int)std::min<uint32_t>(64, (longest + 15) / 16 * 16);
-    uint64_t wgs = 0;
-    while (true) {
-        wgs = 0;
+    if (!p.split) {
+        ca.out = p.S;
+        ca.stride = p.stride;
+        ca.row_bytes = own->rb32;
+        ca.metric = own->cfg.metric;
+        uint32_t longest = 0;
         for (int a = 0; a < m.n; ++a) {
             const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
-            ca.blk[a] = (uint32_t)wgs;
-            if (nqa > 0 && !coarse_by_gemm(nqa, hs[a]))
-                wgs += (uint64_t)((nqa + ca.chunk - 1) / ca.chunk) * (uint64_t)(hs[a]->nlist_pad / 16);
+            if (!coarse_by_gemm(nqa, hs[a])) longest = std::max(longest, nqa);
         }
-        if (wgs >= (uint64_t)own->num_cu || ca.chunk <= 16) break;
-        ca.chunk -= 16;
-    }
-    if (wgs > 0x7fffffffull) return PK_ERR_UNSUPPORTED;
-    ca.blk[m.n] = (uint32_t)wgs;
-    if (wgs > 0) PK_HIP(launch_centroid_scores(ca, m, s));
-    for (int a = 0; a < m.n; ++a) {
-        const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
-        if (nqa == 0 || !coarse_by_gemm(nqa, hs[a])) continue;
-        const pk_index *ix = hs[a];
-        GemmArgs g{};
-        g.q = reinterpret_cast<const float *>(p.qs32) + (size_t)m.qlo[a] * ix->dpad32;
-        g.c = ix->host.cent;
-        g.qnorm = p.qn32 + m.qlo[a];
-        g.cnorm = ix->host.cnorm;
-        g.out = p.S + (size_t)m.qlo[a] * p.stride;
-        g.m = (int)nqa;
-        g.n = ix->cfg.nlist;
-        g.n_pad = ix->nlist_pad;
-        g.n_store = ix->nlist_pad;
-        g.ld = ix->dpad32;
-        g.metric = ix->cfg.metric;
-        g.stride = p.stride;
-        PK_HIP(launch_gemm_scores(g, s));
+        // Queries per workgroup: as many as one workgroup takes (64) when that still leaves a workgroup for every
+        // CU; fewer otherwise, since the kernel is a chain of dependent slices and a chip half empty gains nothing
+        // from the centroid rows a larger group shares.
+        ca.chunk = (int)std::min<uint32_t>(64, (longest + 15) / 16 * 16);
+        uint64_t wgs = 0;
+        while (true) {
+            wgs = 0;
+            for (int a = 0; a < m.n; ++a) {
+                const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
+                ca.blk[a] = (uint32_t)wgs;
+                if (nqa > 0 && !coarse_by_gemm(nqa, hs[a]))
+                    wgs += (uint64_t)((nqa + ca.chunk - 1) / ca.chunk) * (uint64_t)(hs[a]->nlist_pad / 16);
+            }
+            if (wgs >= (uint64_t)own->num_cu || ca.chunk <= 16) break;
+            ca.chunk -= 16;
+        }
+        if (wgs > 0x7fffffffull) return PK_ERR_UNSUPPORTED;
+        ca.blk[m.n] = (uint32_t)wgs;
+        if (wgs > 0) PK_HIP(launch_centroid_scores(ca, m, s));
+        for (int a = 0; a < m.n; ++a) {
+            const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
+            if (nqa == 0 || !coarse_by_gemm(nqa, hs[a])) continue;
+            const pk_index *ix = hs[a];
+            GemmArgs g{};
+            g.q = reinterpret_cast<const float *>(p.qs32) + (size_t)m.qlo[a] * ix->dpad32;
+            g.c = ix->host.cent;
+            g.qnorm = p.qn32 + m.qlo[a];
+            g.cnorm = ix->host.cnorm;
+            g.out = p.S + (size_t)m.qlo[a] * p.stride;
+            g.m = (int)nqa;
+            g.n = ix->cfg.nlist;
+            g.n_pad = ix->nlist_pad;
+            g.n_store = ix->nlist_pad;
+            g.ld = ix->dpad32;
+            g.metric = ix->cfg.metric;
+            g.stride = p.stride;
+            PK_HIP(launch_gemm_scores(g, s));
+        }
     }
     if (p.nlist_max <= kDenseSelectMax && tunables().densesel) {
         if (counted && p.need_fine) {
@@ -692,7 +761,7 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
 int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, int64_t *out_ids, float *out_dist,
              hipStream_t s, bool timed, bool counted, bool fixed)
 {
-    if (p.f16) PK_HIP(launch_prep_queries(q, p.nq, own->cfg.d, PK_F16, own->row_bytes, p.qs, p.qn, s));
+    if (p.f16 && !p.split) PK_HIP(launch_prep_queries(q, p.nq, own->cfg.d, PK_F16, own->row_bytes, p.qs, p.qn, s));
     WorklistArgs w;
     SampleArgs sm;
     fill_worklist_args(p, own, w, sm);
@@ -1097,6 +1166,120 @@ int note_inserted(pk_index *ix, int64_t m, hipStream_t s)
     return snapshot_pages(ix, s);
 }
 
+// Scratch of assign_rows for n vectors in chunks of `chunk`.
+struct AssignScratch {
+    char *xs, *cs;
+    float *xback, *cback, *norm;
+    uint32_t *second, *listed, *words; // words: [0] rows in listed[], [1] largest squared centroid norm
+    void lay(Carver &c, int64_t n, int64_t chunk, int nlist_pad, int rb32)
+    {
+        xs = c.take<char>((size_t)chunk * rb32);
+        cs = c.take<char>((size_t)nlist_pad * rb32);
+        xback = c.take<float>((size_t)chunk);
+        cback = c.take<float>((size_t)nlist_pad);
+        norm = c.take<float>((size_t)n);
+        second = c.take<uint32_t>((size_t)n);
+        listed = c.take<uint32_t>((size_t)n);
+        words = c.take<uint32_t>(2);
+    }
+};
+
+// The centroid table that vectors are assigned with: padded [nlist_pad][ld], in memory and behind a device descriptor.
+struct Table {
+    const DevIndex *dev;
+    const float *cent, *cnorm;
+    int nlist, nlist_pad, d, ld, metric;
+};
+
+// Top-1 assignment of n vectors (Section 3.1: the list of the best centroid): best[i] = (score key << 32 | list), by
+// the scores of the fp32 GEMM.  The split-operand GEMM finds them, two launches per chunk and no score matrix, and the
+// fp32 kernel goes over the few rows whose best two are near; a last chunk that cannot fill tiles (coarse_tiles) takes
+// the centroid kernel, as an insert of its size does.
+int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const AssignScratch &as, int64_t chunk,
+                unsigned long long *best, hipStream_t s)
+{
+    const int64_t tail = n % kFillChunk;
+    const int64_t by_gemm = tail > 0 && !coarse_tiles((uint32_t)tail, t.nlist_pad) ? n - tail : n;
+    MultiArgs mm;
+    std::memset(&mm, 0, sizeof(mm));
+    PK_HIP(launch_fill_u32(as.words, 0u, 2, s));
+    for (int64_t i0 = 0; i0 < by_gemm; i0 += chunk) {
+        const int64_t m = std::min<int64_t>(chunk, by_gemm - i0);
+        SplitRowsArgs sr{};
+        sr.x = x + (size_t)i0 * t.d;
+        sr.c = t.cent;
+        sr.m = (uint32_t)m;
+        sr.n_c = i0 == 0 ? (uint32_t)t.nlist_pad : 0u;
+        sr.d = t.d;
+        sr.ld = t.ld;
+        sr.xs = as.xs;
+        sr.cs = as.cs;
+        sr.x_back = as.xback;
+        sr.c_back = as.cback;
+        sr.qnorm = as.norm + i0;
+        sr.best = best + i0;
+        sr.second = as.second + i0;
+        sr.cmax = as.words + 1;
+        PK_HIP(launch_split_rows(sr, mm, s));
+        SplitGemmArgs g{};
+        g.q = as.xs;
+        g.c = as.cs;
+        g.q_back = as.xback;
+        g.c_back = as.cback;
+        g.qnorm = as.norm + i0;
+        g.cnorm = t.cnorm;
+        g.best = best + i0;
+        g.m = (int)m;
+        g.n = t.nlist;
+        g.n_pad = t.nlist_pad;
+        g.ld = t.ld;
+        g.metric = t.metric;
+        g.second = as.second + i0;
+        g.cmax = as.words + 1;
+        PK_HIP(launch_gemm_split(g, num_cu, s));
+    }
+    if (by_gemm > 0) {
+        GemmArgs g{};
+        g.q = x;
+        g.c = t.cent;
+        g.qnorm = as.norm;
+        g.cnorm = t.cnorm;
+        g.n = t.nlist;
+        g.n_pad = t.nlist_pad;
+        g.n_store = t.nlist_pad;
+        g.ld = t.ld;
+        g.metric = t.metric;
+        g.list = as.listed;
+        g.nlisted = as.words;
+        g.best = best;
+        g.d = t.d;
+        g.m = (int)by_gemm;
+        PK_HIP(launch_gemm_near_ties(g, as.second, as.words + 1, as.listed, as.words, num_cu, s));
+    }
+    if (by_gemm < n) {
+        const float *xt = x + (size_t)by_gemm * t.d;
+        CentroidArgs ca{};
+        ca.row_bytes = t.ld * 4;
+        ca.metric = t.metric;
+        ca.qs = reinterpret_cast<const char *>(xt);
+        if (t.metric != PK_METRIC_IP || t.d != t.ld) { // prepared rows and norms
+            PK_HIP(launch_prep_queries(xt, tail, t.d, PK_F32, ca.row_bytes, as.xs, as.xback, s));
+            ca.qs = as.xs;
+            ca.qnorm = as.xback;
+        }
+        ca.best = best + by_gemm;
+        PK_HIP(launch_fill_u32(reinterpret_cast<uint32_t *>(ca.best), 0xffffffffu, (size_t)tail * 2, s));
+        mm.n = 1;
+        mm.ix[0] = t.dev;
+        mm.qlo[1] = (uint32_t)tail;
+        ca.chunk = (int)std::min<int64_t>(64, (tail + 15) / 16 * 16);
+        while (ca.chunk > 16 && (tail + ca.chunk - 1) / ca.chunk * (t.nlist_pad / 16) < num_cu) ca.chunk -= 16;
+        ca.blk[1] = (uint32_t)((tail + ca.chunk - 1) / ca.chunk * (t.nlist_pad / 16));
+        PK_HIP(launch_centroid_scores(ca, mm, s));
+    }
+    return PK_OK;
+}
+
 // One launch sequence: top-1 coarse search (unless the lists are given), slot reservation and
 // append for the vectors of hs[0..nh), rows [qlo[a], qlo[a+1]) of the batch going to handle a
 // (at most 1024 each).  The workspace is that of hs[0].
@@ -1217,6 +1400,7 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
     if (n > 0x7fffffff00ll) return PK_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Dims x = dims_of(cfg);
+    if (n > 0x7fffffffll) return PK_ERR_NOMEM; // rows are 256 bytes or more: no arena on this device holds so many
     if (arena_bytes < x.header + 1024 + x.page_stride) return PK_ERR_NOMEM;
 
     pk_index *ix = new (std::nothrow) pk_index();
@@ -1287,39 +1471,39 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
 
     std::vector<uint32_t> cnt((size_t)cfg->nlist, 0);
     if (n > 0) {
+        // one block of scratch: every vector's best (score, list), the assignment, counters, the operands of one chunk
+        const int64_t chunk = std::min<int64_t>(kAssignChunk, n);
+        char *scr = nullptr;
+        Carver c{nullptr, 0};
+        unsigned long long *d_best = nullptr;
         int32_t *d_assign = nullptr;
         uint32_t *d_cnt = nullptr;
-        if (hipMalloc(reinterpret_cast<void **>(&d_assign), (size_t)n * sizeof(int32_t)) != hipSuccess)
-            return fail(PK_ERR_NOMEM);
-        if (hipMalloc(reinterpret_cast<void **>(&d_cnt), (size_t)cfg->nlist * 2 * sizeof(uint32_t)) != hipSuccess) {
-            (void)hipFree(d_assign);
+        AssignScratch as{};
+        auto lay = [&](char *at) {
+            c = Carver{at, 0};
+            d_best = c.take<unsigned long long>((size_t)n);
+            d_assign = c.take<int32_t>((size_t)n);
+            d_cnt = c.take<uint32_t>((size_t)cfg->nlist * 2);
+            as.lay(c, n, chunk, x.nlist_pad, x.rb32);
+        };
+        lay(nullptr);
+        if (hipMalloc(reinterpret_cast<void **>(&scr), c.off + 256) != hipSuccess) {
+            (void)hipGetLastError();
             return fail(PK_ERR_NOMEM);
         }
+        lay(scr);
         auto fail2 = [&](int code) {
             (void)hipStreamSynchronize(s);
-            (void)hipFree(d_assign);
-            (void)hipFree(d_cnt);
+            (void)hipFree(scr);
             destroy(ix);
             return code;
         };
         // assignment: a top-1 coarse search per chunk (Section 3.1 rule = rank-1 probe)
-        pk_index *hs[1] = {ix};
-        for (int64_t i0 = 0; i0 < n && rc == PK_OK; i0 += kBuildChunk) {
-            const int64_t mc = std::min<int64_t>(kBuildChunk, n - i0);
-            const uint32_t qlo[2] = {0, (uint32_t)mc};
-            Plan p;
-            rc = make_plan(p, hs, 1, qlo, mc, 1, 1, true, false);
-            if (rc == PK_OK) rc = ensure_ws(ix, p.bytes, s);
-            if (rc != PK_OK) break;
-            carve(p, ix->ws, ix);
-            MultiArgs mm;
-            fill_multi(mm, hs, 1, qlo);
-            rc = run_coarse(p, mm, hs, vectors + (size_t)i0 * cfg->d, s);
-            if (rc == PK_OK && launch_copy_i32(p.probes, d_assign + i0, mc, s) != hipSuccess) rc = PK_ERR_HIP;
-        }
+        const Table table{ix->dev, cent, cnorm, cfg->nlist, x.nlist_pad, cfg->d, x.dpad32, cfg->metric};
+        rc = assign_rows(vectors, n, table, ix->num_cu, as, chunk, d_best, s);
         if (rc != PK_OK) return fail2(rc);
         if (launch_fill_u32(d_cnt, 0u, (size_t)cfg->nlist * 2, s) != hipSuccess ||
-            launch_hist(d_assign, n, d_cnt, s) != hipSuccess ||
+            launch_lists_of_best(d_best, n, cfg->nlist, d_assign, d_cnt, s) != hipSuccess ||
             hipMemcpyAsync(cnt.data(), d_cnt, (size_t)cfg->nlist * sizeof(uint32_t), hipMemcpyDeviceToHost, s) !=
                 hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
@@ -1340,16 +1524,10 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
             launch_scatter_build(ix->dev, vectors, ids, d_assign, n, 0, d_cnt + cfg->nlist, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             return fail2(PK_ERR_HIP);
-        (void)hipFree(d_assign);
-        (void)hipFree(d_cnt);
+        (void)hipFree(scr);
         ix->pages_known = used32;
     }
     if (hipStreamSynchronize(s) != hipSuccess) return fail(PK_ERR_HIP);
-    // the build's own scratch (score matrices of 16 384-vector chunks) is not what searches need
-    if (ix->ws) (void)hipFree(ix->ws);
-    ix->ws = nullptr;
-    ix->ws_bytes = 0;
-    ix->ws_grows = 0;
     ix->n_total = n;
     ix->next_id = n;
     ix->n_inserted = 0;
@@ -1436,57 +1614,64 @@ int pk_kmeans(const float *vectors, int64_t n, int32_t d, int32_t nlist, int32_t
     if (d < 1) return PK_ERR_INVALID_ARG;
     if (d > PK_MAX_DIM || n > 0x7fffffffll) return PK_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // the assignment step is a top-1 coarse search under L2: an index without vectors carries the centroid table
-    pk_config cfg{d, nlist, PK_METRIC_L2, PK_F32, 32, 1};
-    const size_t abytes = pk_arena_bytes(&cfg, 0, 0);
+    // the assignment step is a top-1 coarse search under L2, over the same padded centroid table as an index's
+    const pk_config cfg{d, nlist, PK_METRIC_L2, PK_F32, 32, 1};
+    const Dims x = dims_of(&cfg);
+    int dev = 0, cus = 0;
+    PK_HIP(hipGetDevice(&dev));
+    PK_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int64_t chunk = std::min<int64_t>(kAssignChunk, n);
+    KmeansArgs ka{};
+    AssignScratch as{};
+    unsigned long long *best = nullptr;
+    float *cent = nullptr, *cnorm = nullptr;
+    DevIndex *tdev = nullptr; // what the centroid kernel reads of an index: the table
+    int32_t *assign = nullptr;
+    double *inertia = nullptr;
+    Carver c{nullptr, 0};
+    auto lay = [&](char *at) {
+        c = Carver{at, 0};
+        cent = c.take<float>((size_t)x.nlist_pad * x.dpad32);
+        cnorm = c.take<float>((size_t)x.nlist_pad);
+        as.lay(c, n, chunk, x.nlist_pad, x.rb32);
+        tdev = c.take<DevIndex>(1);
+        best = c.take<unsigned long long>((size_t)n);
+        assign = c.take<int32_t>((size_t)n);
+        inertia = c.take<double>((size_t)iters);
+        ka.cnt = c.take<uint32_t>((size_t)nlist);
+        ka.start = c.take<uint32_t>((size_t)nlist);
+        ka.fill = c.take<uint32_t>((size_t)nlist);
+        ka.members = c.take<uint32_t>((size_t)n);
+        ka.sums = c.take<double>((size_t)nlist * d);
+        ka.sq = c.take<double>((size_t)nlist);
+    };
+    lay(nullptr);
     char *kbuf = nullptr;
-    const size_t nl4 = round_up((size_t)nlist * 4, 256), n4 = round_up((size_t)n * 4, 256);
-    const size_t sums8 = round_up((size_t)nlist * d * 8, 256), sq8 = round_up((size_t)nlist * 8, 256);
-    const size_t sbytes = round_up(abytes, 256) + 3 * nl4 + 2 * n4 + round_up((size_t)iters * 8, 256) + sums8 + sq8;
-    if (hipMalloc(reinterpret_cast<void **>(&kbuf), sbytes) != hipSuccess) {
+    if (hipMalloc(reinterpret_cast<void **>(&kbuf), c.off + 256) != hipSuccess) {
         (void)hipGetLastError();
         return PK_ERR_NOMEM;
     }
-    pk_index *ix = nullptr;
-    int rc = pk_index_build(&cfg, centroids, nullptr, nullptr, 0, kbuf, abytes, stream, &ix);
-    if (rc != PK_OK) {
-        (void)hipFree(kbuf);
-        return rc;
-    }
-    KmeansArgs ka{};
-    char *p = kbuf + round_up(abytes, 256);
-    ka.cnt = reinterpret_cast<uint32_t *>(p);
-    ka.start = reinterpret_cast<uint32_t *>(p + nl4);
-    ka.fill = reinterpret_cast<uint32_t *>(p + 2 * nl4);
-    ka.members = reinterpret_cast<uint32_t *>(p + 3 * nl4);
-    int32_t *assign = reinterpret_cast<int32_t *>(p + 3 * nl4 + n4);
-    double *inertia = reinterpret_cast<double *>(p + 3 * nl4 + 2 * n4);
-    ka.sums = reinterpret_cast<double *>(p + 3 * nl4 + 2 * n4 + round_up((size_t)iters * 8, 256));
-    ka.sq = reinterpret_cast<double *>(p + 3 * nl4 + 2 * n4 + round_up((size_t)iters * 8, 256) + sums8);
+    lay(kbuf);
     ka.x = vectors;
     ka.assign = assign;
     ka.n = n;
     ka.d = d;
     ka.nlist = nlist;
     ka.centroids = centroids;
-    pk_index *hs[1] = {ix};
+    DevIndex D;
+    std::memset(&D, 0, sizeof(D));
+    D.cent = cent;
+    D.cnorm = cnorm;
+    D.nlist = nlist;
+    D.nlist_pad = x.nlist_pad;
+    const Table table{tdev, cent, cnorm, nlist, x.nlist_pad, d, x.dpad32, PK_METRIC_L2};
     auto run = [&]() -> int {
+        PK_HIP(hipMemcpyAsync(tdev, &D, sizeof(D), hipMemcpyHostToDevice, s));
         for (int it = 0; it < iters; ++it) {
-            if (it > 0)
-                PK_HIP(launch_store_centroids(centroids, nlist, d, ix->dpad32, ix->nlist_pad, PK_METRIC_L2,
-                                              const_cast<float *>(ix->host.cent), const_cast<float *>(ix->host.cnorm), s));
-            for (int64_t i0 = 0; i0 < n; i0 += kBuildChunk) {
-                const int64_t mc = std::min<int64_t>(kBuildChunk, n - i0);
-                const uint32_t qlo[2] = {0, (uint32_t)mc};
-                Plan pl;
-                PK_TRY(make_plan(pl, hs, 1, qlo, mc, 1, 1, true, false));
-                PK_TRY(ensure_ws(ix, pl.bytes, s));
-                carve(pl, ix->ws, ix);
-                MultiArgs mm;
-                fill_multi(mm, hs, 1, qlo);
-                PK_TRY(run_coarse(pl, mm, hs, vectors + (size_t)i0 * d, s));
-                PK_HIP(launch_copy_i32(pl.probes, assign + i0, mc, s));
-            }
+            PK_HIP(launch_store_centroids(centroids, nlist, d, x.dpad32, x.nlist_pad, PK_METRIC_L2, cent, cnorm, s));
+            PK_TRY(assign_rows(vectors, n, table, cus > 0 ? cus : 256, as, chunk, best, s));
+            PK_HIP(launch_fill_u32(ka.cnt, 0u, (size_t)nlist, s));
+            PK_HIP(launch_lists_of_best(best, n, nlist, assign, ka.cnt, s));
             ka.inertia = inertia + it;
             PK_HIP(launch_kmeans_update(ka, s));
         }
@@ -1496,9 +1681,8 @@ int pk_kmeans(const float *vectors, int64_t n, int32_t d, int32_t nlist, int32_t
         PK_HIP(hipStreamSynchronize(s));
         return PK_OK;
     };
-    rc = run();
+    const int rc = run();
     if (rc != PK_OK) (void)hipStreamSynchronize(s);
-    destroy(ix);
     (void)hipFree(kbuf);
     return rc;
 }
@@ -1844,6 +2028,11 @@ int pk_workspace_reserve(pk_index *const *handles, int32_t n_handles, int64_t nq
     Plan p;
     PK_TRY(make_plan(p, handles, n_handles, qlo.data(), nq_max, k_max, np, true, true, inserts_ahead, true));
     size_t need = p.bytes;
+    // a coarse step alone (pk_coarse, inserts): its plan holds the centroid table's split copy, but none of the fine step
+    Plan pc;
+    const uint32_t all[2] = {0, (uint32_t)nq_max};
+    PK_TRY(make_plan(pc, handles, 1, all, nq_max, 1, np, true, false));
+    need = std::max(need, pc.bytes);
     need += round_up((size_t)nq_max * 4, 256) + 256; // slot array of an insert batch
     return ensure_ws(handles[0], need, static_cast<hipStream_t>(stream));
 }

@@ -1,6 +1,9 @@
-// Coarse scoring for large query batches (and for the build, where every base vector is a
+// Coarse scoring for large query batches (and for build and k-means, where every vector is a
 // "query"): S[m][n] = <Q_m, C_n> (inner product) or |C_n|^2 - 2 <Q_m, C_n> + |Q_m|^2
 // (squared L2), Section 2.2's ranking of clusters by centroid distance, for all m, n.
+//
+// gemm_split_kernel below does this for one handle; gemm_scores_kernel takes the segments of
+// calls over several handles and the searches whose workspace has no room for split operands.
 //
 // This is a dense contraction, so it runs on the matrix cores with fp32 inputs and fp32
 // accumulation (v_mfma_f32_32x32x2_f32): no down-conversion of queries or centroids, so
@@ -10,17 +13,23 @@
 // the scan layout, so K needs no tail handling.  As in the scan kernel the contraction
 // index is permuted identically on both operands so that a lane's four consecutive floats
 // (one ds_read_b128) feed four MFMAs.
+#include <algorithm>
+
 #include "pk_internal.h"
 
 namespace pk {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 
 constexpr int kGemmTile = 128;
 constexpr int kGemmBK = 32;               // floats per K step
 constexpr int kGemmLdsStride = kGemmBK + 4; // floats; +4 keeps the b128 reads conflict free
 
+// LISTED: the rows are those of a list on the device (a.list, *a.nlisted of them), dense rows of a.d floats, and every
+// row keeps its best (value key, column) by atomicMin instead of writing scores; the grid walks the tiles there are.
+template <bool LISTED>
 __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 {
     __shared__ __align__(16) float sA[2][kGemmTile * kGemmLdsStride];
@@ -28,9 +37,13 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;        // wave's 64 x 64 quadrant
     const int l32 = lane & 31, kg = lane >> 5;      // MFMA row / column and k group
-    const int m0 = blockIdx.y * kGemmTile, n0 = blockIdx.x * kGemmTile;
     const int ld = a.ld;                            // floats per row, multiple of 64
     const int ksteps = ld / kGemmBK;
+    const int rows = LISTED ? (int)*a.nlisted : a.m;
+    [[maybe_unused]] const bool vec = LISTED && (a.d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
+    const uint32_t tn = (uint32_t)(a.n_pad + kGemmTile - 1) / kGemmTile, tm = (uint32_t)(rows + kGemmTile - 1) / kGemmTile;
+    for (uint32_t t = LISTED ? blockIdx.x : blockIdx.y * tn + blockIdx.x; t < tm * tn; t += LISTED ? gridDim.x : tm * tn) {
+    const int m0 = (int)(t / tn) * kGemmTile, n0 = (int)(t % tn) * kGemmTile;
 
     // global -> register staging: each thread moves 4 x 16 B of A and of B per K step
     // row = (tid >> 3) + 32 * i, 16-byte column = tid & 7
@@ -39,9 +52,10 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         int ra = m0 + srow + 32 * i, rb = n0 + srow + 32 * i;
-        ra = ra < a.m ? ra : a.m - 1; // clamp: rows past the end are computed and dropped
+        ra = ra < rows ? ra : rows - 1; // clamp: rows past the end are computed and dropped
         rb = rb < a.n_pad ? rb : a.n_pad - 1;
-        ga[i] = a.q + (size_t)ra * ld + scol;
+        if constexpr (LISTED) ga[i] = a.q + (size_t)a.list[ra] * a.d + scol;
+        else ga[i] = a.q + (size_t)ra * ld + scol;
         gb[i] = a.c + (size_t)rb * ld + scol;
     }
     f32x4 ra4[4], rb4[4];
@@ -56,7 +70,16 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #define PK_GLOAD(ks)                                                                     \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                        \
     {                                                                                    \
-        ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK);       \
+        if constexpr (LISTED) { /* the caller's rows: no padding, any alignment */       \
+            ra4[i] = f32x4{0.f, 0.f, 0.f, 0.f};                                          \
+            if (vec) {                                                                   \
+                if ((ks) * kGemmBK + scol < a.d)                                         \
+                    ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK); \
+            } else {                                                                     \
+                _Pragma("unroll") for (int j = 0; j < 4; ++j)                            \
+                    if ((ks) * kGemmBK + scol + j < a.d) ra4[i][j] = ga[i][(size_t)(ks) * kGemmBK + j]; \
+            }                                                                            \
+        } else ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK); \
         rb4[i] = *reinterpret_cast<const f32x4 *>(gb[i] + (size_t)(ks) * kGemmBK);       \
     }
 #define PK_LSTORE(buf)                                                                                   \
@@ -110,14 +133,23 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int m = m0 + wm * 64 + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
-                if (m < a.m) {
+                if (m < rows) {
+                    const size_t row = LISTED ? (size_t)a.list[m] : (size_t)m;
                     float v = acc[i][j][r];
-                    if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[m], 0.f);
-                    if (!live) v = a.metric == PK_METRIC_IP ? -INFINITY : INFINITY;
-                    a.out[(size_t)m * a.stride + n] = v;
+                    if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[row], 0.f);
+                    if constexpr (LISTED) {
+                        if (!live) continue;
+                        const unsigned long long key = ((unsigned long long)order_bits(v, a.metric) << 32) | (uint32_t)n;
+                        if (key < a.best[row]) atomicMin(a.best + row, key); // (a stale look costs an atomic, never a result)
+                    } else {
+                        if (!live) v = a.metric == PK_METRIC_IP ? -INFINITY : INFINITY;
+                        a.out[row * a.stride + n] = v;
+                    }
                 }
             }
         }
+    }
+    __syncthreads(); // the next tile's first stores into LDS
     }
 }
 
@@ -126,7 +158,443 @@ hipError_t launch_gemm_scores(const GemmArgs &a, hipStream_t s)
     if (a.m <= 0) return hipSuccess;
     if (a.ld % 64 != 0) return hipErrorInvalidValue;
     dim3 grid((a.n_pad + kGemmTile - 1) / kGemmTile, (a.m + kGemmTile - 1) / kGemmTile);
-    hipLaunchKernelGGL(gemm_scores_kernel, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(gemm_scores_kernel<false>, grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- the same products on the 16-bit matrix cores
+
+// An fp32 value as two halfs: x * 2^s = hi + lo + e with hi = half(x * 2^s), lo = half(x * 2^s - hi) and |e| at most
+// 2^-23 of the value (2^-39 of the row's largest for values that are tiny beside it); s makes the row's largest value
+// 2^14 .. 2^15, so nothing overflows.  A product is then hi hi + hi lo + lo hi (lo lo is below 2^-22 of it), three
+// products of 11-bit numbers that are exact in fp32, at a sixteenth of the fp32 product's price each.
+// Rows in memory: blocks of 32 elements, 64 bytes of hi then 64 bytes of lo; as many bytes as the fp32 row.
+
+// Sum of a wave's row in the order in which prep_row (pk_worklist.hip) adds its squares: part[j] is the sum of the
+// lane's elements 4 * lane + j, + 256, ...: what thread 4 * lane + j of its 256 threads holds.  A query's norm is
+// the same bits whichever kernel prepared it.
+__device__ __forceinline__ float row_sum(float (&part)[4])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) part[j] += __shfl_xor(part[j], off);
+    const float w = (part[0] + part[2]) + (part[1] + part[3]);
+    return __shfl(w, 0) + __shfl(w, 16) + __shfl(w, 32) + __shfl(w, 48);
+}
+
+// A wave per row, rows [0, m) from `x` (dense, d floats) and then n_c rows of the (padded) centroid table.
+// Bound by memory: 300 000 rows of 4 KB read and written at 4.3 TB/s.
+__global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiArgs mm)
+{
+    const int lane = threadIdx.x & 63;
+    const uint32_t row = blockIdx.x * 4u + (threadIdx.x >> 6);
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.meta.nclear; i += gridDim.x * blockDim.x) a.meta.clear[i] = 0u;
+    if (row >= a.m + a.n_c) return;
+    const bool cent = row >= a.m;
+    const uint32_t r = cent ? row - a.m : row;
+    const int ld = a.ld, d = cent ? ld : a.d;
+    const float *src = cent ? a.c + (size_t)r * ld : a.x + (size_t)r * d;
+    const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0; // (wave-uniform)
+    constexpr int kT = (PK_MAX_DIM + 255) / 256;
+    f32x4 v[kT];
+    float big = 0.f, sq[4] = {0.f, 0.f, 0.f, 0.f}, sq16[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < kT; ++t) {
+        const int i = lane * 4 + 256 * t;
+        v[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (vec) {
+            if (i < d) v[t] = *reinterpret_cast<const f32x4 *>(src + i);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (i + j < d) v[t][j] = src[i + j];
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            big = fmaxf(big, fabsf(v[t][j]));
+            sq[j] += v[t][j] * v[t][j];
+        }
+    for (int off = 32; off > 0; off >>= 1) big = fmaxf(big, __shfl_xor(big, off));
+    const float norm = row_sum(sq);
+    // 2^e <= big < 2^(e + 1); the scale stays a normal number (a row of zeros, or one below 2^-112, is scaled by 2^126)
+    int s = 14 - ((int)(__float_as_uint(big) >> 23) - 127);
+    s = s < -126 ? -126 : (s > 126 ? 126 : s);
+    const float scale = __uint_as_float((uint32_t)(s + 127) << 23);
+    char *dst = (cent ? a.cs : a.xs) + (size_t)r * ld * 4;
+#pragma unroll
+    for (int t = 0; t < kT; ++t) {
+        const int i = lane * 4 + 256 * t;
+        if (i >= ld) continue;
+        half4 hi, lo;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float y = v[t][j] * scale; // exact
+            hi[j] = (_Float16)y;
+            lo[j] = (_Float16)(y - (float)hi[j]); // the difference is exact
+        }
+        char *p = dst + (size_t)(i >> 5) * 128 + (i & 31) * 2;
+        *reinterpret_cast<half4 *>(p) = hi;
+        *reinterpret_cast<half4 *>(p + 64) = lo;
+        if (!cent && a.copy) *reinterpret_cast<f32x4 *>(a.copy + (size_t)r * ld + i) = v[t];
+    }
+    if (!cent && a.half_rows) { // the row as a half-precision index stores it: rounded to nearest even, norm of the rounded values
+        char *h = a.half_rows + (size_t)r * a.half_bytes;
+#pragma unroll
+        for (int t = 0; t < kT; ++t) {
+            const int i = lane * 4 + 256 * t;
+            if (i * 2 >= a.half_bytes) continue;
+            half4 w;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                w[j] = (_Float16)v[t][j];
+                const float f = (float)w[j];
+                sq16[j] += f * f;
+            }
+            *reinterpret_cast<half4 *>(h + (size_t)i * 2) = w;
+        }
+    }
+    const float norm16 = row_sum(sq16);
+    if (lane != 0) return;
+    const float back = __uint_as_float((uint32_t)(127 - s) << 23);
+    if (cent) {
+        a.c_back[r] = back;
+        if (a.cmax) atomicMax(a.cmax, __float_as_uint(norm)); // (squares: their bits are in the order of the values)
+        return;
+    }
+    a.x_back[r] = back;
+    if (a.second) a.second[r] = 0xffffffffu;
+    if (a.qnorm) a.qnorm[r] = norm;
+    if (a.half_rows) a.half_norm[r] = norm16;
+    if (a.best) a.best[r] = ~0ull;
+    if (a.meta.cand_off) {
+        a.meta.cand_off[r] = r * a.meta.stride;
+        a.meta.cand_cnt[r] = (uint32_t)mm.ix[0]->nlist;
+        a.meta.qagent[r] = 0;
+    }
+}
+
+hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStream_t s)
+{
+    if (a.m + a.n_c == 0) return hipSuccess;
+    if (a.ld % 64 != 0 || a.ld > PK_MAX_DIM || a.d > a.ld) return hipErrorInvalidValue;
+    if (a.half_rows && (a.half_bytes % 256 != 0 || a.half_bytes > PK_MAX_DIM * 2 || a.half_bytes < a.d * 2)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(split_rows_kernel, dim3((a.m + a.n_c + 3) / 4), dim3(256), 0, s, a, mm);
+    return hipGetLastError();
+}
+
+// Smallest of the 32 lanes of each half wave, in the half's last lane (31 and 63): data-parallel moves only, where a
+// butterfly over shuffles would go through LDS (the epilogue took a third of the kernel that way).
+__device__ __forceinline__ uint32_t min_of_half(uint32_t x)
+{
+#define PK_DPP_MIN(ctrl, rows) x = min(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, rows, 0xf, false));
+    PK_DPP_MIN(0x111, 0xf) // row_shr 1, 2, 4, 8: lane 15 of every 16 has their smallest
+    PK_DPP_MIN(0x112, 0xf)
+    PK_DPP_MIN(0x114, 0xf)
+    PK_DPP_MIN(0x118, 0xf)
+    PK_DPP_MIN(0x142, 0xa) // row_bcast 15: into the second and fourth 16 lanes
+#undef PK_DPP_MIN
+    return x;
+}
+
+// Two values of a row closer than this are told apart by the fp32 kernel.  The fp32 sum of ld products, two at a time,
+// is off by about 2^-25 sqrt(ld / 2) of |x| |c| in one standard deviation (measured: 1e-6 |x|^2 between two L2 values
+// at 768 elements), the split's by a third of it; 2^-21 sqrt(ld) is twenty of them.
+__device__ __forceinline__ float near_margin(int ld, int metric, float qn, float cmax)
+{
+    return 4.76837158e-7f * sqrtf((float)ld) * (metric == PK_METRIC_L2 ? qn + cmax : sqrtf(qn) * sqrtf(cmax));
+}
+
+// BM x BN output tile per workgroup of WM x WN waves; K in steps of 32 elements (128 bytes of a split row) through
+// double-buffered LDS, fetched two steps ahead through two register stages (a step is short: 12 MFMAs of 32 cycles per
+// 32 x 32 x 2 blocks, and the operands come from L2).  BEST: every row keeps its best (value key, column) by atomicMin
+// instead of writing scores: top-1 assignment, which then needs no score matrix (268 MB per 16384 rows x 4096) and no
+// selection.  Where a second column is near a row's best (in one tile, or met in memory by the tile's atomic: of two tiles
+// with near best values the later one sees the earlier) its value is kept too; the fp32 kernel then decides for the
+// rows that end up with a near second, so that every assignment is the one that kernel makes.
+// Bound by feeding the matrix cores (LDS reads and stores take three quarters of the MFMA time beside it):
+// 32768 x 4096 x 768 (BEST) in 679 us = 303 TFLOP/s of fp32 products (910 of fp16), where the fp32 kernel's chunk of
+// 16384 took 962 us = 107 and its selection 194; 1024 x 4096 x 768 (search) 69 -> 39 us.  By its own values alone,
+// 28 rows came out on the wrong side of a near tie, against 64 bits, over seven sets of 0.5 - 1 M rows
+// (64 <= d <= 1536), and 46 by the fp32 kernel's.
+template <int BM, int BN, int WM, int WN, bool BEST>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(SplitGemmArgs a)
+{
+    constexpr int TH = WM * WN * 64;
+    constexpr int MI = BM / WM / 32, NI = BN / WN / 32; // 32 x 32 blocks per wave
+    constexpr int LD = 144;                             // LDS bytes per row: 128 + 16, conflict-free b128 reads
+    constexpr int LOADS = (BM + BN) * 8 / TH;           // 16-byte pieces per thread and step
+    static_assert((BM * 8) % TH == 0 && (BN * 8) % TH == 0, "a thread's piece is of A or of B for the whole workgroup");
+    constexpr int ALOADS = BM * 8 / TH;
+    extern __shared__ __align__(16) char smem[]; // [2][BM + BN][LD]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int l32 = lane & 31, kg = lane >> 5;
+    // XCD-aware order: workgroups go to the 8 XCDs in turn; each XCD takes one contiguous part of the tiles, and walks
+    // it in groups of 8 tile rows, so that the tiles in flight on an XCD share their rows and columns in its L2
+    const uint32_t tn = (uint32_t)(a.n_pad + BN - 1) / BN, tm = (uint32_t)(a.m + BM - 1) / BM, total = tn * tm;
+    const uint32_t xcd = blockIdx.x & 7u, per = total / 8u, extra = total % 8u;
+    const uint32_t t = xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
+    constexpr uint32_t GM = 8;
+    const uint32_t grp = t / (GM * tn), in = t - grp * GM * tn;
+    const uint32_t gm = tm - grp * GM < GM ? tm - grp * GM : GM;
+    const int m0 = (int)(grp * GM + in % gm) * BM, n0 = (int)(in / gm) * BN;
+
+    const int steps = a.ld / 32;
+    const size_t row_bytes = (size_t)a.ld * 4;
+    const char *src[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int piece = i < ALOADS ? tid + i * TH : tid + (i - ALOADS) * TH;
+        int r = (i < ALOADS ? m0 : n0) + (piece >> 3);
+        const int last = i < ALOADS ? a.m - 1 : a.n_pad - 1;
+        r = r < last ? r : last; // rows past the end are computed and dropped
+        src[i] = (i < ALOADS ? a.q : a.c) + (size_t)r * row_bytes + (piece & 7) * 16;
+    }
+    char *const put = smem + (size_t)(tid >> 3) * LD + (tid & 7) * 16;
+    constexpr int ROWS_PER = TH / 8; // LDS rows between a thread's pieces
+    u32x4 s0[LOADS], s1[LOADS];
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    // (past the last step the last one is fetched again: every load is unconditional)
+#define PK_FETCH(st, ks)                                                                                   \
+    {                                                                                                      \
+        const size_t at = (size_t)((ks) < steps ? (ks) : steps - 1) * 128;                                 \
+        _Pragma("unroll") for (int i = 0; i < LOADS; ++i) st[i] = *reinterpret_cast<gvec4>(in_global(src[i]) + at); \
+    }
+#define PK_PUT(st, buf)                                                                                    \
+    _Pragma("unroll") for (int i = 0; i < LOADS; ++i)                                                      \
+        *reinterpret_cast<u32x4 *>(put + (size_t)(buf) * (BM + BN) * LD + (size_t)i * ROWS_PER * LD) = st[i];
+#define PK_STEP(buf)                                                                                       \
+    {                                                                                                      \
+        const char *pa = smem + (size_t)(buf) * (BM + BN) * LD + (size_t)(wm * (BM / WM) + l32) * LD + kg * 16; \
+        const char *pb = smem + (size_t)(buf) * (BM + BN) * LD + (size_t)(BM + wn * (BN / WN) + l32) * LD + kg * 16; \
+        _Pragma("unroll") for (int kc = 0; kc < 2; ++kc)                                                   \
+        {                                                                                                  \
+            half8 ah[MI], al[MI], bh[NI], bl[NI];                                                          \
+            _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                 \
+            {                                                                                              \
+                ah[i] = *reinterpret_cast<const half8 *>(pa + i * 32 * LD + kc * 32);                      \
+                al[i] = *reinterpret_cast<const half8 *>(pa + i * 32 * LD + kc * 32 + 64);                 \
+            }                                                                                              \
+            _Pragma("unroll") for (int j = 0; j < NI; ++j)                                                 \
+            {                                                                                              \
+                bh[j] = *reinterpret_cast<const half8 *>(pb + j * 32 * LD + kc * 32);                      \
+                bl[j] = *reinterpret_cast<const half8 *>(pb + j * 32 * LD + kc * 32 + 64);                 \
+            }                                                                                              \
+            _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j)  \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[i], bh[j], acc[i][j], 0, 0, 0);      \
+            _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j)  \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[i], bl[j], acc[i][j], 0, 0, 0);      \
+            _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j)  \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[i], bh[j], acc[i][j], 0, 0, 0);      \
+        }                                                                                                  \
+    }
+    [[maybe_unused]] float *const s_row = reinterpret_cast<float *>(smem + (size_t)2 * (BM + BN) * LD); // [2][BM]
+    PK_FETCH(s0, 0)
+    PK_FETCH(s1, 1)
+    PK_PUT(s0, 0)
+    PK_FETCH(s0, 2)
+    if constexpr (BEST) {
+        // per row: what turns a column's product into t (below), and how near a second value is near, in t's unit
+        if (tid < BM) {
+            const int m = m0 + tid < a.m ? m0 + tid : a.m - 1;
+            const float back = a.q_back[m], margin = near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax));
+            s_row[tid] = a.metric == PK_METRIC_L2 ? -2.f * back : -1.f;
+            s_row[BM + tid] = a.metric == PK_METRIC_L2 ? margin : margin / back;
+        }
+    }
+    __syncthreads();
+    for (int ks = 0; ks < steps; ks += 2) { // steps is even: rows are padded to 64 elements
+        PK_STEP(0)
+        PK_PUT(s1, 1) // (buffer 1 was last read before the barrier that ended the step before)
+        PK_FETCH(s1, ks + 3)
+        __syncthreads();
+        PK_STEP(1)
+        PK_PUT(s0, 0)
+        PK_FETCH(s0, ks + 4)
+        __syncthreads();
+    }
+#undef PK_FETCH
+#undef PK_PUT
+#undef PK_STEP
+
+    // lane holds column l32 of rows kg * 4 + 8 * (r / 4) + r % 4 of each 32 x 32 block
+    float cb[NI], cn[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int n = n0 + wn * (BN / WN) + j * 32 + l32;
+        cb[j] = n < a.n ? a.c_back[n] : 0.f;
+        cn[j] = a.metric == PK_METRIC_L2 && n < a.n ? a.cnorm[n] : 0.f;
+    }
+    if constexpr (!BEST) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int m = m0 + wm * (BM / WM) + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
+                if (m >= a.m) continue;
+                const float back = a.q_back[m], qn = a.metric == PK_METRIC_L2 ? a.qnorm[m] : 0.f;
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const int n = n0 + wn * (BN / WN) + j * 32 + l32;
+                    if (n >= a.n_pad) continue;
+                    float v = acc[i][j][r] * back * cb[j];
+                    if (a.metric == PK_METRIC_L2) v = fmaxf(cn[j] - 2.f * v + qn, 0.f);
+                    if (n >= a.n) v = a.metric == PK_METRIC_IP ? -INFINITY : INFINITY;
+                    a.out[(size_t)m * a.stride + n] = v;
+                }
+            }
+        }
+    } else {
+        // t: smaller is nearer (inner product: -dot in the row's scale; L2: |c|^2 - 2 dot, the row's own norm left out)
+        uint32_t top[MI], second[MI]; // lane r of a half wave: of its row r, the best value's key, the near second's (or all ones)
+        int col[MI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            top[i] = second[i] = 0xffffffffu;
+            col[i] = 0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int local = wm * (BM / WM) + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
+                const float factor = s_row[local], margin = s_row[BM + local];
+                float t[NI];
+                uint32_t key[NI], low = 0xffffffffu;
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    t[j] = fmaf(acc[i][j][r] * cb[j], factor, cn[j]);
+                    if (n0 + wn * (BN / WN) + j * 32 + l32 >= a.n) t[j] = INFINITY;
+                    key[j] = order_bits(t[j], PK_METRIC_L2);
+                    low = min(low, key[j]);
+                }
+                low = min_of_half(low);
+                const uint32_t b0 = __builtin_amdgcn_readlane(low, 31), b1 = __builtin_amdgcn_readlane(low, 63);
+                const uint32_t best = kg ? b1 : b0;
+                const float limit = value_of(best, PK_METRIC_L2) + margin;
+                int at0 = -1, at1 = -1; // column of each half's best inside the wave's part of the tile
+                uint32_t near0 = 0, near1 = 0;
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const unsigned long long eq = __ballot(key[j] == best), nr = __ballot(t[j] <= limit);
+                    if (at0 < 0 && (uint32_t)eq) at0 = j * 32 + __ffs((uint32_t)eq) - 1;
+                    if (at1 < 0 && (uint32_t)(eq >> 32)) at1 = j * 32 + __ffs((uint32_t)(eq >> 32)) - 1;
+                    near0 += (uint32_t)__popc((uint32_t)nr);
+                    near1 += (uint32_t)__popc((uint32_t)(nr >> 32));
+                }
+                uint32_t next = 0xffffffffu;
+                if (near0 > 1u || near1 > 1u) { // rare (wave-uniform): the best but one
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+                        if (j * 32 + l32 != (kg ? at1 : at0)) next = min(next, key[j]);
+                    next = min_of_half(next);
+                    const uint32_t x0 = __builtin_amdgcn_readlane(next, 31), x1 = __builtin_amdgcn_readlane(next, 63);
+                    next = kg ? x1 : x0;
+                }
+                if (l32 == r) {
+                    top[i] = best;
+                    col[i] = kg ? at1 : at0;
+                    second[i] = next;
+                }
+            }
+        }
+        // lanes 0 .. 15 of a half wave: row r = l32 of the block
+        const int rr = kg * 4 + 8 * (l32 >> 2) + (l32 & 3);
+        const bool has = l32 < 16 && n0 + wn * (BN / WN) < a.n; // (some column of the wave's part is a list)
+        uint32_t met[MI], mine[MI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int m = m0 + wm * (BM / WM) + i * 32 + rr;
+            met[i] = mine[i] = 0xffffffffu;
+            if (!has || m >= a.m) continue;
+            float v = value_of(top[i], PK_METRIC_L2);
+            if (a.metric == PK_METRIC_IP) v = -v * a.q_back[m];
+            mine[i] = order_bits(v, a.metric);
+            const unsigned long long k = ((unsigned long long)mine[i] << 32) | (uint32_t)(n0 + wn * (BN / WN) + col[i]);
+            met[i] = (uint32_t)(atomicMin(a.best + m, k) >> 32);
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int m = m0 + wm * (BM / WM) + i * 32 + rr;
+            if (!has || m >= a.m) continue;
+            uint32_t other = max(met[i], mine[i]);
+            if (second[i] != 0xffffffffu) {
+                float v = value_of(second[i], PK_METRIC_L2);
+                if (a.metric == PK_METRIC_IP) v = -v * a.q_back[m];
+                other = min(other, order_bits(v, a.metric));
+            }
+            // (none met: all ones, a NaN, which is near nothing)
+            if (fabsf(value_of(other, a.metric) - value_of(min(met[i], mine[i]), a.metric)) <=
+                near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax)))
+                atomicMin(a.second + m, other);
+        }
+    }
+}
+
+template <int BM, int BN, int WM, int WN, bool BEST>
+static hipError_t launch_split_one(const SplitGemmArgs &a, hipStream_t s)
+{
+    static LdsCleared cleared;
+    const uint32_t tiles = (uint32_t)((a.n_pad + BN - 1) / BN) * (uint32_t)((a.m + BM - 1) / BM);
+    return launch_with_lds(&gemm_split_kernel<BM, BN, WM, WN, BEST>, cleared, 2 * (BM + BN) * 144 + 2 * BM * 4, a, (int)tiles, WM * WN * 64, s);
+}
+
+hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
+{
+    if (a.m <= 0) return hipSuccess;
+    if (a.ld % 64 != 0 || a.n < 1 || a.n > a.n_pad || (a.best == nullptr) == (a.out == nullptr) ||
+        (a.best && !(a.second && a.cmax && a.qnorm))) return hipErrorInvalidValue;
+    auto tiles = [&](int b) { return (int64_t)((a.m + b - 1) / b) * ((a.n_pad + b - 1) / b); };
+    // the largest tile that still gives every CU one
+    if (tiles(256) >= num_cu)
+        return a.best ? launch_split_one<256, 256, 2, 4, true>(a, s) : launch_split_one<256, 256, 2, 4, false>(a, s);
+    if (tiles(128) >= num_cu)
+        return a.best ? launch_split_one<128, 128, 2, 2, true>(a, s) : launch_split_one<128, 128, 2, 2, false>(a, s);
+    return a.best ? launch_split_one<64, 64, 2, 2, true>(a, s) : launch_split_one<64, 64, 2, 2, false>(a, s);
+}
+
+// Rows whose second best value is near the best: into the list, their best[] back to "none yet".
+__global__ __launch_bounds__(256) void near_ties_kernel(GemmArgs a, const uint32_t *second, const uint32_t *cmax, uint32_t *list,
+                                                        uint32_t *nlisted)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t i0 = blockIdx.x * 256u; i0 < (uint32_t)a.m; i0 += gridDim.x * 256u) {
+        const uint32_t i = i0 + threadIdx.x;
+        bool near = false;
+        if (i < (uint32_t)a.m) {
+            const uint32_t s = second[i];
+            near = s != 0xffffffffu &&
+                   fabsf(value_of(s, a.metric) - value_of((uint32_t)(a.best[i] >> 32), a.metric)) <=
+                       near_margin(a.ld, a.metric, a.qnorm[i], __uint_as_float(*cmax));
+        }
+        const unsigned long long m = __ballot(near);
+        if (m == 0ull) continue;
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(nlisted, (uint32_t)__popcll(m));
+        at = __shfl(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (near) {
+            list[at] = i;
+            a.best[i] = ~0ull;
+        }
+    }
+}
+
+hipError_t launch_gemm_near_ties(const GemmArgs &a, const uint32_t *second, const uint32_t *cmax, uint32_t *list, uint32_t *nlisted,
+                                 int num_cu, hipStream_t s)
+{
+    if (a.m <= 0) return hipSuccess;
+    if (a.ld % 64 != 0 || a.d > a.ld || !a.best || a.list != list || a.nlisted != nlisted) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(near_ties_kernel, dim3((uint32_t)std::min((a.m + 255) / 256, 4 * num_cu)), dim3(256), 0, s, a, second, cmax,
+                       list, nlisted);
+    hipLaunchKernelGGL(gemm_scores_kernel<true>, dim3(2 * num_cu), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -35,17 +35,36 @@ hipError_t launch_store_centroids(const float *c, int nlist, int d, int dpad32, 
     return hipGetLastError();
 }
 
-__global__ void hist_kernel(const int32_t *assign, int64_t n, uint32_t *cnt)
+// One word per list serialises its atomics (262 144 rows over 162 lists: 187 us): a workgroup counts a run of rows in
+// LDS first and adds each list's count once.  More lists than LDS takes spread the atomics by themselves.
+__global__ __launch_bounds__(256) void lists_of_best_kernel(const unsigned long long *best, int64_t n, int nlist,
+                                                            int32_t *assign, uint32_t *cnt, int64_t run, bool lds)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        atomicAdd(&cnt[assign[i]], 1u);
+    extern __shared__ uint32_t s_cnt[];
+    if (lds) {
+        for (int l = threadIdx.x; l < nlist; l += 256) s_cnt[l] = 0u;
+        __syncthreads();
+    }
+    const int64_t i0 = (int64_t)blockIdx.x * run, i1 = i0 + run < n ? i0 + run : n;
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
+        const uint32_t l = (uint32_t)best[i];
+        assign[i] = (int32_t)l;
+        if (l < (uint32_t)nlist) atomicAdd(lds ? &s_cnt[l] : &cnt[l], 1u);
+    }
+    if (!lds) return;
+    __syncthreads();
+    for (int l = threadIdx.x; l < nlist; l += 256)
+        if (s_cnt[l]) atomicAdd(&cnt[l], s_cnt[l]);
 }
 
-hipError_t launch_hist(const int32_t *assign, int64_t n, uint32_t *cnt, hipStream_t s)
+hipError_t launch_lists_of_best(const unsigned long long *best, int64_t n, int nlist, int32_t *assign, uint32_t *cnt, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    const int grid = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-    hipLaunchKernelGGL(hist_kernel, dim3(grid), dim3(256), 0, s, assign, n, cnt);
+    const bool lds = nlist <= kLdsLists;
+    int64_t run = 2048; // rows per workgroup: at most 1024 workgroups add their counts to the same words
+    while ((n + run - 1) / run > 1024) run *= 2;
+    hipLaunchKernelGGL(lists_of_best_kernel, dim3((uint32_t)((n + run - 1) / run)), dim3(256), lds ? (size_t)nlist * 4 : 0, s,
+                       best, n, nlist, assign, cnt, run, lds);
     return hipGetLastError();
 }
 

@@ -327,8 +327,8 @@ struct LdsCleared {
     std::atomic<int> on[kMaxDevices];
 };
 
-template <typename K>
-inline hipError_t launch_with_lds(K kernel, LdsCleared &c, int lds, const ScanArgs &a, int grid, int threads, hipStream_t s)
+template <typename K, typename A>
+inline hipError_t launch_with_lds(K kernel, LdsCleared &c, int lds, const A &a, int grid, int threads, hipStream_t s)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -515,11 +515,52 @@ struct GemmArgs {
     float *out;          // [m][stride]
     int m, n, n_pad, n_store, ld, metric;
     uint32_t stride;
+    // launch_gemm_near_ties (m rows): q are the caller's dense rows [.][d], qnorm and best indexed by row like them
+    const uint32_t *list, *nlisted; // rows to score, and how many (on the device)
+    unsigned long long *best;       // [.] out: best (value key << 32 | column) of the listed rows
+    int d;
 };
 hipError_t launch_gemm_scores(const GemmArgs &a, hipStream_t s);
+// rows whose second best value (second[]: as the split GEMM left it) is near their best: listed, and decided in fp32
+hipError_t launch_gemm_near_ties(const GemmArgs &a, const uint32_t *second, const uint32_t *cmax, uint32_t *list, uint32_t *nlisted,
+                                 int num_cu, hipStream_t s);
+
+// the same scores with every fp32 operand held as two halfs (see pk_gemm.hip)
+struct SplitRowsArgs {
+    const float *x;      // [m][d] rows, dense
+    const float *c;      // [n_c][ld] centroid table, zero padded
+    uint32_t m, n_c;
+    int d, ld;
+    char *xs, *cs;       // [m][4 * ld], [n_c][4 * ld] out: split rows
+    float *x_back, *c_back; // [m], [n_c] out: what undoes the row's scale
+    float *qnorm;        // [m] out: squared norms, or null
+    float *copy;         // [m][ld] out: fp32 rows, zero padded, or null
+    char *half_rows;     // [m][half_bytes] out: rows rounded to half precision, zero padded, or null
+    float *half_norm;    // [m] out: their squared norms
+    int half_bytes;
+    unsigned long long *best; // [m] set to ~0, or null
+    uint32_t *second;    // [m] set to all ones, or null
+    uint32_t *cmax;      // raised to the largest squared norm of the centroids (as bits), or null
+    QueryMeta meta;      // as in launch_prep_coarse, one handle (cand_off null: not wanted)
+};
+hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &m, hipStream_t s);
+struct SplitGemmArgs {
+    const char *q, *c;   // split rows [m][4 * ld], [n_pad][4 * ld]
+    const float *q_back, *c_back, *qnorm, *cnorm; // (norms: L2 only)
+    float *out;          // [m][stride] scores, or null:
+    unsigned long long *best; // [m] best (value key << 32 | column) by atomicMin; ~0 on entry
+    int m, n, n_pad, ld, metric;
+    uint32_t stride;
+    // with best: the value key of the second best column where it is near the best (else all ones, as on entry)
+    uint32_t *second;         // [m]
+    const uint32_t *cmax;     // largest squared norm of the centroids (as bits)
+};
+hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s);
 
 // build / insert
-hipError_t launch_hist(const int32_t *assign, int64_t n, uint32_t *cnt, hipStream_t s);
+// the lists of a top-1 assignment (low words of best[]), and how many rows each list gets (cnt: zero before)
+hipError_t launch_lists_of_best(const unsigned long long *best, int64_t n, int nlist, int32_t *assign, uint32_t *cnt, hipStream_t s);
+constexpr int kLdsLists = 8192; // most lists that a workgroup counts in LDS (32 KB)
 hipError_t launch_scatter_build(const DevIndex *ix, const float *x, const int64_t *ids, const int32_t *assign,
                                 int64_t n, int64_t id0, uint32_t *fill, hipStream_t s);
 hipError_t launch_store_centroids(const float *c, int nlist, int d, int dpad32, int nlist_pad, int metric,
@@ -581,7 +622,8 @@ struct KmeansArgs {
     const int32_t *assign; // [n] cluster of each row
     int64_t n;
     int d, nlist;
-    uint32_t *cnt, *start, *fill; // [nlist] each (scratch)
+    uint32_t *cnt;         // [nlist] in: members of each cluster
+    uint32_t *start, *fill; // [nlist] each (scratch)
     uint32_t *members;     // [n] row numbers in cluster-major order (scratch)
     float *centroids;      // [nlist][d] in: centroids the assignment used; out: means of the members
     double *sums;          // [nlist][d] scratch: per-cluster totals

@@ -1,7 +1,7 @@
 // Lloyd's update step on the device, for index training (Section 2.2: the clusters of an IVF
 // index come from k-means; Section 4.4 / 6.1 "IVF-Split" re-runs a light k-means on the GPU).
 // The assignment step is the coarse search with nprobe = 1 under L2 (pk_api.hip); this file
-// turns an assignment into new centroids: histogram, exclusive scan, scatter of the row
+// turns an assignment and its histogram into new centroids: exclusive scan, scatter of the row
 // numbers into cluster-major order, then the members are summed in fp64, 256 at a time per
 // workgroup (thread j owns dimensions j, j + 256, ...; rows are read coalesced; partial sums
 // meet by fp64 atomics), and every cluster divides its total.  An empty cluster keeps its
@@ -11,25 +11,36 @@
 
 namespace pk {
 
-__global__ void km_hist_kernel(KmeansArgs a)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t l = (uint32_t)a.assign[i];
-        if (l < (uint32_t)a.nlist) atomicAdd(&a.cnt[l], 1u);
-    }
-}
-
 __global__ __launch_bounds__(1024) void km_offsets_kernel(KmeansArgs a)
 {
     __shared__ uint32_t s_wave[17];
     block_exscan(a.cnt, a.start, (uint32_t)a.nlist, s_wave);
 }
 
-__global__ void km_scatter_kernel(KmeansArgs a)
+// Row numbers into cluster-major order.  A workgroup takes kKmRun rows, counts them per cluster in LDS and reserves
+// each cluster's room with one atomic (an atomic per row on 162 words took 189 us for 262 144 rows).
+constexpr int kKmRun = 2048;
+__global__ __launch_bounds__(256) void km_scatter_kernel(KmeansArgs a, bool lds)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * blockDim.x) {
+    extern __shared__ uint32_t s_at[];
+    const int64_t i0 = (int64_t)blockIdx.x * kKmRun, i1 = i0 + kKmRun < a.n ? i0 + kKmRun : a.n;
+    if (lds) {
+        for (int l = threadIdx.x; l < a.nlist; l += 256) s_at[l] = 0u;
+        __syncthreads();
+        for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
+            const uint32_t l = (uint32_t)a.assign[i];
+            if (l < (uint32_t)a.nlist) atomicAdd(&s_at[l], 1u);
+        }
+        __syncthreads();
+        for (int l = threadIdx.x; l < a.nlist; l += 256)
+            if (s_at[l]) s_at[l] = a.start[l] + atomicAdd(&a.fill[l], s_at[l]);
+        __syncthreads();
+    }
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
         const uint32_t l = (uint32_t)a.assign[i];
-        if (l < (uint32_t)a.nlist) a.members[a.start[l] + atomicAdd(&a.fill[l], 1u)] = (uint32_t)i;
+        if (l >= (uint32_t)a.nlist) continue;
+        const uint32_t at = lds ? atomicAdd(&s_at[l], 1u) : a.start[l] + atomicAdd(&a.fill[l], 1u);
+        a.members[at] = (uint32_t)i;
     }
 }
 
@@ -112,16 +123,14 @@ __global__ __launch_bounds__(256) void km_finalize_kernel(KmeansArgs a)
 hipError_t launch_kmeans_update(const KmeansArgs &a, hipStream_t s)
 {
     if (a.n <= 0 || a.nlist <= 0 || a.d <= 0 || a.d > PK_MAX_DIM) return hipErrorInvalidValue;
-    hipError_t e = launch_fill_u32(a.cnt, 0u, (size_t)a.nlist, s);
-    if (e != hipSuccess) return e;
-    e = launch_fill_u32(a.fill, 0u, (size_t)a.nlist, s);
+    hipError_t e = launch_fill_u32(a.fill, 0u, (size_t)a.nlist, s);
     if (e != hipSuccess) return e;
     e = launch_fill_u32(reinterpret_cast<uint32_t *>(a.inertia), 0u, 2, s);
     if (e != hipSuccess) return e;
-    const int grid = (int)((a.n + 255) / 256 < 4096 ? (a.n + 255) / 256 : 4096);
-    hipLaunchKernelGGL(km_hist_kernel, dim3(grid), dim3(256), 0, s, a);
+    const bool lds = a.nlist <= kLdsLists;
     hipLaunchKernelGGL(km_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(km_scatter_kernel, dim3(grid), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(km_scatter_kernel, dim3((uint32_t)((a.n + kKmRun - 1) / kKmRun)), dim3(256),
+                       lds ? (size_t)a.nlist * 4 : 0, s, a, lds);
     e = launch_fill_u32(reinterpret_cast<uint32_t *>(a.sums), 0u, (size_t)a.nlist * a.d * 2, s);
     if (e != hipSuccess) return e;
     e = launch_fill_u32(reinterpret_cast<uint32_t *>(a.sq), 0u, (size_t)a.nlist * 2, s);

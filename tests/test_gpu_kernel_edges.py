@@ -59,3 +59,58 @@ def test_tie_groups_of_queries_that_are_scored_again(gpu_device):
             assert torch.equal(gi, wi) and torch.equal(gv, wv)
         finally:
             p.close()
+
+
+@pytest.mark.parametrize("metric", [IP, L2])
+@pytest.mark.parametrize("n,d,nlist,scale", [
+    (1, 1, 1, 1.0), (63, 64, 33, 1.0), (65, 100, 64, 1e-9), (257, 1536, 255, 1e12), (4097, 33, 700, 1.0), (40000, 96, 513, 1e-20)])
+def test_split_operand_assignment_is_within_fp32_of_64_bits(gpu_device, n, d, nlist, scale, metric):
+    """Rows and centroids held as two halfs each, in the three tile sizes of the kernel, with remainders in every
+    direction and rows whose scale is far from 1.  A row may only go to a list whose score is as good as the best to
+    fp32 rounding: the split's own error is below 2^-22 of |x||c|, the accumulation's below K * 2^-24 of it."""
+    rng = np.random.default_rng(n + d)
+    x = (rng.standard_normal((n, d)) * np.exp(rng.standard_normal((n, 1)))).astype(np.float32)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    x[:: 7, : d // 2] *= 1e-4  # elements that are tiny beside the row's largest
+    x, cent = x * np.float32(scale), cent * np.float32(scale)
+    ix = B.Index(dev(cent), dev(x), metric=metric)
+    try:
+        where = np.full(n, -1)
+        for l, m in enumerate(ix.list_lengths()):
+            if m:
+                where[ix.list_ids(l).cpu().numpy()] = l
+        assert (where >= 0).all()
+        x64, c64 = x.astype(np.float64), cent.astype(np.float64)
+        s = x64 @ c64.T
+        if metric == L2:
+            s = 2 * s - (c64 ** 2).sum(1)
+        size = np.linalg.norm(x64, axis=1) * np.linalg.norm(c64, axis=1).max()
+        if metric == L2:
+            size = size + (x64 ** 2).sum(1) + (c64 ** 2).sum(1).max()
+        gap = s.max(1) - s[np.arange(n), where]
+        assert (gap <= (2.0 ** -21 + d * 2.0 ** -23) * size).all(), (gap / size).max()
+    finally:
+        ix.close()
+
+
+@pytest.mark.parametrize("nq,storage,metric,d", [(1024, F16, L2, 100), (1024, F32, IP, 128), (999, F32, L2, 70), (128, F16, IP, 64)])
+def test_searches_through_the_split_gemm(gpu_device, nq, storage, metric, d):
+    """Batches with 128 tiles or more of 128 x 128 scores, against the oracle: every storage's own query copy is made
+    in the pass that splits the rows."""
+    cfg = W.scaled(W.C1, n=20000, d=d, nlist=16384 if nq == 128 else 2050, ncomp=64, train="lloyd", train_iters=0)
+    rng = np.random.default_rng(d)
+    x = W.vectors(cfg, 0, cfg.n)
+    p = Pair(x, x[rng.permutation(len(x))[:cfg.nlist]].copy(), metric, storage)
+    try:
+        q = W.queries(cfg, 1, nq)
+        some = np.sort(rng.permutation(nq)[:40])
+        gi, gv = p.gpu.search(dev(q), 10, 16)
+        # a row does not depend on the batch around it: a few rows again, through the other coarse kernel
+        probes = p.gpu.coarse(dev(q), 16).cpu().numpy()
+        fi, fv = p.gpu.scan_probes(dev(q[some]), 10, dev(probes[some]))
+        assert torch.equal(gi[some.tolist()], fi) and torch.equal(gv[some.tolist()], fv)
+        op, sc = p.orc.coarse(q[some], 17, with_scores=True)
+        assert np.mean(op[:, :16] == probes[some]) > 0.99
+        p.check_scan(q[some], 10, probes[some], where="split gemm")
+    finally:
+        p.close()
