@@ -298,6 +298,7 @@ struct Tunables {
     int mq;       // PK_TUNE_MQ: most query slots per regular tile (0: by expected queries per list)
     int mqh;      // PK_TUNE_MQH: most query slots per tile of the sliced-query kernel
     int ks;       // PK_TUNE_KS: sliced-query kernel 0 never, 1 automatic, 2 every list, 3 lists above one group
+    int sp;       // PK_TUNE_SP: sample pages per query (0: by rule)
     int sp_max;   // PK_TUNE_SP_MAX: most sample pages per query beyond the k rows needed
     int gemm_wgs; // PK_TUNE_GEMM_WGS: fewest 128 x 128 tiles for which the coarse step uses the GEMM
     int densesel; // PK_TUNE_DENSESEL: register top-nprobe selection of the coarse scores (1) or chunked (0)
@@ -337,7 +338,7 @@ const Tunables &tunables()
 #endif
         };
         return Tunables{env("PK_TUNE_WGS", 4),       env("PK_TUNE_MQ", 0),        env("PK_TUNE_MQH", 64),
-                        env("PK_TUNE_KS", 1),        env("PK_TUNE_SP_MAX", 16),   env("PK_TUNE_GEMM_WGS", 128),
+                        env("PK_TUNE_KS", 1),        env("PK_TUNE_SP", 0), env("PK_TUNE_SP_MAX", 16),   env("PK_TUNE_GEMM_WGS", 128),
                         env("PK_TUNE_DENSESEL", 1),  env("PK_TUNE_GRABDIV", 8),   env("PK_TUNE_HIST", 1),
                         env("PK_TUNE_RS_FROM", 0),   env("PK_TUNE_RS_NQ", 512),   env("PK_TUNE_HOT_GRAB", 1),
                         env("PK_TUNE_HOT_CUS", 96),  env("PK_TUNE_WL_ASIDE", 1),  env("PK_TUNE_FUSE_TAU", 1)};
@@ -398,9 +399,9 @@ uint32_t emit_cap_for(const pk_index *own, int K, uint64_t wmax, int64_t nq)
 // ahead > 0 sizes the buffers for what the same call would need after `ahead` more inserts
 // into every handle; worst also takes the largest value of every size that depends on how the
 // queries spread (tile groups, sample pages), which is how pk_workspace_reserve sizes the
-// workspace for every call within its limits.
+// workspace for every call within its limits.  lean: the smallest threshold sample, for a workspace that cannot grow.
 int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t nq, int k, int nprobe,
-              bool need_coarse, bool need_fine, int64_t ahead = 0, bool worst = false)
+              bool need_coarse, bool need_fine, int64_t ahead = 0, bool worst = false, bool lean = false)
 {
     const pk_index *own = hs[0];
     std::memset(&p, 0, sizeof(p));
@@ -460,6 +461,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     p.K = k + 1;
     p.sp = (k + own->P - 1) / own->P; // sample pages: at least k rows when the first pages are full
     uint64_t tiles = 0, wmax = 0, lmax = 0;
+    double lmean = 0; // rows per list on average (the largest over the handles)
     int nlist_hi = 0, pad_hi = 0;
     const int mq_least = worst ? 16 : std::min(p.mq_f, p.mq_h);
     const bool rs_tiles = worst ? (own->row_bytes <= 1536 && own->P % kRrTileRows == 0) : p.hot_rs;
@@ -473,6 +475,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         if (w > 0xfffffff0ull) return PK_ERR_UNSUPPORTED; // positions inside a query's range are 32-bit
         wmax = std::max(wmax, w);
         lmax = std::max(lmax, wq_ub(ix, 1)); // the longest list as it may be now
+        lmean = std::max(lmean, (double)ix->n_total / ix->cfg.nlist);
         const uint64_t pp = w / ix->P + nprobe;
         const uint64_t pages = std::min<uint64_t>(pages_used_ub(ix, ahead), nqa * pp);
         tiles += pages + nqa * pp / mq_least + 1;
@@ -482,28 +485,28 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     }
     if (tiles > 0xfffffff0ull) return PK_ERR_UNSUPPORTED;
     {
-        // Sample pages per query.  A larger sample gives a tighter threshold and a finer bucket
-        // scale, hence fewer emitted candidates; it costs one tile per query and page.  Wanted:
-        // the k-th best of the sample at most its 40 % quantile (large k).  And for batches of
-        // few queries, whose emitted candidates all meet at a handful of counters and serialise
-        // there: the query that lands in the longest list emits a share of that list's rows that
-        // falls as 1 / pages, about 1 ns of serialised emission per row of the list at one page
-        // (measured: 60 k entries from a 444 k-row list, 0.45 ms), while a page costs every query
-        // a tile: 0.7 us of latency plus its bytes at 10 TB/s while the tiles fit the chip side by
-        // side.  The sum is least at pages = sqrt(first cost / second).
-        // Spent: at most 3 % of the scan's tiles, and sp_max pages.
-        const uint64_t afford = tiles * 3u / 100u / (uint64_t)std::max<int64_t>(nq, 1);
-        const uint64_t by_quantile = ((uint64_t)p.K * 10 + 3 * own->P - 1) / (3 * own->P);
-        uint64_t by_size = 0;
-        if (nq <= 64) {
-            const double emit_us = 1.0e-3 * (double)lmax;
-            const double page_us = 0.7 + (double)nq * (double)own->P * (double)own->row_bytes / 1.0e7;
-            by_size = (uint64_t)std::llround(std::sqrt(emit_us / page_us));
-        }
-        uint64_t more = std::min(afford, std::max(by_quantile, by_size));
+        // Sample pages per query.  The threshold is the k-th best of sp * rows sampled rows, so a list of L rows near the
+        // query emits about L k / (sp * rows) of them before the histogram has tightened the gate.  Emission costs
+        // about 12 ns per candidate of the query that meets the longest list (its atomics meet at one counter, one
+        // workgroup selects among them: 60 k entries from a 444 k-row list 0.45 ms; 7 k fewer of 9.4 k from a list of
+        // 1165 rows, k = 77, 63 us) and 0.3 ns per candidate over all queries (1.6 M fewer of 3.2 M, 721 queries, 0.5 ms
+        // beside the overflows they caused).  A page costs 0.7 us of latency, 10 ns per query (a tile each) and its
+        // bytes: at 10 TB/s while the tiles of a page fit the chip side by side (one per CU), else at 5 TB/s.  The sum is
+        // least at sp = sqrt(emission of one page / cost of a page).  Batches of 721 queries of k = 37 over lists of
+        // 10 000 rows of 80 floats take 6 pages and 1.07 ms (one page: 12.7 ms, 2: 1.41, 4: 1.11, 12: 1.00); 256 queries
+        // over lists of 300 rows take one and 54 us (2: 61, 4: 72); 1024 over lists of 2441 rows, k = 100, four and 2.94 ms
+        // (1: 31, 2: 3.34, 3: 2.95, 6: 3.00).
+        // At most sp_max pages, and as many as the threshold takes in registers.
+        const double rows = std::min((double)own->P, std::max(1.0, lmean));
+        const double page_us = 0.7 + 0.01 * (double)nq + (double)nq * (double)own->P * (double)own->row_bytes / (nq <= own->num_cu ? 1.0e7 : 5.0e6);
+        const double emit_us = (0.012 * (double)lmax + 0.0003 * (double)nq * lmean) * (double)k / rows;
+        uint64_t more = (uint64_t)std::llround(std::sqrt(emit_us / page_us));
+        more = std::min<uint64_t>(more, std::max<uint64_t>(1, 16u * (uint32_t)kSelThreads / (uint32_t)own->P));
         more = std::min<uint64_t>(more, (uint64_t)tunables().sp_max);
         if (worst) more = (uint64_t)tunables().sp_max;
+        if (lean) more = 0;
         p.sp = std::max(p.sp, (int)more);
+        if (tunables().sp > 0) p.sp = tunables().sp;
     }
     p.sp = std::min(p.sp, kMaxSamplePages); // (a sample of fewer than k rows gives no threshold: slower, not wrong)
     p.span = (uint32_t)(p.sp * own->P);
@@ -899,6 +902,9 @@ int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, i
     f.rcnt = p.sslot_o;
     f.rregions = p.rescues;
     f.rcap = kRescueCap;
+    f.hist = sa.use_hist && p.hot_from > 0 ? p.hist : nullptr; // (the rows-in-registers kernel does not count: looser, not wrong)
+    f.tlo = p.tlo;
+    f.tinv = p.tinv;
     if (p.rescues > 0) PK_HIP(launch_rescue(f, m, p.nq, 2 * own->num_cu, s));
     PK_HIP(launch_select_final(f, m, p.nq, s));
     if (timed) PK_TRY(mark(own, s));
@@ -937,6 +943,8 @@ int search_impl(pk_index *const *hs, int nh, const int64_t *q_offsets, const flo
         Plan p;
         PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly));
         if (fixed_ws) {
+            if (p.bytes > fixed_bytes)
+                PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, true));
             if (nq != nq_all || p.bytes > fixed_bytes) return PK_ERR_WORKSPACE;
             carve(p, fixed_ws, own);
         } else {
@@ -2003,6 +2011,7 @@ size_t pk_search_noalloc_bytes(pk_index *ix, int64_t nq, int32_t k, int32_t npro
     const uint32_t qlo[2] = {0, (uint32_t)nq};
     Plan p;
     if (make_plan(p, hs, 1, qlo, nq, k, nprobe, true, true) != PK_OK) return 0;
+    if (p.bytes > kScratchBytes && make_plan(p, hs, 1, qlo, nq, k, nprobe, true, true, 0, false, true) != PK_OK) return 0;
     return p.bytes;
 }
 

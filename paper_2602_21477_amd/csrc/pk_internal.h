@@ -383,6 +383,8 @@ struct FinalArgs {
     unsigned long long *rkeys;
     uint32_t *rcnt;                   // [nq] zero before launch_rescue
     uint32_t rregions, rcap;          // rregions 0: launch_rescue was not called
+    const uint32_t *hist;             // [nq][kHistBins] candidates the scan emitted per bucket, stored or not (null: not counted)
+    const float *tlo, *tinv;          // [nq] bucket scale
 };
 constexpr uint32_t kRescueCap = 4096;    // keys per rescue region: what the final selection takes in registers
 constexpr uint32_t kRescueRegions = 128; // most queries of a call that are rescued

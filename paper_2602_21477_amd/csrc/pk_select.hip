@@ -431,8 +431,10 @@ __device__ void rescore_query(const FinalArgs &a, const MultiArgs &h, uint32_t q
 }
 
 // Queries whose emission region overflowed, scored again by the whole chip.  The keys that a region did keep are
-// candidates of the query, so the k-th best of any k of them bounds the k-th best of all: with that as the threshold
-// (a few hundred rows pass it) every probed row is scored once more, and what passes goes to a region of its own.
+// candidates of the query, so the k-th best of any k of them bounds the k-th best of all; and where the scan counted
+// what it emitted per bucket, stored or not, the first bucket at which the count reaches k bounds it too (a region
+// that filled up with the rows of far lists before the near ones were scanned has a loose k-th best).  With both as
+// the threshold every probed row is scored once more, and the few hundred that pass go to a region of their own.
 // Workgroup b serves overflowed query b % n (n of them, counted by every workgroup for itself) and takes every
 // n-th-workgroup's share of its pages.  Bound by latency: a query of 148 000 rows of 1536 bytes (228 MB) takes its
 // 1170 pages to 512 workgroups, where select_final's one workgroup (rescore_query) needed 15.4 ms for it: a batch of
@@ -499,6 +501,20 @@ __global__ __launch_bounds__(kSelThreads) void rescue_kernel(FinalArgs a, MultiA
     uint32_t left, ties;
     const uint32_t tau = radix_kth<VPT>(key, live, (uint32_t)a.k, hist, left, ties); // its barriers publish the LDS arrays
     const uint32_t pages = block_exscan(s_page0, s_page0, nprobe, s_wave);
+    uint32_t bmax = (uint32_t)kHistBins - 1u; // buckets beyond this are cut (every wave works it out for itself)
+    float lo_value = 0.f, inv = 0.f;
+    if (a.hist) {
+        static_assert(kHistBins == 64, "a lane per bucket");
+        uint32_t x = a.hist[(size_t)q * kHistBins + lane];
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off);
+            if (lane >= off) x += y;
+        }
+        const unsigned long long m = __ballot(x >= (uint32_t)a.k);
+        if (m) bmax = (uint32_t)__ffsll(m) - 1u;
+        lo_value = a.tlo[q];
+        inv = a.tinv[q];
+    }
 
     const int ln = lane & 15, lg = lane >> 4;
     const float qn = a.qnorm[q];
@@ -530,7 +546,7 @@ __global__ __launch_bounds__(kSelThreads) void rescue_kernel(FinalArgs a, MultiA
                 float v = nt == 0 ? acc0[0] : acc1[0];
                 if (a.metric == PK_METRIC_L2) v = l2_from_dot(mine ? ar.norm[local + row] : 0.f, v, qn);
                 const uint32_t bits = order_bits(v, a.metric);
-                const bool pass = mine && bits <= tau;
+                const bool pass = mine && bits <= tau && (!a.hist || bucket_of(v, lo_value, inv, a.metric) <= bmax);
                 const uint32_t m = (uint32_t)__ballot(pass); // lanes 0..15
                 if (m == 0u) continue;
                 uint32_t base = 0;

@@ -114,3 +114,22 @@ def test_searches_through_the_split_gemm(gpu_device, nq, storage, metric, d):
         p.check_scan(q[some], 10, probes[some], where="split gemm")
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("n,d,nlist,nprobe,k,nq,page,storage", [
+    (60000, 80, 20, 8, 37, 150, 0, F32), (6000, 100, 40, 12, 90, 20, 1024, F16), (9000, 64, 12, 12, 60, 300, 32, F16), (40000, 48, 3, 3, 100, 5, 64, F32)])
+def test_thresholds_from_several_sample_pages(gpu_device, n, d, nlist, nprobe, k, nq, page, storage):
+    """Long lists and large k take more than one page of sample (short and long pages, few and many queries); the
+    sample decides what is emitted, never what is found."""
+    cfg = W.scaled(W.C1, n=n, d=d, nlist=nlist, ncomp=nlist, train_iters=2)
+    p, _ = make_pair(cfg, metric=L2, storage=storage, page_vecs=page)
+    try:
+        q = W.queries(cfg, 3, nq)
+        probes = p.gpu.coarse(dev(q), nprobe).cpu().numpy()
+        gi, gv = p.gpu.search(dev(q), k, nprobe)
+        some = np.arange(0, nq, max(1, nq // 15))
+        p.check_scan(q[some], k, probes[some], where="sample pages")
+        fi, fv = p.gpu.scan_probes(dev(q[some]), k, dev(probes[some]))
+        assert torch.equal(gi[some.tolist()], fi) and torch.equal(gv[some.tolist()], fv)
+    finally:
+        p.close()
