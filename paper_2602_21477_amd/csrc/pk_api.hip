@@ -19,6 +19,8 @@ constexpr uint64_t kRegionBytes = 256ull << 20; // emission regions of one launc
 constexpr int kFillChunk = 16384;           // vectors of a chunk that fills 128 tiles of 128 x 128 whatever the number of lists
 constexpr int kAssignChunk = 32768;         // vectors assigned per launch pair by the build and by k-means: 512 lists
                                             // give every CU a 256 x 256 tile of scores
+constexpr int kInsertChunk = 8192;          // vectors of one handle per launch sequence of an insert: its scratch is
+                                            // the size of its rows, and five launches are long over in their time
 constexpr int kInsertFast = 1024;           // most vectors of an insert call that takes the two-launch path
 
 #define PK_HIP(expr)                                   \
@@ -83,7 +85,7 @@ struct pk_index {
     // page accounting: last page counter read back, and how many vectors were inserted by then
     uint32_t pages_known;
     int64_t inserted_at_known;
-    uint32_t *pin_pages;
+    uint32_t *pin_pages;    // pinned [16]: [0] page counter read back; [4 .. 6] what a delete tells the host
     hipEvent_t ev;
     bool ev_pending;
     int64_t ev_inserted;
@@ -99,6 +101,7 @@ struct pk_index {
     // small inserts: top-1 keys of the batch (kept at ~0 between calls) and the slots the batch got
     unsigned long long *ins_best; // DEVICE [kInsertFast]
     uint32_t *ins_slots;          // DEVICE [kInsertFast]
+    uint32_t *del_words;          // DEVICE [8] counters of pk_delete (the first is zero between calls)
     // second stream of a search whose lists fall into two tile classes: the kernel for the lists many
     // queries probe is bound by the matrix cores and runs on some of the CUs while the HBM-bound scan of
     // the other lists has the rest (fork and join by events; default priority)
@@ -1199,6 +1202,71 @@ struct Table {
     int nlist, nlist_pad, d, ld, metric;
 };
 
+// Top-1 assignment of m vectors too few to fill tiles: best[i] = (score key << 32 | list) by the centroid kernel.
+// rows, norms: scratch for prepared rows where the caller's cannot be read as they are.  best[] holds ~0, or clear.
+int assign_few(const float *x, int64_t m, const Table &t, int num_cu, char *rows, float *norms, unsigned long long *best,
+               bool clear, hipStream_t s)
+{
+    MultiArgs mm;
+    std::memset(&mm, 0, sizeof(mm));
+    CentroidArgs ca{};
+    ca.row_bytes = t.ld * 4;
+    ca.metric = t.metric;
+    ca.qs = reinterpret_cast<const char *>(x);
+    if (t.metric != PK_METRIC_IP || t.d != t.ld) {
+        PK_HIP(launch_prep_queries(x, m, t.d, PK_F32, ca.row_bytes, rows, norms, s));
+        ca.qs = rows;
+        ca.qnorm = norms;
+    }
+    ca.best = best;
+    if (clear) PK_HIP(launch_fill_u32(reinterpret_cast<uint32_t *>(best), 0xffffffffu, (size_t)m * 2, s));
+    mm.n = 1;
+    mm.ix[0] = t.dev;
+    mm.qlo[1] = (uint32_t)m;
+    // vectors per workgroup: as many as it takes while that leaves a workgroup for every CU
+    ca.chunk = (int)std::min<int64_t>(64, (m + 15) / 16 * 16);
+    auto wgs = [&] { return (m + ca.chunk - 1) / ca.chunk * (t.nlist_pad / 16); };
+    while (ca.chunk > 16 && wgs() < num_cu) ca.chunk -= 16;
+    if (wgs() > 0x7fffffffll) return PK_ERR_UNSUPPORTED;
+    ca.blk[1] = (uint32_t)wgs();
+    PK_HIP(launch_centroid_scores(ca, mm, s));
+    return PK_OK;
+}
+
+// An insert's vectors go through the split-operand GEMM from as many scores on as it takes to beat the centroid kernel,
+// whose time grows with the vectors while the GEMM's small tiles run side by side.  Whole inserts, centroid kernel against
+// GEMM: 256 x 512 lists x 1024 27 and 30 us, 256 x 1024 x 768 35 and 30, 65 x 2048 x 1536 54 and 41, 1000 x 512 x 1024
+// 49 and 40.  (Near ties are left as they come out: its scores are nearer the exact ones than the centroid kernel's.)
+// Against a score matrix, a selection and groups of 1024 one after the other, 2000 x 512 x 1024 went from 159 to 48 us.
+constexpr int64_t kInsertScores = 3 << 16;
+constexpr int64_t kInsertProducts = 150000000; // (wide rows: earlier)
+bool insert_by_gemm(const pk_index *ix, int64_t m)
+{
+    return m * (int64_t)ix->nlist_pad >= kInsertScores || m * (int64_t)ix->nlist_pad * ix->dpad32 >= kInsertProducts;
+}
+
+// Workspace of an insert of m vectors into one handle.
+struct InsertScratch {
+    unsigned long long *best;
+    char *xs, *cs;
+    float *xback, *cback;
+    int32_t *lists;
+    uint32_t *ranks, *slots;
+    size_t lay(char *base, const pk_index *ix, int64_t m)
+    {
+        Carver c{base, 0};
+        best = c.take<unsigned long long>((size_t)m);
+        xs = c.take<char>((size_t)m * ix->rb32);
+        xback = c.take<float>((size_t)m);
+        cs = c.take<char>(insert_by_gemm(ix, m) ? (size_t)ix->nlist_pad * ix->rb32 : 0);
+        cback = c.take<float>((size_t)ix->nlist_pad);
+        lists = c.take<int32_t>((size_t)m);
+        ranks = c.take<uint32_t>((size_t)m);
+        slots = c.take<uint32_t>((size_t)m);
+        return round_up(c.off, 256);
+    }
+};
+
 // Top-1 assignment of n vectors (Section 3.1: the list of the best centroid): best[i] = (score key << 32 | list), by
 // the scores of the fp32 GEMM.  The split-operand GEMM finds them, two launches per chunk and no score matrix, and the
 // fp32 kernel goes over the few rows whose best two are near; a last chunk that cannot fill tiles (coarse_tiles) takes
@@ -1265,32 +1333,14 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
         PK_HIP(launch_gemm_near_ties(g, as.second, as.words + 1, as.listed, as.words, num_cu, s));
     }
     if (by_gemm < n) {
-        const float *xt = x + (size_t)by_gemm * t.d;
-        CentroidArgs ca{};
-        ca.row_bytes = t.ld * 4;
-        ca.metric = t.metric;
-        ca.qs = reinterpret_cast<const char *>(xt);
-        if (t.metric != PK_METRIC_IP || t.d != t.ld) { // prepared rows and norms
-            PK_HIP(launch_prep_queries(xt, tail, t.d, PK_F32, ca.row_bytes, as.xs, as.xback, s));
-            ca.qs = as.xs;
-            ca.qnorm = as.xback;
-        }
-        ca.best = best + by_gemm;
-        PK_HIP(launch_fill_u32(reinterpret_cast<uint32_t *>(ca.best), 0xffffffffu, (size_t)tail * 2, s));
-        mm.n = 1;
-        mm.ix[0] = t.dev;
-        mm.qlo[1] = (uint32_t)tail;
-        ca.chunk = (int)std::min<int64_t>(64, (tail + 15) / 16 * 16);
-        while (ca.chunk > 16 && (tail + ca.chunk - 1) / ca.chunk * (t.nlist_pad / 16) < num_cu) ca.chunk -= 16;
-        ca.blk[1] = (uint32_t)((tail + ca.chunk - 1) / ca.chunk * (t.nlist_pad / 16));
-        PK_HIP(launch_centroid_scores(ca, mm, s));
+        PK_TRY(assign_few(x + (size_t)by_gemm * t.d, tail, t, num_cu, as.xs, as.xback, best + by_gemm, true, s));
     }
     return PK_OK;
 }
 
 // One launch sequence: top-1 coarse search (unless the lists are given), slot reservation and
 // append for the vectors of hs[0..nh), rows [qlo[a], qlo[a+1]) of the batch going to handle a
-// (at most 1024 each).  The workspace is that of hs[0].
+// (at most kInsertGroup each; kInsertChunk for one handle).  The workspace is that of hs[0].
 int insert_batch(pk_index *const *hs, int nh, const uint32_t *qlo, const float *x, const int64_t *ids,
                  const int32_t *forced, int32_t *assigned_out, hipStream_t s)
 {
@@ -1337,28 +1387,70 @@ int insert_batch(pk_index *const *hs, int nh, const uint32_t *qlo, const float *
         for (int a = 0; a < nh; ++a) PK_TRY(note_inserted(hs[a], (int64_t)(qlo[a + 1] - qlo[a]), s));
         return PK_OK;
     }
-    Plan p;
-    PK_TRY(make_plan(p, hs, nh, qlo, m, 1, 1, forced == nullptr, false));
-    const size_t extra = round_up(p.bytes, 256);
-    PK_TRY(ensure_ws(own, extra + round_up((size_t)m * 4, 256), s));
-    carve(p, own->ws, own);
-    uint32_t *slots = reinterpret_cast<uint32_t *>(own->ws + extra);
+    AppendIds idc{};
+    for (int a = 0; a < nh; ++a) idc.id0[a] = hs[a]->next_id;
     MultiArgs mm;
     fill_multi(mm, hs, nh, qlo);
+    if (nh == 1 && !forced) {
+        // top-1 keys without a score matrix, then slots and rows
+        InsertScratch is;
+        PK_TRY(ensure_ws(own, is.lay(nullptr, own, m), s));
+        is.lay(own->ws, own, m);
+        if (insert_by_gemm(own, m)) {
+            SplitRowsArgs sr{};
+            sr.x = x;
+            sr.c = own->host.cent;
+            sr.m = (uint32_t)m;
+            sr.n_c = (uint32_t)own->nlist_pad;
+            sr.d = own->cfg.d;
+            sr.ld = own->dpad32;
+            sr.xs = is.xs;
+            sr.cs = is.cs;
+            sr.x_back = is.xback;
+            sr.c_back = is.cback;
+            sr.best = is.best;
+            PK_HIP(launch_split_rows(sr, mm, s));
+            SplitGemmArgs g{};
+            g.q = is.xs;
+            g.c = is.cs;
+            g.q_back = is.xback;
+            g.c_back = is.cback;
+            g.cnorm = own->host.cnorm;
+            g.best = is.best;
+            g.m = (int)m;
+            g.n = own->cfg.nlist;
+            g.n_pad = own->nlist_pad;
+            g.ld = own->dpad32;
+            g.metric = own->cfg.metric;
+            PK_HIP(launch_gemm_split(g, own->num_cu, s));
+        } else {
+            const Table table{own->dev, own->host.cent, own->host.cnorm, own->cfg.nlist, own->nlist_pad, own->cfg.d, own->dpad32,
+                              own->cfg.metric};
+            if (m <= kInsertFast) is.best = own->ins_best; // holds ~0 between calls: nothing to clear first
+            PK_TRY(assign_few(x, m, table, own->num_cu, is.xs, is.xback, is.best, m > kInsertFast, s));
+        }
+        PK_HIP(launch_reserve(mm, nullptr, is.best, is.lists, is.ranks, is.slots, assigned_out, s));
+        PK_HIP(launch_append(mm, idc, x, ids, is.lists, is.slots, is.best == own->ins_best ? own->ins_best : nullptr, s));
+        return note_inserted(own, m, s);
+    }
+    Plan p;
+    PK_TRY(make_plan(p, hs, nh, qlo, m, 1, 1, forced == nullptr, false));
+    const size_t extra = round_up(p.bytes, 256), words = round_up((size_t)m * 4, 256);
+    PK_TRY(ensure_ws(own, extra + 2 * words, s));
+    carve(p, own->ws, own);
+    uint32_t *slots = reinterpret_cast<uint32_t *>(own->ws + extra), *ranks = reinterpret_cast<uint32_t *>(own->ws + extra + words);
     const int32_t *assign = forced;
     if (!forced) {
         PK_TRY(run_coarse(p, mm, hs, x, s));
         assign = p.probes;
     }
-    AppendIds idc{};
-    for (int a = 0; a < nh; ++a) idc.id0[a] = hs[a]->next_id;
     bool small = true;
     for (int a = 0; a < nh; ++a) small = small && qlo[a + 1] - qlo[a] <= (uint32_t)kFusedAppend;
     if (small) {
         PK_HIP(launch_reserve_append(mm, idc, x, ids, assign, nullptr, slots, assigned_out, s));
     } else {
-        PK_HIP(launch_reserve(mm, assign, slots, assigned_out, s));
-        PK_HIP(launch_append(mm, idc, x, ids, assign, slots, s));
+        PK_HIP(launch_reserve(mm, assign, nullptr, nullptr, ranks, slots, assigned_out, s));
+        PK_HIP(launch_append(mm, idc, x, ids, assign, slots, nullptr, s));
     }
     for (int a = 0; a < nh; ++a) PK_TRY(note_inserted(hs[a], (int64_t)(qlo[a + 1] - qlo[a]), s));
     return PK_OK;
@@ -1372,8 +1464,9 @@ int insert_impl(pk_index *ix, const float *x, const int64_t *ids, int64_t m, con
     if (m == 0) return PK_OK;
     PK_TRY(check_capacity(ix, m, s));
     pk_index *hs[1] = {ix};
-    for (int64_t i0 = 0; i0 < m; i0 += 1024) {
-        const uint32_t qlo[2] = {0, (uint32_t)std::min<int64_t>(1024, m - i0)};
+    const int64_t chunk = forced ? kInsertGroup : kInsertChunk;
+    for (int64_t i0 = 0; i0 < m; i0 += chunk) {
+        const uint32_t qlo[2] = {0, (uint32_t)std::min<int64_t>(chunk, m - i0)};
         PK_TRY(insert_batch(hs, 1, qlo, x + (size_t)i0 * ix->cfg.d, ids ? ids + i0 : nullptr, forced ? forced + i0 : nullptr,
                             assigned_out ? assigned_out + i0 : nullptr, s));
     }
@@ -1449,9 +1542,11 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
         hipEventCreateWithFlags(&ix->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ix->ev_join, hipEventDisableTiming) != hipSuccess)
         return fail(PK_ERR_HIP);
-    if (hipMalloc(reinterpret_cast<void **>(&ix->ins_best), (size_t)kInsertFast * 12) != hipSuccess) return fail(PK_ERR_NOMEM);
+    if (hipMalloc(reinterpret_cast<void **>(&ix->ins_best), (size_t)kInsertFast * 12 + 32) != hipSuccess) return fail(PK_ERR_NOMEM);
     ix->ins_slots = reinterpret_cast<uint32_t *>(ix->ins_best + kInsertFast);
-    if (launch_fill_u32(reinterpret_cast<uint32_t *>(ix->ins_best), 0xffffffffu, (size_t)kInsertFast * 2, s) != hipSuccess)
+    ix->del_words = ix->ins_slots + kInsertFast;
+    if (launch_fill_u32(reinterpret_cast<uint32_t *>(ix->ins_best), 0xffffffffu, (size_t)kInsertFast * 2, s) != hipSuccess ||
+        launch_fill_u32(ix->del_words, 0u, 8, s) != hipSuccess)
         return fail(PK_ERR_HIP);
     {
         // set-up for pk_search_noalloc: resolve this device's copy of its workspace array now, so
@@ -1577,14 +1672,11 @@ int pk_delete(pk_index *ix, const int64_t *ids, int64_t m, int64_t *n_removed, v
     Carver c{nullptr, 0};
     DeleteArgs da{};
     auto lay = [&](Carver &cv) {
-        da.sorted = cv.take<int64_t>(kDeleteChunk);
         da.unit_start = cv.take<uint32_t>((size_t)ix->cfg.nlist + 1);
         da.hits = cv.take<unsigned long long>(kDeleteChunk);
-        da.hit_len0 = cv.take<uint32_t>(kDeleteChunk);
-        da.hit_seg0 = cv.take<uint32_t>(kDeleteChunk);
+        da.hit_rank = cv.take<uint32_t>(kDeleteChunk);
         da.hit_cnt = cv.take<uint32_t>(kDeleteChunk);
-        da.scal = cv.take<uint32_t>(4);
-        da.removed = cv.take<unsigned long long>(1);
+        da.hit_len0 = cv.take<uint32_t>(kDeleteChunk);
     };
     lay(c);
     PK_TRY(ensure_ws(ix, c.off + 256, s));
@@ -1592,22 +1684,22 @@ int pk_delete(pk_index *ix, const int64_t *ids, int64_t m, int64_t *n_removed, v
     lay(c);
     da.ix = ix->dev;
     da.nlist = ix->cfg.nlist;
-    da.grid = ix->num_cu * 8;
-    PK_HIP(launch_fill_u32(da.scal, 0u, 4, s));
-    PK_HIP(launch_fill_u32(reinterpret_cast<uint32_t *>(da.removed), 0u, 2, s));
+    da.scal = ix->del_words;
+    da.removed = reinterpret_cast<unsigned long long *>(ix->del_words + 4);
+    da.host = ix->pin_pages + 4;
     unsigned long long removed = 0;
+    da.first = true;
     for (int pass = 0; pass < 1 << 20; ++pass) {
         for (int64_t i0 = 0; i0 < m; i0 += kDeleteChunk) {
             da.ids = ids + i0;
             da.m = (int)std::min<int64_t>(kDeleteChunk, m - i0);
-            PK_HIP(launch_delete(da, s));
+            PK_HIP(launch_delete(da, ix->num_cu, s));
+            da.first = false;
         }
-        // more rows carried the ids than one pass takes (several rows under one id): go again
-        uint32_t again = 0;
-        PK_HIP(hipMemcpyAsync(&removed, da.removed, sizeof(removed), hipMemcpyDeviceToHost, s));
-        PK_HIP(hipMemcpyAsync(&again, da.scal + 2, sizeof(again), hipMemcpyDeviceToHost, s));
         PK_HIP(hipStreamSynchronize(s));
-        if (!again) break;
+        removed = (unsigned long long)da.host[0] | ((unsigned long long)da.host[1] << 32);
+        // more rows carried the ids than one pass takes (several rows under one id): go again
+        if (!da.host[2]) break;
         PK_HIP(launch_fill_u32(da.scal + 2, 0u, 1, s));
     }
     ix->n_total -= (int64_t)removed;
@@ -2042,7 +2134,11 @@ int pk_workspace_reserve(pk_index *const *handles, int32_t n_handles, int64_t nq
     const uint32_t all[2] = {0, (uint32_t)nq_max};
     PK_TRY(make_plan(pc, handles, 1, all, nq_max, 1, np, true, false));
     need = std::max(need, pc.bytes);
-    need += round_up((size_t)nq_max * 4, 256) + 256; // slot array of an insert batch
+    need += 2 * (round_up((size_t)nq_max * 4, 256) + 256); // slots and ranks of an insert batch
+    InsertScratch is;
+    const int64_t mi = std::min<int64_t>(nq_max, kInsertChunk);
+    need = std::max(need, is.lay(nullptr, handles[0], mi));
+    for (int a = 1; a < n_handles; ++a) need = std::max(need, is.lay(nullptr, handles[a], mi));
     return ensure_ws(handles[0], need, static_cast<hipStream_t>(stream));
 }
 

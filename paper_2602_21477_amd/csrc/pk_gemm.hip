@@ -408,7 +408,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
         // per row: what turns a column's product into t (below), and how near a second value is near, in t's unit
         if (tid < BM) {
             const int m = m0 + tid < a.m ? m0 + tid : a.m - 1;
-            const float back = a.q_back[m], margin = near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax));
+            const float back = a.q_back[m], margin = a.second ? near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax)) : 0.f;
             s_row[tid] = a.metric == PK_METRIC_L2 ? -2.f * back : -1.f;
             s_row[BM + tid] = a.metric == PK_METRIC_L2 ? margin : margin / back;
         }
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             const int m = m0 + wm * (BM / WM) + i * 32 + rr;
-            if (!has || m >= a.m) continue;
+            if (!a.second || !has || m >= a.m) continue;
             uint32_t other = max(met[i], mine[i]);
             if (second[i] != 0xffffffffu) {
                 float v = value_of(second[i], PK_METRIC_L2);
@@ -551,7 +551,7 @@ hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 {
     if (a.m <= 0) return hipSuccess;
     if (a.ld % 64 != 0 || a.n < 1 || a.n > a.n_pad || (a.best == nullptr) == (a.out == nullptr) ||
-        (a.best && !(a.second && a.cmax && a.qnorm))) return hipErrorInvalidValue;
+        (a.second && !(a.best && a.cmax && a.qnorm))) return hipErrorInvalidValue;
     auto tiles = [&](int b) { return (int64_t)((a.m + b - 1) / b) * ((a.n_pad + b - 1) / b); };
     // the largest tile that still gives every CU one
     if (tiles(256) >= num_cu)

@@ -5,6 +5,8 @@
 // cluster in a CPU-side buffer because a device list cannot grow in place; here a list
 // is a chain of fixed-size pages, so growing it means taking the next free page of the
 // arena: no reallocation, no copy of old data, no host involvement.
+#include <algorithm>
+
 #include "pk_internal.h"
 
 namespace pk {
@@ -135,107 +137,154 @@ hipError_t launch_scatter_build(const DevIndex *ix, const float *x, const int64_
     return hipGetLastError();
 }
 
-// Insert, step 2: slot reservation for a batch of at most 1024 vectors by one workgroup.
-// Vector i takes slot list_len[l] + (number of earlier batch members of the same list), so
-// the order inside a list is the arrival order.  A vector whose slot starts a page beyond
-// the build-time extent opens a delta page.  If the arena or a list's delta table cannot
-// take the whole batch, nothing is changed, every slot is 0xffffffff and the sticky error
-// flag is set.  Small batches (x given): the workgroup's 16 waves also write the rows
+// Insert, step 1b (batches of more than kFusedAppend vectors per handle): for every vector the number of earlier members of
+// its group (kInsertGroup consecutive vectors of a handle) that go to the same list, and whether it is the group's
+// last one (top bit).  A wave per vector over the group's lists: the same counts by one workgroup, a thread per
+// vector, were 32 of the 38 us that reserving 1000 slots took.  Also turns the top-1 keys into lists (assign_out).
+__global__ __launch_bounds__(256) void insert_rank_kernel(MultiArgs ma, const int32_t *assign, const unsigned long long *best,
+                                                          int32_t *assign_out, uint32_t *ranks)
+{
+    const uint32_t i = blockIdx.x * 4u + (threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    if (i >= ma.qlo[ma.n]) return;
+    int h = 0;
+    while (h + 1 < ma.n && i >= ma.qlo[h + 1]) ++h;
+    const uint32_t row0 = ma.qlo[h], g0 = row0 + (i - row0) / kInsertGroup * kInsertGroup;
+    const uint32_t g1 = g0 + kInsertGroup < ma.qlo[h + 1] ? g0 + kInsertGroup : ma.qlo[h + 1];
+    auto list_of = [&](uint32_t j) { return best ? (int32_t)(uint32_t)best[j] : assign[j]; };
+    const int32_t l = list_of(i);
+    uint32_t before = 0, after = 0;
+    constexpr int U = 4; // requests in flight
+    for (uint32_t j0 = g0 + lane; j0 < g1; j0 += 64u * U) {
+        int32_t o[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) o[u] = j0 + 64u * u < g1 ? list_of(j0 + 64u * u) : -2;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t j = j0 + 64u * u;
+            before += o[u] == l && j < i ? 1u : 0u;
+            after += o[u] == l && j > i ? 1u : 0u;
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        before += __shfl_xor(before, off);
+        after += __shfl_xor(after, off);
+    }
+    if (lane == 0) {
+        ranks[i] = before | (after == 0u ? 0x80000000u : 0u);
+        if (best) assign_out[i] = l;
+    }
+}
+
+// Insert, step 2: slot reservation, one workgroup per handle, a group of at most kInsertGroup vectors after the other.
+// Vector i takes slot list_len[l] + (number of earlier group members of the same list), so the order inside a list
+// is the arrival order.  A vector whose slot starts a page beyond the build-time extent opens a delta page.  If the
+// arena or a list's delta table cannot take the whole group, nothing of it is inserted, its slots are 0xffffffff and
+// the sticky error flag is set.  Small batches (x given, no ranks): the workgroup's 16 waves also write the rows
 // (step 3), which saves the launch that would otherwise follow.
-__global__ __launch_bounds__(1024) void reserve_kernel(MultiArgs ma, const int32_t *assign, unsigned long long *best,
-                                                       uint32_t *slots, int32_t *assigned_out, AppendIds idc,
-                                                       const float *x, const int64_t *ids)
+template <bool RANKED>
+__global__ __launch_bounds__(1024) void reserve_kernel(MultiArgs ma, const int32_t *assign, const uint32_t *ranks,
+                                                       unsigned long long *best, uint32_t *slots, int32_t *assigned_out,
+                                                       AppendIds idc, const float *x, const int64_t *ids)
 {
     __shared__ int32_t s_l[1024];
     __shared__ uint32_t s_slot[1024];
     __shared__ uint32_t s_need, s_bad, s_page0;
+    static_assert(kInsertGroup == 1024, "a thread per vector of a group");
     // workgroup a serves handle a: its vectors are rows [qlo[a], qlo[a+1]) of the batch
     const DevIndex &ix = *ma.ix[blockIdx.x];
     const uint32_t row0 = ma.qlo[blockIdx.x];
     const int m = (int)(ma.qlo[blockIdx.x + 1] - row0);
     if (m == 0) return;
     if (assign) assign += row0;
+    if constexpr (RANKED) ranks += row0;
     slots += row0;
     if (assigned_out) assigned_out += row0;
-    const int i = threadIdx.x;
-    if (i == 0) {
-        s_need = 0;
-        s_bad = 0;
-    }
-    int32_t l = -1;
-    if (i < m) {
-        if (assign) {
-            l = assign[i];
-        } else { // the top-1 key the centroid kernel left (reset for the next insert on the way out)
-            l = (int32_t)(uint32_t)best[row0 + i];
+    for (int g0 = 0; g0 < (RANKED ? m : 1); g0 += kInsertGroup) { // (without ranks: one group of at most kFusedAppend)
+        const int t = threadIdx.x, i = g0 + t;
+        if (t == 0) {
+            s_need = 0;
+            s_bad = 0;
         }
-        if (l < 0 || l >= ix.nlist) l = -1;
-    }
-    s_l[i] = l;
-    __syncthreads();
-    uint32_t rank = 0, cnt = 0;
-    if (l >= 0) {
-        for (int j = 0; j < m; ++j) {
-            const bool same = s_l[j] == l;
-            cnt += same ? 1u : 0u;
-            rank += (same && j < i) ? 1u : 0u;
+        int32_t l = -1;
+        uint32_t rank = 0;
+        bool last = false;
+        if (i < m) {
+            if (assign) {
+                l = assign[i];
+            } else { // the top-1 key the centroid kernel left (reset for the next insert on the way out)
+                l = (int32_t)(uint32_t)best[row0 + i];
+            }
+            if (l < 0 || l >= ix.nlist) l = -1;
+            if constexpr (RANKED) {
+                rank = ranks[i] & 0x7fffffffu;
+                last = (ranks[i] >> 31) != 0u;
+            }
         }
-    }
-    uint32_t slot = 0xffffffffu, di = 0;
-    bool opens = false;
-    if (l >= 0) {
-        slot = ix.list_len[l] + rank;
-        const uint32_t lp = slot / (uint32_t)ix.P;
-        if (slot % (uint32_t)ix.P == 0 && lp >= ix.main_pages[l]) {
-            di = lp - ix.main_pages[l];
-            if (di >= (uint32_t)ix.max_dp) atomicOr(&s_bad, (uint32_t)kErrListFull);
-            // a list that shrank (deletes) still owns the delta pages it had: take a new one
-            // only where the table has none
-            else opens = ix.dtab[(size_t)l * ix.max_dp + di] == 0xffffffffu;
+        s_l[t] = l;
+        __syncthreads();
+        if (!RANKED && l >= 0) {
+            uint32_t cnt = 0;
+            for (int j = 0; j < m; ++j) {
+                const bool same = s_l[j] == l;
+                cnt += same ? 1u : 0u;
+                rank += (same && j < i) ? 1u : 0u;
+            }
+            last = rank == cnt - 1;
         }
-    } else if (i < m) {
-        atomicOr(&s_bad, (uint32_t)kErrListFull);
+        uint32_t slot = 0xffffffffu, di = 0;
+        bool opens = false;
+        if (l >= 0) {
+            slot = ix.list_len[l] + rank;
+            const uint32_t lp = slot / (uint32_t)ix.P;
+            if (slot % (uint32_t)ix.P == 0 && lp >= ix.main_pages[l]) {
+                di = lp - ix.main_pages[l];
+                if (di >= (uint32_t)ix.max_dp) atomicOr(&s_bad, (uint32_t)kErrListFull);
+                // a list that shrank (deletes) still owns the delta pages it had: take a new one
+                // only where the table has none
+                else opens = ix.dtab[(size_t)l * ix.max_dp + di] == 0xffffffffu;
+            }
+        } else if (i < m) {
+            atomicOr(&s_bad, (uint32_t)kErrListFull);
+        }
+        uint32_t my_page = 0;
+        if (opens) my_page = atomicAdd(&s_need, 1u);
+        __syncthreads();
+        if (t == 0) {
+            const uint32_t p0 = ix.ctr[0];
+            s_page0 = p0;
+            if (p0 + s_need > ix.ctr[2]) s_bad |= (uint32_t)kErrPages;
+            if (s_bad) atomicOr(&ix.ctr[1], s_bad);
+            else ix.ctr[0] = p0 + s_need;
+        }
+        __syncthreads();
+        const bool ok = s_bad == 0;
+        if (ok && opens) ix.dtab[(size_t)l * ix.max_dp + di] = s_page0 + my_page;
+        if (ok && l >= 0 && last) ix.list_len[l] = slot + 1;
+        if (i < m) {
+            slots[i] = ok ? slot : 0xffffffffu;
+            if (assigned_out) assigned_out[i] = l;
+        }
+        s_slot[t] = ok ? slot : 0xffffffffu;
+        __syncthreads(); // slots, and the page table entries and lengths just written, are visible to the whole workgroup
     }
-    uint32_t my_page = 0;
-    if (opens) my_page = atomicAdd(&s_need, 1u);
-    __syncthreads();
-    if (i == 0) {
-        const uint32_t p0 = ix.ctr[0];
-        s_page0 = p0;
-        if (p0 + s_need > ix.ctr[2]) s_bad |= (uint32_t)kErrPages;
-        if (s_bad) atomicOr(&ix.ctr[1], s_bad);
-        else ix.ctr[0] = p0 + s_need;
-    }
-    __syncthreads();
-    const bool ok = s_bad == 0;
-    if (ok && opens) ix.dtab[(size_t)l * ix.max_dp + di] = s_page0 + my_page;
-    if (ok && l >= 0 && rank == cnt - 1) ix.list_len[l] = slot + 1;
-    if (i < m) {
-        slots[i] = ok ? slot : 0xffffffffu;
-        if (assigned_out) assigned_out[i] = l;
-    }
-    if (!x) {
-        if (best && !assign && i < m) best[row0 + i] = ~0ull;
-        return;
-    }
-    s_slot[i] = ok ? slot : 0xffffffffu;
-    __syncthreads(); // slots, and the page table entries just written, are visible to the whole workgroup
-    for (int r = i >> 6; r < m; r += 16) {
+    if constexpr (RANKED) return;
+    for (int r = (int)threadIdx.x >> 6; r < m; r += 16) {
         if (s_slot[r] == 0xffffffffu) continue;
         const uint32_t row = row0 + (uint32_t)r;
         write_row(ix, (uint32_t)s_l[r], s_slot[r], x + (size_t)row * ix.d,
                   ids ? ids[row] : idc.id0[blockIdx.x] + (int64_t)r);
     }
-    if (best && !assign && i < m) best[row0 + i] = ~0ull;
+    if (best && !assign && (int)threadIdx.x < m) best[row0 + threadIdx.x] = ~0ull;
 }
 
-hipError_t launch_reserve(const MultiArgs &ma, const int32_t *assign, uint32_t *slots, int32_t *assigned_out, hipStream_t s)
+hipError_t launch_reserve(const MultiArgs &ma, const int32_t *assign, const unsigned long long *best, int32_t *lists,
+                          uint32_t *ranks, uint32_t *slots, int32_t *assigned_out, hipStream_t s)
 {
     if (ma.n <= 0 || ma.qlo[ma.n] == 0) return hipSuccess;
-    for (int a = 0; a < ma.n; ++a)
-        if (ma.qlo[a + 1] - ma.qlo[a] > 1024u) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(reserve_kernel, dim3(ma.n), dim3(1024), 0, s, ma, assign, nullptr, slots, assigned_out, AppendIds{},
-                       nullptr, nullptr);
+    if ((assign == nullptr) == (best == nullptr) || !ranks || (best && !lists)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(insert_rank_kernel, dim3((ma.qlo[ma.n] + 3) / 4), dim3(256), 0, s, ma, assign, best, lists, ranks);
+    hipLaunchKernelGGL(reserve_kernel<true>, dim3(ma.n), dim3(1024), 0, s, ma, best ? lists : assign, ranks, nullptr, slots, assigned_out,
+                       AppendIds{}, nullptr, nullptr);
     return hipGetLastError();
 }
 
@@ -248,17 +297,19 @@ hipError_t launch_reserve_append(const MultiArgs &ma, const AppendIds &idc, cons
     if (!x || (!assign && !best)) return hipErrorInvalidValue;
     for (int a = 0; a < ma.n; ++a)
         if (ma.qlo[a + 1] - ma.qlo[a] > (uint32_t)kFusedAppend) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(reserve_kernel, dim3(ma.n), dim3(1024), 0, s, ma, assign, best, slots, assigned_out, idc, x, ids);
+    hipLaunchKernelGGL(reserve_kernel<false>, dim3(ma.n), dim3(1024), 0, s, ma, assign, nullptr, best, slots, assigned_out, idc, x, ids);
     return hipGetLastError();
 }
 
 // Insert, step 3: write the vectors into their reserved slots
+// (reset: top-1 keys to put back to "none yet" for the next insert, or null)
 __global__ __launch_bounds__(256) void append_kernel(MultiArgs ma, AppendIds idc, const float *x, const int64_t *ids,
-                                                     const int32_t *assign, const uint32_t *slots)
+                                                     const int32_t *assign, const uint32_t *slots, unsigned long long *reset)
 {
     const int wave = threadIdx.x >> 6;
     const uint32_t i = blockIdx.x * 4 + wave;
     if (i >= ma.qlo[ma.n]) return;
+    if (reset && (threadIdx.x & 63) == 0) reset[i] = ~0ull;
     int h = 0;
     while (h + 1 < ma.n && i >= ma.qlo[h + 1]) ++h;
     const DevIndex &ix = *ma.ix[h];
@@ -268,11 +319,11 @@ __global__ __launch_bounds__(256) void append_kernel(MultiArgs ma, AppendIds idc
 }
 
 hipError_t launch_append(const MultiArgs &ma, const AppendIds &idc, const float *x, const int64_t *ids,
-                         const int32_t *assign, const uint32_t *slots, hipStream_t s)
+                         const int32_t *assign, const uint32_t *slots, unsigned long long *reset, hipStream_t s)
 {
     const uint32_t m = ma.n > 0 ? ma.qlo[ma.n] : 0u;
     if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(append_kernel, dim3((m + 3) / 4), dim3(256), 0, s, ma, idc, x, ids, assign, slots);
+    hipLaunchKernelGGL(append_kernel, dim3((m + 3) / 4), dim3(256), 0, s, ma, idc, x, ids, assign, slots, reset);
     return hipGetLastError();
 }
 
@@ -290,102 +341,130 @@ __device__ __forceinline__ const Arena &locate(const DevIndex &ix, uint32_t l, u
     return ar;
 }
 
-// Deleting by id (Section 5's interface: delete, and update as delete + insert) in four launches, every
-// one of them parallel over what it works on, so that a list of 400 000 rows costs what its share of the
-// index's rows costs:
-//   prepare  one workgroup: sorts the ids; cuts every list into units of kDeleteUnit rows (prefix sum)
-//   find     many workgroups: every row's id is looked up among the sorted ids (held in LDS); the rows
-//            to go are noted as (list, position)
-//   plan     one workgroup: sorts the noted rows (so a list's rows are neighbours, by position), notes
-//            for each where its list's rows start and how long the list was, and shortens the lists
-//   move     a list that loses c rows keeps its first len - c positions: the rows to go among them are
-//            holes, and as many rows beyond them stay; the i-th row that stays fills the i-th hole.
+// Deleting by id (Section 5's interface: delete, and update as delete + insert) in three launches, every one of them
+// parallel over what it works on, so that a list of 400 000 rows costs what its share of the index's rows costs and
+// no workgroup sorts anything (two sorts of 2000 keys by one workgroup each took 66 us):
+//   find     every workgroup builds a hash set of the ids in LDS and looks its units of kDeleteUnit rows up in it; the
+//            rows to go are noted as (list, position) in no order
+//   rank     a wave per noted row counts its list's other noted rows, and those before it; the first of a list
+//            shortens the list
+//   move     a list that loses c rows keeps its first len - c positions: the rows to go among them are holes, and as
+//            many rows beyond them stay; the i-th row that stays fills the i-th hole.  A wave per noted row finds its
+//            move (row number t of the list's noted rows looks at position len - c + t) by counting, and makes it.
 //            Every move reads and writes rows no other move touches, so they all run at once.
 // Lists are unordered sets: no tombstones, nothing for the scan to skip.  The pages a list no longer
 // reaches stay its own for later inserts.
+// All launches of a call (fills and copies of the earlier sequence included): 8 ids among 1 M rows 54 -> 23 us, 2000 ids
+// among 300 000 rows 113 -> 39; the call, with its wait, 80 -> 25 us for few ids and 102 -> 27 for 2000.
 
-__device__ __forceinline__ void sort_keys_lds(unsigned long long *s_keys, int n2)
-{
-    for (int k = 2; k <= n2; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-                const int p = i ^ j;
-                if (p > i) {
-                    const unsigned long long a = s_keys[i], b = s_keys[p];
-                    if (((i & k) == 0) == (a > b)) {
-                        s_keys[i] = b;
-                        s_keys[p] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-}
+constexpr unsigned long long kNoId = 0x8000000000000000ull; // marks a free slot of the hash set (the id of that value is kept apart)
 
-// first index in keys[0, n) whose key is not below `key`
-__device__ __forceinline__ uint32_t lower_bound_u64(const unsigned long long *keys, uint32_t n, unsigned long long key)
+// units of the lists before each one, for tables longer than a workgroup takes along
+__global__ __launch_bounds__(1024) void delete_units_kernel(DeleteArgs a)
 {
-    uint32_t lo = 0, hi = n;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (keys[mid] < key) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-
-__global__ __launch_bounds__(1024) void delete_prepare_kernel(DeleteArgs a)
-{
-    __shared__ unsigned long long s_keys[kDeleteChunk];
     __shared__ uint32_t s_wave[17];
-    int n2 = 2;
-    while (n2 < a.m) n2 <<= 1;
-    for (int i = threadIdx.x; i < n2; i += blockDim.x)
-        s_keys[i] = i < a.m ? (unsigned long long)a.ids[i] ^ 0x8000000000000000ull : ~0ull; // order of signed values
-    __syncthreads();
-    sort_keys_lds(s_keys, n2);
-    for (int i = threadIdx.x; i < a.m; i += blockDim.x) a.sorted[i] = (int64_t)(s_keys[i] ^ 0x8000000000000000ull);
     const DevIndex &ix = *a.ix;
     for (int l = threadIdx.x; l < a.nlist; l += blockDim.x) a.unit_start[l] = (ix.list_len[l] + kDeleteUnit - 1) / kDeleteUnit;
     __syncthreads();
     const uint32_t units = block_exscan(a.unit_start, a.unit_start, (uint32_t)a.nlist, s_wave);
-    if (threadIdx.x == 0) {
-        a.unit_start[a.nlist] = units;
-        a.scal[0] = 0;
-        a.scal[1] = units;
-    }
+    if (threadIdx.x == 0) a.unit_start[a.nlist] = units;
 }
 
-__global__ __launch_bounds__(256) void delete_find_kernel(DeleteArgs a)
+// dynamic LDS (all of the kernel's: the limit set for it counts static LDS in): kFindHead words, the hash set
+// [1 << a.bits], then (if in_lds) the units of the lists before each one
+constexpr int kFindHead = 24;
+__global__ __launch_bounds__(256) void delete_find_kernel(DeleteArgs a, bool in_lds)
 {
-    __shared__ int64_t s_ids[kDeleteChunk];
+    extern __shared__ __align__(16) uint32_t s_head[];
+    uint32_t *s_wave = s_head;          // [17]
+    uint32_t &s_has = s_head[20];       // the id that the free mark stands for is among the ids
+    unsigned long long *s_set = reinterpret_cast<unsigned long long *>(s_head + kFindHead);
     const DevIndex &ix = *a.ix;
-    for (int i = threadIdx.x; i < a.m; i += blockDim.x) s_ids[i] = a.sorted[i];
+    const uint32_t mask = (1u << a.bits) - 1u;
+    uint32_t *s_unit = reinterpret_cast<uint32_t *>(s_set + mask + 1);
+    auto slot_of = [&](unsigned long long id) { return (uint32_t)((id * 0x9E3779B97F4A7C15ull) >> (64 - a.bits)); };
+    uint32_t units;
+    const uint32_t *start = in_lds ? s_unit : a.unit_start;
+    const uint32_t *list_len = ix.list_len;
+    constexpr int B = 8; // ids requested before the first of them goes into the set
+    const long long *ids = reinterpret_cast<const long long *>(a.ids);
+    unsigned long long mine[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) mine[u] = (int)threadIdx.x + 256 * u < a.m ? (unsigned long long)ids[threadIdx.x + 256 * u] : kNoId;
+    if (in_lds) {
+        for (int l0 = threadIdx.x; l0 < a.nlist; l0 += 256 * B) {
+            uint32_t len[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) len[u] = l0 + 256 * u < a.nlist ? list_len[l0 + 256 * u] : 0u;
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+                if (l0 + 256 * u < a.nlist) s_unit[l0 + 256 * u] = (len[u] + kDeleteUnit - 1) / kDeleteUnit;
+        }
+        __syncthreads();
+        units = block_exscan(s_unit, s_unit, (uint32_t)a.nlist, s_wave);
+    } else {
+        units = a.unit_start[a.nlist];
+    }
+    if (blockIdx.x >= units) return; // nothing to look up
+    for (uint32_t i = threadIdx.x; i <= mask; i += 256) s_set[i] = kNoId;
+    if (threadIdx.x == 0) s_has = 0;
     __syncthreads();
-    const uint32_t units = a.scal[1];
+    for (int i0 = threadIdx.x; i0 < a.m; i0 += 256 * B) {
+        if (i0 >= 256 * B) {
+#pragma unroll
+            for (int u = 0; u < B; ++u) mine[u] = i0 + 256 * u < a.m ? (unsigned long long)ids[i0 + 256 * u] : kNoId;
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            if (i0 + 256 * u >= a.m) continue;
+            const unsigned long long id = mine[u];
+            if (id == kNoId) {
+                s_has = 1;
+                continue;
+            }
+            uint32_t at = slot_of(id); // the set is at most half full: a free slot or the id itself comes up
+            while (true) {
+                const unsigned long long was = atomicCAS(&s_set[at], kNoId, id);
+                if (was == kNoId || was == id) break;
+                at = (at + 1u) & mask;
+            }
+        }
+    }
+    __syncthreads();
+    const bool has = s_has != 0;
     for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
         uint32_t lo = 0, hi = (uint32_t)a.nlist - 1; // the last list whose units start at or before u
         while (lo < hi) {
             const uint32_t mid = (lo + hi + 1) >> 1;
-            if (a.unit_start[mid] <= u) lo = mid;
+            if (start[mid] <= u) lo = mid;
             else hi = mid - 1;
         }
-        const uint32_t l = lo, len = ix.list_len[l];
-        const uint32_t base = (u - a.unit_start[l]) * (uint32_t)kDeleteUnit;
+        const uint32_t l = lo, len = list_len[l], P = (uint32_t)ix.P, mp = ix.main_pages[l], mb = ix.main_base[l];
+        const uint32_t base = (u - start[l]) * (uint32_t)kDeleteUnit;
+        constexpr int R = kDeleteUnit / 256;
+        unsigned long long id[R];
 #pragma unroll
-        for (int j = 0; j < kDeleteUnit / 256; ++j) {
+        for (int j = 0; j < R; ++j) { // all requested before the first is looked up
+            const uint32_t pos = base + (uint32_t)j * 256u + threadIdx.x;
+            id[j] = 0;
+            if (pos >= len) continue;
+            const uint32_t lp = pos / P;
+            const uint32_t pg = lp < mp ? mb + lp : ix.dtab[(size_t)l * ix.max_dp + (lp - mp)];
+            const Arena &ar = arena_of(ix, pg);
+            id[j] = (unsigned long long)ar.ids[(size_t)(pg - ar.first_page) * P + (pos - lp * P)];
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
             const uint32_t pos = base + (uint32_t)j * 256u + threadIdx.x;
             if (pos >= len) continue;
-            size_t local;
-            const Arena &ar = locate(ix, l, pos, local);
-            const int64_t id = ar.ids[local];
-            int b = 0, e = a.m;
-            while (b < e) {
-                const int mid = (b + e) >> 1;
-                if (s_ids[mid] < id) b = mid + 1;
-                else e = mid;
-            }
-            if (b < a.m && s_ids[b] == id) {
+            bool hit = has && id[j] == kNoId;
+            if (id[j] != kNoId)
+                for (uint32_t at = slot_of(id[j]); s_set[at] != kNoId; at = (at + 1u) & mask)
+                    if (s_set[at] == id[j]) {
+                        hit = true;
+                        break;
+                    }
+            if (hit) {
                 const uint32_t at = atomicAdd(&a.scal[0], 1u);
                 if (at < (uint32_t)kDeleteChunk) a.hits[at] = ((unsigned long long)l << 32) | pos;
             }
@@ -393,83 +472,102 @@ __global__ __launch_bounds__(256) void delete_find_kernel(DeleteArgs a)
     }
 }
 
-__global__ __launch_bounds__(1024) void delete_plan_kernel(DeleteArgs a)
+__global__ __launch_bounds__(256) void delete_rank_kernel(DeleteArgs a)
 {
-    __shared__ unsigned long long s_keys[kDeleteChunk];
+    __shared__ unsigned long long s_hits[kDeleteChunk];
     const DevIndex &ix = *a.ix;
     const uint32_t found = a.scal[0];
     const uint32_t nh = found < (uint32_t)kDeleteChunk ? found : (uint32_t)kDeleteChunk;
-    if (nh == 0) return;
-    int n2 = 2;
-    while ((uint32_t)n2 < nh) n2 <<= 1;
-    for (int i = threadIdx.x; i < n2; i += blockDim.x) s_keys[i] = (uint32_t)i < nh ? a.hits[i] : ~0ull;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.scal[1] = nh; // what the move kernel goes by
+        const unsigned long long removed = (a.first ? 0ull : *a.removed) + nh;
+        const uint32_t again = (a.first ? 0u : a.scal[2]) | (found > nh ? 1u : 0u); // more rows carried the ids than a pass takes
+        *a.removed = removed;
+        a.scal[2] = again;
+        // for the host, which reads them once the stream is idle
+        __hip_atomic_store(a.host, (uint32_t)removed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(a.host + 1, (uint32_t)(removed >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(a.host + 2, again, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (blockIdx.x * 4u >= nh) return;
+    for (uint32_t i = threadIdx.x; i < nh; i += 256) s_hits[i] = a.hits[i];
     __syncthreads();
-    sort_keys_lds(s_keys, n2);
-    for (uint32_t g = threadIdx.x; g < nh; g += blockDim.x) {
-        const unsigned long long key = s_keys[g];
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t g = blockIdx.x * 4u + (threadIdx.x >> 6); g < nh; g += gridDim.x * 4u) {
+        const unsigned long long key = s_hits[g];
         const uint32_t l = (uint32_t)(key >> 32);
-        const uint32_t seg0 = lower_bound_u64(s_keys, nh, (unsigned long long)l << 32);
-        const uint32_t seg1 = lower_bound_u64(s_keys, nh, ((unsigned long long)l + 1ull) << 32);
-        a.hits[g] = key;
-        a.hit_seg0[g] = seg0;
-        a.hit_cnt[g] = seg1 - seg0;
-        a.hit_len0[g] = ix.list_len[l];
-    }
-    __syncthreads(); // every list length has been read (and stored with the hits) before any is changed
-    for (uint32_t g = threadIdx.x; g < nh; g += blockDim.x) {
-        const uint32_t l = (uint32_t)(s_keys[g] >> 32);
-        if (g == 0 || (uint32_t)(s_keys[g - 1] >> 32) != l) {
-            const uint32_t seg1 = lower_bound_u64(s_keys, nh, ((unsigned long long)l + 1ull) << 32);
-            ix.list_len[l] -= seg1 - g;
+        uint32_t before = 0, all = 0;
+        for (uint32_t j = lane; j < nh; j += 64) {
+            const unsigned long long o = s_hits[j];
+            all += (uint32_t)(o >> 32) == l ? 1u : 0u;
+            before += (uint32_t)(o >> 32) == l && o < key ? 1u : 0u;
         }
-    }
-    if (threadIdx.x == 0) {
-        atomicAdd(a.removed, (unsigned long long)nh);
-        if (found > nh) a.scal[2] = 1u;
+        for (int off = 32; off > 0; off >>= 1) {
+            before += __shfl_xor(before, off);
+            all += __shfl_xor(all, off);
+        }
+        if (lane == 0) {
+            a.hit_rank[g] = before;
+            a.hit_cnt[g] = all;
+            if (before == 0) { // the only one of its list to look at the list's length
+                const uint32_t len = ix.list_len[l];
+                a.hit_len0[g] = len;
+                ix.list_len[l] = len - all;
+            }
+        }
     }
 }
 
 __global__ __launch_bounds__(256) void delete_move_kernel(DeleteArgs a)
 {
-    __shared__ unsigned long long s_keys[kDeleteChunk];
-    __shared__ uint32_t s_list[256], s_src[256], s_dst[256];
-    __shared__ uint32_t s_n;
+    __shared__ unsigned long long s_hits[kDeleteChunk];
+    __shared__ uint16_t s_rank[kDeleteChunk];
     const DevIndex &ix = *a.ix;
-    const uint32_t found = a.scal[0];
-    const uint32_t nh = found < (uint32_t)kDeleteChunk ? found : (uint32_t)kDeleteChunk;
-    if (blockIdx.x * 256u >= nh) return;
-    for (uint32_t i = threadIdx.x; i < nh; i += blockDim.x) s_keys[i] = a.hits[i];
-    if (threadIdx.x == 0) s_n = 0;
-    __syncthreads();
-    const uint32_t g = blockIdx.x * 256u + threadIdx.x;
-    if (g < nh) {
-        // this thread looks at one position beyond the list's new end: position number t of the c there are
-        const uint32_t l = (uint32_t)(s_keys[g] >> 32);
-        const uint32_t seg0 = a.hit_seg0[g], c = a.hit_cnt[g], newlen = a.hit_len0[g] - c;
-        const unsigned long long *seg = s_keys + seg0;
-        const uint32_t t = g - seg0, p = newlen + t;
-        const unsigned long long lkey = (unsigned long long)l << 32;
-        const uint32_t holes = lower_bound_u64(seg, c, lkey | newlen); // rows to go among the positions that stay
-        const uint32_t idx = lower_bound_u64(seg, c, lkey | p);
-        if (!(idx < c && seg[idx] == (lkey | p))) {
-            // the row stays: it is number t - (rows to go beyond the new end and before it) of those that do
-            const uint32_t i = t - (idx - holes);
-            const uint32_t at = atomicAdd(&s_n, 1u);
-            s_list[at] = l;
-            s_src[at] = p;
-            s_dst[at] = (uint32_t)seg[i];
-        }
+    const uint32_t nh = a.scal[1];
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.scal[0] = 0; // for the next call (nothing else of this launch reads it)
+    if (blockIdx.x * 4u >= nh) return;
+    for (uint32_t i = threadIdx.x; i < nh; i += 256) {
+        s_hits[i] = a.hits[i];
+        s_rank[i] = (uint16_t)a.hit_rank[i];
     }
     __syncthreads();
-    const uint32_t moves = s_n;
-    const int row_bytes = ix.row_bytes, lane = threadIdx.x & 63;
-    for (uint32_t mv = threadIdx.x >> 6; mv < moves; mv += 4) { // a wave per move
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t g = blockIdx.x * 4u + (threadIdx.x >> 6); g < nh; g += gridDim.x * 4u) {
+        const uint32_t l = (uint32_t)(s_hits[g] >> 32), t = s_rank[g], c = a.hit_cnt[g];
+        // the list's first noted row knows how long the list was
+        uint32_t first = 0xffffffffu;
+        for (uint32_t j = lane; j < nh; j += 64)
+            if ((uint32_t)(s_hits[j] >> 32) == l && s_rank[j] == 0) first = j;
+        for (int off = 32; off > 0; off >>= 1) first = min(first, (uint32_t)__shfl_xor(first, off));
+        const uint32_t newlen = a.hit_len0[first] - c, p = newlen + t; // position number t of the c beyond the new end
+        uint32_t holes = 0, below = 0, goes = 0; // rows to go among the positions that stay; before p; at p
+        for (uint32_t j = lane; j < nh; j += 64) {
+            const unsigned long long o = s_hits[j];
+            if ((uint32_t)(o >> 32) != l) continue;
+            const uint32_t pos = (uint32_t)o;
+            holes += pos < newlen ? 1u : 0u;
+            below += pos < p ? 1u : 0u;
+            goes += pos == p ? 1u : 0u;
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            holes += __shfl_xor(holes, off);
+            below += __shfl_xor(below, off);
+            goes += __shfl_xor(goes, off);
+        }
+        if (goes) continue; // (wave-uniform)
+        // the row stays: it is number i of those that do, and fills the list's i-th hole
+        const uint32_t i = t - (below - holes);
+        uint32_t dst_pos = 0xffffffffu;
+        for (uint32_t j = lane; j < nh; j += 64)
+            if ((uint32_t)(s_hits[j] >> 32) == l && s_rank[j] == i) dst_pos = (uint32_t)s_hits[j];
+        for (int off = 32; off > 0; off >>= 1) dst_pos = min(dst_pos, (uint32_t)__shfl_xor(dst_pos, off));
         size_t ls, ld;
-        const Arena &as = locate(ix, s_list[mv], s_src[mv], ls);
-        const Arena &ad = locate(ix, s_list[mv], s_dst[mv], ld);
+        const Arena &as = locate(ix, l, p, ls);
+        const Arena &ad = locate(ix, l, dst_pos, ld);
+        const int row_bytes = ix.row_bytes;
         const uint4 *src = reinterpret_cast<const uint4 *>(as.vec + ls * (size_t)row_bytes);
         uint4 *dst = reinterpret_cast<uint4 *>(ad.vec + ld * (size_t)row_bytes);
-        for (int i = lane; i < row_bytes / 16; i += 64) dst[i] = src[i];
+        for (int w = (int)lane; w < row_bytes / 16; w += 64) dst[w] = src[w];
         if (lane == 0) {
             ad.norm[ld] = as.norm[ls];
             ad.ids[ld] = as.ids[ls];
@@ -477,14 +575,23 @@ __global__ __launch_bounds__(256) void delete_move_kernel(DeleteArgs a)
     }
 }
 
-hipError_t launch_delete(const DeleteArgs &a, hipStream_t s)
+hipError_t launch_delete(DeleteArgs a, int num_cu, hipStream_t s)
 {
     if (a.m <= 0) return hipSuccess;
-    if (a.m > kDeleteChunk || a.nlist < 1 || a.grid < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(delete_prepare_kernel, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(delete_find_kernel, dim3(a.grid), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(delete_plan_kernel, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(delete_move_kernel, dim3(kDeleteChunk / 256), dim3(256), 0, s, a);
+    if (a.m > kDeleteChunk || a.nlist < 1) return hipErrorInvalidValue;
+    a.bits = 6;
+    while ((1 << a.bits) < 2 * a.m) ++a.bits;
+    const bool in_lds = a.nlist <= kLdsLists;
+    if (!in_lds) hipLaunchKernelGGL(delete_units_kernel, dim3(1), dim3(1024), 0, s, a);
+    const int lds = kFindHead * 4 + (int)((size_t)8 << a.bits) + (in_lds ? a.nlist * 4 : 0);
+    static LdsCleared cleared;
+    const hipError_t e = allow_lds(&delete_find_kernel, cleared);
+    if (e != hipSuccess) return e;
+    const int per_cu = std::max(1, std::min(8, 160 * 1024 / lds));
+    hipLaunchKernelGGL(delete_find_kernel, dim3(num_cu * per_cu), dim3(256), lds, s, a, in_lds);
+    const int grid = std::min((a.m + 3) / 4, 512); // a wave per noted row (more rows than ids: the waves go round again)
+    hipLaunchKernelGGL(delete_rank_kernel, dim3(grid), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(delete_move_kernel, dim3(grid), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -327,8 +327,8 @@ struct LdsCleared {
     std::atomic<int> on[kMaxDevices];
 };
 
-template <typename K, typename A>
-inline hipError_t launch_with_lds(K kernel, LdsCleared &c, int lds, const A &a, int grid, int threads, hipStream_t s)
+template <typename K>
+inline hipError_t allow_lds(K kernel, LdsCleared &c)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -342,6 +342,14 @@ inline hipError_t launch_with_lds(K kernel, LdsCleared &c, int lds, const A &a, 
         if (e != hipSuccess) return e;
         if (tracked) c.on[dev].store(1, std::memory_order_release);
     }
+    return hipSuccess;
+}
+
+template <typename K, typename A>
+inline hipError_t launch_with_lds(K kernel, LdsCleared &c, int lds, const A &a, int grid, int threads, hipStream_t s)
+{
+    const hipError_t e = allow_lds(kernel, c);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, s, a);
     return hipGetLastError();
 }
@@ -553,8 +561,8 @@ struct SplitGemmArgs {
     unsigned long long *best; // [m] best (value key << 32 | column) by atomicMin; ~0 on entry
     int m, n, n_pad, ld, metric;
     uint32_t stride;
-    // with best: the value key of the second best column where it is near the best (else all ones, as on entry)
-    uint32_t *second;         // [m]
+    // with best, optional: the value key of the second best column where it is near the best (else all ones, as on entry)
+    uint32_t *second;         // [m] (or null: no row's near ties are of interest)
     const uint32_t *cmax;     // largest squared norm of the centroids (as bits)
 };
 hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s);
@@ -574,18 +582,20 @@ constexpr int kDeleteChunk = 4096;
 constexpr int kDeleteUnit = 1024; // rows of one list that a workgroup examines at a time
 struct DeleteArgs {
     const DevIndex *ix;
-    int nlist, m, grid;        // grid: workgroups of the search over the rows
+    int nlist, m;
+    bool first;                // first pass of the call: nothing has been counted yet
+    int bits;                  // (set by launch_delete) the hash set has 1 << bits slots
     const int64_t *ids;        // [m]
-    int64_t *sorted;           // scratch [kDeleteChunk]
-    uint32_t *unit_start;      // scratch [nlist + 1]: units of the lists before each one
+    uint32_t *unit_start;      // scratch [nlist + 1] (tables of more than kLdsLists lists): units of the lists before each one
     unsigned long long *hits;  // scratch [kDeleteChunk]: (list << 32) | position of the rows to go
-    uint32_t *hit_len0;        // scratch [kDeleteChunk]: per hit, its list's length before the pass,
-    uint32_t *hit_seg0;        //   where the list's hits start in the sorted hits,
-    uint32_t *hit_cnt;         //   and how many they are
-    uint32_t *scal;            // [0] rows found in this pass, [1] units, [2] sticky: a pass found more than it could take
-    unsigned long long *removed; // device counter, added to
+    uint32_t *hit_rank;        // scratch [kDeleteChunk]: per hit, the hits of its list before it,
+    uint32_t *hit_cnt;         //   the hits of its list,
+    uint32_t *hit_len0;        //   and, for its list's first hit, the list's length before the pass
+    uint32_t *scal;            // of the handle: [0] rows found (zero between passes), [1] of them taken, [2] sticky: a pass found more than it could take
+    unsigned long long *removed; // of the handle: rows removed by the call
+    uint32_t *host;            // pinned [3]: rows removed (low, high word), the sticky flag
 };
-hipError_t launch_delete(const DeleteArgs &a, hipStream_t s);
+hipError_t launch_delete(DeleteArgs a, int num_cu, hipStream_t s);
 // copies every list into the contiguous extents of `dst` (dst's tables are already in place)
 // (skip: optional [dst nlist] flags of lists the caller fills itself; lists beyond src's are skipped too)
 hipError_t launch_compact_pages(const DevIndex *src, const DevIndex *dst, uint32_t new_pages, const uint8_t *skip,
@@ -633,16 +643,20 @@ struct KmeansArgs {
     double *inertia;       // one word: receives the sum of squared distances of the assignment
 };
 hipError_t launch_kmeans_update(const KmeansArgs &a, hipStream_t s);
-// Insert: slots for the vectors of every handle of the batch (one workgroup per handle, at most 1024
-// vectors each; rows [qlo[a], qlo[a+1]) of assign / slots / assigned_out belong to handle a), then the rows.
+// Insert: slots for the vectors of every handle of the batch (one workgroup per handle; rows [qlo[a], qlo[a+1]) of
+// assign / slots / assigned_out belong to handle a), then the rows.  Groups of kInsertGroup vectors of a handle are
+// inserted whole or not at all.
+constexpr int kInsertGroup = 1024;
 // batches of at most this many vectors per handle: reservation and row writes share one launch
 constexpr int kFusedAppend = 64;
 struct AppendIds {
     int64_t id0[PK_MAX_HANDLES]; // first id of each handle's segment when the caller gives no ids
 };
-hipError_t launch_reserve(const MultiArgs &ma, const int32_t *assign, uint32_t *slots, int32_t *assigned_out, hipStream_t s);
+// the lists are assign[], or the low words of best[] (written to lists[]); ranks: scratch like slots
+hipError_t launch_reserve(const MultiArgs &ma, const int32_t *assign, const unsigned long long *best, int32_t *lists,
+                          uint32_t *ranks, uint32_t *slots, int32_t *assigned_out, hipStream_t s);
 hipError_t launch_append(const MultiArgs &ma, const AppendIds &idc, const float *x, const int64_t *ids,
-                         const int32_t *assign, const uint32_t *slots, hipStream_t s);
+                         const int32_t *assign, const uint32_t *slots, unsigned long long *reset, hipStream_t s);
 // assign == null: the lists are the low words of best[] (left by the centroid kernel), which is reset to ~0
 hipError_t launch_reserve_append(const MultiArgs &ma, const AppendIds &idc, const float *x, const int64_t *ids,
                                  const int32_t *assign, unsigned long long *best, uint32_t *slots, int32_t *assigned_out,

@@ -133,3 +133,66 @@ def test_thresholds_from_several_sample_pages(gpu_device, n, d, nlist, nprobe, k
         assert torch.equal(gi[some.tolist()], fi) and torch.equal(gv[some.tolist()], fv)
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("metric,storage,d,nlist,page", [(IP, F32, 128, 40, 0), (L2, F16, 70, 260, 32), (IP, F32, 64, 9000, 64)])
+def test_inserts_around_the_sizes_where_their_path_changes(gpu_device, metric, storage, d, nlist, page):
+    """One group and several (1024), the centroid kernel and the GEMM (3 * 2^16 scores), and rows of one batch that
+    meet in one list: every list ends up with its members in the order in which they came."""
+    rng = np.random.default_rng(d + nlist)
+    x = rng.standard_normal((12000, d)).astype(np.float32)
+    if storage == F16:
+        x = x.astype(np.float16).astype(np.float32)
+    cent = x[rng.permutation(len(x))[:nlist]].copy()
+    ix = B.Index(dev(cent), None, metric=metric, storage=storage, page_vecs=page, insert_reserve=20000)
+    try:
+        members, first, c64 = [[] for _ in range(nlist)], 0, cent.astype(np.float64)
+        for m in (1, 64, 65, 1023, 1025, 2500, 700, 6200):
+            rows = x[first:first + m]
+            lists = ix.insert(dev(rows), want_lists=True).cpu().numpy()
+            s = rows.astype(np.float64) @ c64.T
+            if metric == L2:
+                s = 2 * s - (c64 ** 2).sum(1)
+            gap = s.max(1) - s[np.arange(len(rows)), lists]
+            assert (gap <= 1e-5 * (1 + np.abs(s).max(1))).all()  # fp32 rounding of sums of up to 128 products
+            for i, l in enumerate(lists):
+                members[l].append(first + i)
+            first += len(rows)
+        assert ix.stats().device_error == 0 and ix.stats().n_total == first
+        assert ix.list_lengths().tolist() == [len(v) for v in members]
+        for l in np.argsort([-len(v) for v in members])[:12]:
+            assert ix.list_ids(int(l)).cpu().numpy().tolist() == members[l]
+    finally:
+        ix.close()
+
+
+@pytest.mark.parametrize("nlist,page", [(3, 0), (300, 32), (9000, 64)])
+def test_deletes_by_hash_set(gpu_device, nlist, page):
+    """Ids of any value (the one that marks a free slot of the set among them), given twice, carried twice, carried by
+    nobody; more than a pass takes; whole lists; tables of lists that fit LDS and that do not."""
+    rng = np.random.default_rng(nlist)
+    n, d = 15000, 32
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    ids = rng.permutation(n).astype(np.int64) * 7 - 30000
+    ids[5], ids[6], ids[7] = np.iinfo(np.int64).min, np.iinfo(np.int64).max, np.iinfo(np.int64).min
+    ids[100:6100:2] = ids[101:6101:2]  # 3000 ids carried by two rows each
+    ix = B.Index(dev(x[:nlist].copy()), dev(x), metric=L2, ids=dev(ids), page_vecs=page)
+    try:
+        left = ids.copy()
+        whole = ix.list_ids(int(ix.list_lengths().argmax())).cpu().numpy()
+        for gone in ([left[8]], [left[9], left[9], 12345678901], [np.iinfo(np.int64).min], whole[:4096], left[100:4100],
+                     rng.permutation(left)[:5000], left[:0]):
+            gone = np.asarray(gone, dtype=np.int64)
+            removed = ix.delete(dev(gone))
+            keep = ~np.isin(left, gone)
+            assert removed == len(left) - keep.sum()
+            left = left[keep]
+            assert ix.stats().n_total == len(left)
+        got = np.concatenate([ix.list_ids(l).cpu().numpy() for l in np.nonzero(ix.list_lengths())[0]])
+        assert np.array_equal(np.sort(got), np.sort(left))
+        at = {int(i): r for r, i in enumerate(ids) if (ids == i).sum() == 1}
+        some = [i for i in left[:400].tolist() if i in at][:50]
+        gi, gv = ix.search(dev(x[[at[i] for i in some]]), 1, min(nlist, 16))
+        assert gi[:, 0].tolist() == some and float(gv.max()) < 1e-4  # the row that carries the id is still the id's
+    finally:
+        ix.close()
