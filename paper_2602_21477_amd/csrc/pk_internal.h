@@ -137,6 +137,22 @@ typedef const u32x4 __attribute__((address_space(1))) *gvec4;
 __device__ __forceinline__ gbytes in_global(const char *p) { return (gbytes)p; }
 __device__ __forceinline__ gfloats in_global(const float *p) { return (gfloats)p; }
 
+// Rows are fetched a whole 128-byte line at a time: two loads cover 8 rows x 128 bytes each (lane l: row l & 7, 16-byte
+// piece (l >> 4) + 4 * ((l >> 3) & 1)), and two moves within 16 lanes then put the pieces where MFMA wants them
+// (lane l: row l & 15, piece l >> 4, of the first 64 bytes in a and of the second in b).  That is for the rows' sake that
+// are read once, by non-temporal loads: a bare loop of loads over pages of 1536-byte rows, two workgroups per CU,
+// reads 6.2 TB/s either way with ordinary loads, 5.1 with non-temporal loads of half a line each (the other half is
+// fetched again) and 6.4 - 6.8 with non-temporal loads of whole lines (3072 bytes: 6.0, 5.5, 6.5; 4096: 5.8, 5.7, 6.2).
+__device__ __forceinline__ void line_to_operands(u32x4 &a, u32x4 &b)
+{
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const int x = (int)a[d], y = (int)b[d];
+        a[d] = (uint32_t)__builtin_amdgcn_update_dpp(x, y, 0x128, 0xf, 0xc, false); // lanes 8 .. 15 of 16: y's lanes 0 .. 7
+        b[d] = (uint32_t)__builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false); // lanes 0 .. 7: x's lanes 8 .. 15
+    }
+}
+
 // 16 bytes of a query row (A) against 16 bytes of a stored row (B), fp32 accumulation: one
 // v_mfma_f32_16x16x32_f16, or four v_mfma_f32_16x16x4_f32.  Every kernel that scores a
 // (row, query) pair issues these in the same order over the row, so the value of a pair does
@@ -254,6 +270,7 @@ struct ScanArgs {
     uint32_t *tile_ctr;          // device scalar, zero before the launch: batches handed out after the first round
     int k, use_hist;
     int row_bytes, metric, storage, mq;
+    bool nt;                     // gated mode: the rows are read past the caches (they would not stay in them anyway)
 };
 hipError_t launch_scan(const ScanArgs &a, int grid, hipStream_t s);
 hipError_t launch_scan_ks(const ScanArgs &a, int grid, hipStream_t s);

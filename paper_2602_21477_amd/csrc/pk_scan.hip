@@ -6,14 +6,15 @@
 // plus a group of query slots.  Inserted vectors (Section 4.4's buffer) live in ordinary
 // pages of the list and are scored by the same tiles.
 //
-// Mapping to CDNA4.  The rows are the streaming operand and go HBM -> registers directly
-// in MFMA operand layout; the queries come from LDS.  With A = queries (M = 16 slots) and
-// B = rows (N = 16 rows) the 16x16 accumulator puts rows along lanes, so each store
-// instruction writes 64 contiguous bytes per 16 lanes.  The contraction index may be
-// permuted freely as long as A and B use the same permutation, which lets every lane fetch
-// 16 contiguous bytes per load (4 lanes cover a 64-byte segment of one row, 16 rows per
-// instruction) and feed them straight into v_mfma_f32_16x16x32_f16 (fp16 storage) or four
-// v_mfma_f32_16x16x4_f32 (fp32 storage), always with fp32 accumulation.
+// Mapping to CDNA4.  The rows are the streaming operand and go HBM -> registers; the queries
+// come from LDS.  With A = queries (M = 16 slots) and B = rows (N = 16 rows) the 16x16
+// accumulator puts rows along lanes, so each store instruction writes 64 contiguous bytes per
+// 16 lanes.  The contraction index may be permuted freely as long as A and B use the same
+// permutation, which lets every lane hold 16 contiguous bytes (4 lanes a 64-byte segment of one
+// row, 16 rows per register) and feed them into v_mfma_f32_16x16x32_f16 (fp16 storage) or four
+// v_mfma_f32_16x16x4_f32 (fp32 storage), always with fp32 accumulation.  Rows of memories that
+// the caches hold are fetched that way, straight in operand layout; those of larger ones a whole
+// line at a time and past the caches, and put in that layout by moves between lanes.
 //
 // Two list-scan kernels differ in how the queries reach LDS:
 //   scan_kernel     the whole query group (up to 64 slots x full rows) sits in LDS and is
@@ -135,6 +136,33 @@ __device__ __forceinline__ void load_slots(const ScanArgs &a, const Slots &s, in
         }
     }
 }
+
+// The rows of a scan.  NT: whole lines, past the caches, then into operand layout (line_to_operands); otherwise half lines,
+// straight in operand layout.
+template <bool NT>
+struct RowLoad {
+    // first byte of the lane's part of row `row` of a block of 16
+    static __device__ __forceinline__ gbytes start(gbytes rows, int ln, int lg, int row_bytes)
+    {
+        if constexpr (NT) return rows + (size_t)(ln & 7) * row_bytes + lg * 16 + (ln >> 3) * 64;
+        else return rows + (size_t)ln * row_bytes + lg * 16;
+    }
+    // the s4-th of the four loads of slice `it`
+    static __device__ __forceinline__ u32x4 load(gbytes p, int it, int s4, int row_bytes)
+    {
+        const gbytes at = p + (size_t)it * kIterBytes;
+        if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<gvec4>(at + (size_t)(s4 & 1) * 8 * row_bytes + (s4 >> 1) * 128));
+        else return *reinterpret_cast<gvec4>(at + s4 * 64);
+    }
+    // the four registers of a slice, as MFMA wants them
+    static __device__ __forceinline__ void arrange(u32x4 (&b)[4])
+    {
+        if constexpr (NT) {
+            line_to_operands(b[0], b[1]);
+            line_to_operands(b[2], b[3]);
+        }
+    }
+};
 
 // same query group as the previous tile: pick up bucket limits other workgroups have tightened
 __device__ __forceinline__ void refresh_slot(const ScanArgs &a, const Slots &s, int tid, uint32_t qcnt)
@@ -306,7 +334,7 @@ __device__ __forceinline__ void finish_block(const ScanArgs &a, const Slots &s, 
 // FUSED (threshold sample of a small batch; sm, extra_off given): the workgroup that scores the last of a
 // query's sample tiles goes on to work out that query's threshold, so that no launch of its own is needed
 // for it.  bid / nblk: this workgroup's number among those of the launch that take tiles.
-template <int STORAGE, int MT, int WAVES, bool GATED, bool FUSED>
+template <int STORAGE, int MT, int WAVES, bool GATED, bool FUSED, bool NT>
 __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_t bid, uint32_t nblk, const SampleArgs *sm,
                                           uint32_t extra_off)
 {
@@ -358,15 +386,17 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
         u32x4 xa[2][4], xb[2][4]; // two register buffers of one 256-byte slice of 32 rows each
         gbytes p0, p1;
 #define PK_ROWS(rb)                                                                               \
-    p0 = tx + (size_t)((rb) * kRowBlock + ln) * row_bytes + lg * 16;                              \
+    p0 = RowLoad<NT>::start(tx + (size_t)((rb) * kRowBlock) * row_bytes, ln, lg, row_bytes);       \
     p1 = p0 + (size_t)16 * row_bytes;
 #define PK_LOAD(buf, it)                                                                          \
     _Pragma("unroll") for (int s4 = 0; s4 < 4; ++s4)                                              \
     {                                                                                             \
-        buf[0][s4] = *reinterpret_cast<gvec4>(p0 + (size_t)(it) * kIterBytes + s4 * 64);  \
-        buf[1][s4] = *reinterpret_cast<gvec4>(p1 + (size_t)(it) * kIterBytes + s4 * 64);  \
+        buf[0][s4] = RowLoad<NT>::load(p0, it, s4, row_bytes);                                    \
+        buf[1][s4] = RowLoad<NT>::load(p1, it, s4, row_bytes);                                    \
     }
 #define PK_COMPUTE(buf, it)                                                                       \
+    RowLoad<NT>::arrange(buf[0]);                                                                 \
+    RowLoad<NT>::arrange(buf[1]);                                                                 \
     _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                             \
     {                                                                                             \
         if (mt < mt_used) {                                                                       \
@@ -545,11 +575,11 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
     }
 }
 
-template <int STORAGE, int MT, int WAVES, bool GATED>
+template <int STORAGE, int MT, int WAVES, bool GATED, bool NT>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu((!GATED && MT == 1) ? 2 : 3, 8))) void scan_kernel(ScanArgs a)
 {
     extern __shared__ __align__(16) char smem[];
-    scan_body<STORAGE, MT, WAVES, GATED, false>(a, smem, blockIdx.x, gridDim.x, nullptr, 0u);
+    scan_body<STORAGE, MT, WAVES, GATED, false, NT>(a, smem, blockIdx.x, gridDim.x, nullptr, 0u);
 }
 
 // The threshold sample of a small batch with everything that hangs on it, in one launch.  The first sm.nq
@@ -574,7 +604,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
         PK_MARK(scan, 23);
         return;
     }
-    scan_body<STORAGE, 1, 4, false, true>(a, smem, blockIdx.x - nq, gridDim.x - nq, &sm, extra_off);
+    scan_body<STORAGE, 1, 4, false, true, false>(a, smem, blockIdx.x - nq, gridDim.x - nq, &sm, extra_off);
 }
 
 // ------------------------------------------------------------------ sliced-query kernel
@@ -584,7 +614,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 // the queries (registers, then LDS) is already on its way.  One barrier per slice keeps the
 // four waves of the workgroup in step.  MT up to 4 (64 slots).  Always 4 waves, one 32-row
 // block each per pass over the page.
-template <int STORAGE, int MT, bool GATED>
+template <int STORAGE, int MT, bool GATED, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void scan_ks_kernel(ScanArgs a)
 {
     extern __shared__ __align__(16) char smem[];
@@ -645,8 +675,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
                 const int rb = pass * 4 + wave;
                 // a wave past the end of the page keeps in step (barriers) on the page's first rows
                 const bool active = rb * kRowBlock < nrows;
-                const int row_a = (active ? rb * kRowBlock : 0) + ln;
-                const gbytes p0 = tx + (size_t)row_a * row_bytes + lg * 16;
+                const gbytes p0 = RowLoad<NT>::start(tx + (size_t)(active ? rb * kRowBlock : 0) * row_bytes, ln, lg, row_bytes);
                 const gbytes p1 = p0 + (size_t)16 * row_bytes;
                 f32x4 acc[MT][2];
 #pragma unroll
@@ -660,8 +689,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 #define PK_LOAD(buf, it)                                                                          \
     _Pragma("unroll") for (int s4 = 0; s4 < 4; ++s4)                                              \
     {                                                                                             \
-        buf[0][s4] = *reinterpret_cast<gvec4>(p0 + (size_t)(it) * kIterBytes + s4 * 64);  \
-        buf[1][s4] = *reinterpret_cast<gvec4>(p1 + (size_t)(it) * kIterBytes + s4 * 64);  \
+        buf[0][s4] = RowLoad<NT>::load(p0, it, s4, row_bytes);                                    \
+        buf[1][s4] = RowLoad<NT>::load(p1, it, s4, row_bytes);                                    \
     }
 #define PK_QLOAD(it)                                                                              \
     _Pragma("unroll") for (int j = 0; j < QLOADS; ++j)                                            \
@@ -677,6 +706,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
             *reinterpret_cast<u32x4 *>(qbuf + ((size_t)(b) * MQ + j * 16 + qm) * kKsStride + qpiece) = qr[j]; \
     }
 #define PK_COMPUTE(buf, b)                                                                        \
+    RowLoad<NT>::arrange(buf[0]);                                                                 \
+    RowLoad<NT>::arrange(buf[1]);                                                                 \
     _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                             \
     {                                                                                             \
         if (mt < mt_used) {                                                                       \
@@ -907,40 +938,40 @@ int scan_max_mq(int row_bytes, int storage, int lds_limit)
     return best;
 }
 
-template <int STORAGE, int MT, int WAVES, bool GATED>
+template <int STORAGE, int MT, int WAVES, bool GATED, bool NT>
 static hipError_t launch_one(const ScanArgs &a, int grid, hipStream_t s)
 {
     static LdsCleared cleared;
-    return launch_with_lds(&scan_kernel<STORAGE, MT, WAVES, GATED>, cleared, scan_lds_bytes(a.row_bytes, a.mq), a, grid,
+    return launch_with_lds(&scan_kernel<STORAGE, MT, WAVES, GATED, NT>, cleared, scan_lds_bytes(a.row_bytes, a.mq), a, grid,
                            WAVES * 64, s);
 }
 
-template <int STORAGE, int MT, bool GATED>
+template <int STORAGE, int MT, bool NT>
 static hipError_t launch_ks_one(const ScanArgs &a, int grid, hipStream_t s)
 {
     static LdsCleared cleared;
-    return launch_with_lds(&scan_ks_kernel<STORAGE, MT, GATED>, cleared, scan_ks_lds_bytes(MT * 16), a, grid, 256, s);
+    return launch_with_lds(&scan_ks_kernel<STORAGE, MT, true, NT>, cleared, scan_ks_lds_bytes(MT * 16), a, grid, 256, s);
 }
 
-template <int STORAGE, int WAVES, bool GATED>
+template <int STORAGE, int WAVES, bool GATED, bool NT>
 static hipError_t launch_mt(const ScanArgs &a, int grid, hipStream_t s)
 {
-    if (a.mq >= 1 && a.mq < 16) return launch_one<STORAGE, 1, WAVES, GATED>(a, grid, s);
+    if (a.mq >= 1 && a.mq < 16) return launch_one<STORAGE, 1, WAVES, GATED, NT>(a, grid, s);
     switch (a.mq) {
-    case 16: return launch_one<STORAGE, 1, WAVES, GATED>(a, grid, s);
-    case 32: return launch_one<STORAGE, 2, WAVES, GATED>(a, grid, s);
-    case 64: return launch_one<STORAGE, 4, WAVES, GATED>(a, grid, s);
+    case 16: return launch_one<STORAGE, 1, WAVES, GATED, NT>(a, grid, s);
+    case 32: return launch_one<STORAGE, 2, WAVES, GATED, NT>(a, grid, s);
+    case 64: return launch_one<STORAGE, 4, WAVES, GATED, NT>(a, grid, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-template <int STORAGE, bool GATED>
+template <int STORAGE, bool NT>
 static hipError_t launch_ks_mt(const ScanArgs &a, int grid, hipStream_t s)
 {
     switch (a.mq) {
-    case 16: return launch_ks_one<STORAGE, 1, GATED>(a, grid, s);
-    case 32: return launch_ks_one<STORAGE, 2, GATED>(a, grid, s);
-    case 64: return launch_ks_one<STORAGE, 4, GATED>(a, grid, s);
+    case 16: return launch_ks_one<STORAGE, 1, NT>(a, grid, s);
+    case 32: return launch_ks_one<STORAGE, 2, NT>(a, grid, s);
+    case 64: return launch_ks_one<STORAGE, 4, NT>(a, grid, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -986,18 +1017,19 @@ hipError_t launch_sample_tau(const ScanArgs &a, const SampleArgs &sm, const Work
 hipError_t launch_scan(const ScanArgs &a, int grid, hipStream_t s)
 {
     if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0) return hipErrorInvalidValue;
-    const bool gated = a.tau != nullptr;
-    if (a.storage == PK_F16) return gated ? launch_mt<PK_F16, 4, true>(a, grid, s) : launch_mt<PK_F16, 4, false>(a, grid, s);
-    return gated ? launch_mt<PK_F32, 4, true>(a, grid, s) : launch_mt<PK_F32, 4, false>(a, grid, s);
+    const bool f16 = a.storage == PK_F16;
+    if (a.tau == nullptr) return f16 ? launch_mt<PK_F16, 4, false, false>(a, grid, s) : launch_mt<PK_F32, 4, false, false>(a, grid, s);
+    if (a.nt) return f16 ? launch_mt<PK_F16, 4, true, true>(a, grid, s) : launch_mt<PK_F32, 4, true, true>(a, grid, s);
+    return f16 ? launch_mt<PK_F16, 4, true, false>(a, grid, s) : launch_mt<PK_F32, 4, true, false>(a, grid, s);
 }
 
 // the sliced-query kernel (gated fine search only; fp32 rows are held to 32 slots)
 hipError_t launch_scan_ks(const ScanArgs &a, int grid, hipStream_t s)
 {
     if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || a.tau == nullptr) return hipErrorInvalidValue;
-    if (a.storage == PK_F16) return launch_ks_mt<PK_F16, true>(a, grid, s);
+    if (a.storage == PK_F16) return a.nt ? launch_ks_mt<PK_F16, true>(a, grid, s) : launch_ks_mt<PK_F16, false>(a, grid, s);
     if (a.mq > 32) return hipErrorInvalidValue;
-    return launch_ks_mt<PK_F32, true>(a, grid, s);
+    return a.nt ? launch_ks_mt<PK_F32, true>(a, grid, s) : launch_ks_mt<PK_F32, false>(a, grid, s);
 }
 
 } // namespace pk
