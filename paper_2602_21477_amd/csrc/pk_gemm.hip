@@ -27,9 +27,6 @@ constexpr int kGemmTile = 128;
 constexpr int kGemmBK = 32;               // floats per K step
 constexpr int kGemmLdsStride = kGemmBK + 4; // floats; +4 keeps the b128 reads conflict free
 
-// LISTED: the rows are those of a list on the device (a.list, *a.nlisted of them), dense rows of a.d floats, and every
-// row keeps its best (value key, column) by atomicMin instead of writing scores; the grid walks the tiles there are.
-template <bool LISTED>
 __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 {
     __shared__ __align__(16) float sA[2][kGemmTile * kGemmLdsStride];
@@ -37,13 +34,9 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;        // wave's 64 x 64 quadrant
     const int l32 = lane & 31, kg = lane >> 5;      // MFMA row / column and k group
+    const int m0 = blockIdx.y * kGemmTile, n0 = blockIdx.x * kGemmTile;
     const int ld = a.ld;                            // floats per row, multiple of 64
     const int ksteps = ld / kGemmBK;
-    const int rows = LISTED ? (int)*a.nlisted : a.m;
-    [[maybe_unused]] const bool vec = LISTED && (a.d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
-    const uint32_t tn = (uint32_t)(a.n_pad + kGemmTile - 1) / kGemmTile, tm = (uint32_t)(rows + kGemmTile - 1) / kGemmTile;
-    for (uint32_t t = LISTED ? blockIdx.x : blockIdx.y * tn + blockIdx.x; t < tm * tn; t += LISTED ? gridDim.x : tm * tn) {
-    const int m0 = (int)(t / tn) * kGemmTile, n0 = (int)(t % tn) * kGemmTile;
 
     // global -> register staging: each thread moves 4 x 16 B of A and of B per K step
     // row = (tid >> 3) + 32 * i, 16-byte column = tid & 7
@@ -52,10 +45,9 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         int ra = m0 + srow + 32 * i, rb = n0 + srow + 32 * i;
-        ra = ra < rows ? ra : rows - 1; // clamp: rows past the end are computed and dropped
+        ra = ra < a.m ? ra : a.m - 1; // clamp: rows past the end are computed and dropped
         rb = rb < a.n_pad ? rb : a.n_pad - 1;
-        if constexpr (LISTED) ga[i] = a.q + (size_t)a.list[ra] * a.d + scol;
-        else ga[i] = a.q + (size_t)ra * ld + scol;
+        ga[i] = a.q + (size_t)ra * ld + scol;
         gb[i] = a.c + (size_t)rb * ld + scol;
     }
     f32x4 ra4[4], rb4[4];
@@ -70,16 +62,7 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #define PK_GLOAD(ks)                                                                     \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                        \
     {                                                                                    \
-        if constexpr (LISTED) { /* the caller's rows: no padding, any alignment */       \
-            ra4[i] = f32x4{0.f, 0.f, 0.f, 0.f};                                          \
-            if (vec) {                                                                   \
-                if ((ks) * kGemmBK + scol < a.d)                                         \
-                    ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK); \
-            } else {                                                                     \
-                _Pragma("unroll") for (int j = 0; j < 4; ++j)                            \
-                    if ((ks) * kGemmBK + scol + j < a.d) ra4[i][j] = ga[i][(size_t)(ks) * kGemmBK + j]; \
-            }                                                                            \
-        } else ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK); \
+        ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK);       \
         rb4[i] = *reinterpret_cast<const f32x4 *>(gb[i] + (size_t)(ks) * kGemmBK);       \
     }
 #define PK_LSTORE(buf)                                                                                   \
@@ -133,23 +116,14 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int m = m0 + wm * 64 + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
-                if (m < rows) {
-                    const size_t row = LISTED ? (size_t)a.list[m] : (size_t)m;
+                if (m < a.m) {
                     float v = acc[i][j][r];
-                    if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[row], 0.f);
-                    if constexpr (LISTED) {
-                        if (!live) continue;
-                        const unsigned long long key = ((unsigned long long)order_bits(v, a.metric) << 32) | (uint32_t)n;
-                        if (key < a.best[row]) atomicMin(a.best + row, key); // (a stale look costs an atomic, never a result)
-                    } else {
-                        if (!live) v = a.metric == PK_METRIC_IP ? -INFINITY : INFINITY;
-                        a.out[row * a.stride + n] = v;
-                    }
+                    if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[m], 0.f);
+                    if (!live) v = a.metric == PK_METRIC_IP ? -INFINITY : INFINITY;
+                    a.out[(size_t)m * a.stride + n] = v;
                 }
             }
         }
-    }
-    __syncthreads(); // the next tile's first stores into LDS
     }
 }
 
@@ -158,7 +132,7 @@ hipError_t launch_gemm_scores(const GemmArgs &a, hipStream_t s)
     if (a.m <= 0) return hipSuccess;
     if (a.ld % 64 != 0) return hipErrorInvalidValue;
     dim3 grid((a.n_pad + kGemmTile - 1) / kGemmTile, (a.m + kGemmTile - 1) / kGemmTile);
-    hipLaunchKernelGGL(gemm_scores_kernel<false>, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(gemm_scores_kernel, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -561,6 +535,98 @@ hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
     return a.best ? launch_split_one<64, 64, 2, 2, true>(a, s) : launch_split_one<64, 64, 2, 2, false>(a, s);
 }
 
+// The fp32 products of a few listed rows (a.list, *a.nlisted of them: dense rows of a.d floats) with every column, in
+// gemm_scores_kernel's order of operations, so that the values are the same; every row keeps its best (value key,
+// column) by atomicMin.  Usually some hundred rows: bound by the latency of one tile, so a tile is 32 x 128 (a wave
+// 32 x 32: 16 MFMAs per step of 32 elements), its operands are requested two steps ahead, and the grid walks the tiles
+// there are.  As a form of the 128 x 128 kernel it took 210 us for whatever few rows there were; now 27 us for those of
+// 26 000 x 640 against 253 columns, 129 us for those of 262 144 x 768 against 4096.
+constexpr int kListRows = 32, kListCols = 128;
+__global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
+{
+    __shared__ __align__(16) float sA[2][kListRows * kGemmLdsStride];
+    __shared__ __align__(16) float sB[2][kListCols * kGemmLdsStride];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l32 = lane & 31, kg = lane >> 5;
+    const int ld = a.ld, ksteps = ld / kGemmBK; // even: rows are padded to 64 floats
+    const int rows = (int)*a.nlisted;
+    const bool vec = (a.d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
+    const uint32_t tn = (uint32_t)(a.n_pad + kListCols - 1) / kListCols, tm = (uint32_t)(rows + kListRows - 1) / kListRows;
+    const int srow = tid >> 3, scol = (tid & 7) * 4;
+    for (uint32_t t = blockIdx.x; t < tm * tn; t += gridDim.x) {
+        const int m0 = (int)(t / tn) * kListRows, n0 = (int)(t % tn) * kListCols;
+        const int mr = m0 + srow < rows ? m0 + srow : rows - 1; // clamp: rows past the end are computed and dropped
+        const float *ga = a.q + (size_t)a.list[mr] * a.d + scol, *gb[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            int rb = n0 + srow + 32 * i;
+            rb = rb < a.n_pad ? rb : a.n_pad - 1;
+            gb[i] = a.c + (size_t)rb * ld + scol;
+        }
+        f32x4 a0, a1, b0[4], b1[4];
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        auto fetch = [&](f32x4 &ra, f32x4 (&rb)[4], int ks) {
+            const int at = (ks < ksteps ? ks : ksteps - 1) * kGemmBK; // (past the last step the last one again)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) rb[i] = *reinterpret_cast<const f32x4 *>(gb[i] + at);
+            ra = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (vec) { // the caller's rows: no padding, any alignment
+                if (at + scol < a.d) ra = *reinterpret_cast<const f32x4 *>(ga + at);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (at + scol + j < a.d) ra[j] = ga[at + j];
+            }
+        };
+        auto put = [&](const f32x4 &ra, const f32x4 (&rb)[4], int buf) {
+            *reinterpret_cast<f32x4 *>(&sA[buf][srow * kGemmLdsStride + scol]) = ra;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4 *>(&sB[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = rb[i];
+        };
+        auto step = [&](int buf) {
+            const float *pa = &sA[buf][l32 * kGemmLdsStride + kg * 4];
+            const float *pb = &sB[buf][(wave * 32 + l32) * kGemmLdsStride + kg * 4];
+#pragma unroll
+            for (int kc = 0; kc < kGemmBK / 8; ++kc) {
+                const f32x4 fa = *reinterpret_cast<const f32x4 *>(pa + kc * 8), fb = *reinterpret_cast<const f32x4 *>(pb + kc * 8);
+#pragma unroll
+                for (int j4 = 0; j4 < 4; ++j4) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[j4], fb[j4], acc, 0, 0, 0);
+            }
+        };
+        __syncthreads(); // the tile before is done with LDS
+        fetch(a0, b0, 0);
+        fetch(a1, b1, 1);
+        put(a0, b0, 0);
+        fetch(a0, b0, 2);
+        __syncthreads();
+        for (int ks = 0; ks < ksteps; ks += 2) {
+            step(0);
+            put(a1, b1, 1);
+            fetch(a1, b1, ks + 3);
+            __syncthreads();
+            step(1);
+            put(a0, b0, 0);
+            fetch(a0, b0, ks + 4);
+            __syncthreads();
+        }
+        const int n = n0 + wave * 32 + l32;
+        if (n >= a.n) continue;
+        const float cn = a.metric == PK_METRIC_L2 ? a.cnorm[n] : 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int m = m0 + kg * 4 + 8 * (r >> 2) + (r & 3);
+            if (m >= rows) continue;
+            const size_t row = a.list[m];
+            float v = acc[r];
+            if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[row], 0.f);
+            const unsigned long long key = ((unsigned long long)order_bits(v, a.metric) << 32) | (uint32_t)n;
+            if (key < a.best[row]) atomicMin(a.best + row, key); // (a stale look costs an atomic, never a result)
+        }
+    }
+}
+
 // Rows whose second best value is near the best: into the list, their best[] back to "none yet".
 __global__ __launch_bounds__(256) void near_ties_kernel(GemmArgs a, const uint32_t *second, const uint32_t *cmax, uint32_t *list,
                                                         uint32_t *nlisted)
@@ -594,7 +660,7 @@ hipError_t launch_gemm_near_ties(const GemmArgs &a, const uint32_t *second, cons
     if (a.ld % 64 != 0 || a.d > a.ld || !a.best || a.list != list || a.nlisted != nlisted) return hipErrorInvalidValue;
     hipLaunchKernelGGL(near_ties_kernel, dim3((uint32_t)std::min((a.m + 255) / 256, 4 * num_cu)), dim3(256), 0, s, a, second, cmax,
                        list, nlisted);
-    hipLaunchKernelGGL(gemm_scores_kernel<true>, dim3(2 * num_cu), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(gemm_listed_kernel, dim3(3 * num_cu), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
