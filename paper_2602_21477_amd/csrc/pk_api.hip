@@ -1748,6 +1748,7 @@ int pk_kmeans(const float *vectors, int64_t n, int32_t d, int32_t nlist, int32_t
         ka.cnt = c.take<uint32_t>((size_t)nlist);
         ka.start = c.take<uint32_t>((size_t)nlist);
         ka.fill = c.take<uint32_t>((size_t)nlist);
+        ka.piece0 = c.take<uint32_t>((size_t)nlist + 1);
         ka.members = c.take<uint32_t>((size_t)n);
         ka.sums = c.take<double>((size_t)nlist * d);
         ka.sq = c.take<double>((size_t)nlist);

@@ -653,6 +653,7 @@ struct KmeansArgs {
     int d, nlist;
     uint32_t *cnt;         // [nlist] in: members of each cluster
     uint32_t *start, *fill; // [nlist] each (scratch)
+    uint32_t *piece0;      // [nlist + 1] (scratch) parts of at most 256 members of the clusters before each one
     uint32_t *members;     // [n] row numbers in cluster-major order (scratch)
     float *centroids;      // [nlist][d] in: centroids the assignment used; out: means of the members
     double *sums;          // [nlist][d] scratch: per-cluster totals
