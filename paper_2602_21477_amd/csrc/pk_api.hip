@@ -355,6 +355,8 @@ constexpr int kSampleSlots = 1;
 
 // largest batch whose queries all get emission regions of 32768 entries (see emit_cap_for)
 constexpr int64_t kRoomyBatch = 128;
+// largest emission region whose overflow is provided for (see make_plan)
+constexpr uint32_t kRescueFrom = 8192;
 
 // bytes of the split operands of one handle's coarse step over nq queries
 size_t split_bytes(const pk_index *ix, int64_t nq)
@@ -494,29 +496,47 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         // query emits about L k / (sp * rows) of them before the histogram has tightened the gate.  Emission costs
         // about 12 ns per candidate of the query that meets the longest list (its atomics meet at one counter, one
         // workgroup selects among them: 60 k entries from a 444 k-row list 0.45 ms; 7 k fewer of 9.4 k from a list of
-        // 1165 rows, k = 77, 63 us) and 0.3 ns per candidate over all queries (1.6 M fewer of 3.2 M, 721 queries, 0.5 ms
-        // beside the overflows they caused).  A page costs 0.7 us of latency, 10 ns per query (a tile each) and its
-        // bytes: at 10 TB/s while the tiles of a page fit the chip side by side (one per CU), else at 5 TB/s.  The sum is
-        // least at sp = sqrt(emission of one page / cost of a page).  Batches of 721 queries of k = 37 over lists of
-        // 10 000 rows of 80 floats take 6 pages and 1.07 ms (one page: 12.7 ms, 2: 1.41, 4: 1.11, 12: 1.00); 256 queries
-        // over lists of 300 rows take one and 54 us (2: 61, 4: 72); 1024 over lists of 2441 rows, k = 100, four and 2.94 ms
-        // (1: 31, 2: 3.34, 3: 2.95, 6: 3.00).
-        // At most sp_max pages, and as many as the threshold takes in registers.
+        // 1165 rows, k = 77, 63 us) and 0.3 ns per candidate over all queries for those beyond some 400 of a query
+        // (0.55 M fewer of 1.6 M, 721 queries, 0.25 ms; fewer than that are selected in registers and cost next to
+        // nothing).  A page costs 0.7 us of latency, 10 ns per query (a tile each) and its bytes: at 10 TB/s while the
+        // tiles of a page fit the chip side by side (one per CU), else at 5 TB/s.  The cheapest number is taken: 721
+        // queries of k = 37 over lists of 10 000 rows of 80 floats take 6 pages and 1.07 ms (one page: 12.7 ms, 2: 1.41,
+        // 4: 1.11, 12: 1.00); 256 queries over lists of 300 rows take one and 54 us (2: 61, 4: 72); 1024 over lists of
+        // 2441 rows, k = 100, four and 2.94 ms (1: 31, 2: 3.34, 3: 2.95, 6: 3.00); 893 of k = 65 over 684 rows one and
+        // 161 us (2: 179).  At most sp_max pages, and as many as the threshold takes in registers.
         const double rows = std::min((double)own->P, std::max(1.0, lmean));
-        const double page_us = 0.7 + 0.01 * (double)nq + (double)nq * (double)own->P * (double)own->row_bytes / (nq <= own->num_cu ? 1.0e7 : 5.0e6);
-        const double emit_us = (0.012 * (double)lmax + 0.0003 * (double)nq * lmean) * (double)k / rows;
-        uint64_t more = (uint64_t)std::llround(std::sqrt(emit_us / page_us));
-        more = std::min<uint64_t>(more, std::max<uint64_t>(1, 16u * (uint32_t)kSelThreads / (uint32_t)own->P));
-        more = std::min<uint64_t>(more, (uint64_t)tunables().sp_max);
+        const double page_us = 0.7 + 0.01 * (double)nq +
+                               (double)nq * (double)own->P * (double)own->row_bytes / (nq <= own->num_cu ? 1.0e7 : 5.0e6);
+        const uint64_t most = std::min<uint64_t>(std::max<uint64_t>(1, 16u * (uint32_t)kSelThreads / (uint32_t)own->P),
+                                                 (uint64_t)tunables().sp_max);
+        uint64_t more = 1;
+        double least = 0;
+        for (uint64_t pg = 1; pg <= most; ++pg) {
+            const double share = (double)k / ((double)pg * rows);
+            const double cost = (double)pg * page_us + 0.012 * (double)lmax * share +
+                                0.0003 * (double)nq * std::max(0.0, lmean * share - 400.0);
+            if (pg == 1 || cost < least) {
+                least = cost;
+                more = pg;
+            }
+        }
         if (worst) more = (uint64_t)tunables().sp_max;
         if (lean) more = 0;
         p.sp = std::max(p.sp, (int)more);
         if (tunables().sp > 0) p.sp = tunables().sp;
     }
-    // Rows of memories that fit the last-level cache (256 MB) stay there from one search to the next: those are read
-    // through the caches (20 000 x 128, 256 queries: 54 us, and 56.6 past them), larger ones past them (1 M x 768, 64
-    // queries: scan 432 -> 386 us; 10 M x 768 fp16, 1024: 2641 -> 2420).
-    p.stream_rows = bytes > (256ull << 20);
+    // Rows of memories that fit the last-level cache (256 MB), or half of them, stay there from one search to the next:
+    // those are read through the caches (20 000 x 128, 256 queries: 54 us, and 57 past them; 110 000 x 1152, 53 queries,
+    // 508 MB: scan 71 us and 75), larger ones past them (585 000 x 1330, 10 queries, 3.1 GB: 768 and 658; 1 M x 768, 64
+    // queries: 432 and 386; 10 M x 768 fp16, 1024: 2641 and 2420).
+    // Not where the lists are probed by more queries than a tile holds, which reads their rows once per group, nor by the
+    // sliced-query kernel's groups of 64, which have no registers left for it (225 000 x 1408 fp16, 394 queries: scan 216
+    // us, and 237 past the caches).
+    // And not by calls that touch little: their lists may be asked for again soon (374 000 x 704, 2 queries of 9 lists: 78 us
+    // when they are, and 86 past the caches).
+    const double touched = (double)nq * nprobe * lmean * (double)own->row_bytes;
+    p.stream_rows = bytes > (768ull << 20) && touched > (double)(256ull << 20) &&
+                    p.avg_per_list * 2 <= (double)(p.hot_from == 0 ? std::min(p.mq_h, 32) : p.mq_f);
     p.sp = std::min(p.sp, kMaxSamplePages); // (a sample of fewer than k rows gives no threshold: slower, not wrong)
     p.span = (uint32_t)(p.sp * own->P);
     p.nlist_max = nlist_hi;
@@ -537,11 +557,12 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
               (!need_fine || split_bytes(own, nq) <= (size_t)p.cbuf_entries * sizeof(unsigned long long));
     // few lists, pairs and tiles: the threshold kernel's workgroups lay out slots and tiles as well (see wl_spread)
     p.wl_small = (uint64_t)nh * (uint64_t)nlist_hi <= kWlSmallLists && (uint64_t)nq * (uint64_t)nprobe <= 16384 && tiles <= 65536;
-    // A batch large enough that its regions are not the roomy ones (32768 entries) can have a query overflow in
-    // ordinary use (a query whose nearest list is a merged cluster: its sample's k-th best lets a tenth of all its
-    // rows through); the launch that scores such queries again, 3 us when there is none, then pays for itself.  Its
-    // regions are the sample's values, which nothing reads any more by then.
-    if (need_fine && nq > kRoomyBatch && (uint64_t)p.ecap < round_up(wmax, 16))
+    // A batch of 512 queries or more has regions of 8192 entries or fewer and can have a query overflow in ordinary use
+    // (a query whose nearest list is a merged cluster: its sample's k-th best lets a tenth of all its rows through); the
+    // launch that scores such queries again, 3 us when there is none, then pays for itself.  The regions of smaller
+    // batches are roomier.  The rescued keys' regions are the sample's values, which nothing reads any more by then.
+    // Nor does it take a launch to be ready for a query that would have to emit a quarter of all its rows.
+    if (need_fine && nq > kRoomyBatch && p.ecap <= kRescueFrom && 4ull * p.ecap < round_up(wmax, 16))
         p.rescues = (uint32_t)std::min<uint64_t>((uint64_t)nq * p.span * 4 / (kRescueCap * 8), kRescueRegions);
     p.tile_cap = (uint32_t)tiles;
     carve(p, nullptr, own);

@@ -137,22 +137,32 @@ __device__ __forceinline__ void load_slots(const ScanArgs &a, const Slots &s, in
     }
 }
 
+// a pointer that is the same in every lane, in scalar registers
+__device__ __forceinline__ gbytes uniform(gbytes p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (gbytes)(((uint64_t)hi << 32) | lo);
+}
+
 // The rows of a scan.  NT: whole lines, past the caches, then into operand layout (line_to_operands); otherwise half lines,
-// straight in operand layout.
+// straight in operand layout.  Addresses are a scalar base and one 32-bit offset per lane: the loads of a slice share
+// that one register (with a 64-bit address per lane for every group of rows, the NT kernels spilled).
 template <bool NT>
 struct RowLoad {
-    // first byte of the lane's part of row `row` of a block of 16
-    static __device__ __forceinline__ gbytes start(gbytes rows, int ln, int lg, int row_bytes)
+    // the lane's offset inside a block of 16 rows
+    static __device__ __forceinline__ uint32_t lane_offset(int ln, int lg, int row_bytes)
     {
-        if constexpr (NT) return rows + (size_t)(ln & 7) * row_bytes + lg * 16 + (ln >> 3) * 64;
-        else return rows + (size_t)ln * row_bytes + lg * 16;
+        if constexpr (NT) return (uint32_t)((ln & 7) * row_bytes + lg * 16 + (ln >> 3) * 64);
+        else return (uint32_t)(ln * row_bytes + lg * 16);
     }
-    // the s4-th of the four loads of slice `it`
-    static __device__ __forceinline__ u32x4 load(gbytes p, int it, int s4, int row_bytes)
+    // the s4-th of the four loads of slice `it` of the 16 rows at `rows` (uniform)
+    static __device__ __forceinline__ u32x4 load(gbytes rows, uint32_t lane, int it, int s4, int row_bytes)
     {
-        const gbytes at = p + (size_t)it * kIterBytes;
-        if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<gvec4>(at + (size_t)(s4 & 1) * 8 * row_bytes + (s4 >> 1) * 128));
-        else return *reinterpret_cast<gvec4>(at + s4 * 64);
+        const gbytes at = rows + (size_t)it * kIterBytes;
+        if constexpr (NT)
+            return __builtin_nontemporal_load(reinterpret_cast<gvec4>(at + (size_t)(s4 & 1) * 8 * row_bytes + (s4 >> 1) * 128 + lane));
+        else return *reinterpret_cast<gvec4>(at + s4 * 64 + lane);
     }
     // the four registers of a slice, as MFMA wants them
     static __device__ __forceinline__ void arrange(u32x4 (&b)[4])
@@ -351,8 +361,10 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
     s.carve(smem + (size_t)qheld * qstride, MQ);
     uint32_t *s_misc = s.bmax + MQ; // kScanSlotWords per-slot arrays precede this: keep scan_lds_bytes in step
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ln = lane & 15, lg = lane >> 4;
+    // (the sample's kernels have registers to spare and one tile per workgroup to wait for: a 64-bit address per lane there)
+    const uint32_t lane_part = RowLoad<NT>::lane_offset(ln, lg, row_bytes), lane_off = GATED ? lane_part : 0u;
     const int nit = row_bytes / kIterBytes;
     const int chunks_per_row = row_bytes / 16;
     uint32_t cur_qbeg = 0xffffffffu, cur_qcnt = 0;
@@ -375,7 +387,7 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
     [[maybe_unused]] float *const sv = reinterpret_cast<float *>(fx + 4 * 256 + 16);      // [span] values (one tile per query)
     Tile cur = a.tiles[sc.t];
     while (sc.t < sc.ntiles) {
-        const gbytes tx = in_global(cur.x);
+        const gbytes tx = GATED ? uniform(in_global(cur.x)) : in_global(cur.x) + lane_part;
         const gfloats txn = in_global(cur.xn);
         const uint32_t row0 = cur.row0;
         PK_MARK_IF(scan, GATED ? 1 : 9, bid == 0);
@@ -386,13 +398,13 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
         u32x4 xa[2][4], xb[2][4]; // two register buffers of one 256-byte slice of 32 rows each
         gbytes p0, p1;
 #define PK_ROWS(rb)                                                                               \
-    p0 = RowLoad<NT>::start(tx + (size_t)((rb) * kRowBlock) * row_bytes, ln, lg, row_bytes);       \
+    p0 = tx + (size_t)((rb) * kRowBlock) * row_bytes;                                             \
     p1 = p0 + (size_t)16 * row_bytes;
 #define PK_LOAD(buf, it)                                                                          \
     _Pragma("unroll") for (int s4 = 0; s4 < 4; ++s4)                                              \
     {                                                                                             \
-        buf[0][s4] = RowLoad<NT>::load(p0, it, s4, row_bytes);                                    \
-        buf[1][s4] = RowLoad<NT>::load(p1, it, s4, row_bytes);                                    \
+        buf[0][s4] = RowLoad<NT>::load(p0, lane_off, it, s4, row_bytes);                          \
+        buf[1][s4] = RowLoad<NT>::load(p1, lane_off, it, s4, row_bytes);                          \
     }
 #define PK_COMPUTE(buf, it)                                                                       \
     RowLoad<NT>::arrange(buf[0]);                                                                 \
@@ -626,9 +638,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
     uint32_t *s_slotq = reinterpret_cast<uint32_t *>(s.bmax + MQ); // query row of each slot (all modes)
     uint32_t *s_misc = s_slotq + MQ;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ln = lane & 15, lg = lane >> 4;
     const int row_bytes = a.row_bytes;
+    const uint32_t lane_off = RowLoad<NT>::lane_offset(ln, lg, row_bytes);
     const int nit = row_bytes / kIterBytes;
     uint32_t cur_qbeg = 0xffffffffu, cur_qcnt = 0;
     const int qm = tid >> 4, qpiece = (tid & 15) * 16; // this thread's slot (mod 16) and piece of a slice
@@ -644,7 +657,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
         const uint32_t tn = sc.peek(s_misc, next_end, next_fresh);
         const Tile nxt = a.tiles[tn < sc.ntiles ? tn : sc.ntiles - 1]; // in flight while this tile is scored
         {
-            const gbytes tx = in_global(cur.x);
+            const gbytes tx = uniform(in_global(cur.x));
             const gfloats txn = in_global(cur.xn);
             const uint32_t row0 = cur.row0;
             const uint32_t qbeg = __builtin_amdgcn_readfirstlane(cur.qbeg);
@@ -673,10 +686,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
             const int npass = (nrows + 4 * kRowBlock - 1) / (4 * kRowBlock);
             for (int pass = 0; pass < npass; ++pass) {
                 const int rb = pass * 4 + wave;
-                // a wave past the end of the page keeps in step (barriers) on the page's first rows
+                // a wave past the end of the page keeps in step (barriers) on the page's first 16 bytes
                 const bool active = rb * kRowBlock < nrows;
-                const gbytes p0 = RowLoad<NT>::start(tx + (size_t)(active ? rb * kRowBlock : 0) * row_bytes, ln, lg, row_bytes);
-                const gbytes p1 = p0 + (size_t)16 * row_bytes;
+                const int walk = active ? -1 : 0, stride = row_bytes & walk;
+                const uint32_t lane_at = lane_off & (uint32_t)walk;
+                const gbytes p0 = tx + (size_t)(active ? rb * kRowBlock : 0) * row_bytes;
+                const gbytes p1 = p0 + (size_t)16 * stride;
                 f32x4 acc[MT][2];
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
@@ -689,8 +704,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 #define PK_LOAD(buf, it)                                                                          \
     _Pragma("unroll") for (int s4 = 0; s4 < 4; ++s4)                                              \
     {                                                                                             \
-        buf[0][s4] = RowLoad<NT>::load(p0, it, s4, row_bytes);                                    \
-        buf[1][s4] = RowLoad<NT>::load(p1, it, s4, row_bytes);                                    \
+        buf[0][s4] = RowLoad<NT>::load(p0, lane_at, (it) & walk, s4, stride);                     \
+        buf[1][s4] = RowLoad<NT>::load(p1, lane_at, (it) & walk, s4, stride);                     \
     }
 #define PK_QLOAD(it)                                                                              \
     _Pragma("unroll") for (int j = 0; j < QLOADS; ++j)                                            \
@@ -971,7 +986,7 @@ static hipError_t launch_ks_mt(const ScanArgs &a, int grid, hipStream_t s)
     switch (a.mq) {
     case 16: return launch_ks_one<STORAGE, 1, NT>(a, grid, s);
     case 32: return launch_ks_one<STORAGE, 2, NT>(a, grid, s);
-    case 64: return launch_ks_one<STORAGE, 4, NT>(a, grid, s);
+    case 64: return launch_ks_one<STORAGE, 4, false>(a, grid, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -447,6 +447,10 @@ __global__ __launch_bounds__(kSelThreads) void rescue_kernel(FinalArgs a, MultiA
     __shared__ uint32_t s_wave[17];
     __shared__ uint32_t s_over[kRescueRegions]; // the overflowed queries, ascending
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // (usually there is none: one round of loads and one barrier say so)
+    bool any = false;
+    for (uint32_t q = (uint32_t)tid; q < nq; q += kSelThreads) any = any || a.qcnt[q] > a.ecap;
+    if (!__syncthreads_or(any)) return;
     // the overflowed queries, in query order
     uint32_t n = 0;
     for (uint32_t q0 = 0; q0 < nq && n < a.rregions; q0 += kSelThreads) {
