@@ -884,10 +884,18 @@ int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, i
     sh.mq = p.mq_h;
     if (beside) {
         sh.use_hist = 0;
+        sh.rr_first = (uint32_t)tunables().hot_cus;
         PK_HIP(hipEventRecord(own->ev_fork, s));
         PK_HIP(launch_scan_rr(sh, tunables().hot_cus, s));
         PK_HIP(hipStreamWaitEvent(own->side, own->ev_fork, 0));
         PK_HIP(launch_scan(sa, p.grid_f, own->side));
+        // Where the first kernel has more to do than its share of the chip, the CUs that the scan leaves join it (10 M x 768
+        // fp16 under L2 with a third of the rows probed: 1507 us on 96 CUs beside a scan of 1109 us, 1380 us joined; the
+        // batch 1.74 -> 1.55 ms, and within 2 % of that for any share from 64 to 160 CUs); where it is done by then, the
+        // joining launch finds no tiles and costs its 3 us (inner product: 2.66 ms either way).
+        ScanArgs sj = sh;
+        sj.rr_join = true;
+        PK_HIP(launch_scan_rr(sj, own->num_cu - tunables().hot_cus, own->side));
         PK_HIP(hipEventRecord(own->ev_join, own->side));
         if (timed) {
             own->prof_beside.push_back(1);
@@ -904,6 +912,7 @@ int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, i
         if (p.hot_from != 0xffffffffu) {
             if (p.hot_rs) {
                 sh.use_hist = 0; // the regular lists' scan has published its limits; this one only reads them
+                sh.rr_first = (uint32_t)p.grid_h;
                 PK_HIP(launch_scan_rr(sh, p.grid_h, s));
             } else {
                 PK_HIP(launch_scan_ks(sh, p.grid_h, s));

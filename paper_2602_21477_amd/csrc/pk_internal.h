@@ -270,6 +270,8 @@ struct ScanArgs {
     uint32_t *tile_ctr;          // device scalar, zero before the launch: batches handed out after the first round
     int k, use_hist;
     int row_bytes, metric, storage, mq;
+    uint32_t rr_first;           // rows-in-registers kernel: pairs of tiles its (first) launch starts with, one per workgroup
+    bool rr_join;                // ... this launch joins one that is running (same counter, same rr_first)
     bool nt;                     // gated mode: the rows are read past the caches (they would not stay in them anyway)
 };
 hipError_t launch_scan(const ScanArgs &a, int grid, hipStream_t s);

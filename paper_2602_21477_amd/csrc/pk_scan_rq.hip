@@ -82,9 +82,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // pair i + 1, and the descriptor of the next tile is fetched while the current one runs.
     const uint32_t ntiles = *a.ntiles;
     const uint32_t npairs = (ntiles + 1u) >> 1;
-    if (blockIdx.x >= npairs) return;
-    if (tid == 0) s_misc[0] = gridDim.x + atomicAdd(a.tile_ctr, 1u);
+    // A second launch may join the first while it runs (a.rr_join: the CUs that the regular lists' scan has left): its
+    // workgroups have no pair of their own and claim their first one, too.
     uint32_t pair = blockIdx.x;
+    if (a.rr_join) {
+        if (tid == 0) s_misc[1] = a.rr_first + atomicAdd(a.tile_ctr, 1u);
+        __syncthreads();
+        pair = __builtin_amdgcn_readfirstlane(s_misc[1]);
+    }
+    if (pair >= npairs) return;
+    if (tid == 0) s_misc[0] = a.rr_first + atomicAdd(a.tile_ctr, 1u);
     int half = 0;
     Tile cur = a.tiles[2u * pair];
     while (true) {
@@ -100,7 +107,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         const uint32_t t_next = last_of_pair ? 2u * p_next : 2u * pair + 1u;
         const Tile nxt = a.tiles[t_next < ntiles ? t_next : ntiles - 1]; // on its way while this tile is scored
         uint32_t claim = npairs;
-        if (tid == 0 && last_of_pair && p_next < npairs) claim = gridDim.x + atomicAdd(a.tile_ctr, 1u); // read when the pair ends
+        if (tid == 0 && last_of_pair && p_next < npairs) claim = a.rr_first + atomicAdd(a.tile_ctr, 1u); // read when the pair ends
         // ---- this wave's 32 rows, whole, into registers, requested first of all: they come from HBM, and the
         // per-slot arrays and the first query slices (L2) are fetched while they are on their way (rows past
         // the tile's last lie inside the page and hold stale bytes: h = +inf keeps them out)
