@@ -216,6 +216,7 @@ struct Plan {
     bool need_coarse, need_fine, f16;
     bool raw_queries; // the coarse step reads the caller's query rows directly (no preparation launch)
     bool stream_rows; // the rows are read past the caches
+    bool halves_first; // the coarse step's preparation also makes the half-precision copy of the queries
     bool split;       // the coarse scores come from the split-operand GEMM
     bool wl_small;    // the second half of the work list is small enough for one workgroup (rides in the threshold launch)
     // buffers
@@ -555,6 +556,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     // needs a larger workspace for them (the fp32 GEMM takes the others, and calls over several handles).
     p.split = need_coarse && nh == 1 && !worst && coarse_by_gemm(qlo[1] - qlo[0], own) &&
               (!need_fine || split_bytes(own, nq) <= (size_t)p.cbuf_entries * sizeof(unsigned long long));
+    p.halves_first = need_coarse && need_fine && nh == 1 && p.f16 && !p.split && !p.raw_queries;
     // few lists, pairs and tiles: the threshold kernel's workgroups lay out slots and tiles as well (see wl_spread)
     p.wl_small = (uint64_t)nh * (uint64_t)nlist_hi <= kWlSmallLists && (uint64_t)nq * (uint64_t)nprobe <= 16384 && tiles <= 65536;
     // A batch of 512 queries or more has regions of 8192 entries or fewer and can have a query overflow in ordinary use
@@ -702,6 +704,22 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
         g.metric = own->cfg.metric;
         g.stride = p.stride;
         PK_HIP(launch_gemm_split(g, own->num_cu, s));
+    } else if (p.halves_first) {
+        // one launch prepares both copies, the coarse step's and the half-precision one that the scan reads
+        SplitRowsArgs sr{};
+        sr.x = q;
+        sr.m = (uint32_t)p.nq;
+        sr.d = own->cfg.d;
+        sr.ld = own->dpad32;
+        sr.qnorm = p.qn32;
+        sr.copy = reinterpret_cast<float *>(p.qs32);
+        sr.half_rows = p.qs;
+        sr.half_norm = p.qn;
+        sr.half_bytes = own->row_bytes;
+        sr.meta = qm;
+        PK_HIP(launch_split_rows(sr, m, s));
+        ca.qs = p.qs32;
+        ca.qnorm = p.qn32;
     } else if (p.raw_queries) {
         // the caller's rows are usable as they are and no norms are needed: the centroid kernel does the bookkeeping
         ca.qs = reinterpret_cast<const char *>(q);
@@ -794,7 +812,7 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
 int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, int64_t *out_ids, float *out_dist,
              hipStream_t s, bool timed, bool counted, bool fixed)
 {
-    if (p.f16 && !p.split) PK_HIP(launch_prep_queries(q, p.nq, own->cfg.d, PK_F16, own->row_bytes, p.qs, p.qn, s));
+    if (p.f16 && !p.split && !p.halves_first) PK_HIP(launch_prep_queries(q, p.nq, own->cfg.d, PK_F16, own->row_bytes, p.qs, p.qn, s));
     WorklistArgs w;
     SampleArgs sm;
     fill_worklist_args(p, own, w, sm);

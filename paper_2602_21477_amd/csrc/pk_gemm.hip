@@ -198,7 +198,8 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     int s = 14 - ((int)(__float_as_uint(big) >> 23) - 127);
     s = s < -126 ? -126 : (s > 126 ? 126 : s);
     const float scale = __uint_as_float((uint32_t)(s + 127) << 23);
-    char *dst = (cent ? a.cs : a.xs) + (size_t)r * ld * 4;
+    char *dst = cent ? a.cs : a.xs;
+    if (dst) dst += (size_t)r * ld * 4; // (null: the rows are wanted in their other forms only)
 #pragma unroll
     for (int t = 0; t < kT; ++t) {
         const int i = lane * 4 + 256 * t;
@@ -210,9 +211,11 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
             hi[j] = (_Float16)y;
             lo[j] = (_Float16)(y - (float)hi[j]); // the difference is exact
         }
-        char *p = dst + (size_t)(i >> 5) * 128 + (i & 31) * 2;
-        *reinterpret_cast<half4 *>(p) = hi;
-        *reinterpret_cast<half4 *>(p + 64) = lo;
+        if (dst) {
+            char *p = dst + (size_t)(i >> 5) * 128 + (i & 31) * 2;
+            *reinterpret_cast<half4 *>(p) = hi;
+            *reinterpret_cast<half4 *>(p + 64) = lo;
+        }
         if (!cent && a.copy) *reinterpret_cast<f32x4 *>(a.copy + (size_t)r * ld + i) = v[t];
     }
     if (!cent && a.half_rows) { // the row as a half-precision index stores it: rounded to nearest even, norm of the rounded values
@@ -239,7 +242,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
         if (a.cmax) atomicMax(a.cmax, __float_as_uint(norm)); // (squares: their bits are in the order of the values)
         return;
     }
-    a.x_back[r] = back;
+    if (a.x_back) a.x_back[r] = back;
     if (a.second) a.second[r] = 0xffffffffu;
     if (a.qnorm) a.qnorm[r] = norm;
     if (a.half_rows) a.half_norm[r] = norm16;

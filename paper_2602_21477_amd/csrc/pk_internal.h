@@ -560,8 +560,8 @@ struct SplitRowsArgs {
     const float *c;      // [n_c][ld] centroid table, zero padded
     uint32_t m, n_c;
     int d, ld;
-    char *xs, *cs;       // [m][4 * ld], [n_c][4 * ld] out: split rows
-    float *x_back, *c_back; // [m], [n_c] out: what undoes the row's scale
+    char *xs, *cs;       // [m][4 * ld] (or null), [n_c][4 * ld] out: split rows
+    float *x_back, *c_back; // [m] (or null), [n_c] out: what undoes the row's scale
     float *qnorm;        // [m] out: squared norms, or null
     float *copy;         // [m][ld] out: fp32 rows, zero padded, or null
     char *half_rows;     // [m][half_bytes] out: rows rounded to half precision, zero padded, or null
