@@ -33,8 +33,8 @@ HBM_PEAK_GBS = 8000.0  # MI355X datasheet HBM3E bandwidth
 METRIC_NAME = "search queries/sec at recall@10>=0.9 (1 GPU); list-scan HBM GB/s vs peak"
 
 
-MEASURED_STREAM_GBS = 6000.0  # what a bare copy of the scan's load pattern reads on this chip (profiles/scan_kernel_c4_ip.md, section 3)
-MEASURED_STREAM_SOURCE = "profiles/scan_kernel_c4_ip.md section 3 (scan load pattern, random data, 6.0-6.3 TB/s)"
+MEASURED_STREAM_GBS = 6870.0  # the most that bare loads in the scan's pattern read on this chip (profiles/scan_kernel_c4_ip.md, section 3)
+MEASURED_STREAM_SOURCE = "profiles/scan_kernel_c4_ip.md section 3 (scan load pattern, 6.2-6.9 TB/s by workgroups per CU)"
 
 
 def kernel_sources_sha():
