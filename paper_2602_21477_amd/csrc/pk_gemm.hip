@@ -285,6 +285,11 @@ __device__ __forceinline__ float near_margin(int ld, int metric, float qn, float
     return 4.76837158e-7f * sqrtf((float)ld) * (metric == PK_METRIC_L2 ? qn + cmax : sqrtf(qn) * sqrtf(cmax));
 }
 
+// Rows whose values cannot all be compared (a NaN among them: from a NaN or an infinity in the row or in a centroid, or
+// from finite values whose products overflow) are decided by the fp32 kernel too: their second value is kNoOrder.
+constexpr uint32_t kNoOrder = 0u;           // below the key of every number
+constexpr uint32_t kWorstKey = 0xfffffffeu; // the most a list's key can be, so that all ones stays "no list"
+
 // BM x BN output tile per workgroup of WM x WN waves; K in steps of 32 elements (128 bytes of a split row) through
 // double-buffered LDS, fetched two steps ahead through two register stages (a step is short: 12 MFMAs of 32 cycles per
 // 32 x 32 x 2 blocks, and the operands come from L2).  BEST: every row keeps its best (value key, column) by atomicMin
@@ -445,12 +450,11 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
                 const int local = wm * (BM / WM) + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
                 const float factor = s_row[local], margin = s_row[BM + local];
                 float t[NI];
-                uint32_t key[NI], low = 0xffffffffu;
+                uint32_t key[NI], low = 0xffffffffu; // (all ones: not a list; below it for every list, whatever its value)
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
                     t[j] = fmaf(acc[i][j][r] * cb[j], factor, cn[j]);
-                    if (n0 + wn * (BN / WN) + j * 32 + l32 >= a.n) t[j] = INFINITY;
-                    key[j] = order_bits(t[j], PK_METRIC_L2);
+                    key[j] = n0 + wn * (BN / WN) + j * 32 + l32 < a.n ? min(order_bits(t[j], PK_METRIC_L2), kWorstKey) : 0xffffffffu;
                     low = min(low, key[j]);
                 }
                 low = min_of_half(low);
@@ -461,7 +465,8 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
                 uint32_t near0 = 0, near1 = 0;
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
-                    const unsigned long long eq = __ballot(key[j] == best), nr = __ballot(t[j] <= limit);
+                    // (a value that cannot be compared is near whatever the best is)
+                    const unsigned long long eq = __ballot(key[j] == best), nr = __ballot(key[j] != 0xffffffffu && !(t[j] > limit));
                     if (at0 < 0 && (uint32_t)eq) at0 = j * 32 + __ffs((uint32_t)eq) - 1;
                     if (at1 < 0 && (uint32_t)(eq >> 32)) at1 = j * 32 + __ffs((uint32_t)(eq >> 32)) - 1;
                     near0 += (uint32_t)__popc((uint32_t)nr);
@@ -470,8 +475,10 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
                 uint32_t next = 0xffffffffu;
                 if (near0 > 1u || near1 > 1u) { // rare (wave-uniform): the best but one
 #pragma unroll
-                    for (int j = 0; j < NI; ++j)
+                    for (int j = 0; j < NI; ++j) {
                         if (j * 32 + l32 != (kg ? at1 : at0)) next = min(next, key[j]);
+                        if (key[j] != 0xffffffffu && t[j] != t[j]) next = kNoOrder;
+                    }
                     next = min_of_half(next);
                     const uint32_t x0 = __builtin_amdgcn_readlane(next, 31), x1 = __builtin_amdgcn_readlane(next, 63);
                     next = kg ? x1 : x0;
@@ -494,7 +501,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
             if (!has || m >= a.m) continue;
             float v = value_of(top[i], PK_METRIC_L2);
             if (a.metric == PK_METRIC_IP) v = -v * a.q_back[m];
-            mine[i] = order_bits(v, a.metric);
+            mine[i] = min(order_bits(v, a.metric), kWorstKey);
             const unsigned long long k = ((unsigned long long)mine[i] << 32) | (uint32_t)(n0 + wn * (BN / WN) + col[i]);
             met[i] = (uint32_t)(atomicMin(a.best + m, k) >> 32);
         }
@@ -502,16 +509,18 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
         for (int i = 0; i < MI; ++i) {
             const int m = m0 + wm * (BM / WM) + i * 32 + rr;
             if (!a.second || !has || m >= a.m) continue;
-            uint32_t other = max(met[i], mine[i]);
-            if (second[i] != 0xffffffffu) {
+            uint32_t other = max(met[i], mine[i]); // (all ones: none met)
+            if (second[i] == kNoOrder) {
+                other = kNoOrder;
+            } else if (second[i] != 0xffffffffu) {
                 float v = value_of(second[i], PK_METRIC_L2);
                 if (a.metric == PK_METRIC_IP) v = -v * a.q_back[m];
-                other = min(other, order_bits(v, a.metric));
+                other = min(other, min(order_bits(v, a.metric), kWorstKey));
             }
-            // (none met: all ones, a NaN, which is near nothing)
-            if (fabsf(value_of(other, a.metric) - value_of(min(met[i], mine[i]), a.metric)) <=
-                near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax)))
-                atomicMin(a.second + m, other);
+            if (other == 0xffffffffu) continue;
+            const float gap = fabsf(value_of(other, a.metric) - value_of(min(met[i], mine[i]), a.metric));
+            if (gap > near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax))) continue;
+            atomicMin(a.second + m, gap == gap ? other : kNoOrder);
         }
     }
 }
@@ -640,9 +649,9 @@ __global__ __launch_bounds__(256) void near_ties_kernel(GemmArgs a, const uint32
         bool near = false;
         if (i < (uint32_t)a.m) {
             const uint32_t s = second[i];
-            near = s != 0xffffffffu &&
-                   fabsf(value_of(s, a.metric) - value_of((uint32_t)(a.best[i] >> 32), a.metric)) <=
-                       near_margin(a.ld, a.metric, a.qnorm[i], __uint_as_float(*cmax));
+            near = s == kNoOrder ||
+                   (s != 0xffffffffu && !(fabsf(value_of(s, a.metric) - value_of((uint32_t)(a.best[i] >> 32), a.metric)) >
+                                          near_margin(a.ld, a.metric, a.qnorm[i], __uint_as_float(*cmax))));
         }
         const unsigned long long m = __ballot(near);
         if (m == 0ull) continue;

@@ -120,6 +120,7 @@ __global__ __launch_bounds__(256) void scatter_build_kernel(const DevIndex *ixp,
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int64_t i = (int64_t)blockIdx.x * 4 + wave; i < n; i += (int64_t)gridDim.x * 4) {
         const uint32_t l = (uint32_t)assign[i];
+        if (l >= (uint32_t)ix.nlist) continue; // (not counted either; no assignment leaves such a number)
         uint32_t slot = 0;
         if (lane == 0) slot = atomicAdd(&fill[l], 1u);
         slot = __shfl(slot, 0);

@@ -93,6 +93,56 @@ def test_split_operand_assignment_is_within_fp32_of_64_bits(gpu_device, n, d, nl
         ix.close()
 
 
+def lists_of(ix, n):
+    """The list of each of the ids 0 .. n - 1, every one of which is in exactly one list."""
+    where, found = np.full(n, -1), 0
+    for l in np.nonzero(ix.list_lengths())[0]:
+        ids = ix.list_ids(int(l)).cpu().numpy()
+        where[ids] = l
+        found += len(ids)
+    assert found == n and (where >= 0).all()
+    return where
+
+
+@pytest.mark.parametrize("metric", [IP, L2])
+@pytest.mark.parametrize("nlist,kind", [(33, "plain"), (200, "plain"), (513, "plain"), (33, "huge"), (513, "huge"), (65, "nan"), (1, "plain")])
+def test_rows_without_a_comparable_score_go_to_some_list(gpu_device, nlist, kind, metric):
+    """Rows and centroids with NaN, infinities and values whose products overflow, in all three tile sizes of the
+    assignment, with lists that do not fill their tiles: every row ends up in a list that exists, the rows beside it in
+    their own."""
+    rng = np.random.default_rng(nlist)
+    n, d = 32768 + 16384, 48  # a chunk of each size: 256 x 256 (513 lists) or 128 x 128 tiles, then smaller ones
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    odd = np.arange(0, n, 997)
+    for i, r in enumerate(odd):
+        x[r, i % d] = [np.nan, np.inf, -np.inf, 3e38, 1e25, -np.nan][i % 6]
+    if kind == "huge":
+        cent[rng.permutation(nlist)[: nlist // 2 + 1]] *= np.float32(1e33)
+    if kind == "nan":
+        cent[3, 2], cent[nlist - 1, 0] = np.nan, np.inf
+    ix = B.Index(dev(cent), dev(x), metric=metric, insert_reserve=20000)
+    try:
+        where = lists_of(ix, n)
+        if kind == "plain":
+            fine = np.setdiff1d(np.arange(n), odd)
+            s = x[fine].astype(np.float64) @ cent.astype(np.float64).T
+            if metric == L2:
+                s = 2 * s - (cent.astype(np.float64) ** 2).sum(1)
+            # fp32 rounding of sums of 48 products, as in the tests below
+            assert (s.max(1) - s[np.arange(len(fine)), where[fine]] <= 1e-5 * (1 + np.abs(s).max(1))).all()
+        lists = ix.insert(dev(x[:8192]), want_lists=True).cpu().numpy()
+        assert ((lists >= 0) & (lists < nlist)).all()
+        assert ix.stats().device_error == 0 and ix.stats().n_total == n + 8192
+        assert ix.list_lengths().sum() == n + 8192
+    finally:
+        ix.close()
+    if metric == L2:
+        assign = torch.empty(n, dtype=torch.int32, device="cuda")
+        B.pk_kmeans(dev(x), dev(cent), 1, assign)
+        assert int(assign.min()) >= 0 and int(assign.max()) < nlist
+
+
 @pytest.mark.parametrize("nq,storage,metric,d", [(1024, F16, L2, 100), (1024, F32, IP, 128), (999, F32, L2, 70), (128, F16, IP, 64)])
 def test_searches_through_the_split_gemm(gpu_device, nq, storage, metric, d):
     """Batches with 128 tiles or more of 128 x 128 scores, against the oracle: every storage's own query copy is made
