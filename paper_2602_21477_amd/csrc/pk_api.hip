@@ -217,12 +217,9 @@ struct Plan {
     bool raw_queries; // the coarse step reads the caller's query rows directly (no preparation launch)
     bool stream_rows; // the rows are read past the caches
     bool halves_first; // the coarse step's preparation also makes the half-precision copy of the queries
-    bool split;       // the coarse scores come from the split-operand GEMM
     bool wl_small;    // the second half of the work list is small enough for one workgroup (rides in the threshold launch)
     // buffers
     char *qs32, *qs;
-    char *xs, *cs;    // split: query rows and centroid table as halfs,
-    float *xback, *cback; // and what undoes their rows' scales
     float *qn32, *qn, *S, *svals, *tlo, *tinv;
     uint32_t *cand_off, *cand_cnt, *lcnt, *lstart, *lfill, *ltile, *lhtile, *pair_off, *slot_q, *slot_o, *scalars,
         *tau, *tcur, *hist, *ccnt, *sslot_q, *sslot_o;
@@ -248,12 +245,6 @@ void carve(Plan &p, char *base, const pk_index *own)
     }
     p.qagent = c.take<uint16_t>(nq);
     p.scalars = c.take<uint32_t>(32);
-    if (p.split && !p.need_fine) { // nobody reads the queries in fp32 then
-        p.xs = p.qs32;
-        p.cs = c.take<char>((size_t)own->nlist_pad * own->rb32);
-        p.xback = c.take<float>(nq);
-        p.cback = c.take<float>(own->nlist_pad);
-    }
     p.probes = c.take<int32_t>(nq * p.nprobe);
     p.cand_off = c.take<uint32_t>(nq);
     p.cand_cnt = c.take<uint32_t>(nq);
@@ -284,13 +275,6 @@ void carve(Plan &p, char *base, const pk_index *own)
         p.stiles = c.take<Tile>(nq * p.sp + 1);
         p.svals = c.take<float>(nq * p.span + 16);
         p.cbuf = c.take<unsigned long long>((size_t)p.cbuf_entries + 16);
-        if (p.split) { // the emission regions are written after the coarse step is over
-            Carver o{reinterpret_cast<char *>(p.cbuf), 0};
-            p.xs = o.take<char>(nq * own->rb32);
-            p.cs = o.take<char>((size_t)own->nlist_pad * own->rb32);
-            p.xback = o.take<float>(nq);
-            p.cback = o.take<float>(own->nlist_pad);
-        }
     }
     p.bytes = round_up(c.off, 256);
 }
@@ -358,13 +342,6 @@ constexpr int kSampleSlots = 1;
 constexpr int64_t kRoomyBatch = 128;
 // largest emission region whose overflow is provided for (see make_plan)
 constexpr uint32_t kRescueFrom = 8192;
-
-// bytes of the split operands of one handle's coarse step over nq queries
-size_t split_bytes(const pk_index *ix, int64_t nq)
-{
-    return round_up((size_t)nq * ix->rb32, 256) + round_up((size_t)ix->nlist_pad * ix->rb32, 256) +
-           round_up((size_t)nq * 4, 256) + round_up((size_t)ix->nlist_pad * 4, 256);
-}
 
 int grid_for(const pk_index *ix, int row_bytes, int mq)
 {
@@ -552,11 +529,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     p.cbuf_entries = (uint64_t)nq * p.ecap;
     // a smaller batch has larger regions: none needs more in all than this
     if (worst) p.cbuf_entries = std::max<uint64_t>(p.cbuf_entries, std::min<uint64_t>(32768ull * (uint64_t)nq, 4ull << 20));
-    // The split operands of a search lie where the emitted candidates will: only where they fit, so that no search
-    // needs a larger workspace for them (the fp32 GEMM takes the others, and calls over several handles).
-    p.split = need_coarse && nh == 1 && !worst && coarse_by_gemm(qlo[1] - qlo[0], own) &&
-              (!need_fine || split_bytes(own, nq) <= (size_t)p.cbuf_entries * sizeof(unsigned long long));
-    p.halves_first = need_coarse && need_fine && nh == 1 && p.f16 && !p.split && !p.raw_queries;
+    p.halves_first = need_coarse && need_fine && nh == 1 && p.f16 && !p.raw_queries;
     // few lists, pairs and tiles: the threshold kernel's workgroups lay out slots and tiles as well (see wl_spread)
     p.wl_small = (uint64_t)nh * (uint64_t)nlist_hi <= kWlSmallLists && (uint64_t)nq * (uint64_t)nprobe <= 16384 && tiles <= 65536;
     // A batch of 512 queries or more has regions of 8192 entries or fewer and can have a query overflow in ordinary use
@@ -667,44 +640,7 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
     qm.nclear = p.need_fine ? 2u * (uint32_t)p.nh * (uint32_t)p.nlist_max : 0u; // and the fill marks behind them
     // small segments: one launch of the centroid kernel for all of them
     CentroidArgs ca{};
-    if (p.split) {
-        SplitRowsArgs sr{};
-        sr.x = q;
-        sr.c = own->host.cent;
-        sr.m = (uint32_t)p.nq;
-        sr.n_c = (uint32_t)own->nlist_pad;
-        sr.d = own->cfg.d;
-        sr.ld = own->dpad32;
-        sr.xs = p.xs;
-        sr.cs = p.cs;
-        sr.x_back = p.xback;
-        sr.c_back = p.cback;
-        sr.qnorm = p.qn32;
-        if (p.need_fine && p.f16) { // what the scan reads, made in the same pass
-            sr.half_rows = p.qs;
-            sr.half_norm = p.qn;
-            sr.half_bytes = own->row_bytes;
-        } else if (p.need_fine) {
-            sr.copy = reinterpret_cast<float *>(p.qs32);
-        }
-        sr.meta = qm;
-        PK_HIP(launch_split_rows(sr, m, s));
-        SplitGemmArgs g{};
-        g.q = p.xs;
-        g.c = p.cs;
-        g.q_back = p.xback;
-        g.c_back = p.cback;
-        g.qnorm = p.qn32;
-        g.cnorm = own->host.cnorm;
-        g.out = p.S;
-        g.m = (int)p.nq;
-        g.n = own->cfg.nlist;
-        g.n_pad = own->nlist_pad;
-        g.ld = own->dpad32;
-        g.metric = own->cfg.metric;
-        g.stride = p.stride;
-        PK_HIP(launch_gemm_split(g, own->num_cu, s));
-    } else if (p.halves_first) {
+    if (p.halves_first) {
         // one launch prepares both copies, the coarse step's and the half-precision one that the scan reads
         SplitRowsArgs sr{};
         sr.x = q;
@@ -730,54 +666,52 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
         ca.qs = p.qs32;
         ca.qnorm = p.qn32;
     }
-    if (!p.split) {
-        ca.out = p.S;
-        ca.stride = p.stride;
-        ca.row_bytes = own->rb32;
-        ca.metric = own->cfg.metric;
-        uint32_t longest = 0;
+    ca.out = p.S;
+    ca.stride = p.stride;
+    ca.row_bytes = own->rb32;
+    ca.metric = own->cfg.metric;
+    uint32_t longest = 0;
+    for (int a = 0; a < m.n; ++a) {
+        const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
+        if (!coarse_by_gemm(nqa, hs[a])) longest = std::max(longest, nqa);
+    }
+    // Queries per workgroup: as many as one workgroup takes (64) when that still leaves a workgroup for every
+    // CU; fewer otherwise, since the kernel is a chain of dependent slices and a chip half empty gains nothing
+    // from the centroid rows a larger group shares.
+    ca.chunk = (int)std::min<uint32_t>(64, (longest + 15) / 16 * 16);
+    uint64_t wgs = 0;
+    while (true) {
+        wgs = 0;
         for (int a = 0; a < m.n; ++a) {
             const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
-            if (!coarse_by_gemm(nqa, hs[a])) longest = std::max(longest, nqa);
+            ca.blk[a] = (uint32_t)wgs;
+            if (nqa > 0 && !coarse_by_gemm(nqa, hs[a]))
+                wgs += (uint64_t)((nqa + ca.chunk - 1) / ca.chunk) * (uint64_t)(hs[a]->nlist_pad / 16);
         }
-        // Queries per workgroup: as many as one workgroup takes (64) when that still leaves a workgroup for every
-        // CU; fewer otherwise, since the kernel is a chain of dependent slices and a chip half empty gains nothing
-        // from the centroid rows a larger group shares.
-        ca.chunk = (int)std::min<uint32_t>(64, (longest + 15) / 16 * 16);
-        uint64_t wgs = 0;
-        while (true) {
-            wgs = 0;
-            for (int a = 0; a < m.n; ++a) {
-                const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
-                ca.blk[a] = (uint32_t)wgs;
-                if (nqa > 0 && !coarse_by_gemm(nqa, hs[a]))
-                    wgs += (uint64_t)((nqa + ca.chunk - 1) / ca.chunk) * (uint64_t)(hs[a]->nlist_pad / 16);
-            }
-            if (wgs >= (uint64_t)own->num_cu || ca.chunk <= 16) break;
-            ca.chunk -= 16;
-        }
-        if (wgs > 0x7fffffffull) return PK_ERR_UNSUPPORTED;
-        ca.blk[m.n] = (uint32_t)wgs;
-        if (wgs > 0) PK_HIP(launch_centroid_scores(ca, m, s));
-        for (int a = 0; a < m.n; ++a) {
-            const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
-            if (nqa == 0 || !coarse_by_gemm(nqa, hs[a])) continue;
-            const pk_index *ix = hs[a];
-            GemmArgs g{};
-            g.q = reinterpret_cast<const float *>(p.qs32) + (size_t)m.qlo[a] * ix->dpad32;
-            g.c = ix->host.cent;
-            g.qnorm = p.qn32 + m.qlo[a];
-            g.cnorm = ix->host.cnorm;
-            g.out = p.S + (size_t)m.qlo[a] * p.stride;
-            g.m = (int)nqa;
-            g.n = ix->cfg.nlist;
-            g.n_pad = ix->nlist_pad;
-            g.n_store = ix->nlist_pad;
-            g.ld = ix->dpad32;
-            g.metric = ix->cfg.metric;
-            g.stride = p.stride;
-            PK_HIP(launch_gemm_scores(g, s));
-        }
+        if (wgs >= (uint64_t)own->num_cu || ca.chunk <= 16) break;
+        ca.chunk -= 16;
+    }
+    if (wgs > 0x7fffffffull) return PK_ERR_UNSUPPORTED;
+    ca.blk[m.n] = (uint32_t)wgs;
+    if (wgs > 0) PK_HIP(launch_centroid_scores(ca, m, s));
+    for (int a = 0; a < m.n; ++a) {
+        const uint32_t nqa = m.qlo[a + 1] - m.qlo[a];
+        if (nqa == 0 || !coarse_by_gemm(nqa, hs[a])) continue;
+        const pk_index *ix = hs[a];
+        GemmArgs g{};
+        g.q = reinterpret_cast<const float *>(p.qs32) + (size_t)m.qlo[a] * ix->dpad32;
+        g.c = ix->host.cent;
+        g.qnorm = p.qn32 + m.qlo[a];
+        g.cnorm = ix->host.cnorm;
+        g.out = p.S + (size_t)m.qlo[a] * p.stride;
+        g.m = (int)nqa;
+        g.n = ix->cfg.nlist;
+        g.n_pad = ix->nlist_pad;
+        g.n_store = ix->nlist_pad;
+        g.ld = ix->dpad32;
+        g.metric = ix->cfg.metric;
+        g.stride = p.stride;
+        PK_HIP(launch_gemm_scores(g, s));
     }
     if (p.nlist_max <= kDenseSelectMax && tunables().densesel) {
         if (counted && p.need_fine) {
@@ -812,7 +746,7 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
 int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, int64_t *out_ids, float *out_dist,
              hipStream_t s, bool timed, bool counted, bool fixed)
 {
-    if (p.f16 && !p.split && !p.halves_first) PK_HIP(launch_prep_queries(q, p.nq, own->cfg.d, PK_F16, own->row_bytes, p.qs, p.qn, s));
+    if (p.f16 && !p.halves_first) PK_HIP(launch_prep_queries(q, p.nq, own->cfg.d, PK_F16, own->row_bytes, p.qs, p.qn, s));
     WorklistArgs w;
     SampleArgs sm;
     fill_worklist_args(p, own, w, sm);
@@ -2185,11 +2119,6 @@ int pk_workspace_reserve(pk_index *const *handles, int32_t n_handles, int64_t nq
     Plan p;
     PK_TRY(make_plan(p, handles, n_handles, qlo.data(), nq_max, k_max, np, true, true, inserts_ahead, true));
     size_t need = p.bytes;
-    // a coarse step alone (pk_coarse, inserts): its plan holds the centroid table's split copy, but none of the fine step
-    Plan pc;
-    const uint32_t all[2] = {0, (uint32_t)nq_max};
-    PK_TRY(make_plan(pc, handles, 1, all, nq_max, 1, np, true, false));
-    need = std::max(need, pc.bytes);
     need += 2 * (round_up((size_t)nq_max * 4, 256) + 256); // slots and ranks of an insert batch
     InsertScratch is;
     const int64_t mi = std::min<int64_t>(nq_max, kInsertChunk);

@@ -2,8 +2,8 @@
 // "query"): S[m][n] = <Q_m, C_n> (inner product) or |C_n|^2 - 2 <Q_m, C_n> + |Q_m|^2
 // (squared L2), Section 2.2's ranking of clusters by centroid distance, for all m, n.
 //
-// gemm_split_kernel below does this for one handle; gemm_scores_kernel takes the segments of
-// calls over several handles and the searches whose workspace has no room for split operands.
+// gemm_scores_kernel writes the scores: the coarse step of searches.  gemm_split_kernel finds every row's best
+// column: the assignments of build, k-means and large inserts.
 //
 // This is a dense contraction, so it runs on the matrix cores with fp32 inputs and fp32
 // accumulation (v_mfma_f32_32x32x2_f32): no down-conversion of queries or centroids, so
@@ -292,17 +292,18 @@ constexpr uint32_t kWorstKey = 0xfffffffeu; // the most a list's key can be, so 
 
 // BM x BN output tile per workgroup of WM x WN waves; K in steps of 32 elements (128 bytes of a split row) through
 // double-buffered LDS, fetched two steps ahead through two register stages (a step is short: 12 MFMAs of 32 cycles per
-// 32 x 32 x 2 blocks, and the operands come from L2).  BEST: every row keeps its best (value key, column) by atomicMin
+// 32 x 32 x 2 blocks, and the operands come from L2).  Every row keeps its best (value key, column) by atomicMin
 // instead of writing scores: top-1 assignment, which then needs no score matrix (268 MB per 16384 rows x 4096) and no
 // selection.  Where a second column is near a row's best (in one tile, or met in memory by the tile's atomic: of two tiles
 // with near best values the later one sees the earlier) its value is kept too; the fp32 kernel then decides for the
 // rows that end up with a near second, so that every assignment is the one that kernel makes.
 // Bound by feeding the matrix cores (LDS reads and stores take three quarters of the MFMA time beside it):
-// 32768 x 4096 x 768 (BEST) in 679 us = 303 TFLOP/s of fp32 products (910 of fp16), where the fp32 kernel's chunk of
-// 16384 took 962 us = 107 and its selection 194; 1024 x 4096 x 768 (search) 69 -> 39 us.  By its own values alone,
+// 32768 x 4096 x 768 in 679 us = 303 TFLOP/s of fp32 products (910 of fp16), where the fp32 kernel's chunk of
+// 16384 took 962 us = 107 and its selection 194.  (Not for the coarse step of searches, 1024 x 4096 x 768 69 -> 39 us: a
+// query's probes at a near tie would then depend on which kernel its call takes.)  By its own values alone,
 // 28 rows came out on the wrong side of a near tie, against 64 bits, over seven sets of 0.5 - 1 M rows
 // (64 <= d <= 1536), and 46 by the fp32 kernel's.
-template <int BM, int BN, int WM, int WN, bool BEST>
+template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(SplitGemmArgs a)
 {
     constexpr int TH = WM * WN * 64;
@@ -381,19 +382,17 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[i], bh[j], acc[i][j], 0, 0, 0);      \
         }                                                                                                  \
     }
-    [[maybe_unused]] float *const s_row = reinterpret_cast<float *>(smem + (size_t)2 * (BM + BN) * LD); // [2][BM]
+    float *const s_row = reinterpret_cast<float *>(smem + (size_t)2 * (BM + BN) * LD); // [2][BM]
     PK_FETCH(s0, 0)
     PK_FETCH(s1, 1)
     PK_PUT(s0, 0)
     PK_FETCH(s0, 2)
-    if constexpr (BEST) {
-        // per row: what turns a column's product into t (below), and how near a second value is near, in t's unit
-        if (tid < BM) {
-            const int m = m0 + tid < a.m ? m0 + tid : a.m - 1;
-            const float back = a.q_back[m], margin = a.second ? near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax)) : 0.f;
-            s_row[tid] = a.metric == PK_METRIC_L2 ? -2.f * back : -1.f;
-            s_row[BM + tid] = a.metric == PK_METRIC_L2 ? margin : margin / back;
-        }
+    // per row: what turns a column's product into t (below), and how near a second value is near, in t's unit
+    if (tid < BM) {
+        const int m = m0 + tid < a.m ? m0 + tid : a.m - 1;
+        const float back = a.q_back[m], margin = a.second ? near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax)) : 0.f;
+        s_row[tid] = a.metric == PK_METRIC_L2 ? -2.f * back : -1.f;
+        s_row[BM + tid] = a.metric == PK_METRIC_L2 ? margin : margin / back;
     }
     __syncthreads();
     for (int ks = 0; ks < steps; ks += 2) { // steps is even: rows are padded to 64 elements
@@ -418,133 +417,109 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
         cb[j] = n < a.n ? a.c_back[n] : 0.f;
         cn[j] = a.metric == PK_METRIC_L2 && n < a.n ? a.cnorm[n] : 0.f;
     }
-    if constexpr (!BEST) {
+    // t: smaller is nearer (inner product: -dot in the row's scale; L2: |c|^2 - 2 dot, the row's own norm left out)
+    uint32_t top[MI], second[MI]; // lane r of a half wave: of its row r, the best value's key, the near second's (or all ones)
+    int col[MI];
 #pragma unroll
-        for (int i = 0; i < MI; ++i) {
+    for (int i = 0; i < MI; ++i) {
+        top[i] = second[i] = 0xffffffffu;
+        col[i] = 0;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = m0 + wm * (BM / WM) + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
-                if (m >= a.m) continue;
-                const float back = a.q_back[m], qn = a.metric == PK_METRIC_L2 ? a.qnorm[m] : 0.f;
+        for (int r = 0; r < 16; ++r) {
+            const int local = wm * (BM / WM) + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
+            const float factor = s_row[local], margin = s_row[BM + local];
+            float t[NI];
+            uint32_t key[NI], low = 0xffffffffu; // (all ones: not a list; below it for every list, whatever its value)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                t[j] = fmaf(acc[i][j][r] * cb[j], factor, cn[j]);
+                key[j] = n0 + wn * (BN / WN) + j * 32 + l32 < a.n ? min(order_bits(t[j], PK_METRIC_L2), kWorstKey) : 0xffffffffu;
+                low = min(low, key[j]);
+            }
+            low = min_of_half(low);
+            const uint32_t b0 = __builtin_amdgcn_readlane(low, 31), b1 = __builtin_amdgcn_readlane(low, 63);
+            const uint32_t best = kg ? b1 : b0;
+            const float limit = value_of(best, PK_METRIC_L2) + margin;
+            int at0 = -1, at1 = -1; // column of each half's best inside the wave's part of the tile
+            uint32_t near0 = 0, near1 = 0;
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                // (a value that cannot be compared is near whatever the best is)
+                const unsigned long long eq = __ballot(key[j] == best), nr = __ballot(key[j] != 0xffffffffu && !(t[j] > limit));
+                if (at0 < 0 && (uint32_t)eq) at0 = j * 32 + __ffs((uint32_t)eq) - 1;
+                if (at1 < 0 && (uint32_t)(eq >> 32)) at1 = j * 32 + __ffs((uint32_t)(eq >> 32)) - 1;
+                near0 += (uint32_t)__popc((uint32_t)nr);
+                near1 += (uint32_t)__popc((uint32_t)(nr >> 32));
+            }
+            uint32_t next = 0xffffffffu;
+            if (near0 > 1u || near1 > 1u) { // rare (wave-uniform): the best but one
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
-                    const int n = n0 + wn * (BN / WN) + j * 32 + l32;
-                    if (n >= a.n_pad) continue;
-                    float v = acc[i][j][r] * back * cb[j];
-                    if (a.metric == PK_METRIC_L2) v = fmaxf(cn[j] - 2.f * v + qn, 0.f);
-                    if (n >= a.n) v = a.metric == PK_METRIC_IP ? -INFINITY : INFINITY;
-                    a.out[(size_t)m * a.stride + n] = v;
+                    if (j * 32 + l32 != (kg ? at1 : at0)) next = min(next, key[j]);
+                    if (key[j] != 0xffffffffu && t[j] != t[j]) next = kNoOrder;
                 }
+                next = min_of_half(next);
+                const uint32_t x0 = __builtin_amdgcn_readlane(next, 31), x1 = __builtin_amdgcn_readlane(next, 63);
+                next = kg ? x1 : x0;
+            }
+            if (l32 == r) {
+                top[i] = best;
+                col[i] = kg ? at1 : at0;
+                second[i] = next;
             }
         }
-    } else {
-        // t: smaller is nearer (inner product: -dot in the row's scale; L2: |c|^2 - 2 dot, the row's own norm left out)
-        uint32_t top[MI], second[MI]; // lane r of a half wave: of its row r, the best value's key, the near second's (or all ones)
-        int col[MI];
+    }
+    // lanes 0 .. 15 of a half wave: row r = l32 of the block
+    const int rr = kg * 4 + 8 * (l32 >> 2) + (l32 & 3);
+    const bool has = l32 < 16 && n0 + wn * (BN / WN) < a.n; // (some column of the wave's part is a list)
+    uint32_t met[MI], mine[MI];
 #pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            top[i] = second[i] = 0xffffffffu;
-            col[i] = 0;
+    for (int i = 0; i < MI; ++i) {
+        const int m = m0 + wm * (BM / WM) + i * 32 + rr;
+        met[i] = mine[i] = 0xffffffffu;
+        if (!has || m >= a.m) continue;
+        float v = value_of(top[i], PK_METRIC_L2);
+        if (a.metric == PK_METRIC_IP) v = -v * a.q_back[m];
+        mine[i] = min(order_bits(v, a.metric), kWorstKey);
+        const unsigned long long k = ((unsigned long long)mine[i] << 32) | (uint32_t)(n0 + wn * (BN / WN) + col[i]);
+        met[i] = (uint32_t)(atomicMin(a.best + m, k) >> 32);
+    }
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int local = wm * (BM / WM) + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
-                const float factor = s_row[local], margin = s_row[BM + local];
-                float t[NI];
-                uint32_t key[NI], low = 0xffffffffu; // (all ones: not a list; below it for every list, whatever its value)
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    t[j] = fmaf(acc[i][j][r] * cb[j], factor, cn[j]);
-                    key[j] = n0 + wn * (BN / WN) + j * 32 + l32 < a.n ? min(order_bits(t[j], PK_METRIC_L2), kWorstKey) : 0xffffffffu;
-                    low = min(low, key[j]);
-                }
-                low = min_of_half(low);
-                const uint32_t b0 = __builtin_amdgcn_readlane(low, 31), b1 = __builtin_amdgcn_readlane(low, 63);
-                const uint32_t best = kg ? b1 : b0;
-                const float limit = value_of(best, PK_METRIC_L2) + margin;
-                int at0 = -1, at1 = -1; // column of each half's best inside the wave's part of the tile
-                uint32_t near0 = 0, near1 = 0;
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    // (a value that cannot be compared is near whatever the best is)
-                    const unsigned long long eq = __ballot(key[j] == best), nr = __ballot(key[j] != 0xffffffffu && !(t[j] > limit));
-                    if (at0 < 0 && (uint32_t)eq) at0 = j * 32 + __ffs((uint32_t)eq) - 1;
-                    if (at1 < 0 && (uint32_t)(eq >> 32)) at1 = j * 32 + __ffs((uint32_t)(eq >> 32)) - 1;
-                    near0 += (uint32_t)__popc((uint32_t)nr);
-                    near1 += (uint32_t)__popc((uint32_t)(nr >> 32));
-                }
-                uint32_t next = 0xffffffffu;
-                if (near0 > 1u || near1 > 1u) { // rare (wave-uniform): the best but one
-#pragma unroll
-                    for (int j = 0; j < NI; ++j) {
-                        if (j * 32 + l32 != (kg ? at1 : at0)) next = min(next, key[j]);
-                        if (key[j] != 0xffffffffu && t[j] != t[j]) next = kNoOrder;
-                    }
-                    next = min_of_half(next);
-                    const uint32_t x0 = __builtin_amdgcn_readlane(next, 31), x1 = __builtin_amdgcn_readlane(next, 63);
-                    next = kg ? x1 : x0;
-                }
-                if (l32 == r) {
-                    top[i] = best;
-                    col[i] = kg ? at1 : at0;
-                    second[i] = next;
-                }
-            }
-        }
-        // lanes 0 .. 15 of a half wave: row r = l32 of the block
-        const int rr = kg * 4 + 8 * (l32 >> 2) + (l32 & 3);
-        const bool has = l32 < 16 && n0 + wn * (BN / WN) < a.n; // (some column of the wave's part is a list)
-        uint32_t met[MI], mine[MI];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            const int m = m0 + wm * (BM / WM) + i * 32 + rr;
-            met[i] = mine[i] = 0xffffffffu;
-            if (!has || m >= a.m) continue;
-            float v = value_of(top[i], PK_METRIC_L2);
+    for (int i = 0; i < MI; ++i) {
+        const int m = m0 + wm * (BM / WM) + i * 32 + rr;
+        if (!a.second || !has || m >= a.m) continue;
+        uint32_t other = max(met[i], mine[i]); // (all ones: none met)
+        if (second[i] == kNoOrder) {
+            other = kNoOrder;
+        } else if (second[i] != 0xffffffffu) {
+            float v = value_of(second[i], PK_METRIC_L2);
             if (a.metric == PK_METRIC_IP) v = -v * a.q_back[m];
-            mine[i] = min(order_bits(v, a.metric), kWorstKey);
-            const unsigned long long k = ((unsigned long long)mine[i] << 32) | (uint32_t)(n0 + wn * (BN / WN) + col[i]);
-            met[i] = (uint32_t)(atomicMin(a.best + m, k) >> 32);
+            other = min(other, min(order_bits(v, a.metric), kWorstKey));
         }
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            const int m = m0 + wm * (BM / WM) + i * 32 + rr;
-            if (!a.second || !has || m >= a.m) continue;
-            uint32_t other = max(met[i], mine[i]); // (all ones: none met)
-            if (second[i] == kNoOrder) {
-                other = kNoOrder;
-            } else if (second[i] != 0xffffffffu) {
-                float v = value_of(second[i], PK_METRIC_L2);
-                if (a.metric == PK_METRIC_IP) v = -v * a.q_back[m];
-                other = min(other, min(order_bits(v, a.metric), kWorstKey));
-            }
-            if (other == 0xffffffffu) continue;
-            const float gap = fabsf(value_of(other, a.metric) - value_of(min(met[i], mine[i]), a.metric));
-            if (gap > near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax))) continue;
-            atomicMin(a.second + m, gap == gap ? other : kNoOrder);
-        }
+        if (other == 0xffffffffu) continue;
+        const float gap = fabsf(value_of(other, a.metric) - value_of(min(met[i], mine[i]), a.metric));
+        if (gap > near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax))) continue;
+        atomicMin(a.second + m, gap == gap ? other : kNoOrder);
     }
 }
 
-template <int BM, int BN, int WM, int WN, bool BEST>
+template <int BM, int BN, int WM, int WN>
 static hipError_t launch_split_one(const SplitGemmArgs &a, hipStream_t s)
 {
     static LdsCleared cleared;
     const uint32_t tiles = (uint32_t)((a.n_pad + BN - 1) / BN) * (uint32_t)((a.m + BM - 1) / BM);
-    return launch_with_lds(&gemm_split_kernel<BM, BN, WM, WN, BEST>, cleared, 2 * (BM + BN) * 144 + 2 * BM * 4, a, (int)tiles, WM * WN * 64, s);
+    return launch_with_lds(&gemm_split_kernel<BM, BN, WM, WN>, cleared, 2 * (BM + BN) * 144 + 2 * BM * 4, a, (int)tiles, WM * WN * 64, s);
 }
 
 hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 {
     if (a.m <= 0) return hipSuccess;
-    if (a.ld % 64 != 0 || a.n < 1 || a.n > a.n_pad || (a.best == nullptr) == (a.out == nullptr) ||
-        (a.second && !(a.best && a.cmax && a.qnorm))) return hipErrorInvalidValue;
+    if (a.ld % 64 != 0 || a.n < 1 || a.n > a.n_pad || !a.best || (a.second && !(a.cmax && a.qnorm))) return hipErrorInvalidValue;
     auto tiles = [&](int b) { return (int64_t)((a.m + b - 1) / b) * ((a.n_pad + b - 1) / b); };
     // the largest tile that still gives every CU one
-    if (tiles(256) >= num_cu)
-        return a.best ? launch_split_one<256, 256, 2, 4, true>(a, s) : launch_split_one<256, 256, 2, 4, false>(a, s);
-    if (tiles(128) >= num_cu)
-        return a.best ? launch_split_one<128, 128, 2, 2, true>(a, s) : launch_split_one<128, 128, 2, 2, false>(a, s);
-    return a.best ? launch_split_one<64, 64, 2, 2, true>(a, s) : launch_split_one<64, 64, 2, 2, false>(a, s);
+    if (tiles(256) >= num_cu) return launch_split_one<256, 256, 2, 4>(a, s);
+    if (tiles(128) >= num_cu) return launch_split_one<128, 128, 2, 2>(a, s);
+    return launch_split_one<64, 64, 2, 2>(a, s);
 }
 
 // The fp32 products of a few listed rows (a.list, *a.nlisted of them: dense rows of a.d floats) with every column, in

@@ -554,7 +554,7 @@ hipError_t launch_gemm_scores(const GemmArgs &a, hipStream_t s);
 hipError_t launch_gemm_near_ties(const GemmArgs &a, const uint32_t *second, const uint32_t *cmax, uint32_t *list, uint32_t *nlisted,
                                  int num_cu, hipStream_t s);
 
-// the same scores with every fp32 operand held as two halfs (see pk_gemm.hip)
+// top-1 of the same products, every fp32 operand held as two halfs (see pk_gemm.hip)
 struct SplitRowsArgs {
     const float *x;      // [m][d] rows, dense
     const float *c;      // [n_c][ld] centroid table, zero padded
@@ -576,11 +576,9 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &m, hipStre
 struct SplitGemmArgs {
     const char *q, *c;   // split rows [m][4 * ld], [n_pad][4 * ld]
     const float *q_back, *c_back, *qnorm, *cnorm; // (norms: L2 only)
-    float *out;          // [m][stride] scores, or null:
     unsigned long long *best; // [m] best (value key << 32 | column) by atomicMin; ~0 on entry
     int m, n, n_pad, ld, metric;
-    uint32_t stride;
-    // with best, optional: the value key of the second best column where it is near the best (else all ones, as on entry)
+    // optional: the value key of the second best column where it is near the best (else all ones, as on entry)
     uint32_t *second;         // [m] (or null: no row's near ties are of interest)
     const uint32_t *cmax;     // largest squared norm of the centroids (as bits)
 };

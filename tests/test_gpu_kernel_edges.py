@@ -143,10 +143,37 @@ def test_rows_without_a_comparable_score_go_to_some_list(gpu_device, nlist, kind
         assert int(assign.min()) >= 0 and int(assign.max()) < nlist
 
 
+@pytest.mark.parametrize("metric,storage,d", [(IP, F32, 100), (L2, F16, 64)])
+def test_probes_of_near_tied_lists_do_not_depend_on_the_call(gpu_device, metric, storage, d):
+    """Centroids in pairs that differ in the last bits, and one probe, so that rounding decides which of a pair is
+    searched: one handle's search, the same segment in a call over two handles, and a search of the probes that the
+    coarse step gives alone have the same rows, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(d)
+    half, n, nq, nprobe = 1030, 400000, 1024, 1
+
+    def around(m):
+        at = torch.randint(half, (m,), device="cuda", generator=g)
+        return c[at] + 0.5 * torch.randn((m, d), device="cuda", generator=g)
+
+    c = torch.randn((half, d), device="cuda", generator=g)
+    cent = torch.cat([c, c * (1 + torch.randint(-2, 3, c.shape, device="cuda", generator=g) * 2.0 ** -23)])
+    x, q = around(n), around(nq + 70)
+    a, b = B.Index(cent, x, metric=metric, storage=storage), B.Index(cent, x, metric=metric, storage=storage)
+    try:
+        ids, dist = a.search(q[:nq], 10, nprobe)
+        mi, md = B.search_multi([a, b], [0, nq, nq + 70], q, 10, nprobe)
+        assert torch.equal(ids, mi[:nq]) and torch.equal(dist, md[:nq])
+        ci, cd = a.scan_probes(q[:nq], 10, a.coarse(q[:nq], nprobe))
+        assert torch.equal(ids, ci) and torch.equal(dist, cd)
+    finally:
+        a.close()
+        b.close()
+
+
 @pytest.mark.parametrize("nq,storage,metric,d", [(1024, F16, L2, 100), (1024, F32, IP, 128), (999, F32, L2, 70), (128, F16, IP, 64)])
-def test_searches_through_the_split_gemm(gpu_device, nq, storage, metric, d):
-    """Batches with 128 tiles or more of 128 x 128 scores, against the oracle: every storage's own query copy is made
-    in the pass that splits the rows."""
+def test_searches_whose_coarse_step_is_a_gemm(gpu_device, nq, storage, metric, d):
+    """Batches with 128 tiles or more of 128 x 128 scores, against the oracle; both copies of a half-precision memory's
+    queries are made in one pass."""
     cfg = W.scaled(W.C1, n=20000, d=d, nlist=16384 if nq == 128 else 2050, ncomp=64, train="lloyd", train_iters=0)
     rng = np.random.default_rng(d)
     x = W.vectors(cfg, 0, cfg.n)
@@ -161,7 +188,7 @@ def test_searches_through_the_split_gemm(gpu_device, nq, storage, metric, d):
         assert torch.equal(gi[some.tolist()], fi) and torch.equal(gv[some.tolist()], fv)
         op, sc = p.orc.coarse(q[some], 17, with_scores=True)
         assert np.mean(op[:, :16] == probes[some]) > 0.99
-        p.check_scan(q[some], 10, probes[some], where="split gemm")
+        p.check_scan(q[some], 10, probes[some], where="gemm")
     finally:
         p.close()
 
