@@ -101,7 +101,7 @@ struct pk_index {
     // small inserts: top-1 keys of the batch (kept at ~0 between calls) and the slots the batch got
     unsigned long long *ins_best; // DEVICE [kInsertFast]
     uint32_t *ins_slots;          // DEVICE [kInsertFast]
-    uint32_t *del_words;          // DEVICE [8] counters of pk_delete (the first is zero between calls)
+    uint32_t *del_words;          // DEVICE [8] counters of pk_delete (the first is zero between calls); [6] what no centroid's squared norm exceeds
     // second stream of a search whose lists fall into two tile classes: the kernel for the lists many
     // queries probe is bound by the matrix cores and runs on some of the CUs while the HBM-bound scan of
     // the other lists has the rest (fork and join by events; default priority)
@@ -1223,32 +1223,41 @@ int assign_few(const float *x, int64_t m, const Table &t, int num_cu, char *rows
 }
 
 // An insert's vectors go through the split-operand GEMM from as many scores on as it takes to beat the centroid kernel,
-// whose time grows with the vectors while the GEMM's small tiles run side by side.  Whole inserts, centroid kernel against
-// GEMM: 256 x 512 lists x 1024 27 and 30 us, 256 x 1024 x 768 35 and 30, 65 x 2048 x 1536 54 and 41, 1000 x 512 x 1024
-// 49 and 40.  (Near ties are left as they come out: its scores are nearer the exact ones than the centroid kernel's.)
-// Against a score matrix, a selection and groups of 1024 one after the other, 2000 x 512 x 1024 went from 159 to 48 us.
-constexpr int64_t kInsertScores = 3 << 16;
-constexpr int64_t kInsertProducts = 150000000; // (wide rows: earlier)
+// whose time grows with the vectors while the GEMM's small tiles run side by side, the sooner the more lists there are.
+// Rows whose best two lists are near go to the centroid kernel all the same, so that no vector's list depends on how many
+// came with it (8 - 12 us of the GEMM's times).  Whole inserts, vectors x lists x dimensions, centroid kernel and GEMM, us:
+//   512 x 512 x 1024 33 and 42, 1000 x 512 x 1024 47 and 44, 1000 x 512 x 128 27 and 29, 2000 x 512 x 128 39 and 33,
+//   128 x 1024 x 768 27 and 32, 256 x 1024 x 768 34 and 32, 65 x 2048 x 384 39 and 28, 65 x 4096 x 300 50 and 31,
+//   4000 x 64 x 128 41 and 38, 8000 x 64 x 128 59 and 54; 2000 x 512 x 1024 74 and 57.
+constexpr double kInsertScores = 5e5, kInsertScoresByLists = 2e8; // (the second: scores times lists)
 bool insert_by_gemm(const pk_index *ix, int64_t m)
 {
-    return m * (int64_t)ix->nlist_pad >= kInsertScores || m * (int64_t)ix->nlist_pad * ix->dpad32 >= kInsertProducts;
+    const double scores = (double)m * ix->nlist_pad;
+    return scores >= kInsertScores || scores * ix->nlist_pad >= kInsertScoresByLists;
 }
 
 // Workspace of an insert of m vectors into one handle.
 struct InsertScratch {
-    unsigned long long *best;
-    char *xs, *cs;
-    float *xback, *cback;
+    unsigned long long *best, *redo;
+    char *xs, *cs, *rows; // rows: fp32, padded (null: the caller's can be read as they are)
+    float *xback, *cback, *norm;
     int32_t *lists;
-    uint32_t *ranks, *slots;
+    uint32_t *ranks, *slots, *second;
     size_t lay(char *base, const pk_index *ix, int64_t m)
     {
         Carver c{base, 0};
         best = c.take<unsigned long long>((size_t)m);
         xs = c.take<char>((size_t)m * ix->rb32);
         xback = c.take<float>((size_t)m);
-        cs = c.take<char>(insert_by_gemm(ix, m) ? (size_t)ix->nlist_pad * ix->rb32 : 0);
+        const bool gemm = insert_by_gemm(ix, m), raw = ix->cfg.metric == PK_METRIC_IP && ix->cfg.d * 4 == ix->rb32;
+        cs = c.take<char>(gemm ? (size_t)ix->nlist_pad * ix->rb32 : 0);
         cback = c.take<float>((size_t)ix->nlist_pad);
+        redo = c.take<unsigned long long>(gemm ? (size_t)m : 0);
+        norm = c.take<float>(gemm ? (size_t)m : 0);
+        second = c.take<uint32_t>(gemm ? (size_t)m : 0);
+        rows = c.take<char>(gemm && !raw ? (size_t)m * ix->rb32 : 0);
+        if (!gemm || raw) rows = nullptr;
+        if (!gemm) redo = nullptr;
         lists = c.take<int32_t>((size_t)m);
         ranks = c.take<uint32_t>((size_t)m);
         slots = c.take<uint32_t>((size_t)m);
@@ -1397,13 +1406,19 @@ int insert_batch(pk_index *const *hs, int nh, const uint32_t *qlo, const float *
             sr.cs = is.cs;
             sr.x_back = is.xback;
             sr.c_back = is.cback;
+            sr.qnorm = is.norm;
+            sr.copy = reinterpret_cast<float *>(is.rows);
             sr.best = is.best;
+            sr.redo = is.redo;
+            sr.second = is.second;
+            sr.cmax = own->del_words + 6;
             PK_HIP(launch_split_rows(sr, mm, s));
             SplitGemmArgs g{};
             g.q = is.xs;
             g.c = is.cs;
             g.q_back = is.xback;
             g.c_back = is.cback;
+            g.qnorm = is.norm;
             g.cnorm = own->host.cnorm;
             g.best = is.best;
             g.m = (int)m;
@@ -1411,14 +1426,28 @@ int insert_batch(pk_index *const *hs, int nh, const uint32_t *qlo, const float *
             g.n_pad = own->nlist_pad;
             g.ld = own->dpad32;
             g.metric = own->cfg.metric;
+            g.second = is.second;
+            g.cmax = own->del_words + 6;
             PK_HIP(launch_gemm_split(g, own->num_cu, s));
+            CentroidArgs ca{};
+            ca.qs = is.rows ? is.rows : reinterpret_cast<const char *>(x);
+            ca.qnorm = is.norm;
+            ca.row_bytes = own->rb32;
+            ca.metric = own->cfg.metric;
+            ca.best = is.redo;
+            ca.near_best = is.best;
+            ca.second = is.second;
+            ca.cmax = own->del_words + 6;
+            ca.near_lists = is.lists;
+            PK_HIP(launch_centroid_near(ca, mm, own->nlist_pad, s));
         } else {
             const Table table{own->dev, own->host.cent, own->host.cnorm, own->cfg.nlist, own->nlist_pad, own->cfg.d, own->dpad32,
                               own->cfg.metric};
             if (m <= kInsertFast) is.best = own->ins_best; // holds ~0 between calls: nothing to clear first
             PK_TRY(assign_few(x, m, table, own->num_cu, is.xs, is.xback, is.best, m > kInsertFast, s));
         }
-        PK_HIP(launch_reserve(mm, nullptr, is.best, is.lists, is.ranks, is.slots, assigned_out, s));
+        PK_HIP(launch_reserve(mm, is.redo ? is.lists : nullptr, is.redo ? nullptr : is.best, is.redo, is.lists, is.ranks, is.slots,
+                              assigned_out, s));
         PK_HIP(launch_append(mm, idc, x, ids, is.lists, is.slots, is.best == own->ins_best ? own->ins_best : nullptr, s));
         return note_inserted(own, m, s);
     }
@@ -1438,7 +1467,7 @@ int insert_batch(pk_index *const *hs, int nh, const uint32_t *qlo, const float *
     if (small) {
         PK_HIP(launch_reserve_append(mm, idc, x, ids, assign, nullptr, slots, assigned_out, s));
     } else {
-        PK_HIP(launch_reserve(mm, assign, nullptr, nullptr, ranks, slots, assigned_out, s));
+        PK_HIP(launch_reserve(mm, assign, nullptr, nullptr, nullptr, ranks, slots, assigned_out, s));
         PK_HIP(launch_append(mm, idc, x, ids, assign, slots, nullptr, s));
     }
     for (int a = 0; a < nh; ++a) PK_TRY(note_inserted(hs[a], (int64_t)(qlo[a + 1] - qlo[a]), s));

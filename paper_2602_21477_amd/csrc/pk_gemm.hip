@@ -239,11 +239,14 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     const float back = __uint_as_float((uint32_t)(127 - s) << 23);
     if (cent) {
         a.c_back[r] = back;
-        if (a.cmax) atomicMax(a.cmax, __float_as_uint(norm)); // (squares: their bits are in the order of the values)
+        // (squares: their bits are in the order of the values; a look first, as every row's atomic meets the others' at one word)
+        if (a.cmax && __hip_atomic_load(a.cmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < __float_as_uint(norm))
+            atomicMax(a.cmax, __float_as_uint(norm));
         return;
     }
     if (a.x_back) a.x_back[r] = back;
     if (a.second) a.second[r] = 0xffffffffu;
+    if (a.redo) a.redo[r] = ~0ull;
     if (a.qnorm) a.qnorm[r] = norm;
     if (a.half_rows) a.half_norm[r] = norm16;
     if (a.best) a.best[r] = ~0ull;
@@ -276,19 +279,6 @@ __device__ __forceinline__ uint32_t min_of_half(uint32_t x)
 #undef PK_DPP_MIN
     return x;
 }
-
-// Two values of a row closer than this are told apart by the fp32 kernel.  The fp32 sum of ld products, two at a time,
-// is off by about 2^-25 sqrt(ld / 2) of |x| |c| in one standard deviation (measured: 1e-6 |x|^2 between two L2 values
-// at 768 elements), the split's by a third of it; 2^-21 sqrt(ld) is twenty of them.
-__device__ __forceinline__ float near_margin(int ld, int metric, float qn, float cmax)
-{
-    return 4.76837158e-7f * sqrtf((float)ld) * (metric == PK_METRIC_L2 ? qn + cmax : sqrtf(qn) * sqrtf(cmax));
-}
-
-// Rows whose values cannot all be compared (a NaN among them: from a NaN or an infinity in the row or in a centroid, or
-// from finite values whose products overflow) are decided by the fp32 kernel too: their second value is kNoOrder.
-constexpr uint32_t kNoOrder = 0u;           // below the key of every number
-constexpr uint32_t kWorstKey = 0xfffffffeu; // the most a list's key can be, so that all ones stays "no list"
 
 // BM x BN output tile per workgroup of WM x WN waves; K in steps of 32 elements (128 bytes of a split row) through
 // double-buffered LDS, fetched two steps ahead through two register stages (a step is short: 12 MFMAs of 32 cycles per
@@ -623,10 +613,7 @@ __global__ __launch_bounds__(256) void near_ties_kernel(GemmArgs a, const uint32
         const uint32_t i = i0 + threadIdx.x;
         bool near = false;
         if (i < (uint32_t)a.m) {
-            const uint32_t s = second[i];
-            near = s == kNoOrder ||
-                   (s != 0xffffffffu && !(fabsf(value_of(s, a.metric) - value_of((uint32_t)(a.best[i] >> 32), a.metric)) >
-                                          near_margin(a.ld, a.metric, a.qnorm[i], __uint_as_float(*cmax))));
+            near = near_tie(a.best[i], second[i], a.ld, a.metric, a.qnorm[i], __uint_as_float(*cmax));
         }
         const unsigned long long m = __ballot(near);
         if (m == 0ull) continue;

@@ -143,7 +143,7 @@ hipError_t launch_scatter_build(const DevIndex *ix, const float *x, const int64_
 // last one (top bit).  A wave per vector over the group's lists: the same counts by one workgroup, a thread per
 // vector, were 32 of the 38 us that reserving 1000 slots took.  Also turns the top-1 keys into lists (assign_out).
 __global__ __launch_bounds__(256) void insert_rank_kernel(MultiArgs ma, const int32_t *assign, const unsigned long long *best,
-                                                          int32_t *assign_out, uint32_t *ranks)
+                                                          const unsigned long long *redo, int32_t *assign_out, uint32_t *ranks)
 {
     const uint32_t i = blockIdx.x * 4u + (threadIdx.x >> 6), lane = threadIdx.x & 63u;
     if (i >= ma.qlo[ma.n]) return;
@@ -152,7 +152,9 @@ __global__ __launch_bounds__(256) void insert_rank_kernel(MultiArgs ma, const in
     const uint32_t row0 = ma.qlo[h], g0 = row0 + (i - row0) / kInsertGroup * kInsertGroup;
     const uint32_t g1 = g0 + kInsertGroup < ma.qlo[h + 1] ? g0 + kInsertGroup : ma.qlo[h + 1];
     auto list_of = [&](uint32_t j) { return best ? (int32_t)(uint32_t)best[j] : assign[j]; };
-    const int32_t l = list_of(i);
+    auto open = [&](int32_t l) { return redo && l == kListByRedo; }; // (one of many)
+    int32_t l = list_of(i);
+    if (open(l)) l = (int32_t)(uint32_t)redo[i];
     uint32_t before = 0, after = 0;
     constexpr int U = 4; // requests in flight
     for (uint32_t j0 = g0 + lane; j0 < g1; j0 += 64u * U) {
@@ -162,6 +164,7 @@ __global__ __launch_bounds__(256) void insert_rank_kernel(MultiArgs ma, const in
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const uint32_t j = j0 + 64u * u;
+            if (open(o[u])) o[u] = (int32_t)(uint32_t)redo[j];
             before += o[u] == l && j < i ? 1u : 0u;
             after += o[u] == l && j > i ? 1u : 0u;
         }
@@ -172,7 +175,7 @@ __global__ __launch_bounds__(256) void insert_rank_kernel(MultiArgs ma, const in
     }
     if (lane == 0) {
         ranks[i] = before | (after == 0u ? 0x80000000u : 0u);
-        if (best) assign_out[i] = l;
+        if (best || redo) assign_out[i] = l;
     }
 }
 
@@ -278,12 +281,12 @@ __global__ __launch_bounds__(1024) void reserve_kernel(MultiArgs ma, const int32
     if (best && !assign && (int)threadIdx.x < m) best[row0 + threadIdx.x] = ~0ull;
 }
 
-hipError_t launch_reserve(const MultiArgs &ma, const int32_t *assign, const unsigned long long *best, int32_t *lists,
-                          uint32_t *ranks, uint32_t *slots, int32_t *assigned_out, hipStream_t s)
+hipError_t launch_reserve(const MultiArgs &ma, const int32_t *assign, const unsigned long long *best,
+                          const unsigned long long *redo, int32_t *lists, uint32_t *ranks, uint32_t *slots, int32_t *assigned_out, hipStream_t s)
 {
     if (ma.n <= 0 || ma.qlo[ma.n] == 0) return hipSuccess;
-    if ((assign == nullptr) == (best == nullptr) || !ranks || (best && !lists)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(insert_rank_kernel, dim3((ma.qlo[ma.n] + 3) / 4), dim3(256), 0, s, ma, assign, best, lists, ranks);
+    if ((assign == nullptr) == (best == nullptr) || !ranks || (best && !lists) || (redo && assign != lists)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(insert_rank_kernel, dim3((ma.qlo[ma.n] + 3) / 4), dim3(256), 0, s, ma, assign, best, redo, lists, ranks);
     hipLaunchKernelGGL(reserve_kernel<true>, dim3(ma.n), dim3(1024), 0, s, ma, best ? lists : assign, ranks, nullptr, slots, assigned_out,
                        AppendIds{}, nullptr, nullptr);
     return hipGetLastError();

@@ -446,7 +446,15 @@ struct CentroidArgs {
     //   atomicMin (top-1 assignment of inserts; best[] must hold ~0 on entry).
     QueryMeta meta;
     unsigned long long *best;
+    // launch_centroid_near (one handle): of the rows whose best two values (near_best[], second[]: as the split GEMM
+    // left them) are near, best[] is found, and near_lists[] is kListByRedo; of the others it is near_best's list.
+    // qnorm is given whatever the metric
+    const unsigned long long *near_best;
+    const uint32_t *second, *cmax;
+    int32_t *near_lists;
+    uint32_t parts;      // workgroups that share a group of 64 rows
 };
+hipError_t launch_centroid_near(CentroidArgs a, const MultiArgs &m, int nlist_pad, hipStream_t s);
 hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hipStream_t s);
 
 // merge of per-handle result rows into one row per query (k <= 1024: rank fits 10 bits, handle 7)
@@ -554,6 +562,27 @@ hipError_t launch_gemm_scores(const GemmArgs &a, hipStream_t s);
 hipError_t launch_gemm_near_ties(const GemmArgs &a, const uint32_t *second, const uint32_t *cmax, uint32_t *list, uint32_t *nlisted,
                                  int num_cu, hipStream_t s);
 
+// Two values of a row closer than this are told apart by the fp32 kernel.  The fp32 sum of ld products, two at a time,
+// is off by about 2^-25 sqrt(ld / 2) of |x| |c| in one standard deviation (measured: 1e-6 |x|^2 between two L2 values
+// at 768 elements), the split's by a third of it; 2^-21 sqrt(ld) is twenty of them.
+__device__ __forceinline__ float near_margin(int ld, int metric, float qn, float cmax)
+{
+    return 4.76837158e-7f * sqrtf((float)ld) * (metric == PK_METRIC_L2 ? qn + cmax : sqrtf(qn) * sqrtf(cmax));
+}
+
+// Rows whose values cannot all be compared (a NaN among them: from a NaN or an infinity in the row or in a centroid, or
+// from finite values whose products overflow) are decided by the fp32 kernel too: their second value is kNoOrder.
+constexpr uint32_t kNoOrder = 0u;           // below the key of every number
+constexpr uint32_t kWorstKey = 0xfffffffeu; // the most a list's key can be, so that all ones stays "no list"
+
+// whether a row with that best (value key << 32 | column) and that second value goes to the fp32 kernels
+__device__ __forceinline__ bool near_tie(unsigned long long best, uint32_t second, int ld, int metric, float qn, float cmax)
+{
+    if (second == kNoOrder || second == 0xffffffffu) return second == kNoOrder;
+    const float gap = fabsf(value_of(second, metric) - value_of((uint32_t)(best >> 32), metric));
+    return !(gap > near_margin(ld, metric, qn, cmax));
+}
+
 // top-1 of the same products, every fp32 operand held as two halfs (see pk_gemm.hip)
 struct SplitRowsArgs {
     const float *x;      // [m][d] rows, dense
@@ -569,6 +598,7 @@ struct SplitRowsArgs {
     int half_bytes;
     unsigned long long *best; // [m] set to ~0, or null
     uint32_t *second;    // [m] set to all ones, or null
+    unsigned long long *redo; // [m] set to ~0, or null
     uint32_t *cmax;      // raised to the largest squared norm of the centroids (as bits), or null
     QueryMeta meta;      // as in launch_prep_coarse, one handle (cand_off null: not wanted)
 };
@@ -671,8 +701,10 @@ struct AppendIds {
     int64_t id0[PK_MAX_HANDLES]; // first id of each handle's segment when the caller gives no ids
 };
 // the lists are assign[], or the low words of best[] (written to lists[]); ranks: scratch like slots
-hipError_t launch_reserve(const MultiArgs &ma, const int32_t *assign, const unsigned long long *best, int32_t *lists,
-                          uint32_t *ranks, uint32_t *slots, int32_t *assigned_out, hipStream_t s);
+// (redo, with assign = lists: entries that are kListByRedo are the low words of redo[], and written, too)
+constexpr int32_t kListByRedo = -1;
+hipError_t launch_reserve(const MultiArgs &ma, const int32_t *assign, const unsigned long long *best,
+                          const unsigned long long *redo, int32_t *lists, uint32_t *ranks, uint32_t *slots, int32_t *assigned_out, hipStream_t s);
 hipError_t launch_append(const MultiArgs &ma, const AppendIds &idc, const float *x, const int64_t *ids,
                          const int32_t *assign, const uint32_t *slots, unsigned long long *reset, hipStream_t s);
 // assign == null: the lists are the low words of best[] (left by the centroid kernel), which is reset to ~0

@@ -783,7 +783,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // contraction index, so each wave streams a quarter of every row (centroids and queries
 // alike come straight from global memory / L2 in MFMA operand layout, no LDS staging), and
 // the four partial accumulators meet in LDS.  Output: out[query * stride + centroid].
-template <int MT, int WAVES>
+// NEAR: of 64 rows only those whose assignment is a near tie, 16 at a time, and only their best.  Usually there is none
+// and the workgroup is done after one look: of 2000 rows against 512 x 1024 a handful are near ties, 10.8 us.
+template <int MT, int WAVES, bool NEAR>
 __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArgs a, MultiArgs m)
 {
     __shared__ float s_red[WAVES][MT][4][64];
@@ -793,23 +795,52 @@ __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArg
     while (h + 1 < m.n && blockIdx.x >= a.blk[h + 1]) ++h;
     const DevIndex &ix = *m.ix[h];
     const uint32_t nblk = (uint32_t)ix.nlist_pad / 16u;
-    const uint32_t local = blockIdx.x - a.blk[h];
-    const uint32_t qc = local / nblk, cb = local - qc * nblk;
-    const uint32_t q0 = m.qlo[h] + qc * (uint32_t)(MT * 16);
+    const uint32_t local = blockIdx.x - a.blk[h], across = NEAR ? a.parts : nblk;
+    const uint32_t qc = local / across;
+    uint32_t cb = local - qc * across; // block of 16 centroids
+    const uint32_t q0 = m.qlo[h] + qc * (NEAR ? 64u : (uint32_t)(MT * 16));
     const uint32_t left = m.qlo[h + 1] - q0;
-    const uint32_t qcnt = left < (uint32_t)(MT * 16) ? left : (uint32_t)(MT * 16);
-    const int mt_used = (int)((qcnt + 15u) >> 4);
     const int row_bytes = a.row_bytes;
+    uint32_t qcnt = left < (uint32_t)(MT * 16) ? left : (uint32_t)(MT * 16);
+    __shared__ uint32_t s_rows[NEAR ? 16 : 1]; // NEAR: the rows in the slots
+    [[maybe_unused]] unsigned long long near = 0ull; // NEAR: the rows still to do (the same in every wave)
+    if constexpr (NEAR) {
+        bool mine = false;
+        if ((uint32_t)lane < left) {
+            const uint32_t q = q0 + (uint32_t)lane;
+            const unsigned long long key = a.near_best[q];
+            mine = near_tie(key, a.second[q], row_bytes / 4, a.metric, a.qnorm[q], __uint_as_float(*a.cmax));
+            if (cb == 0 && wave == 0) a.near_lists[q] = mine ? kListByRedo : (int32_t)(uint32_t)key;
+        }
+        near = __ballot(mine);
+        if (near == 0ull) return;
+    }
+    do { // (NEAR: 16 rows at a time, else once)
+    if constexpr (NEAR) {
+        const uint32_t rank = (uint32_t)__popcll(near & ((1ull << lane) - 1ull));
+        const bool now = (near >> lane & 1ull) != 0ull && rank < 16u;
+        if (wave == 0 && now) s_rows[rank] = q0 + (uint32_t)lane;
+        near &= ~__ballot(now);
+        qcnt = (uint32_t)__popcll(__ballot(now));
+        __syncthreads();
+    }
+    auto row_of = [&](uint32_t slot) {
+        if constexpr (NEAR) return s_rows[slot];
+        else return q0 + slot;
+    };
+    const int mt_used = (int)((qcnt + 15u) >> 4);
     const int nit = row_bytes / kIterBytes;
     const int per = (nit + WAVES - 1) / WAVES;
     const int it0 = wave * per, it1 = it0 + per < nit ? it0 + per : nit;
-    const char *xp = reinterpret_cast<const char *>(ix.cent) + (size_t)(cb * 16u + ln) * row_bytes + lg * 16;
     const char *qp[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const uint32_t slot = (uint32_t)(mt * 16 + ln);
-        qp[mt] = slot < qcnt ? a.qs + (size_t)(q0 + slot) * row_bytes + lg * 16 : nullptr;
+        qp[mt] = slot < qcnt ? a.qs + (size_t)row_of(slot) * row_bytes + lg * 16 : nullptr;
     }
+    cb = local - qc * across;
+    do { // (NEAR: every a.parts-th block of centroids, else one)
+    const char *xp = reinterpret_cast<const char *>(ix.cent) + (size_t)(cb * 16u + ln) * row_bytes + lg * 16;
     f32x4 acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -863,7 +894,7 @@ __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArg
         const uint32_t slot = (uint32_t)(mt * 16 + lg * 4 + i);
         if (slot >= qcnt || c >= (uint32_t)ix.nlist) continue;
         float v = partial_sum(mt);
-        if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[q0 + slot], 0.f);
+        if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[row_of(slot)], 0.f);
         if (!a.best) a.out[(size_t)(q0 + slot) * a.stride + c] = v;
     }
     if (a.best) {
@@ -875,7 +906,7 @@ __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArg
             unsigned long long key = ~0ull;
             if (slot < qcnt && c < (uint32_t)ix.nlist) {
                 float v = partial_sum(mt);
-                if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[q0 + slot], 0.f);
+                if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[row_of(slot)], 0.f);
                 key = ((unsigned long long)order_bits(v, a.metric) << 32) | c;
             }
 #pragma unroll
@@ -883,15 +914,19 @@ __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArg
                 const unsigned long long o = __shfl_xor(key, off);
                 key = o < key ? o : key;
             }
-            if (ln == 0 && slot < qcnt && key != ~0ull) atomicMin(a.best + q0 + slot, key);
+            if (ln == 0 && slot < qcnt && key != ~0ull) atomicMin(a.best + row_of(slot), key);
         }
     }
     } // wave < 4
-    if (a.meta.cand_off) {
+    if constexpr (NEAR) __syncthreads(); // s_red and s_rows are written again
+    cb += across;
+    } while (NEAR && cb < nblk);
+    } while (NEAR && near != 0ull);
+    if (!NEAR && a.meta.cand_off) {
         // bookkeeping of the coarse step (otherwise done while the queries are prepared); last, so that no
         // load of this kernel queues behind these stores
         for (uint32_t i = blockIdx.x * blockDim.x + tid; i < a.meta.nclear; i += gridDim.x * blockDim.x) a.meta.clear[i] = 0u;
-        if (cb == 0 && (uint32_t)tid < qcnt) {
+        if (cb == across && (uint32_t)tid < qcnt) { // the first block's workgroup
             const uint32_t t = q0 + (uint32_t)tid;
             a.meta.cand_off[t] = t * a.meta.stride;
             a.meta.cand_cnt[t] = (uint32_t)ix.nlist;
@@ -908,10 +943,10 @@ static hipError_t launch_centroid_mt(const CentroidArgs &a, const MultiArgs &m, 
     static_assert(MT >= 1, "");
     if (MT == 1 && a.row_bytes / kIterBytes >= 16) {
         // one group of queries over long rows: eight waves share the row, so that each has few slices in a row to wait for
-        hipLaunchKernelGGL((centroid_scores_kernel<1, 8>), dim3(a.blk[m.n]), dim3(512), 0, s, a, m);
+        hipLaunchKernelGGL((centroid_scores_kernel<1, 8, false>), dim3(a.blk[m.n]), dim3(512), 0, s, a, m);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((centroid_scores_kernel<MT, 4>), dim3(a.blk[m.n]), dim3(256), 0, s, a, m);
+    hipLaunchKernelGGL((centroid_scores_kernel<MT, 4, false>), dim3(a.blk[m.n]), dim3(256), 0, s, a, m);
     return hipGetLastError();
 }
 
@@ -926,6 +961,25 @@ hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hip
     case 64: return launch_centroid_mt<4>(a, m, s);
     default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_centroid_near(CentroidArgs a, const MultiArgs &m, int nlist_pad, hipStream_t s)
+{
+    if (m.n != 1 || a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || !a.best || !a.near_best || !a.second || !a.cmax || !a.qnorm ||
+        !a.near_lists)
+        return hipErrorInvalidValue;
+    const uint32_t rows = m.qlo[1] - m.qlo[0];
+    if (rows == 0) return hipSuccess;
+    a.chunk = 16;
+    // a workgroup without a near tie costs its launch, one with some 3 us per block of centroids (2000 rows, 512 lists x 1024:
+    // 16 parts 14.0 us, 32 10.8)
+    const uint32_t parts = std::max(8u, std::min(64u, 1024u / ((rows + 63u) / 64u)));
+    a.parts = std::min((uint32_t)nlist_pad / 16u, parts);
+    a.blk[0] = 0;
+    a.blk[1] = (rows + 63u) / 64u * a.parts;
+    if (a.row_bytes / kIterBytes >= 16) hipLaunchKernelGGL((centroid_scores_kernel<1, 8, true>), dim3(a.blk[1]), dim3(512), 0, s, a, m);
+    else hipLaunchKernelGGL((centroid_scores_kernel<1, 4, true>), dim3(a.blk[1]), dim3(256), 0, s, a, m);
+    return hipGetLastError();
 }
 
 int scan_lds_bytes(int row_bytes, int mq)

@@ -170,6 +170,42 @@ def test_probes_of_near_tied_lists_do_not_depend_on_the_call(gpu_device, metric,
         b.close()
 
 
+def near_pairs(d, half, apart, seed):
+    """Centroids in pairs `apart` lists from each other that differ in the last bits, and a source of rows around them."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    c = torch.randn((half, d), device="cuda", generator=g)
+    twin = c * (1 + torch.randint(-2, 3, c.shape, device="cuda", generator=g) * 2.0 ** -23)
+    cent = torch.empty((2 * half, d), device="cuda")
+    at = torch.arange(half, device="cuda")
+    at = at // apart * (2 * apart) + at % apart  # blocks of `apart` centroids (a divisor of half), each followed by its twins
+    cent[at], cent[at + apart] = c, twin
+
+    def around(m):
+        return c[torch.randint(half, (m,), device="cuda", generator=g)] + 0.5 * torch.randn((m, d), device="cuda", generator=g)
+
+    return cent, around
+
+
+@pytest.mark.parametrize("metric,d,half,apart", [(IP, 128, 128, 1), (L2, 100, 130, 130), (L2, 64, 256, 64), (IP, 33, 1100, 1100)])
+def test_near_tied_vectors_go_to_the_same_lists_in_inserts_of_any_size(gpu_device, metric, d, half, apart):
+    """Every vector has two lists that differ in the last bits of their scores, in one tile or in two: an insert large
+    enough for the split GEMM takes the ones that inserts of 64 (fp32 throughout) and calls over handles take."""
+    cent, around = near_pairs(d, half, apart, half)
+    x = around(4097)
+    a, b, c = (B.Index(cent, None, metric=metric, insert_reserve=9000) for _ in range(3))
+    try:
+        large = a.insert(x, want_lists=True)
+        small = torch.cat([b.insert(x[i:i + 64].contiguous(), want_lists=True) for i in range(0, len(x), 64)])
+        assert torch.equal(large, small)
+        if 8 * ((2 * half + 127) // 128) < 128:  # (with more lists, segments of 1000 take their scores from the fp32 GEMM)
+            multi = torch.empty(2000, dtype=torch.int32, device="cuda")
+            B.pk_insert_multi([b.handle, c.handle], [0, 1000, 2000], x[:2000].contiguous(), None, multi)
+            assert torch.equal(multi, small[:2000])
+    finally:
+        for ix in (a, b, c):
+            ix.close()
+
+
 @pytest.mark.parametrize("nq,storage,metric,d", [(1024, F16, L2, 100), (1024, F32, IP, 128), (999, F32, L2, 70), (128, F16, IP, 64)])
 def test_searches_whose_coarse_step_is_a_gemm(gpu_device, nq, storage, metric, d):
     """Batches with 128 tiles or more of 128 x 128 scores, against the oracle; both copies of a half-precision memory's
@@ -214,8 +250,8 @@ def test_thresholds_from_several_sample_pages(gpu_device, n, d, nlist, nprobe, k
 
 @pytest.mark.parametrize("metric,storage,d,nlist,page", [(IP, F32, 128, 40, 0), (L2, F16, 70, 260, 32), (IP, F32, 64, 9000, 64)])
 def test_inserts_around_the_sizes_where_their_path_changes(gpu_device, metric, storage, d, nlist, page):
-    """One group and several (1024), the centroid kernel and the GEMM (3 * 2^16 scores), and rows of one batch that
-    meet in one list: every list ends up with its members in the order in which they came."""
+    """One group and several (1024), the centroid kernel and the GEMM (500 000 scores, or fewer over many lists), and rows
+    of one batch that meet in one list: every list ends up with its members in the order in which they came."""
     rng = np.random.default_rng(d + nlist)
     x = rng.standard_normal((12000, d)).astype(np.float32)
     if storage == F16:
