@@ -1170,7 +1170,7 @@ int note_inserted(pk_index *ix, int64_t m, hipStream_t s)
 struct AssignScratch {
     char *xs, *cs;
     float *xback, *cback, *norm;
-    uint32_t *second, *listed, *words; // words: [0] rows in listed[], [1] largest squared centroid norm
+    uint32_t *second, *listed, *words; // words: [0] rows in listed[], [1] largest squared centroid norm, [2] rows of the first chunk in listed[]
     void lay(Carver &c, int64_t n, int64_t chunk, int nlist_pad, int rb32)
     {
         xs = c.take<char>((size_t)chunk * rb32);
@@ -1180,7 +1180,7 @@ struct AssignScratch {
         norm = c.take<float>((size_t)n);
         second = c.take<uint32_t>((size_t)n);
         listed = c.take<uint32_t>((size_t)n);
-        words = c.take<uint32_t>(2);
+        words = c.take<uint32_t>(3);
     }
 };
 
@@ -1268,7 +1268,9 @@ struct InsertScratch {
 // Top-1 assignment of n vectors (Section 3.1: the list of the best centroid): best[i] = (score key << 32 | list), by
 // the scores of the fp32 GEMM.  The split-operand GEMM finds them, two launches per chunk and no score matrix, and the
 // fp32 kernel goes over the few rows whose best two are near; a last chunk that cannot fill tiles (coarse_tiles) takes
-// the centroid kernel, as an insert of its size does.
+// the centroid kernel, as an insert of its size does.  Where most rows of the first chunk are near ties (lists given
+// twice; data whose common offset is large beside its spread) the others go to the fp32 kernel whole: it takes three and
+// a half times as long as the split GEMM, so that the two together are the longer way from five rows in seven on.
 int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const AssignScratch &as, int64_t chunk,
                 unsigned long long *best, hipStream_t s)
 {
@@ -1276,7 +1278,25 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
     const int64_t by_gemm = tail > 0 && !coarse_tiles((uint32_t)tail, t.nlist_pad) ? n - tail : n;
     MultiArgs mm;
     std::memset(&mm, 0, sizeof(mm));
-    PK_HIP(launch_fill_u32(as.words, 0u, 2, s));
+    PK_HIP(launch_fill_u32(as.words, 0u, 3, s));
+    const uint32_t skip_from = (uint32_t)(std::min(chunk, by_gemm) / 7 * 5);
+    auto list_near = [&](int64_t first, int64_t last, bool start) {
+        NearTiesArgs nt{};
+        nt.first = (uint32_t)first;
+        nt.last = (uint32_t)last;
+        nt.best = best;
+        nt.second = as.second;
+        nt.cmax = as.words + 1;
+        nt.qnorm = as.norm;
+        nt.skipped = start ? nullptr : as.words + 2;
+        nt.skip_from = skip_from;
+        nt.list = as.listed;
+        nt.nlisted = as.words;
+        nt.also = start ? as.words + 2 : nullptr;
+        nt.ld = t.ld;
+        nt.metric = t.metric;
+        return launch_near_ties(nt, num_cu, s);
+    };
     for (int64_t i0 = 0; i0 < by_gemm; i0 += chunk) {
         const int64_t m = std::min<int64_t>(chunk, by_gemm - i0);
         SplitRowsArgs sr{};
@@ -1310,9 +1330,13 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
         g.metric = t.metric;
         g.second = as.second + i0;
         g.cmax = as.words + 1;
+        g.skipped = i0 > 0 ? as.words + 2 : nullptr;
+        g.skip_from = skip_from;
         PK_HIP(launch_gemm_split(g, num_cu, s));
+        if (i0 == 0) PK_HIP(list_near(0, m, true));
     }
     if (by_gemm > 0) {
+        PK_HIP(list_near(std::min(chunk, by_gemm), by_gemm, false));
         GemmArgs g{};
         g.q = x;
         g.c = t.cent;
@@ -1327,8 +1351,7 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
         g.nlisted = as.words;
         g.best = best;
         g.d = t.d;
-        g.m = (int)by_gemm;
-        PK_HIP(launch_gemm_near_ties(g, as.second, as.words + 1, as.listed, as.words, num_cu, s));
+        PK_HIP(launch_gemm_listed(g, num_cu, s));
     }
     if (by_gemm < n) {
         PK_TRY(assign_few(x + (size_t)by_gemm * t.d, tail, t, num_cu, as.xs, as.xback, best + by_gemm, true, s));

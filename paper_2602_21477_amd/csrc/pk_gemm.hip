@@ -27,17 +27,108 @@ constexpr int kGemmTile = 128;
 constexpr int kGemmBK = 32;               // floats per K step
 constexpr int kGemmLdsStride = kGemmBK + 4; // floats; +4 keeps the b128 reads conflict free
 
+// tiles of the kernel for few listed rows: 32 rows x 128 columns each
+constexpr int kListRows = 32, kListCols = 128;
+__device__ __forceinline__ uint32_t listed_tiles(uint32_t rows, int n_pad)
+{
+    return (rows + kListRows - 1) / kListRows * ((uint32_t)(n_pad + kListCols - 1) / kListCols);
+}
+
+// four floats of a dense row of d (at: column 0 of the thread's pieces), from column `first` + scol on, zeros past its end
+__device__ __forceinline__ f32x4 dense_piece(const float *at, int first, int scol, int d, bool vec)
+{
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (vec) { // rows of whole 16-byte pieces
+        if (first + scol < d) v = *reinterpret_cast<const f32x4 *>(at + first);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (first + scol + j < d) v[j] = at[first + j];
+    }
+    return v;
+}
+
+// Smallest of the 32 lanes of each half wave, in the half's last lane (31 and 63): data-parallel moves only, where a
+// butterfly over shuffles would go through LDS (the epilogue took a third of the kernel that way).
+__device__ __forceinline__ uint32_t min_of_half(uint32_t x)
+{
+#define PK_DPP_MIN(ctrl, rows) x = min(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, rows, 0xf, false));
+    PK_DPP_MIN(0x111, 0xf) // row_shr 1, 2, 4, 8: lane 15 of every 16 has their smallest
+    PK_DPP_MIN(0x112, 0xf)
+    PK_DPP_MIN(0x114, 0xf)
+    PK_DPP_MIN(0x118, 0xf)
+    PK_DPP_MIN(0x142, 0xa) // row_bcast 15: into the second and fourth 16 lanes
+#undef PK_DPP_MIN
+    return x;
+}
+
+// A wave's 64 x 64 scores (blocks of 32 x 32: lane l of a half wave holds column l of the rows kg * 4 + 8 * (r / 4) + r % 4)
+// into the best (value key, column) of the listed rows.
+__device__ __forceinline__ void best_of_tile(const GemmArgs &a, const f32x16 (&acc)[2][2], int m0, int n0, int rows, int lane)
+{
+    const int l32 = lane & 31, kg = lane >> 5;
+    if (n0 >= a.n) return; // (the same for the whole wave)
+    float cn[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int n = n0 + j * 32 + l32;
+        cn[j] = a.metric == PK_METRIC_L2 && n < a.n ? a.cnorm[n] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int rr = kg * 4 + 8 * ((l32 & 15) >> 2) + (l32 & 3); // the row that lanes 0 .. 15 of a half wave answer for
+        uint32_t top = 0xffffffffu;
+        int col = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int m = m0 + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
+            const float qn = a.metric == PK_METRIC_L2 && m < rows ? a.qnorm[a.list[m]] : 0.f;
+            uint32_t key[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                float v = acc[i][j][r];
+                if (a.metric == PK_METRIC_L2) v = fmaxf(cn[j] - 2.f * v + qn, 0.f);
+                key[j] = n0 + j * 32 + l32 < a.n ? min(order_bits(v, a.metric), kWorstKey) : 0xffffffffu;
+            }
+            const uint32_t low = min_of_half(min(key[0], key[1]));
+            const uint32_t b0 = __builtin_amdgcn_readlane(low, 31), b1 = __builtin_amdgcn_readlane(low, 63);
+            const uint32_t best = kg ? b1 : b0;
+            const unsigned long long e0 = __ballot(key[0] == best), e1 = __ballot(key[1] == best);
+            const uint32_t h0 = (uint32_t)(kg ? e0 >> 32 : e0), h1 = (uint32_t)(kg ? e1 >> 32 : e1);
+            if (l32 == r) {
+                top = best;
+                col = h0 ? __ffs(h0) - 1 : 32 + __ffs(h1) - 1;
+            }
+        }
+        const int m = m0 + i * 32 + rr;
+        if (l32 < 16 && m < rows) atomicMin(a.best + a.list[m], ((unsigned long long)top << 32) | (uint32_t)(n0 + col));
+    }
+}
+
+// LISTED: the rows are those of a list on the device (a.list, *a.nlisted of them, dense rows of a.d floats), and every row
+// keeps its best (value key, column) by atomicMin instead of its scores; the grid walks the tiles there are.  For lists
+// that fill tiles (see gemm_listed_kernel): 262 144 listed rows x 4096 x 768
+// in 18.0 ms = 92 TFLOP/s, where the kernel for few of them took 82.
+template <bool LISTED>
 __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 {
+    const int rows = LISTED ? (int)*a.nlisted : a.m;
+    const uint32_t tn = (uint32_t)(a.n_pad + kGemmTile - 1) / kGemmTile;
+    if constexpr (LISTED)
+        if (listed_tiles((uint32_t)rows, a.n_pad) <= a.many) return;
+    [[maybe_unused]] const uint32_t tiles = tn * ((uint32_t)(rows + kGemmTile - 1) / kGemmTile);
+    [[maybe_unused]] const bool vec = LISTED && (a.d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
     __shared__ __align__(16) float sA[2][kGemmTile * kGemmLdsStride];
     __shared__ __align__(16) float sB[2][kGemmTile * kGemmLdsStride];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;        // wave's 64 x 64 quadrant
     const int l32 = lane & 31, kg = lane >> 5;      // MFMA row / column and k group
-    const int m0 = blockIdx.y * kGemmTile, n0 = blockIdx.x * kGemmTile;
     const int ld = a.ld;                            // floats per row, multiple of 64
     const int ksteps = ld / kGemmBK;
 
+    [[maybe_unused]] uint32_t t = blockIdx.x;
+    do {
+    const int m0 = (int)(LISTED ? t / tn : blockIdx.y) * kGemmTile, n0 = (int)(LISTED ? t % tn : blockIdx.x) * kGemmTile;
     // global -> register staging: each thread moves 4 x 16 B of A and of B per K step
     // row = (tid >> 3) + 32 * i, 16-byte column = tid & 7
     const int srow = tid >> 3, scol = (tid & 7) * 4;
@@ -45,9 +136,9 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         int ra = m0 + srow + 32 * i, rb = n0 + srow + 32 * i;
-        ra = ra < a.m ? ra : a.m - 1; // clamp: rows past the end are computed and dropped
+        ra = ra < rows ? ra : rows - 1; // clamp: rows past the end are computed and dropped
         rb = rb < a.n_pad ? rb : a.n_pad - 1;
-        ga[i] = a.q + (size_t)ra * ld + scol;
+        ga[i] = a.q + (LISTED ? (size_t)a.list[ra] * a.d : (size_t)ra * ld) + scol;
         gb[i] = a.c + (size_t)rb * ld + scol;
     }
     f32x4 ra4[4], rb4[4];
@@ -62,8 +153,9 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #define PK_GLOAD(ks)                                                                     \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                        \
     {                                                                                    \
-        ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK);       \
         rb4[i] = *reinterpret_cast<const f32x4 *>(gb[i] + (size_t)(ks) * kGemmBK);       \
+        if constexpr (LISTED) ra4[i] = dense_piece(ga[i], (ks) * kGemmBK, scol, a.d, vec); \
+        else ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK);  \
     }
 #define PK_LSTORE(buf)                                                                                   \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                        \
@@ -104,6 +196,11 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #undef PK_GLOAD
 #undef PK_LSTORE
 
+    if constexpr (LISTED) {
+        best_of_tile(a, acc, m0 + wm * 64, n0 + wn * 64, rows, lane);
+        t += gridDim.x;
+        continue;
+    }
     // epilogue: lane holds column n = l32 of rows (kg*4 + 8*(r/4) + r%4) of each 32 x 32 block
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -125,6 +222,7 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
             }
         }
     }
+    } while (LISTED && t < tiles);
 }
 
 hipError_t launch_gemm_scores(const GemmArgs &a, hipStream_t s)
@@ -132,7 +230,7 @@ hipError_t launch_gemm_scores(const GemmArgs &a, hipStream_t s)
     if (a.m <= 0) return hipSuccess;
     if (a.ld % 64 != 0) return hipErrorInvalidValue;
     dim3 grid((a.n_pad + kGemmTile - 1) / kGemmTile, (a.m + kGemmTile - 1) / kGemmTile);
-    hipLaunchKernelGGL(gemm_scores_kernel, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(gemm_scores_kernel<false>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -266,20 +364,6 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStr
     return hipGetLastError();
 }
 
-// Smallest of the 32 lanes of each half wave, in the half's last lane (31 and 63): data-parallel moves only, where a
-// butterfly over shuffles would go through LDS (the epilogue took a third of the kernel that way).
-__device__ __forceinline__ uint32_t min_of_half(uint32_t x)
-{
-#define PK_DPP_MIN(ctrl, rows) x = min(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, rows, 0xf, false));
-    PK_DPP_MIN(0x111, 0xf) // row_shr 1, 2, 4, 8: lane 15 of every 16 has their smallest
-    PK_DPP_MIN(0x112, 0xf)
-    PK_DPP_MIN(0x114, 0xf)
-    PK_DPP_MIN(0x118, 0xf)
-    PK_DPP_MIN(0x142, 0xa) // row_bcast 15: into the second and fourth 16 lanes
-#undef PK_DPP_MIN
-    return x;
-}
-
 // BM x BN output tile per workgroup of WM x WN waves; K in steps of 32 elements (128 bytes of a split row) through
 // double-buffered LDS, fetched two steps ahead through two register stages (a step is short: 12 MFMAs of 32 cycles per
 // 32 x 32 x 2 blocks, and the operands come from L2).  Every row keeps its best (value key, column) by atomicMin
@@ -303,6 +387,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     static_assert((BM * 8) % TH == 0 && (BN * 8) % TH == 0, "a thread's piece is of A or of B for the whole workgroup");
     constexpr int ALOADS = BM * 8 / TH;
     extern __shared__ __align__(16) char smem[]; // [2][BM + BN][LD]
+    if (a.skipped && *a.skipped > a.skip_from) return; // near ties are the rule: the fp32 kernel takes these rows whole
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int l32 = lane & 31, kg = lane >> 5;
@@ -517,8 +602,9 @@ hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 // column) by atomicMin.  Usually some hundred rows: bound by the latency of one tile, so a tile is 32 x 128 (a wave
 // 32 x 32: 16 MFMAs per step of 32 elements), its operands are requested two steps ahead, and the grid walks the tiles
 // there are.  As a form of the 128 x 128 kernel it took 210 us for whatever few rows there were; now 27 us for those of
-// 26 000 x 640 against 253 columns, 129 us for those of 262 144 x 768 against 4096.
-constexpr int kListRows = 32, kListCols = 128;
+// 26 000 x 640 against 253 columns, 129 us for those of 262 144 x 768 against 4096.  Lists of more than a.many tiles (two
+// rounds of the grid, then longer than one round of 128 x 128 tiles) are gemm_scores_kernel<true>'s, and one of the two
+// launches ends at once.
 __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
 {
     __shared__ __align__(16) float sA[2][kListRows * kGemmLdsStride];
@@ -527,6 +613,7 @@ __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
     const int l32 = lane & 31, kg = lane >> 5;
     const int ld = a.ld, ksteps = ld / kGemmBK; // even: rows are padded to 64 floats
     const int rows = (int)*a.nlisted;
+    if (listed_tiles((uint32_t)rows, a.n_pad) > a.many) return;
     const bool vec = (a.d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
     const uint32_t tn = (uint32_t)(a.n_pad + kListCols - 1) / kListCols, tm = (uint32_t)(rows + kListRows - 1) / kListRows;
     const int srow = tid >> 3, scol = (tid & 7) * 4;
@@ -548,14 +635,7 @@ __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
             const int at = (ks < ksteps ? ks : ksteps - 1) * kGemmBK; // (past the last step the last one again)
 #pragma unroll
             for (int i = 0; i < 4; ++i) rb[i] = *reinterpret_cast<const f32x4 *>(gb[i] + at);
-            ra = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (vec) { // the caller's rows: no padding, any alignment
-                if (at + scol < a.d) ra = *reinterpret_cast<const f32x4 *>(ga + at);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (at + scol + j < a.d) ra[j] = ga[at + j];
-            }
+            ra = dense_piece(ga, at, scol, a.d, vec); // the caller's rows: no padding, any alignment
         };
         auto put = [&](const f32x4 &ra, const f32x4 (&rb)[4], int buf) {
             *reinterpret_cast<f32x4 *>(&sA[buf][srow * kGemmLdsStride + scol]) = ra;
@@ -604,37 +684,46 @@ __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
     }
 }
 
-// Rows whose second best value is near the best: into the list, their best[] back to "none yet".
-__global__ __launch_bounds__(256) void near_ties_kernel(GemmArgs a, const uint32_t *second, const uint32_t *cmax, uint32_t *list,
-                                                        uint32_t *nlisted)
+// Rows whose second best value is near the best: into the list, their best[] back to "none yet".  Where the split GEMM
+// left the rows out (skipped), all of them.
+__global__ __launch_bounds__(256) void near_ties_kernel(NearTiesArgs a)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    for (uint32_t i0 = blockIdx.x * 256u; i0 < (uint32_t)a.m; i0 += gridDim.x * 256u) {
+    const bool all = a.skipped && *a.skipped > a.skip_from;
+    for (uint32_t i0 = a.first + blockIdx.x * 256u; i0 < a.last; i0 += gridDim.x * 256u) {
         const uint32_t i = i0 + threadIdx.x;
         bool near = false;
-        if (i < (uint32_t)a.m) {
-            near = near_tie(a.best[i], second[i], a.ld, a.metric, a.qnorm[i], __uint_as_float(*cmax));
-        }
+        if (i < a.last)
+            near = all || near_tie(a.best[i], a.second[i], a.ld, a.metric, a.qnorm[i], __uint_as_float(*a.cmax));
         const unsigned long long m = __ballot(near);
         if (m == 0ull) continue;
         uint32_t at = 0;
-        if (lane == 0) at = atomicAdd(nlisted, (uint32_t)__popcll(m));
+        if (lane == 0) {
+            at = atomicAdd(a.nlisted, (uint32_t)__popcll(m));
+            if (a.also) atomicAdd(a.also, (uint32_t)__popcll(m));
+        }
         at = __shfl(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
         if (near) {
-            list[at] = i;
+            a.list[at] = i;
             a.best[i] = ~0ull;
         }
     }
 }
 
-hipError_t launch_gemm_near_ties(const GemmArgs &a, const uint32_t *second, const uint32_t *cmax, uint32_t *list, uint32_t *nlisted,
-                                 int num_cu, hipStream_t s)
+hipError_t launch_near_ties(const NearTiesArgs &a, int num_cu, hipStream_t s)
 {
-    if (a.m <= 0) return hipSuccess;
-    if (a.ld % 64 != 0 || a.d > a.ld || !a.best || a.list != list || a.nlisted != nlisted) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(near_ties_kernel, dim3((uint32_t)std::min((a.m + 255) / 256, 4 * num_cu)), dim3(256), 0, s, a, second, cmax,
-                       list, nlisted);
+    if (a.last <= a.first) return hipSuccess;
+    if (a.ld % 64 != 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(near_ties_kernel, dim3(std::min((a.last - a.first + 255u) / 256u, 4u * (uint32_t)num_cu)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_listed(GemmArgs a, int num_cu, hipStream_t s)
+{
+    if (a.ld % 64 != 0 || a.d > a.ld || !a.best || !a.list || !a.nlisted) return hipErrorInvalidValue;
+    a.many = 6u * (uint32_t)num_cu;
     hipLaunchKernelGGL(gemm_listed_kernel, dim3(3 * num_cu), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(gemm_scores_kernel<true>, dim3(2 * num_cu), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

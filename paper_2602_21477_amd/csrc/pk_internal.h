@@ -552,15 +552,26 @@ struct GemmArgs {
     float *out;          // [m][stride]
     int m, n, n_pad, n_store, ld, metric;
     uint32_t stride;
-    // launch_gemm_near_ties (m rows): q are the caller's dense rows [.][d], qnorm and best indexed by row like them
+    // launch_gemm_listed: q are the caller's dense rows [.][d], qnorm and best indexed by row like them
     const uint32_t *list, *nlisted; // rows to score, and how many (on the device)
     unsigned long long *best;       // [.] out: best (value key << 32 | column) of the listed rows
     int d;
+    uint32_t many;                  // (set by launch_gemm_listed)
 };
 hipError_t launch_gemm_scores(const GemmArgs &a, hipStream_t s);
-// rows whose second best value (second[]: as the split GEMM left it) is near their best: listed, and decided in fp32
-hipError_t launch_gemm_near_ties(const GemmArgs &a, const uint32_t *second, const uint32_t *cmax, uint32_t *list, uint32_t *nlisted,
-                                 int num_cu, hipStream_t s);
+hipError_t launch_gemm_listed(GemmArgs a, int num_cu, hipStream_t s); // the same values, of listed rows: their best columns
+// rows whose second best value (second[]: as the split GEMM left it) is near their best, into a list
+struct NearTiesArgs {
+    uint32_t first, last;        // rows [first, last) of best, second, qnorm
+    unsigned long long *best;    // of the listed rows: back to ~0
+    const uint32_t *second, *cmax;
+    const float *qnorm;
+    const uint32_t *skipped;     // or null: more than skip_from in it and the rows are listed all, whatever best and second hold
+    uint32_t skip_from;
+    uint32_t *list, *nlisted, *also; // also (or null): raised as nlisted is
+    int ld, metric;
+};
+hipError_t launch_near_ties(const NearTiesArgs &a, int num_cu, hipStream_t s);
 
 // Two values of a row closer than this are told apart by the fp32 kernel.  The fp32 sum of ld products, two at a time,
 // is off by about 2^-25 sqrt(ld / 2) of |x| |c| in one standard deviation (measured: 1e-6 |x|^2 between two L2 values
@@ -611,6 +622,8 @@ struct SplitGemmArgs {
     // optional: the value key of the second best column where it is near the best (else all ones, as on entry)
     uint32_t *second;         // [m] (or null: no row's near ties are of interest)
     const uint32_t *cmax;     // largest squared norm of the centroids (as bits)
+    const uint32_t *skipped;  // or null: with more than skip_from in it the launch does nothing
+    uint32_t skip_from;
 };
 hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s);
 

@@ -170,20 +170,47 @@ def test_probes_of_near_tied_lists_do_not_depend_on_the_call(gpu_device, metric,
         b.close()
 
 
-def near_pairs(d, half, apart, seed):
-    """Centroids in pairs `apart` lists from each other that differ in the last bits, and a source of rows around them."""
+def near_pairs(d, half, apart, seed, every=1):
+    """Centroids in pairs `apart` lists from each other, and a source of rows around them.  Those of one pair in `every`
+    differ in the last bits."""
     g = torch.Generator(device="cuda").manual_seed(seed)
     c = torch.randn((half, d), device="cuda", generator=g)
     twin = c * (1 + torch.randint(-2, 3, c.shape, device="cuda", generator=g) * 2.0 ** -23)
     cent = torch.empty((2 * half, d), device="cuda")
     at = torch.arange(half, device="cuda")
     at = at // apart * (2 * apart) + at % apart  # blocks of `apart` centroids (a divisor of half), each followed by its twins
+    twin = torch.where(at[:, None] % every == 0, twin, torch.randn((half, d), device="cuda", generator=g))
     cent[at], cent[at + apart] = c, twin
 
     def around(m):
         return c[torch.randint(half, (m,), device="cuda", generator=g)] + 0.5 * torch.randn((m, d), device="cuda", generator=g)
 
     return cent, around
+
+
+@pytest.mark.parametrize("n,metric,d,half,apart,every", [
+    (16384, IP, 100, 128, 1, 1),  # every row is a near tie: large tiles of listed rows
+    (16384, L2, 64, 130, 130, 1),  # ... of lists in different tiles
+    (2 * 32768 + 16384 + 70, IP, 33, 96, 32, 1),  # ... found out in the first chunk, a last one that fills no tiles
+    (2 * 32768 + 5, L2, 128, 300, 300, 1),
+    (32768 + 16384, L2, 100, 192, 1, 3),  # one in three: the second chunk takes the split GEMM, too
+    (16384, IP, 64, 512, 512, 200),  # a few hundred rows: small tiles of listed rows
+    (16384 + 3, L2, 36, 600, 600, 150)])
+def test_near_tied_rows_of_a_build_go_where_the_fp32_scores_say(gpu_device, n, metric, d, half, apart, every):
+    """Centroids that differ in the last bits of their scores: the lists are those of the fp32 coarse step, row for row."""
+    cent, around = near_pairs(d, half, apart, n + d, every)
+    x = around(n)
+    ix = B.Index(cent, x, metric=metric)
+    try:
+        where = torch.from_numpy(lists_of(ix, n))
+        want = torch.cat([ix.coarse(x[i:i + 16384].contiguous(), 1)[:, 0].cpu() for i in range(0, n, 16384)])
+        assert torch.equal(where, want.long())
+    finally:
+        ix.close()
+    if metric == L2:
+        assign = torch.empty(n, dtype=torch.int32, device="cuda")
+        B.pk_kmeans(x, cent.clone(), 1, assign)
+        assert torch.equal(assign.cpu(), want)
 
 
 @pytest.mark.parametrize("metric,d,half,apart", [(IP, 128, 128, 1), (L2, 100, 130, 130), (L2, 64, 256, 64), (IP, 33, 1100, 1100)])
