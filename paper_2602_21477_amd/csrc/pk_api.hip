@@ -897,7 +897,7 @@ int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, i
     f.hist = sa.use_hist && p.hot_from > 0 ? p.hist : nullptr; // (the rows-in-registers kernel does not count: looser, not wrong)
     f.tlo = p.tlo;
     f.tinv = p.tinv;
-    if (p.rescues > 0) PK_HIP(launch_rescue(f, m, p.nq, 2 * own->num_cu, s));
+    if (p.rescues > 0) PK_HIP(launch_rescue(f, m, p.nq, rescue_grid(own->num_cu, p.rescues), s));
     PK_HIP(launch_select_final(f, m, p.nq, s));
     if (timed) PK_TRY(mark(own, s));
     return PK_OK;

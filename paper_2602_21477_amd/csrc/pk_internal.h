@@ -415,6 +415,8 @@ struct FinalArgs {
 };
 constexpr uint32_t kRescueCap = 4096;    // keys per rescue region: what the final selection takes in registers
 constexpr uint32_t kRescueRegions = 128; // most queries of a call that are rescued
+// workgroups of launch_rescue: two per CU, and one at least for every region (a device of few CUs has fewer than regions)
+inline int rescue_grid(int num_cu, uint32_t regions) { return 2 * num_cu > (int)regions ? 2 * num_cu : (int)regions; }
 hipError_t launch_rescue(const FinalArgs &a, const MultiArgs &m, int64_t nq, int grid, hipStream_t s);
 hipError_t launch_select_final(const FinalArgs &a, const MultiArgs &m, int64_t nq, hipStream_t s);
 

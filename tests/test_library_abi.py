@@ -3,6 +3,7 @@ Only host-side paths are exercised here (no kernel is launched)."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -88,3 +89,28 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(B, "LIB_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(FileNotFoundError):
         B.lib()
+
+
+def test_every_rescue_region_has_a_workgroup_on_devices_of_any_size(tmp_path):
+    """The host's rule for the launch that scores overflowed queries again, compiled by itself: a partition of few CUs
+    has fewer workgroups by CU count than a large batch has regions, and the launch refuses less than one each."""
+    root = os.path.dirname(os.path.dirname(HEADER))
+    src = tmp_path / "grid.hip"
+    src.write_text('''#include "pk_internal.h"
+#include <cstdio>
+int main()
+{
+    int bad = 0;
+    for (int cus = 1; cus <= 304; ++cus)
+        for (uint32_t regions = 1; regions <= pk::kRescueRegions; ++regions) {
+            const int grid = pk::rescue_grid(cus, regions);
+            if (grid < (int)regions || grid < 2 * cus) ++bad;
+        }
+    printf("%d bad, %d\\n", bad, pk::rescue_grid(32, 128));
+}
+''')
+    exe = tmp_path / "grid"
+    subprocess.run(["hipcc", "-O1", "-std=c++17", "--offload-arch=gfx950", "-I", os.path.join(root, "include"),
+                    "-I", os.path.join(root, "paper_2602_21477_amd", "csrc"), str(src), "-o", str(exe)], check=True,
+                   capture_output=True)
+    assert subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout == "0 bad, 128\n"
