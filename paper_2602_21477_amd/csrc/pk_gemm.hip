@@ -486,9 +486,13 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
 
     // lane holds column l32 of rows kg * 4 + 8 * (r / 4) + r % 4 of each 32 x 32 block
     float cb[NI], cn[NI];
+    uint32_t dead[NI];            // all ones for a column that is no list, the key that no list comes behind
+    unsigned long long lists[NI]; // the lanes whose column is a list
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
         const int n = n0 + wn * (BN / WN) + j * 32 + l32;
+        dead[j] = n < a.n ? 0u : 0xffffffffu;
+        lists[j] = __ballot(n < a.n);
         cb[j] = n < a.n ? a.c_back[n] : 0.f;
         cn[j] = a.metric == PK_METRIC_L2 && n < a.n ? a.cnorm[n] : 0.f;
     }
@@ -504,11 +508,11 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
             const int local = wm * (BM / WM) + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
             const float factor = s_row[local], margin = s_row[BM + local];
             float t[NI];
-            uint32_t key[NI], low = 0xffffffffu; // (all ones: not a list; below it for every list, whatever its value)
+            uint32_t key[NI], low = 0xffffffffu;
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
                 t[j] = fmaf(acc[i][j][r] * cb[j], factor, cn[j]);
-                key[j] = n0 + wn * (BN / WN) + j * 32 + l32 < a.n ? min(order_bits(t[j], PK_METRIC_L2), kWorstKey) : 0xffffffffu;
+                key[j] = order_bits(t[j], PK_METRIC_L2) | dead[j];
                 low = min(low, key[j]);
             }
             low = min_of_half(low);
@@ -520,7 +524,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
                 // (a value that cannot be compared is near whatever the best is)
-                const unsigned long long eq = __ballot(key[j] == best), nr = __ballot(key[j] != 0xffffffffu && !(t[j] > limit));
+                const unsigned long long eq = __ballot(key[j] == best), nr = __ballot(!(t[j] > limit)) & lists[j];
                 if (at0 < 0 && (uint32_t)eq) at0 = j * 32 + __ffs((uint32_t)eq) - 1;
                 if (at1 < 0 && (uint32_t)(eq >> 32)) at1 = j * 32 + __ffs((uint32_t)(eq >> 32)) - 1;
                 near0 += (uint32_t)__popc((uint32_t)nr);
@@ -531,7 +535,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
                 for (int j = 0; j < NI; ++j) {
                     if (j * 32 + l32 != (kg ? at1 : at0)) next = min(next, key[j]);
-                    if (key[j] != 0xffffffffu && t[j] != t[j]) next = kNoOrder;
+                    if (dead[j] == 0u && t[j] != t[j]) next = kNoOrder;
                 }
                 next = min_of_half(next);
                 const uint32_t x0 = __builtin_amdgcn_readlane(next, 31), x1 = __builtin_amdgcn_readlane(next, 63);
