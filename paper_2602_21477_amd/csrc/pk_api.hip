@@ -1226,10 +1226,10 @@ int assign_few(const float *x, int64_t m, const Table &t, int num_cu, char *rows
 // whose time grows with the vectors while the GEMM's small tiles run side by side, the sooner the more lists there are.
 // Rows whose best two lists are near go to the centroid kernel all the same, so that no vector's list depends on how many
 // came with it (8 - 12 us of the GEMM's times).  Whole inserts, vectors x lists x dimensions, centroid kernel and GEMM, us:
-//   512 x 512 x 1024 33 and 42, 1000 x 512 x 1024 47 and 44, 1000 x 512 x 128 27 and 29, 2000 x 512 x 128 39 and 33,
-//   128 x 1024 x 768 27 and 32, 256 x 1024 x 768 34 and 32, 65 x 2048 x 384 39 and 28, 65 x 4096 x 300 50 and 31,
-//   4000 x 64 x 128 41 and 38, 8000 x 64 x 128 59 and 54; 2000 x 512 x 1024 74 and 57.
-constexpr double kInsertScores = 5e5, kInsertScoresByLists = 2e8; // (the second: scores times lists)
+//   512 x 512 x 1024 33 and 42, 1000 x 512 x 1024 47 and 47, 1000 x 512 x 128 27 and 34, 2000 x 512 x 128 39 and 38,
+//   256 x 1024 x 768 34 and 38, 512 x 1024 x 768 42 and 43, 1000 x 1024 x 768 63 and 49, 65 x 2048 x 384 39 and 33,
+//   65 x 4096 x 300 50 and 36, 4000 x 64 x 128 41 and 43, 8000 x 64 x 128 59 and 55; 2000 x 512 x 1024 74 and 56.
+constexpr double kInsertScores = 5.2e5, kInsertScoresByLists = 2.7e8; // (the second: scores times lists)
 bool insert_by_gemm(const pk_index *ix, int64_t m)
 {
     const double scores = (double)m * ix->nlist_pad;

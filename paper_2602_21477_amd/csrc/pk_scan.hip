@@ -784,7 +784,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // alike come straight from global memory / L2 in MFMA operand layout, no LDS staging), and
 // the four partial accumulators meet in LDS.  Output: out[query * stride + centroid].
 // NEAR: of 64 rows only those whose assignment is a near tie, 16 at a time, and only their best.  Usually there is none
-// and the workgroup is done after one look: of 2000 rows against 512 x 1024 a handful are near ties, 10.8 us.
+// and the workgroup is done after one look: of 2000 rows against 512 x 1024 a handful are near ties, 9.7 us.
 template <int MT, int WAVES, bool NEAR>
 __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArgs a, MultiArgs m)
 {
@@ -970,15 +970,14 @@ hipError_t launch_centroid_near(CentroidArgs a, const MultiArgs &m, int nlist_pa
         return hipErrorInvalidValue;
     const uint32_t rows = m.qlo[1] - m.qlo[0];
     if (rows == 0) return hipSuccess;
+    // A workgroup without a near tie costs its launch, one with some 3 us per block of 16 centroids.  Four waves whatever the
+    // row: the order of the sums is that of inserts of 17 vectors and more.
+    const uint32_t groups = (rows + 63u) / 64u, blocks = (uint32_t)nlist_pad / 16u;
     a.chunk = 16;
-    // a workgroup without a near tie costs its launch, one with some 3 us per block of centroids (2000 rows, 512 lists x 1024:
-    // 16 parts 14.0 us, 32 10.8)
-    const uint32_t parts = std::max(8u, std::min(64u, 1024u / ((rows + 63u) / 64u)));
-    a.parts = std::min((uint32_t)nlist_pad / 16u, parts);
+    a.parts = std::min(blocks, std::min(64u, std::max(std::max(8u, 1024u / groups), blocks / 8u)));
     a.blk[0] = 0;
-    a.blk[1] = (rows + 63u) / 64u * a.parts;
-    if (a.row_bytes / kIterBytes >= 16) hipLaunchKernelGGL((centroid_scores_kernel<1, 8, true>), dim3(a.blk[1]), dim3(512), 0, s, a, m);
-    else hipLaunchKernelGGL((centroid_scores_kernel<1, 4, true>), dim3(a.blk[1]), dim3(256), 0, s, a, m);
+    a.blk[1] = groups * a.parts;
+    hipLaunchKernelGGL((centroid_scores_kernel<1, 4, true>), dim3(a.blk[1]), dim3(256), 0, s, a, m);
     return hipGetLastError();
 }
 
