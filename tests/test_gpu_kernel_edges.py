@@ -61,13 +61,23 @@ def test_tie_groups_of_queries_that_are_scored_again(gpu_device):
             p.close()
 
 
+def rows_by_split_gemm(n, nlist):
+    """How many of a build's rows the split GEMM takes: chunks of 16384 always fill 128 tiles of 128 x 128, a tail may not."""
+    tail = n % 16384
+    return n if tail == 0 or -(-tail // 128) * -(-nlist // 128) >= 128 else n - tail
+
+
 @pytest.mark.parametrize("metric", [IP, L2])
-@pytest.mark.parametrize("n,d,nlist,scale", [
-    (1, 1, 1, 1.0), (63, 64, 33, 1.0), (65, 100, 64, 1e-9), (257, 1536, 255, 1e12), (4097, 33, 700, 1.0), (40000, 96, 513, 1e-20)])
-def test_split_operand_assignment_is_within_fp32_of_64_bits(gpu_device, n, d, nlist, scale, metric):
+@pytest.mark.parametrize("n,d,nlist,scale,gemm", [
+    (1, 1, 1, 1.0, 0), (63, 64, 33, 1.0, 0), (65, 100, 64, 1e-9, 0), (257, 1536, 255, 1e12, 0),
+    (4097, 33, 700, 1.0, 4097), (40000, 96, 513, 1e-20, 40000), (16384, 1, 1, 1.0, 16384), (16384 + 63, 64, 33, 1.0, 16384),
+    (16384 + 65, 100, 64, 1e-9, 16384), (32768, 1536, 255, 1e12, 32768), (33000, 1500, 300, 1e-9, 32768), (5000, 70, 513, 1e12, 5000)])
+def test_split_operand_assignment_is_within_fp32_of_64_bits(gpu_device, n, d, nlist, scale, gemm, metric):
     """Rows and centroids held as two halfs each, in the three tile sizes of the kernel, with remainders in every
-    direction and rows whose scale is far from 1.  A row may only go to a list whose score is as good as the best to
-    fp32 rounding: the split's own error is below 2^-22 of |x||c|, the accumulation's below K * 2^-24 of it."""
+    direction and rows whose scale is far from 1; tails too short for it go to the centroid kernel, which keeps the same
+    bound.  A row may only go to a list whose score is as good as the best to fp32 rounding: the split's own error is
+    below 2^-22 of |x||c|, the accumulation's below K * 2^-24 of it."""
+    assert rows_by_split_gemm(n, nlist) == gemm
     rng = np.random.default_rng(n + d)
     x = (rng.standard_normal((n, d)) * np.exp(rng.standard_normal((n, 1)))).astype(np.float32)
     cent = rng.standard_normal((nlist, d)).astype(np.float32)
@@ -255,6 +265,60 @@ def test_searches_whose_coarse_step_is_a_gemm(gpu_device, nq, storage, metric, d
         p.check_scan(q[some], 10, probes[some], where="gemm")
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("n,d,storage,metric,nq,page", [
+    (300_000, 700, F32, IP, 60, 0),  # the kernel that holds whole query groups
+    (150_000, 1500, F32, L2, 40, 96),  # the kernel that stages slices of them
+    (600_000, 680, F16, L2, 60, 64), (300_000, 1500, F16, IP, 250, 0)])
+def test_rows_of_large_memories_are_read_a_line_at_a_time(gpu_device, n, d, storage, metric, nq, page):
+    """More than 768 MB of rows and a call that reads more than 256 MB of them: whole lines, past the caches, moved into
+    place between lanes.  A query alone reads less and its rows the other way: the same results, bit for bit."""
+    nlist, nprobe = 512, 24
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn((n, d), device="cuda", generator=g)
+    cent = x[torch.randperm(n, device="cuda", generator=g)[:nlist]].contiguous()
+    width = (d * (2 if storage == F16 else 4) + 255) // 256 * 256
+    assert n * width > 768 << 20 and nq * nprobe * n / nlist * width > 256 << 20 > nprobe * n / nlist * width
+    q = x[:nq] + 0.3 * torch.randn((nq, d), device="cuda", generator=g)
+    ix = B.Index(cent, x, metric=metric, storage=storage, page_vecs=page)
+    del x
+    try:
+        probes = ix.coarse(q, nprobe)  # (one probe list: a near tie may fall either way in the two kernels' coarse steps)
+        ids, dist = ix.scan_probes(q, 10, probes)
+        for i in list(range(0, nq, 7)) + [nq - 1]:
+            one_ids, one_dist = ix.scan_probes(q[i:i + 1].contiguous(), 10, probes[i:i + 1].contiguous())
+            assert torch.equal(one_ids[0], ids[i]) and torch.equal(one_dist[0], dist[i]), i
+        assert ids[:, 0].tolist() == list(range(nq)) or metric == IP  # (the row a query was made from is its nearest)
+    finally:
+        ix.close()
+
+
+def test_overflowed_queries_of_calls_over_handles_and_beside_the_rows_in_registers_kernel(gpu_device):
+    """Queries that are scored again belong to either of two handles; and in a batch whose busiest lists go to the kernel
+    that counts no candidates, beside the scan that does: the rows of regions that hold everything, bit for bit."""
+    pairs = [make_pair(W.scaled(W.C1, n=n, d=96), agent=a, metric=IP, storage=F16)[0] for a, n in enumerate((9001, 7000))]
+    cfg = W.scaled(W.C1, n=30000, ncomp=96, nlist=96)
+    hot, _ = make_pair(cfg, metric=L2, storage=F16)
+    try:
+        q = torch.cat([dev(W.queries(W.scaled(W.C1, d=96), 30, m, agent=a)) for a, m in enumerate((150, 110))])
+        qh = dev(W.queries(cfg, 40, 768))
+        gpus = [p.gpu for p in pairs]
+        calls = [(gpus[0], lambda: B.search_multi(gpus, [0, 150, 260], q, 20, 16)), (hot.gpu, lambda: hot.gpu.search(qh, 10, 6))]
+        for own, call in calls:
+            want = call()
+            for cap in (1, 48):  # (1: the fewest the library takes, k + 1)
+                B.pk_index_set_emit_cap(own.handle, cap)
+                B.pk_profile_begin(own.handle)
+                got = call()
+                pr = B.pk_profile_end(own.handle)
+                B.pk_index_set_emit_cap(own.handle, 0)
+                assert pr.overflowed > 0 or cap > 1
+                assert own is gpus[0] or pr.scan_hot_ms > 0
+                assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    finally:
+        for p in pairs + [hot]:
+            p.close()
 
 
 @pytest.mark.parametrize("n,d,nlist,nprobe,k,nq,page,storage", [
