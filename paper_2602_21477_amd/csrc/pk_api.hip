@@ -571,12 +571,13 @@ void fill_worklist_args(const Plan &p, const pk_index *own, WorklistArgs &w, Sam
     sm = SampleArgs{};
     sm.probes = p.probes;
     sm.qagent = p.qagent;
-    sm.nq = p.nq;
+    sm.nq = (int)p.nq; // (at most 32768 in a launch sequence)
     sm.nprobe = p.nprobe;
     sm.sp = p.sp;
     sm.k = p.k;
     sm.metric = own->cfg.metric;
     sm.scan_grid = p.grid_s;
+    sm.rescued = p.rescues > 0;
     sm.span = p.span;
     sm.tiles = p.stiles;
     sm.slot_query = p.sslot_q;
@@ -1458,11 +1459,12 @@ int insert_batch(pk_index *const *hs, int nh, const uint32_t *qlo, const float *
             ca.row_bytes = own->rb32;
             ca.metric = own->cfg.metric;
             ca.best = is.redo;
-            ca.near_best = is.best;
-            ca.second = is.second;
-            ca.cmax = own->del_words + 6;
-            ca.near_lists = is.lists;
-            PK_HIP(launch_centroid_near(ca, mm, own->nlist_pad, s));
+            NearRowsArgs nr{};
+            nr.split_best = is.best;
+            nr.second = is.second;
+            nr.cmax = own->del_words + 6;
+            nr.lists = is.lists;
+            PK_HIP(launch_centroid_near(ca, mm, nr, own->nlist_pad, s));
         } else {
             const Table table{own->dev, own->host.cent, own->host.cnorm, own->cfg.nlist, own->nlist_pad, own->cfg.d, own->dpad32,
                               own->cfg.metric};

@@ -448,16 +448,18 @@ struct CentroidArgs {
     //   atomicMin (top-1 assignment of inserts; best[] must hold ~0 on entry).
     QueryMeta meta;
     unsigned long long *best;
-    // launch_centroid_near (one handle): of the rows whose best two values (near_best[], second[]: as the split GEMM
-    // left them) are near, best[] is found, and near_lists[] is kListByRedo; of the others it is near_best's list.
-    // qnorm is given whatever the metric
-    const unsigned long long *near_best;
-    const uint32_t *second, *cmax;
-    int32_t *near_lists;
-    uint32_t parts;      // workgroups that share a group of 64 rows
 };
-hipError_t launch_centroid_near(CentroidArgs a, const MultiArgs &m, int nlist_pad, hipStream_t s);
 hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hipStream_t s);
+// Of the rows (of one handle) whose best two values are near, as the split GEMM left them, the best by the centroid kernel.
+// (Arguments of their own: the other launches' would be a line longer, 0.3 us of a search of one query.)
+struct NearRowsArgs {
+    const unsigned long long *split_best; // [.] the split GEMM's best (value key << 32 | list)
+    const uint32_t *second, *cmax;        // and second values; largest squared centroid norm (as bits)
+    int32_t *lists;                       // [.] out: split_best's list, or kListByRedo for a row whose best is in CentroidArgs::best
+    uint32_t parts;                       // (set by the launch) workgroups that share a group of 64 rows
+};
+// (a.best: ~0 on entry; a.qnorm is given whatever the metric)
+hipError_t launch_centroid_near(CentroidArgs a, const MultiArgs &m, NearRowsArgs n, int nlist_pad, hipStream_t s);
 
 // merge of per-handle result rows into one row per query (k <= 1024: rank fits 10 bits, handle 7)
 struct UnionArgs {
@@ -518,12 +520,13 @@ struct WorklistArgs {
 struct SampleArgs {
     const int32_t *probes;     // [nq][nprobe]
     const uint16_t *qagent;
-    int64_t nq;
+    int nq;
+    int rescued;               // queries whose region overflows may be scored again: slot_out is cleared for that
     int nprobe, sp, k, metric, scan_grid;
     uint32_t span;             // values per query = sp * rows per page (same for all handles)
     Tile *tiles;               // [nq * sp]
     uint32_t *slot_query;      // [nq] = q
-    uint32_t *slot_out;        // [nq] = q * span; once the threshold exists: 0 (the query's rescue counter)
+    uint32_t *slot_out;        // [nq] = q * span; with `rescued`, once the threshold exists: 0 (the query's rescue counter)
     float *vals;               // [nq][span], pre-filled with the padding value by the kernel
     uint32_t *scalars;         // [0] ntiles [1] tile counter [2] grab size
     uint32_t *tau;             // [nq] out: k-th best sample key, or 0xffffffff

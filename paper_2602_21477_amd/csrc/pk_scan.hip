@@ -786,7 +786,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // NEAR: of 64 rows only those whose assignment is a near tie, 16 at a time, and only their best.  Usually there is none
 // and the workgroup is done after one look: of 2000 rows against 512 x 1024 a handful are near ties, 9.7 us.
 template <int MT, int WAVES, bool NEAR>
-__global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArgs a, MultiArgs m)
+__device__ __forceinline__ void centroid_body(const CentroidArgs &a, const MultiArgs &m, [[maybe_unused]] const NearRowsArgs *nr)
 {
     __shared__ float s_red[WAVES][MT][4][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -795,7 +795,7 @@ __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArg
     while (h + 1 < m.n && blockIdx.x >= a.blk[h + 1]) ++h;
     const DevIndex &ix = *m.ix[h];
     const uint32_t nblk = (uint32_t)ix.nlist_pad / 16u;
-    const uint32_t local = blockIdx.x - a.blk[h], across = NEAR ? a.parts : nblk;
+    const uint32_t local = blockIdx.x - a.blk[h], across = NEAR ? nr->parts : nblk;
     const uint32_t qc = local / across;
     uint32_t cb = local - qc * across; // block of 16 centroids
     const uint32_t q0 = m.qlo[h] + qc * (NEAR ? 64u : (uint32_t)(MT * 16));
@@ -808,9 +808,9 @@ __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArg
         bool mine = false;
         if ((uint32_t)lane < left) {
             const uint32_t q = q0 + (uint32_t)lane;
-            const unsigned long long key = a.near_best[q];
-            mine = near_tie(key, a.second[q], row_bytes / 4, a.metric, a.qnorm[q], __uint_as_float(*a.cmax));
-            if (cb == 0 && wave == 0) a.near_lists[q] = mine ? kListByRedo : (int32_t)(uint32_t)key;
+            const unsigned long long key = nr->split_best[q];
+            mine = near_tie(key, nr->second[q], row_bytes / 4, a.metric, a.qnorm[q], __uint_as_float(*nr->cmax));
+            if (cb == 0 && wave == 0) nr->lists[q] = mine ? kListByRedo : (int32_t)(uint32_t)key;
         }
         near = __ballot(mine);
         if (near == 0ull) return;
@@ -839,7 +839,7 @@ __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArg
         qp[mt] = slot < qcnt ? a.qs + (size_t)row_of(slot) * row_bytes + lg * 16 : nullptr;
     }
     cb = local - qc * across;
-    do { // (NEAR: every a.parts-th block of centroids, else one)
+    do { // (NEAR: every parts-th block of centroids, else one)
     const char *xp = reinterpret_cast<const char *>(ix.cent) + (size_t)(cb * 16u + ln) * row_bytes + lg * 16;
     f32x4 acc[MT];
 #pragma unroll
@@ -935,6 +935,17 @@ __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArg
     }
 }
 
+template <int MT, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArgs a, MultiArgs m)
+{
+    centroid_body<MT, WAVES, false>(a, m, nullptr);
+}
+
+__global__ __launch_bounds__(256) void centroid_near_kernel(CentroidArgs a, MultiArgs m, NearRowsArgs nr)
+{
+    centroid_body<1, 4, true>(a, m, &nr);
+}
+
 // ------------------------------------------------------------------------ host side
 
 template <int MT>
@@ -943,10 +954,10 @@ static hipError_t launch_centroid_mt(const CentroidArgs &a, const MultiArgs &m, 
     static_assert(MT >= 1, "");
     if (MT == 1 && a.row_bytes / kIterBytes >= 16) {
         // one group of queries over long rows: eight waves share the row, so that each has few slices in a row to wait for
-        hipLaunchKernelGGL((centroid_scores_kernel<1, 8, false>), dim3(a.blk[m.n]), dim3(512), 0, s, a, m);
+        hipLaunchKernelGGL((centroid_scores_kernel<1, 8>), dim3(a.blk[m.n]), dim3(512), 0, s, a, m);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((centroid_scores_kernel<MT, 4, false>), dim3(a.blk[m.n]), dim3(256), 0, s, a, m);
+    hipLaunchKernelGGL((centroid_scores_kernel<MT, 4>), dim3(a.blk[m.n]), dim3(256), 0, s, a, m);
     return hipGetLastError();
 }
 
@@ -963,10 +974,10 @@ hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hip
     }
 }
 
-hipError_t launch_centroid_near(CentroidArgs a, const MultiArgs &m, int nlist_pad, hipStream_t s)
+hipError_t launch_centroid_near(CentroidArgs a, const MultiArgs &m, NearRowsArgs n, int nlist_pad, hipStream_t s)
 {
-    if (m.n != 1 || a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || !a.best || !a.near_best || !a.second || !a.cmax || !a.qnorm ||
-        !a.near_lists)
+    if (m.n != 1 || a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || !a.best || !a.qnorm || !n.split_best || !n.second || !n.cmax ||
+        !n.lists)
         return hipErrorInvalidValue;
     const uint32_t rows = m.qlo[1] - m.qlo[0];
     if (rows == 0) return hipSuccess;
@@ -974,10 +985,10 @@ hipError_t launch_centroid_near(CentroidArgs a, const MultiArgs &m, int nlist_pa
     // row: the order of the sums is that of inserts of 17 vectors and more.
     const uint32_t groups = (rows + 63u) / 64u, blocks = (uint32_t)nlist_pad / 16u;
     a.chunk = 16;
-    a.parts = std::min(blocks, std::min(64u, std::max(std::max(8u, 1024u / groups), blocks / 8u)));
+    n.parts = std::min(blocks, std::min(64u, std::max(std::max(8u, 1024u / groups), blocks / 8u)));
     a.blk[0] = 0;
-    a.blk[1] = groups * a.parts;
-    hipLaunchKernelGGL((centroid_scores_kernel<1, 4, true>), dim3(a.blk[1]), dim3(256), 0, s, a, m);
+    a.blk[1] = groups * n.parts;
+    hipLaunchKernelGGL(centroid_near_kernel, dim3(a.blk[1]), dim3(256), 0, s, a, m, n);
     return hipGetLastError();
 }
 

@@ -120,7 +120,7 @@ __device__ __forceinline__ void tau_publish(const SampleArgs &a, uint32_t q, uin
         const bool full = cnt >= (uint32_t)a.k;
         a.tau[q] = full ? kth : 0xffffffffu;
         a.tcur[q] = (uint32_t)kHistBins - 1u;
-        a.slot_out[q] = 0u; // the sample is scored: from here on the word counts the query's rescued candidates
+        if (a.rescued) a.slot_out[q] = 0u; // the sample is scored: from here on the word counts the query's rescued candidates
         float lo = 0.f, inv = 0.f;
         if (cnt > 0) {
             lo = value_of(first, a.metric);
