@@ -371,10 +371,11 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStr
 // selection.  Where a second column is near a row's best (in one tile, or met in memory by the tile's atomic: of two tiles
 // with near best values the later one sees the earlier) its value is kept too; the fp32 kernel then decides for the
 // rows that end up with a near second, so that every assignment is the one that kernel makes.
-// Bound by feeding the matrix cores (LDS reads and stores take three quarters of the MFMA time beside it):
-// 32768 x 4096 x 768 in 679 us = 303 TFLOP/s of fp32 products (910 of fp16), where the fp32 kernel's chunk of
-// 16384 took 962 us = 107 and its selection 194.  (Not for the coarse step of searches, 1024 x 4096 x 768 69 -> 39 us: a
-// query's probes at a near tie would then depend on which kernel its call takes.)  By its own values alone,
+// Bound by the chain of short steps: 256 x 256 tiles, eight waves on a CU, keep the matrix cores busy for 45 % of the cycles
+// and LDS for 20 (no bank conflicts); waves wait for memory and barriers a third of their time.  32768 x 4096 x 768 in
+// 616 - 670 us by box = 310 - 335 TFLOP/s of fp32 products, where the fp32 kernel's chunk of 16384 took 962 us = 107 and its
+// selection 194.  (Not for the coarse step of searches, 1024 x 4096 x 768 69 -> 39 us: a query's probes at a near tie would
+// then depend on which kernel its call takes.)  By its own values alone,
 // 28 rows came out on the wrong side of a near tie, against 64 bits, over seven sets of 0.5 - 1 M rows
 // (64 <= d <= 1536), and 46 by the fp32 kernel's.
 template <int BM, int BN, int WM, int WN>
