@@ -359,7 +359,7 @@ __device__ __forceinline__ const Arena &locate(const DevIndex &ix, uint32_t l, u
 // Lists are unordered sets: no tombstones, nothing for the scan to skip.  The pages a list no longer
 // reaches stay its own for later inserts.
 // All launches of a call (fills and copies of the earlier sequence included): 8 ids among 1 M rows 54 -> 23 us, 2000 ids
-// among 300 000 rows 113 -> 39; the call, with its wait, 80 -> 25 us for few ids and 102 -> 27 for 2000.
+// among 300 000 rows 113 -> 39; the calls, with their wait on the host, 89 -> 34 us and 265 -> 71 (no more than 27 where nobody carries the ids).
 
 constexpr unsigned long long kNoId = 0x8000000000000000ull; // marks a free slot of the hash set (the id of that value is kept apart)
 
