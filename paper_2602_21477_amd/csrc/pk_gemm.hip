@@ -371,9 +371,12 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStr
 // selection.  Where a second column is near a row's best (in one tile, or met in memory by the tile's atomic: of two tiles
 // with near best values the later one sees the earlier) its value is kept too; the fp32 kernel then decides for the
 // rows that end up with a near second, so that every assignment is the one that kernel makes.
-// Bound by the chain of short steps: 256 x 256 tiles, eight waves on a CU, keep the matrix cores busy for 45 % of the cycles
-// and LDS for 20 (no bank conflicts); waves wait for memory and barriers a third of their time.  32768 x 4096 x 768 in
-// 616 - 670 us by box = 310 - 335 TFLOP/s of fp32 products, where the fp32 kernel's chunk of 16384 took 962 us = 107 and its
+// The centroids are the matrix instructions' first operand and the rows the second, so that a lane holds 16 columns of ONE
+// row per block and looks for their best without a word to its neighbours: 6 instructions a value.  (With the rows first a
+// row lay across 32 lanes, and the moves and ballots over them took 75 us of each launch: 658 -> 582 us.)
+// Bound by the chain of short steps: 256 x 256 tiles, eight waves on a CU, keep the matrix cores busy for half of the cycles
+// and LDS for 20 % (no bank conflicts); waves wait for memory and barriers a third of their time.  32768 x 4096 x 768 in
+// 582 us = 354 TFLOP/s of fp32 products, where the fp32 kernel's chunk of 16384 took 962 us = 107 and its
 // selection 194.  (Not for the coarse step of searches, 1024 x 4096 x 768 69 -> 39 us: a query's probes at a near tie would
 // then depend on which kernel its call takes.)  By its own values alone,
 // 28 rows came out on the wrong side of a near tie, against 64 bits, over seven sets of 0.5 - 1 M rows
@@ -451,24 +454,23 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
                 bl[j] = *reinterpret_cast<const half8 *>(pb + j * 32 * LD + kc * 32 + 64);                 \
             }                                                                                              \
             _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j)  \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[i], bh[j], acc[i][j], 0, 0, 0);      \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[j], al[i], acc[i][j], 0, 0, 0);      \
             _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j)  \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[i], bl[j], acc[i][j], 0, 0, 0);      \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bl[j], ah[i], acc[i][j], 0, 0, 0);      \
             _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j)  \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[i], bh[j], acc[i][j], 0, 0, 0);      \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[j], ah[i], acc[i][j], 0, 0, 0);      \
         }                                                                                                  \
     }
-    float *const s_row = reinterpret_cast<float *>(smem + (size_t)2 * (BM + BN) * LD); // [2][BM]
+    float *const s_col = reinterpret_cast<float *>(smem + (size_t)2 * (BM + BN) * LD); // [2][BN]
     PK_FETCH(s0, 0)
     PK_FETCH(s1, 1)
     PK_PUT(s0, 0)
     PK_FETCH(s0, 2)
-    // per row: what turns a column's product into t (below), and how near a second value is near, in t's unit
-    if (tid < BM) {
-        const int m = m0 + tid < a.m ? m0 + tid : a.m - 1;
-        const float back = a.q_back[m], margin = a.second ? near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax)) : 0.f;
-        s_row[tid] = a.metric == PK_METRIC_L2 ? -2.f * back : -1.f;
-        s_row[BM + tid] = a.metric == PK_METRIC_L2 ? margin : margin / back;
+    // per column: what undoes its scale, and what its product is added to (a column that is no list comes behind every list)
+    if (tid < BN) {
+        const int n = n0 + tid;
+        s_col[tid] = n < a.n ? a.c_back[n] : 0.f;
+        s_col[BN + tid] = n < a.n ? (a.metric == PK_METRIC_L2 ? a.cnorm[n] : 0.f) : INFINITY;
     }
     __syncthreads();
     for (int ks = 0; ks < steps; ks += 2) { // steps is even: rows are padded to 64 elements
@@ -485,100 +487,78 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
 #undef PK_PUT
 #undef PK_STEP
 
-    // lane holds column l32 of rows kg * 4 + 8 * (r / 4) + r % 4 of each 32 x 32 block
-    float cb[NI], cn[NI];
-    uint32_t dead[NI];            // all ones for a column that is no list, the key that no list comes behind
-    unsigned long long lists[NI]; // the lanes whose column is a list
-#pragma unroll
-    for (int j = 0; j < NI; ++j) {
-        const int n = n0 + wn * (BN / WN) + j * 32 + l32;
-        dead[j] = n < a.n ? 0u : 0xffffffffu;
-        lists[j] = __ballot(n < a.n);
-        cb[j] = n < a.n ? a.c_back[n] : 0.f;
-        cn[j] = a.metric == PK_METRIC_L2 && n < a.n ? a.cnorm[n] : 0.f;
-    }
+    if (n0 + wn * (BN / WN) >= a.n) return; // no column of the wave's part is a list
+    // A lane holds, of row l32 of each block, columns kg * 4 + 8 * (r / 4) + r % 4.
     // t: smaller is nearer (inner product: -dot in the row's scale; L2: |c|^2 - 2 dot, the row's own norm left out)
-    uint32_t top[MI], second[MI]; // lane r of a half wave: of its row r, the best value's key, the near second's (or all ones)
-    int col[MI];
+    float factor[MI], low[MI], next[MI]; // (smallest t, smallest but one)
+    int col[MI];                         // the smallest's first column inside the wave's part of the tile
+    bool odd[MI];                        // a value that cannot be compared
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        top[i] = second[i] = 0xffffffffu;
+        const int m = m0 + wm * (BM / WM) + i * 32 + l32;
+        const float back = a.q_back[m < a.m ? m : a.m - 1];
+        factor[i] = a.metric == PK_METRIC_L2 ? -2.f * back : -1.f;
+        low[i] = next[i] = INFINITY;
         col[i] = 0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int local = wm * (BM / WM) + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
-            const float factor = s_row[local], margin = s_row[BM + local];
-            float t[NI];
-            uint32_t key[NI], low = 0xffffffffu;
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                t[j] = fmaf(acc[i][j][r] * cb[j], factor, cn[j]);
-                key[j] = order_bits(t[j], PK_METRIC_L2) | dead[j];
-                low = min(low, key[j]);
-            }
-            low = min_of_half(low);
-            const uint32_t b0 = __builtin_amdgcn_readlane(low, 31), b1 = __builtin_amdgcn_readlane(low, 63);
-            const uint32_t best = kg ? b1 : b0;
-            const float limit = value_of(best, PK_METRIC_L2) + margin;
-            int at0 = -1, at1 = -1; // column of each half's best inside the wave's part of the tile
-            uint32_t near0 = 0, near1 = 0;
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                // (a value that cannot be compared is near whatever the best is)
-                const unsigned long long eq = __ballot(key[j] == best), nr = __ballot(!(t[j] > limit)) & lists[j];
-                if (at0 < 0 && (uint32_t)eq) at0 = j * 32 + __ffs((uint32_t)eq) - 1;
-                if (at1 < 0 && (uint32_t)(eq >> 32)) at1 = j * 32 + __ffs((uint32_t)(eq >> 32)) - 1;
-                near0 += (uint32_t)__popc((uint32_t)nr);
-                near1 += (uint32_t)__popc((uint32_t)(nr >> 32));
-            }
-            uint32_t next = 0xffffffffu;
-            if (near0 > 1u || near1 > 1u) { // rare (wave-uniform): the best but one
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    if (j * 32 + l32 != (kg ? at1 : at0)) next = min(next, key[j]);
-                    if (dead[j] == 0u && t[j] != t[j]) next = kNoOrder;
-                }
-                next = min_of_half(next);
-                const uint32_t x0 = __builtin_amdgcn_readlane(next, 31), x1 = __builtin_amdgcn_readlane(next, 63);
-                next = kg ? x1 : x0;
-            }
-            if (l32 == r) {
-                top[i] = best;
-                col[i] = kg ? at1 : at0;
-                second[i] = next;
-            }
-        }
+        odd[i] = false;
     }
-    // lanes 0 .. 15 of a half wave: row r = l32 of the block
-    const int rr = kg * 4 + 8 * (l32 >> 2) + (l32 & 3);
-    const bool has = l32 < 16 && n0 + wn * (BN / WN) < a.n; // (some column of the wave's part is a list)
-    uint32_t met[MI], mine[MI];
+    const float *const pc = s_col + wn * (BN / WN) + kg * 4;
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 cb = *reinterpret_cast<const f32x4 *>(pc + j * 32 + g * 8);
+            const f32x4 cn = *reinterpret_cast<const f32x4 *>(pc + BN + j * 32 + g * 8);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float t = fmaf(acc[i][j][g * 4 + e] * cb[e], factor[i], cn[e]);
+                    odd[i] |= t != t;
+                    col[i] = t < low[i] ? j * 32 + g * 8 + e : col[i];
+                    next[i] = __builtin_amdgcn_fmed3f(low[i], next[i], t); // (low <= next)
+                    low[i] = fminf(low[i], t);
+                }
+        }
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        const int m = m0 + wm * (BM / WM) + i * 32 + rr;
-        met[i] = mine[i] = 0xffffffffu;
-        if (!has || m >= a.m) continue;
-        float v = value_of(top[i], PK_METRIC_L2);
-        if (a.metric == PK_METRIC_IP) v = -v * a.q_back[m];
-        mine[i] = min(order_bits(v, a.metric), kWorstKey);
-        const unsigned long long k = ((unsigned long long)mine[i] << 32) | (uint32_t)(n0 + wn * (BN / WN) + col[i]);
+        // the other half wave's columns of the row
+        const float low2 = __shfl_xor(low[i], 32), next2 = __shfl_xor(next[i], 32);
+        const int col1 = col[i] + kg * 4, col2 = __shfl_xor(col1, 32);
+        odd[i] |= __shfl_xor((int)odd[i], 32) != 0;
+        const bool mine = low[i] < low2 || (low[i] == low2 && col1 < col2);
+        col[i] = mine ? col1 : col2;
+        next[i] = fminf(fmaxf(low[i], low2), fminf(next[i], next2));
+        low[i] = fminf(low[i], low2);
+    }
+    // either half wave goes on with every second block
+    uint32_t met[MI], key[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const int m = m0 + wm * (BM / WM) + i * 32 + l32;
+        met[i] = key[i] = 0xffffffffu;
+        if (((i ^ kg) & 1) != 0 || m >= a.m) continue;
+        const float v = a.metric == PK_METRIC_IP ? -low[i] * a.q_back[m] : low[i];
+        key[i] = min(order_bits(v, a.metric), kWorstKey);
+        const unsigned long long k = ((unsigned long long)key[i] << 32) | (uint32_t)(n0 + wn * (BN / WN) + col[i]);
         met[i] = (uint32_t)(atomicMin(a.best + m, k) >> 32);
     }
+    if (!a.second) return;
+    const float cmax = __uint_as_float(*a.cmax);
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        const int m = m0 + wm * (BM / WM) + i * 32 + rr;
-        if (!a.second || !has || m >= a.m) continue;
-        uint32_t other = max(met[i], mine[i]); // (all ones: none met)
-        if (second[i] == kNoOrder) {
-            other = kNoOrder;
-        } else if (second[i] != 0xffffffffu) {
-            float v = value_of(second[i], PK_METRIC_L2);
-            if (a.metric == PK_METRIC_IP) v = -v * a.q_back[m];
-            other = min(other, min(order_bits(v, a.metric), kWorstKey));
+        const int m = m0 + wm * (BM / WM) + i * 32 + l32;
+        if (((i ^ kg) & 1) != 0 || m >= a.m) continue;
+        if (odd[i]) {
+            atomicMin(a.second + m, kNoOrder);
+            continue;
         }
-        if (other == 0xffffffffu) continue;
-        const float gap = fabsf(value_of(other, a.metric) - value_of(min(met[i], mine[i]), a.metric));
-        if (gap > near_margin(a.ld, a.metric, a.qnorm[m], __uint_as_float(*a.cmax))) continue;
+        // the second best that this wave knows of: its own, or the worse of its best and the one it met (all ones: none)
+        uint32_t other = max(met[i], key[i]);
+        const float v = a.metric == PK_METRIC_IP ? -next[i] * a.q_back[m] : next[i];
+        other = min(other, min(order_bits(v, a.metric), kWorstKey));
+        const float gap = fabsf(value_of(other, a.metric) - value_of(min(met[i], key[i]), a.metric));
+        if (gap > near_margin(a.ld, a.metric, a.qnorm[m], cmax)) continue;
         atomicMin(a.second + m, gap == gap ? other : kNoOrder);
     }
 }
@@ -588,7 +568,7 @@ static hipError_t launch_split_one(const SplitGemmArgs &a, hipStream_t s)
 {
     static LdsCleared cleared;
     const uint32_t tiles = (uint32_t)((a.n_pad + BN - 1) / BN) * (uint32_t)((a.m + BM - 1) / BM);
-    return launch_with_lds(&gemm_split_kernel<BM, BN, WM, WN>, cleared, 2 * (BM + BN) * 144 + 2 * BM * 4, a, (int)tiles, WM * WN * 64, s);
+    return launch_with_lds(&gemm_split_kernel<BM, BN, WM, WN>, cleared, 2 * (BM + BN) * 144 + 2 * BN * 4, a, (int)tiles, WM * WN * 64, s);
 }
 
 hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
