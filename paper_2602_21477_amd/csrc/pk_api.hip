@@ -1169,19 +1169,25 @@ int note_inserted(pk_index *ix, int64_t m, hipStream_t s)
 
 // Scratch of assign_rows for n vectors in chunks of `chunk`.
 struct AssignScratch {
-    char *xs, *cs;
-    float *xback, *cback, *norm;
-    uint32_t *second, *listed, *words; // words: [0] rows in listed[], [1] largest squared centroid norm, [2] rows of the first chunk in listed[]
+    char *xh, *ch, *cs;
+    float *xback, *cback, *norm, *left;
+    uint32_t *second, *close, *listed, *words;
+    // words: [0] rows in listed[], [1] largest squared centroid norm, [2] rows of the first chunk in listed[], [3] rows of the
+    // first chunk in close[], [4] rows of the others in close[] behind them, [5] the most that first halfs leave out of a centroid
     void lay(Carver &c, int64_t n, int64_t chunk, int nlist_pad, int rb32)
     {
-        xs = c.take<char>((size_t)chunk * rb32);
+        // (the last vectors, if they cannot fill tiles, are prepared in fp32: fewer than kFillChunk)
+        xh = c.take<char>(std::max((size_t)chunk * (rb32 / 2), (size_t)std::min<int64_t>(n, kFillChunk) * rb32));
+        ch = c.take<char>((size_t)nlist_pad * (rb32 / 2));
         cs = c.take<char>((size_t)nlist_pad * rb32);
-        xback = c.take<float>((size_t)chunk);
+        xback = c.take<float>((size_t)n);
         cback = c.take<float>((size_t)nlist_pad);
         norm = c.take<float>((size_t)n);
+        left = c.take<float>((size_t)n);
         second = c.take<uint32_t>((size_t)n);
+        close = c.take<uint32_t>((size_t)n);
         listed = c.take<uint32_t>((size_t)n);
-        words = c.take<uint32_t>(3);
+        words = c.take<uint32_t>(6);
     }
 };
 
@@ -1267,11 +1273,15 @@ struct InsertScratch {
 };
 
 // Top-1 assignment of n vectors (Section 3.1: the list of the best centroid): best[i] = (score key << 32 | list), by
-// the scores of the fp32 GEMM.  The split-operand GEMM finds them, two launches per chunk and no score matrix, and the
-// fp32 kernel goes over the few rows whose best two are near; a last chunk that cannot fill tiles (coarse_tiles) takes
-// the centroid kernel, as an insert of its size does.  Where most rows of the first chunk are near ties (lists given
-// twice; data whose common offset is large beside its spread) the others go to the fp32 kernel whole: it takes three and
-// a half times as long as the split GEMM, so that the two together are the longer way from five rows in seven on.
+// the scores of the fp32 GEMM, in three rounds, each for the rows that the one before cannot decide:
+//   1. the products of the first halfs alone, two launches per chunk and no score matrix; a row whose best two are
+//      further apart than what the halfs leave out can move them (row_margin) is done,
+//   2. all three products of the split rows (close[]: a few rows in a hundred, or a third of them in early k-means
+//      iterations), again done where the best two are not near,
+//   3. the fp32 kernel (listed[]: usually a handful).
+// A last chunk that cannot fill tiles (coarse_tiles) takes the centroid kernel, as an insert of its size does.  What the
+// first chunk leaves undecided says what the others are spared: a round takes a third (1 of 2) or two sevenths (2 of 3)
+// of the next one's time, so that it is the longer way from two rows in three (five in seven) on.
 int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const AssignScratch &as, int64_t chunk,
                 unsigned long long *best, hipStream_t s)
 {
@@ -1279,24 +1289,67 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
     const int64_t by_gemm = tail > 0 && !coarse_tiles((uint32_t)tail, t.nlist_pad) ? n - tail : n;
     MultiArgs mm;
     std::memset(&mm, 0, sizeof(mm));
-    PK_HIP(launch_fill_u32(as.words, 0u, 3, s));
-    const uint32_t skip_from = (uint32_t)(std::min(chunk, by_gemm) / 7 * 5);
-    auto list_near = [&](int64_t first, int64_t last, bool start) {
+    PK_HIP(launch_fill_u32(as.words, 0u, 6, s));
+    const int64_t head = std::min(chunk, by_gemm);
+    const uint32_t skip1_from = (uint32_t)(head / 3 * 2), skip2_from = (uint32_t)(head / 7 * 5);
+    SplitGemmArgs g{};
+    g.c = as.ch;
+    g.q_back = as.xback;
+    g.c_back = as.cback;
+    g.qnorm = as.norm;
+    g.cnorm = t.cnorm;
+    g.n = t.nlist;
+    g.n_pad = t.nlist_pad;
+    g.ld = t.ld;
+    g.metric = t.metric;
+    g.best = best;
+    g.second = as.second;
+    g.cmax = as.words + 1;
+    // rounds 1 (its end) and 2 of rows [first, last)
+    auto decide = [&](int64_t first, int64_t last) -> int {
+        const bool start = first == 0;
+        uint32_t *const close = as.close + first, *const n_close = as.words + (start ? 3 : 4);
         NearTiesArgs nt{};
         nt.first = (uint32_t)first;
         nt.last = (uint32_t)last;
         nt.best = best;
         nt.second = as.second;
         nt.cmax = as.words + 1;
+        nt.cmax_left = as.words + 5;
         nt.qnorm = as.norm;
-        nt.skipped = start ? nullptr : as.words + 2;
-        nt.skip_from = skip_from;
+        nt.left = as.left;
+        nt.skipped = start ? nullptr : as.words + 3;
+        nt.skip_from = skip1_from;
+        nt.skipped2 = start ? nullptr : as.words + 2;
+        nt.skip_from2 = skip2_from;
+        nt.list = close;
+        nt.nlisted = n_close;
+        nt.ld = t.ld;
+        nt.metric = t.metric;
+        PK_HIP(launch_near_ties(nt, num_cu, s));
+        SplitGemmArgs g2 = g;
+        g2.c = as.cs;
+        g2.x = x;
+        g2.d = t.d;
+        g2.list = close;
+        g2.nlisted = n_close;
+        g2.skipped = start ? nullptr : as.words + 2;
+        g2.skip_from = skip2_from;
+        PK_HIP(launch_gemm_split_listed(g2, num_cu, s));
+        nt.first = 0;
+        nt.last = (uint32_t)(last - first);
+        nt.among = close;
+        nt.n_among = n_close;
+        nt.cmax_left = nullptr;
+        nt.left = nullptr;
+        nt.skipped = nt.skipped2;
+        nt.skip_from = skip2_from;
+        nt.skipped2 = nullptr;
         nt.list = as.listed;
         nt.nlisted = as.words;
         nt.also = start ? as.words + 2 : nullptr;
-        nt.ld = t.ld;
-        nt.metric = t.metric;
-        return launch_near_ties(nt, num_cu, s);
+        PK_HIP(launch_near_ties(nt, num_cu, s));
+        return PK_OK;
     };
     for (int64_t i0 = 0; i0 < by_gemm; i0 += chunk) {
         const int64_t m = std::min<int64_t>(chunk, by_gemm - i0);
@@ -1307,37 +1360,36 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
         sr.n_c = i0 == 0 ? (uint32_t)t.nlist_pad : 0u;
         sr.d = t.d;
         sr.ld = t.ld;
-        sr.xs = as.xs;
+        sr.xh = as.xh;
+        sr.ch = as.ch;
         sr.cs = as.cs;
-        sr.x_back = as.xback;
+        sr.x_back = as.xback + i0;
         sr.c_back = as.cback;
         sr.qnorm = as.norm + i0;
+        sr.left = as.left + i0;
         sr.best = best + i0;
         sr.second = as.second + i0;
         sr.cmax = as.words + 1;
+        sr.cmax_left = as.words + 5;
         PK_HIP(launch_split_rows(sr, mm, s));
-        SplitGemmArgs g{};
-        g.q = as.xs;
-        g.c = as.cs;
-        g.q_back = as.xback;
-        g.c_back = as.cback;
-        g.qnorm = as.norm + i0;
-        g.cnorm = t.cnorm;
-        g.best = best + i0;
-        g.m = (int)m;
-        g.n = t.nlist;
-        g.n_pad = t.nlist_pad;
-        g.ld = t.ld;
-        g.metric = t.metric;
-        g.second = as.second + i0;
-        g.cmax = as.words + 1;
-        g.skipped = i0 > 0 ? as.words + 2 : nullptr;
-        g.skip_from = skip_from;
-        PK_HIP(launch_gemm_split(g, num_cu, s));
-        if (i0 == 0) PK_HIP(list_near(0, m, true));
+        SplitGemmArgs g1 = g;
+        g1.q = as.xh;
+        g1.q_back += i0;
+        g1.qnorm += i0;
+        g1.left = as.left + i0;
+        g1.cmax_left = as.words + 5;
+        g1.best += i0;
+        g1.second += i0;
+        g1.m = (int)m;
+        g1.skipped = i0 > 0 ? as.words + 3 : nullptr;
+        g1.skip_from = skip1_from;
+        g1.skipped2 = i0 > 0 ? as.words + 2 : nullptr;
+        g1.skip_from2 = skip2_from;
+        PK_HIP(launch_gemm_split(g1, num_cu, s));
+        if (i0 == 0) PK_TRY(decide(0, head));
     }
+    if (by_gemm > head) PK_TRY(decide(head, by_gemm));
     if (by_gemm > 0) {
-        PK_HIP(list_near(std::min(chunk, by_gemm), by_gemm, false));
         GemmArgs g{};
         g.q = x;
         g.c = t.cent;
@@ -1355,7 +1407,7 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
         PK_HIP(launch_gemm_listed(g, num_cu, s));
     }
     if (by_gemm < n) {
-        PK_TRY(assign_few(x + (size_t)by_gemm * t.d, tail, t, num_cu, as.xs, as.xback, best + by_gemm, true, s));
+        PK_TRY(assign_few(x + (size_t)by_gemm * t.d, tail, t, num_cu, as.xh, as.norm + by_gemm, best + by_gemm, true, s));
     }
     return PK_OK;
 }

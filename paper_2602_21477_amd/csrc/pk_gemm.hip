@@ -3,7 +3,7 @@
 // (squared L2), Section 2.2's ranking of clusters by centroid distance, for all m, n.
 //
 // gemm_scores_kernel writes the scores: the coarse step of searches.  gemm_split_kernel finds every row's best
-// column: the assignments of build, k-means and large inserts.
+// column: the assignments of large inserts and, of the rows that gemm_first_kernel leaves undecided, of build and k-means.
 //
 // This is a dense contraction, so it runs on the matrix cores with fp32 inputs and fp32
 // accumulation (v_mfma_f32_32x32x2_f32): no down-conversion of queries or centroids, so
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0; // (wave-uniform)
     constexpr int kT = (PK_MAX_DIM + 255) / 256;
     f32x4 v[kT];
-    float big = 0.f, sq[4] = {0.f, 0.f, 0.f, 0.f}, sq16[4] = {0.f, 0.f, 0.f, 0.f};
+    float big = 0.f, sq[4] = {0.f, 0.f, 0.f, 0.f}, sq16[4] = {0.f, 0.f, 0.f, 0.f}, off[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < kT; ++t) {
         const int i = lane * 4 + 256 * t;
@@ -296,8 +296,9 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     int s = 14 - ((int)(__float_as_uint(big) >> 23) - 127);
     s = s < -126 ? -126 : (s > 126 ? 126 : s);
     const float scale = __uint_as_float((uint32_t)(s + 127) << 23);
-    char *dst = cent ? a.cs : a.xs;
+    char *dst = cent ? a.cs : a.xs, *first = cent ? a.ch : a.xh;
     if (dst) dst += (size_t)r * ld * 4; // (null: the rows are wanted in their other forms only)
+    if (first) first += (size_t)r * ld * 2;
 #pragma unroll
     for (int t = 0; t < kT; ++t) {
         const int i = lane * 4 + 256 * t;
@@ -307,8 +308,11 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
         for (int j = 0; j < 4; ++j) {
             const float y = v[t][j] * scale; // exact
             hi[j] = (_Float16)y;
-            lo[j] = (_Float16)(y - (float)hi[j]); // the difference is exact
+            const float rest = y - (float)hi[j]; // exact
+            lo[j] = (_Float16)rest;
+            off[j] += rest * rest;
         }
+        if (first) *reinterpret_cast<half4 *>(first + (size_t)i * 2) = hi;
         if (dst) {
             char *p = dst + (size_t)(i >> 5) * 128 + (i & 31) * 2;
             *reinterpret_cast<half4 *>(p) = hi;
@@ -333,15 +337,22 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
         }
     }
     const float norm16 = row_sum(sq16);
+    const float rest = row_sum(off);
     if (lane != 0) return;
     const float back = __uint_as_float((uint32_t)(127 - s) << 23);
+    const float left = sqrtf(rest) * back; // length of what the first halfs leave out
     if (cent) {
         a.c_back[r] = back;
-        // (squares: their bits are in the order of the values; a look first, as every row's atomic meets the others' at one word)
-        if (a.cmax && __hip_atomic_load(a.cmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < __float_as_uint(norm))
-            atomicMax(a.cmax, __float_as_uint(norm));
+        // (not negative: their bits are in the order of the values; a look first, as every row's atomic meets the others' at one word)
+        auto raise = [](uint32_t *word, float v) {
+            if (word && __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < __float_as_uint(v))
+                atomicMax(word, __float_as_uint(v));
+        };
+        raise(a.cmax, norm);
+        raise(a.cmax_left, left);
         return;
     }
+    if (a.left) a.left[r] = left;
     if (a.x_back) a.x_back[r] = back;
     if (a.second) a.second[r] = 0xffffffffu;
     if (a.redo) a.redo[r] = ~0ull;
@@ -381,128 +392,30 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStr
 // then depend on which kernel its call takes.)  By its own values alone,
 // 28 rows came out on the wrong side of a near tie, against 64 bits, over seven sets of 0.5 - 1 M rows
 // (64 <= d <= 1536), and 46 by the fp32 kernel's.
-template <int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(SplitGemmArgs a)
+// A wave's products (blocks of 32 columns x 32 rows: lane l holds, of row m0 + l % 32 of each block, columns
+// n0 + (l / 32) * 4 + 8 * (r / 4) + r % 4) into the rows' best and near second values.  s_col: of the wave's columns.
+template <int BN, int MI, int NI>
+__device__ __forceinline__ void best_of_split(const SplitGemmArgs &a, const f32x16 (&acc)[MI][NI], const float *s_col, int m0, int n0, int rows,
+                                              int lane, bool listed)
 {
-    constexpr int TH = WM * WN * 64;
-    constexpr int MI = BM / WM / 32, NI = BN / WN / 32; // 32 x 32 blocks per wave
-    constexpr int LD = 144;                             // LDS bytes per row: 128 + 16, conflict-free b128 reads
-    constexpr int LOADS = (BM + BN) * 8 / TH;           // 16-byte pieces per thread and step
-    static_assert((BM * 8) % TH == 0 && (BN * 8) % TH == 0, "a thread's piece is of A or of B for the whole workgroup");
-    constexpr int ALOADS = BM * 8 / TH;
-    extern __shared__ __align__(16) char smem[]; // [2][BM + BN][LD]
-    if (a.skipped && *a.skipped > a.skip_from) return; // near ties are the rule: the fp32 kernel takes these rows whole
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
     const int l32 = lane & 31, kg = lane >> 5;
-    // XCD-aware order: workgroups go to the 8 XCDs in turn; each XCD takes one contiguous part of the tiles, and walks
-    // it in groups of 8 tile rows, so that the tiles in flight on an XCD share their rows and columns in its L2
-    const uint32_t tn = (uint32_t)(a.n_pad + BN - 1) / BN, tm = (uint32_t)(a.m + BM - 1) / BM, total = tn * tm;
-    const uint32_t xcd = blockIdx.x & 7u, per = total / 8u, extra = total % 8u;
-    const uint32_t t = xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
-    constexpr uint32_t GM = 8;
-    const uint32_t grp = t / (GM * tn), in = t - grp * GM * tn;
-    const uint32_t gm = tm - grp * GM < GM ? tm - grp * GM : GM;
-    const int m0 = (int)(grp * GM + in % gm) * BM, n0 = (int)(in / gm) * BN;
-
-    const int steps = a.ld / 32;
-    const size_t row_bytes = (size_t)a.ld * 4;
-    const char *src[LOADS];
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-        const int piece = i < ALOADS ? tid + i * TH : tid + (i - ALOADS) * TH;
-        int r = (i < ALOADS ? m0 : n0) + (piece >> 3);
-        const int last = i < ALOADS ? a.m - 1 : a.n_pad - 1;
-        r = r < last ? r : last; // rows past the end are computed and dropped
-        src[i] = (i < ALOADS ? a.q : a.c) + (size_t)r * row_bytes + (piece & 7) * 16;
-    }
-    char *const put = smem + (size_t)(tid >> 3) * LD + (tid & 7) * 16;
-    constexpr int ROWS_PER = TH / 8; // LDS rows between a thread's pieces
-    u32x4 s0[LOADS], s1[LOADS];
-    f32x16 acc[MI][NI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    // (past the last step the last one is fetched again: every load is unconditional)
-#define PK_FETCH(st, ks)                                                                                   \
-    {                                                                                                      \
-        const size_t at = (size_t)((ks) < steps ? (ks) : steps - 1) * 128;                                 \
-        _Pragma("unroll") for (int i = 0; i < LOADS; ++i) st[i] = *reinterpret_cast<gvec4>(in_global(src[i]) + at); \
-    }
-#define PK_PUT(st, buf)                                                                                    \
-    _Pragma("unroll") for (int i = 0; i < LOADS; ++i)                                                      \
-        *reinterpret_cast<u32x4 *>(put + (size_t)(buf) * (BM + BN) * LD + (size_t)i * ROWS_PER * LD) = st[i];
-#define PK_STEP(buf)                                                                                       \
-    {                                                                                                      \
-        const char *pa = smem + (size_t)(buf) * (BM + BN) * LD + (size_t)(wm * (BM / WM) + l32) * LD + kg * 16; \
-        const char *pb = smem + (size_t)(buf) * (BM + BN) * LD + (size_t)(BM + wn * (BN / WN) + l32) * LD + kg * 16; \
-        _Pragma("unroll") for (int kc = 0; kc < 2; ++kc)                                                   \
-        {                                                                                                  \
-            half8 ah[MI], al[MI], bh[NI], bl[NI];                                                          \
-            _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                 \
-            {                                                                                              \
-                ah[i] = *reinterpret_cast<const half8 *>(pa + i * 32 * LD + kc * 32);                      \
-                al[i] = *reinterpret_cast<const half8 *>(pa + i * 32 * LD + kc * 32 + 64);                 \
-            }                                                                                              \
-            _Pragma("unroll") for (int j = 0; j < NI; ++j)                                                 \
-            {                                                                                              \
-                bh[j] = *reinterpret_cast<const half8 *>(pb + j * 32 * LD + kc * 32);                      \
-                bl[j] = *reinterpret_cast<const half8 *>(pb + j * 32 * LD + kc * 32 + 64);                 \
-            }                                                                                              \
-            _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j)  \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[j], al[i], acc[i][j], 0, 0, 0);      \
-            _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j)  \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bl[j], ah[i], acc[i][j], 0, 0, 0);      \
-            _Pragma("unroll") for (int i = 0; i < MI; ++i) _Pragma("unroll") for (int j = 0; j < NI; ++j)  \
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[j], ah[i], acc[i][j], 0, 0, 0);      \
-        }                                                                                                  \
-    }
-    float *const s_col = reinterpret_cast<float *>(smem + (size_t)2 * (BM + BN) * LD); // [2][BN]
-    PK_FETCH(s0, 0)
-    PK_FETCH(s1, 1)
-    PK_PUT(s0, 0)
-    PK_FETCH(s0, 2)
-    // per column: what undoes its scale, and what its product is added to (a column that is no list comes behind every list)
-    if (tid < BN) {
-        const int n = n0 + tid;
-        s_col[tid] = n < a.n ? a.c_back[n] : 0.f;
-        s_col[BN + tid] = n < a.n ? (a.metric == PK_METRIC_L2 ? a.cnorm[n] : 0.f) : INFINITY;
-    }
-    __syncthreads();
-    for (int ks = 0; ks < steps; ks += 2) { // steps is even: rows are padded to 64 elements
-        PK_STEP(0)
-        PK_PUT(s1, 1) // (buffer 1 was last read before the barrier that ended the step before)
-        PK_FETCH(s1, ks + 3)
-        __syncthreads();
-        PK_STEP(1)
-        PK_PUT(s0, 0)
-        PK_FETCH(s0, ks + 4)
-        __syncthreads();
-    }
-#undef PK_FETCH
-#undef PK_PUT
-#undef PK_STEP
-
-    if (n0 + wn * (BN / WN) >= a.n) return; // no column of the wave's part is a list
-    // A lane holds, of row l32 of each block, columns kg * 4 + 8 * (r / 4) + r % 4.
+    if (n0 >= a.n) return; // no column of the wave's part is a list
     // t: smaller is nearer (inner product: -dot in the row's scale; L2: |c|^2 - 2 dot, the row's own norm left out)
+    uint32_t row[MI];
     float factor[MI], low[MI], next[MI]; // (smallest t, smallest but one)
     int col[MI];                         // the smallest's first column inside the wave's part of the tile
     bool odd[MI];                        // a value that cannot be compared
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        const int m = m0 + wm * (BM / WM) + i * 32 + l32;
-        const float back = a.q_back[m < a.m ? m : a.m - 1];
+        const int m = m0 + i * 32 + l32 < rows ? m0 + i * 32 + l32 : rows - 1;
+        row[i] = listed ? a.list[m] : (uint32_t)m;
+        const float back = a.q_back[row[i]];
         factor[i] = a.metric == PK_METRIC_L2 ? -2.f * back : -1.f;
         low[i] = next[i] = INFINITY;
         col[i] = 0;
         odd[i] = false;
     }
-    const float *const pc = s_col + wn * (BN / WN) + kg * 4;
+    const float *const pc = s_col + kg * 4;
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
@@ -535,51 +448,319 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     uint32_t met[MI], key[MI];
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        const int m = m0 + wm * (BM / WM) + i * 32 + l32;
+        const int m = m0 + i * 32 + l32;
         met[i] = key[i] = 0xffffffffu;
-        if (((i ^ kg) & 1) != 0 || m >= a.m) continue;
-        const float v = a.metric == PK_METRIC_IP ? -low[i] * a.q_back[m] : low[i];
+        if (((i ^ kg) & 1) != 0 || m >= rows) continue;
+        const float v = a.metric == PK_METRIC_IP ? -low[i] * a.q_back[row[i]] : low[i];
         key[i] = min(order_bits(v, a.metric), kWorstKey);
-        const unsigned long long k = ((unsigned long long)key[i] << 32) | (uint32_t)(n0 + wn * (BN / WN) + col[i]);
-        met[i] = (uint32_t)(atomicMin(a.best + m, k) >> 32);
+        const unsigned long long k = ((unsigned long long)key[i] << 32) | (uint32_t)(n0 + col[i]);
+        met[i] = (uint32_t)(atomicMin(a.best + row[i], k) >> 32);
     }
     if (!a.second) return;
-    const float cmax = __uint_as_float(*a.cmax);
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        const int m = m0 + wm * (BM / WM) + i * 32 + l32;
-        if (((i ^ kg) & 1) != 0 || m >= a.m) continue;
+        const int m = m0 + i * 32 + l32;
+        if (((i ^ kg) & 1) != 0 || m >= rows) continue;
         if (odd[i]) {
-            atomicMin(a.second + m, kNoOrder);
+            atomicMin(a.second + row[i], kNoOrder);
             continue;
         }
         // the second best that this wave knows of: its own, or the worse of its best and the one it met (all ones: none)
         uint32_t other = max(met[i], key[i]);
-        const float v = a.metric == PK_METRIC_IP ? -next[i] * a.q_back[m] : next[i];
+        const float v = a.metric == PK_METRIC_IP ? -next[i] * a.q_back[row[i]] : next[i];
         other = min(other, min(order_bits(v, a.metric), kWorstKey));
         const float gap = fabsf(value_of(other, a.metric) - value_of(min(met[i], key[i]), a.metric));
-        if (gap > near_margin(a.ld, a.metric, a.qnorm[m], cmax)) continue;
-        atomicMin(a.second + m, gap == gap ? other : kNoOrder);
+        if (gap > row_margin(a.ld, a.metric, a.qnorm[row[i]], a.cmax, a.left ? a.left[row[i]] : 0.f, a.cmax_left)) continue;
+        atomicMin(a.second + row[i], gap == gap ? other : kNoOrder);
     }
+}
+
+// LISTED: the rows are listed fp32 rows, which are split on their way into LDS, and the grid walks the tiles there are.
+template <int BM, int BN, int WM, int WN, bool LISTED>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(SplitGemmArgs a)
+{
+    constexpr int TH = WM * WN * 64;
+    constexpr int MI = BM / WM / 32, NI = BN / WN / 32; // 32 x 32 blocks per wave
+    constexpr int LD = 144;                             // LDS bytes per row: 128 + 16, conflict-free b128 reads
+    constexpr int LOADS = (BM + BN) * 8 / TH;           // 16-byte pieces per thread and step
+    static_assert((BM * 8) % TH == 0 && (BN * 8) % TH == 0, "a thread's piece is of A or of B for the whole workgroup");
+    constexpr int ALOADS = BM * 8 / TH;
+    extern __shared__ __align__(16) char smem[]; // [2][BM + BN][LD]
+    if (a.skipped && *a.skipped > a.skip_from) return; // near ties are the rule: the next kernel takes these rows whole
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int l32 = lane & 31, kg = lane >> 5;
+    const int rows = LISTED ? (int)*a.nlisted : a.m;
+    const uint32_t tn = (uint32_t)(a.n_pad + BN - 1) / BN, tm = (uint32_t)(rows + BM - 1) / BM, total = tn * tm;
+    float *const s_col = reinterpret_cast<float *>(smem + (size_t)2 * (BM + BN) * LD); // [2][BN]
+    char *const put = smem + (size_t)(tid >> 3) * LD + (tid & 7) * 16;
+    constexpr int ROWS_PER = TH / 8; // LDS rows between a thread's pieces
+    const int steps = a.ld / 32;
+    const size_t row_bytes = (size_t)a.ld * 4;
+    [[maybe_unused]] const bool vec = LISTED && (a.d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.x) & 15) == 0;
+
+    for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
+    // XCD-aware order: workgroups go to the 8 XCDs in turn; each XCD takes one contiguous part of the tiles, and walks
+    // it in groups of 8 tile rows, so that the tiles in flight on an XCD share their rows and columns in its L2
+    const uint32_t xcd = b & 7u, per = total / 8u, extra = total % 8u;
+    const uint32_t t = xcd * per + (xcd < extra ? xcd : extra) + (b >> 3);
+    constexpr uint32_t GM = 8;
+    const uint32_t grp = t / (GM * tn), in = t - grp * GM * tn;
+    const uint32_t gm = tm - grp * GM < GM ? tm - grp * GM : GM;
+    const int m0 = (int)(grp * GM + in % gm) * BM, n0 = (int)(in / gm) * BN;
+
+    const char *src[LOADS];
+    [[maybe_unused]] float scale[ALOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int piece = i < ALOADS ? tid + i * TH : tid + (i - ALOADS) * TH;
+        int r = (i < ALOADS ? m0 : n0) + (piece >> 3);
+        const int last = i < ALOADS ? rows - 1 : a.n_pad - 1;
+        r = r < last ? r : last; // rows past the end are computed and dropped
+        if (LISTED && i < ALOADS) {
+            const uint32_t row = a.list[r];
+            src[i] = reinterpret_cast<const char *>(a.x + (size_t)row * a.d + (piece & 7) * 4);
+            scale[i] = 1.f / a.q_back[row]; // (a power of two: exact)
+        } else {
+            src[i] = (i < ALOADS ? a.q : a.c) + (size_t)r * row_bytes + (piece & 7) * 16;
+        }
+    }
+    u32x4 s0[LOADS], s1[LOADS];
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    // (past the last step the last one is fetched again: every load is unconditional)
+    auto fetch = [&](u32x4 (&st)[LOADS], int ks) {
+        ks = ks < steps ? ks : steps - 1;
+        const size_t at = (size_t)ks * 128;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            if (LISTED && i < ALOADS)
+                st[i] = __builtin_bit_cast(u32x4, dense_piece(reinterpret_cast<const float *>(src[i]), ks * 32, (tid & 7) * 4, a.d, vec));
+            else
+                st[i] = *reinterpret_cast<gvec4>(in_global(src[i]) + at);
+        }
+    };
+    auto store = [&](const u32x4 (&st)[LOADS], int buf) {
+        char *const to = put + (size_t)buf * (BM + BN) * LD;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            if (LISTED && i < ALOADS) { // 4 floats: their first halfs into the row's first 64 bytes, the rest behind
+                const f32x4 v = __builtin_bit_cast(f32x4, st[i]);
+                half4 hi, lo;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { // (the same values as split_rows_kernel's)
+                    const float y = v[j] * scale[i];
+                    hi[j] = (_Float16)y;
+                    lo[j] = (_Float16)(y - (float)hi[j]);
+                }
+                char *const p = to + (size_t)i * ROWS_PER * LD - (tid & 7) * 8;
+                *reinterpret_cast<half4 *>(p) = hi;
+                *reinterpret_cast<half4 *>(p + 64) = lo;
+            } else {
+                *reinterpret_cast<u32x4 *>(to + (size_t)i * ROWS_PER * LD) = st[i];
+            }
+        }
+    };
+    auto step = [&](int buf) {
+        const char *pa = smem + (size_t)buf * (BM + BN) * LD + (size_t)(wm * (BM / WM) + l32) * LD + kg * 16;
+        const char *pb = smem + (size_t)buf * (BM + BN) * LD + (size_t)(BM + wn * (BN / WN) + l32) * LD + kg * 16;
+#pragma unroll
+        for (int kc = 0; kc < 2; ++kc) {
+            half8 ah[MI], al[MI], bh[NI], bl[NI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                ah[i] = *reinterpret_cast<const half8 *>(pa + i * 32 * LD + kc * 32);
+                al[i] = *reinterpret_cast<const half8 *>(pa + i * 32 * LD + kc * 32 + 64);
+            }
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                bh[j] = *reinterpret_cast<const half8 *>(pb + j * 32 * LD + kc * 32);
+                bl[j] = *reinterpret_cast<const half8 *>(pb + j * 32 * LD + kc * 32 + 64);
+            }
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[j], al[i], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bl[j], ah[i], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[j], ah[i], acc[i][j], 0, 0, 0);
+        }
+    };
+    fetch(s0, 0);
+    fetch(s1, 1);
+    if constexpr (LISTED) __syncthreads(); // the tile before is done with LDS
+    store(s0, 0);
+    fetch(s0, 2);
+    // per column: what undoes its scale, and what its product is added to (a column that is no list comes behind every list)
+    if (tid < BN) {
+        const int n = n0 + tid;
+        s_col[tid] = n < a.n ? a.c_back[n] : 0.f;
+        s_col[BN + tid] = n < a.n ? (a.metric == PK_METRIC_L2 ? a.cnorm[n] : 0.f) : INFINITY;
+    }
+    __syncthreads();
+    for (int ks = 0; ks < steps; ks += 2) { // steps is even: rows are padded to 64 elements
+        step(0);
+        store(s1, 1); // (buffer 1 was last read before the barrier that ended the step before)
+        fetch(s1, ks + 3);
+        __syncthreads();
+        step(1);
+        store(s0, 0);
+        fetch(s0, ks + 4);
+        __syncthreads();
+    }
+    best_of_split<BN, MI, NI>(a, acc, s_col + wn * (BN / WN), m0 + wm * (BM / WM), n0 + wn * (BN / WN), rows, lane, LISTED);
+    if constexpr (!LISTED) return;
+    }
+}
+
+// The products of the first halfs alone: what decides all but a few rows of an assignment, at a third of the price.
+// Same tiles, order and epilogue as gemm_split_kernel; the operands go from memory into LDS without registers in between
+// (one instruction per wave moves 16 rows x 64 bytes), three steps of 32 elements ahead of the one being multiplied, in
+// four buffers.  The 16-byte pieces of a row lie in the order piece ^ ((row >> 1) & 3), so that the reads of a piece of 8
+// consecutive rows meet no bank twice.  The loads are counted by hand (the compiler would wait for all of them before the
+// next LDS read): they are the only memory operations of the loop, complete in order, and a
+// step's have arrived when at most those of the two steps behind it are outstanding.  32768 x 4096 x 768 in 252 us =
+// 816 TFLOP/s, where gemm_split_kernel takes 582 for the three products; the rows it leaves undecided (a tenth of them in
+// the first k-means iteration over 4096 clusters, from random rows; fewer where the centroids are trained) cost 83 us more
+// per 32768: one such iteration over 262 144 rows 5710 -> 3729 us, the build of 300 000 x 1024 with 512 lists 2836 -> 2585.
+template <int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_first_kernel(SplitGemmArgs a)
+{
+    constexpr int TH = WM * WN * 64;
+    constexpr int MI = BM / WM / 32, NI = BN / WN / 32;
+    constexpr int STEP = (BM + BN) * 64;            // bytes of one step's buffer
+    constexpr int LOADS = STEP / 16 / TH;           // loads per wave and step
+    constexpr int ALOADS = BM * 64 / 16 / TH;       // ... of them of rows (the others: of centroids)
+    static_assert((BM * 4) % TH == 0 && (BN * 4) % TH == 0, "a load is of A or of B for the whole workgroup");
+    extern __shared__ __align__(16) char smem[]; // [4][BM + BN][64], then [2][BN] floats
+    if (a.skipped && *a.skipped > a.skip_from) return; // near ties are the rule: the next kernel takes these rows whole
+    if (a.skipped2 && *a.skipped2 > a.skip_from2) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int l32 = lane & 31, kg = lane >> 5;
+    const uint32_t tn = (uint32_t)(a.n_pad + BN - 1) / BN, tm = (uint32_t)(a.m + BM - 1) / BM, total = tn * tm;
+    const uint32_t xcd = blockIdx.x & 7u, per = total / 8u, extra = total % 8u;
+    const uint32_t t = xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
+    constexpr uint32_t GM = 8;
+    const uint32_t grp = t / (GM * tn), in = t - grp * GM * tn;
+    const uint32_t gm = tm - grp * GM < GM ? tm - grp * GM : GM;
+    const int m0 = (int)(grp * GM + in % gm) * BM, n0 = (int)(in / gm) * BN;
+
+    const int steps = a.ld / 32; // (two at least: rows are padded to 64 elements)
+    const uint32_t row_bytes = (uint32_t)a.ld * 2u;
+    const char *const base_a = a.q + (size_t)m0 * row_bytes, *const base_b = a.c + (size_t)n0 * row_bytes;
+    uint32_t off[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int piece = (i < ALOADS ? i : i - ALOADS) * TH + tid; // of the operand's part of the buffer: row piece / 4
+        int r = piece >> 2;
+        const int p = (piece & 3) ^ ((r >> 1) & 3);
+        const int last = i < ALOADS ? a.m - 1 - m0 : a.n_pad - 1 - n0;
+        r = r < last ? r : last; // rows past the end are computed and dropped
+        off[i] = (uint32_t)r * row_bytes + (uint32_t)p * 16u;
+    }
+    // where this wave's loads of a step go: 1024 bytes each, lane by lane
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + (uint32_t)wave * 1024u;
+    auto request = [&](int ks) { // (past the last step the last one again: the count of loads is the same for every step)
+        const int at = (ks < steps ? ks : steps - 1) * 64;
+        const char *const pa = base_a + at, *const pb = base_b + at;
+        const uint32_t to = lds0 + (uint32_t)(ks & 3) * STEP;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i)
+            asm volatile("s_mov_b32 m0, %0\n\t"
+                         "s_nop 0\n\t"
+                         "global_load_lds_dwordx4 %1, %2"
+                         :
+                         : "s"(to + (uint32_t)i * (TH * 16)), "v"(off[i]), "s"(i < ALOADS ? pa : pb)
+                         : "memory");
+    };
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    // per column: what undoes its scale, and what its product is added to (a column that is no list comes behind every list)
+    float *const s_col = reinterpret_cast<float *>(smem + 4 * STEP);
+    for (int i = tid; i < BN; i += TH) {
+        const int n = n0 + i;
+        s_col[i] = n < a.n ? a.c_back[n] : 0.f;
+        s_col[BN + i] = n < a.n ? (a.metric == PK_METRIC_L2 ? a.cnorm[n] : 0.f) : INFINITY;
+    }
+    // byte offsets inside a buffer of the 16 bytes that the lane reads of a block's row, in each half of a step
+    const uint32_t sw = (uint32_t)((l32 >> 1) & 3);
+    const uint32_t at0 = (uint32_t)l32 * 64u + (((uint32_t)kg) ^ sw) * 16u, at1 = (uint32_t)l32 * 64u + (((uint32_t)kg + 2u) ^ sw) * 16u;
+    request(0);
+    request(1);
+    request(2);
+    for (int ks = 0; ks < steps; ++ks) {
+        // this step's operands are there (this wave's by its count, the others' by the barrier), and every wave has read
+        // what it wanted of the step before, whose buffer the next request fills
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(2 * LOADS) : "memory");
+        request(ks + 3);
+        const char *const buf = smem + (ks & 3) * STEP;
+        const char *const pa = buf + wm * (BM / WM) * 64, *const pb = buf + (BM + wn * (BN / WN)) * 64;
+#pragma unroll
+        for (int kc = 0; kc < 2; ++kc) {
+            const uint32_t at = kc ? at1 : at0;
+            half8 ah[MI], bh[NI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) ah[i] = *reinterpret_cast<const half8 *>(pa + at + i * 32 * 64);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) bh[j] = *reinterpret_cast<const half8 *>(pb + at + j * 32 * 64);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[j], ah[i], acc[i][j], 0, 0, 0);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); // nothing may still be on its way into LDS when the workgroup ends
+    best_of_split<BN, MI, NI>(a, acc, s_col + wn * (BN / WN), m0 + wm * (BM / WM), n0 + wn * (BN / WN), a.m, lane, false);
 }
 
 template <int BM, int BN, int WM, int WN>
 static hipError_t launch_split_one(const SplitGemmArgs &a, hipStream_t s)
 {
-    static LdsCleared cleared;
-    const uint32_t tiles = (uint32_t)((a.n_pad + BN - 1) / BN) * (uint32_t)((a.m + BM - 1) / BM);
-    return launch_with_lds(&gemm_split_kernel<BM, BN, WM, WN>, cleared, 2 * (BM + BN) * 144 + 2 * BN * 4, a, (int)tiles, WM * WN * 64, s);
+    static LdsCleared cleared, cleared_first;
+    const int tiles = (a.n_pad + BN - 1) / BN * ((a.m + BM - 1) / BM);
+    if (a.left)
+        return launch_with_lds(&gemm_first_kernel<BM, BN, WM, WN>, cleared_first, 4 * (BM + BN) * 64 + 2 * BN * 4, a, tiles, WM * WN * 64, s);
+    return launch_with_lds(&gemm_split_kernel<BM, BN, WM, WN, false>, cleared, 2 * (BM + BN) * 144 + 2 * BN * 4, a, tiles, WM * WN * 64, s);
+}
+
+static bool split_gemm_valid(const SplitGemmArgs &a)
+{
+    return a.ld % 64 == 0 && a.n >= 1 && a.n <= a.n_pad && a.best && !(a.second && !(a.cmax && a.qnorm)) && !a.left == !a.cmax_left;
 }
 
 hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 {
     if (a.m <= 0) return hipSuccess;
-    if (a.ld % 64 != 0 || a.n < 1 || a.n > a.n_pad || !a.best || (a.second && !(a.cmax && a.qnorm))) return hipErrorInvalidValue;
+    if (!split_gemm_valid(a)) return hipErrorInvalidValue;
     auto tiles = [&](int b) { return (int64_t)((a.m + b - 1) / b) * ((a.n_pad + b - 1) / b); };
     // the largest tile that still gives every CU one
     if (tiles(256) >= num_cu) return launch_split_one<256, 256, 2, 4>(a, s);
     if (tiles(128) >= num_cu) return launch_split_one<128, 128, 2, 2>(a, s);
     return launch_split_one<64, 64, 2, 2>(a, s);
+}
+
+hipError_t launch_gemm_split_listed(const SplitGemmArgs &a, int num_cu, hipStream_t s)
+{
+    if (!split_gemm_valid(a) || a.left || !a.list || !a.nlisted || !a.x || a.d > a.ld) return hipErrorInvalidValue;
+    static LdsCleared cleared;
+    return launch_with_lds(&gemm_split_kernel<128, 128, 2, 2, true>, cleared, 2 * 256 * 144 + 2 * 128 * 4, a, 2 * num_cu, 256, s);
 }
 
 // The fp32 products of a few listed rows (a.list, *a.nlisted of them: dense rows of a.d floats) with every column, in
@@ -673,13 +854,15 @@ __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
 // left the rows out (skipped), all of them.
 __global__ __launch_bounds__(256) void near_ties_kernel(NearTiesArgs a)
 {
-    const uint32_t lane = threadIdx.x & 63u;
-    const bool all = a.skipped && *a.skipped > a.skip_from;
-    for (uint32_t i0 = a.first + blockIdx.x * 256u; i0 < a.last; i0 += gridDim.x * 256u) {
-        const uint32_t i = i0 + threadIdx.x;
+    const uint32_t lane = threadIdx.x & 63u, last = a.among ? *a.n_among : a.last;
+    const bool all = (a.skipped && *a.skipped > a.skip_from) || (a.skipped2 && *a.skipped2 > a.skip_from2);
+    for (uint32_t i0 = a.first + blockIdx.x * 256u; i0 < last; i0 += gridDim.x * 256u) {
+        uint32_t i = i0 + threadIdx.x;
         bool near = false;
-        if (i < a.last)
-            near = all || near_tie(a.best[i], a.second[i], a.ld, a.metric, a.qnorm[i], __uint_as_float(*a.cmax));
+        if (i < last) {
+            if (a.among) i = a.among[i];
+            near = all || near_tie(a.best[i], a.second[i], row_margin(a.ld, a.metric, a.qnorm[i], a.cmax, a.left ? a.left[i] : 0.f, a.cmax_left), a.metric);
+        }
         const unsigned long long m = __ballot(near);
         if (m == 0ull) continue;
         uint32_t at = 0;
@@ -691,6 +874,7 @@ __global__ __launch_bounds__(256) void near_ties_kernel(NearTiesArgs a)
         if (near) {
             a.list[at] = i;
             a.best[i] = ~0ull;
+            a.second[i] = 0xffffffffu;
         }
     }
 }
@@ -698,7 +882,7 @@ __global__ __launch_bounds__(256) void near_ties_kernel(NearTiesArgs a)
 hipError_t launch_near_ties(const NearTiesArgs &a, int num_cu, hipStream_t s)
 {
     if (a.last <= a.first) return hipSuccess;
-    if (a.ld % 64 != 0) return hipErrorInvalidValue;
+    if (a.ld % 64 != 0 || (a.among && (a.first != 0 || !a.n_among))) return hipErrorInvalidValue;
     hipLaunchKernelGGL(near_ties_kernel, dim3(std::min((a.last - a.first + 255u) / 256u, 4u * (uint32_t)num_cu)), dim3(256), 0, s, a);
     return hipGetLastError();
 }

@@ -568,11 +568,13 @@ hipError_t launch_gemm_listed(GemmArgs a, int num_cu, hipStream_t s); // the sam
 // rows whose second best value (second[]: as the split GEMM left it) is near their best, into a list
 struct NearTiesArgs {
     uint32_t first, last;        // rows [first, last) of best, second, qnorm
-    unsigned long long *best;    // of the listed rows: back to ~0
-    const uint32_t *second, *cmax;
-    const float *qnorm;
-    const uint32_t *skipped;     // or null: more than skip_from in it and the rows are listed all, whatever best and second hold
-    uint32_t skip_from;
+    const uint32_t *among, *n_among; // or (among not null) the *n_among rows in it, at most last of them; first is 0 then
+    unsigned long long *best;    // of the listed rows: back to ~0,
+    uint32_t *second;            //   and to all ones
+    const uint32_t *cmax, *cmax_left;
+    const float *qnorm, *left;   // (left: null for values of all three products)
+    const uint32_t *skipped, *skipped2; // or null: more than skip_from in it and the rows are listed all, whatever best and second hold
+    uint32_t skip_from, skip_from2;
     uint32_t *list, *nlisted, *also; // also (or null): raised as nlisted is
     int ld, metric;
 };
@@ -586,17 +588,30 @@ __device__ __forceinline__ float near_margin(int ld, int metric, float qn, float
     return 4.76837158e-7f * sqrtf((float)ld) * (metric == PK_METRIC_L2 ? qn + cmax : sqrtf(qn) * sqrtf(cmax));
 }
 
+// What two values of a row may differ by and still be in the other order for the fp32 kernel.  With `left` (of a row: the
+// length of what its first halfs leave out of it; cmax_left: the most that is of a centroid's) they are sums of the first
+// halfs' products alone, <x', c'> where x = x' + x", c = c' + c": off by <x", c> + <x', c">, which is
+// |x"| |c| + |x| |c"| at most (Cauchy-Schwarz; the factor covers the rounding of the lengths themselves).
+__device__ __forceinline__ float row_margin(int ld, int metric, float qn, const uint32_t *cmax, float left, const uint32_t *cmax_left)
+{
+    const float cm = __uint_as_float(*cmax);
+    const float near = near_margin(ld, metric, qn, cm);
+    if (!cmax_left) return near;
+    const float off = 1.001f * (left * sqrtf(cm) + sqrtf(qn) * __uint_as_float(*cmax_left));
+    return near + (metric == PK_METRIC_L2 ? 4.f : 2.f) * off; // (two products, and twice each under L2)
+}
+
 // Rows whose values cannot all be compared (a NaN among them: from a NaN or an infinity in the row or in a centroid, or
 // from finite values whose products overflow) are decided by the fp32 kernel too: their second value is kNoOrder.
 constexpr uint32_t kNoOrder = 0u;           // below the key of every number
 constexpr uint32_t kWorstKey = 0xfffffffeu; // the most a list's key can be, so that all ones stays "no list"
 
-// whether a row with that best (value key << 32 | column) and that second value goes to the fp32 kernels
-__device__ __forceinline__ bool near_tie(unsigned long long best, uint32_t second, int ld, int metric, float qn, float cmax)
+// whether a row with that best (value key << 32 | column) and that second value is decided by more exact values
+__device__ __forceinline__ bool near_tie(unsigned long long best, uint32_t second, float margin, int metric)
 {
     if (second == kNoOrder || second == 0xffffffffu) return second == kNoOrder;
     const float gap = fabsf(value_of(second, metric) - value_of((uint32_t)(best >> 32), metric));
-    return !(gap > near_margin(ld, metric, qn, cmax));
+    return !(gap > margin);
 }
 
 // top-1 of the same products, every fp32 operand held as two halfs (see pk_gemm.hip)
@@ -605,7 +620,8 @@ struct SplitRowsArgs {
     const float *c;      // [n_c][ld] centroid table, zero padded
     uint32_t m, n_c;
     int d, ld;
-    char *xs, *cs;       // [m][4 * ld] (or null), [n_c][4 * ld] out: split rows
+    char *xs, *cs;       // [m][4 * ld], [n_c][4 * ld] out: split rows (or null)
+    char *xh, *ch;       // [m][2 * ld], [n_c][2 * ld] out: the first halfs alone (or null)
     float *x_back, *c_back; // [m] (or null), [n_c] out: what undoes the row's scale
     float *qnorm;        // [m] out: squared norms, or null
     float *copy;         // [m][ld] out: fp32 rows, zero padded, or null
@@ -616,21 +632,30 @@ struct SplitRowsArgs {
     uint32_t *second;    // [m] set to all ones, or null
     unsigned long long *redo; // [m] set to ~0, or null
     uint32_t *cmax;      // raised to the largest squared norm of the centroids (as bits), or null
+    float *left;         // [m] out: length of what the first halfs leave out of the row, or null
+    uint32_t *cmax_left; // raised to the most that is of a centroid (as bits), or null
     QueryMeta meta;      // as in launch_prep_coarse, one handle (cand_off null: not wanted)
 };
 hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &m, hipStream_t s);
 struct SplitGemmArgs {
-    const char *q, *c;   // split rows [m][4 * ld], [n_pad][4 * ld]
+    const char *q, *c;   // split rows [m][4 * ld], [n_pad][4 * ld]; or, with `left`, first halfs [m][2 * ld], [n_pad][2 * ld]
     const float *q_back, *c_back, *qnorm, *cnorm; // (norms: L2 only)
     unsigned long long *best; // [m] best (value key << 32 | column) by atomicMin; ~0 on entry
     int m, n, n_pad, ld, metric;
     // optional: the value key of the second best column where it is near the best (else all ones, as on entry)
     uint32_t *second;         // [m] (or null: no row's near ties are of interest)
     const uint32_t *cmax;     // largest squared norm of the centroids (as bits)
-    const uint32_t *skipped;  // or null: with more than skip_from in it the launch does nothing
-    uint32_t skip_from;
+    const uint32_t *skipped, *skipped2; // or null: with more than skip_from in it the launch does nothing
+    uint32_t skip_from, skip_from2;
+    const float *left;        // [m] or null: the products of the first halfs alone, near by row_margin
+    const uint32_t *cmax_left;
+    // launch_gemm_split_listed: dense fp32 rows [.][d], split on the way; best, second, q_back, qnorm indexed by row like them
+    const float *x;
+    const uint32_t *list, *nlisted; // rows to score, and how many (on the device)
+    int d;
 };
 hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s);
+hipError_t launch_gemm_split_listed(const SplitGemmArgs &a, int num_cu, hipStream_t s);
 
 // build / insert
 // the lists of a top-1 assignment (low words of best[]), and how many rows each list gets (cnt: zero before)

@@ -809,7 +809,7 @@ __device__ __forceinline__ void centroid_body(const CentroidArgs &a, const Multi
         if ((uint32_t)lane < left) {
             const uint32_t q = q0 + (uint32_t)lane;
             const unsigned long long key = nr->split_best[q];
-            mine = near_tie(key, nr->second[q], row_bytes / 4, a.metric, a.qnorm[q], __uint_as_float(*nr->cmax));
+            mine = near_tie(key, nr->second[q], near_margin(row_bytes / 4, a.metric, a.qnorm[q], __uint_as_float(*nr->cmax)), a.metric);
             if (cb == 0 && wave == 0) nr->lists[q] = mine ? kListByRedo : (int32_t)(uint32_t)key;
         }
         near = __ballot(mine);

@@ -223,6 +223,29 @@ def test_near_tied_rows_of_a_build_go_where_the_fp32_scores_say(gpu_device, n, m
         assert torch.equal(assign.cpu(), want)
 
 
+@pytest.mark.parametrize("n,metric,d,half,apart,every", [
+    (16384, IP, 64, 40, 1, 1),  # 128 x 128 tiles that the lists do not fill; two steps
+    (32768 + 16384 + 3, L2, 200, 130, 130, 1),  # the rule: the second chunk goes to all three products at once; odd rows
+    (2 * 32768 + 5, IP, 33, 300, 300, 4),  # one in four: the first halves' kernel goes on; rows that are not aligned
+    (65536, L2, 1536, 512, 1, 8),  # 256 x 256 tiles, the longest rows
+    (16384, L2, 256, 16, 4, 2)])  # 64 x 64 tiles
+def test_rows_that_first_halves_cannot_tell_apart_go_where_the_fp32_scores_say(gpu_device, n, metric, d, half, apart, every):
+    """Pairs of centroids that differ by 2^-11 of their elements: less than the first halves leave out, far more than
+    what fp32 sums are off by.  The lists are those of the fp32 coarse step, row for row."""
+    cent, around = near_pairs(d, half, apart, n + d, every)
+    g = torch.Generator(device="cuda").manual_seed(d)
+    cent *= 1 + torch.randint(-1, 2, cent.shape, device="cuda", generator=g) * 2.0 ** -11
+    x = around(n)
+    ix = B.Index(cent, x, metric=metric)
+    try:
+        where = torch.from_numpy(lists_of(ix, n))
+        # (chunks that the GEMM scores; a shorter last one takes the centroid kernel in both)
+        want = torch.cat([ix.coarse(x[i:i + 16384].contiguous(), 1)[:, 0].cpu() for i in range(0, n, 16384)])
+        assert torch.equal(where, want.long())
+    finally:
+        ix.close()
+
+
 @pytest.mark.parametrize("metric,d,half,apart", [(IP, 128, 128, 1), (L2, 100, 130, 130), (L2, 64, 256, 64), (IP, 33, 1100, 1100), (IP, 1536, 130, 130), (L2, 1024, 150, 1)])
 def test_near_tied_vectors_go_to_the_same_lists_in_inserts_of_any_size(gpu_device, metric, d, half, apart):
     """Every vector has two lists that differ in the last bits of their scores, in one tile or in two: an insert large
