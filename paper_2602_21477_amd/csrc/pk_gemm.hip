@@ -34,74 +34,77 @@ __device__ __forceinline__ uint32_t listed_tiles(uint32_t rows, int n_pad)
     return (rows + kListRows - 1) / kListRows * ((uint32_t)(n_pad + kListCols - 1) / kListCols);
 }
 
-// four floats of a dense row of d (at: column 0 of the thread's pieces), from column `first` + scol on, zeros past its end
-__device__ __forceinline__ f32x4 dense_piece(const float *at, int first, int scol, int d, bool vec)
+// Four floats of a dense row of d from column `col` on: the load, and zeros past the row's end.  VEC: rows of whole 16-byte
+// pieces (d a multiple of 4, the rows aligned).  The load is unconditional, past the end from the row's last floats, as the
+// compiler waits for a load under a condition before it issues the next; the zeros are put in when the floats are used,
+// as putting them in waits for the load.
+template <bool VEC>
+__device__ __forceinline__ f32x4 dense_load(const float *row, int col, int d)
 {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (vec) { // rows of whole 16-byte pieces
-        if (first + scol < d) v = *reinterpret_cast<const f32x4 *>(at + first);
+    f32x4 v;
+    if constexpr (VEC) {
+        v = *reinterpret_cast<const f32x4 *>(row + (col < d ? col : d - 4));
     } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (first + scol + j < d) v[j] = at[first + j];
+        for (int j = 0; j < 4; ++j) v[j] = row[col + j < d ? col + j : d - 1];
     }
     return v;
 }
-
-// Smallest of the 32 lanes of each half wave, in the half's last lane (31 and 63): data-parallel moves only, where a
-// butterfly over shuffles would go through LDS (the epilogue took a third of the kernel that way).
-__device__ __forceinline__ uint32_t min_of_half(uint32_t x)
+__device__ __forceinline__ f32x4 dense_zeros(f32x4 v, int col, int d)
 {
-#define PK_DPP_MIN(ctrl, rows) x = min(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, rows, 0xf, false));
-    PK_DPP_MIN(0x111, 0xf) // row_shr 1, 2, 4, 8: lane 15 of every 16 has their smallest
-    PK_DPP_MIN(0x112, 0xf)
-    PK_DPP_MIN(0x114, 0xf)
-    PK_DPP_MIN(0x118, 0xf)
-    PK_DPP_MIN(0x142, 0xa) // row_bcast 15: into the second and fourth 16 lanes
-#undef PK_DPP_MIN
-    return x;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = col + j < d ? v[j] : 0.f;
+    return v;
 }
+static bool whole_pieces(const float *rows, int d) { return (d & 3) == 0 && (reinterpret_cast<uintptr_t>(rows) & 15) == 0; }
 
-// A wave's 64 x 64 scores (blocks of 32 x 32: lane l of a half wave holds column l of the rows kg * 4 + 8 * (r / 4) + r % 4)
-// into the best (value key, column) of the listed rows.
-__device__ __forceinline__ void best_of_tile(const GemmArgs &a, const f32x16 (&acc)[2][2], int m0, int n0, int rows, int lane)
+// A wave's scores of listed rows into their best (value key, column): blocks of 32 columns x 32 rows, lane l holds, of row
+// m0 + l % 32 of each block, columns n0 + (l / 32) * 4 + 8 * (r / 4) + r % 4.  One atomic per row: one per value, behind a
+// look at the best so far, took 140 us of 311 rows and 4096 columns.
+template <int MI, int NI>
+__device__ __forceinline__ void best_of_listed(const GemmArgs &a, const f32x16 (&acc)[MI][NI], int m0, int n0, int rows, int lane)
 {
     const int l32 = lane & 31, kg = lane >> 5;
-    if (n0 >= a.n) return; // (the same for the whole wave)
-    float cn[2];
+    uint32_t row[MI], top[MI];
+    int col[MI];
+    float qn[MI];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int n = n0 + j * 32 + l32;
-        cn[j] = a.metric == PK_METRIC_L2 && n < a.n ? a.cnorm[n] : 0.f;
+    for (int i = 0; i < MI; ++i) {
+        const int m = m0 + i * 32 + l32;
+        row[i] = a.list[m < rows ? m : rows - 1];
+        top[i] = 0xffffffffu;
+        col[i] = 0;
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int rr = kg * 4 + 8 * ((l32 & 15) >> 2) + (l32 & 3); // the row that lanes 0 .. 15 of a half wave answer for
-        uint32_t top = 0xffffffffu;
-        int col = 0;
+    for (int i = 0; i < MI; ++i) qn[i] = a.metric == PK_METRIC_L2 ? a.qnorm[row[i]] : 0.f;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        if (n0 + j * 32 >= a.n) continue; // (the same for the whole wave; the table has whole blocks of 32)
+        f32x4 cn[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            cn[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (a.metric == PK_METRIC_L2) cn[g] = *reinterpret_cast<const f32x4 *>(a.cnorm + n0 + j * 32 + kg * 4 + g * 8);
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int m = m0 + i * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
-            const float qn = a.metric == PK_METRIC_L2 && m < rows ? a.qnorm[a.list[m]] : 0.f;
-            uint32_t key[2];
+            const int n = n0 + j * 32 + kg * 4 + 8 * (r >> 2) + (r & 3);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int i = 0; i < MI; ++i) {
                 float v = acc[i][j][r];
-                if (a.metric == PK_METRIC_L2) v = fmaxf(cn[j] - 2.f * v + qn, 0.f);
-                key[j] = n0 + j * 32 + l32 < a.n ? min(order_bits(v, a.metric), kWorstKey) : 0xffffffffu;
-            }
-            const uint32_t low = min_of_half(min(key[0], key[1]));
-            const uint32_t b0 = __builtin_amdgcn_readlane(low, 31), b1 = __builtin_amdgcn_readlane(low, 63);
-            const uint32_t best = kg ? b1 : b0;
-            const unsigned long long e0 = __ballot(key[0] == best), e1 = __ballot(key[1] == best);
-            const uint32_t h0 = (uint32_t)(kg ? e0 >> 32 : e0), h1 = (uint32_t)(kg ? e1 >> 32 : e1);
-            if (l32 == r) {
-                top = best;
-                col = h0 ? __ffs(h0) - 1 : 32 + __ffs(h1) - 1;
+                if (a.metric == PK_METRIC_L2) v = fmaxf(cn[r >> 2][r & 3] - 2.f * v + qn[i], 0.f);
+                const uint32_t key = n < a.n ? min(order_bits(v, a.metric), kWorstKey) : 0xffffffffu;
+                col[i] = key < top[i] ? n : col[i];
+                top[i] = min(top[i], key);
             }
         }
-        const int m = m0 + i * 32 + rr;
-        if (l32 < 16 && m < rows) atomicMin(a.best + a.list[m], ((unsigned long long)top << 32) | (uint32_t)(n0 + col));
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        unsigned long long best = ((unsigned long long)top[i] << 32) | (uint32_t)col[i];
+        const unsigned long long other = __shfl_xor(best, 32);
+        best = other < best ? other : best;
+        if (kg == 0 && m0 + i * 32 + l32 < rows && (uint32_t)(best >> 32) != 0xffffffffu) atomicMin(a.best + row[i], best);
     }
 }
 
@@ -109,7 +112,7 @@ __device__ __forceinline__ void best_of_tile(const GemmArgs &a, const f32x16 (&a
 // keeps its best (value key, column) by atomicMin instead of its scores; the grid walks the tiles there are.  For lists
 // that fill tiles (see gemm_listed_kernel): 262 144 listed rows x 4096 x 768
 // in 18.0 ms = 92 TFLOP/s, where the kernel for few of them took 82.
-template <bool LISTED>
+template <bool LISTED, bool VEC = true>
 __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 {
     const int rows = LISTED ? (int)*a.nlisted : a.m;
@@ -117,7 +120,6 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
     if constexpr (LISTED)
         if (listed_tiles((uint32_t)rows, a.n_pad) <= a.many) return;
     [[maybe_unused]] const uint32_t tiles = tn * ((uint32_t)(rows + kGemmTile - 1) / kGemmTile);
-    [[maybe_unused]] const bool vec = LISTED && (a.d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
     __shared__ __align__(16) float sA[2][kGemmTile * kGemmLdsStride];
     __shared__ __align__(16) float sB[2][kGemmTile * kGemmLdsStride];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
         int ra = m0 + srow + 32 * i, rb = n0 + srow + 32 * i;
         ra = ra < rows ? ra : rows - 1; // clamp: rows past the end are computed and dropped
         rb = rb < a.n_pad ? rb : a.n_pad - 1;
-        ga[i] = a.q + (LISTED ? (size_t)a.list[ra] * a.d : (size_t)ra * ld) + scol;
+        ga[i] = a.q + (LISTED ? (size_t)a.list[ra] * a.d : (size_t)ra * ld + scol);
         gb[i] = a.c + (size_t)rb * ld + scol;
     }
     f32x4 ra4[4], rb4[4];
@@ -154,18 +156,19 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                        \
     {                                                                                    \
         rb4[i] = *reinterpret_cast<const f32x4 *>(gb[i] + (size_t)(ks) * kGemmBK);       \
-        if constexpr (LISTED) ra4[i] = dense_piece(ga[i], (ks) * kGemmBK, scol, a.d, vec); \
+        if constexpr (LISTED) ra4[i] = dense_load<VEC>(ga[i], (ks) * kGemmBK + scol, a.d); \
         else ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK);  \
     }
-#define PK_LSTORE(buf)                                                                                   \
+#define PK_LSTORE(buf, ks)                                                                               \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                        \
     {                                                                                                    \
+        if constexpr (LISTED) ra4[i] = dense_zeros(ra4[i], (ks) * kGemmBK + scol, a.d);                  \
         *reinterpret_cast<f32x4 *>(&sA[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = ra4[i];          \
         *reinterpret_cast<f32x4 *>(&sB[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = rb4[i];          \
     }
 
     PK_GLOAD(0)
-    PK_LSTORE(0)
+    PK_LSTORE(0, 0)
     __syncthreads();
     for (int ks = 0; ks < ksteps; ++ks) {
         const int buf = ks & 1;
@@ -185,11 +188,12 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][j4], fb[j][j4], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < 2; ++j) // (either way the same sums; a listed row's values belong into one lane)
+                        acc[i][j] = LISTED ? __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j][j4], fa[i][j4], acc[i][j], 0, 0, 0)
+                                           : __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][j4], fb[j][j4], acc[i][j], 0, 0, 0);
         }
         if (ks + 1 < ksteps) {
-            PK_LSTORE(buf ^ 1) // the other buffer was last read before the previous barrier
+            PK_LSTORE(buf ^ 1, ks + 1) // the other buffer was last read before the previous barrier
         }
         __syncthreads();
     }
@@ -197,7 +201,7 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #undef PK_LSTORE
 
     if constexpr (LISTED) {
-        best_of_tile(a, acc, m0 + wm * 64, n0 + wn * 64, rows, lane);
+        best_of_listed<2, 2>(a, acc, m0 + wm * 64, n0 + wn * 64, rows, lane);
         t += gridDim.x;
         continue;
     }
@@ -257,6 +261,8 @@ __device__ __forceinline__ float row_sum(float (&part)[4])
 
 // A wave per row, rows [0, m) from `x` (dense, d floats) and then n_c rows of the (padded) centroid table.
 // Bound by memory: 300 000 rows of 4 KB read and written at 4.3 TB/s.
+// T: 256-element parts of a row.
+template <int T>
 __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiArgs mm)
 {
     const int lane = threadIdx.x & 63;
@@ -268,23 +274,19 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     const int ld = a.ld, d = cent ? ld : a.d;
     const float *src = cent ? a.c + (size_t)r * ld : a.x + (size_t)r * d;
     const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0; // (wave-uniform)
-    constexpr int kT = (PK_MAX_DIM + 255) / 256;
-    f32x4 v[kT];
+    f32x4 v[T];
     float big = 0.f, sq[4] = {0.f, 0.f, 0.f, 0.f}, sq16[4] = {0.f, 0.f, 0.f, 0.f}, off[4] = {0.f, 0.f, 0.f, 0.f};
+    if (vec) { // (all of a row's loads in flight at once: none of them under a condition)
 #pragma unroll
-    for (int t = 0; t < kT; ++t) {
-        const int i = lane * 4 + 256 * t;
-        v[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (vec) {
-            if (i < d) v[t] = *reinterpret_cast<const f32x4 *>(src + i);
-        } else {
+        for (int t = 0; t < T; ++t) v[t] = dense_load<true>(src, lane * 4 + 256 * t, d);
+    } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (i + j < d) v[t][j] = src[i + j];
-        }
+        for (int t = 0; t < T; ++t) v[t] = dense_load<false>(src, lane * 4 + 256 * t, d);
     }
 #pragma unroll
-    for (int t = 0; t < kT; ++t)
+    for (int t = 0; t < T; ++t) v[t] = dense_zeros(v[t], lane * 4 + 256 * t, d);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             big = fmaxf(big, fabsf(v[t][j]));
@@ -300,7 +302,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     if (dst) dst += (size_t)r * ld * 4; // (null: the rows are wanted in their other forms only)
     if (first) first += (size_t)r * ld * 2;
 #pragma unroll
-    for (int t = 0; t < kT; ++t) {
+    for (int t = 0; t < T; ++t) {
         const int i = lane * 4 + 256 * t;
         if (i >= ld) continue;
         half4 hi, lo;
@@ -323,7 +325,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     if (!cent && a.half_rows) { // the row as a half-precision index stores it: rounded to nearest even, norm of the rounded values
         char *h = a.half_rows + (size_t)r * a.half_bytes;
 #pragma unroll
-        for (int t = 0; t < kT; ++t) {
+        for (int t = 0; t < T; ++t) {
             const int i = lane * 4 + 256 * t;
             if (i * 2 >= a.half_bytes) continue;
             half4 w;
@@ -371,7 +373,12 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStr
     if (a.m + a.n_c == 0) return hipSuccess;
     if (a.ld % 64 != 0 || a.ld > PK_MAX_DIM || a.d > a.ld) return hipErrorInvalidValue;
     if (a.half_rows && (a.half_bytes % 256 != 0 || a.half_bytes > PK_MAX_DIM * 2 || a.half_bytes < a.d * 2)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(split_rows_kernel, dim3((a.m + a.n_c + 3) / 4), dim3(256), 0, s, a, mm);
+    using Kernel = void (*)(SplitRowsArgs, MultiArgs);
+    static constexpr Kernel by_parts[] = {split_rows_kernel<1>, split_rows_kernel<2>, split_rows_kernel<3>,
+                                          split_rows_kernel<4>, split_rows_kernel<5>, split_rows_kernel<6>};
+    static_assert(PK_MAX_DIM <= 6 * 256, "a row has six parts at most");
+    const int wide = a.half_rows ? std::max(a.ld, a.half_bytes / 2) : a.ld; // (a half-precision row may be padded further)
+    hipLaunchKernelGGL(by_parts[(wide + 255) / 256 - 1], dim3((a.m + a.n_c + 3) / 4), dim3(256), 0, s, a, mm);
     return hipGetLastError();
 }
 
@@ -476,7 +483,7 @@ __device__ __forceinline__ void best_of_split(const SplitGemmArgs &a, const f32x
 }
 
 // LISTED: the rows are listed fp32 rows, which are split on their way into LDS, and the grid walks the tiles there are.
-template <int BM, int BN, int WM, int WN, bool LISTED>
+template <int BM, int BN, int WM, int WN, bool LISTED, bool VEC = true>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(SplitGemmArgs a)
 {
     constexpr int TH = WM * WN * 64;
@@ -497,7 +504,6 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     constexpr int ROWS_PER = TH / 8; // LDS rows between a thread's pieces
     const int steps = a.ld / 32;
     const size_t row_bytes = (size_t)a.ld * 4;
-    [[maybe_unused]] const bool vec = LISTED && (a.d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.x) & 15) == 0;
 
     for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
     // XCD-aware order: workgroups go to the 8 XCDs in turn; each XCD takes one contiguous part of the tiles, and walks
@@ -519,7 +525,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
         r = r < last ? r : last; // rows past the end are computed and dropped
         if (LISTED && i < ALOADS) {
             const uint32_t row = a.list[r];
-            src[i] = reinterpret_cast<const char *>(a.x + (size_t)row * a.d + (piece & 7) * 4);
+            src[i] = reinterpret_cast<const char *>(a.x + (size_t)row * a.d);
             scale[i] = 1.f / a.q_back[row]; // (a power of two: exact)
         } else {
             src[i] = (i < ALOADS ? a.q : a.c) + (size_t)r * row_bytes + (piece & 7) * 16;
@@ -541,17 +547,17 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
             if (LISTED && i < ALOADS)
-                st[i] = __builtin_bit_cast(u32x4, dense_piece(reinterpret_cast<const float *>(src[i]), ks * 32, (tid & 7) * 4, a.d, vec));
+                st[i] = __builtin_bit_cast(u32x4, dense_load<VEC>(reinterpret_cast<const float *>(src[i]), ks * 32 + (tid & 7) * 4, a.d));
             else
                 st[i] = *reinterpret_cast<gvec4>(in_global(src[i]) + at);
         }
     };
-    auto store = [&](const u32x4 (&st)[LOADS], int buf) {
+    auto store = [&](const u32x4 (&st)[LOADS], int buf, [[maybe_unused]] int ks) {
         char *const to = put + (size_t)buf * (BM + BN) * LD;
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
             if (LISTED && i < ALOADS) { // 4 floats: their first halfs into the row's first 64 bytes, the rest behind
-                const f32x4 v = __builtin_bit_cast(f32x4, st[i]);
+                const f32x4 v = dense_zeros(__builtin_bit_cast(f32x4, st[i]), ks * 32 + (tid & 7) * 4, a.d);
                 half4 hi, lo;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) { // (the same values as split_rows_kernel's)
@@ -600,7 +606,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     fetch(s0, 0);
     fetch(s1, 1);
     if constexpr (LISTED) __syncthreads(); // the tile before is done with LDS
-    store(s0, 0);
+    store(s0, 0, 0);
     fetch(s0, 2);
     // per column: what undoes its scale, and what its product is added to (a column that is no list comes behind every list)
     if (tid < BN) {
@@ -611,11 +617,11 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     __syncthreads();
     for (int ks = 0; ks < steps; ks += 2) { // steps is even: rows are padded to 64 elements
         step(0);
-        store(s1, 1); // (buffer 1 was last read before the barrier that ended the step before)
+        store(s1, 1, ks + 1); // (buffer 1 was last read before the barrier that ended the step before)
         fetch(s1, ks + 3);
         __syncthreads();
         step(1);
-        store(s0, 0);
+        store(s0, 0, ks + 2);
         fetch(s0, ks + 4);
         __syncthreads();
     }
@@ -634,6 +640,9 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
 // 816 TFLOP/s, where gemm_split_kernel takes 582 for the three products; the rows it leaves undecided (a tenth of them in
 // the first k-means iteration over 4096 clusters, from random rows; fewer where the centroids are trained) cost 83 us more
 // per 32768: one such iteration over 262 144 rows 5710 -> 3729 us, the build of 300 000 x 1024 with 512 lists 2836 -> 2585.
+// Of the 252 us, 150 go to the matrix instructions at the clock they leave (timed alone), 50 to the search for the best;
+// reading the next half step's operands ahead of this one's products (253), two workgroups per CU with tiles of half the
+// size (249) and three buffers (247) change nothing, waves of 128 x 128, one per SIMD, take 289.
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_first_kernel(SplitGemmArgs a)
 {
@@ -759,18 +768,21 @@ hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 hipError_t launch_gemm_split_listed(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 {
     if (!split_gemm_valid(a) || a.left || !a.list || !a.nlisted || !a.x || a.d > a.ld) return hipErrorInvalidValue;
-    static LdsCleared cleared;
-    return launch_with_lds(&gemm_split_kernel<128, 128, 2, 2, true>, cleared, 2 * 256 * 144 + 2 * 128 * 4, a, 2 * num_cu, 256, s);
+    static LdsCleared cleared, cleared_any;
+    constexpr int lds = 2 * 256 * 144 + 2 * 128 * 4;
+    if (whole_pieces(a.x, a.d)) return launch_with_lds(&gemm_split_kernel<128, 128, 2, 2, true, true>, cleared, lds, a, 2 * num_cu, 256, s);
+    return launch_with_lds(&gemm_split_kernel<128, 128, 2, 2, true, false>, cleared_any, lds, a, 2 * num_cu, 256, s);
 }
 
 // The fp32 products of a few listed rows (a.list, *a.nlisted of them: dense rows of a.d floats) with every column, in
 // gemm_scores_kernel's order of operations, so that the values are the same; every row keeps its best (value key,
 // column) by atomicMin.  Usually some hundred rows: bound by the latency of one tile, so a tile is 32 x 128 (a wave
 // 32 x 32: 16 MFMAs per step of 32 elements), its operands are requested two steps ahead, and the grid walks the tiles
-// there are.  As a form of the 128 x 128 kernel it took 210 us for whatever few rows there were; now 27 us for those of
-// 26 000 x 640 against 253 columns, 129 us for those of 262 144 x 768 against 4096.  Lists of more than a.many tiles (two
+// there are.  As a form of the 128 x 128 kernel it took 210 us for whatever few rows there were; now 41 us for 311 rows of
+// 768 against 4096 columns (140 with zeros put in as the rows were loaded, which waited for each load, and an atomic per value).  Lists of more than a.many tiles (two
 // rounds of the grid, then longer than one round of 128 x 128 tiles) are gemm_scores_kernel<true>'s, and one of the two
 // launches ends at once.
+template <bool VEC>
 __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
 {
     __shared__ __align__(16) float sA[2][kListRows * kGemmLdsStride];
@@ -780,13 +792,12 @@ __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
     const int ld = a.ld, ksteps = ld / kGemmBK; // even: rows are padded to 64 floats
     const int rows = (int)*a.nlisted;
     if (listed_tiles((uint32_t)rows, a.n_pad) > a.many) return;
-    const bool vec = (a.d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
     const uint32_t tn = (uint32_t)(a.n_pad + kListCols - 1) / kListCols, tm = (uint32_t)(rows + kListRows - 1) / kListRows;
     const int srow = tid >> 3, scol = (tid & 7) * 4;
     for (uint32_t t = blockIdx.x; t < tm * tn; t += gridDim.x) {
         const int m0 = (int)(t / tn) * kListRows, n0 = (int)(t % tn) * kListCols;
         const int mr = m0 + srow < rows ? m0 + srow : rows - 1; // clamp: rows past the end are computed and dropped
-        const float *ga = a.q + (size_t)a.list[mr] * a.d + scol, *gb[4];
+        const float *ga = a.q + (size_t)a.list[mr] * a.d, *gb[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             int rb = n0 + srow + 32 * i;
@@ -794,17 +805,17 @@ __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
             gb[i] = a.c + (size_t)rb * ld + scol;
         }
         f32x4 a0, a1, b0[4], b1[4];
-        f32x16 acc;
+        f32x16 acc[1][1];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
         auto fetch = [&](f32x4 &ra, f32x4 (&rb)[4], int ks) {
             const int at = (ks < ksteps ? ks : ksteps - 1) * kGemmBK; // (past the last step the last one again)
 #pragma unroll
             for (int i = 0; i < 4; ++i) rb[i] = *reinterpret_cast<const f32x4 *>(gb[i] + at);
-            ra = dense_piece(ga, at, scol, a.d, vec); // the caller's rows: no padding, any alignment
+            ra = dense_load<VEC>(ga, at + scol, a.d); // the caller's rows: no padding, any alignment
         };
-        auto put = [&](const f32x4 &ra, const f32x4 (&rb)[4], int buf) {
-            *reinterpret_cast<f32x4 *>(&sA[buf][srow * kGemmLdsStride + scol]) = ra;
+        auto put = [&](const f32x4 &ra, const f32x4 (&rb)[4], int buf, int ks) {
+            *reinterpret_cast<f32x4 *>(&sA[buf][srow * kGemmLdsStride + scol]) = dense_zeros(ra, ks * kGemmBK + scol, a.d);
 #pragma unroll
             for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4 *>(&sB[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = rb[i];
         };
@@ -815,67 +826,77 @@ __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
             for (int kc = 0; kc < kGemmBK / 8; ++kc) {
                 const f32x4 fa = *reinterpret_cast<const f32x4 *>(pa + kc * 8), fb = *reinterpret_cast<const f32x4 *>(pb + kc * 8);
 #pragma unroll
-                for (int j4 = 0; j4 < 4; ++j4) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[j4], fb[j4], acc, 0, 0, 0);
+                for (int j4 = 0; j4 < 4; ++j4) acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j4], fa[j4], acc[0][0], 0, 0, 0);
             }
         };
         __syncthreads(); // the tile before is done with LDS
         fetch(a0, b0, 0);
         fetch(a1, b1, 1);
-        put(a0, b0, 0);
+        put(a0, b0, 0, 0);
         fetch(a0, b0, 2);
         __syncthreads();
         for (int ks = 0; ks < ksteps; ks += 2) {
             step(0);
-            put(a1, b1, 1);
+            put(a1, b1, 1, ks + 1);
             fetch(a1, b1, ks + 3);
             __syncthreads();
             step(1);
-            put(a0, b0, 0);
+            put(a0, b0, 0, ks + 2);
             fetch(a0, b0, ks + 4);
             __syncthreads();
         }
-        const int n = n0 + wave * 32 + l32;
-        if (n >= a.n) continue;
-        const float cn = a.metric == PK_METRIC_L2 ? a.cnorm[n] : 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int m = m0 + kg * 4 + 8 * (r >> 2) + (r & 3);
-            if (m >= rows) continue;
-            const size_t row = a.list[m];
-            float v = acc[r];
-            if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[row], 0.f);
-            const unsigned long long key = ((unsigned long long)order_bits(v, a.metric) << 32) | (uint32_t)n;
-            if (key < a.best[row]) atomicMin(a.best + row, key); // (a stale look costs an atomic, never a result)
-        }
+        best_of_listed<1, 1>(a, acc, m0, n0 + wave * 32, rows, lane);
     }
 }
 
 // Rows whose second best value is near the best: into the list, their best[] back to "none yet".  Where the split GEMM
 // left the rows out (skipped), all of them.
+constexpr uint32_t kNearRows = 1024; // rows a workgroup looks at before it counts: one atomic each (a wave's own cost 40 us of 230 000 rows)
 __global__ __launch_bounds__(256) void near_ties_kernel(NearTiesArgs a)
 {
-    const uint32_t lane = threadIdx.x & 63u, last = a.among ? *a.n_among : a.last;
+    __shared__ uint32_t s_wave[4], s_at;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, last = a.among ? *a.n_among : a.last;
     const bool all = (a.skipped && *a.skipped > a.skip_from) || (a.skipped2 && *a.skipped2 > a.skip_from2);
-    for (uint32_t i0 = a.first + blockIdx.x * 256u; i0 < last; i0 += gridDim.x * 256u) {
-        uint32_t i = i0 + threadIdx.x;
-        bool near = false;
-        if (i < last) {
-            if (a.among) i = a.among[i];
-            near = all || near_tie(a.best[i], a.second[i], row_margin(a.ld, a.metric, a.qnorm[i], a.cmax, a.left ? a.left[i] : 0.f, a.cmax_left), a.metric);
+    for (uint32_t i0 = a.first + blockIdx.x * kNearRows; i0 < last; i0 += gridDim.x * kNearRows) {
+        constexpr uint32_t kEach = kNearRows / 256u;
+        uint32_t row[kEach], count = 0;
+        bool near[kEach];
+#pragma unroll
+        for (uint32_t u = 0; u < kEach; ++u) {
+            const uint32_t i = i0 + u * 256u + tid;
+            row[u] = i < last ? (a.among ? a.among[i] : i) : 0u;
+            near[u] = i < last;
         }
-        const unsigned long long m = __ballot(near);
-        if (m == 0ull) continue;
-        uint32_t at = 0;
-        if (lane == 0) {
-            at = atomicAdd(a.nlisted, (uint32_t)__popcll(m));
-            if (a.also) atomicAdd(a.also, (uint32_t)__popcll(m));
+#pragma unroll
+        for (uint32_t u = 0; u < kEach; ++u) {
+            if (!near[u]) continue;
+            const uint32_t r = row[u];
+            near[u] = all || near_tie(a.best[r], a.second[r], row_margin(a.ld, a.metric, a.qnorm[r], a.cmax, a.left ? a.left[r] : 0.f, a.cmax_left), a.metric);
+            count += near[u];
         }
-        at = __shfl(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-        if (near) {
-            a.list[at] = i;
-            a.best[i] = ~0ull;
-            a.second[i] = 0xffffffffu;
+        uint32_t upto = count; // of this thread and the lanes before it
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(upto, off);
+            if (lane >= (uint32_t)off) upto += y;
         }
+        if (lane == 63u) s_wave[wave] = upto;
+        __syncthreads();
+        if (tid == 0) {
+            const uint32_t sum = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+            s_at = sum ? atomicAdd(a.nlisted, sum) : 0u;
+            if (a.also && sum) atomicAdd(a.also, sum);
+        }
+        __syncthreads();
+        uint32_t at = s_at + upto - count;
+        for (uint32_t w = 0; w < wave; ++w) at += s_wave[w];
+#pragma unroll
+        for (uint32_t u = 0; u < kEach; ++u) {
+            if (!near[u]) continue;
+            a.list[at++] = row[u];
+            a.best[row[u]] = ~0ull;
+            a.second[row[u]] = 0xffffffffu;
+        }
+        __syncthreads(); // (s_wave, s_at: read before the next round writes them)
     }
 }
 
@@ -883,7 +904,7 @@ hipError_t launch_near_ties(const NearTiesArgs &a, int num_cu, hipStream_t s)
 {
     if (a.last <= a.first) return hipSuccess;
     if (a.ld % 64 != 0 || (a.among && (a.first != 0 || !a.n_among))) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(near_ties_kernel, dim3(std::min((a.last - a.first + 255u) / 256u, 4u * (uint32_t)num_cu)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(near_ties_kernel, dim3(std::min((a.last - a.first + kNearRows - 1u) / kNearRows, 4u * (uint32_t)num_cu)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -891,8 +912,9 @@ hipError_t launch_gemm_listed(GemmArgs a, int num_cu, hipStream_t s)
 {
     if (a.ld % 64 != 0 || a.d > a.ld || !a.best || !a.list || !a.nlisted) return hipErrorInvalidValue;
     a.many = 6u * (uint32_t)num_cu;
-    hipLaunchKernelGGL(gemm_listed_kernel, dim3(3 * num_cu), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(gemm_scores_kernel<true>, dim3(2 * num_cu), dim3(256), 0, s, a);
+    const bool vec = whole_pieces(a.q, a.d);
+    hipLaunchKernelGGL(vec ? gemm_listed_kernel<true> : gemm_listed_kernel<false>, dim3(3 * num_cu), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((vec ? gemm_scores_kernel<true, true> : gemm_scores_kernel<true, false>), dim3(2 * num_cu), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
