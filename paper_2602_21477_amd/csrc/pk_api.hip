@@ -217,6 +217,8 @@ struct Plan {
     bool raw_queries; // the coarse step reads the caller's query rows directly (no preparation launch)
     bool stream_rows; // the rows are read past the caches
     bool halves_first; // the coarse step's preparation also makes the half-precision copy of the queries
+    bool dense;       // every value of the probed rows is written, and the best selected among them: no sample, no gate
+    uint32_t cap, width; // dense: slots of each list, values of each query
     bool wl_small;    // the second half of the work list is small enough for one workgroup (rides in the threshold launch)
     // buffers
     char *qs32, *qs;
@@ -228,6 +230,8 @@ struct Plan {
     unsigned long long *cpartial, *cbuf;
     int32_t *probes;
     size_t bytes;
+    size_t need;    // what the workspace is made to hold: dense calls leave room for the same call through sample and gate
+                    // (which is what it takes when it is captured)
 };
 
 void carve(Plan &p, char *base, const pk_index *own)
@@ -254,15 +258,19 @@ void carve(Plan &p, char *base, const pk_index *own)
     }
     if (p.need_fine) {
         const size_t nl = (size_t)p.nh * p.nlist_max;
-        p.lcnt = c.take<uint32_t>(2 * nl); // pair counters, then the fill marks: cleared together
+        p.lcnt = c.take<uint32_t>(2 * nl + 2); // pair counters, then the fill marks, then the dense layout's tile counters: cleared together
         p.lfill = p.lcnt ? p.lcnt + nl : nullptr;
         p.lstart = c.take<uint32_t>(nl);
         p.ltile = c.take<uint32_t>(nl);
         p.lhtile = c.take<uint32_t>(nl);
         p.pair_off = c.take<uint32_t>(nq * (p.nprobe + 1));
-        p.slot_q = c.take<uint32_t>(nq * p.nprobe);
-        p.slot_o = c.take<uint32_t>(nq * p.nprobe);
+        const size_t slots = std::max(nq * p.nprobe, nl * p.cap);
+        p.slot_q = c.take<uint32_t>(slots);
+        p.slot_o = c.take<uint32_t>(slots);
         p.tiles = c.take<Tile>((size_t)p.tile_cap + 1);
+        p.cbuf = c.take<unsigned long long>((size_t)p.cbuf_entries + 16);
+    }
+    if (p.need_fine && !p.dense) {
         p.tiles_hot = c.take<Tile>((size_t)p.tile_cap + 1);
         p.tau = c.take<uint32_t>(nq);
         p.tlo = c.take<float>(nq);
@@ -274,7 +282,6 @@ void carve(Plan &p, char *base, const pk_index *own)
         p.sslot_o = c.take<uint32_t>(nq);
         p.stiles = c.take<Tile>(nq * p.sp + 1);
         p.svals = c.take<float>(nq * p.span + 16);
-        p.cbuf = c.take<unsigned long long>((size_t)p.cbuf_entries + 16);
     }
     p.bytes = round_up(c.off, 256);
 }
@@ -301,6 +308,7 @@ struct Tunables {
                   // lists' scan (0: one after the other on the caller's stream)
     int wl_aside; // PK_TUNE_WL_ASIDE: large batches build the second half of the work list beside the sample scan
     int fuse_tau; // PK_TUNE_FUSE_TAU: small batches take sample, thresholds and work list in one launch
+    int dense;    // PK_TUNE_DENSE: calls of few values write them whole (1), or go through sample and gate (0)
 };
 
 #ifdef PK_DEV_TUNABLES
@@ -330,7 +338,8 @@ const Tunables &tunables()
                         env("PK_TUNE_KS", 1),        env("PK_TUNE_SP", 0), env("PK_TUNE_SP_MAX", 16),   env("PK_TUNE_GEMM_WGS", 128),
                         env("PK_TUNE_DENSESEL", 1),  env("PK_TUNE_GRABDIV", 8),   env("PK_TUNE_HIST", 1),
                         env("PK_TUNE_RS_FROM", 0),   env("PK_TUNE_RS_NQ", 512),   env("PK_TUNE_HOT_GRAB", 1),
-                        env("PK_TUNE_HOT_CUS", 96),  env("PK_TUNE_WL_ASIDE", 1),  env("PK_TUNE_FUSE_TAU", 1)};
+                        env("PK_TUNE_HOT_CUS", 96),  env("PK_TUNE_WL_ASIDE", 1),  env("PK_TUNE_FUSE_TAU", 1),
+                        env("PK_TUNE_DENSE", 1)};
     }();
     return t;
 }
@@ -342,6 +351,11 @@ constexpr int kSampleSlots = 1;
 constexpr int64_t kRoomyBatch = 128;
 // largest emission region whose overflow is provided for (see make_plan)
 constexpr uint32_t kRescueFrom = 8192;
+
+// Limits of the calls whose values are written whole (see make_plan).
+constexpr uint64_t kDenseWidth = 1u << 18;   // values of a query
+constexpr uint64_t kDenseValues = 32u << 20; // values of a call: 128 MB
+constexpr uint64_t kDenseSlots = 1u << 20;   // slots of all lists: two tables of 4 MB
 
 int grid_for(const pk_index *ix, int row_bytes, int mq)
 {
@@ -384,8 +398,9 @@ uint32_t emit_cap_for(const pk_index *own, int K, uint64_t wmax, int64_t nq)
 // into every handle; worst also takes the largest value of every size that depends on how the
 // queries spread (tile groups, sample pages), which is how pk_workspace_reserve sizes the
 // workspace for every call within its limits.  lean: the smallest threshold sample, for a workspace that cannot grow.
+// dense_ok: the call may write all its values (coarse and fine step in one go, and lists as long as the host knows them).
 int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t nq, int k, int nprobe,
-              bool need_coarse, bool need_fine, int64_t ahead = 0, bool worst = false, bool lean = false)
+              bool need_coarse, bool need_fine, int64_t ahead = 0, bool worst = false, bool lean = false, bool dense_ok = false)
 {
     const pk_index *own = hs[0];
     std::memset(&p, 0, sizeof(p));
@@ -529,6 +544,28 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     p.cbuf_entries = (uint64_t)nq * p.ecap;
     // a smaller batch has larger regions: none needs more in all than this
     if (worst) p.cbuf_entries = std::max<uint64_t>(p.cbuf_entries, std::min<uint64_t>(32768ull * (uint64_t)nq, 4ull << 20));
+    const uint64_t gated_entries = p.cbuf_entries;
+    uint32_t most = 0; // queries of a handle
+    for (int a = 0; a < nh; ++a) most = std::max(most, worst ? (uint32_t)nq : qlo[a + 1] - qlo[a]);
+    {
+        // Values written whole: DENSE_RULE
+        const uint64_t width = round_up(std::max<uint64_t>(wmax, 16), 16), slots = (uint64_t)nh * (uint64_t)nlist_hi * most;
+        const uint64_t values = (uint64_t)nq * width;
+        if (worst) { // (what any call within the limits may take)
+            p.cap = (uint32_t)std::min<uint64_t>(most, kDenseSlots / ((uint64_t)nh * (uint64_t)nlist_hi));
+            p.cbuf_entries = std::max<uint64_t>(p.cbuf_entries, std::min<uint64_t>((uint64_t)nq * std::min<uint64_t>(width, kDenseWidth), kDenseValues) / 2);
+        } else if (dense_ok && need_coarse && need_fine && !lean && tunables().dense && own->emit_cap == 0 && nlist_hi <= kDenseSelectMax &&
+                   width <= kDenseWidth && values <= kDenseValues && slots <= kDenseSlots && (p.K <= kSelThreads || width <= 16u * kSelThreads)) {
+            p.dense = true;
+            p.cap = most;
+            p.width = (uint32_t)width;
+            if (p.hot_rs) { // (few values in all: the regular tiles take every list)
+                p.hot_rs = false;
+                p.hot_from = 0xffffffffu;
+            }
+            p.cbuf_entries = (values + 1) / 2;
+        }
+    }
     p.halves_first = need_coarse && need_fine && nh == 1 && p.f16 && !p.raw_queries;
     // few lists, pairs and tiles: the threshold kernel's workgroups lay out slots and tiles as well (see wl_spread)
     p.wl_small = (uint64_t)nh * (uint64_t)nlist_hi <= kWlSmallLists && (uint64_t)nq * (uint64_t)nprobe <= 16384 && tiles <= 65536;
@@ -537,10 +574,19 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     // launch that scores such queries again, 3 us when there is none, then pays for itself.  The regions of smaller
     // batches are roomier.  The rescued keys' regions are the sample's values, which nothing reads any more by then.
     // Nor does it take a launch to be ready for a query that would have to emit a quarter of all its rows.
-    if (need_fine && nq > kRoomyBatch && p.ecap <= kRescueFrom && 4ull * p.ecap < round_up(wmax, 16))
+    if (need_fine && !p.dense && nq > kRoomyBatch && p.ecap <= kRescueFrom && 4ull * p.ecap < round_up(wmax, 16))
         p.rescues = (uint32_t)std::min<uint64_t>((uint64_t)nq * p.span * 4 / (kRescueCap * 8), kRescueRegions);
     p.tile_cap = (uint32_t)tiles;
+    if (p.dense) {
+        Plan gated = p;
+        gated.dense = false;
+        gated.cap = 0;
+        gated.cbuf_entries = gated_entries;
+        carve(gated, nullptr, own);
+        p.need = gated.bytes;
+    }
     carve(p, nullptr, own);
+    p.need = std::max(p.need, p.bytes);
     return PK_OK;
 }
 
@@ -619,6 +665,12 @@ void fill_worklist_args(const Plan &p, const pk_index *own, WorklistArgs &w, Sam
     w.scalars = p.scalars + 4;
     w.scalars_hot = p.scalars + 12;
     w.lcnt_cleared = p.need_coarse;
+    if (p.dense) {
+        w.cap = p.cap;
+        w.width = p.width;
+        w.mq = p.hot_from == 0 ? p.mq_h : p.mq_f;
+        w.scalars = p.lcnt + 2 * (size_t)p.nh * p.nlist_max;
+    }
     if (p.nh == 1) {
         w.len1 = own->host.list_len;
         w.P1 = (uint32_t)own->host.P;
@@ -638,7 +690,7 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
     qm.cand_cnt = p.cand_cnt;
     qm.qagent = p.qagent;
     qm.clear = p.need_fine ? p.lcnt : nullptr;
-    qm.nclear = p.need_fine ? 2u * (uint32_t)p.nh * (uint32_t)p.nlist_max : 0u; // and the fill marks behind them
+    qm.nclear = p.need_fine ? 2u * (uint32_t)p.nh * (uint32_t)p.nlist_max + 2u : 0u; // and what lies behind them
     // small segments: one launch of the centroid kernel for all of them
     CentroidArgs ca{};
     if (p.halves_first) {
@@ -743,6 +795,58 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
     return PK_OK;
 }
 
+// Fine search over the work list that the coarse selection has laid out whole: every value is written, and the best of
+// each query's are selected.
+int run_dense(const Plan &p, const MultiArgs &m, pk_index *own, int64_t *out_ids, float *out_dist, hipStream_t s, bool timed)
+{
+    if (timed) PK_TRY(mark(own, s));
+    const bool sliced = p.hot_from == 0;
+    ScanArgs sa{};
+    sa.tiles = p.tiles;
+    sa.ntiles = p.lcnt + 2 * (size_t)p.nh * p.nlist_max;
+    sa.tile_ctr = p.lcnt + 2 * (size_t)p.nh * p.nlist_max + 1;
+    sa.qs = p.qs;
+    sa.qnorm = p.qn;
+    sa.slot_query = p.slot_q;
+    sa.slot_out = p.slot_o;
+    sa.out = reinterpret_cast<float *>(p.cbuf);
+    sa.k = p.k;
+    sa.row_bytes = own->row_bytes;
+    sa.metric = own->cfg.metric;
+    sa.storage = own->cfg.storage;
+    sa.mq = sliced ? p.mq_h : p.mq_f;
+    sa.nt = p.stream_rows;
+    sa.lcnt = p.lcnt;
+    sa.tile_cap = p.tile_cap;
+    sa.grab_div = tunables().grabdiv;
+    // (no more workgroups than tiles)
+    const int grid = (int)std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)(sliced ? p.grid_h : p.grid_f), p.tile_cap));
+    if (!sliced) PK_HIP(launch_scan(sa, grid, s));
+    if (timed) {
+        own->prof_beside.push_back(0);
+        PK_TRY(mark(own, s));
+    }
+    if (sliced) PK_HIP(launch_scan_ks(sa, grid, s));
+    if (timed) PK_TRY(mark(own, s));
+    FinalArgs f{};
+    f.K = p.K;
+    f.k = p.k;
+    f.nprobe = p.nprobe;
+    f.metric = own->cfg.metric;
+    f.storage = own->cfg.storage;
+    f.row_bytes = own->row_bytes;
+    f.pair_off = p.pair_off;
+    f.probes = p.probes;
+    f.qagent = p.qagent;
+    f.out_ids = out_ids;
+    f.out_dist = out_dist;
+    f.vals = sa.out;
+    f.width = p.width;
+    PK_HIP(launch_select_final(f, m, p.nq, s));
+    if (timed) PK_TRY(mark(own, s));
+    return PK_OK;
+}
+
 // Fine search of one batch over p.probes.
 int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, int64_t *out_ids, float *out_dist,
              hipStream_t s, bool timed, bool counted, bool fixed)
@@ -751,6 +855,7 @@ int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, i
     WorklistArgs w;
     SampleArgs sm;
     fill_worklist_args(p, own, w, sm);
+    if (p.dense) return counted ? run_dense(p, m, own, out_ids, out_dist, s, timed) : PK_ERR_UNSUPPORTED;
     if (!counted) PK_HIP(launch_worklist_count(w, sm, m, s));
     ScanArgs ss{};
     ss.tiles = p.stiles;
@@ -934,14 +1039,16 @@ int search_impl(pk_index *const *hs, int nh, const int64_t *q_offsets, const flo
         for (int a = 0; a <= nh; ++a)
             qlo[a] = (uint32_t)std::min<int64_t>(std::max<int64_t>(q_offsets[a] - q0, 0), nq);
         Plan p;
-        PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly));
+        // (under capture the lists may have grown when the graph runs: by more than the host knows of)
+        PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, false,
+                         mode == kFull && !capturing(s)));
         if (fixed_ws) {
-            if (p.bytes > fixed_bytes)
-                PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, true));
+            for (int lean = 0; lean < 2 && p.bytes > fixed_bytes; ++lean)
+                PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, lean != 0));
             if (nq != nq_all || p.bytes > fixed_bytes) return PK_ERR_WORKSPACE;
             carve(p, fixed_ws, own);
         } else {
-            PK_TRY(ensure_ws(own, p.bytes, s));
+            PK_TRY(ensure_ws(own, p.need, s));
             carve(p, own->ws, own);
         }
         MultiArgs m;

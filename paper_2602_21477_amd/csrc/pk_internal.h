@@ -225,8 +225,8 @@ struct Tile {
     uint32_t row0;    // position of the page's first row in the list
     uint32_t qbeg;    // first slot of the group in slot_query / slot_out
     uint16_t nrows;   // rows to score (<= rows per page)
-    uint16_t qcnt;    // slots in the group (<= MQ)
-    uint32_t pad;
+    uint16_t qcnt;    // slots in the group (<= MQ); of wl_lay_query's tiles: the group's number in its list
+    uint32_t list;    // of wl_lay_query's tiles: handle * nlist_max + list
 };
 static_assert(sizeof(Tile) == 32, "Tile is 32 bytes");
 
@@ -272,7 +272,11 @@ struct ScanArgs {
     int row_bytes, metric, storage, mq;
     uint32_t rr_first;           // rows-in-registers kernel: pairs of tiles its (first) launch starts with, one per workgroup
     bool rr_join;                // ... this launch joins one that is running (same counter, same rr_first)
-    bool nt;                     // gated mode: the rows are read past the caches (they would not stay in them anyway)
+    bool nt;                     // fine search: the rows are read past the caches (they would not stay in them anyway)
+    // laid mode (lcnt != NULL): the tiles and slots are those of wl_lay_query, and every value is written
+    const uint32_t *lcnt;        // pairs of each list (of all handles)
+    uint32_t tile_cap;           // more tiles than this: the layout was refused, nothing is scanned
+    int grab_div;                // tiles per grab = tiles / (grid * this), 1 .. 8
 };
 hipError_t launch_scan(const ScanArgs &a, int grid, hipStream_t s);
 hipError_t launch_scan_ks(const ScanArgs &a, int grid, hipStream_t s);
@@ -346,8 +350,9 @@ struct LdsCleared {
     std::atomic<int> on[kMaxDevices];
 };
 
+// (fixed: bytes of LDS that the kernel declares itself; the two together are at most what a workgroup can have)
 template <typename K>
-inline hipError_t allow_lds(K kernel, LdsCleared &c)
+inline hipError_t allow_lds(K kernel, LdsCleared &c, int fixed = 0)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -357,7 +362,7 @@ inline hipError_t allow_lds(K kernel, LdsCleared &c)
         int most = 0;
         e = hipDeviceGetAttribute(&most, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
         if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, most - fixed);
         if (e != hipSuccess) return e;
         if (tracked) c.on[dev].store(1, std::memory_order_release);
     }
@@ -412,6 +417,9 @@ struct FinalArgs {
     uint32_t rregions, rcap;          // rregions 0: launch_rescue was not called
     const uint32_t *hist;             // [nq][kHistBins] candidates the scan emitted per bucket, stored or not (null: not counted)
     const float *tlo, *tinv;          // [nq] bucket scale
+    // every value of the query's range instead of emitted keys (keys is null): query q's at vals[q * width]
+    const float *vals;
+    uint32_t width;
 };
 constexpr uint32_t kRescueCap = 4096;    // keys per rescue region: what the final selection takes in registers
 constexpr uint32_t kRescueRegions = 128; // most queries of a call that are rescued
@@ -509,6 +517,9 @@ struct WorklistArgs {
     uint32_t tile_cap;
     uint32_t *scalars;         // [0] ntiles [1] tile counter [2] grab size
     uint32_t *scalars_hot;     // [0] hot tiles [1] tile counter [2] grab size
+    // whole layout in one go (wl_lay_query), values written whole:
+    uint32_t cap;              // slots of each list (the most queries of a handle)
+    uint32_t width;            // elements of each query's range
     // one handle only: its list lengths, page size and list count, so that the work-list layout of a small batch
     // reads them without first chasing the handle's descriptor (null / 0 otherwise)
     const uint32_t *len1;
@@ -543,7 +554,8 @@ hipError_t launch_tau(const SampleArgs &a, hipStream_t s, const WorklistArgs *wa
 // launch_scan over the sample, launch_tau and launch_worklist_tiles); sm.span at most 4096
 hipError_t launch_sample_tau(const ScanArgs &a, const SampleArgs &sm, const WorklistArgs &wa, const MultiArgs &ma, int grid,
                              hipStream_t s);
-// wa / sm / ma given: the selection's workgroups also do launch_worklist_count's work for their queries
+// wa / sm / ma given: the selection's workgroups also do launch_worklist_count's work for their queries, or with wa->width
+// the whole work list (a.slot_query and slot_out then have wa->cap entries per list, a.scalars' first two words are zero)
 hipError_t launch_select_dense(const float *vals, const uint32_t *qoff, const uint32_t *qcnt, uint32_t max_cnt, int metric,
                                int K, int64_t nq, int32_t *probes, hipStream_t s, const WorklistArgs *wa = nullptr,
                                const SampleArgs *sm = nullptr, const MultiArgs *ma = nullptr);

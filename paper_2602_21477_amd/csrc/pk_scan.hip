@@ -38,6 +38,12 @@ PK_DEV_MARKS(scan)
 
 namespace pk {
 
+// What becomes of the values of a scan:
+//   kSample  written; one query per tile (the threshold sample)
+//   kGated   those that pass the query's gate are emitted (fine search)
+//   kLaid    written, over the tiles and slots of wl_lay_query (fine search of calls whose values fit the workspace whole)
+enum ScanMode { kSample, kGated, kLaid };
+
 // per-slot LDS arrays of the scan kernels: out, qn, thr, q, base, lo, inv, bmax
 constexpr int kScanSlotWords = 8;
 constexpr int kKsStride = kIterBytes + kQPadBytes; // LDS bytes per slot and staged slice
@@ -297,7 +303,8 @@ __device__ __forceinline__ void emit_block(const ScanArgs &a, const Slots &s, f3
 // mt*16 + lg*4 + i.  Dense mode writes every value; gated mode emits the survivors.
 // COHERENT (dense mode): the values are written through to where every CU of the device reads them
 // (another workgroup of the same launch goes on to read them).
-template <int MT, bool GATED, bool COHERENT = false>
+// LAID: a query whose values have no place is left out.
+template <int MT, bool GATED, bool COHERENT = false, bool LAID = false>
 __device__ __forceinline__ void finish_block(const ScanArgs &a, const Slots &s, f32x4 (&acc)[MT][2], int rb, int ln, int lg,
                                              int nrows, uint32_t qcnt, uint32_t row0, gfloats txn, float *lds_vals = nullptr)
 {
@@ -321,7 +328,7 @@ __device__ __forceinline__ void finish_block(const ScanArgs &a, const Slots &s, 
                     const int m = mt * 16 + lg * 4 + i;
                     float v = acc[mt][nt][i];
                     if (a.metric == PK_METRIC_L2) v = l2_from_dot(xn, v, s.qn[m & (MQ - 1)]);
-                    if ((uint32_t)m < qcnt && row < nrows_pad) {
+                    if ((uint32_t)m < qcnt && row < nrows_pad && (!LAID || s.out[m] != 0xffffffffu)) {
                         float *dst = a.out + (size_t)s.out[m] + row0 + row;
                         if constexpr (COHERENT) {
                             if (lds_vals) lds_vals[row0 + row] = live ? v : worst; // (one slot, one tile: the values' only reader is this workgroup)
@@ -336,6 +343,26 @@ __device__ __forceinline__ void finish_block(const ScanArgs &a, const Slots &s, 
     }
 }
 
+// The schedule over wl_lay_query's tiles, whose number is final by now (more than there is room for: none are scanned).
+__device__ __forceinline__ void start_laid(const ScanArgs &a, Sched &sc, uint32_t bid, uint32_t nblk)
+{
+    uint32_t nt = *a.ntiles;
+    if (nt > a.tile_cap) nt = 0;
+    const uint32_t g = nt / (nblk * (uint32_t)a.grab_div);
+    sc.start(nt, g < 1 ? 1 : (g > 8 ? 8 : g), bid, nblk);
+}
+
+// Slots in a tile's group: in the descriptor, or (kLaid) those of the list's pairs that came into this group.
+template <ScanMode MODE, int MQ>
+__device__ __forceinline__ uint32_t tile_slots(const ScanArgs &a, const Tile &cur, uint32_t qbeg, uint32_t cur_qbeg, uint32_t cur_qcnt)
+{
+    const uint32_t n = __builtin_amdgcn_readfirstlane((uint32_t)cur.qcnt);
+    if constexpr (MODE != kLaid) return n;
+    if (qbeg == cur_qbeg) return cur_qcnt;
+    const uint32_t left = __builtin_amdgcn_readfirstlane(a.lcnt[cur.list]) - n * (uint32_t)MQ;
+    return left < (uint32_t)MQ ? left : (uint32_t)MQ;
+}
+
 // ------------------------------------------------------------------ whole-group kernel
 
 // MT = query tiles of 16 slots held in LDS (MQ = 16*MT); WAVES = waves per workgroup;
@@ -344,10 +371,11 @@ __device__ __forceinline__ void finish_block(const ScanArgs &a, const Slots &s, 
 // FUSED (threshold sample of a small batch; sm, extra_off given): the workgroup that scores the last of a
 // query's sample tiles goes on to work out that query's threshold, so that no launch of its own is needed
 // for it.  bid / nblk: this workgroup's number among those of the launch that take tiles.
-template <int STORAGE, int MT, int WAVES, bool GATED, bool FUSED, bool NT>
+template <int STORAGE, int MT, int WAVES, ScanMode MODE, bool FUSED, bool NT>
 __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_t bid, uint32_t nblk, const SampleArgs *sm,
                                           uint32_t extra_off)
 {
+    constexpr bool GATED = MODE == kGated, FINE = MODE != kSample;
     constexpr int MQ = MT * 16;
     const int row_bytes = a.row_bytes;
     const int qstride = row_bytes + kQPadBytes;
@@ -364,7 +392,7 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ln = lane & 15, lg = lane >> 4;
     // (the sample's kernels have registers to spare and one tile per workgroup to wait for: a 64-bit address per lane there)
-    const uint32_t lane_part = RowLoad<NT>::lane_offset(ln, lg, row_bytes), lane_off = GATED ? lane_part : 0u;
+    const uint32_t lane_part = RowLoad<NT>::lane_offset(ln, lg, row_bytes), lane_off = FINE ? lane_part : 0u;
     const int nit = row_bytes / kIterBytes;
     const int chunks_per_row = row_bytes / 16;
     uint32_t cur_qbeg = 0xffffffffu, cur_qcnt = 0;
@@ -377,6 +405,8 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
         const uint32_t nt = (uint32_t)sm->nq * (uint32_t)sm->sp;
         const uint32_t g = nt / (uint32_t)(sm->scan_grid * 4);
         sc.start(nt, g < 1 ? 1 : (g > 8 ? 8 : g), bid, nblk);
+    } else if constexpr (MODE == kLaid) {
+        start_laid(a, sc, bid, nblk);
     } else {
         sc.start(*a.ntiles, *a.batch, bid, nblk);
     }
@@ -387,12 +417,11 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
     [[maybe_unused]] float *const sv = reinterpret_cast<float *>(fx + 4 * 256 + 16);      // [span] values (one tile per query)
     Tile cur = a.tiles[sc.t];
     while (sc.t < sc.ntiles) {
-        const gbytes tx = GATED ? uniform(in_global(cur.x)) : in_global(cur.x) + lane_part;
+        const gbytes tx = FINE ? uniform(in_global(cur.x)) : in_global(cur.x) + lane_part;
         const gfloats txn = in_global(cur.xn);
         const uint32_t row0 = cur.row0;
         PK_MARK_IF(scan, GATED ? 1 : 9, bid == 0);
         const uint32_t qbeg = __builtin_amdgcn_readfirstlane(cur.qbeg);
-        const uint32_t qcnt = __builtin_amdgcn_readfirstlane((uint32_t)cur.qcnt);
         const int nrows = __builtin_amdgcn_readfirstlane((int)cur.nrows);
 
         u32x4 xa[2][4], xb[2][4]; // two register buffers of one 256-byte slice of 32 rows each
@@ -436,6 +465,7 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
         bool next_fresh;
         const uint32_t tn = sc.peek(s_misc, next_end, next_fresh);
         const Tile nxt = a.tiles[tn < sc.ntiles ? tn : sc.ntiles - 1]; // in flight while this tile is scored
+        const uint32_t qcnt = tile_slots<MODE, MQ>(a, cur, qbeg, cur_qbeg, cur_qcnt);
         if (qbeg != cur_qbeg || qcnt != cur_qcnt) {
             __syncthreads(); // everyone is done with the previous query group
             const int mrows = qrows < MQ ? qheld : (int)((qcnt + 15u) & ~15u); // rows past the group's last: zeros
@@ -497,7 +527,7 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
             }
             preloaded = false;
             bool scored = false;
-            if constexpr (!GATED && MT == 1) {
+            if constexpr (MODE == kSample && MT == 1) {
                 // The threshold sample: one query per tile, one 32-row block per wave, so a wave's time is its
                 // chain of slices.  Long rows keep three slices in flight ahead of the one being multiplied
                 // (four register buffers; the multiplication order is unchanged, so the values are too).
@@ -533,7 +563,7 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
                 }
             }
             PK_MARK_IF(scan, GATED ? 3 : 11, bid == 0);
-            finish_block<MT, GATED, FUSED>(a, s, acc, rb, ln, lg, nrows, qcnt, row0, txn, FUSED && one ? sv : nullptr);
+            finish_block<MT, GATED, FUSED, MODE == kLaid>(a, s, acc, rb, ln, lg, nrows, qcnt, row0, txn, FUSED && one ? sv : nullptr);
             PK_MARK_IF(scan, GATED ? 4 : 12, bid == 0);
         }
 #undef PK_ROWS
@@ -587,11 +617,11 @@ __device__ __forceinline__ void scan_body(const ScanArgs &a, char *smem, uint32_
     }
 }
 
-template <int STORAGE, int MT, int WAVES, bool GATED, bool NT>
-__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu((!GATED && MT == 1) ? 2 : 3, 8))) void scan_kernel(ScanArgs a)
+template <int STORAGE, int MT, int WAVES, ScanMode MODE, bool NT>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu((MODE == kSample && MT == 1) ? 2 : 3, 8))) void scan_kernel(ScanArgs a)
 {
     extern __shared__ __align__(16) char smem[];
-    scan_body<STORAGE, MT, WAVES, GATED, false, NT>(a, smem, blockIdx.x, gridDim.x, nullptr, 0u);
+    scan_body<STORAGE, MT, WAVES, MODE, false, NT>(a, smem, blockIdx.x, gridDim.x, nullptr, 0u);
 }
 
 // The threshold sample of a small batch with everything that hangs on it, in one launch.  The first sm.nq
@@ -616,7 +646,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
         PK_MARK(scan, 23);
         return;
     }
-    scan_body<STORAGE, 1, 4, false, true, false>(a, smem, blockIdx.x - nq, gridDim.x - nq, &sm, extra_off);
+    scan_body<STORAGE, 1, 4, kSample, true, false>(a, smem, blockIdx.x - nq, gridDim.x - nq, &sm, extra_off);
 }
 
 // ------------------------------------------------------------------ sliced-query kernel
@@ -626,11 +656,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 // the queries (registers, then LDS) is already on its way.  One barrier per slice keeps the
 // four waves of the workgroup in step.  MT up to 4 (64 slots).  Always 4 waves, one 32-row
 // block each per pass over the page.
-template <int STORAGE, int MT, bool GATED, bool NT>
+template <int STORAGE, int MT, ScanMode MODE, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void scan_ks_kernel(ScanArgs a)
 {
     extern __shared__ __align__(16) char smem[];
     constexpr int MQ = MT * 16;
+    constexpr bool GATED = MODE == kGated;
     constexpr int QLOADS = MQ / 16; // 16-byte pieces of a slice each thread moves: MQ slots x 16 pieces / 256 threads
     char *qbuf = smem;              // [2][MQ][kKsStride]
     Slots s;
@@ -647,7 +678,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
     const int qm = tid >> 4, qpiece = (tid & 15) * 16; // this thread's slot (mod 16) and piece of a slice
 
     Sched sc;
-    sc.start(*a.ntiles, *a.batch, blockIdx.x, gridDim.x);
+    if constexpr (MODE == kLaid) start_laid(a, sc, blockIdx.x, gridDim.x);
+    else sc.start(*a.ntiles, *a.batch, blockIdx.x, gridDim.x);
     if (sc.t >= sc.ntiles) return;
     Tile cur = a.tiles[sc.t];
     while (sc.t < sc.ntiles) {
@@ -661,7 +693,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
             const gfloats txn = in_global(cur.xn);
             const uint32_t row0 = cur.row0;
             const uint32_t qbeg = __builtin_amdgcn_readfirstlane(cur.qbeg);
-            const uint32_t qcnt = __builtin_amdgcn_readfirstlane((uint32_t)cur.qcnt);
+            const uint32_t qcnt = tile_slots<MODE, MQ>(a, cur, qbeg, cur_qbeg, cur_qcnt);
             const int nrows = __builtin_amdgcn_readfirstlane((int)cur.nrows);
             if (qbeg != cur_qbeg || qcnt != cur_qcnt) {
                 __syncthreads();
@@ -763,7 +795,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 #undef PK_QLOAD
 #undef PK_QSTORE
 #undef PK_COMPUTE
-                if (active) finish_block<MT, GATED>(a, s, acc, rb, ln, lg, nrows, qcnt, row0, txn);
+                if (active) finish_block<MT, GATED, false, MODE == kLaid>(a, s, acc, rb, ln, lg, nrows, qcnt, row0, txn);
             }
         }
         sc.t = tn;
@@ -1017,40 +1049,40 @@ int scan_max_mq(int row_bytes, int storage, int lds_limit)
     return best;
 }
 
-template <int STORAGE, int MT, int WAVES, bool GATED, bool NT>
+template <int STORAGE, int MT, int WAVES, ScanMode MODE, bool NT>
 static hipError_t launch_one(const ScanArgs &a, int grid, hipStream_t s)
 {
     static LdsCleared cleared;
-    return launch_with_lds(&scan_kernel<STORAGE, MT, WAVES, GATED, NT>, cleared, scan_lds_bytes(a.row_bytes, a.mq), a, grid,
+    return launch_with_lds(&scan_kernel<STORAGE, MT, WAVES, MODE, NT>, cleared, scan_lds_bytes(a.row_bytes, a.mq), a, grid,
                            WAVES * 64, s);
 }
 
-template <int STORAGE, int MT, bool NT>
+template <int STORAGE, int MT, ScanMode MODE, bool NT>
 static hipError_t launch_ks_one(const ScanArgs &a, int grid, hipStream_t s)
 {
     static LdsCleared cleared;
-    return launch_with_lds(&scan_ks_kernel<STORAGE, MT, true, NT>, cleared, scan_ks_lds_bytes(MT * 16), a, grid, 256, s);
+    return launch_with_lds(&scan_ks_kernel<STORAGE, MT, MODE, NT>, cleared, scan_ks_lds_bytes(MT * 16), a, grid, 256, s);
 }
 
-template <int STORAGE, int WAVES, bool GATED, bool NT>
+template <int STORAGE, int WAVES, ScanMode MODE, bool NT>
 static hipError_t launch_mt(const ScanArgs &a, int grid, hipStream_t s)
 {
-    if (a.mq >= 1 && a.mq < 16) return launch_one<STORAGE, 1, WAVES, GATED, NT>(a, grid, s);
+    if (MODE != kLaid && a.mq >= 1 && a.mq < 16) return launch_one<STORAGE, 1, WAVES, MODE, NT>(a, grid, s);
     switch (a.mq) {
-    case 16: return launch_one<STORAGE, 1, WAVES, GATED, NT>(a, grid, s);
-    case 32: return launch_one<STORAGE, 2, WAVES, GATED, NT>(a, grid, s);
-    case 64: return launch_one<STORAGE, 4, WAVES, GATED, NT>(a, grid, s);
+    case 16: return launch_one<STORAGE, 1, WAVES, MODE, NT>(a, grid, s);
+    case 32: return launch_one<STORAGE, 2, WAVES, MODE, NT>(a, grid, s);
+    case 64: return launch_one<STORAGE, 4, WAVES, MODE, NT>(a, grid, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-template <int STORAGE, bool NT>
+template <int STORAGE, ScanMode MODE, bool NT>
 static hipError_t launch_ks_mt(const ScanArgs &a, int grid, hipStream_t s)
 {
     switch (a.mq) {
-    case 16: return launch_ks_one<STORAGE, 1, NT>(a, grid, s);
-    case 32: return launch_ks_one<STORAGE, 2, NT>(a, grid, s);
-    case 64: return launch_ks_one<STORAGE, 4, false>(a, grid, s);
+    case 16: return launch_ks_one<STORAGE, 1, MODE, NT>(a, grid, s);
+    case 32: return launch_ks_one<STORAGE, 2, MODE, NT>(a, grid, s);
+    case 64: return launch_ks_one<STORAGE, 4, MODE, false>(a, grid, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1092,23 +1124,33 @@ hipError_t launch_sample_tau(const ScanArgs &a, const SampleArgs &sm, const Work
     return hipGetLastError();
 }
 
-// whole-group kernel: gated (fine search) when a.tau is set, else every value is written (threshold sampling)
+// whole-group kernel: fine search (over wl_lay_query's tiles when a.lcnt is set, gated when a.tau is), else the threshold sample
+template <int STORAGE>
+static hipError_t launch_scan_of(const ScanArgs &a, int grid, hipStream_t s)
+{
+    if (a.lcnt) return a.nt ? launch_mt<STORAGE, 4, kLaid, true>(a, grid, s) : launch_mt<STORAGE, 4, kLaid, false>(a, grid, s);
+    if (a.tau == nullptr) return launch_mt<STORAGE, 4, kSample, false>(a, grid, s);
+    return a.nt ? launch_mt<STORAGE, 4, kGated, true>(a, grid, s) : launch_mt<STORAGE, 4, kGated, false>(a, grid, s);
+}
 hipError_t launch_scan(const ScanArgs &a, int grid, hipStream_t s)
 {
     if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0) return hipErrorInvalidValue;
-    const bool f16 = a.storage == PK_F16;
-    if (a.tau == nullptr) return f16 ? launch_mt<PK_F16, 4, false, false>(a, grid, s) : launch_mt<PK_F32, 4, false, false>(a, grid, s);
-    if (a.nt) return f16 ? launch_mt<PK_F16, 4, true, true>(a, grid, s) : launch_mt<PK_F32, 4, true, true>(a, grid, s);
-    return f16 ? launch_mt<PK_F16, 4, true, false>(a, grid, s) : launch_mt<PK_F32, 4, true, false>(a, grid, s);
+    return a.storage == PK_F16 ? launch_scan_of<PK_F16>(a, grid, s) : launch_scan_of<PK_F32>(a, grid, s);
 }
 
-// the sliced-query kernel (gated fine search only; fp32 rows are held to 32 slots)
+// the sliced-query kernel (fine search only; fp32 rows are held to 32 slots)
+template <int STORAGE>
+static hipError_t launch_scan_ks_of(const ScanArgs &a, int grid, hipStream_t s)
+{
+    if (a.lcnt) return a.nt ? launch_ks_mt<STORAGE, kLaid, true>(a, grid, s) : launch_ks_mt<STORAGE, kLaid, false>(a, grid, s);
+    return a.nt ? launch_ks_mt<STORAGE, kGated, true>(a, grid, s) : launch_ks_mt<STORAGE, kGated, false>(a, grid, s);
+}
 hipError_t launch_scan_ks(const ScanArgs &a, int grid, hipStream_t s)
 {
-    if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || a.tau == nullptr) return hipErrorInvalidValue;
-    if (a.storage == PK_F16) return a.nt ? launch_ks_mt<PK_F16, true>(a, grid, s) : launch_ks_mt<PK_F16, false>(a, grid, s);
+    if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || (a.tau == nullptr && a.lcnt == nullptr)) return hipErrorInvalidValue;
+    if (a.storage == PK_F16) return launch_scan_ks_of<PK_F16>(a, grid, s);
     if (a.mq > 32) return hipErrorInvalidValue;
-    return a.nt ? launch_ks_mt<PK_F32, true>(a, grid, s) : launch_ks_mt<PK_F32, false>(a, grid, s);
+    return launch_scan_ks_of<PK_F32>(a, grid, s);
 }
 
 } // namespace pk

@@ -186,9 +186,10 @@ __global__ __launch_bounds__(kSelThreads) void select_probes_kernel(const u64 *p
 // radix passes over a 256-bin LDS histogram), then the keys below it and as many of the keys
 // equal to it as are needed, lowest positions first, are collected and sorted.  Positions
 // are list numbers, so ties go to the lower list number.
-// COUNT: the workgroup goes on to do its query's share of the work-list construction (pairs per list,
-// candidate layout, sample tiles), which saves the launch that would otherwise follow the selection.
-template <int VPT, bool COUNT>
+// GO_ON: the workgroup goes on to do its query's share of the work-list construction (kCount: pairs per list,
+// candidate layout, sample tiles; kLay: all of it), which saves the launch that would otherwise follow the selection.
+enum GoOn { kStop, kCount, kLay };
+template <int VPT, GoOn GO_ON>
 __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, const uint32_t *qoff, const uint32_t *qcnt,
                                                            int metric, int K, int32_t *probes, WorklistArgs wa,
                                                            SampleArgs sm, MultiArgs ma)
@@ -197,8 +198,9 @@ __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, co
     __shared__ uint32_t s_w[4];
     __shared__ uint32_t s_n;
     __shared__ __align__(16) u64 sel[PK_MAX_NPROBE + 2];
+    constexpr bool COUNT = GO_ON != kStop;
     __shared__ int32_t s_probe[COUNT ? PK_MAX_NPROBE : 1];
-    __shared__ std::conditional_t<COUNT, WlCountLds, uint32_t> s_wl;
+    __shared__ std::conditional_t<GO_ON == kCount, WlCountLds, std::conditional_t<GO_ON == kLay, WlLayLds, uint32_t>> s_wl;
     PK_MARK(sel, 0);
     const uint32_t q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t n = qcnt[q];
@@ -216,6 +218,44 @@ __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, co
 #pragma unroll
     for (int j = 0; j < VPT; ++j) live[j] = tid + 256u * j < n;
     PK_MARK(sel, 1);
+    // few probes of many lists: the scores within a bound on the K-th best, put in order by counting
+    bool done = false;
+    if (K <= (int)kMostParts) {
+        uint32_t bound = 0xffffffffu;
+        if (n > 256u) {
+            uint32_t least = key[0];
+#pragma unroll
+            for (int j = 1; j < VPT; ++j) least = min(least, key[j]);
+            bound = bound_of_parts(least, (uint32_t)K, hist[0]);
+        } else {
+            __syncthreads(); // (s_n)
+        }
+#pragma unroll
+        for (int j = 0; j < VPT; ++j)
+            if (live[j] && key[j] <= bound) {
+                const uint32_t at = atomicAdd(&s_n, 1u);
+                if (at < 256u) sel[at] = ((u64)key[j] << 32) | (tid + 256u * j);
+            }
+        __syncthreads();
+        const uint32_t within = s_n;
+        if (within <= 256u) { // (the same for the whole workgroup)
+            if (tid < 2) sel[within + tid] = kMaxKey; // padding: the keys are read in pairs
+            __syncthreads();
+            if (tid < within) {
+                const u64 mine = sel[tid];
+                const uint32_t rank = rank_among(sel, within, mine);
+                if (rank < (uint32_t)K) {
+                    if constexpr (COUNT) s_probe[rank] = (int32_t)(uint32_t)mine; // the count stores the list, after its loads
+                    else probes[(size_t)q * K + rank] = (int32_t)(uint32_t)mine;
+                }
+            }
+            done = true;
+        } else { // equal scores are the rule
+            __syncthreads();
+            if (tid == 0) s_n = 0;
+        }
+    }
+    if (!done) {
     uint32_t krem, ties;
     const uint32_t prefix = radix_kth<VPT>(key, live, (uint32_t)K, hist, krem, ties);
     PK_MARK(sel, 2);
@@ -249,11 +289,7 @@ __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, co
         // rank of each selected key among the K of them (keys are unique): its place in the probe list
         if (tid < (uint32_t)K) {
             const u64 mine = sel[tid];
-            uint32_t rank = 0;
-            for (int o = 0; o < K; o += 2) {
-                const u64x2 w = *reinterpret_cast<const u64x2 *>(sel + o);
-                rank += (w[0] < mine ? 1u : 0u) + (w[1] < mine ? 1u : 0u);
-            }
+            const uint32_t rank = rank_among(sel, (uint32_t)K, mine);
             if constexpr (COUNT) s_probe[rank] = (int32_t)(uint32_t)mine; // the count stores the list, after its loads
             else probes[(size_t)q * K + rank] = (int32_t)(uint32_t)mine;
         }
@@ -267,10 +303,12 @@ __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, co
             else probes[(size_t)q * K + r] = (int32_t)(uint32_t)sel[r];
         }
     }
+    } // !done
     PK_MARK(sel, 4);
     if constexpr (COUNT) {
         __syncthreads(); // the probe list is in s_probe
-        wl_count_query(wa, sm, ma, q, s_wl, s_probe, probes + (size_t)q * K, view);
+        if constexpr (GO_ON == kCount) wl_count_query(wa, sm, ma, q, s_wl, s_probe, probes + (size_t)q * K, view);
+        if constexpr (GO_ON == kLay) wl_lay_query(wa, ma, q, s_wl, s_probe, probes + (size_t)q * K, view);
         PK_MARK(sel, 7);
     }
 }
@@ -282,31 +320,28 @@ hipError_t launch_select_dense(const float *vals, const uint32_t *qoff, const ui
     if (nq <= 0) return hipSuccess;
     if (max_cnt > (uint32_t)kDenseSelectMax || K > PK_MAX_NPROBE) return hipErrorInvalidValue;
     const dim3 g((uint32_t)nq), b(256);
-    if (wa) {
-        if (!sm || !ma || wa->nprobe != K) return hipErrorInvalidValue;
-        if (max_cnt <= 1024)
-            hipLaunchKernelGGL((select_dense_kernel<4, true>), g, b, 0, s, vals, qoff, qcnt, metric, K, probes, *wa, *sm, *ma);
-        else if (max_cnt <= 4096)
-            hipLaunchKernelGGL((select_dense_kernel<16, true>), g, b, 0, s, vals, qoff, qcnt, metric, K, probes, *wa, *sm, *ma);
-        else
-            hipLaunchKernelGGL((select_dense_kernel<32, true>), g, b, 0, s, vals, qoff, qcnt, metric, K, probes, *wa, *sm, *ma);
-        return hipGetLastError();
-    }
-    const WorklistArgs w0{};
-    const SampleArgs s0{};
+    if (wa && (!sm || !ma || wa->nprobe != K)) return hipErrorInvalidValue;
+    WorklistArgs w0{};
+    SampleArgs s0{};
     MultiArgs m0;
     m0.n = 0;
-    if (max_cnt <= 1024)
-        hipLaunchKernelGGL((select_dense_kernel<4, false>), g, b, 0, s, vals, qoff, qcnt, metric, K, probes, w0, s0, m0);
-    else if (max_cnt <= 4096)
-        hipLaunchKernelGGL((select_dense_kernel<16, false>), g, b, 0, s, vals, qoff, qcnt, metric, K, probes, w0, s0, m0);
-    else
-        hipLaunchKernelGGL((select_dense_kernel<32, false>), g, b, 0, s, vals, qoff, qcnt, metric, K, probes, w0, s0, m0);
+    auto go = [&](auto vpt) {
+        constexpr int VPT = decltype(vpt)::value;
+        auto run = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, g, b, 0, s, vals, qoff, qcnt, metric, K, probes, wa ? *wa : w0, wa ? *sm : s0, wa ? *ma : m0);
+        };
+        if (!wa) run(select_dense_kernel<VPT, kStop>);
+        else if (wa->width == 0) run(select_dense_kernel<VPT, kCount>);
+        else run(select_dense_kernel<VPT, kLay>);
+    };
+    if (max_cnt <= 1024) go(std::integral_constant<int, 4>{});
+    else if (max_cnt <= 4096) go(std::integral_constant<int, 16>{});
+    else go(std::integral_constant<int, 32>{});
     return hipGetLastError();
 }
 
 // position inside the query's candidate range -> id stored in the list page
-__device__ int64_t resolve_id(const FinalArgs &a, const MultiArgs &h, uint32_t q, uint32_t pos)
+__device__ __forceinline__ int64_t resolve_id(const FinalArgs &a, const MultiArgs &h, uint32_t q, uint32_t pos)
 {
     const uint32_t *po = a.pair_off + (size_t)q * (a.nprobe + 1);
     int lo = 0, hi = a.nprobe - 1;
@@ -325,8 +360,9 @@ __device__ int64_t resolve_id(const FinalArgs &a, const MultiArgs &h, uint32_t q
 }
 
 
-// the same with the query's rows of pair_off and probes in LDS
-__device__ int64_t resolve_id_lds(const FinalArgs &a, const DevIndex &ix, uint32_t pos, const uint32_t *po, const uint32_t *pr)
+// the same with the query's rows of pair_off and probes in LDS, and the build-time extents of the probed lists
+__device__ __forceinline__ int64_t resolve_id_lds(const FinalArgs &a, const DevIndex &ix, uint32_t pos, const uint32_t *po, const uint32_t *pr,
+                                  const uint32_t *mp, const uint32_t *mb)
 {
     int lo = 0, hi = a.nprobe - 1;
     while (lo < hi) { // largest r with po[r] <= pos
@@ -335,9 +371,8 @@ __device__ int64_t resolve_id_lds(const FinalArgs &a, const DevIndex &ix, uint32
         else hi = mid - 1;
     }
     const uint32_t row = pos - po[lo];
-    const uint32_t list = pr[lo];
     const uint32_t lp = row / (uint32_t)ix.P;
-    const uint32_t pg = phys_page(ix, list, lp);
+    const uint32_t pg = lp < mp[lo] ? mb[lo] + lp : ix.dtab[(size_t)pr[lo] * ix.max_dp + (lp - mp[lo])];
     const Arena &ar = arena_of(ix, pg);
     return ar.ids[(size_t)(pg - ar.first_page) * ix.P + (row - lp * ix.P)];
 }
@@ -563,13 +598,12 @@ __global__ __launch_bounds__(kSelThreads) void rescue_kernel(FinalArgs a, MultiA
     }
 }
 
-// Best K of the cnt_q <= 256 * VPT keys of a query's region, held in registers: the K-th smallest value by
+// Best K of cnt_q <= 256 * VPT keys, held in registers: the K-th smallest value by
 // radix selection; among the keys with that value, if not all of them are needed, the lowest positions by a
 // second selection over the low words.  The kept keys end up sorted in keys[0, min(K, cnt_q)); *s_cnt is
-// their number.  early: key number threadIdx.x of the region, already loaded.  hist: LDS [4][256].
-template <int VPT>
-__device__ __forceinline__ void final_by_radix(const u64 *v, uint32_t cnt_q, uint32_t K, u64 early, uint32_t (*hist)[256],
-                                               u64 *keys, uint32_t *s_cnt)
+// their number.  get(j, p): key number p, the thread's j-th.  hist: LDS [4][256].
+template <int VPT, typename G>
+__device__ __forceinline__ void final_by_radix(G get, uint32_t cnt_q, uint32_t K, uint32_t (*hist)[256], u64 *keys, uint32_t *s_cnt)
 {
     const uint32_t tid = threadIdx.x;
     u64 k64[VPT];
@@ -579,7 +613,7 @@ __device__ __forceinline__ void final_by_radix(const u64 *v, uint32_t cnt_q, uin
     for (int j = 0; j < VPT; ++j) {
         const uint32_t p = tid + (uint32_t)kSelThreads * j;
         live[j] = p < cnt_q;
-        k64[j] = live[j] ? (j == 0 ? early : v[p]) : kMaxKey;
+        k64[j] = live[j] ? get(j, p) : kMaxKey;
         hi[j] = (uint32_t)(k64[j] >> 32);
     }
     if (tid == 0) *s_cnt = 0;
@@ -612,12 +646,7 @@ __device__ __forceinline__ void final_by_radix(const u64 *v, uint32_t cnt_q, uin
         if (tid < 2) keys[n + tid] = kMaxKey; // padding: the keys are read in pairs
         __syncthreads();
         const u64 mine = tid < n ? keys[tid] : kMaxKey;
-        uint32_t rank = 0;
-        if (tid < n)
-            for (uint32_t o = 0; o < n; o += 2) {
-                const u64x2 w = *reinterpret_cast<const u64x2 *>(keys + o);
-                rank += (w[0] < mine ? 1u : 0u) + (w[1] < mine ? 1u : 0u);
-            }
+        const uint32_t rank = tid < n ? rank_among(keys, n, mine) : 0u;
         __syncthreads();
         if (tid < n) keys[rank] = mine;
         __syncthreads();
@@ -629,6 +658,99 @@ __device__ __forceinline__ void final_by_radix(const u64 *v, uint32_t cnt_q, uin
     }
 }
 
+// The same of all cnt_q values of a query's range (DENSE calls).  A bound on the K-th best by parts (bound_of_parts; for K
+// of some hundred, the K-th best of 1024 parts), and the few values within it, collected in surv and put in order by counting;
+// ranges of up to 8192 values are read once.  False: more than fit are within the bound, or K is too large; nothing is
+// selected.
+constexpr uint32_t kSurvivors = 2048;
+__device__ __forceinline__ bool final_of_values(const float *vals, uint32_t cnt_q, uint32_t K, int metric, uint32_t (*hist)[256],
+                                                u64 *keys, u64 *surv, uint32_t *s_cnt)
+{
+    const uint32_t tid = threadIdx.x;
+    if (K > (uint32_t)kSelThreads) { // (the first 1024 values alone give 256 parts)
+        if (cnt_q > 16u * kSelThreads) return false;
+        final_by_radix<16>([=](int, uint32_t p) { return ((u64)order_bits(vals[p], metric) << 32) | p; }, cnt_q, K, hist, keys, s_cnt);
+        return true;
+    }
+    constexpr int U = 8; // loads in flight
+    constexpr uint32_t kRound = U * 4u * kSelThreads;
+    f32x4 v[U];
+    auto load = [&](uint32_t p0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t p = p0 + u * 4u * kSelThreads;
+            v[u] = *reinterpret_cast<const f32x4 *>(vals + (p < cnt_q ? p : 0u)); // (ranges are padded to 16 values)
+        }
+    };
+    uint32_t mn[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+    for (uint32_t r = 0; r < cnt_q; r += kRound) {
+        load(r + 4u * tid);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (r + 4u * tid + u * 4u * kSelThreads < cnt_q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mn[u & 3] = min(mn[u & 3], min(order_bits(v[u][e], metric), 0xfffffffeu));
+    }
+    PK_MARK(sel, 41);
+    uint32_t bound;
+    if (K <= kMostParts) {
+        bound = bound_of_parts(min(min(mn[0], mn[1]), min(mn[2], mn[3])), K, hist[0]);
+    } else if (cnt_q > K) {
+        bool live[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) live[j] = mn[j] != 0xffffffffu;
+        uint32_t left, ties;
+        // (fewer values than 1024 leave parts without one: as many as K have one only if a thread's first part always does)
+        bound = cnt_q >= 4u * kSelThreads ? radix_kth<4>(mn, live, K, hist, left, ties) : 0xffffffffu;
+    } else {
+        bound = 0xffffffffu;
+    }
+    PK_MARK(sel, 42);
+    auto collect = [&](uint32_t p0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t p = p0 + u * 4u * kSelThreads, key = order_bits(v[u][e], metric);
+                if (p < cnt_q && key <= bound && key < kWorstBits) { // (padding is no candidate)
+                    const uint32_t at = atomicAdd(s_cnt, 1u);
+                    if (at < kSurvivors) surv[at] = ((u64)key << 32) | (p + e);
+                }
+            }
+    };
+    if (cnt_q <= kRound) {
+        collect(4u * tid); // still in registers
+    } else {
+        for (uint32_t r = 0; r < cnt_q; r += kRound) {
+            load(r + 4u * tid);
+            collect(r + 4u * tid);
+        }
+    }
+    __syncthreads();
+    const uint32_t n = *s_cnt;
+    PK_MARK(sel, 43);
+    if (n > kSurvivors) {
+        __syncthreads(); // (the caller counts in the same word)
+        return false;
+    }
+    if (n <= (uint32_t)kSelThreads) {
+        if (tid < 2) surv[n + tid] = kMaxKey; // padding: the keys are read in pairs
+        __syncthreads();
+        if (tid < n) {
+            const u64 mine = surv[tid];
+            const uint32_t rank = rank_among(surv, n, mine);
+            if (rank < K) keys[rank] = mine;
+        }
+        if (tid == 0) *s_cnt = n < K ? n : K;
+        __syncthreads();
+    } else {
+        __syncthreads(); // (the selection counts in the same word)
+        final_by_radix<kSurvivors / kSelThreads>([=](int, uint32_t p) { return surv[p]; }, n, K, hist, keys, s_cnt);
+    }
+    return true;
+}
+
+template <bool DENSE>
 __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, MultiArgs h, uint32_t cap, uint32_t qbytes)
 {
     // LDS sized by K, not by the largest K the library takes: small k leaves room for every
@@ -638,8 +760,10 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     int64_t *s_id = reinterpret_cast<int64_t *>(keys + cap);     // [k]
     // [2][row_bytes + kQPadBytes] when rescoring; the histograms of the radix selection otherwise
     char *s_q = reinterpret_cast<char *>(s_id + ((a.k + 1) & ~1));
+    [[maybe_unused]] u64 *const s_surv = reinterpret_cast<u64 *>(s_q + qbytes) - (DENSE ? kSurvivors : 0u); // DENSE: the last part of qbytes
     uint32_t *s_po = reinterpret_cast<uint32_t *>(s_q + qbytes); // [nprobe + 1] the query's row of pair_off
-    uint32_t *s_pr = s_po + a.nprobe + 1;                        // [nprobe] its probe list
+    uint32_t *s_pr = s_po + a.nprobe + 1;                        // [nprobe] its probe list,
+    uint32_t *s_mp = s_pr + a.nprobe, *s_mb = s_mp + a.nprobe;   // [nprobe] pages and first page of the lists' build-time extents
     __shared__ uint32_t s_cnt;
     __shared__ long long s_red[kSelThreads / 64];
     __shared__ uint32_t s_redpos[kSelThreads / 64];
@@ -649,17 +773,23 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     const int k = a.k;
     const int qstride = a.row_bytes + kQPadBytes;
     PK_MARK(sel, 32);
-    const size_t region = (size_t)q * a.ecap;
+    const size_t region = DENSE ? 0 : (size_t)q * a.ecap;
     // everything the usual path reads from global memory is requested at once: the count, the thread's key
     // of a short region (the entry exists whatever the count; it is used only if it is below it), the
     // query's rows of the candidate layout, its index
-    uint32_t cnt_q = a.qcnt[q];
-    u64 early = threadIdx.x < a.ecap ? a.keys[region + threadIdx.x] : kMaxKey;
+    uint32_t cnt_q = DENSE ? a.pair_off[(size_t)q * (a.nprobe + 1) + a.nprobe] : a.qcnt[q];
+    u64 early = !DENSE && threadIdx.x < a.ecap ? a.keys[region + threadIdx.x] : kMaxKey;
+    const DevIndex &qix = *h.ix[a.qagent[q]];
     for (int r = threadIdx.x; r <= a.nprobe; r += blockDim.x) {
         s_po[r] = a.pair_off[(size_t)q * (a.nprobe + 1) + r];
-        if (r < a.nprobe) s_pr[r] = (uint32_t)a.probes[(size_t)q * a.nprobe + r];
+        if (r < a.nprobe) {
+            const uint32_t l = (uint32_t)a.probes[(size_t)q * a.nprobe + r];
+            const bool valid = l < (uint32_t)qix.nlist;
+            s_pr[r] = l;
+            s_mp[r] = valid ? qix.main_pages[l] : 0u;
+            s_mb[r] = valid ? qix.main_base[l] : 0u;
+        }
     }
-    const DevIndex &qix = *h.ix[a.qagent[q]];
     // Running sums of the call (candidates met, candidates emitted, most emitted by one query, queries whose
     // region overflowed): workgroup 0 adds up every query's numbers, so that they cost four atomics per call
     // and not several per query on the same words.
@@ -667,18 +797,18 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     uint32_t st_max = 0, st_over = 0;
     if (blockIdx.x == 0) {
         for (uint32_t t = threadIdx.x; t < gridDim.x; t += blockDim.x) {
-            const uint32_t c = a.qcnt[t];
-            st_cand += a.pair_off[(size_t)t * (a.nprobe + 1) + a.nprobe];
+            const uint32_t all = a.pair_off[(size_t)t * (a.nprobe + 1) + a.nprobe], c = DENSE ? all : a.qcnt[t];
+            st_cand += all;
             st_emit += c;
             st_max = c > st_max ? c : st_max;
-            st_over += c > a.ecap ? 1u : 0u;
+            st_over += !DENSE && c > a.ecap ? 1u : 0u;
         }
     }
     Selector sel;
     sel.init(keys, &s_cnt, a.K, cap);
-    bool overflow = cnt_q > a.ecap; // the region lost candidates: select by rescoring the query's rows
-    const u64 *v = a.keys + region; // where the query's candidates are
-    if (overflow && a.rregions > 0) {
+    bool overflow = !DENSE && cnt_q > a.ecap; // the region lost candidates: select by rescoring the query's rows
+    const u64 *v = a.keys + region;           // where the query's candidates are
+    if (!DENSE && overflow && a.rregions > 0) {
         // ... unless they were scored again already: the query's region is its number among the overflowed queries
         uint32_t before = 0;
         for (uint32_t t = threadIdx.x; t < q; t += blockDim.x) before += a.qcnt[t] > a.ecap ? 1u : 0u;
@@ -694,12 +824,28 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
             early = threadIdx.x < got ? v[threadIdx.x] : kMaxKey;
         }
     }
-    const bool in_registers = cnt_q <= 16u * kSelThreads && !overflow;
-    if (in_registers) {
-        uint32_t(*hist)[256] = reinterpret_cast<uint32_t(*)[256]>(s_q);
-        if (cnt_q <= (uint32_t)kSelThreads) final_by_radix<1>(v, cnt_q, (uint32_t)a.K, early, hist, keys, &s_cnt);
-        else if (cnt_q <= 4u * kSelThreads) final_by_radix<4>(v, cnt_q, (uint32_t)a.K, early, hist, keys, &s_cnt);
-        else final_by_radix<16>(v, cnt_q, (uint32_t)a.K, early, hist, keys, &s_cnt);
+    bool in_registers = cnt_q <= 16u * kSelThreads && !overflow;
+    uint32_t(*hist)[256] = reinterpret_cast<uint32_t(*)[256]>(s_q);
+    [[maybe_unused]] const float *const values = DENSE ? a.vals + (size_t)q * a.width : nullptr;
+    if constexpr (DENSE) in_registers = final_of_values(values, cnt_q, (uint32_t)a.K, a.metric, hist, keys, s_surv, &s_cnt);
+    if (DENSE && !in_registers) {
+        // equal values are the rule: all of them through the streaming selector
+        if (threadIdx.x == 0) s_cnt = 0;
+        __syncthreads();
+        for (uint32_t lo = 0; lo < cnt_q; lo += kSelThreads) {
+            sel.reserve(kSelThreads);
+            const uint32_t p = lo + threadIdx.x;
+            if (p < cnt_q) {
+                const uint32_t bits = order_bits(values[p], a.metric);
+                if (bits < kWorstBits) sel.push(((u64)bits << 32) | p);
+            }
+        }
+    } else if (DENSE) {
+    } else if (in_registers) {
+        auto get = [=](int j, uint32_t p) { return j == 0 ? early : v[p]; };
+        if (cnt_q <= (uint32_t)kSelThreads) final_by_radix<1>(get, cnt_q, (uint32_t)a.K, hist, keys, &s_cnt);
+        else if (cnt_q <= 4u * kSelThreads) final_by_radix<4>(get, cnt_q, (uint32_t)a.K, hist, keys, &s_cnt);
+        else final_by_radix<16>(get, cnt_q, (uint32_t)a.K, hist, keys, &s_cnt);
     } else if (!overflow) {
         // short ranges go one key per thread and round, so the buffer that gets sorted stays small
         const uint32_t per = cnt_q <= 8192u ? 1u : (uint32_t)kSelVec;
@@ -732,12 +878,10 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     // entries carrying the padding value are not candidates
     const uint32_t worst = kWorstBits;
     uint32_t n_valid = 0;
-    for (uint32_t i = 0; i < n; ++i) { // n <= K, uniform loop
-        if ((uint32_t)(keys[i] >> 32) >= worst) break;
-        ++n_valid;
-    }
+    for (uint32_t i = 0; i < n; i += kSelThreads) // (sorted: they come last)
+        n_valid += (uint32_t)__syncthreads_count(i + threadIdx.x < n && (uint32_t)(keys[i + threadIdx.x] >> 32) < worst);
     const uint32_t kk = n_valid < (uint32_t)k ? n_valid : (uint32_t)k;
-    for (uint32_t i = threadIdx.x; i < kk; i += blockDim.x) s_id[i] = resolve_id_lds(a, qix, (uint32_t)keys[i], s_po, s_pr);
+    for (uint32_t i = threadIdx.x; i < kk; i += blockDim.x) s_id[i] = resolve_id_lds(a, qix, (uint32_t)keys[i], s_po, s_pr, s_mp, s_mb);
     __syncthreads();
     PK_MARK(sel, 34);
 
@@ -767,7 +911,11 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
             __syncthreads();
         } else {
         const uint32_t total = cnt_q;
-        const u64 *rk = v;
+        const int metric = a.metric;
+        auto key_at = [=](uint32_t p) { // (nothing by reference: the kernel's arguments would be copied to memory)
+            if constexpr (DENSE) return ((u64)order_bits(values[p], metric) << 32) | p;
+            else return v[p];
+        };
         // Members are taken in (id, position) order: several rows may carry one id, and each
         // of them is a candidate of its own.
         long long last_id = 0;
@@ -777,7 +925,7 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
             long long best = INT64_MAX;
             uint32_t best_pos = 0xffffffffu;
             for (uint32_t p = threadIdx.x; p < total; p += blockDim.x) {
-                const u64 key = rk[p];
+                const u64 key = key_at(p);
                 if ((uint32_t)(key >> 32) == tau) {
                     const uint32_t pos = (uint32_t)key;
                     const long long id = resolve_id(a, h, q, pos);
@@ -830,11 +978,10 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
         if (i < kk) {
             const uint32_t ki = (uint32_t)(keys[i] >> 32);
             const int64_t idi = s_id[i];
-            uint32_t rank = 0;
-            for (uint32_t j = 0; j < kk; ++j) {
-                const uint32_t kj = (uint32_t)(keys[j] >> 32);
-                rank += (kj < ki || (kj == ki && (s_id[j] < idi || (s_id[j] == idi && j < i)))) ? 1u : 0u;
-            }
+            // keys[] is sorted by (value key, position): only neighbours of the same value can change places
+            uint32_t rank = i;
+            for (uint32_t j = i; j > 0 && (uint32_t)(keys[j - 1] >> 32) == ki; --j) rank -= s_id[j - 1] > idi ? 1u : 0u;
+            for (uint32_t j = i + 1; j < kk && (uint32_t)(keys[j] >> 32) == ki; ++j) rank += s_id[j] < idi ? 1u : 0u;
             a.out_ids[(size_t)q * k + rank] = idi;
             a.out_dist[(size_t)q * k + rank] = value_of(ki, a.metric);
         } else {
@@ -988,14 +1135,24 @@ hipError_t launch_rescue(const FinalArgs &a, const MultiArgs &m, int64_t nq, int
 hipError_t launch_select_final(const FinalArgs &a, const MultiArgs &h, int64_t nq, hipStream_t s)
 {
     if (nq <= 0) return hipSuccess;
-    if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || a.ecap < (uint32_t)a.K) return hipErrorInvalidValue;
+    const bool dense = a.vals != nullptr;
+    if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || (!dense && a.ecap < (uint32_t)a.K)) return hipErrorInvalidValue;
+    if (dense && (a.width % 16 != 0 || (reinterpret_cast<uintptr_t>(a.vals) & 15) != 0)) return hipErrorInvalidValue;
     const uint32_t cap = final_cap(a.K);
-    // keys, ids, and the query row + a row of zeros for a query that has to be rescored
-    const size_t qbytes = std::max((size_t)2 * (a.row_bytes + kQPadBytes), (size_t)4 * 256 * sizeof(uint32_t));
+    // keys, ids, and the query row + a row of zeros for a query that has to be rescored; or the histograms (and what is
+    // collected from a range of values)
+    const size_t hists = (size_t)4 * 256 * sizeof(uint32_t);
+    const size_t qbytes = dense ? hists + kSurvivors * sizeof(u64) : std::max((size_t)2 * (a.row_bytes + kQPadBytes), hists);
     // ..., and the query's rows of the candidate layout
     const size_t lds = (size_t)cap * sizeof(u64) + (size_t)((a.k + 1) & ~1) * sizeof(int64_t) + qbytes +
-                       (size_t)(2 * a.nprobe + 1) * sizeof(uint32_t);
-    hipLaunchKernelGGL(select_final_kernel, dim3((uint32_t)nq), dim3(kSelThreads), lds, s, a, h, cap, (uint32_t)qbytes);
+                       (size_t)(4 * a.nprobe + 1) * sizeof(uint32_t);
+    static LdsCleared cleared[2]; // (k and nprobe of some hundreds take more than 64 KB)
+    const auto kernel = dense ? select_final_kernel<true> : select_final_kernel<false>;
+    if (lds > 48 * 1024) {
+        const hipError_t e = allow_lds(kernel, cleared[dense], 1024);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)nq), dim3(kSelThreads), lds, s, a, h, cap, (uint32_t)qbytes);
     return hipGetLastError();
 }
 

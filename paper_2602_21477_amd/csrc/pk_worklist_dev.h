@@ -45,6 +45,7 @@ struct WlCountLds {
     uint16_t sr[kMaxSamplePages];    // the sample's pages: which probed list,
     uint32_t slp[kMaxSamplePages];   //   and which of its pages
     uint32_t ns;                     // how many there are
+    uint32_t wave[17];
 };
 __device__ __forceinline__ void wl_count_query(const WorklistArgs &a, const SampleArgs &sm, const MultiArgs &m, uint32_t q,
                                                WlCountLds &s, const int32_t *probes_q, int32_t *probes_out,
@@ -58,16 +59,13 @@ __device__ __forceinline__ void wl_count_query(const WorklistArgs &a, const Samp
         s.len[r] = valid ? v.list_len[l] : 0u;
         s.mp[r] = valid ? v.main_pages[l] : 0u;
         s.mb[r] = valid ? v.main_base[l] : 0u;
+        s.po[r] = (s.len[r] + 15u) & ~15u; // segments are padded to the 16-row MFMA tile
     }
     __syncthreads();
     PK_WL_MARK(5);
+    const uint32_t total = block_exscan(s.po, s.po, (uint32_t)a.nprobe, s.wave);
     if (threadIdx.x == 0) {
-        uint32_t acc = 0;
-        for (int r = 0; r < a.nprobe; ++r) {
-            s.po[r] = acc;
-            acc += (s.len[r] + 15u) & ~15u; // segments are padded to the 16-row MFMA tile
-        }
-        s.po[a.nprobe] = acc;
+        s.po[a.nprobe] = total;
         // The sample's pages: full pages first, nearest lists first, then the lists' last, partly filled
         // pages: short lists at the head of the probe list cannot leave the sample with fewer than k
         // rows (and the query without a threshold) while longer lists follow.
@@ -95,7 +93,7 @@ __device__ __forceinline__ void wl_count_query(const WorklistArgs &a, const Samp
         tl.qbeg = q;
         tl.nrows = 0;
         tl.qcnt = 1;
-        tl.pad = 0;
+        tl.list = 0;
         if (p < s.ns) {
             const int r = s.sr[p];
             const uint32_t l = (uint32_t)probes_q[r];
@@ -135,6 +133,127 @@ __device__ __forceinline__ void wl_count_query(const WorklistArgs &a, const Samp
             const uint32_t g = ntiles / (uint32_t)(sm.scan_grid * 4);
             sm.scalars[2] = g < 1 ? 1 : (g > 8 ? 8 : g);
         }
+    }
+}
+
+// The whole work list, by the workgroups of the coarse selection (one of 256 threads per query; same arguments as above)
+// and without a word between them.  A pair's slot is the next one of its list, which has room for a.cap; the pair that
+// opens a group of a.mq slots also writes the group's tiles, one per page, in a range taken from the tile counter: how
+// many slots the group will have is read from the pair counters by the scan.  Needs no prefix sums over the lists and no
+// sample: for calls whose values are written whole (a.width per query).
+struct WlLayLds {
+    uint32_t len[PK_MAX_NPROBE];     // rows of each probed list
+    uint32_t mp[PK_MAX_NPROBE];      // pages of its build-time extent
+    uint32_t mb[PK_MAX_NPROBE];      // first page of that extent
+    uint32_t slot[PK_MAX_NPROBE];    // the pair's slot
+    uint32_t po[PK_MAX_NPROBE];      // candidates of the probed lists before each one
+    uint32_t to[PK_MAX_NPROBE];      // tiles of the groups opened before each one
+    uint32_t wave[17];
+    uint32_t first;                  // where the query's tiles start
+};
+__device__ __forceinline__ void wl_lay_query(const WorklistArgs &a, const MultiArgs &m, uint32_t q, WlLayLds &s,
+                                             const int32_t *probes_q, int32_t *probes_out, const WlIndexView &v)
+{
+    const DevIndex &ix = *v.ix;
+    const uint32_t P = v.P, np = (uint32_t)a.nprobe, tid = threadIdx.x, mq = (uint32_t)a.mq;
+    unsigned long long rows = 0; // of the lists that this query is the first to probe
+    for (uint32_t r = tid; r < np; r += blockDim.x) {
+        const uint32_t l = (uint32_t)probes_q[r];
+        const bool valid = l < v.nlist;
+        const uint32_t len = valid ? v.list_len[l] : 0u;
+        s.mp[r] = valid ? v.main_pages[l] : 0u;
+        s.mb[r] = valid ? v.main_base[l] : 0u;
+        const uint32_t slot = valid ? atomicAdd(&a.lcnt[(size_t)v.ag * a.nlist_max + l], 1u) : 1u;
+        s.len[r] = len;
+        s.slot[r] = slot;
+        s.po[r] = (len + 15u) & ~15u; // segments are padded to the 16-row MFMA tile
+        s.to[r] = slot % mq == 0u ? (len + P - 1u) / P : 0u;
+        if (slot == 0u) rows += len;
+    }
+    __syncthreads();
+    PK_WL_MARK(5);
+    uint32_t total, tiles;
+    if (np <= 256u) { // both sums at once, a pair per thread: one barrier
+        const uint32_t lane = tid & 63u, wave = tid >> 6;
+        const uint32_t x = tid < np ? s.po[tid] : 0u, y = tid < np ? s.to[tid] : 0u;
+        uint32_t xi = x, yi = y;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t xs = __shfl_up(xi, off), ys = __shfl_up(yi, off);
+            if (lane >= (uint32_t)off) {
+                xi += xs;
+                yi += ys;
+            }
+        }
+        if (lane == 63u) {
+            s.wave[wave] = xi;
+            s.wave[4 + wave] = yi;
+        }
+        __syncthreads();
+        uint32_t xb = xi - x, yb = yi - y;
+        total = tiles = 0;
+        for (uint32_t w = 0; w < 4; ++w) {
+            xb += w < wave ? s.wave[w] : 0u;
+            yb += w < wave ? s.wave[4 + w] : 0u;
+            total += s.wave[w];
+            tiles += s.wave[4 + w];
+        }
+        if (tid < np) {
+            s.po[tid] = xb;
+            s.to[tid] = yb;
+        }
+    } else {
+        total = block_exscan(s.po, s.po, np, s.wave);
+        tiles = block_exscan(s.to, s.to, np, s.wave);
+    }
+    // cannot happen while the host bounds hold: the query's values are written nowhere, and nothing is found for it
+    const bool fits = total <= a.width;
+    if (tid == 0) {
+        s.first = tiles ? atomicAdd(&a.scalars[0], tiles) : 0u;
+        if (!fits || (tiles && s.first + tiles > a.tile_cap)) atomicOr(&m.ix[0]->ctr[1], (uint32_t)kErrWorklist);
+    }
+    // (np > 256: other threads' sums, behind the scans' barriers)
+    uint32_t *po = a.pair_off + (size_t)q * (np + 1);
+    for (uint32_t r = tid; r < np; r += blockDim.x) {
+        const uint32_t l = (uint32_t)probes_q[r];
+        probes_out[r] = (int32_t)l;
+        po[r] = s.po[r]; // (np <= 256: the thread's own)
+        if (l < v.nlist) {
+            const size_t at = ((size_t)v.ag * a.nlist_max + l) * a.cap + s.slot[r];
+            a.slot_query[at] = q;
+            a.slot_out[at] = fits ? q * a.width + s.po[r] : 0xffffffffu;
+        }
+    }
+    __syncthreads();
+    PK_WL_MARK(6);
+    const uint32_t first = s.first;
+    const bool room = first + tiles <= a.tile_cap; // (else the scan refuses the whole list)
+    for (uint32_t t = tid; room && t < tiles; t += blockDim.x) {
+        uint32_t lo = 0, hi = np - 1; // last pair whose first tile is at or before t: the pair that tile t belongs to
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) >> 1;
+            if (s.to[mid] <= t) lo = mid;
+            else hi = mid - 1;
+        }
+        const uint32_t l = (uint32_t)probes_q[lo], p = t - s.to[lo];
+        const uint32_t pg = p < s.mp[lo] ? s.mb[lo] + p : ix.dtab[(size_t)l * ix.max_dp + (p - s.mp[lo])];
+        const Arena &ar = arena_of(ix, pg);
+        const size_t local = (size_t)(pg - ar.first_page) * P;
+        const uint32_t gl = v.ag * (uint32_t)a.nlist_max + l, g = s.slot[lo] / mq, left = s.len[lo] - p * P;
+        Tile tl;
+        tl.x = ar.vec + local * (size_t)ix.row_bytes;
+        tl.xn = ar.norm + local;
+        tl.row0 = p * P;
+        tl.qbeg = gl * a.cap + g * mq;
+        tl.nrows = (uint16_t)(left < P ? left : P);
+        tl.qcnt = (uint16_t)g;
+        tl.list = gl;
+        a.tiles[first + t] = tl;
+    }
+    for (int off = 32; off > 0; off >>= 1) rows += __shfl_xor(rows, off);
+    if ((tid & 63u) == 0u && rows) atomicAdd(&m.ix[0]->stats[0], rows);
+    if (tid == 0) {
+        po[np] = fits ? total : 0u;
+        if (tiles) atomicAdd(&m.ix[0]->stats[2], (unsigned long long)tiles);
     }
 }
 
@@ -235,7 +354,7 @@ __device__ __forceinline__ void wl_write_tile(const WorklistArgs &a, const Multi
     tl.nrows = (uint16_t)(left < R ? left : R);
     const uint32_t ql = c - g * mq;
     tl.qcnt = (uint16_t)(ql < mq ? ql : mq);
-    tl.pad = 0;
+    tl.list = 0;
     out[j] = tl;
 }
 
