@@ -257,10 +257,12 @@ int pk_search(pk_index *index, const float *queries, int64_t nq, int32_t k, int3
  * first) with at most nq_max queries (or vectors) in total, k <= k_max and nprobe <=
  * nprobe_max finds it large enough, until inserts_ahead more vectors have been inserted into
  * any one of the handles: such calls then never allocate and never wait for the device.
- * The size does not depend on how many candidates the queries meet: a query's emitted
- * candidates live in a region of a few dozen times k entries, and a query that emits more
- * (no usable threshold, or a tie group larger than the region) is selected by rescoring its
- * rows instead, with the same values.
+ * Calls whose queries can meet few candidates (64 million at most, over all queries and at the
+ * longest lists) write all their values; the size is 4.25 bytes for each of those, and 16 MB at most
+ * for the work list.  For other calls it does not depend on how many candidates the queries meet: a
+ * query's emitted candidates live in a region of a few dozen times k entries, and a query that emits
+ * more (no usable threshold, or a tie group larger than the region) is selected by rescoring its rows
+ * instead, with the same values.
  *   handles   HOST [n_handles] live handles of equal d, metric, storage, page size
  *   nq_max    1 .. 32768;  inserts_ahead >= 0
  * May synchronise `stream` and allocate (once); PK_ERR_NOMEM if the device is out of memory.
@@ -270,7 +272,8 @@ int pk_workspace_reserve(pk_index *const *handles, int32_t n_handles, int64_t nq
 
 /* Test seam / tuning: entries of each query's emission region in later searches on this
  * handle (0 = the default, a few dozen times k; the library never uses fewer than k + 1).
- * A small value forces queries down the rescoring path. */
+ * Any size but the default sends searches through those regions whatever their number of candidates;
+ * a small one forces queries down the rescoring path. */
 int pk_index_set_emit_cap(pk_index *index, int32_t entries);
 
 /*

@@ -211,7 +211,8 @@ struct Plan {
     bool hot_rs; // the hot class is scored by the rows-in-registers kernel (tiles of kRrTileRows rows x up to kRrSlots slots)
     double avg_per_list; // queries per list on average (the largest over the handles of the call)
     uint32_t stride, ecap, tile_cap, span;
-    uint64_t cbuf_entries; // entries of all emission regions together
+    uint64_t cbuf_entries; // entries of all emission regions together (dense: half the values)
+    uint64_t mins;         // dense: best keys of every 16 values (0: not written)
     uint32_t rescues;      // overflowed queries of the call that have a region to be scored again into (0: none can overflow)
     bool need_coarse, need_fine, f16;
     bool raw_queries; // the coarse step reads the caller's query rows directly (no preparation launch)
@@ -224,7 +225,7 @@ struct Plan {
     char *qs32, *qs;
     float *qn32, *qn, *S, *svals, *tlo, *tinv;
     uint32_t *cand_off, *cand_cnt, *lcnt, *lstart, *lfill, *ltile, *lhtile, *pair_off, *slot_q, *slot_o, *scalars,
-        *tau, *tcur, *hist, *ccnt, *sslot_q, *sslot_o;
+        *tau, *tcur, *hist, *ccnt, *sslot_q, *sslot_o, *block_min;
     uint16_t *qagent;
     Tile *tiles, *tiles_hot, *stiles;
     unsigned long long *cpartial, *cbuf;
@@ -269,6 +270,7 @@ void carve(Plan &p, char *base, const pk_index *own)
         p.slot_o = c.take<uint32_t>(slots);
         p.tiles = c.take<Tile>((size_t)p.tile_cap + 1);
         p.cbuf = c.take<unsigned long long>((size_t)p.cbuf_entries + 16);
+        p.block_min = p.mins > 0 ? c.take<uint32_t>((size_t)p.mins) : nullptr;
     }
     if (p.need_fine && !p.dense) {
         p.tiles_hot = c.take<Tile>((size_t)p.tile_cap + 1);
@@ -353,9 +355,8 @@ constexpr int64_t kRoomyBatch = 128;
 constexpr uint32_t kRescueFrom = 8192;
 
 // Limits of the calls whose values are written whole (see make_plan).
-constexpr uint64_t kDenseWidth = 1u << 18;   // values of a query
-constexpr uint64_t kDenseValues = 32u << 20; // values of a call: 128 MB
-constexpr uint64_t kDenseSlots = 1u << 20;   // slots of all lists: two tables of 4 MB
+constexpr uint64_t kDenseValues = 64u << 20; // values of a call: 256 MB
+constexpr uint64_t kDenseSlots = 2u << 20;   // slots of all lists: two tables of 8 MB
 
 int grid_for(const pk_index *ix, int row_bytes, int mq)
 {
@@ -548,14 +549,23 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     uint32_t most = 0; // queries of a handle
     for (int a = 0; a < nh; ++a) most = std::max(most, worst ? (uint32_t)nq : qlo[a + 1] - qlo[a]);
     {
-        // Values written whole: DENSE_RULE
-        const uint64_t width = round_up(std::max<uint64_t>(wmax, 16), 16), slots = (uint64_t)nh * (uint64_t)nlist_hi * most;
+        // Values written whole.  A value costs its 4 bytes in and a sixteenth of them out, and the layout has no prefix sums;
+        // sample, gate and emission cost 10 - 27 us of a small batch, and the more the more queries meet the same counters.
+        // Searches of 1 - 1024 queries, gated and whole, us: 20 000 x 128, 64 lists, 4 probes, 1024 queries 179 and 50; 1 M x 64,
+        // 256 lists, 48 probes, 64 queries 288 and 145 (one query 75 and 63); 1 M x 256 fp16, 48 of 1024 lists, 8 queries 89
+        // and 87, 256 queries 220 and 188.  The sliced-query kernel's waves wait for their stores before the next tile's
+        // loads: 400 000 x 1024, 16 probes, 256 queries (8 per list) 378 and 350, 48 probes (24 per list) 471 and 503, 16 probes
+        // of 1024 queries (32) 638 and 655, sixteen memories of 590 rows per list (one per list) 1950 and 1864: there
+        // lists probed by few queries only.
+        const uint64_t width = round_up(std::max<uint64_t>(wmax, 16), 64), slots = (uint64_t)nh * (uint64_t)nlist_hi * most;
         const uint64_t values = (uint64_t)nq * width;
         if (worst) { // (what any call within the limits may take)
             p.cap = (uint32_t)std::min<uint64_t>(most, kDenseSlots / ((uint64_t)nh * (uint64_t)nlist_hi));
-            p.cbuf_entries = std::max<uint64_t>(p.cbuf_entries, std::min<uint64_t>((uint64_t)nq * std::min<uint64_t>(width, kDenseWidth), kDenseValues) / 2);
+            p.cbuf_entries = std::max<uint64_t>(p.cbuf_entries, std::min<uint64_t>(values, kDenseValues) / 2);
+            p.mins = std::min<uint64_t>(values, kDenseValues) / 16;
         } else if (dense_ok && need_coarse && need_fine && !lean && tunables().dense && own->emit_cap == 0 && nlist_hi <= kDenseSelectMax &&
-                   width <= kDenseWidth && values <= kDenseValues && slots <= kDenseSlots && (p.K <= kSelThreads || width <= 16u * kSelThreads)) {
+                   values <= kDenseValues && slots <= kDenseSlots &&
+                   (p.hot_from != 0 || p.avg_per_list <= 12.0) && (p.K <= kSelThreads || width <= 16u * kSelThreads)) {
             p.dense = true;
             p.cap = most;
             p.width = (uint32_t)width;
@@ -564,6 +574,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
                 p.hot_from = 0xffffffffu;
             }
             p.cbuf_entries = (values + 1) / 2;
+            p.mins = width > kReadOnce ? values / 16 : 0;
         }
     }
     p.halves_first = need_coarse && need_fine && nh == 1 && p.f16 && !p.raw_queries;
@@ -581,6 +592,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         Plan gated = p;
         gated.dense = false;
         gated.cap = 0;
+        gated.mins = 0;
         gated.cbuf_entries = gated_entries;
         carve(gated, nullptr, own);
         p.need = gated.bytes;
@@ -817,6 +829,7 @@ int run_dense(const Plan &p, const MultiArgs &m, pk_index *own, int64_t *out_ids
     sa.mq = sliced ? p.mq_h : p.mq_f;
     sa.nt = p.stream_rows;
     sa.lcnt = p.lcnt;
+    sa.mins = p.block_min;
     sa.tile_cap = p.tile_cap;
     sa.grab_div = tunables().grabdiv;
     // (no more workgroups than tiles)
@@ -841,6 +854,7 @@ int run_dense(const Plan &p, const MultiArgs &m, pk_index *own, int64_t *out_ids
     f.out_ids = out_ids;
     f.out_dist = out_dist;
     f.vals = sa.out;
+    f.mins = p.block_min;
     f.width = p.width;
     PK_HIP(launch_select_final(f, m, p.nq, s));
     if (timed) PK_TRY(mark(own, s));

@@ -275,6 +275,7 @@ struct ScanArgs {
     bool nt;                     // fine search: the rows are read past the caches (they would not stay in them anyway)
     // laid mode (lcnt != NULL): the tiles and slots are those of wl_lay_query, and every value is written
     const uint32_t *lcnt;        // pairs of each list (of all handles)
+    uint32_t *mins;              // or null: best key of every 16 values, as they lie in `out`
     uint32_t tile_cap;           // more tiles than this: the layout was refused, nothing is scanned
     int grab_div;                // tiles per grab = tiles / (grid * this), 1 .. 8
 };
@@ -419,8 +420,10 @@ struct FinalArgs {
     const float *tlo, *tinv;          // [nq] bucket scale
     // every value of the query's range instead of emitted keys (keys is null): query q's at vals[q * width]
     const float *vals;
+    const uint32_t *mins;             // best key of every 16 values: where width is more than kReadOnce
     uint32_t width;
 };
+constexpr uint32_t kReadOnce = 8192; // values that the workgroup of a final selection holds in registers
 constexpr uint32_t kRescueCap = 4096;    // keys per rescue region: what the final selection takes in registers
 constexpr uint32_t kRescueRegions = 128; // most queries of a call that are rescued
 // workgroups of launch_rescue: two per CU, and one at least for every region (a device of few CUs has fewer than regions)

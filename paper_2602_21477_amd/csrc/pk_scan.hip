@@ -299,6 +299,48 @@ __device__ __forceinline__ void emit_block(const ScanArgs &a, const Slots &s, f3
     }
 }
 
+// Smallest of each 16 lanes, in all of them.
+__device__ __forceinline__ uint32_t min_of_16(uint32_t x)
+{
+#define PK_DPP_MIN(ctrl) x = min(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, 0xf, 0xf, false));
+    PK_DPP_MIN(0x121) // row_ror 1, 2, 4, 8
+    PK_DPP_MIN(0x122)
+    PK_DPP_MIN(0x124)
+    PK_DPP_MIN(0x128)
+#undef PK_DPP_MIN
+    return x;
+}
+
+// The best key of the block's two times 16 rows for every slot: what the final selection of a long range reads first.
+template <int MT>
+__device__ __forceinline__ void write_mins(const ScanArgs &a, const Slots &s, const f32x4 (&acc)[MT][2], int rb, int ln, int lg, int nrows,
+                                           uint32_t qcnt, uint32_t row0, gfloats txn)
+{
+    constexpr int MQ = MT * 16;
+    float xn[2] = {0.f, 0.f};
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+        const int row = rb * kRowBlock + nt * 16 + ln;
+        if (a.metric == PK_METRIC_L2 && row < nrows) xn[nt] = txn[row];
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        if ((uint32_t)(mt * 16) >= qcnt) break; // wave-uniform
+        uint32_t mine = 0xffffffffu; // lane ln < 8 of a group: of its slot ln & 3 and 16 rows ln >> 2
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float v = acc[mt][nt][i];
+                if (a.metric == PK_METRIC_L2) v = l2_from_dot(xn[nt], v, s.qn[(mt * 16 + lg * 4 + i) & (MQ - 1)]);
+                const uint32_t best = min_of_16(rb * kRowBlock + nt * 16 + ln < nrows ? order_bits(v, a.metric) : 0xffffffffu);
+                mine = ln == nt * 4 + i ? best : mine;
+            }
+        const int m = mt * 16 + lg * 4 + (ln & 3), first = rb * kRowBlock + (ln >> 2) * 16;
+        if (ln < 8 && (uint32_t)m < qcnt && first < nrows && s.out[m] != 0xffffffffu) a.mins[(s.out[m] + row0 + (uint32_t)first) >> 4] = mine;
+    }
+}
+
 // Epilogue of one 32-row block: the lane holds rows (rb*32 + nt*16 + ln) for slots
 // mt*16 + lg*4 + i.  Dense mode writes every value; gated mode emits the survivors.
 // COHERENT (dense mode): the values are written through to where every CU of the device reads them
@@ -314,6 +356,9 @@ __device__ __forceinline__ void finish_block(const ScanArgs &a, const Slots &s, 
         constexpr int MQ = MT * 16;
         const float worst = a.metric == PK_METRIC_IP ? -INFINITY : INFINITY;
         const int nrows_pad = (nrows + 15) & ~15;
+        if constexpr (LAID) {
+            if (a.mins) write_mins<MT>(a, s, acc, rb, ln, lg, nrows, qcnt, row0, txn);
+        }
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
             const int row = rb * kRowBlock + nt * 16 + ln;

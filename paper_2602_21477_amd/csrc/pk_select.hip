@@ -58,7 +58,7 @@ struct Selector {
     uint32_t cap; // entries of keys (a power of two >= 512)
     u64 thr;
 
-    __device__ void init(u64 *k, uint32_t *c, int kk, uint32_t capacity = (uint32_t)kSelCap)
+    __device__ __forceinline__ void init(u64 *k, uint32_t *c, int kk, uint32_t capacity = (uint32_t)kSelCap)
     {
         keys = k;
         cnt = c;
@@ -69,7 +69,7 @@ struct Selector {
         __syncthreads();
     }
     // sort what is buffered, keep the best K, tighten the threshold (block-wide)
-    __device__ void flush()
+    __device__ __forceinline__ void flush()
     {
         __syncthreads();
         const uint32_t n = *cnt;
@@ -84,7 +84,7 @@ struct Selector {
         __syncthreads();
     }
     // make room for one round of at most `room` pushes (block-wide)
-    __device__ void reserve(uint32_t room)
+    __device__ __forceinline__ void reserve(uint32_t room)
     {
         __syncthreads();
         const uint32_t n = *cnt; // read by everyone before anyone pushes again
@@ -189,18 +189,27 @@ __global__ __launch_bounds__(kSelThreads) void select_probes_kernel(const u64 *p
 // GO_ON: the workgroup goes on to do its query's share of the work-list construction (kCount: pairs per list,
 // candidate layout, sample tiles; kLay: all of it), which saves the launch that would otherwise follow the selection.
 enum GoOn { kStop, kCount, kLay };
+// keys that the selection of K probes holds in LDS: 256 within a bound, or K and what rounds them up to a power of two; two of padding
+__device__ __host__ __forceinline__ uint32_t dense_keys(uint32_t K) { return (K <= 256u ? 256u : K <= 512u ? 512u : 1024u) + 2u; }
+static size_t dense_lds(uint32_t K, GoOn go_on)
+{
+    const size_t wl = go_on == kCount ? WlCountLds::bytes(K) : go_on == kLay ? WlLayLds::bytes(K) : 0;
+    return 4096 + dense_keys(K) * sizeof(u64) + K * sizeof(int32_t) + wl;
+}
 template <int VPT, GoOn GO_ON>
 __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, const uint32_t *qoff, const uint32_t *qcnt,
                                                            int metric, int K, int32_t *probes, WorklistArgs wa,
                                                            SampleArgs sm, MultiArgs ma)
 {
-    __shared__ __align__(16) uint32_t hist[4][256]; // one histogram per radix pass: zeroed once
     __shared__ uint32_t s_w[4];
     __shared__ uint32_t s_n;
-    __shared__ __align__(16) u64 sel[PK_MAX_NPROBE + 2];
+    extern __shared__ __align__(16) unsigned char s_dyn[]; // (see dense_lds)
+    uint32_t(*hist)[256] = reinterpret_cast<uint32_t(*)[256]>(s_dyn); // [4][256] one histogram per radix pass: zeroed once
+    u64 *const sel = reinterpret_cast<u64 *>(s_dyn + 4096);            // [dense_keys(K)]
     constexpr bool COUNT = GO_ON != kStop;
-    __shared__ int32_t s_probe[COUNT ? PK_MAX_NPROBE : 1];
-    __shared__ std::conditional_t<GO_ON == kCount, WlCountLds, std::conditional_t<GO_ON == kLay, WlLayLds, uint32_t>> s_wl;
+    int32_t *const s_probe = reinterpret_cast<int32_t *>(sel + dense_keys((uint32_t)K)); // [K]
+    [[maybe_unused]] std::conditional_t<GO_ON == kCount, WlCountLds, std::conditional_t<GO_ON == kLay, WlLayLds, uint32_t>> s_wl;
+    if constexpr (COUNT) s_wl.carve(reinterpret_cast<uint32_t *>(s_probe + K), (uint32_t)K);
     PK_MARK(sel, 0);
     const uint32_t q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t n = qcnt[q];
@@ -327,12 +336,12 @@ hipError_t launch_select_dense(const float *vals, const uint32_t *qoff, const ui
     m0.n = 0;
     auto go = [&](auto vpt) {
         constexpr int VPT = decltype(vpt)::value;
-        auto run = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, g, b, 0, s, vals, qoff, qcnt, metric, K, probes, wa ? *wa : w0, wa ? *sm : s0, wa ? *ma : m0);
+        auto run = [&](auto kernel, GoOn go_on) {
+            hipLaunchKernelGGL(kernel, g, b, dense_lds((uint32_t)K, go_on), s, vals, qoff, qcnt, metric, K, probes, wa ? *wa : w0, wa ? *sm : s0, wa ? *ma : m0);
         };
-        if (!wa) run(select_dense_kernel<VPT, kStop>);
-        else if (wa->width == 0) run(select_dense_kernel<VPT, kCount>);
-        else run(select_dense_kernel<VPT, kLay>);
+        if (!wa) run(select_dense_kernel<VPT, kStop>, kStop);
+        else if (wa->width == 0) run(select_dense_kernel<VPT, kCount>, kCount);
+        else run(select_dense_kernel<VPT, kLay>, kLay);
     };
     if (max_cnt <= 1024) go(std::integral_constant<int, 4>{});
     else if (max_cnt <= 4096) go(std::integral_constant<int, 16>{});
@@ -658,81 +667,147 @@ __device__ __forceinline__ void final_by_radix(G get, uint32_t cnt_q, uint32_t K
     }
 }
 
-// The same of all cnt_q values of a query's range (DENSE calls).  A bound on the K-th best by parts (bound_of_parts; for K
-// of some hundred, the K-th best of 1024 parts), and the few values within it, collected in surv and put in order by counting;
-// ranges of up to 8192 values are read once.  False: more than fit are within the bound, or K is too large; nothing is
-// selected.
-constexpr uint32_t kSurvivors = 2048;
-__device__ __forceinline__ bool final_of_values(const float *vals, uint32_t cnt_q, uint32_t K, int metric, uint32_t (*hist)[256],
-                                                u64 *keys, u64 *surv, uint32_t *s_cnt)
+// A bound on the K-th smallest (K up to 256) of what the workgroup's threads met: mn[]: each thread's smallest keys of four
+// parts of it, all ones for a part with none; `all`: every thread has met something.
+__device__ __forceinline__ uint32_t bound_on_kth(u32x4 mn, bool all, uint32_t K, uint32_t (*hist)[256])
+{
+    if (K <= kMostParts) return bound_of_parts(min(min(mn[0], mn[1]), min(mn[2], mn[3])), K, hist[0]);
+    if (!all) return 0xffffffffu;
+    const uint32_t key[4] = {mn[0], mn[1], mn[2], mn[3]};
+    const bool live[4] = {key[0] != 0xffffffffu, key[1] != 0xffffffffu, key[2] != 0xffffffffu, key[3] != 0xffffffffu};
+    uint32_t left, ties;
+    return radix_kth<4>(key, live, K, hist, left, ties);
+}
+
+// The same of all cnt_q values of a query's range (DENSE calls): a bound on the K-th best by parts, and the few values within
+// it, collected in surv and put in order by counting.  Ranges of up to kReadOnce values are read once, into registers; of
+// longer ones the best keys of every 16 values are, and then only those 16 that have one within the bound: 250 000 values
+// of one query in ... us where reading them twice took 75.  False: more than fit are within the bound, or K is too large;
+// nothing is selected.  n_surv: how many keys surv holds, every one that is no worse than the K-th best among them (0: none).
+constexpr uint32_t kBlocks = 1024;
+// Keys that surv holds.  Where the query's nearest list has less than K parts' worth of values, all of it is within the
+// bound, and some from other lists: a part is 4 neighbours of ranges that are read once, 16 of others, and four times that
+// where there are 64 parts.
+constexpr uint32_t kMostSurvivors = 18u * kSelThreads;
+__device__ __host__ __forceinline__ uint32_t survivors(uint32_t K, uint32_t width)
+{
+    const uint32_t want = (width <= kReadOnce ? 4u : 16u) * (K <= kFewParts ? 4u : 1u) * K + 512u;
+    return want < 1024u ? 1024u : (want < kMostSurvivors ? want : kMostSurvivors);
+}
+__device__ __forceinline__ bool final_of_values(const float *vals, const uint32_t *mins, uint32_t width, uint32_t cnt_q, uint32_t K, int metric,
+                                                uint32_t (*hist)[256], u64 *keys, u64 *surv, uint32_t &n_surv, uint32_t *s_cnt)
 {
     const uint32_t tid = threadIdx.x;
+    n_surv = 0;
     if (K > (uint32_t)kSelThreads) { // (the first 1024 values alone give 256 parts)
         if (cnt_q > 16u * kSelThreads) return false;
         final_by_radix<16>([=](int, uint32_t p) { return ((u64)order_bits(vals[p], metric) << 32) | p; }, cnt_q, K, hist, keys, s_cnt);
         return true;
     }
+    const uint32_t room = survivors(K, width);
     constexpr int U = 8; // loads in flight
-    constexpr uint32_t kRound = U * 4u * kSelThreads;
-    f32x4 v[U];
-    auto load = [&](uint32_t p0) {
+    constexpr uint32_t kStep = 4u * kSelThreads;
+    static_assert(kReadOnce == U * kStep, "a round of loads");
+    u32x4 v[U];
+    auto load = [&](const float *from, uint32_t p0, uint32_t n) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t p = p0 + u * 4u * kSelThreads;
-            v[u] = *reinterpret_cast<const f32x4 *>(vals + (p < cnt_q ? p : 0u)); // (ranges are padded to 16 values)
+            const uint32_t p = p0 + u * kStep;
+            v[u] = reinterpret_cast<const u32x4 *>(from)[(p < n ? p : 0u) >> 2];
         }
     };
-    uint32_t mn[4] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
-    for (uint32_t r = 0; r < cnt_q; r += kRound) {
-        load(r + 4u * tid);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (r + 4u * tid + u * 4u * kSelThreads < cnt_q)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) mn[u & 3] = min(mn[u & 3], min(order_bits(v[u][e], metric), 0xfffffffeu));
-    }
-    PK_MARK(sel, 41);
-    uint32_t bound;
-    if (K <= kMostParts) {
-        bound = bound_of_parts(min(min(mn[0], mn[1]), min(mn[2], mn[3])), K, hist[0]);
-    } else if (cnt_q > K) {
-        bool live[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) live[j] = mn[j] != 0xffffffffu;
-        uint32_t left, ties;
-        // (fewer values than 1024 leave parts without one: as many as K have one only if a thread's first part always does)
-        bound = cnt_q >= 4u * kSelThreads ? radix_kth<4>(mn, live, K, hist, left, ties) : 0xffffffffu;
-    } else {
-        bound = 0xffffffffu;
-    }
-    PK_MARK(sel, 42);
-    auto collect = [&](uint32_t p0) {
+    u32x4 mn = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu};
+    if (cnt_q <= kReadOnce) {
+        load(vals, 4u * tid, cnt_q); // (ranges are padded to 16 values)
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const uint32_t p = p0 + u * 4u * kSelThreads, key = order_bits(v[u][e], metric);
+                v[u][e] = 4u * tid + u * kStep < cnt_q ? order_bits(__uint_as_float(v[u][e]), metric) : 0xffffffffu;
+                mn[u & 3] = min(mn[u & 3], min(v[u][e], 0xfffffffeu) | (4u * tid + u * kStep < cnt_q ? 0u : 1u));
+            }
+        PK_MARK(sel, 41);
+        const uint32_t bound = cnt_q > K ? bound_on_kth(mn, cnt_q >= kStep, K, hist) : 0xffffffffu;
+        if (cnt_q <= K) __syncthreads();
+        PK_MARK(sel, 42);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t p = 4u * tid + u * kStep + e, key = v[u][e];
                 if (p < cnt_q && key <= bound && key < kWorstBits) { // (padding is no candidate)
                     const uint32_t at = atomicAdd(s_cnt, 1u);
-                    if (at < kSurvivors) surv[at] = ((u64)key << 32) | (p + e);
+                    if (at < room) surv[at] = ((u64)key << 32) | p;
                 }
             }
-    };
-    if (cnt_q <= kRound) {
-        collect(4u * tid); // still in registers
     } else {
-        for (uint32_t r = 0; r < cnt_q; r += kRound) {
-            load(r + 4u * tid);
-            collect(r + 4u * tid);
+        // Neighbouring blocks go to neighbouring threads: the query's nearest list lies in one piece, and where it has
+        // K blocks of values or more the bound is one of theirs; where it has fewer, all of it (16 K values) and a few more
+        // are within the bound.
+        const uint32_t nb = cnt_q >> 4; // (more than 512)
+        constexpr uint32_t V = kReadOnce / kSelThreads;
+        uint32_t w[V];
+        auto load_mins = [&](uint32_t r) {
+#pragma unroll
+            for (uint32_t u = 0; u < V; ++u) {
+                const uint32_t b = r + u * kSelThreads + tid;
+                w[u] = mins[b < nb ? b : 0u];
+            }
+        };
+        for (uint32_t r = 0; r < nb; r += kReadOnce) {
+            load_mins(r);
+#pragma unroll
+            for (uint32_t u = 0; u < V; ++u)
+                if (r + u * kSelThreads + tid < nb) mn[u & 3] = min(mn[u & 3], min(w[u], 0xfffffffeu));
+        }
+        PK_MARK(sel, 41);
+        const uint32_t bound = bound_on_kth(mn, nb >= (uint32_t)kSelThreads, K, hist);
+        PK_MARK(sel, 42);
+        uint32_t *const blocks = reinterpret_cast<uint32_t *>(keys); // (the kept keys come later)
+        for (uint32_t r = 0; r < nb; r += kReadOnce) {
+            if (nb > kReadOnce) load_mins(r);
+#pragma unroll
+            for (uint32_t u = 0; u < V; ++u) {
+                const uint32_t b = r + u * kSelThreads + tid;
+                if (b < nb && w[u] <= bound && w[u] < kWorstBits) {
+                    const uint32_t at = atomicAdd(s_cnt, 1u);
+                    if (at < kBlocks) blocks[at] = b;
+                }
+            }
+        }
+        __syncthreads();
+        const uint32_t within = *s_cnt;
+        __syncthreads();
+        if (within > kBlocks) return false;
+        if (tid == 0) *s_cnt = 0;
+        __syncthreads();
+        for (uint32_t i = tid; i < within * 16u; i += 4u * kSelThreads) { // 16 threads a block, four blocks in flight
+            u32x4 p;
+            f32x4 x;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t j = i + u * kSelThreads;
+                p[u] = blocks[j < within * 16u ? j >> 4 : 0u] * 16u + (j & 15u);
+                x[u] = vals[p[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t key = order_bits(x[u], metric);
+                if (i + u * kSelThreads < within * 16u && key <= bound && key < kWorstBits) {
+                    const uint32_t at = atomicAdd(s_cnt, 1u);
+                    if (at < room) surv[at] = ((u64)key << 32) | p[u];
+                }
+            }
         }
     }
     __syncthreads();
     const uint32_t n = *s_cnt;
     PK_MARK(sel, 43);
-    if (n > kSurvivors) {
+    if (n > room) {
         __syncthreads(); // (the caller counts in the same word)
         return false;
     }
+    n_surv = n;
     if (n <= (uint32_t)kSelThreads) {
         if (tid < 2) surv[n + tid] = kMaxKey; // padding: the keys are read in pairs
         __syncthreads();
@@ -745,7 +820,8 @@ __device__ __forceinline__ bool final_of_values(const float *vals, uint32_t cnt_
         __syncthreads();
     } else {
         __syncthreads(); // (the selection counts in the same word)
-        final_by_radix<kSurvivors / kSelThreads>([=](int, uint32_t p) { return surv[p]; }, n, K, hist, keys, s_cnt);
+        if (n <= 4u * kSelThreads) final_by_radix<4>([=](int, uint32_t p) { return surv[p]; }, n, K, hist, keys, s_cnt);
+        else final_by_radix<kMostSurvivors / kSelThreads>([=](int, uint32_t p) { return surv[p]; }, n, K, hist, keys, s_cnt);
     }
     return true;
 }
@@ -760,7 +836,7 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     int64_t *s_id = reinterpret_cast<int64_t *>(keys + cap);     // [k]
     // [2][row_bytes + kQPadBytes] when rescoring; the histograms of the radix selection otherwise
     char *s_q = reinterpret_cast<char *>(s_id + ((a.k + 1) & ~1));
-    [[maybe_unused]] u64 *const s_surv = reinterpret_cast<u64 *>(s_q + qbytes) - (DENSE ? kSurvivors : 0u); // DENSE: the last part of qbytes
+    [[maybe_unused]] u64 *const s_surv = reinterpret_cast<u64 *>(s_q + 4 * 256 * sizeof(uint32_t)); // DENSE: behind the histograms
     uint32_t *s_po = reinterpret_cast<uint32_t *>(s_q + qbytes); // [nprobe + 1] the query's row of pair_off
     uint32_t *s_pr = s_po + a.nprobe + 1;                        // [nprobe] its probe list,
     uint32_t *s_mp = s_pr + a.nprobe, *s_mb = s_mp + a.nprobe;   // [nprobe] pages and first page of the lists' build-time extents
@@ -827,7 +903,9 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     bool in_registers = cnt_q <= 16u * kSelThreads && !overflow;
     uint32_t(*hist)[256] = reinterpret_cast<uint32_t(*)[256]>(s_q);
     [[maybe_unused]] const float *const values = DENSE ? a.vals + (size_t)q * a.width : nullptr;
-    if constexpr (DENSE) in_registers = final_of_values(values, cnt_q, (uint32_t)a.K, a.metric, hist, keys, s_surv, &s_cnt);
+    [[maybe_unused]] uint32_t n_surv = 0;
+    if constexpr (DENSE) in_registers = final_of_values(values, a.mins ? a.mins + (size_t)q * (a.width / 16u) : nullptr, a.width, cnt_q, (uint32_t)a.K,
+                                                        a.metric, hist, keys, s_surv, n_surv, &s_cnt);
     if (DENSE && !in_registers) {
         // equal values are the rule: all of them through the streaming selector
         if (threadIdx.x == 0) s_cnt = 0;
@@ -910,10 +988,10 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
                 keys[t] = t < nb ? spill[t] : (((u64)tau << 32) | t); // the low word is no longer used
             __syncthreads();
         } else {
-        const uint32_t total = cnt_q;
+        const uint32_t total = n_surv > 0 ? n_surv : cnt_q;
         const int metric = a.metric;
         auto key_at = [=](uint32_t p) { // (nothing by reference: the kernel's arguments would be copied to memory)
-            if constexpr (DENSE) return ((u64)order_bits(values[p], metric) << 32) | p;
+            if constexpr (DENSE) return n_surv > 0 ? s_surv[p] : ((u64)order_bits(values[p], metric) << 32) | p;
             else return v[p];
         };
         // Members are taken in (id, position) order: several rows may carry one id, and each
@@ -1137,12 +1215,16 @@ hipError_t launch_select_final(const FinalArgs &a, const MultiArgs &h, int64_t n
     if (nq <= 0) return hipSuccess;
     const bool dense = a.vals != nullptr;
     if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || (!dense && a.ecap < (uint32_t)a.K)) return hipErrorInvalidValue;
-    if (dense && (a.width % 16 != 0 || (reinterpret_cast<uintptr_t>(a.vals) & 15) != 0)) return hipErrorInvalidValue;
-    const uint32_t cap = final_cap(a.K);
+    if (dense && (a.width % 64 != 0 || (reinterpret_cast<uintptr_t>(a.vals) & 15) != 0 || (a.width > kReadOnce && !a.mins) ||
+                  (reinterpret_cast<uintptr_t>(a.mins) & 15) != 0))
+        return hipErrorInvalidValue;
+    // (dense calls buffer a round of one key per thread, if any)
+    uint32_t cap = dense ? 512u : final_cap(a.K);
+    while (dense && cap < (uint32_t)a.K + kSelThreads) cap <<= 1;
     // keys, ids, and the query row + a row of zeros for a query that has to be rescored; or the histograms (and what is
     // collected from a range of values)
     const size_t hists = (size_t)4 * 256 * sizeof(uint32_t);
-    const size_t qbytes = dense ? hists + kSurvivors * sizeof(u64) : std::max((size_t)2 * (a.row_bytes + kQPadBytes), hists);
+    const size_t qbytes = dense ? hists + survivors((uint32_t)a.K, a.width) * sizeof(u64) : std::max((size_t)2 * (a.row_bytes + kQPadBytes), hists);
     // ..., and the query's rows of the candidate layout
     const size_t lds = (size_t)cap * sizeof(u64) + (size_t)((a.k + 1) & ~1) * sizeof(int64_t) + qbytes +
                        (size_t)(4 * a.nprobe + 1) * sizeof(uint32_t);

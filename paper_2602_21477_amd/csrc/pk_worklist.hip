@@ -104,7 +104,9 @@ hipError_t launch_prep_coarse(const float *q, int64_t nq, int d, int row_bytes, 
 // per query: pairs per list, candidate layout, tiles of the threshold sample
 __global__ __launch_bounds__(256) void wl_count_kernel(WorklistArgs a, SampleArgs sm, MultiArgs m)
 {
-    __shared__ WlCountLds s;
+    extern __shared__ uint32_t s_dyn[];
+    WlCountLds s;
+    s.carve(s_dyn, (uint32_t)a.nprobe);
     wl_count_query(a, sm, m, blockIdx.x, s, a.probes + (size_t)blockIdx.x * a.nprobe, nullptr, wl_index_view(a, m, blockIdx.x));
 }
 
@@ -138,7 +140,7 @@ hipError_t launch_worklist_count(const WorklistArgs &a, const SampleArgs &sm, co
         const hipError_t e = launch_fill_u32(a.lcnt, 0u, (size_t)2 * (size_t)a.n_handles * (size_t)a.nlist_max, s);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(wl_count_kernel, dim3((uint32_t)a.nq), dim3(256), 0, s, a, sm, m);
+    hipLaunchKernelGGL(wl_count_kernel, dim3((uint32_t)a.nq), dim3(256), WlCountLds::bytes((uint32_t)a.nprobe), s, a, sm, m);
     return hipGetLastError();
 }
 

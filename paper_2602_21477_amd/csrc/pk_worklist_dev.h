@@ -37,15 +37,27 @@ __device__ __forceinline__ WlIndexView wl_index_view(const WorklistArgs &a, cons
     v.nlist = (uint32_t)v.ix->nlist;
     return v;
 }
-struct WlCountLds {
-    uint32_t len[PK_MAX_NPROBE];     // rows of each probed list
-    uint32_t mp[PK_MAX_NPROBE];      // pages of its build-time extent
-    uint32_t mb[PK_MAX_NPROBE];      // first page of that extent
-    uint32_t po[PK_MAX_NPROBE + 1];  // candidates of the probed lists before each one
-    uint16_t sr[kMaxSamplePages];    // the sample's pages: which probed list,
-    uint32_t slp[kMaxSamplePages];   //   and which of its pages
-    uint32_t ns;                     // how many there are
-    uint32_t wave[17];
+struct WlCountLds {    // (sized by the call's probes: what the largest number of them takes leaves three workgroups per CU)
+    uint32_t *len;     // [nprobe] rows of each probed list
+    uint32_t *mp;      // [nprobe] pages of its build-time extent
+    uint32_t *mb;      // [nprobe] first page of that extent
+    uint32_t *po;      // [nprobe + 1] candidates of the probed lists before each one
+    uint32_t *slp;     // [kMaxSamplePages] the sample's pages: which of a list's pages,
+    uint16_t *sr;      // [kMaxSamplePages]   and which probed list
+    uint32_t *wave;    // [17]
+    uint32_t *ns;      // how many sample pages there are
+    static constexpr size_t bytes(uint32_t np) { return (4u * np + 1u + kMaxSamplePages + kMaxSamplePages / 2 + 17u + 1u) * 4u; }
+    __device__ __forceinline__ void carve(uint32_t *at, uint32_t np)
+    {
+        len = at;
+        mp = len + np;
+        mb = mp + np;
+        po = mb + np;
+        slp = po + np + 1;
+        wave = slp + kMaxSamplePages;
+        ns = wave + 17;
+        sr = reinterpret_cast<uint16_t *>(ns + 1);
+    }
 };
 __device__ __forceinline__ void wl_count_query(const WorklistArgs &a, const SampleArgs &sm, const MultiArgs &m, uint32_t q,
                                                WlCountLds &s, const int32_t *probes_q, int32_t *probes_out,
@@ -81,7 +93,7 @@ __device__ __forceinline__ void wl_count_query(const WorklistArgs &a, const Samp
                 s.sr[ns] = (uint16_t)r;
                 s.slp[ns++] = s.len[r] / P;
             }
-        s.ns = ns;
+        *s.ns = ns;
     }
     __syncthreads();
     PK_WL_MARK(6);
@@ -94,7 +106,7 @@ __device__ __forceinline__ void wl_count_query(const WorklistArgs &a, const Samp
         tl.nrows = 0;
         tl.qcnt = 1;
         tl.list = 0;
-        if (p < s.ns) {
+        if (p < *s.ns) {
             const int r = s.sr[p];
             const uint32_t l = (uint32_t)probes_q[r];
             const uint32_t lp = s.slp[p];
@@ -142,14 +154,26 @@ __device__ __forceinline__ void wl_count_query(const WorklistArgs &a, const Samp
 // many slots the group will have is read from the pair counters by the scan.  Needs no prefix sums over the lists and no
 // sample: for calls whose values are written whole (a.width per query).
 struct WlLayLds {
-    uint32_t len[PK_MAX_NPROBE];     // rows of each probed list
-    uint32_t mp[PK_MAX_NPROBE];      // pages of its build-time extent
-    uint32_t mb[PK_MAX_NPROBE];      // first page of that extent
-    uint32_t slot[PK_MAX_NPROBE];    // the pair's slot
-    uint32_t po[PK_MAX_NPROBE];      // candidates of the probed lists before each one
-    uint32_t to[PK_MAX_NPROBE];      // tiles of the groups opened before each one
-    uint32_t wave[17];
-    uint32_t first;                  // where the query's tiles start
+    uint32_t *len;     // [nprobe] rows of each probed list
+    uint32_t *mp;      // [nprobe] pages of its build-time extent
+    uint32_t *mb;      // [nprobe] first page of that extent
+    uint32_t *slot;    // [nprobe] the pair's slot
+    uint32_t *po;      // [nprobe] candidates of the probed lists before each one
+    uint32_t *to;      // [nprobe] tiles of the groups opened before each one
+    uint32_t *wave;    // [17]
+    uint32_t *first;   // where the query's tiles start
+    static constexpr size_t bytes(uint32_t np) { return (6u * np + 17u + 1u) * 4u; }
+    __device__ __forceinline__ void carve(uint32_t *at, uint32_t np)
+    {
+        len = at;
+        mp = len + np;
+        mb = mp + np;
+        slot = mb + np;
+        po = slot + np;
+        to = po + np;
+        wave = to + np;
+        first = wave + 17;
+    }
 };
 __device__ __forceinline__ void wl_lay_query(const WorklistArgs &a, const MultiArgs &m, uint32_t q, WlLayLds &s,
                                              const int32_t *probes_q, int32_t *probes_out, const WlIndexView &v)
@@ -208,8 +232,8 @@ __device__ __forceinline__ void wl_lay_query(const WorklistArgs &a, const MultiA
     // cannot happen while the host bounds hold: the query's values are written nowhere, and nothing is found for it
     const bool fits = total <= a.width;
     if (tid == 0) {
-        s.first = tiles ? atomicAdd(&a.scalars[0], tiles) : 0u;
-        if (!fits || (tiles && s.first + tiles > a.tile_cap)) atomicOr(&m.ix[0]->ctr[1], (uint32_t)kErrWorklist);
+        *s.first = tiles ? atomicAdd(&a.scalars[0], tiles) : 0u;
+        if (!fits || (tiles && *s.first + tiles > a.tile_cap)) atomicOr(&m.ix[0]->ctr[1], (uint32_t)kErrWorklist);
     }
     // (np > 256: other threads' sums, behind the scans' barriers)
     uint32_t *po = a.pair_off + (size_t)q * (np + 1);
@@ -225,7 +249,7 @@ __device__ __forceinline__ void wl_lay_query(const WorklistArgs &a, const MultiA
     }
     __syncthreads();
     PK_WL_MARK(6);
-    const uint32_t first = s.first;
+    const uint32_t first = *s.first;
     const bool room = first + tiles <= a.tile_cap; // (else the scan refuses the whole list)
     for (uint32_t t = tid; room && t < tiles; t += blockDim.x) {
         uint32_t lo = 0, hi = np - 1; // last pair whose first tile is at or before t: the pair that tile t belongs to

@@ -424,3 +424,48 @@ def test_deletes_by_hash_set(gpu_device, nlist, page):
         assert gi[:, 0].tolist() == some and float(gv.max()) < 1e-4  # the row that carries the id is still the id's
     finally:
         ix.close()
+
+
+@pytest.mark.parametrize("n,d,nlist,nprobe,k,nq,page,storage,metric,equal", [
+    (700, 40, 60, 5, 10, 3, 32, F32, IP, 0),  # ranges of a hundred values
+    (3000, 40, 30, 9, 150, 33, 64, F32, L2, 0),  # a thousand values and a K beyond what parts serve
+    (9000, 100, 12, 6, 300, 17, 0, F16, IP, 0),  # up to 4096 values, K beyond the workgroup's threads
+    (9000, 64, 900, 600, 20, 5, 0, F32, L2, 0),  # more probes than threads
+    (60000, 48, 20, 8, 23, 70, 0, F32, IP, 0),  # long ranges: 64 parts, the most for them
+    (60000, 48, 20, 8, 127, 40, 96, F16, L2, 0),  # ... 256 parts, the most for them
+    (60000, 48, 20, 8, 255, 9, 1024, F32, L2, 0),  # ... 1024 parts, the most for them
+    (60000, 1100, 20, 20, 10, 20, 0, F32, IP, 0),  # sliced queries, every list
+    (60000, 64, 4, 2, 100, 300, 0, F16, IP, 0),  # several groups per list
+    (30000, 32, 8, 4, 50, 12, 0, F32, IP, 6000),  # equal values: more than are collected
+    (90000, 32, 4, 4, 50, 3, 0, F32, L2, 60000)])  # ... more blocks than are
+def test_values_written_whole_give_the_rows_of_the_gated_scan(gpu_device, n, d, nlist, nprobe, k, nq, page, storage, metric, equal):
+    """A forced emission region sends the call through sample and gate; without it the values are written whole.  The same
+    rows, bit for bit, after inserts (delta pages) and deletes too, and for two memories in one call."""
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    x = torch.randn((n, d), device="cuda", generator=g)
+    if equal:
+        x[torch.randperm(n, device="cuda", generator=g)[:equal]] = x[0].clone()
+    x = x.half().float()
+    cent = x[torch.randperm(n, device="cuda", generator=g)[:nlist]].clone()
+    cent += 1e-3 * torch.randn(cent.shape, device="cuda", generator=g)
+    q = torch.randn((nq, d), device="cuda", generator=g)
+    q[0] = x[0]
+    ids = torch.randperm(3 * n, device="cuda", generator=g)[:n].contiguous()
+    ix, other = (B.Index(cent, rows, metric=metric, storage=storage, page_vecs=page, ids=i, insert_reserve=4096)
+                 for rows, i in ((x, ids), (x[: n // 3].contiguous(), None)))
+    try:
+        for stage in ("built", "changed"):
+            if stage == "changed":
+                ix.delete(ids[: n // 10].contiguous())
+                ix.insert(x[:700].contiguous(), ids[:700].contiguous())
+            offs = [0, nq - nq // 3, nq]
+            whole = ix.search(q, k, nprobe), B.search_multi([ix, other], offs, q, k, nprobe)
+            B.pk_index_set_emit_cap(ix.handle, 32768)
+            gated = ix.search(q, k, nprobe), B.search_multi([ix, other], offs, q, k, nprobe)
+            B.pk_index_set_emit_cap(ix.handle, 0)
+            for (wi, wv), (gi, gv) in zip(whole, gated):
+                assert torch.equal(wi, gi) and torch.equal(wv, gv), stage
+        assert ix.stats().device_error == 0 and other.stats().device_error == 0
+    finally:
+        ix.close()
+        other.close()
