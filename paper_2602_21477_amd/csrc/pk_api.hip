@@ -577,7 +577,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
             p.mins = width > kReadOnce ? values / 16 : 0;
         }
     }
-    p.halves_first = need_coarse && need_fine && nh == 1 && p.f16 && !p.raw_queries;
+    p.halves_first = need_coarse && need_fine && p.f16;
     // few lists, pairs and tiles: the threshold kernel's workgroups lay out slots and tiles as well (see wl_spread)
     p.wl_small = (uint64_t)nh * (uint64_t)nlist_hi <= kWlSmallLists && (uint64_t)nq * (uint64_t)nprobe <= 16384 && tiles <= 65536;
     // A batch of 512 queries or more has regions of 8192 entries or fewer and can have a query overflow in ordinary use
@@ -705,7 +705,7 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
     qm.nclear = p.need_fine ? 2u * (uint32_t)p.nh * (uint32_t)p.nlist_max + 2u : 0u; // and what lies behind them
     // small segments: one launch of the centroid kernel for all of them
     CentroidArgs ca{};
-    if (p.halves_first) {
+    if (p.halves_first && !p.raw_queries) {
         // one launch prepares both copies, the coarse step's and the half-precision one that the scan reads
         SplitRowsArgs sr{};
         sr.x = q;
@@ -726,6 +726,11 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
         ca.qs = reinterpret_cast<const char *>(q);
         ca.qnorm = nullptr;
         ca.meta = qm;
+        if (p.halves_first) { // (inner product: no norms)
+            ca.halves = p.qs;
+            ca.half_bytes = own->row_bytes;
+            ca.d = own->cfg.d;
+        }
     } else {
         PK_HIP(launch_prep_coarse(q, p.nq, own->cfg.d, own->rb32, p.qs32, p.qn32, qm, m, s));
         ca.qs = p.qs32;

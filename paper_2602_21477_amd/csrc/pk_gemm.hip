@@ -362,9 +362,11 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     if (a.half_rows) a.half_norm[r] = norm16;
     if (a.best) a.best[r] = ~0ull;
     if (a.meta.cand_off) {
+        int h = 0;
+        while (h + 1 < mm.n && r >= mm.qlo[h + 1]) ++h;
         a.meta.cand_off[r] = r * a.meta.stride;
-        a.meta.cand_cnt[r] = (uint32_t)mm.ix[0]->nlist;
-        a.meta.qagent[r] = 0;
+        a.meta.cand_cnt[r] = (uint32_t)mm.ix[h]->nlist;
+        a.meta.qagent[r] = (uint16_t)h;
     }
 }
 

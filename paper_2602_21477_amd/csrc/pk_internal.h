@@ -459,6 +459,9 @@ struct CentroidArgs {
     //   atomicMin (top-1 assignment of inserts; best[] must hold ~0 on entry).
     QueryMeta meta;
     unsigned long long *best;
+    //   halves != null (with meta): the rows of the segment are also written rounded to half precision, zero padded to half_bytes.
+    char *halves;
+    int half_bytes, d;
 };
 hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hipStream_t s);
 // Of the rows (of one handle) whose best two values are near, as the split GEMM left them, the best by the centroid kernel.
@@ -649,7 +652,7 @@ struct SplitRowsArgs {
     uint32_t *cmax;      // raised to the largest squared norm of the centroids (as bits), or null
     float *left;         // [m] out: length of what the first halfs leave out of the row, or null
     uint32_t *cmax_left; // raised to the most that is of a centroid (as bits), or null
-    QueryMeta meta;      // as in launch_prep_coarse, one handle (cand_off null: not wanted)
+    QueryMeta meta;      // as in launch_prep_coarse (cand_off null: not wanted)
 };
 hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &m, hipStream_t s);
 struct SplitGemmArgs {
