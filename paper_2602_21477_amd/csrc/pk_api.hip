@@ -1795,7 +1795,10 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
 
     std::vector<uint32_t> cnt((size_t)cfg->nlist, 0);
     if (n > 0) {
-        // one block of scratch: every vector's best (score, list), the assignment, counters, the operands of one chunk
+        // Scratch: the assignment and the counters, which the rows are scattered by, and what the assignment is made with
+        // (every vector's best (score, list), the operands of one chunk).  The latter is over before the first row is
+        // written: it lies where the rows will, if there is room for it (mapping and unmapping 100 MB takes 0.3 ms, a
+        // seventh of the build of 300 000 x 1024).
         const int64_t chunk = std::min<int64_t>(kAssignChunk, n);
         char *scr = nullptr;
         Carver c{nullptr, 0};
@@ -1803,19 +1806,29 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
         int32_t *d_assign = nullptr;
         uint32_t *d_cnt = nullptr;
         AssignScratch as{};
-        auto lay = [&](char *at) {
+        auto lay_kept = [&](char *at) {
             c = Carver{at, 0};
-            d_best = c.take<unsigned long long>((size_t)n);
             d_assign = c.take<int32_t>((size_t)n);
             d_cnt = c.take<uint32_t>((size_t)cfg->nlist * 2);
+        };
+        auto lay_passing = [&](char *at, size_t from) {
+            c = Carver{at, from};
+            d_best = c.take<unsigned long long>((size_t)n);
             as.lay(c, n, chunk, x.nlist_pad, x.rb32);
         };
-        lay(nullptr);
-        if (hipMalloc(reinterpret_cast<void **>(&scr), c.off + 256) != hipSuccess) {
+        lay_kept(nullptr);
+        const size_t kept = c.off;
+        lay_passing(nullptr, 0);
+        const size_t rows_at = round_up(reinterpret_cast<uintptr_t>(D.arenas[0].vec), 256) - reinterpret_cast<uintptr_t>(D.arenas[0].vec);
+        const bool in_arena = rows_at + c.off + 256 <= (size_t)D.arenas[0].npages * x.P * x.row_bytes;
+        lay_passing(nullptr, kept);
+        if (hipMalloc(reinterpret_cast<void **>(&scr), (in_arena ? kept : c.off) + 256) != hipSuccess) {
             (void)hipGetLastError();
             return fail(PK_ERR_NOMEM);
         }
-        lay(scr);
+        lay_kept(scr);
+        if (in_arena) lay_passing(D.arenas[0].vec + rows_at, 0);
+        else lay_passing(scr, kept);
         auto fail2 = [&](int code) {
             (void)hipStreamSynchronize(s);
             (void)hipFree(scr);
