@@ -215,6 +215,7 @@ struct Plan {
     uint64_t mins;         // dense: best keys of every 16 values (0: not written)
     uint32_t rescues;      // overflowed queries of the call that have a region to be scored again into (0: none can overflow)
     bool need_coarse, need_fine, f16;
+    bool fold;        // the centroid kernel makes the queries' padded copies and norms (no preparation launch)
     bool raw_queries; // the coarse step reads the caller's query rows directly (no preparation launch)
     bool stream_rows; // the rows are read past the caches
     bool halves_first; // the coarse step's preparation also makes the half-precision copy of the queries
@@ -577,6 +578,13 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
             p.mins = width > kReadOnce ? values / 16 : 0;
         }
     }
+    // Other rows (padding, or the norms of L2): the same kernel reads them as they are too and makes the copies and norms on the
+    // side, unless the GEMM wants them first or the chunked selection, which adds no norm.  A whole search of 1 query with the
+    // preparation as launches of its own and without: 100 000 x 130 fp16 L2 33.2 and 29.4 us, 100 000 x 100 fp32 33.7 and 30.6;
+    // of 1024 queries 75.6 and 75.1, 81.6 and 80.2 (nowhere slower from 1 to 4096 queries, 16 to 1024 lists).
+    p.fold = need_coarse && !worst && !p.raw_queries && nlist_hi <= kDenseSelectMax && tunables().densesel;
+    for (int a = 0; a < nh && p.fold; ++a)
+        if (coarse_by_gemm(qlo[a + 1] - qlo[a], hs[a])) p.fold = false;
     p.halves_first = need_coarse && need_fine && p.f16;
     // few lists, pairs and tiles: the threshold kernel's workgroups lay out slots and tiles as well (see wl_spread)
     p.wl_small = (uint64_t)nh * (uint64_t)nlist_hi <= kWlSmallLists && (uint64_t)nq * (uint64_t)nprobe <= 16384 && tiles <= 65536;
@@ -705,7 +713,7 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
     qm.nclear = p.need_fine ? 2u * (uint32_t)p.nh * (uint32_t)p.nlist_max + 2u : 0u; // and what lies behind them
     // small segments: one launch of the centroid kernel for all of them
     CentroidArgs ca{};
-    if (p.halves_first && !p.raw_queries) {
+    if (p.halves_first && !p.raw_queries && !p.fold) {
         // one launch prepares both copies, the coarse step's and the half-precision one that the scan reads
         SplitRowsArgs sr{};
         sr.x = q;
@@ -726,10 +734,24 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
         ca.qs = reinterpret_cast<const char *>(q);
         ca.qnorm = nullptr;
         ca.meta = qm;
+        ca.d = own->cfg.d;
         if (p.halves_first) { // (inner product: no norms)
             ca.halves = p.qs;
             ca.half_bytes = own->row_bytes;
-            ca.d = own->cfg.d;
+        }
+    } else if (p.fold) {
+        // the centroid kernel reads the caller's rows and makes the padded copies and the norms on the side
+        const bool l2 = own->cfg.metric == PK_METRIC_L2;
+        ca.qs = reinterpret_cast<const char *>(q);
+        ca.d = own->cfg.d;
+        ca.raw = (ca.d & 3) == 0 && (reinterpret_cast<uintptr_t>(q) & 15) == 0 ? kRawVec : kRawAny;
+        ca.meta = qm;
+        if (l2) ca.norm = p.qn32;
+        if (p.need_fine && !p.f16) ca.rows = p.qs32;
+        if (p.need_fine && p.f16) {
+            ca.halves = p.qs;
+            ca.half_bytes = own->row_bytes;
+            if (l2) ca.half_norm = p.qn;
         }
     } else {
         PK_HIP(launch_prep_coarse(q, p.nq, own->cfg.d, own->rb32, p.qs32, p.qn32, qm, m, s));
@@ -784,18 +806,19 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
         PK_HIP(launch_gemm_scores(g, s));
     }
     if (p.nlist_max <= kDenseSelectMax && tunables().densesel) {
+        const float *const add = p.fold && own->cfg.metric == PK_METRIC_L2 ? p.qn32 : nullptr;
         if (counted && p.need_fine) {
             // the selection's workgroups go on to count their queries' pairs and lay out the sample
             WorklistArgs w;
             SampleArgs sm;
             fill_worklist_args(p, own, w, sm);
             PK_HIP(launch_select_dense(p.S, p.cand_off, p.cand_cnt, (uint32_t)p.nlist_max, own->cfg.metric, p.nprobe, p.nq,
-                                       p.probes, s, &w, &sm, &m));
+                                       p.probes, s, &w, &sm, &m, add));
             *counted = true;
             return PK_OK;
         }
         PK_HIP(launch_select_dense(p.S, p.cand_off, p.cand_cnt, (uint32_t)p.nlist_max, own->cfg.metric, p.nprobe, p.nq,
-                                   p.probes, s));
+                                   p.probes, s, nullptr, nullptr, nullptr, add));
         return PK_OK;
     }
     SelectArgs se{};

@@ -459,10 +459,15 @@ struct CentroidArgs {
     //   atomicMin (top-1 assignment of inserts; best[] must hold ~0 on entry).
     QueryMeta meta;
     unsigned long long *best;
-    //   halves != null (with meta): the rows of the segment are also written rounded to half precision, zero padded to half_bytes.
-    char *halves;
-    int half_bytes, d;
+    //   raw (with meta): qs are the caller's dense rows of d floats; under L2 the scores are written without the query's own
+    //   norm (kRawVec: rows of whole 16-byte pieces);
+    //   rows, norm: the fp32 rows, zero padded to row_bytes, and their squared norms are written too; halves, half_norm: the
+    //   same of the rows rounded to half precision, padded to half_bytes (each of them, or null).
+    int raw, d, half_bytes;
+    char *rows, *halves;
+    float *norm, *half_norm;
 };
+enum { kRawNot, kRawVec, kRawAny };
 hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hipStream_t s);
 // Of the rows (of one handle) whose best two values are near, as the split GEMM left them, the best by the centroid kernel.
 // (Arguments of their own: the other launches' would be a line longer, 0.3 us of a search of one query.)
@@ -561,10 +566,11 @@ hipError_t launch_tau(const SampleArgs &a, hipStream_t s, const WorklistArgs *wa
 hipError_t launch_sample_tau(const ScanArgs &a, const SampleArgs &sm, const WorklistArgs &wa, const MultiArgs &ma, int grid,
                              hipStream_t s);
 // wa / sm / ma given: the selection's workgroups also do launch_worklist_count's work for their queries, or with wa->width
-// the whole work list (a.slot_query and slot_out then have wa->cap entries per list, a.scalars' first two words are zero)
+// the whole work list (a.slot_query and slot_out then have wa->cap entries per list, a.scalars' first two words are zero);
+// add: the scores (L2) lack the query's squared norm
 hipError_t launch_select_dense(const float *vals, const uint32_t *qoff, const uint32_t *qcnt, uint32_t max_cnt, int metric,
                                int K, int64_t nq, int32_t *probes, hipStream_t s, const WorklistArgs *wa = nullptr,
-                               const SampleArgs *sm = nullptr, const MultiArgs *ma = nullptr);
+                               const SampleArgs *sm = nullptr, const MultiArgs *ma = nullptr, const float *add = nullptr);
 
 // dense coarse scoring on the matrix cores (large query batches, build)
 struct GemmArgs {

@@ -853,6 +853,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 
 // ------------------------------------------------------------------ centroid scoring, small batches
 
+// Four floats of a dense row of d from column `col` on (kRawVec: d a multiple of 4, rows aligned): the load, unconditional and
+// past the row's end from its last floats, and the zeros behind the end, which wait for the load and go in when it is used.
+template <int RAW>
+__device__ __forceinline__ u32x4 raw_load(const char *row, int col, int d)
+{
+    const uint32_t *const x = reinterpret_cast<const uint32_t *>(row);
+    if constexpr (RAW == kRawVec) return *reinterpret_cast<const u32x4 *>(x + (col < d ? col : d - 4));
+    u32x4 v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = x[col + j < d ? col + j : d - 1];
+    return v;
+}
+__device__ __forceinline__ u32x4 raw_zeros(u32x4 v, int col, int d)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = col + j < d ? v[j] : 0u;
+    return v;
+}
+
+// The copies of one query that the fine step reads and their norms, by one wave: what prep_row (pk_worklist.hip) makes, in the
+// same order of summation.
+__device__ __forceinline__ void copy_query(const CentroidArgs &a, uint32_t q, int lane)
+{
+    const float *const src = reinterpret_cast<const float *>(a.qs) + (size_t)q * a.d;
+    const int n32 = a.row_bytes / 4, n16 = a.halves ? a.half_bytes / 2 : 0, n = n32 > n16 ? n32 : n16;
+    float sum[4] = {}, sum16[4] = {};
+    for (int i0 = lane; i0 < n; i0 += 256) {
+        float v[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v[w] = src[i0 + 64 * w < a.d ? i0 + 64 * w : a.d - 1];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const int i = i0 + 64 * w;
+            v[w] = i < a.d ? v[w] : 0.f;
+            if (a.rows && i < n32) reinterpret_cast<float *>(a.rows + (size_t)q * a.row_bytes)[i] = v[w];
+            sum[w] += v[w] * v[w];
+            const _Float16 h = (_Float16)v[w]; // round to nearest even
+            if (i < n16) reinterpret_cast<_Float16 *>(a.halves + (size_t)q * a.half_bytes)[i] = h;
+            sum16[w] += (float)h * (float)h;
+        }
+    }
+    if (!a.norm && !a.half_norm) return; // (the same for the whole launch)
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+        for (int off = 32; off > 0; off >>= 1) {
+            sum[w] += __shfl_xor(sum[w], off);
+            sum16[w] += __shfl_xor(sum16[w], off);
+        }
+    if (lane == 0) {
+        if (a.norm) a.norm[q] = sum[0] + sum[1] + sum[2] + sum[3];
+        if (a.half_norm) a.half_norm[q] = sum16[0] + sum16[1] + sum16[2] + sum16[3];
+    }
+}
+
 // Coarse step (Section 2.2) for query segments too small to fill the GEMM's 128 x 128
 // tiles: inserts of a few vectors, search batches of tens of queries.  The whole centroid
 // table is a few MB, so latency, not bandwidth, sets the time: the work is cut fine.  A
@@ -862,7 +916,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // the four partial accumulators meet in LDS.  Output: out[query * stride + centroid].
 // NEAR: of 64 rows only those whose assignment is a near tie, 16 at a time, and only their best.  Usually there is none
 // and the workgroup is done after one look: of 2000 rows against 512 x 1024 a handful are near ties, 9.7 us.
-template <int MT, int WAVES, bool NEAR>
+// RAW: the queries are the caller's own rows, of any width and alignment; their padded copies and norms are made on the side.
+template <int MT, int WAVES, bool NEAR, int RAW>
 __device__ __forceinline__ void centroid_body(const CentroidArgs &a, const MultiArgs &m, [[maybe_unused]] const NearRowsArgs *nr)
 {
     __shared__ float s_red[WAVES][MT][4][64];
@@ -913,7 +968,8 @@ __device__ __forceinline__ void centroid_body(const CentroidArgs &a, const Multi
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const uint32_t slot = (uint32_t)(mt * 16 + ln);
-        qp[mt] = slot < qcnt ? a.qs + (size_t)row_of(slot) * row_bytes + lg * 16 : nullptr;
+        if constexpr (RAW != kRawNot) qp[mt] = a.qs + (size_t)(q0 + (slot < qcnt ? slot : 0u)) * (size_t)a.d * 4;
+        else qp[mt] = slot < qcnt ? a.qs + (size_t)row_of(slot) * row_bytes + lg * 16 : nullptr;
     }
     cb = local - qc * across;
     do { // (NEAR: every parts-th block of centroids, else one)
@@ -928,24 +984,32 @@ __device__ __forceinline__ void centroid_body(const CentroidArgs &a, const Multi
         xbuf[s4] = *reinterpret_cast<const u32x4 *>(xp + (size_t)(it) * kIterBytes + s4 * 64);    \
         _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                         \
         {                                                                                         \
-            qbuf[mt][s4] = u32x4{0u, 0u, 0u, 0u};                                                 \
-            if (mt < mt_used && qp[mt])                                                           \
-                qbuf[mt][s4] = *reinterpret_cast<const u32x4 *>(qp[mt] + (size_t)(it) * kIterBytes + s4 * 64); \
+            if constexpr (RAW != kRawNot) {                                                       \
+                if (mt < mt_used) qbuf[mt][s4] = raw_load<RAW>(qp[mt], (it) * 64 + s4 * 16 + lg * 4, a.d); \
+            } else {                                                                              \
+                qbuf[mt][s4] = u32x4{0u, 0u, 0u, 0u};                                             \
+                if (mt < mt_used && qp[mt])                                                       \
+                    qbuf[mt][s4] = *reinterpret_cast<const u32x4 *>(qp[mt] + (size_t)(it) * kIterBytes + s4 * 64); \
+            }                                                                                     \
         }                                                                                         \
     }
-#define PK_CCOMPUTE(xbuf, qbuf)                                                                   \
+#define PK_CCOMPUTE(xbuf, qbuf, it)                                                               \
     _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                             \
     {                                                                                             \
         if (mt < mt_used) {                                                                       \
-            _Pragma("unroll") for (int s4 = 0; s4 < 4; ++s4) mfma_step<PK_F32>(acc[mt], qbuf[mt][s4], xbuf[s4]); \
+            _Pragma("unroll") for (int s4 = 0; s4 < 4; ++s4)                                      \
+            {                                                                                     \
+                if constexpr (RAW != kRawNot) qbuf[mt][s4] = raw_zeros(qbuf[mt][s4], (it) * 64 + s4 * 16 + lg * 4, a.d); \
+                mfma_step<PK_F32>(acc[mt], qbuf[mt][s4], xbuf[s4]);                               \
+            }                                                                                     \
         }                                                                                         \
     }
     if (it0 < it1) { PK_CLOAD(xa, qa, it0) }
     for (int it = it0; it < it1; it += 2) {
         if (it + 1 < it1) { PK_CLOAD(xb, qb, it + 1) }
-        PK_CCOMPUTE(xa, qa)
+        PK_CCOMPUTE(xa, qa, it)
         if (it + 2 < it1) { PK_CLOAD(xa, qa, it + 2) }
-        if (it + 1 < it1) { PK_CCOMPUTE(xb, qb) }
+        if (it + 1 < it1) { PK_CCOMPUTE(xb, qb, it + 1) }
     }
 #undef PK_CLOAD
 #undef PK_CCOMPUTE
@@ -971,7 +1035,7 @@ __device__ __forceinline__ void centroid_body(const CentroidArgs &a, const Multi
         const uint32_t slot = (uint32_t)(mt * 16 + lg * 4 + i);
         if (slot >= qcnt || c >= (uint32_t)ix.nlist) continue;
         float v = partial_sum(mt);
-        if (a.metric == PK_METRIC_L2) v = fmaxf(cn - 2.f * v + a.qnorm[row_of(slot)], 0.f);
+        if (a.metric == PK_METRIC_L2) v = RAW != kRawNot ? cn - 2.f * v : fmaxf(cn - 2.f * v + a.qnorm[row_of(slot)], 0.f);
         if (!a.best) a.out[(size_t)(q0 + slot) * a.stride + c] = v;
     }
     if (a.best) {
@@ -1009,54 +1073,60 @@ __device__ __forceinline__ void centroid_body(const CentroidArgs &a, const Multi
             a.meta.cand_cnt[t] = (uint32_t)ix.nlist;
             a.meta.qagent[t] = (uint16_t)h;
         }
-        // (two elements a thread; the group's workgroups share its rows.  As a launch of its own 3.5 - 5 us)
-        if (a.halves)
-            for (uint32_t slot = cb - across; slot < qcnt; slot += across) {
-                const float *src = reinterpret_cast<const float *>(a.qs + (size_t)(q0 + slot) * row_bytes);
-                uint32_t *dst = reinterpret_cast<uint32_t *>(a.halves + (size_t)(q0 + slot) * a.half_bytes);
-                for (int i = tid; i < a.half_bytes / 4; i += blockDim.x) {
-                    const float x = 2 * i < a.d ? src[2 * i] : 0.f, y = 2 * i + 1 < a.d ? src[2 * i + 1] : 0.f; // (rounded to nearest even)
-                    dst[i] = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)x) | ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)y) << 16);
-                }
-            }
+        // The queries' copies: the group's workgroups share its rows, a wave each.  As a launch of its own 2 - 5 us.
+        if (a.rows || a.halves || a.norm)
+            for (uint32_t slot = cb - across + (uint32_t)wave * across; slot < qcnt; slot += across * (uint32_t)WAVES)
+                copy_query(a, q0 + slot, lane);
     }
 }
 
-template <int MT, int WAVES>
+template <int MT, int WAVES, int RAW>
 __global__ __launch_bounds__(WAVES * 64) void centroid_scores_kernel(CentroidArgs a, MultiArgs m)
 {
-    centroid_body<MT, WAVES, false>(a, m, nullptr);
+    centroid_body<MT, WAVES, false, RAW>(a, m, nullptr);
 }
 
 __global__ __launch_bounds__(256) void centroid_near_kernel(CentroidArgs a, MultiArgs m, NearRowsArgs nr)
 {
-    centroid_body<1, 4, true>(a, m, &nr);
+    centroid_body<1, 4, true, kRawNot>(a, m, &nr);
 }
 
 // ------------------------------------------------------------------------ host side
 
-template <int MT>
+template <int MT, int RAW>
 static hipError_t launch_centroid_mt(const CentroidArgs &a, const MultiArgs &m, hipStream_t s)
 {
     static_assert(MT >= 1, "");
     if (MT == 1 && a.row_bytes / kIterBytes >= 16) {
         // one group of queries over long rows: eight waves share the row, so that each has few slices in a row to wait for
-        hipLaunchKernelGGL((centroid_scores_kernel<1, 8>), dim3(a.blk[m.n]), dim3(512), 0, s, a, m);
+        hipLaunchKernelGGL((centroid_scores_kernel<1, 8, RAW>), dim3(a.blk[m.n]), dim3(512), 0, s, a, m);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((centroid_scores_kernel<MT, 4>), dim3(a.blk[m.n]), dim3(256), 0, s, a, m);
+    hipLaunchKernelGGL((centroid_scores_kernel<MT, 4, RAW>), dim3(a.blk[m.n]), dim3(256), 0, s, a, m);
     return hipGetLastError();
+}
+
+template <int RAW>
+static hipError_t launch_centroid_raw(const CentroidArgs &a, const MultiArgs &m, hipStream_t s)
+{
+    switch (a.chunk) {
+    case 16: return launch_centroid_mt<1, RAW>(a, m, s);
+    case 32: return launch_centroid_mt<2, RAW>(a, m, s);
+    case 48: return launch_centroid_mt<3, RAW>(a, m, s);
+    case 64: return launch_centroid_mt<4, RAW>(a, m, s);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hipStream_t s)
 {
     if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0) return hipErrorInvalidValue;
     if (a.blk[m.n] == 0) return hipSuccess;
-    switch (a.chunk) {
-    case 16: return launch_centroid_mt<1>(a, m, s);
-    case 32: return launch_centroid_mt<2>(a, m, s);
-    case 48: return launch_centroid_mt<3>(a, m, s);
-    case 64: return launch_centroid_mt<4>(a, m, s);
+    if (a.raw != kRawNot && (a.best || !a.meta.cand_off || a.d < 1 || a.d * 4 > a.row_bytes)) return hipErrorInvalidValue;
+    switch (a.raw) {
+    case kRawNot: return launch_centroid_raw<kRawNot>(a, m, s);
+    case kRawVec: return launch_centroid_raw<kRawVec>(a, m, s);
+    case kRawAny: return launch_centroid_raw<kRawAny>(a, m, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -198,7 +198,7 @@ static size_t dense_lds(uint32_t K, GoOn go_on)
 }
 template <int VPT, GoOn GO_ON>
 __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, const uint32_t *qoff, const uint32_t *qcnt,
-                                                           int metric, int K, int32_t *probes, WorklistArgs wa,
+                                                           const float *add, int metric, int K, int32_t *probes, WorklistArgs wa,
                                                            SampleArgs sm, MultiArgs ma)
 {
     __shared__ uint32_t s_w[4];
@@ -214,13 +214,16 @@ __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, co
     const uint32_t q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t n = qcnt[q];
     const float *v = vals + qoff[q];
+    const float own = add ? add[q] : 0.f;
     WlIndexView view{};
     if constexpr (COUNT) view = wl_index_view(wa, ma, q); // these loads are over by the time the count needs them
     uint32_t key[VPT];
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
         const uint32_t p = tid + 256u * j;
-        key[j] = p < n ? order_bits(v[p], metric) : 0xffffffffu;
+        float x = v[p < n ? p : 0u];
+        if (add) x = fmaxf(x + own, 0.f);
+        key[j] = p < n ? order_bits(x, metric) : 0xffffffffu;
     }
     if (tid == 0) s_n = 0;
     bool live[VPT];
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, co
 
 hipError_t launch_select_dense(const float *vals, const uint32_t *qoff, const uint32_t *qcnt, uint32_t max_cnt, int metric,
                                int K, int64_t nq, int32_t *probes, hipStream_t s, const WorklistArgs *wa, const SampleArgs *sm,
-                               const MultiArgs *ma)
+                               const MultiArgs *ma, const float *add)
 {
     if (nq <= 0) return hipSuccess;
     if (max_cnt > (uint32_t)kDenseSelectMax || K > PK_MAX_NPROBE) return hipErrorInvalidValue;
@@ -337,7 +340,7 @@ hipError_t launch_select_dense(const float *vals, const uint32_t *qoff, const ui
     auto go = [&](auto vpt) {
         constexpr int VPT = decltype(vpt)::value;
         auto run = [&](auto kernel, GoOn go_on) {
-            hipLaunchKernelGGL(kernel, g, b, dense_lds((uint32_t)K, go_on), s, vals, qoff, qcnt, metric, K, probes, wa ? *wa : w0, wa ? *sm : s0, wa ? *ma : m0);
+            hipLaunchKernelGGL(kernel, g, b, dense_lds((uint32_t)K, go_on), s, vals, qoff, qcnt, add, metric, K, probes, wa ? *wa : w0, wa ? *sm : s0, wa ? *ma : m0);
         };
         if (!wa) run(select_dense_kernel<VPT, kStop>, kStop);
         else if (wa->width == 0) run(select_dense_kernel<VPT, kCount>, kCount);

@@ -469,3 +469,46 @@ def test_values_written_whole_give_the_rows_of_the_gated_scan(gpu_device, n, d, 
     finally:
         ix.close()
         other.close()
+
+
+@pytest.mark.parametrize("storage", [F32, F16])
+@pytest.mark.parametrize("metric", [IP, L2])
+@pytest.mark.parametrize("d,nlist,nq", [
+    (1, 3, 1), (63, 40, 17), (64, 130, 49), (65, 16, 200), (100, 40, 64), (130, 300, 33), (1030, 70, 12)])
+def test_queries_copied_beside_the_coarse_step(gpu_device, storage, metric, d, nlist, nq):
+    """Small batches have their padded copies and norms made by the centroid kernel: the probes are the best by 64 bits, and
+    the rows those of a scan of the same probes, which prepares the queries by itself.  Of any alignment, over two memories."""
+    g = torch.Generator(device="cuda").manual_seed(d * nlist + nq)
+    n, nprobe, k = 20 * nlist, min(3, nlist // 2 + 1), 10
+    cent = torch.randn((nlist, d), device="cuda", generator=g)
+    x = torch.randn((n, d), device="cuda", generator=g)
+    flat = torch.randn(nq * d + 1, device="cuda", generator=g)
+    q = flat[:-1].view(nq, d)
+    off = torch.empty_like(flat)[1:].view(nq, d)  # 4 bytes from any wider boundary
+    off.copy_(q)
+    ix, other = (B.Index(c, rows, metric=metric, storage=storage) for c, rows in ((cent, x), (cent[: nlist // 2 + 1].contiguous(), x)))
+    try:
+        probes = ix.coarse(q, nprobe)
+        c64, q64 = cent.double(), q.double()
+        score = q64 @ c64.T if metric == IP else -((q64 ** 2).sum(1)[:, None] - 2 * q64 @ c64.T + (c64 ** 2).sum(1))
+        # fp32 sums of d products, each term rounded once and added in some order: d + 4 halves of an ulp of the sum of magnitudes
+        tol = (d + 4) * 2.0 ** -24 * ((q64.abs() @ c64.abs().T).max() * 2 + (q64 ** 2).sum(1).max() + (c64 ** 2).sum(1).max())
+        got = score.gather(1, probes.long())
+        best = score.topk(nprobe, 1).values
+        assert (got.sort(1, descending=True).values >= best - 2 * tol).all()
+        ids, vals = ix.search(q, k, nprobe)
+        want = ix.scan_probes(q, k, probes)
+        assert torch.equal(ids, want[0]) and torch.equal(vals, want[1])
+        cut = nq // 3
+        both = B.search_multi([ix, other], [0, cut, nq], q, k, nprobe)
+        if cut:
+            assert torch.equal(both[0][:cut], ids[:cut]) and torch.equal(both[1][:cut], vals[:cut])
+        rest = other.search(q[cut:].contiguous(), k, nprobe)
+        assert torch.equal(both[0][cut:], rest[0]) and torch.equal(both[1][cut:], rest[1])
+        if d % 64:  # (rows that are padded)
+            a, b = ix.search(off, k, nprobe), B.search_multi([ix, other], [0, cut, nq], off, k, nprobe)
+            assert torch.equal(a[0], ids) and torch.equal(a[1], vals)
+            assert torch.equal(b[0], both[0]) and torch.equal(b[1], both[1])
+    finally:
+        ix.close()
+        other.close()
