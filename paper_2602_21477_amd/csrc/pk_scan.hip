@@ -23,6 +23,8 @@
 //                   buffered), so LDS use is independent of the row length and up to 128
 //                   slots fit: for lists probed by many queries of the batch and for rows
 //                   too wide for the first kernel to keep several workgroups per CU.
+// What becomes of the values: those that pass a query's gate are emitted (large calls: most of them are never written), or all
+// are written, which needs no gate and hence neither sample nor thresholds (calls whose values are few; launches bound these).
 // sample_tau_kernel is scan_kernel's one-query form for the threshold sample of a small batch,
 // with the thresholds and the work-list layout in the same launch (Section 3.3: small
 // batches are bound by launches).
