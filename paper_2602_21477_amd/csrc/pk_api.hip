@@ -1818,7 +1818,7 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
 
     std::vector<uint32_t> cnt((size_t)cfg->nlist, 0);
     if (n > 0) {
-        // Scratch: the assignment and the rows' places, which they are scattered by, and what the assignment is made with
+        // Scratch: the rows' places, which they are scattered by, and the assignment and what it is made with
         // (every vector's best (score, list), the operands of one chunk).  The latter is over before the first row is
         // written: it lies where the rows will, if there is room for it (mapping and unmapping 100 MB takes 0.3 ms, a
         // seventh of the build of 300 000 x 1024).
@@ -1831,13 +1831,13 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
         AssignScratch as{};
         auto lay_kept = [&](char *at) {
             c = Carver{at, 0};
-            d_assign = c.take<int32_t>((size_t)n);
             d_slots = c.take<uint32_t>((size_t)n);
             d_cnt = c.take<uint32_t>((size_t)cfg->nlist);
         };
         auto lay_passing = [&](char *at, size_t from) {
             c = Carver{at, from};
             d_best = c.take<unsigned long long>((size_t)n);
+            d_assign = c.take<int32_t>((size_t)n);
             as.lay(c, n, chunk, x.nlist_pad, x.rb32);
         };
         lay_kept(nullptr);
@@ -1882,7 +1882,8 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
             hipMemcpyAsync(D.main_pages, mpages.data(), mpages.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
             hipMemcpyAsync(D.list_len, cnt.data(), cnt.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
             hipMemcpyAsync(D.ctr, &used32, 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-            launch_scatter_build(ix->dev, vectors, ids, d_assign, d_slots, n, 0, x.row_bytes / (cfg->storage == PK_F16 ? 128 : 256), s) != hipSuccess ||
+            launch_build_places(ix->dev, d_assign, n, d_slots, s) != hipSuccess ||
+            launch_scatter_build(ix->dev, vectors, ids, d_slots, n, 0, x.row_bytes / (cfg->storage == PK_F16 ? 128 : 256), s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             return fail2(PK_ERR_HIP);
         (void)hipFree(scr);

@@ -686,8 +686,9 @@ hipError_t launch_gemm_split_listed(const SplitGemmArgs &a, int num_cu, hipStrea
 // place of its own for every row among those of its list
 hipError_t launch_lists_of_best(const unsigned long long *best, int64_t n, int nlist, int32_t *assign, uint32_t *cnt, uint32_t *slots, hipStream_t s);
 constexpr int kLdsLists = 8192; // most lists that a workgroup counts in LDS (32 KB)
-hipError_t launch_scatter_build(const DevIndex *ix, const float *x, const int64_t *ids, const int32_t *assign, const uint32_t *slots,
-                                int64_t n, int64_t id0, int pieces, hipStream_t s); // (pieces: of 64 elements in a stored row)
+hipError_t launch_build_places(const DevIndex *ix, const int32_t *assign, int64_t n, uint32_t *slots, hipStream_t s);
+hipError_t launch_scatter_build(const DevIndex *ix, const float *x, const int64_t *ids, const uint32_t *rows_at, int64_t n, int64_t id0,
+                                int pieces, hipStream_t s); // (pieces: of 64 elements in a stored row)
 hipError_t launch_store_centroids(const float *c, int nlist, int d, int dpad32, int nlist_pad, int metric,
                                   float *cent, float *cnorm, hipStream_t s);
 // Removes the rows whose id is among ids[0..m), m <= kDeleteChunk.  One pass removes at most kDeleteChunk
