@@ -607,8 +607,13 @@ hipError_t launch_near_ties(const NearTiesArgs &a, int num_cu, hipStream_t s);
 // Two values of a row closer than this are told apart by the fp32 kernel.  The fp32 sum of ld products, two at a time,
 // is off by about 2^-25 sqrt(ld / 2) of |x| |c| in one standard deviation (measured: 1e-6 |x|^2 between two L2 values
 // at 768 elements), the split's by a third of it; 2^-21 sqrt(ld) is twenty of them.
+// Squared lengths below kTinySquare have lost what makes them a bound (elements below 2^-63 leave nothing in them, while the
+// scaled products of such rows still tell lists apart): nothing is further apart than that, and the fp32 kernel decides.
+// Above it the squares that were lost are 2^-24 of the sum at most, whatever the row's width.
+constexpr float kTinySquare = 8.07793567e-28f; // 2^-90
 __device__ __forceinline__ float near_margin(int ld, int metric, float qn, float cmax)
 {
+    if (metric == PK_METRIC_L2 ? qn + cmax < kTinySquare : qn < kTinySquare || cmax < kTinySquare) return INFINITY;
     return 4.76837158e-7f * sqrtf((float)ld) * (metric == PK_METRIC_L2 ? qn + cmax : sqrtf(qn) * sqrtf(cmax));
 }
 

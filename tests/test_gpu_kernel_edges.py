@@ -1,5 +1,7 @@
 """Edges of single kernels and of the rules that choose between them: tile remainders, the smallest and
 largest sizes of a path, and the sizes on both sides of a dispatch."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -390,6 +392,32 @@ def test_inserts_around_the_sizes_where_their_path_changes(gpu_device, metric, s
         assert ix.list_lengths().tolist() == [len(v) for v in members]
         for l in np.argsort([-len(v) for v in members])[:12]:
             assert ix.list_ids(int(l)).cpu().numpy().tolist() == members[l]
+    finally:
+        ix.close()
+
+
+@pytest.mark.parametrize("of_rows,of_lists", [(1e-24, 1.0), (1.0, 1e-24), (1e-12, 1e-12), (1e-24, 1e-10), (1e-19, 1.0)])
+def test_assignment_of_rows_whose_squared_length_is_nothing(gpu_device, of_rows, of_lists):
+    """Inner product, rows or lists so short that their squared lengths underflow: lists that lie closer together than half
+    precision can tell are still told apart as fp32 sums do, by builds and by large inserts."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    n, d, nlist = 16384, 64, 256
+    half = torch.randn((nlist // 2, d), device="cuda", generator=g)
+    cent = torch.stack([half, half * (1 + 2.0 ** -12 * torch.randn(half.shape, device="cuda", generator=g))], 1).reshape(nlist, d) * of_lists
+    # (whole numbers: what half precision leaves out of the products is then all the lists')
+    x = torch.randint(-8, 9, (n, d), device="cuda", generator=g) * 2.0 ** round(math.log2(of_rows))
+    ix = B.Index(cent, x, metric=IP, insert_reserve=n)
+    try:
+        built = torch.empty(n, dtype=torch.int64, device="cuda")
+        for l in np.nonzero(ix.list_lengths())[0].tolist():
+            built[ix.list_ids(l)] = l
+        inserted = ix.insert(x, want_lists=True).long()
+        score = x.double() @ cent.double().T
+        # as in fp32 sums of d products, and (the products themselves may be below fp32's smallest) d of those
+        tol = (d + 4) * 2.0 ** -24 * (x.double().abs() @ cent.double().abs().T).amax(1) + d * 2.0 ** -149
+        for lists in (built, inserted):
+            short = score.amax(1) - score.gather(1, lists[:, None])[:, 0]
+            assert (short <= 2 * tol).all(), (short / tol).max()
     finally:
         ix.close()
 
