@@ -276,6 +276,11 @@ int pk_workspace_reserve(pk_index *const *handles, int32_t n_handles, int64_t nq
  * a small one forces queries down the rescoring path. */
 int pk_index_set_emit_cap(pk_index *index, int32_t entries);
 
+/* Test seam: most tiles that the work list of later searches on this handle has room for (0 = the default, what
+ * the lists' lengths can ask for at most).  A search that needs more scans nothing: its rows are all padding, and
+ * pk_stats.device_error has its 4 set. */
+int pk_index_set_tile_cap(pk_index *index, int32_t tiles);
+
 /*
  * pk_search for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and

@@ -94,6 +94,7 @@ struct pk_index {
     size_t ws_bytes;
     int64_t ws_grows;       // times the workspace was (re)allocated since the build
     int32_t emit_cap;       // entries of a query's emission region set by the caller (0: by k)
+    int32_t tile_cap;       // most tiles of a work list, set by the caller (0: by the lists' lengths)
     // staging of scope-union searches (replicated queries, per-handle results); grow-only
     char *ubuf;
     size_t ubuf_bytes;
@@ -595,7 +596,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     // Nor does it take a launch to be ready for a query that would have to emit a quarter of all its rows.
     if (need_fine && !p.dense && nq > kRoomyBatch && p.ecap <= kRescueFrom && 4ull * p.ecap < round_up(wmax, 16))
         p.rescues = (uint32_t)std::min<uint64_t>((uint64_t)nq * p.span * 4 / (kRescueCap * 8), kRescueRegions);
-    p.tile_cap = (uint32_t)tiles;
+    p.tile_cap = own->tile_cap > 0 ? (uint32_t)std::min<uint64_t>(tiles, (uint64_t)own->tile_cap) : (uint32_t)tiles;
     if (p.dense) {
         Plan gated = p;
         gated.dense = false;
@@ -884,6 +885,8 @@ int run_dense(const Plan &p, const MultiArgs &m, pk_index *own, int64_t *out_ids
     f.vals = sa.out;
     f.mins = p.block_min;
     f.width = p.width;
+    f.ntiles = sa.ntiles;
+    f.tile_cap = p.tile_cap;
     PK_HIP(launch_select_final(f, m, p.nq, s));
     if (timed) PK_TRY(mark(own, s));
     return PK_OK;
@@ -2402,6 +2405,14 @@ int pk_index_set_emit_cap(pk_index *ix, int32_t entries)
     if (!live(ix)) return PK_ERR_BAD_HANDLE;
     if (entries < 0 || entries > (1 << 20)) return PK_ERR_INVALID_ARG;
     ix->emit_cap = entries;
+    return PK_OK;
+}
+
+int pk_index_set_tile_cap(pk_index *ix, int32_t tiles)
+{
+    if (!live(ix)) return PK_ERR_BAD_HANDLE;
+    if (tiles < 0) return PK_ERR_INVALID_ARG;
+    ix->tile_cap = tiles;
     return PK_OK;
 }
 

@@ -422,6 +422,8 @@ struct FinalArgs {
     const float *vals;
     const uint32_t *mins;             // best key of every 16 values: where width is more than kReadOnce
     uint32_t width;
+    const uint32_t *ntiles;           // with vals: more tiles than tile_cap, and nothing was scanned
+    uint32_t tile_cap;
 };
 constexpr uint32_t kReadOnce = 8192; // values that the workgroup of a final selection holds in registers
 constexpr uint32_t kRescueCap = 4096;    // keys per rescue region: what the final selection takes in registers

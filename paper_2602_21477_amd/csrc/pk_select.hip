@@ -857,6 +857,8 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     // of a short region (the entry exists whatever the count; it is used only if it is below it), the
     // query's rows of the candidate layout, its index
     uint32_t cnt_q = DENSE ? a.pair_off[(size_t)q * (a.nprobe + 1) + a.nprobe] : a.qcnt[q];
+    [[maybe_unused]] bool refused = false; // the work list had no room: no query has values (cannot happen while the host bounds hold)
+    if constexpr (DENSE) refused = *a.ntiles > a.tile_cap;
     u64 early = !DENSE && threadIdx.x < a.ecap ? a.keys[region + threadIdx.x] : kMaxKey;
     const DevIndex &qix = *h.ix[a.qagent[q]];
     for (int r = threadIdx.x; r <= a.nprobe; r += blockDim.x) {
@@ -876,13 +878,14 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
     uint32_t st_max = 0, st_over = 0;
     if (blockIdx.x == 0) {
         for (uint32_t t = threadIdx.x; t < gridDim.x; t += blockDim.x) {
-            const uint32_t all = a.pair_off[(size_t)t * (a.nprobe + 1) + a.nprobe], c = DENSE ? all : a.qcnt[t];
+            const uint32_t all = a.pair_off[(size_t)t * (a.nprobe + 1) + a.nprobe], c = DENSE ? (refused ? 0u : all) : a.qcnt[t];
             st_cand += all;
             st_emit += c;
             st_max = c > st_max ? c : st_max;
             st_over += !DENSE && c > a.ecap ? 1u : 0u;
         }
     }
+    if (DENSE && refused) cnt_q = 0u;
     Selector sel;
     sel.init(keys, &s_cnt, a.K, cap);
     bool overflow = !DENSE && cnt_q > a.ecap; // the region lost candidates: select by rescoring the query's rows

@@ -499,6 +499,32 @@ def test_values_written_whole_give_the_rows_of_the_gated_scan(gpu_device, n, d, 
         other.close()
 
 
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("d,nq,k,metric", [(32, 1, 10, IP), (64, 40, 200, L2), (100, 300, 10, IP), (1100, 6, 5, L2)])
+def test_a_work_list_without_room_scans_nothing(gpu_device, gated, d, nq, k, metric):
+    """Whichever way the values go: padding for every query and the sticky flag, and the same rows as before once there is room
+    again."""
+    g = torch.Generator(device="cuda").manual_seed(d)
+    n, nlist, nprobe = 6000, 12, 5
+    x = torch.randn((n, d), device="cuda", generator=g)
+    q = torch.randn((nq, d), device="cuda", generator=g)
+    ix = B.Index(x[:nlist].clone(), x, metric=metric)
+    try:
+        B.pk_index_set_emit_cap(ix.handle, 4096 if gated else 0)
+        ids, dist = ix.search(q, k, nprobe)
+        assert ix.stats().device_error == 0 and int(ids.min()) >= 0
+        for cap in (1, 4):
+            B.pk_index_set_tile_cap(ix.handle, cap)
+            none, worst = ix.search(q, k, nprobe)
+            assert (none == -1).all() and torch.isinf(worst).all()
+            assert ix.stats().device_error == 4
+        B.pk_index_set_tile_cap(ix.handle, 0)
+        again = ix.search(q, k, nprobe)
+        assert torch.equal(again[0], ids) and torch.equal(again[1], dist)
+    finally:
+        ix.close()
+
+
 @pytest.mark.parametrize("storage", [F32, F16])
 @pytest.mark.parametrize("metric", [IP, L2])
 @pytest.mark.parametrize("d,nlist,nq", [
