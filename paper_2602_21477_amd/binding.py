@@ -23,7 +23,7 @@ PK_ERR_INVALID_ARG, PK_ERR_BAD_HANDLE, PK_ERR_DIM_MISMATCH, PK_ERR_NOMEM, PK_ERR
 PK_ERR_WORKSPACE = -7
 PK_NOALLOC_WORKSPACE_BYTES = 64 << 20
 
-EXPORTS = ["pk_workspace_reserve", "pk_index_set_emit_cap", "pk_index_set_tile_cap", "pk_search_noalloc", "pk_search_noalloc_bytes", "pk_search_levels", "pk_search_union", "pk_insert_multi", "pk_delete", "pk_index_split", "pk_index_centroids", "pk_list_ids", "pk_arena_bytes", "pk_index_build", "pk_index_add_arena", "pk_index_compact", "pk_kmeans", "pk_insert", "pk_insert_assigned", "pk_search",
+EXPORTS = ["pk_workspace_reserve", "pk_index_set_emit_cap", "pk_index_set_tile_cap", "pk_index_set_values_cap", "pk_search_noalloc", "pk_search_noalloc_bytes", "pk_search_levels", "pk_search_union", "pk_insert_multi", "pk_delete", "pk_index_split", "pk_index_centroids", "pk_list_ids", "pk_arena_bytes", "pk_index_build", "pk_index_add_arena", "pk_index_compact", "pk_kmeans", "pk_insert", "pk_insert_assigned", "pk_search",
            "pk_search_multi", "pk_coarse", "pk_scan_probes", "pk_index_stats", "pk_list_lengths", "pk_profile_begin",
            "pk_profile_end", "pk_index_free", "pk_strerror"]
 
@@ -81,6 +81,7 @@ def lib():
         L.pk_workspace_reserve.argtypes = [C.POINTER(vp), i32, i64, i32, i32, i64, vp]
         L.pk_index_set_emit_cap.argtypes = [vp, i32]
         L.pk_index_set_tile_cap.argtypes = [vp, i32]
+        L.pk_index_set_values_cap.argtypes = [vp, i64]
         L.pk_search_noalloc.argtypes = [vp, vp, i64, i32, i32, vp, vp, vp]
         L.pk_search_noalloc_bytes.restype = C.c_size_t
         L.pk_search_noalloc_bytes.argtypes = [vp, i64, i32, i32]
@@ -218,6 +219,10 @@ def pk_index_set_emit_cap(handle: int, entries: int):
 
 def pk_index_set_tile_cap(handle: int, tiles: int):
     _check(lib().pk_index_set_tile_cap(handle, int(tiles)), "pk_index_set_tile_cap")
+
+
+def pk_index_set_values_cap(handle: int, nbytes: int):
+    _check(lib().pk_index_set_values_cap(handle, int(nbytes)), "pk_index_set_values_cap")
 
 
 def pk_search_noalloc(handle: int, queries, k: int, nprobe: int, out_ids, out_dist):

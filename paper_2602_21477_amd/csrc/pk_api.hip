@@ -92,7 +92,13 @@ struct pk_index {
     // library-owned workspace
     char *ws;
     size_t ws_bytes;
-    int64_t ws_grows;       // times the workspace was (re)allocated since the build
+    // values of searches that write them whole, and the slots that go with them: a buffer of its own, so that a captured
+    // search (which is gated) keeps its workspace when this one grows, and a search that cannot have it goes on without
+    char *vals;
+    size_t vals_bytes;
+    size_t vals_refused;    // a size that the device had no room for (0: none): not asked for again until the next reservation
+    int64_t vals_cap;       // most bytes of it, set by the caller (0: what the device gives)
+    int64_t ws_grows;       // times the workspace (either buffer) was (re)allocated since the build, once per call
     int32_t emit_cap;       // entries of a query's emission region set by the caller (0: by k)
     int32_t tile_cap;       // most tiles of a work list, set by the caller (0: by the lists' lengths)
     // staging of scope-union searches (replicated queries, per-handle results); grow-only
@@ -181,6 +187,31 @@ int ensure_ws(pk_index *ix, size_t bytes, hipStream_t s)
     return PK_OK;
 }
 
+// PK_ERR_NOMEM: the buffer for whole values cannot be had, the search goes through sample and gate.  spare: what a new
+// buffer gets beyond that, as its size follows the lists' lengths.  once: the call has counted a growth already.
+int ensure_vals(pk_index *ix, size_t bytes, size_t spare, hipStream_t s, bool once)
+{
+    if (ix->vals_cap > 0 && bytes > (size_t)ix->vals_cap) return PK_ERR_NOMEM;
+    if (bytes <= ix->vals_bytes) return PK_OK;
+    if (ix->vals_refused > 0 && bytes >= ix->vals_refused) return PK_ERR_NOMEM;
+    PK_HIP(hipStreamSynchronize(s)); // earlier work on this handle's stream may still use the old buffer
+    if (ix->vals) PK_HIP(hipFree(ix->vals));
+    ix->vals = nullptr;
+    ix->vals_bytes = 0;
+    size_t want = round_up(bytes + spare, 1 << 20);
+    if (ix->vals_cap > 0) want = std::min(want, (size_t)ix->vals_cap);
+    void *p = nullptr;
+    if (hipMalloc(&p, want) != hipSuccess) {
+        (void)hipGetLastError();
+        ix->vals_refused = bytes;
+        return PK_ERR_NOMEM;
+    }
+    ix->vals = static_cast<char *>(p);
+    ix->vals_bytes = want;
+    if (!once) ix->ws_grows += 1;
+    return PK_OK;
+}
+
 // Pages that `t` more vectors can open at most: one per touched list (its tail page may be
 // full) plus one per P vectors.
 uint64_t pages_for(const pk_index *ix, uint64_t t)
@@ -212,8 +243,8 @@ struct Plan {
     bool hot_rs; // the hot class is scored by the rows-in-registers kernel (tiles of kRrTileRows rows x up to kRrSlots slots)
     double avg_per_list; // queries per list on average (the largest over the handles of the call)
     uint32_t stride, ecap, tile_cap, span;
-    uint64_t cbuf_entries; // entries of all emission regions together (dense: half the values)
-    uint64_t mins;         // dense: best keys of every 16 values (0: not written)
+    uint64_t cbuf_entries; // entries of all emission regions together
+    uint64_t values, mins, slots; // dense: values of all queries, best keys of every 16 of them (0: not written), slots of all lists
     uint32_t rescues;      // overflowed queries of the call that have a region to be scored again into (0: none can overflow)
     bool need_coarse, need_fine, f16;
     bool fold;        // the centroid kernel makes the queries' padded copies and norms (no preparation launch)
@@ -228,16 +259,18 @@ struct Plan {
     float *qn32, *qn, *S, *svals, *tlo, *tinv;
     uint32_t *cand_off, *cand_cnt, *lcnt, *lstart, *lfill, *ltile, *lhtile, *pair_off, *slot_q, *slot_o, *scalars,
         *tau, *tcur, *hist, *ccnt, *sslot_q, *sslot_o, *block_min;
+    float *vals;
     uint16_t *qagent;
     Tile *tiles, *tiles_hot, *stiles;
     unsigned long long *cpartial, *cbuf;
     int32_t *probes;
-    size_t bytes;
+    size_t bytes, vbytes; // what the plan takes of the workspace, and (values > 0) of the buffer for whole values
     size_t need;    // what the workspace is made to hold: dense calls leave room for the same call through sample and gate
                     // (which is what it takes when it is captured)
 };
 
-void carve(Plan &p, char *base, const pk_index *own)
+// base: workspace, vbase: buffer for whole values (null: sizes only)
+void carve(Plan &p, char *base, char *vbase, const pk_index *own)
 {
     Carver c{base, 0};
     const size_t nq = (size_t)p.nq;
@@ -267,14 +300,20 @@ void carve(Plan &p, char *base, const pk_index *own)
         p.ltile = c.take<uint32_t>(nl);
         p.lhtile = c.take<uint32_t>(nl);
         p.pair_off = c.take<uint32_t>(nq * (p.nprobe + 1));
-        const size_t slots = std::max(nq * p.nprobe, nl * p.cap);
-        p.slot_q = c.take<uint32_t>(slots);
-        p.slot_o = c.take<uint32_t>(slots);
         p.tiles = c.take<Tile>((size_t)p.tile_cap + 1);
-        p.cbuf = c.take<unsigned long long>((size_t)p.cbuf_entries + 16);
-        p.block_min = p.mins > 0 ? c.take<uint32_t>((size_t)p.mins) : nullptr;
+    }
+    if (p.values > 0) {
+        Carver v{vbase, 0};
+        p.vals = v.take<float>((size_t)p.values);
+        p.block_min = p.mins > 0 ? v.take<uint32_t>((size_t)p.mins) : nullptr;
+        p.slot_q = v.take<uint32_t>((size_t)p.slots);
+        p.slot_o = v.take<uint32_t>((size_t)p.slots);
+        p.vbytes = round_up(v.off, 256);
     }
     if (p.need_fine && !p.dense) {
+        p.slot_q = c.take<uint32_t>(nq * p.nprobe);
+        p.slot_o = c.take<uint32_t>(nq * p.nprobe);
+        p.cbuf = c.take<unsigned long long>((size_t)p.cbuf_entries + 16);
         p.tiles_hot = c.take<Tile>((size_t)p.tile_cap + 1);
         p.tau = c.take<uint32_t>(nq);
         p.tlo = c.take<float>(nq);
@@ -547,7 +586,6 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     p.cbuf_entries = (uint64_t)nq * p.ecap;
     // a smaller batch has larger regions: none needs more in all than this
     if (worst) p.cbuf_entries = std::max<uint64_t>(p.cbuf_entries, std::min<uint64_t>(32768ull * (uint64_t)nq, 4ull << 20));
-    const uint64_t gated_entries = p.cbuf_entries;
     uint32_t most = 0; // queries of a handle
     for (int a = 0; a < nh; ++a) most = std::max(most, worst ? (uint32_t)nq : qlo[a + 1] - qlo[a]);
     {
@@ -562,9 +600,9 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         const uint64_t width = round_up(std::max<uint64_t>(wmax, 16), 64), slots = (uint64_t)nh * (uint64_t)nlist_hi * most;
         const uint64_t values = (uint64_t)nq * width;
         if (worst) { // (what any call within the limits may take)
-            p.cap = (uint32_t)std::min<uint64_t>(most, kDenseSlots / ((uint64_t)nh * (uint64_t)nlist_hi));
-            p.cbuf_entries = std::max<uint64_t>(p.cbuf_entries, std::min<uint64_t>(values, kDenseValues) / 2);
-            p.mins = std::min<uint64_t>(values, kDenseValues) / 16;
+            p.values = std::min<uint64_t>(values, kDenseValues);
+            p.mins = p.values / 16;
+            p.slots = std::min<uint64_t>(slots, kDenseSlots);
         } else if (dense_ok && need_coarse && need_fine && !lean && tunables().dense && own->emit_cap == 0 && nlist_hi <= kDenseSelectMax &&
                    values <= kDenseValues && slots <= kDenseSlots &&
                    (p.hot_from != 0 || p.avg_per_list <= 12.0) && (p.K <= kSelThreads || width <= 16u * kSelThreads)) {
@@ -575,8 +613,9 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
                 p.hot_rs = false;
                 p.hot_from = 0xffffffffu;
             }
-            p.cbuf_entries = (values + 1) / 2;
+            p.values = values;
             p.mins = width > kReadOnce ? values / 16 : 0;
+            p.slots = slots;
         }
     }
     // Other rows (padding, or the norms of L2): the same kernel reads them as they are too and makes the copies and norms on the
@@ -600,13 +639,11 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     if (p.dense) {
         Plan gated = p;
         gated.dense = false;
-        gated.cap = 0;
-        gated.mins = 0;
-        gated.cbuf_entries = gated_entries;
-        carve(gated, nullptr, own);
+        gated.values = 0;
+        carve(gated, nullptr, nullptr, own);
         p.need = gated.bytes;
     }
-    carve(p, nullptr, own);
+    carve(p, nullptr, nullptr, own);
     p.need = std::max(p.need, p.bytes);
     return PK_OK;
 }
@@ -850,7 +887,7 @@ int run_dense(const Plan &p, const MultiArgs &m, pk_index *own, int64_t *out_ids
     sa.qnorm = p.qn;
     sa.slot_query = p.slot_q;
     sa.slot_out = p.slot_o;
-    sa.out = reinterpret_cast<float *>(p.cbuf);
+    sa.out = p.vals;
     sa.k = p.k;
     sa.row_bytes = own->row_bytes;
     sa.metric = own->cfg.metric;
@@ -1084,17 +1121,32 @@ int search_impl(pk_index *const *hs, int nh, const int64_t *q_offsets, const flo
         for (int a = 0; a <= nh; ++a)
             qlo[a] = (uint32_t)std::min<int64_t>(std::max<int64_t>(q_offsets[a] - q0, 0), nq);
         Plan p;
+        auto plan = [&](bool lean, bool dense_ok) {
+            return make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, lean, dense_ok);
+        };
         // (under capture the lists may have grown when the graph runs: by more than the host knows of)
-        PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, false,
-                         mode == kFull && !capturing(s)));
+        const bool whole_ok = mode == kFull && !capturing(s);
         if (fixed_ws) {
-            for (int lean = 0; lean < 2 && p.bytes > fixed_bytes; ++lean)
-                PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, lean != 0));
+            // what the array must hold is the gated search's need, whichever way the values then go
+            PK_TRY(plan(false, false));
+            const bool lean = p.bytes > fixed_bytes;
+            if (lean) PK_TRY(plan(true, false));
             if (nq != nq_all || p.bytes > fixed_bytes) return PK_ERR_WORKSPACE;
-            carve(p, fixed_ws, own);
+            if (whole_ok) {
+                PK_TRY(plan(false, true));
+                if (p.bytes + p.vbytes > fixed_bytes) PK_TRY(plan(lean, false));
+            }
+            carve(p, fixed_ws, fixed_ws + p.bytes, own);
         } else {
+            PK_TRY(plan(false, whole_ok));
+            const int64_t grows = own->ws_grows;
             PK_TRY(ensure_ws(own, p.need, s));
-            carve(p, own->ws, own);
+            if (p.dense) {
+                const int rc = ensure_vals(own, p.vbytes, p.vbytes / 4, s, own->ws_grows != grows);
+                if (rc == PK_ERR_NOMEM) PK_TRY(plan(false, false)); // (its workspace is there: p.need)
+                else PK_TRY(rc);
+            }
+            carve(p, own->ws, own->vals, own);
         }
         MultiArgs m;
         fill_multi(m, hs, nh, qlo.data());
@@ -1262,6 +1314,7 @@ void destroy(pk_index *ix)
 {
     if (!ix) return;
     if (ix->ws) (void)hipFree(ix->ws);
+    if (ix->vals) (void)hipFree(ix->vals);
     if (ix->ubuf) (void)hipFree(ix->ubuf);
     if (ix->ins_best) (void)hipFree(ix->ins_best);
     if (ix->pin_pages) (void)hipHostFree(ix->pin_pages);
@@ -1684,7 +1737,7 @@ int insert_batch(pk_index *const *hs, int nh, const uint32_t *qlo, const float *
     PK_TRY(make_plan(p, hs, nh, qlo, m, 1, 1, forced == nullptr, false));
     const size_t extra = round_up(p.bytes, 256), words = round_up((size_t)m * 4, 256);
     PK_TRY(ensure_ws(own, extra + 2 * words, s));
-    carve(p, own->ws, own);
+    carve(p, own->ws, nullptr, own);
     uint32_t *slots = reinterpret_cast<uint32_t *>(own->ws + extra), *ranks = reinterpret_cast<uint32_t *>(own->ws + extra + words);
     const int32_t *assign = forced;
     if (!forced) {
@@ -2397,7 +2450,23 @@ int pk_workspace_reserve(pk_index *const *handles, int32_t n_handles, int64_t nq
     const int64_t mi = std::min<int64_t>(nq_max, kInsertChunk);
     need = std::max(need, is.lay(nullptr, handles[0], mi));
     for (int a = 1; a < n_handles; ++a) need = std::max(need, is.lay(nullptr, handles[a], mi));
-    return ensure_ws(handles[0], need, static_cast<hipStream_t>(stream));
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int64_t grows = handles[0]->ws_grows;
+    PK_TRY(ensure_ws(handles[0], need, s));
+    // (without the buffer for whole values the searches go through sample and gate)
+    handles[0]->vals_refused = 0;
+    size_t whole = p.vbytes;
+    if (handles[0]->vals_cap > 0) whole = std::min(whole, (size_t)handles[0]->vals_cap);
+    const int rc = capturing(s) ? PK_OK : ensure_vals(handles[0], whole, 0, s, handles[0]->ws_grows != grows);
+    return rc == PK_ERR_NOMEM ? PK_OK : rc;
+}
+
+int pk_index_set_values_cap(pk_index *ix, int64_t bytes)
+{
+    if (!live(ix)) return PK_ERR_BAD_HANDLE;
+    if (bytes < 0) return PK_ERR_INVALID_ARG;
+    ix->vals_cap = bytes;
+    return PK_OK;
 }
 
 int pk_index_set_emit_cap(pk_index *ix, int32_t entries)
@@ -2617,7 +2686,7 @@ int pk_index_stats(pk_index *ix, pk_stats *out, void *stream)
     out->pages_total = ix->pages_total;
     out->pages_used = ctr[0];
     out->arena_bytes = (int64_t)ix->arena_bytes;
-    out->workspace_bytes = (int64_t)ix->ws_bytes;
+    out->workspace_bytes = (int64_t)(ix->ws_bytes + ix->vals_bytes);
     out->workspace_grows = ix->ws_grows;
     out->max_list_len = len.empty() ? 0 : *std::max_element(len.begin(), len.end());
     out->device_error = (int32_t)ctr[1];

@@ -499,6 +499,64 @@ def test_values_written_whole_give_the_rows_of_the_gated_scan(gpu_device, n, d, 
         other.close()
 
 
+def profiled(ix, call):
+    """What `call` returns, and whether it wrote its values whole (every candidate then counts as emitted)."""
+    B.pk_profile_begin(ix.handle)
+    out = call()
+    pr = B.pk_profile_end(ix.handle)
+    return out, pr.emitted == pr.candidates
+
+
+@pytest.mark.parametrize("reserve", [False, True])
+@pytest.mark.parametrize("nq,k,nprobe,storage,metric", [(1, 10, 6, F32, IP), (64, 20, 12, F16, L2), (700, 5, 3, F32, L2)])
+def test_searches_without_the_buffer_for_whole_values(gpu_device, reserve, nq, k, nprobe, storage, metric):
+    """A search that cannot have the buffer for its values goes through sample and gate: the same rows, and no more memory
+    than that route takes.  The buffer comes and grows beside a captured search without invalidating its graph."""
+    g = torch.Generator(device="cuda").manual_seed(nq)
+    n, d, nlist = 60000, 48, 40
+    x = torch.randn((n, d), device="cuda", generator=g)
+    q = torch.randn((nq, d), device="cuda", generator=g)
+    ix = B.Index(x[:nlist].clone(), x, metric=metric, storage=storage, insert_reserve=1000)
+    try:
+        def gated(cap):
+            B.pk_index_set_values_cap(ix.handle, cap)
+            if reserve:
+                ix.reserve(nq, k, nprobe)
+            rows, whole = profiled(ix, lambda: ix.search(q, k, nprobe))
+            assert not whole
+            return rows, ix.stats()
+
+        rows, st = gated(1)
+        width = int(np.sort(ix.list_lengths())[-nprobe:].sum())
+        assert st.workspace_grows == 1
+        ids, dist = torch.empty_like(rows[0]), torch.empty_like(rows[1])
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            with torch.cuda.graph(graph, stream=side):
+                B.pk_search(ix.handle, q, k, nprobe, ids, dist)
+        for cap in (4 * nq * width, 0):  # (of the values alone: not enough for what goes with them; then as much as it takes)
+            if cap:
+                again, grown = gated(cap)
+                assert reserve or grown.workspace_bytes == st.workspace_bytes
+            else:
+                B.pk_index_set_values_cap(ix.handle, 0)
+                again, whole = profiled(ix, lambda: ix.search(q, k, nprobe))
+                assert whole
+                grown = ix.stats()
+                assert grown.workspace_bytes >= st.workspace_bytes + 4 * nq * width
+            assert torch.equal(again[0], rows[0]) and torch.equal(again[1], rows[1])
+            for _ in range(2):
+                ids.fill_(-7)
+                torch.cuda.synchronize()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(ids, rows[0]) and torch.equal(dist, rows[1])
+        assert ix.stats().workspace_grows == grown.workspace_grows
+    finally:
+        ix.close()
+
+
 @pytest.mark.parametrize("gated", [False, True])
 @pytest.mark.parametrize("d,nq,k,metric", [(32, 1, 10, IP), (64, 40, 200, L2), (100, 300, 10, IP), (1100, 6, 5, L2)])
 def test_a_work_list_without_room_scans_nothing(gpu_device, gated, d, nq, k, metric):

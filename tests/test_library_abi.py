@@ -57,6 +57,7 @@ def test_host_side_argument_checks_without_gpu(lib):
     assert lib.pk_search_noalloc(null, null, 1, 1, 1, null, null, null) == B.PK_ERR_BAD_HANDLE
     assert lib.pk_index_set_emit_cap(null, 0) == B.PK_ERR_BAD_HANDLE
     assert lib.pk_index_set_tile_cap(null, 0) == B.PK_ERR_BAD_HANDLE
+    assert lib.pk_index_set_values_cap(null, 0) == B.PK_ERR_BAD_HANDLE
     assert lib.pk_search_noalloc_bytes(null, 1, 1, 1) == 0
     assert lib.pk_insert(null, null, null, 1, null, null) == B.PK_ERR_BAD_HANDLE
     assert lib.pk_coarse(null, null, 1, 1, null, null) == B.PK_ERR_BAD_HANDLE
