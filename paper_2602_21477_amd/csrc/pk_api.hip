@@ -96,9 +96,10 @@ struct pk_index {
     // search (which is gated) keeps its workspace when this one grows, and a search that cannot have it goes on without
     char *vals;
     size_t vals_bytes;
+    bool vals_inside;       // it lies behind the workspace, in the same allocation
     size_t vals_refused;    // a size that the device had no room for (0: none): not asked for again until the next reservation
     int64_t vals_cap;       // most bytes of it, set by the caller (0: what the device gives)
-    int64_t ws_grows;       // times the workspace (either buffer) was (re)allocated since the build, once per call
+    int64_t ws_grows;       // calls since the build that (re)allocated either buffer
     int32_t emit_cap;       // entries of a query's emission region set by the caller (0: by k)
     int32_t tile_cap;       // most tiles of a work list, set by the caller (0: by the lists' lengths)
     // staging of scope-union searches (replicated queries, per-handle results); grow-only
@@ -165,50 +166,73 @@ bool capturing(hipStream_t s)
     return st != hipStreamCaptureStatusNone;
 }
 
-int ensure_ws(pk_index *ix, size_t bytes, hipStream_t s)
+// The handle's workspace and, with vals > 0, its buffer for whole values hold at least that.  PK_ERR_NOMEM with *no_vals
+// null: no workspace.  *no_vals: the buffer cannot be had, the search goes through sample and gate in the workspace, which is
+// there.  vals_spare: what a new buffer gets beyond `vals`, as its size follows the lists' lengths.
+int ensure_ws(pk_index *ix, size_t bytes, hipStream_t s, size_t vals = 0, size_t vals_spare = 0, bool *no_vals = nullptr)
 {
-    if (bytes <= ix->ws_bytes) return PK_OK;
-    // A captured graph would keep pointers into the buffer that is about to be freed.
-    if (capturing(s)) return PK_ERR_WORKSPACE;
-    // grow: earlier work on this handle's stream may still use the old buffer
+    if (vals > 0 && ((ix->vals_cap > 0 && vals > (size_t)ix->vals_cap) || (ix->vals_refused > 0 && vals >= ix->vals_refused && vals > ix->vals_bytes))) {
+        *no_vals = true;
+        vals = 0;
+    }
+    const bool grow = bytes > ix->ws_bytes;
+    // (a buffer inside the workspace goes with it)
+    const bool grow_vals = vals > 0 && (vals > ix->vals_bytes || (grow && ix->vals_inside));
+    if (!grow && !grow_vals) return PK_OK;
+    if (capturing(s)) {
+        // A captured graph would keep pointers into the workspace that is about to be freed.
+        if (grow) return PK_ERR_WORKSPACE;
+        *no_vals = true;
+        return PK_OK;
+    }
+    // grow: earlier work on this handle's stream may still use the old buffers
     PK_HIP(hipStreamSynchronize(s));
+    if (ix->vals && (grow_vals || (grow && ix->vals_inside))) {
+        if (!ix->vals_inside) PK_HIP(hipFree(ix->vals));
+        ix->vals = nullptr;
+        ix->vals_bytes = 0;
+        ix->vals_inside = false;
+    }
+    size_t want_vals = grow_vals ? round_up(vals + vals_spare, 1 << 20) : 0;
+    if (ix->vals_cap > 0) want_vals = std::min(want_vals, (size_t)ix->vals_cap);
+    void *p = nullptr;
+    auto refuse = [&] {
+        (void)hipGetLastError();
+        ix->vals_refused = vals;
+        *no_vals = true;
+    };
+    if (!grow) {
+        if (hipMalloc(&p, want_vals) != hipSuccess) {
+            refuse();
+            return PK_OK;
+        }
+        ix->vals = static_cast<char *>(p);
+        ix->vals_bytes = want_vals;
+        ix->ws_grows += 1;
+        return PK_OK;
+    }
     if (ix->ws) PK_HIP(hipFree(ix->ws));
     ix->ws = nullptr;
     ix->ws_bytes = 0;
+    // (one allocation for both: a second one costs the first search of a memory 0.2 ms, most of it when it is freed)
     const size_t want = round_up(bytes + bytes / 8, 1 << 20);
-    void *p = nullptr;
-    if (hipMalloc(&p, want) != hipSuccess) {
+    if (want_vals > 0 && hipMalloc(&p, want + want_vals) != hipSuccess) {
+        refuse();
+        want_vals = 0;
+        p = nullptr;
+    }
+    if (!p && hipMalloc(&p, want) != hipSuccess) {
         (void)hipGetLastError();
         return PK_ERR_NOMEM;
     }
     ix->ws = static_cast<char *>(p);
     ix->ws_bytes = want;
-    ix->ws_grows += 1;
-    return PK_OK;
-}
-
-// PK_ERR_NOMEM: the buffer for whole values cannot be had, the search goes through sample and gate.  spare: what a new
-// buffer gets beyond that, as its size follows the lists' lengths.  once: the call has counted a growth already.
-int ensure_vals(pk_index *ix, size_t bytes, size_t spare, hipStream_t s, bool once)
-{
-    if (ix->vals_cap > 0 && bytes > (size_t)ix->vals_cap) return PK_ERR_NOMEM;
-    if (bytes <= ix->vals_bytes) return PK_OK;
-    if (ix->vals_refused > 0 && bytes >= ix->vals_refused) return PK_ERR_NOMEM;
-    PK_HIP(hipStreamSynchronize(s)); // earlier work on this handle's stream may still use the old buffer
-    if (ix->vals) PK_HIP(hipFree(ix->vals));
-    ix->vals = nullptr;
-    ix->vals_bytes = 0;
-    size_t want = round_up(bytes + spare, 1 << 20);
-    if (ix->vals_cap > 0) want = std::min(want, (size_t)ix->vals_cap);
-    void *p = nullptr;
-    if (hipMalloc(&p, want) != hipSuccess) {
-        (void)hipGetLastError();
-        ix->vals_refused = bytes;
-        return PK_ERR_NOMEM;
+    if (want_vals > 0) {
+        ix->vals = ix->ws + want;
+        ix->vals_bytes = want_vals;
+        ix->vals_inside = true;
     }
-    ix->vals = static_cast<char *>(p);
-    ix->vals_bytes = want;
-    if (!once) ix->ws_grows += 1;
+    ix->ws_grows += 1;
     return PK_OK;
 }
 
@@ -1139,13 +1163,9 @@ int search_impl(pk_index *const *hs, int nh, const int64_t *q_offsets, const flo
             carve(p, fixed_ws, fixed_ws + p.bytes, own);
         } else {
             PK_TRY(plan(false, whole_ok));
-            const int64_t grows = own->ws_grows;
-            PK_TRY(ensure_ws(own, p.need, s));
-            if (p.dense) {
-                const int rc = ensure_vals(own, p.vbytes, p.vbytes / 4, s, own->ws_grows != grows);
-                if (rc == PK_ERR_NOMEM) PK_TRY(plan(false, false)); // (its workspace is there: p.need)
-                else PK_TRY(rc);
-            }
+            bool no_vals = false;
+            PK_TRY(ensure_ws(own, p.need, s, p.vbytes, p.vbytes / 4, &no_vals));
+            if (no_vals) PK_TRY(plan(false, false)); // (its workspace is there: p.need)
             carve(p, own->ws, own->vals, own);
         }
         MultiArgs m;
@@ -1314,7 +1334,7 @@ void destroy(pk_index *ix)
 {
     if (!ix) return;
     if (ix->ws) (void)hipFree(ix->ws);
-    if (ix->vals) (void)hipFree(ix->vals);
+    if (ix->vals && !ix->vals_inside) (void)hipFree(ix->vals);
     if (ix->ubuf) (void)hipFree(ix->ubuf);
     if (ix->ins_best) (void)hipFree(ix->ins_best);
     if (ix->pin_pages) (void)hipHostFree(ix->pin_pages);
@@ -2451,14 +2471,11 @@ int pk_workspace_reserve(pk_index *const *handles, int32_t n_handles, int64_t nq
     need = std::max(need, is.lay(nullptr, handles[0], mi));
     for (int a = 1; a < n_handles; ++a) need = std::max(need, is.lay(nullptr, handles[a], mi));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t grows = handles[0]->ws_grows;
-    PK_TRY(ensure_ws(handles[0], need, s));
-    // (without the buffer for whole values the searches go through sample and gate)
     handles[0]->vals_refused = 0;
     size_t whole = p.vbytes;
     if (handles[0]->vals_cap > 0) whole = std::min(whole, (size_t)handles[0]->vals_cap);
-    const int rc = capturing(s) ? PK_OK : ensure_vals(handles[0], whole, 0, s, handles[0]->ws_grows != grows);
-    return rc == PK_ERR_NOMEM ? PK_OK : rc;
+    bool no_vals = false; // (without the buffer for whole values the searches go through sample and gate)
+    return ensure_ws(handles[0], need, s, whole, 0, &no_vals);
 }
 
 int pk_index_set_values_cap(pk_index *ix, int64_t bytes)
