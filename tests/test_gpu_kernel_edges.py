@@ -499,6 +499,46 @@ def test_values_written_whole_give_the_rows_of_the_gated_scan(gpu_device, n, d, 
         other.close()
 
 
+@pytest.mark.parametrize("n,kinds,k,nprobe,nq,page,metric,storage", [
+    (300000, 50, 100, 16, 1, 0, IP, F32), (300000, 50, 10, 16, 3, 96, L2, F16), (100000, 1, 30, 2, 5, 0, L2, F32),
+    (200000, 7, 200, 40, 4, 1024, IP, F16), (300000, 2000, 255, 40, 2, 32, L2, F32), (70000, 3, 1, 40, 9, 0, IP, F32)])
+def test_equal_values_beyond_what_is_collected_cost_no_more_than_the_gated_scan(gpu_device, n, kinds, k, nprobe, nq, page, metric, storage):
+    """A memory of few different rows: groups of equal values that are larger than what the final selection collects.  The rows of
+    the gated scan, ids in ascending order within a group, the largest and the smallest id there is among them; and one more
+    pass over the values, not one for each member of a group: the gated route's time is not exceeded (twice it would be a pass
+    per member, here three times and more)."""
+    g = torch.Generator(device="cuda").manual_seed(kinds)
+    d, nlist = 64, 40
+    some = torch.randn((kinds, d), device="cuda", generator=g)
+    x = some[torch.randint(kinds, (n,), device="cuda", generator=g)].contiguous()
+    ids = torch.randperm(5 * n, device="cuda", generator=g)[:n] - 2 * n
+    ids[n // 2], ids[n // 3] = 2 ** 63 - 1, -(2 ** 63)
+    ix = B.Index(torch.randn((nlist, d), device="cuda", generator=g), x, ids=ids.contiguous(), metric=metric, storage=storage, page_vecs=page,
+                 insert_reserve=4096)
+    try:
+        ix.insert(x[:2000].contiguous(), ids[:2000].contiguous())
+        q = torch.randn((nq, d), device="cuda", generator=g)
+        rows, times = [], []
+        for cap in (32768, 0):
+            B.pk_index_set_emit_cap(ix.handle, cap)
+            out, whole = profiled(ix, lambda: ix.search(q, k, nprobe))
+            assert whole == (cap == 0) or ix.list_lengths().max() == n + 2000
+            rows.append(out)
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            best = math.inf
+            for _ in range(3):
+                start.record()
+                ix.search(q, k, nprobe)
+                stop.record()
+                stop.synchronize()
+                best = min(best, start.elapsed_time(stop))
+            times.append(best)
+        assert torch.equal(rows[0][0], rows[1][0]) and torch.equal(rows[0][1], rows[1][1])
+        assert times[1] < 2 * times[0] + 0.1, times
+    finally:
+        ix.close()
+
+
 def profiled(ix, call):
     """What `call` returns, and whether it wrote its values whole (every candidate then counts as emitted)."""
     B.pk_profile_begin(ix.handle)
