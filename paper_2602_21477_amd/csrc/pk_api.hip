@@ -527,6 +527,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     p.sp = (k + own->P - 1) / own->P; // sample pages: at least k rows when the first pages are full
     uint64_t tiles = 0, wmax = 0, lmax = 0, bytes = 0;
     double lmean = 0; // rows per list on average (the largest over the handles)
+    double distinct = 0; // bytes of rows in lists that some query probes, where the queries spread evenly
     int nlist_hi = 0, pad_hi = 0;
     const int mq_least = worst ? 16 : std::min(p.mq_f, p.mq_h);
     const bool rs_tiles = worst ? (own->row_bytes <= 1536 && own->P % kRrTileRows == 0) : p.hot_rs;
@@ -542,6 +543,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         lmax = std::max(lmax, wq_ub(ix, 1)); // the longest list as it may be now
         bytes += (uint64_t)ix->n_total * (uint64_t)own->row_bytes;
         lmean = std::max(lmean, (double)ix->n_total / ix->cfg.nlist);
+        distinct += (1.0 - std::pow(1.0 - (double)std::min(nprobe, ix->cfg.nlist) / ix->cfg.nlist, (double)nqa)) * (double)ix->n_total * own->row_bytes;
         const uint64_t pp = w / ix->P + nprobe;
         const uint64_t pages = std::min<uint64_t>(pages_used_ub(ix, ahead), nqa * pp);
         tiles += pages + nqa * pp / mq_least + 1;
@@ -615,21 +617,35 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     {
         // Values written whole.  A value costs its 4 bytes in and a sixteenth of them out, and the layout has no prefix sums;
         // sample, gate and emission cost 10 - 27 us of a small batch, and the more the more queries meet the same counters.
-        // Searches of 1 - 1024 queries, gated and whole, us: 20 000 x 128, 64 lists, 4 probes, 1024 queries 179 and 50; 1 M x 64,
-        // 256 lists, 48 probes, 64 queries 288 and 145 (one query 75 and 63); 1 M x 256 fp16, 48 of 1024 lists, 8 queries 89
-        // and 87, 256 queries 220 and 188.  The sliced-query kernel's waves wait for their stores before the next tile's
-        // loads: 400 000 x 1024, 16 probes, 256 queries (8 per list) 378 and 350, 48 probes (24 per list) 471 and 503, 16 probes
-        // of 1024 queries (32) 638 and 655, sixteen memories of 590 rows per list (one per list) 1950 and 1864: there
-        // lists probed by few queries only.
+        // Searches of 1 - 4096 queries, gated and whole, us: 20 000 x 128, 64 lists, 4 probes, 1024 queries 179 and 50; 100 000 x 64,
+        // 64 lists, 32 probes, 1024 queries 379 and 236; 200 000 x 64, 128 lists, 8 probes, 4096 queries 683 and 347.
+        // Long lists are emitted from by the thousand, so that the range of a query is no limit there: 4 M x 128 fp16, 256
+        // lists, 64 queries of 64 probes (1 M values each) 1432 and 436; 60 M x 128 fp16, 64 lists, one query over 0.9 M, 15 M and
+        // 57 M values 171 and 148, 1537 and 1458, 6066 and 5999.  (Of some forty such calls over rows of 1 KB and more, four lose:
+        // 1.5 M x 200, 100 lists, 4 queries of 64 probes 328 and 378, 16 of 16 304 and 323, but 64 of 16 473 and 387.)
+        // Where short lists of a memory beyond the caches are read, the stores cost the scan a tenth to a fifth of its time, which
+        // the gate's fixed cost (some 25 us, more from 512 queries on, whose samples no longer fit the chip side by side) pays for
+        // while the values are few.  2 M x 512 fp16, 1024 lists: 16 queries of 32 probes (1.0 M values) 180 and 175, 64 (4 M) 335
+        // and 376, 256 (16 M) 415 and 488; 2 probes of 1024 queries (4 M) 427 and 399, 8 of 512 (8 M) 419 and 463; 1 M x 768 fp32:
+        // 64 of 32 (2.1 M) 492 and 475, 256 of 32 (8 M) 591 and 642; 2 M x 384 fp16: 512 of 32 (32 M) 441 and 409; 1 M x 256: 1024
+        // of 8 (8.5 M) 335 and 307; 4 M x 768 fp16, 2048 lists: 512 of 2 (2.1 M) 495 and 450, of 32 (32 M) 1115 and 1255.
+        // And the sliced-query kernel's waves wait for their stores before the next tile's loads: 1 M x 1024, 1024 lists, 512 queries
+        // of 4 probes (2 per list) 720 and 617, 200 of 16 (3) 769 and 699, 512 of 16 (8) 790 and 812; 1 M x 1536 fp16, 512 lists, 64
+        // queries of 64 (8) 573 and 607; 400 000 x 1024, 48 probes of 256 queries (24) 471 and 503.
         const uint64_t width = round_up(std::max<uint64_t>(wmax, 16), 64), slots = (uint64_t)nh * (uint64_t)nlist_hi * most;
         const uint64_t values = (uint64_t)nq * width;
+        bool pays = true;
+        if (p.hot_from == 0) pays = p.avg_per_list <= (width <= kReadOnce ? 12.0 : 6.0);
+        else if (lmean >= 3072.0) pays = true;
+        else if (nq >= 512) pays = width <= (p.stream_rows && distinct > 1.6e9 ? (uint64_t)kReadOnce : 81920u); // (200 000 x 64, 64 of 128 lists, 512 queries 240 and 261)
+        else if (p.stream_rows) pays = values <= 1536ull * (uint64_t)std::max(own->row_bytes, 1024);
         if (worst) { // (what any call within the limits may take)
             p.values = std::min<uint64_t>(values, kDenseValues);
             p.mins = p.values / 16;
             p.slots = std::min<uint64_t>(slots, kDenseSlots);
         } else if (dense_ok && need_coarse && need_fine && !lean && tunables().dense && own->emit_cap == 0 && nlist_hi <= kDenseSelectMax &&
                    values <= kDenseValues && slots <= kDenseSlots &&
-                   (p.hot_from != 0 || p.avg_per_list <= 12.0) && (p.K <= kSelThreads || width <= 16u * kSelThreads)) {
+                   pays && (p.K <= kSelThreads || width <= 16u * kSelThreads)) {
             p.dense = true;
             p.cap = most;
             p.width = (uint32_t)width;

@@ -547,6 +547,36 @@ def profiled(ix, call):
     return out, pr.emitted == pr.candidates
 
 
+@pytest.mark.parametrize("n,d,nlist,storage,calls", [
+    (800_000, 256, 800, F32, [(200, 4, True), (256, 10, False), (600, 20, True), (1, 64, True)]),  # short lists beyond the caches
+    (800_000, 1024, 800, F16, [(200, 10, True), (256, 20, False)]),  # ... of wider rows, whose values weigh less
+    (1_700_000, 256, 1700, F32, [(600, 6, True), (600, 16, False)]),  # ... of many bytes, for batches with large samples
+    (1_000_000, 256, 250, F32, [(64, 32, True), (256, 20, True)]),  # long lists
+    (300_000, 256, 300, F32, [(256, 20, True), (512, 15, True)]),  # lists that the caches hold
+    (120_000, 1024, 120, F32, [(60, 8, True), (60, 14, False), (110, 7, True)]),  # sliced queries, lists probed by few and by more
+    (120_000, 1024, 20, F32, [(500, 1, False)])])
+def test_which_calls_write_their_values_whole(gpu_device, n, d, nlist, storage, calls):
+    """Both sides of the lines between the two ways: which one a call takes, and the same rows."""
+    g = torch.Generator(device="cuda").manual_seed(nlist)
+    mu = torch.randn((nlist, d), device="cuda", generator=g)
+    x = mu[torch.randint(nlist, (n,), device="cuda", generator=g)]
+    for a in range(0, n, 1 << 18):
+        x[a:a + (1 << 18)] += 0.3 * torch.randn(x[a:a + (1 << 18)].shape, device="cuda", generator=g)
+    ix = B.Index(mu, x, metric=IP, storage=storage)
+    del x
+    try:
+        for nq, nprobe, expected in calls:
+            q = mu[torch.randint(nlist, (nq,), device="cuda", generator=g)] + 0.3 * torch.randn((nq, d), device="cuda", generator=g)
+            rows, whole = profiled(ix, lambda: ix.search(q, 10, nprobe))
+            assert whole == expected, (nq, nprobe, ix.list_lengths().max())
+            B.pk_index_set_emit_cap(ix.handle, 32768)
+            gated, whole = profiled(ix, lambda: ix.search(q, 10, nprobe))
+            B.pk_index_set_emit_cap(ix.handle, 0)
+            assert not whole and torch.equal(rows[0], gated[0]) and torch.equal(rows[1], gated[1])
+    finally:
+        ix.close()
+
+
 @pytest.mark.parametrize("reserve", [False, True])
 @pytest.mark.parametrize("nq,k,nprobe,storage,metric", [(1, 10, 6, F32, IP), (64, 20, 12, F16, L2), (700, 5, 3, F32, L2)])
 def test_searches_without_the_buffer_for_whole_values(gpu_device, reserve, nq, k, nprobe, storage, metric):
