@@ -830,12 +830,13 @@ __device__ __forceinline__ bool final_of_values(const float *vals, const uint32_
 }
 
 // All n values of a query's range (aligned, padded to 16) through a selector, for queries among whose values equal ones are the
-// rule.  key(bits, p): what the value with these order bits at position p is selected by, all ones for not at all.  A round
-// is 8192 values, and only those 256 of it are pushed among which some thread has a key below the threshold.  700 000 values of
-// 50 kinds: values and the ids of a group in 0.6 ms, 1 M equal ones 4.2 (gated, whose rows are scored again 1.4 - 10 and 76).
+// rule.  key(bits, p): what the value with these order bits at position p is selected by, all ones for not at all, which is what
+// all values have that may(bits, threshold) refuses.  A round is 8192 values, and only those 256 of it are pushed among which
+// some thread has a key below the threshold.  700 000 values of
+// 50 kinds: values and the ids of a group in 0.5 ms, 1 M equal ones 4.7 (gated, whose rows are scored again, 1.4 - 10 and 76).
 // s_mask: LDS, zero.
-template <typename Key>
-__device__ __forceinline__ void stream_values(Selector &sel, uint32_t *s_mask, const float *vals, uint32_t n, int metric, Key key)
+template <typename May, typename Key>
+__device__ __forceinline__ void stream_values(Selector &sel, uint32_t *s_mask, const float *vals, uint32_t n, int metric, May may, Key key)
 {
     constexpr uint32_t U = 8, kStep = 4u * kSelThreads;
     const uint32_t tid = threadIdx.x;
@@ -846,29 +847,31 @@ __device__ __forceinline__ void stream_values(Selector &sel, uint32_t *s_mask, c
             const uint32_t p = r + u * kStep + 4u * tid;
             v[u] = reinterpret_cast<const u32x4 *>(vals)[(p < n ? p : 0u) >> 2];
         }
-        uint32_t pass = 0;
+        uint32_t some = 0, pass = 0;
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u)
 #pragma unroll
             for (uint32_t e = 0; e < 4; ++e) {
                 const uint32_t p = r + u * kStep + 4u * tid + e;
-                if (p < n && key(order_bits(__uint_as_float(v[u][e]), metric), p) < sel.thr) pass |= 1u << (u * 4u + e);
+                if (p < n && may(order_bits(__uint_as_float(v[u][e]), metric), sel.thr)) some |= 1u << (u * 4u + e);
             }
+        // (from here on one value at a time, read again: as 32 copies of the loops' bodies this was most of the kernel's code)
+        auto at = [=](uint32_t b) { return r + (b >> 2) * kStep + 4u * tid + (b & 3u); };
+        for (; some != 0u; some &= some - 1u) {
+            const uint32_t b = (uint32_t)__ffs(some) - 1u;
+            if (key(order_bits(vals[at(b)], metric), at(b)) < sel.thr) pass |= 1u << b;
+        }
         for (int off = 32; off > 0; off >>= 1) pass |= __shfl_xor(pass, off);
         if ((tid & 63u) == 0u && pass) atomicOr(s_mask, pass);
         __syncthreads();
-        const uint32_t some = *s_mask; // (the same for the whole workgroup)
+        pass = *s_mask; // (the same for the whole workgroup)
         __syncthreads();
         if (tid == 0) *s_mask = 0u;
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u)
-#pragma unroll
-            for (uint32_t e = 0; e < 4; ++e) {
-                if ((some >> (u * 4u + e) & 1u) == 0u) continue;
-                sel.reserve(kSelThreads);
-                const uint32_t p = r + u * kStep + 4u * tid + e;
-                if (p < n) sel.push(key(order_bits(__uint_as_float(v[u][e]), metric), p));
-            }
+        for (; pass != 0u; pass &= pass - 1u) {
+            const uint32_t p = at((uint32_t)__ffs(pass) - 1u);
+            sel.reserve(kSelThreads);
+            if (p < n) sel.push(key(order_bits(vals[p], metric), p));
+        }
         __syncthreads(); // (s_mask: written again)
     }
 }
@@ -960,7 +963,9 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
         // equal values are the rule: all of them through the streaming selector
         if (threadIdx.x == 0) s_cnt = s_pickpos = 0;
         __syncthreads();
-        stream_values(sel, &s_pickpos, values, cnt_q, a.metric, [](uint32_t bits, uint32_t p) { return bits < kWorstBits ? ((u64)bits << 32) | p : kMaxKey; });
+        stream_values(sel, &s_pickpos, values, cnt_q, a.metric,
+                      [](uint32_t bits, u64 thr) { return bits < kWorstBits && bits <= (uint32_t)(thr >> 32); },
+                      [](uint32_t bits, uint32_t p) { return bits < kWorstBits ? ((u64)bits << 32) | p : kMaxKey; });
     } else if (DENSE) {
     } else if (in_registers) {
         auto get = [=](int j, uint32_t p) { return j == 0 ? early : v[p]; };
@@ -1040,9 +1045,10 @@ __global__ __launch_bounds__(kSelThreads) void select_final_kernel(FinalArgs a, 
             sel.init(keys, &s_cnt, (int)((uint32_t)k - nb), cap);
             const DevIndex *const ix = &qix;
             const int nprobe = a.nprobe;
-            stream_values(sel, &s_pickpos, values, cnt_q, a.metric, [=](uint32_t bits, uint32_t p) {
-                return bits == tau ? (u64)resolve_id_lds(nprobe, *ix, p, s_po, s_pr, s_mp, s_mb) ^ 0x8000000000000000ull : kMaxKey;
-            });
+            stream_values(sel, &s_pickpos, values, cnt_q, a.metric, [=](uint32_t bits, u64) { return bits == tau; },
+                          [=](uint32_t bits, uint32_t p) {
+                              return bits == tau ? (u64)resolve_id_lds(nprobe, *ix, p, s_po, s_pr, s_mp, s_mb) ^ 0x8000000000000000ull : kMaxKey;
+                          });
             sel.flush();
             for (uint32_t t = nb + threadIdx.x; t < (uint32_t)k; t += blockDim.x) // (the largest id there is has the key of none)
                 s_id[t] = t - nb < s_cnt ? (int64_t)(keys[t - nb] ^ 0x8000000000000000ull) : INT64_MAX;
