@@ -634,11 +634,13 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         // queries of 64 (8) 573 and 607; 400 000 x 1024, 48 probes of 256 queries (24) 471 and 503.
         const uint64_t width = round_up(std::max<uint64_t>(wmax, 16), 64), slots = (uint64_t)nh * (uint64_t)nlist_hi * most;
         const uint64_t values = (uint64_t)nq * width;
+        // (width is what the longest lists can hold, and grows with every insert: the line is drawn by what a query meets on average)
+        const double meets = nprobe * lmean;
         bool pays = true;
-        if (p.hot_from == 0) pays = p.avg_per_list <= (width <= kReadOnce ? 12.0 : 6.0);
+        if (p.hot_from == 0) pays = p.avg_per_list <= (meets <= (double)kReadOnce ? 12.0 : 6.0);
         else if (lmean >= 3072.0) pays = true;
-        else if (nq >= 512) pays = width <= (p.stream_rows && distinct > 1.6e9 ? (uint64_t)kReadOnce : 81920u); // (200 000 x 64, 64 of 128 lists, 512 queries 240 and 261)
-        else if (p.stream_rows) pays = values <= 1536ull * (uint64_t)std::max(own->row_bytes, 1024);
+        else if (nq >= 512) pays = meets <= (p.stream_rows && distinct > 1.6e9 ? (double)kReadOnce : 81920.0); // (200 000 x 64, 64 of 128 lists, 512 queries 240 and 261)
+        else if (p.stream_rows) pays = (double)nq * meets <= 1536.0 * std::max(own->row_bytes, 1024);
         if (worst) { // (what any call within the limits may take)
             p.values = std::min<uint64_t>(values, kDenseValues);
             p.mins = p.values / 16;
