@@ -393,7 +393,8 @@ int pk_list_lengths(pk_index *index, int64_t *out_len, void *stream);
  *   select_ms   per-query top-k over the scored candidates (Section 4.4 merge)
  * scanned_rows counts each probed list once per launch sequence (the rows the scan must
  * read from memory); candidates counts (query, vector) pairs scored, emitted those that
- * passed the running per-query threshold and reached the top-k selection.  pk_profile_end synchronises
+ * passed the running per-query threshold and reached the top-k selection (of calls whose values are
+ * written whole: all of them).  pk_profile_end synchronises
  * `stream`.  out: HOST.
  */
 typedef struct {
@@ -402,7 +403,7 @@ typedef struct {
     int64_t scanned_rows, candidates, tiles, emitted; /* sums over all sequences          */
     int64_t overflowed;  /* queries whose emission region overflowed (selected by rescoring) */
     int64_t max_emitted; /* most candidates a single query emitted                          */
-    float scan_hot_ms;   /* the part of scan_ms spent in the launch for lists probed by many queries */
+    float scan_hot_ms;   /* the part of scan_ms spent in the launch for lists probed by many queries (0: none) */
 } pk_profile;
 int pk_profile_begin(pk_index *index, void *stream);
 int pk_profile_end(pk_index *index, pk_profile *out, void *stream);

@@ -118,8 +118,9 @@ struct pk_index {
     // stage timing (pk_profile_begin .. pk_profile_end)
     bool prof_on;
     std::vector<hipEvent_t> prof_ev; // 6 events per recorded launch sequence
-    std::vector<uint8_t> prof_beside; // per sequence: the two scan kernels ran side by side (the fourth event then
-                                      // follows the kernel of the lists many queries probe, not the regular scan)
+    std::vector<uint8_t> prof_beside; // per sequence: 1 the two scan kernels ran side by side (the fourth event then
+                                      // follows the kernel of the lists many queries probe, not the regular scan), 0 one after
+                                      // the other, 2 there was no kernel for lists that many queries probe
     size_t prof_used;
 };
 
@@ -944,7 +945,7 @@ int run_dense(const Plan &p, const MultiArgs &m, pk_index *own, int64_t *out_ids
     const int grid = (int)std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)(sliced ? p.grid_h : p.grid_f), p.tile_cap));
     if (!sliced) PK_HIP(launch_scan(sa, grid, s));
     if (timed) {
-        own->prof_beside.push_back(0);
+        own->prof_beside.push_back(2);
         PK_TRY(mark(own, s));
     }
     if (sliced) PK_HIP(launch_scan_ks(sa, grid, s));
@@ -1088,7 +1089,7 @@ int run_fine(const Plan &p, const MultiArgs &m, pk_index *own, const float *q, i
     } else {
         if (p.hot_from > 0) PK_HIP(launch_scan(sa, p.grid_f, s));
         if (timed) {
-            own->prof_beside.push_back(0);
+            own->prof_beside.push_back(p.hot_from != 0xffffffffu ? 0 : 2);
             PK_TRY(mark(own, s)); // after the regular lists' scan
         }
         if (p.hot_from != 0xffffffffu) {
@@ -2770,7 +2771,8 @@ int pk_profile_end(pk_index *ix, pk_profile *out, void *stream)
         out->coarse_ms += ms[0];
         out->worklist_ms += ms[1];
         out->scan_ms += ms[2] + ms[3];
-        out->scan_hot_ms += i < ix->prof_beside.size() && ix->prof_beside[i] ? ms[2] : ms[3];
+        const uint8_t how = i < ix->prof_beside.size() ? ix->prof_beside[i] : 2;
+        out->scan_hot_ms += how == 1 ? ms[2] : (how == 0 ? ms[3] : 0.f); // (the interval of no launch is no time)
         out->select_ms += ms[4];
     }
     out->launches = (int32_t)n;
