@@ -15,6 +15,25 @@ KX = 48  # extra oracle results past k (fp32), so the comparator can look near-t
 KX_F16 = 1500  # the 1e-2 tolerance of fp16 storage makes near-tie runs that long
 
 
+class route:
+    """with route(gpu, whole) as ran: ... -- searches of that handle (or led by it) that go through sample and gate (whole
+    False) or, where the library does, have their values written whole.  Afterwards `ran` has the profile of the searches and
+    whether all of them did write their values whole (all candidates then count as emitted)."""
+
+    def __init__(self, gpu, whole):
+        self.gpu, self.asked = gpu, whole
+
+    def __enter__(self):
+        B.pk_index_set_values_cap(self.gpu.handle, 0 if self.asked else 1)
+        B.pk_profile_begin(self.gpu.handle)
+        return self
+
+    def __exit__(self, *exc):
+        self.profile = B.pk_profile_end(self.gpu.handle)
+        self.whole = self.profile.emitted == self.profile.candidates
+        B.pk_index_set_values_cap(self.gpu.handle, 0)
+
+
 def dev(a, dtype=None):
     t = torch.from_numpy(np.ascontiguousarray(a))
     if dtype is not None:

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import Pair, dev, make_pair
+from gpu_util import Pair, dev, make_pair, route
 from paper_2602_21477_amd import binding as B
 from paper_2602_21477_amd import workload as W
 
@@ -457,17 +457,19 @@ def test_deletes_by_hash_set(gpu_device, nlist, page):
 @pytest.mark.parametrize("n,d,nlist,nprobe,k,nq,page,storage,metric,equal", [
     (700, 40, 60, 5, 10, 3, 32, F32, IP, 0),  # ranges of a hundred values
     (3000, 40, 30, 9, 150, 33, 64, F32, L2, 0),  # a thousand values and a K beyond what parts serve
-    (9000, 100, 12, 6, 300, 17, 0, F16, IP, 0),  # up to 4096 values, K beyond the workgroup's threads
+    (5000, 100, 12, 6, 300, 17, 0, F16, IP, 0),  # up to 4096 values, K beyond the workgroup's threads
     (9000, 64, 900, 600, 20, 5, 0, F32, L2, 0),  # more probes than threads
     (60000, 48, 20, 8, 23, 70, 0, F32, IP, 0),  # long ranges: 64 parts, the most for them
     (60000, 48, 20, 8, 127, 40, 96, F16, L2, 0),  # ... 256 parts, the most for them
     (60000, 48, 20, 8, 255, 9, 1024, F32, L2, 0),  # ... 1024 parts, the most for them
-    (60000, 1100, 20, 20, 10, 20, 0, F32, IP, 0),  # sliced queries, every list
+    (60000, 1100, 60, 20, 10, 15, 0, F32, L2, 0),  # sliced queries, 16 slots, long ranges
+    (60000, 1100, 60, 8, 10, 75, 0, F32, IP, 0),  # ... 32 slots, several groups of some lists
+    (60000, 1100, 60, 8, 40, 75, 96, F16, L2, 0),
     (60000, 64, 4, 2, 100, 300, 0, F16, IP, 0),  # several groups per list
     (30000, 32, 8, 4, 50, 12, 0, F32, IP, 6000),  # equal values: more than are collected
     (90000, 32, 4, 4, 50, 3, 0, F32, L2, 60000)])  # ... more blocks than are
 def test_values_written_whole_give_the_rows_of_the_gated_scan(gpu_device, n, d, nlist, nprobe, k, nq, page, storage, metric, equal):
-    """A forced emission region sends the call through sample and gate; without it the values are written whole.  The same
+    """Without the buffer for values, or with a forced emission region, the call goes through sample and gate.  The same
     rows, bit for bit, after inserts (delta pages) and deletes too, and for two memories in one call."""
     g = torch.Generator(device="cuda").manual_seed(n + d)
     x = torch.randn((n, d), device="cuda", generator=g)
@@ -478,6 +480,8 @@ def test_values_written_whole_give_the_rows_of_the_gated_scan(gpu_device, n, d, 
     cent += 1e-3 * torch.randn(cent.shape, device="cuda", generator=g)
     q = torch.randn((nq, d), device="cuda", generator=g)
     q[0] = x[0]
+    if d == 1100:  # half of the queries ask the same lists
+        q[: nq // 2 + 1] = x[0] + 0.1 * q[: nq // 2 + 1]
     ids = torch.randperm(3 * n, device="cuda", generator=g)[:n].contiguous()
     ix, other = (B.Index(cent, rows, metric=metric, storage=storage, page_vecs=page, ids=i, insert_reserve=4096)
                  for rows, i in ((x, ids), (x[: n // 3].contiguous(), None)))
@@ -487,11 +491,18 @@ def test_values_written_whole_give_the_rows_of_the_gated_scan(gpu_device, n, d, 
                 ix.delete(ids[: n // 10].contiguous())
                 ix.insert(x[:700].contiguous(), ids[:700].contiguous())
             offs = [0, nq - nq // 3, nq]
-            whole = ix.search(q, k, nprobe), B.search_multi([ix, other], offs, q, k, nprobe)
+            with route(ix, True) as ran:
+                whole = ix.search(q, k, nprobe), B.search_multi([ix, other], offs, q, k, nprobe)
+            assert ran.whole
+            with route(ix, False):
+                gated = ix.search(q, k, nprobe), B.search_multi([ix, other], offs, q, k, nprobe)
             B.pk_index_set_emit_cap(ix.handle, 32768)
-            gated = ix.search(q, k, nprobe), B.search_multi([ix, other], offs, q, k, nprobe)
+            gated += ix.search(q, k, nprobe), B.search_multi([ix, other], offs, q, k, nprobe)
             B.pk_index_set_emit_cap(ix.handle, 0)
-            for (wi, wv), (gi, gv) in zip(whole, gated):
+            if d == 1100:
+                asked = torch.bincount(ix.coarse(q, nprobe).flatten().long())
+                assert (asked.max() > 32) == (nq > 32) and np.sort(ix.list_lengths())[-nprobe:].sum() > 8192
+            for (wi, wv), (gi, gv) in zip(whole * 2, gated):
                 assert torch.equal(wi, gi) and torch.equal(wv, gv), stage
         assert ix.stats().device_error == 0 and other.stats().device_error == 0
     finally:
@@ -521,9 +532,9 @@ def test_equal_values_beyond_what_is_collected_cost_no_more_than_the_gated_scan(
         rows, times = [], []
         for cap in (32768, 0):
             B.pk_index_set_emit_cap(ix.handle, cap)
-            out, whole = profiled(ix, lambda: ix.search(q, k, nprobe))
-            assert whole == (cap == 0) or ix.list_lengths().max() == n + 2000
-            rows.append(out)
+            with route(ix, True) as ran:
+                rows.append(ix.search(q, k, nprobe))
+            assert ran.whole == (cap == 0) or ix.list_lengths().max() == n + 2000
             start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             best = math.inf
             for _ in range(3):
@@ -537,14 +548,6 @@ def test_equal_values_beyond_what_is_collected_cost_no_more_than_the_gated_scan(
         assert times[1] < 2 * times[0] + 0.1, times
     finally:
         ix.close()
-
-
-def profiled(ix, call):
-    """What `call` returns, and whether it wrote its values whole (every candidate then counts as emitted)."""
-    B.pk_profile_begin(ix.handle)
-    out = call()
-    pr = B.pk_profile_end(ix.handle)
-    return out, pr.emitted == pr.candidates
 
 
 @pytest.mark.parametrize("n,d,nlist,storage,calls", [
@@ -567,12 +570,12 @@ def test_which_calls_write_their_values_whole(gpu_device, n, d, nlist, storage, 
     try:
         for nq, nprobe, expected in calls:
             q = mu[torch.randint(nlist, (nq,), device="cuda", generator=g)] + 0.3 * torch.randn((nq, d), device="cuda", generator=g)
-            rows, whole = profiled(ix, lambda: ix.search(q, 10, nprobe))
-            assert whole == expected, (nq, nprobe, ix.list_lengths().max())
-            B.pk_index_set_emit_cap(ix.handle, 32768)
-            gated, whole = profiled(ix, lambda: ix.search(q, 10, nprobe))
-            B.pk_index_set_emit_cap(ix.handle, 0)
-            assert not whole and torch.equal(rows[0], gated[0]) and torch.equal(rows[1], gated[1])
+            with route(ix, True) as ran:
+                rows = ix.search(q, 10, nprobe)
+            assert ran.whole == expected, (nq, nprobe, ix.list_lengths().max())
+            with route(ix, False) as ran:
+                gated = ix.search(q, 10, nprobe)
+            assert not ran.whole and torch.equal(rows[0], gated[0]) and torch.equal(rows[1], gated[1])
     finally:
         ix.close()
 
@@ -592,8 +595,10 @@ def test_searches_without_the_buffer_for_whole_values(gpu_device, reserve, nq, k
             B.pk_index_set_values_cap(ix.handle, cap)
             if reserve:
                 ix.reserve(nq, k, nprobe)
-            rows, whole = profiled(ix, lambda: ix.search(q, k, nprobe))
-            assert not whole
+            B.pk_profile_begin(ix.handle)
+            rows = ix.search(q, k, nprobe)
+            pr = B.pk_profile_end(ix.handle)
+            assert pr.emitted < pr.candidates
             return rows, ix.stats()
 
         rows, st = gated(1)
@@ -610,9 +615,9 @@ def test_searches_without_the_buffer_for_whole_values(gpu_device, reserve, nq, k
                 again, grown = gated(cap)
                 assert reserve or grown.workspace_bytes == st.workspace_bytes
             else:
-                B.pk_index_set_values_cap(ix.handle, 0)
-                again, whole = profiled(ix, lambda: ix.search(q, k, nprobe))
-                assert whole
+                with route(ix, True) as ran:
+                    again = ix.search(q, k, nprobe)
+                assert ran.whole
                 grown = ix.stats()
                 assert grown.workspace_bytes >= st.workspace_bytes + 4 * nq * width
             assert torch.equal(again[0], rows[0]) and torch.equal(again[1], rows[1])

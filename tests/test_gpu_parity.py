@@ -10,7 +10,7 @@ import torch
 
 import oracle
 from compare import check_results, recall_at
-from gpu_util import KX, Pair, dev, make_pair
+from gpu_util import KX, Pair, dev, make_pair, route
 from paper_2602_21477_amd import binding as B
 from paper_2602_21477_amd import workload as W
 import training
@@ -663,20 +663,29 @@ def test_wide_rows_many_queries_per_list(gpu_device):
 def test_hot_lists_rows_stationary_kernel(gpu_device):
     """Batches of >= 512 queries over few lists: every list is probed by hundreds of queries and goes
     to the rows-stationary kernel (64-row tiles against all slots of the list), next to regular lists;
-    ragged list tails, delta pages, more than 1024 queries on one list (two slot groups)."""
+    ragged list tails, delta pages, more than 1024 queries on one list (two slot groups).  That kernel serves the gated
+    route; memories as small as these otherwise have their values written whole, by the regular kernel alone."""
+    def check(p, q, k, nprobe, whole):
+        with route(p.gpu, whole) as ran:
+            p.check_search(q, k, nprobe)
+        assert ran.whole == whole and (ran.profile.scan_hot_ms > 0) == (not whole)
+
     cfg = W.scaled(W.C1, n=9000, ncomp=12, nlist=12)
     for storage, metric in ((F32, IP), (F16, L2), (F32, L2)):
         p, _ = make_pair(cfg, metric=metric, storage=storage, insert_reserve=2048)
         try:
             q = W.queries(cfg, 30, 640)
             say(f"hot lists storage={storage} metric={metric}: 640 queries, nprobe 6")
-            p.check_search(q, 10, 6)
+            for whole in (False, True):
+                check(p, q, 10, 6, whole)
             p.insert_both(W.inserts(cfg, 0, 700), where="hot lists")
             say("hot lists: after 700 inserts, k 100")
-            p.check_search(q, 100, 5)
+            for whole in (False, True):
+                check(p, q, 100, 5, whole)
             q2 = W.queries(cfg, 31, 1300)
             say("hot lists: 1300 queries on every list")
-            p.check_search(q2, 10, 12)
+            for whole in (False, True):
+                check(p, q2, 10, 12, whole)
         finally:
             p.close()
     # wide-ish fp16 rows (d = 768: the widest rows the kernel takes), lists of uneven length
@@ -684,25 +693,36 @@ def test_hot_lists_rows_stationary_kernel(gpu_device):
     p, _ = make_pair(cfg, metric=L2, storage=F16)
     try:
         q = W.queries(cfg, 32, 768)
-        say("hot lists: d=768 fp16, 768 queries, nprobe 16")
+        say("hot lists: d=768 fp16, 768 queries, nprobe 16: the sliced-query kernel's")
         p.check_search(q, 20, 16)
+        # (19 per list on average: regular tiles of 32 slots; the lists that more of them ask for go to the other kernel)
+        say("hot lists: d=768 fp16, 768 queries on a few lists, nprobe 1")
+        near = p.gpu.coarse(dev(W.queries(cfg, 33, 4000)), 1)[:, 0].cpu().numpy()
+        few = W.queries(cfg, 33, 4000)[np.isin(near, np.argsort(np.bincount(near, minlength=40))[-6:])]
+        q = np.concatenate([few[:400], q[:368]])
+        for whole in (False, True):
+            check(p, q, 20, 1, whole)
     finally:
         p.close()
 
 
-def test_two_tile_classes_side_by_side_on_two_streams(gpu_device):
+@pytest.mark.parametrize("whole", [False, True])
+def test_two_tile_classes_side_by_side_on_two_streams(gpu_device, whole):
     """A batch of 512 queries or more whose lists fall into both tile classes has the kernel for the lists
     many queries probe and the scan of the other lists run side by side (the second on a stream of the
     handle's own, forked from and joined to the caller's by events).  The call must stay stream-ordered for
     the caller: searches issued back to back on a stream other than the default one, with an insert between
     them, give bit for bit the rows of the same searches run one at a time between device-wide waits; those
     match the oracle; and a captured graph (under capture the two kernels run one after the other) replays
-    to the same rows."""
+    to the same rows.  (whole: the same of searches whose values are written whole, one kernel on the caller's stream.)"""
     cfg = W.scaled(W.C1, n=30000, ncomp=96, nlist=96)
     p, _ = make_pair(cfg, metric=L2, storage=F16, insert_reserve=4096)
     try:
         k, nprobe, nq = 10, 6, 768
         qs = [dev(W.queries(cfg, 40 + b, nq)) for b in range(3)]
+        asked = np.bincount(p.gpu.coarse(qs[0], nprobe).cpu().numpy().ravel(), minlength=96)
+        assert 0 < asked[asked > 0].min() <= 64 < asked.max(), "the batch has lists of both tile classes"
+        B.pk_index_set_values_cap(p.gpu.handle, 0 if whole else 1)
         new = W.inserts(cfg, 5, 300).astype(np.float16).astype(np.float32)
         say("one search at a time")
         alone = []
@@ -713,7 +733,8 @@ def test_two_tile_classes_side_by_side_on_two_streams(gpu_device):
         B.pk_profile_begin(p.gpu.handle)
         p.gpu.search(qs[0], k, nprobe)
         pr = B.pk_profile_end(p.gpu.handle)
-        assert pr.scan_hot_ms > 0 and pr.scan_ms >= pr.scan_hot_ms, "the batch has lists of both tile classes"
+        assert (pr.emitted == pr.candidates) == whole
+        assert (pr.scan_hot_ms > 0) == (not whole) and pr.scan_ms >= pr.scan_hot_ms
         say("back to back on a second stream")
         side = torch.cuda.Stream()
         with torch.cuda.stream(side):
@@ -765,11 +786,17 @@ def test_hot_lists_across_agents_in_one_call(gpu_device):
             qs.append(W.queries(cfg, 3, 400, agent=a))
             offs.append(offs[-1] + 400)
         q = np.concatenate(qs)
-        say("hot lists, two agents, one launch")
-        mi, mv = B.search_multi([p.gpu for p in pairs], offs, dev(q), 10, 8)
+        for whole in (False, True):
+            say("hot lists, two agents, one launch")
+            with route(pairs[0].gpu, whole) as ran:
+                mi, mv = B.search_multi([p.gpu for p in pairs], offs, dev(q), 10, 8)
+            assert ran.whole == whole and (ran.profile.scan_hot_ms > 0) == (not whole)
+            for a, p in enumerate(pairs):
+                with route(p.gpu, whole) as ran:
+                    si, sv = p.gpu.search(dev(qs[a]), 10, 8)
+                assert ran.whole == whole and ran.profile.scan_hot_ms == 0
+                assert torch.equal(mi[offs[a]:offs[a + 1]], si) and torch.equal(mv[offs[a]:offs[a + 1]], sv)
         for a, p in enumerate(pairs):
-            si, sv = p.gpu.search(dev(qs[a]), 10, 8)
-            assert torch.equal(mi[offs[a]:offs[a + 1]], si) and torch.equal(mv[offs[a]:offs[a + 1]], sv)
             p.check_search(qs[a], 10, 8, where=f"agent {a}")
     finally:
         for p in pairs:
@@ -784,7 +811,13 @@ def test_very_large_query_batch(gpu_device):
     try:
         q = np.concatenate([W.queries(cfg, 40 + b, 3000) for b in range(11)])  # 33 000 queries
         say("33 000 queries in one call")
-        gi, gv = p.gpu.search(dev(q), 5, 2)
+        with route(p.gpu, True) as ran:
+            wi, wv = p.gpu.search(dev(q), 5, 2)
+        assert ran.whole
+        with route(p.gpu, False) as ran:
+            gi, gv = p.gpu.search(dev(q), 5, 2)
+        assert not ran.whole and ran.profile.scan_hot_ms > 0
+        assert torch.equal(wi, gi) and torch.equal(wv, gv)
         gp = p.gpu.coarse(dev(q), 2).cpu().numpy()
         oi, ov = p.orc.scan_probes(q, 5 + KX, gp)
         check_results(gi.cpu().numpy(), gv.cpu().numpy(), oi, ov, 5, p.tol, p.scale(q), L2, where="large batch")
@@ -902,7 +935,8 @@ def test_small_batches_take_fewer_launches_and_give_the_same_results(gpu_device)
     (no launches of its own), and a few single inserts are assigned by the centroid kernel itself.  Which
     launch sequence a query goes through must not show in its result: the rows of a small call are
     bit-identical to the same queries' rows in a batch large enough for the separate work-list kernels (and,
-    with 512 queries or more, the rows-in-registers kernel for the lists many queries probe); single inserts
+    with 512 queries or more, the rows-in-registers kernel for the lists many queries probe), whether their values
+    are gated, as that batch's are, or written whole; single inserts
     and inserts of a few vectors land in the lists the oracle's rule picks."""
     cfg = W.scaled(W.C1, n=24000, nlist=96)
     for storage, metric in ((F32, IP), (F32, L2), (F16, L2)):
@@ -911,14 +945,19 @@ def test_small_batches_take_fewer_launches_and_give_the_same_results(gpu_device)
             k, nprobe, big = 10, 24, 1024  # 1024 x 24 pairs: beyond what the fused path takes
             q = np.concatenate([W.queries(cfg, 30 + b, 256) for b in range(big // 256)])
             say(f"large batch storage={storage} metric={metric}")
-            bi, bv = p.gpu.search(dev(q), k, nprobe)
+            with route(p.gpu, False) as ran:
+                bi, bv = p.gpu.search(dev(q), k, nprobe)
+            assert not ran.whole and ran.profile.scan_hot_ms > 0
             bi, bv = bi.cpu().numpy(), bv.cpu().numpy()
             p.check_search(q[:64], k, nprobe, where="64 queries on their own")
-            for lo, cnt in ((0, 1), (5, 16), (100, 48), (900, 64)):
-                say(f"small batch [{lo}, {lo + cnt})")
-                si, sv = p.gpu.search(dev(q[lo:lo + cnt]), k, nprobe)
-                assert np.array_equal(si.cpu().numpy(), bi[lo:lo + cnt]), f"ids of queries {lo}..{lo + cnt} differ"
-                assert np.array_equal(sv.cpu().numpy(), bv[lo:lo + cnt]), f"values of queries {lo}..{lo + cnt} differ"
+            for whole in (False, True):
+                for lo, cnt in ((0, 1), (5, 16), (100, 48), (900, 64)):
+                    say(f"small batch [{lo}, {lo + cnt}) whole={whole}")
+                    with route(p.gpu, whole) as ran:
+                        si, sv = p.gpu.search(dev(q[lo:lo + cnt]), k, nprobe)
+                    assert ran.whole == whole
+                    assert np.array_equal(si.cpu().numpy(), bi[lo:lo + cnt]), f"ids of queries {lo}..{lo + cnt} differ"
+                    assert np.array_equal(sv.cpu().numpy(), bv[lo:lo + cnt]), f"values of queries {lo}..{lo + cnt} differ"
             new = W.inserts(cfg, 3, 40)
             say("single inserts")
             for r in range(8):
@@ -934,7 +973,8 @@ def test_small_batch_thresholds_from_one_tile_several_tiles_and_long_samples(gpu
     (values through LDS), several tiles (values through memory, the last workgroup to finish reads them
     back) with samples of up to 1024 rows, and longer samples (a very long list in a batch of one or two
     queries asks for many pages).  Each must give the rows the oracle gives, and the rows the same queries
-    get inside a 1024-query batch, whose sample, thresholds and work list come from separate launches."""
+    get inside a 1024-query batch, whose sample, thresholds and work list come from separate launches; and both the rows
+    of calls that have no sample, as their values are written whole."""
     rng = np.random.default_rng(77)
     d, nlist = 32, 16
     cent = rng.standard_normal((nlist, d)).astype(np.float32)
@@ -950,15 +990,21 @@ def test_small_batch_thresholds_from_one_tile_several_tiles_and_long_samples(gpu
             assert p.gpu.list_lengths()[3] > 50000
             for k, nprobe in ((10, 4), (100, 3), (300, 4)):
                 say(f"large batch storage={storage} metric={metric} P={page_vecs} k={k}")
-                bi, bv = p.gpu.search(dev(q), k, nprobe)
+                with route(p.gpu, False) as ran:
+                    bi, bv = p.gpu.search(dev(q), k, nprobe)
+                assert not ran.whole
                 bi, bv = bi.cpu().numpy(), bv.cpu().numpy()
-                for lo, cnt in ((0, 1), (1, 2), (8, 8), (100, 64)):
-                    say(f"small batch [{lo}, {lo + cnt}) k={k}")
-                    si, sv = p.gpu.search(dev(q[lo:lo + cnt]), k, nprobe)
-                    assert np.array_equal(si.cpu().numpy(), bi[lo:lo + cnt]), f"ids of queries {lo}..{lo + cnt} differ (k={k})"
-                    assert np.array_equal(sv.cpu().numpy(), bv[lo:lo + cnt]), f"values of queries {lo}..{lo + cnt} differ (k={k})"
-                p.check_search(q[:2], k, nprobe, where=f"two queries k={k}")
-                p.check_search(q[100:132], k, nprobe, where=f"32 queries k={k}")
+                for whole in (False, True):
+                    for lo, cnt in ((0, 1), (1, 2), (8, 8), (100, 64)):
+                        say(f"small batch [{lo}, {lo + cnt}) k={k} whole={whole}")
+                        with route(p.gpu, whole) as ran:
+                            si, sv = p.gpu.search(dev(q[lo:lo + cnt]), k, nprobe)
+                        assert ran.whole == (whole and k < 256)
+                        assert np.array_equal(si.cpu().numpy(), bi[lo:lo + cnt]), f"ids of queries {lo}..{lo + cnt} differ (k={k})"
+                        assert np.array_equal(sv.cpu().numpy(), bv[lo:lo + cnt]), f"values of queries {lo}..{lo + cnt} differ (k={k})"
+                    with route(p.gpu, whole) as ran:
+                        p.check_search(q[:2], k, nprobe, where=f"two queries k={k}")
+                        p.check_search(q[100:132], k, nprobe, where=f"32 queries k={k}")
             assert p.gpu.stats().device_error == 0
         finally:
             p.close()
