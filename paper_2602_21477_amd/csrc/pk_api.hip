@@ -1411,25 +1411,35 @@ int note_inserted(pk_index *ix, int64_t m, hipStream_t s)
     return snapshot_pages(ix, s);
 }
 
+// Products of an assignment from which on assign_rows' first round pays for the launches that come with it.  Eight k-means
+// iterations without it and with it, us: 20 000 x 128, 64 lists (0.3e9) 1390 and 1490; 50 000 x 384, 256 lists (5e9) 2170 and 2430;
+// 50 000 x 384, 512 (10e9) 2420 and 2600; 100 000 x 96, 1024 (13e9) 3280 and 3360; 30 000 x 768, 1024 (24e9) 2870 and 2270.  But
+// also where the whole operands of a chunk are large: allocating them costs more than the launches do (50 000 x 768, 256
+// lists: one iteration 724 with 100 MB and 480 with half of that, 50 000 x 384 390 and 432).
+constexpr double kHalvesFrom = 1.5e10;
+constexpr size_t kHalvesBytes = 64u << 20;
+
 // Scratch of assign_rows for n vectors in chunks of `chunk`.
 struct AssignScratch {
-    char *xh, *ch, *cs;
+    bool halves; // assign_rows begins with the products of the first halfs alone
+    char *xh, *ch, *cs; // rows of a chunk (first halfs, or split), centroids (first halfs; split)
     float *xback, *cback, *norm, *left;
     uint32_t *second, *close, *listed, *words;
     // words: [0] rows in listed[], [1] largest squared centroid norm, [2] rows of the first chunk in listed[], [3] rows of the
     // first chunk in close[], [4] rows of the others in close[] behind them, [5] the most that first halfs leave out of a centroid
     void lay(Carver &c, int64_t n, int64_t chunk, int nlist_pad, int rb32)
     {
+        halves = (double)n * nlist_pad * (rb32 / 4) >= kHalvesFrom || (size_t)chunk * rb32 > kHalvesBytes;
         // (the last vectors, if they cannot fill tiles, are prepared in fp32: fewer than kFillChunk)
-        xh = c.take<char>(std::max((size_t)chunk * (rb32 / 2), (size_t)std::min<int64_t>(n, kFillChunk) * rb32));
-        ch = c.take<char>((size_t)nlist_pad * (rb32 / 2));
+        xh = c.take<char>(std::max((size_t)chunk * (halves ? rb32 / 2 : rb32), (size_t)std::min<int64_t>(n, kFillChunk) * rb32));
+        ch = c.take<char>(halves ? (size_t)nlist_pad * (rb32 / 2) : 0);
         cs = c.take<char>((size_t)nlist_pad * rb32);
         xback = c.take<float>((size_t)n);
         cback = c.take<float>((size_t)nlist_pad);
         norm = c.take<float>((size_t)n);
-        left = c.take<float>((size_t)n);
+        left = c.take<float>(halves ? (size_t)n : 0);
         second = c.take<uint32_t>((size_t)n);
-        close = c.take<uint32_t>((size_t)n);
+        close = c.take<uint32_t>(halves ? (size_t)n : 0);
         listed = c.take<uint32_t>((size_t)n);
         words = c.take<uint32_t>(6);
     }
@@ -1526,6 +1536,7 @@ struct InsertScratch {
 // A last chunk that cannot fill tiles (coarse_tiles) takes the centroid kernel, as an insert of its size does.  What the
 // first chunk leaves undecided says what the others are spared: a round takes a third (1 of 2) or two sevenths (2 of 3)
 // of the next one's time, so that it is the longer way from two rows in three (five in seven) on.
+// Small sets (as.halves false) go without round 1: round 2 is one launch for all rows then.
 int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const AssignScratch &as, int64_t chunk,
                 unsigned long long *best, hipStream_t s)
 {
@@ -1537,7 +1548,7 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
     const int64_t head = std::min(chunk, by_gemm);
     const uint32_t skip1_from = (uint32_t)(head / 3 * 2), skip2_from = (uint32_t)(head / 7 * 5);
     SplitGemmArgs g{};
-    g.c = as.ch;
+    g.c = as.halves ? as.ch : as.cs;
     g.q_back = as.xback;
     g.c_back = as.cback;
     g.qnorm = as.norm;
@@ -1549,18 +1560,29 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
     g.best = best;
     g.second = as.second;
     g.cmax = as.words + 1;
-    // rounds 1 (its end) and 2 of rows [first, last)
+    // what round 2, or rounds 1 (its end) and 2, leave of rows [first, last)
     auto decide = [&](int64_t first, int64_t last) -> int {
         const bool start = first == 0;
-        uint32_t *const close = as.close + first, *const n_close = as.words + (start ? 3 : 4);
         NearTiesArgs nt{};
         nt.first = (uint32_t)first;
         nt.last = (uint32_t)last;
         nt.best = best;
         nt.second = as.second;
         nt.cmax = as.words + 1;
-        nt.cmax_left = as.words + 5;
         nt.qnorm = as.norm;
+        if (!as.halves) {
+            nt.skipped = start ? nullptr : as.words + 2;
+            nt.skip_from = skip2_from;
+            nt.list = as.listed;
+            nt.nlisted = as.words;
+            nt.also = start ? as.words + 2 : nullptr;
+            nt.ld = t.ld;
+            nt.metric = t.metric;
+            PK_HIP(launch_near_ties(nt, num_cu, s));
+            return PK_OK;
+        }
+        uint32_t *const close = as.close + first, *const n_close = as.words + (start ? 3 : 4);
+        nt.cmax_left = as.words + 5;
         nt.left = as.left;
         nt.skipped = start ? nullptr : as.words + 3;
         nt.skip_from = skip1_from;
@@ -1604,31 +1626,40 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
         sr.n_c = i0 == 0 ? (uint32_t)t.nlist_pad : 0u;
         sr.d = t.d;
         sr.ld = t.ld;
-        sr.xh = as.xh;
-        sr.ch = as.ch;
+        if (as.halves) {
+            sr.xh = as.xh;
+            sr.ch = as.ch;
+            sr.left = as.left + i0;
+            sr.cmax_left = as.words + 5;
+        } else {
+            sr.xs = as.xh;
+        }
         sr.cs = as.cs;
         sr.x_back = as.xback + i0;
         sr.c_back = as.cback;
         sr.qnorm = as.norm + i0;
-        sr.left = as.left + i0;
         sr.best = best + i0;
         sr.second = as.second + i0;
         sr.cmax = as.words + 1;
-        sr.cmax_left = as.words + 5;
         PK_HIP(launch_split_rows(sr, mm, s));
         SplitGemmArgs g1 = g;
         g1.q = as.xh;
         g1.q_back += i0;
         g1.qnorm += i0;
-        g1.left = as.left + i0;
-        g1.cmax_left = as.words + 5;
         g1.best += i0;
         g1.second += i0;
         g1.m = (int)m;
-        g1.skipped = i0 > 0 ? as.words + 3 : nullptr;
-        g1.skip_from = skip1_from;
-        g1.skipped2 = i0 > 0 ? as.words + 2 : nullptr;
-        g1.skip_from2 = skip2_from;
+        if (as.halves) {
+            g1.left = as.left + i0;
+            g1.cmax_left = as.words + 5;
+            g1.skipped = i0 > 0 ? as.words + 3 : nullptr;
+            g1.skip_from = skip1_from;
+            g1.skipped2 = i0 > 0 ? as.words + 2 : nullptr;
+            g1.skip_from2 = skip2_from;
+        } else {
+            g1.skipped = i0 > 0 ? as.words + 2 : nullptr;
+            g1.skip_from = skip2_from;
+        }
         PK_HIP(launch_gemm_split(g1, num_cu, s));
         if (i0 == 0) PK_TRY(decide(0, head));
     }

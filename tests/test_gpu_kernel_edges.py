@@ -116,14 +116,22 @@ def lists_of(ix, n):
     return where
 
 
+def by_first_halves(n, d, nlist):
+    """Whether a build's (or k-means') assignment begins with the products of the first halves alone: many products, or
+    chunks of large rows."""
+    row = -(-d // 64) * 256
+    return n * -(-nlist // 32) * 32 * (row // 4) >= 1.5e10 or min(n, 32768) * row > 64 << 20
+
+
 @pytest.mark.parametrize("metric", [IP, L2])
-@pytest.mark.parametrize("nlist,kind", [(33, "plain"), (200, "plain"), (513, "plain"), (33, "huge"), (513, "huge"), (65, "nan"), (1, "plain")])
-def test_rows_without_a_comparable_score_go_to_some_list(gpu_device, nlist, kind, metric):
+@pytest.mark.parametrize("nlist,kind,d", [(33, "plain", 48), (200, "plain", 48), (513, "plain", 48), (33, "huge", 48), (513, "huge", 48), (65, "nan", 48),
+                                          (1, "plain", 48), (33, "plain", 600), (513, "plain", 600), (513, "huge", 600), (65, "nan", 600)])
+def test_rows_without_a_comparable_score_go_to_some_list(gpu_device, nlist, kind, d, metric):
     """Rows and centroids with NaN, infinities and values whose products overflow, in all three tile sizes of the
     assignment, with lists that do not fill their tiles: every row ends up in a list that exists, the rows beside it in
-    their own."""
+    their own.  (d = 600: by the first halves' products to begin with.)"""
     rng = np.random.default_rng(nlist)
-    n, d = 32768 + 16384, 48  # a chunk of each size: 256 x 256 (513 lists) or 128 x 128 tiles, then smaller ones
+    n = 32768 + 16384  # a chunk of each size: 256 x 256 (513 lists) or 128 x 128 tiles, then smaller ones
     x = rng.standard_normal((n, d)).astype(np.float32)
     cent = rng.standard_normal((nlist, d)).astype(np.float32)
     odd = np.arange(0, n, 997)
@@ -141,8 +149,9 @@ def test_rows_without_a_comparable_score_go_to_some_list(gpu_device, nlist, kind
             s = x[fine].astype(np.float64) @ cent.astype(np.float64).T
             if metric == L2:
                 s = 2 * s - (cent.astype(np.float64) ** 2).sum(1)
-            # fp32 rounding of sums of 48 products, as in the tests below
-            assert (s.max(1) - s[np.arange(len(fine)), where[fine]] <= 1e-5 * (1 + np.abs(s).max(1))).all()
+            # fp32 rounding of sums of 48 products, as in the tests below (of 600: by the root of their number more)
+            assert (s.max(1) - s[np.arange(len(fine)), where[fine]] <= 1e-5 * math.sqrt(d / 48) * (1 + np.abs(s).max(1))).all()
+        assert by_first_halves(n, d, nlist) == (d == 600)
         lists = ix.insert(dev(x[:8192]), want_lists=True).cpu().numpy()
         assert ((lists >= 0) & (lists < nlist)).all()
         assert ix.stats().device_error == 0 and ix.stats().n_total == n + 8192
@@ -207,7 +216,9 @@ def near_pairs(d, half, apart, seed, every=1):
     (2 * 32768 + 5, L2, 128, 300, 300, 1),
     (32768 + 16384, L2, 100, 192, 1, 3),  # one in three: the second chunk takes the split GEMM, too
     (16384, IP, 64, 512, 512, 200),  # a few hundred rows: small tiles of listed rows
-    (16384 + 3, L2, 36, 600, 600, 150)])
+    (16384 + 3, L2, 36, 600, 600, 150),
+    (2 * 32768 + 16384 + 70, IP, 520, 96, 32, 1),  # after the first halves: every row a near tie, found out in the first chunk
+    (32768 + 16384, L2, 600, 192, 1, 3)])  # ... one in three
 def test_near_tied_rows_of_a_build_go_where_the_fp32_scores_say(gpu_device, n, metric, d, half, apart, every):
     """Centroids that differ in the last bits of their scores: the lists are those of the fp32 coarse step, row for row."""
     cent, around = near_pairs(d, half, apart, n + d, every)
@@ -226,14 +237,17 @@ def test_near_tied_rows_of_a_build_go_where_the_fp32_scores_say(gpu_device, n, m
 
 
 @pytest.mark.parametrize("n,metric,d,half,apart,every", [
-    (16384, IP, 64, 40, 1, 1),  # 128 x 128 tiles that the lists do not fill; two steps
-    (32768 + 16384 + 3, L2, 200, 130, 130, 1),  # the rule: the second chunk goes to all three products at once; odd rows
-    (2 * 32768 + 5, IP, 33, 300, 300, 4),  # one in four: the first halves' kernel goes on; rows that are not aligned
+    (32768, IP, 600, 40, 1, 1),  # 128 x 128 tiles that the lists do not fill
+    (5 * 32768 + 5, IP, 64, 960, 960, 3),  # two steps
+    (32768 + 16384 + 3, L2, 600, 130, 130, 1),  # the rule: the second chunk goes to all three products at once; odd rows
+    (2 * 32768 + 5, IP, 603, 300, 300, 4),  # one in four: the first halves' kernel goes on; rows that are not aligned
     (65536, L2, 1536, 512, 1, 8),  # 256 x 256 tiles, the longest rows
-    (16384, L2, 256, 16, 4, 2)])  # 64 x 64 tiles
+    (16384, L2, 1300, 16, 4, 2),  # 64 x 64 tiles
+    (16384, IP, 64, 40, 1, 1), (32768 + 16384 + 3, L2, 200, 130, 130, 1), (2 * 32768 + 5, IP, 33, 300, 300, 4)])  # small sets: all three products of every row
 def test_rows_that_first_halves_cannot_tell_apart_go_where_the_fp32_scores_say(gpu_device, n, metric, d, half, apart, every):
     """Pairs of centroids that differ by 2^-11 of their elements: less than the first halves leave out, far more than
     what fp32 sums are off by.  The lists are those of the fp32 coarse step, row for row."""
+    assert by_first_halves(n, d, 2 * half) == ((n, d) not in ((16384, 64), (32768 + 16384 + 3, 200), (2 * 32768 + 5, 33)))
     cent, around = near_pairs(d, half, apart, n + d, every)
     g = torch.Generator(device="cuda").manual_seed(d)
     cent *= 1 + torch.randint(-1, 2, cent.shape, device="cuda", generator=g) * 2.0 ** -11
@@ -396,12 +410,14 @@ def test_inserts_around_the_sizes_where_their_path_changes(gpu_device, metric, s
         ix.close()
 
 
+@pytest.mark.parametrize("n,nlist", [(16384, 256), (5 * 32768, 1536)])  # (by all three products; by those of the first halves to begin with)
 @pytest.mark.parametrize("of_rows,of_lists", [(1e-24, 1.0), (1.0, 1e-24), (1e-12, 1e-12), (1e-24, 1e-10), (1e-19, 1.0)])
-def test_assignment_of_rows_whose_squared_length_is_nothing(gpu_device, of_rows, of_lists):
+def test_assignment_of_rows_whose_squared_length_is_nothing(gpu_device, of_rows, of_lists, n, nlist):
     """Inner product, rows or lists so short that their squared lengths underflow: lists that lie closer together than half
     precision can tell are still told apart as fp32 sums do, by builds and by large inserts."""
     g = torch.Generator(device="cuda").manual_seed(3)
-    n, d, nlist = 16384, 64, 256
+    d = 64
+    assert by_first_halves(n, d, nlist) == (nlist > 256)
     half = torch.randn((nlist // 2, d), device="cuda", generator=g)
     cent = torch.stack([half, half * (1 + 2.0 ** -12 * torch.randn(half.shape, device="cuda", generator=g))], 1).reshape(nlist, d) * of_lists
     # (whole numbers: what half precision leaves out of the products is then all the lists')
