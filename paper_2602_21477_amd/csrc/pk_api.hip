@@ -266,6 +266,7 @@ struct Plan {
     int mq_f, mq_h, grid_f, grid_h, grid_s, cchunks, K, nlist_max, sp;
     uint32_t hot_from;
     bool hot_rs; // the hot class is scored by the rows-in-registers kernel (tiles of kRrTileRows rows x up to kRrSlots slots)
+    double coarse_products; // products of the coarse step
     double avg_per_list; // queries per list on average (the largest over the handles of the call)
     uint32_t stride, ecap, tile_cap, span;
     uint64_t cbuf_entries; // entries of all emission regions together
@@ -419,6 +420,16 @@ constexpr int kSampleSlots = 1;
 constexpr int64_t kRoomyBatch = 128;
 // largest emission region whose overflow is provided for (see make_plan)
 constexpr uint32_t kRescueFrom = 8192;
+
+// Rows of d floats that can be read in 16-byte pieces.
+bool whole_pieces(const float *rows, int d) { return (d & 3) == 0 && (reinterpret_cast<uintptr_t>(rows) & 15) == 0; }
+
+// Most products of a coarse step whose kernel reads queries of any width and alignment as they are, float by float, for every
+// block of centroids again; a preparation launch is 5 us.  Coarse steps with the launch and without, us: 1030 wide, 333 lists, 64
+// queries (22 M) 20.8 and 18.9, 512 (176 M) 31.2 and 37; 832 lists, 2048 queries (1755 M) 102 and 175; 767 wide, 333 lists, 200
+// queries (51 M) 19.5 and 21; 411 wide, 333 lists, 200 queries (27 M) 21 and 15.5, 832 lists (68 M) 21 and 21, 512 queries (175 M)
+// 28.3 and 31.5.
+constexpr double kFoldAny = 5e7;
 
 // Limits of the calls whose values are written whole (see make_plan).
 constexpr uint64_t kDenseValues = 64u << 20; // values of a call: 256 MB
@@ -664,10 +675,11 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     // Other rows (padding, or the norms of L2): the same kernel reads them as they are too and makes the copies and norms on the
     // side, unless the GEMM wants them first or the chunked selection, which adds no norm.  A whole search of 1 query with the
     // preparation as launches of its own and without: 100 000 x 130 fp16 L2 33.2 and 29.4 us, 100 000 x 100 fp32 33.7 and 30.6;
-    // of 1024 queries 75.6 and 75.1, 81.6 and 80.2 (nowhere slower from 1 to 4096 queries, 16 to 1024 lists).
+    // of 1024 queries 75.6 and 75.1, 81.6 and 80.2.  (Rows of odd widths: kFoldAny.)
     p.fold = need_coarse && !worst && !p.raw_queries && nlist_hi <= kDenseSelectMax && tunables().densesel;
     for (int a = 0; a < nh && p.fold; ++a)
         if (coarse_by_gemm(qlo[a + 1] - qlo[a], hs[a])) p.fold = false;
+    for (int a = 0; a < nh; ++a) p.coarse_products += (double)(qlo[a + 1] - qlo[a]) * hs[a]->cfg.nlist * own->cfg.d;
     p.halves_first = need_coarse && need_fine && p.f16;
     // few lists, pairs and tiles: the threshold kernel's workgroups lay out slots and tiles as well (see wl_spread)
     p.wl_small = (uint64_t)nh * (uint64_t)nlist_hi <= kWlSmallLists && (uint64_t)nq * (uint64_t)nprobe <= 16384 && tiles <= 65536;
@@ -825,7 +837,7 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
         const bool l2 = own->cfg.metric == PK_METRIC_L2;
         ca.qs = reinterpret_cast<const char *>(q);
         ca.d = own->cfg.d;
-        ca.raw = (ca.d & 3) == 0 && (reinterpret_cast<uintptr_t>(q) & 15) == 0 ? kRawVec : kRawAny;
+        ca.raw = whole_pieces(q, ca.d) ? kRawVec : kRawAny;
         ca.meta = qm;
         if (l2) ca.norm = p.qn32;
         if (p.need_fine && !p.f16) ca.rows = p.qs32;
@@ -1164,8 +1176,10 @@ int search_impl(pk_index *const *hs, int nh, const int64_t *q_offsets, const flo
         for (int a = 0; a <= nh; ++a)
             qlo[a] = (uint32_t)std::min<int64_t>(std::max<int64_t>(q_offsets[a] - q0, 0), nq);
         Plan p;
-        auto plan = [&](bool lean, bool dense_ok) {
-            return make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, lean, dense_ok);
+        auto plan = [&](bool lean, bool dense_ok) -> int {
+            PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, lean, dense_ok));
+            if (!whole_pieces(queries, d) && p.coarse_products > kFoldAny) p.fold = false;
+            return PK_OK;
         };
         // (under capture the lists may have grown when the graph runs: by more than the host knows of)
         const bool whole_ok = mode == kFull && !capturing(s);

@@ -677,9 +677,10 @@ def test_a_work_list_without_room_scans_nothing(gpu_device, gated, d, nq, k, met
 @pytest.mark.parametrize("storage", [F32, F16])
 @pytest.mark.parametrize("metric", [IP, L2])
 @pytest.mark.parametrize("d,nlist,nq", [
-    (1, 3, 1), (63, 40, 17), (64, 130, 49), (65, 16, 200), (100, 40, 64), (130, 300, 33), (1030, 70, 12)])
+    (1, 3, 1), (63, 40, 17), (64, 130, 49), (65, 16, 200), (100, 40, 64), (130, 300, 33), (1030, 70, 12),
+    (411, 333, 365), (411, 333, 366), (1030, 832, 90), (100, 1200, 700)])  # (both sides of 5e7 products; those of 100 by their alignment only)
 def test_queries_copied_beside_the_coarse_step(gpu_device, storage, metric, d, nlist, nq):
-    """Small batches have their padded copies and norms made by the centroid kernel: the probes are the best by 64 bits, and
+    """Small batches, and larger ones of whole 16-byte pieces, have their padded copies and norms made by the centroid kernel: the probes are the best by 64 bits, and
     the rows those of a scan of the same probes, which prepares the queries by itself.  Of any alignment, over two memories."""
     g = torch.Generator(device="cuda").manual_seed(d * nlist + nq)
     n, nprobe, k = 20 * nlist, min(3, nlist // 2 + 1), 10
