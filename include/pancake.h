@@ -22,10 +22,11 @@
  *     (including arenas); the library owns only the host-side handle and a
  *     grow-only device workspace per handle that it allocates itself: tens of MB for a
  *     batch of 1024 queries, whose size follows the batch, k and nprobe, not the index, and
- *     a buffer of its own for calls of few values, which write them all: 4.25 bytes for
+ *     room for calls of few values, which write them all: 4.25 bytes for
  *     each value that the probed lists can hold for the batch and 8 for each pair of a list and
- *     a query, 288 MB at most.  Where the device has no room for that buffer, or
- *     pk_index_set_values_cap forbids it, such calls do without it, more slowly and with the same rows.
+ *     a query, 288 MB at most, in the same allocation or, where that has not the room, in a buffer
+ *     beside it.  Where the device has no memory for it, or
+ *     pk_index_set_values_cap forbids it, such calls do without, more slowly and with the same rows.
  *     The workspace grows (stream synchronisation, hipFree, hipMalloc) only when a call
  *     needs more than it holds.  pk_workspace_reserve sizes it once for every call
  *     within stated limits, inserts to come included; after that no search or insert
@@ -33,7 +34,7 @@
  *     growths).  Searches may then be captured into a HIP graph (inserts may not: they
  *     advance host-side counters); a captured search never writes its values whole, so that a
  *     replay of a call of few values takes longer than the eager call.  A graph holds pointers into
- *     the workspace (not into the buffer for values): its growth
+ *     the workspace (not into the buffer beside it, which comes and grows without harm): its growth
  *     invalidates it, so reserve before capturing; a call that would have to grow the
  *     workspace while its stream is capturing fails with PK_ERR_WORKSPACE instead.
  *     Inserts between replays are fine as long as they stay within the reserved
@@ -105,8 +106,8 @@ typedef struct {
     int64_t pages_total;     /* pages available in all arenas                          */
     int64_t pages_used;      /* pages handed to lists                                  */
     int64_t arena_bytes;     /* sum of arena sizes                                     */
-    int64_t workspace_bytes; /* current size of the library-owned search workspace, buffer for values included */
-    int64_t workspace_grows; /* calls since the build that (re)allocated either         */
+    int64_t workspace_bytes; /* current size of the library-owned search workspace, the buffer beside it included */
+    int64_t workspace_grows; /* times either was (re)allocated since the build          */
     int64_t max_list_len;    /* longest list                                           */
     int32_t device_error;    /* sticky device-side flag: 0 ok, 1 out of pages, 2 list full, 4 work list overflow */
     int32_t n_arenas;
@@ -264,8 +265,8 @@ int pk_search(pk_index *index, const float *queries, int64_t nq, int32_t k, int3
  * nprobe_max finds it large enough, until inserts_ahead more vectors have been inserted into
  * any one of the handles: such calls then never allocate and never wait for the device.
  * Calls whose queries can meet few candidates (64 million at most, over all queries and at the
- * longest lists) write all their values, into a buffer of 4.25 bytes for each of those and 16 MB at most
- * for the work list; if the device has no room for that, this call still succeeds, and they go the way of
+ * longest lists) write all their values, which takes 4.25 bytes for each of those and 16 MB at most
+ * for the work list; if the device has no memory for that, this call still succeeds, and they go the way of
  * the others.  For the others the size does not depend on how many candidates the queries meet: a
  * query's emitted candidates live in a region of a few dozen times k entries, and a query that emits
  * more (no usable threshold, or a tie group larger than the region) is selected by rescoring its rows
@@ -283,8 +284,8 @@ int pk_workspace_reserve(pk_index *const *handles, int32_t n_handles, int64_t nq
  * a small one forces queries down the rescoring path. */
 int pk_index_set_emit_cap(pk_index *index, int32_t entries);
 
-/* Limit of the handle's buffer for values that are written whole (0 = the default, what the device gives): searches
- * that need more of it go through sample and gate, with the same rows.  A buffer that is there stays. */
+/* Limit of the room for values that are written whole (0 = the default, what the device gives): searches
+ * that need more of it go through sample and gate, with the same rows.  Memory that the handle has already stays. */
 int pk_index_set_values_cap(pk_index *index, int64_t bytes);
 
 /* Test seam: most tiles that the work list of later searches on this handle has room for (0 = the default, what

@@ -92,14 +92,14 @@ struct pk_index {
     // library-owned workspace
     char *ws;
     size_t ws_bytes;
-    // values of searches that write them whole, and the slots that go with them: a buffer of its own, so that a captured
-    // search (which is gated) keeps its workspace when this one grows, and a search that cannot have it goes on without
+    // values of searches that write them whole, and the slots that go with them, where the workspace has no room for them: a
+    // buffer of its own, so that a captured search (which is gated) keeps its workspace when this one grows, and a search that
+    // cannot have it goes on without
     char *vals;
     size_t vals_bytes;
-    bool vals_inside;       // it lies behind the workspace, in the same allocation
     size_t vals_refused;    // a size that the device had no room for (0: none): not asked for again until the next reservation
     int64_t vals_cap;       // most bytes of it, set by the caller (0: what the device gives)
-    int64_t ws_grows;       // calls since the build that (re)allocated either buffer
+    int64_t ws_grows;       // allocations of either since the build
     int32_t emit_cap;       // entries of a query's emission region set by the caller (0: by k)
     int32_t tile_cap;       // most tiles of a work list, set by the caller (0: by the lists' lengths)
     // staging of scope-union searches (replicated queries, per-handle results); grow-only
@@ -167,73 +167,66 @@ bool capturing(hipStream_t s)
     return st != hipStreamCaptureStatusNone;
 }
 
-// The handle's workspace and, with vals > 0, its buffer for whole values hold at least that.  PK_ERR_NOMEM with *no_vals
-// null: no workspace.  *no_vals: the buffer cannot be had, the search goes through sample and gate in the workspace, which is
-// there.  vals_spare: what a new buffer gets beyond `vals`, as its size follows the lists' lengths.
-int ensure_ws(pk_index *ix, size_t bytes, hipStream_t s, size_t vals = 0, size_t vals_spare = 0, bool *no_vals = nullptr)
+// Where a call's whole values go: nowhere (it is gated), behind the rest of its plan in the workspace, or into the handle's
+// buffer for them.
+enum Place { kNoPlace, kInWorkspace, kInBuffer };
+
+// The handle's workspace holds at least `bytes`; with vals > 0 there is also a place for that much behind the first `before`
+// bytes of it (what a plan whose values are written whole takes of the workspace), or in the buffer for such values.
+// spare: what a new buffer gets beyond `vals`, as its size follows the lists' lengths.
+int ensure_ws(pk_index *ix, size_t bytes, hipStream_t s, size_t before = 0, size_t vals = 0, size_t spare = 0, Place *place = nullptr)
 {
-    if (vals > 0 && ((ix->vals_cap > 0 && vals > (size_t)ix->vals_cap) || (ix->vals_refused > 0 && vals >= ix->vals_refused && vals > ix->vals_bytes))) {
-        *no_vals = true;
-        vals = 0;
+    if (place) *place = kNoPlace;
+    if (ix->vals_cap > 0 && vals > (size_t)ix->vals_cap) vals = 0;
+    const bool refused = ix->vals_refused > 0 && vals >= ix->vals_refused;
+    if (bytes > ix->ws_bytes) {
+        // A captured graph would keep pointers into the buffer that is about to be freed.
+        if (capturing(s)) return PK_ERR_WORKSPACE;
+        // grow: earlier work on this handle's stream may still use the old buffers
+        PK_HIP(hipStreamSynchronize(s));
+        if (ix->ws) PK_HIP(hipFree(ix->ws));
+        ix->ws = nullptr;
+        ix->ws_bytes = 0;
+        // One allocation, large enough for the values where that can be had: a larger total or a second allocation makes the first
+        // search of a memory, and its end, 0.2 ms longer now and then.
+        const size_t least = round_up(bytes + bytes / 8, 1 << 20);
+        size_t want = vals > 0 && !refused ? std::max(least, round_up((before + vals) / 8 * 9, 1 << 20)) : least;
+        void *p = nullptr;
+        while (hipMalloc(&p, want) != hipSuccess) {
+            (void)hipGetLastError();
+            if (want == least) return PK_ERR_NOMEM;
+            ix->vals_refused = vals;
+            want = least;
+        }
+        ix->ws = static_cast<char *>(p);
+        ix->ws_bytes = want;
+        ix->ws_grows += 1;
     }
-    const bool grow = bytes > ix->ws_bytes;
-    // (a buffer inside the workspace goes with it)
-    const bool grow_vals = vals > 0 && (vals > ix->vals_bytes || (grow && ix->vals_inside));
-    if (!grow && !grow_vals) return PK_OK;
-    if (capturing(s)) {
-        // A captured graph would keep pointers into the workspace that is about to be freed.
-        if (grow) return PK_ERR_WORKSPACE;
-        *no_vals = true;
+    if (vals == 0) return PK_OK;
+    if (before + vals <= ix->ws_bytes) {
+        *place = kInWorkspace;
         return PK_OK;
     }
-    // grow: earlier work on this handle's stream may still use the old buffers
-    PK_HIP(hipStreamSynchronize(s));
-    if (ix->vals && (grow_vals || (grow && ix->vals_inside))) {
-        if (!ix->vals_inside) PK_HIP(hipFree(ix->vals));
+    if (vals > ix->vals_bytes) {
+        // (the workspace stays as it is: captured graphs refer to it, and only to it)
+        if ((ix->vals_refused > 0 && vals >= ix->vals_refused) || capturing(s)) return PK_OK;
+        PK_HIP(hipStreamSynchronize(s));
+        if (ix->vals) PK_HIP(hipFree(ix->vals));
         ix->vals = nullptr;
         ix->vals_bytes = 0;
-        ix->vals_inside = false;
-    }
-    size_t want_vals = grow_vals ? round_up(vals + vals_spare, 1 << 20) : 0;
-    if (ix->vals_cap > 0) want_vals = std::min(want_vals, (size_t)ix->vals_cap);
-    void *p = nullptr;
-    auto refuse = [&] {
-        (void)hipGetLastError();
-        ix->vals_refused = vals;
-        *no_vals = true;
-    };
-    if (!grow) {
-        if (hipMalloc(&p, want_vals) != hipSuccess) {
-            refuse();
+        size_t want = round_up(vals + spare, 1 << 20);
+        if (ix->vals_cap > 0) want = std::min(want, (size_t)ix->vals_cap);
+        void *p = nullptr;
+        if (hipMalloc(&p, want) != hipSuccess) {
+            (void)hipGetLastError();
+            ix->vals_refused = vals;
             return PK_OK;
         }
         ix->vals = static_cast<char *>(p);
-        ix->vals_bytes = want_vals;
+        ix->vals_bytes = want;
         ix->ws_grows += 1;
-        return PK_OK;
     }
-    if (ix->ws) PK_HIP(hipFree(ix->ws));
-    ix->ws = nullptr;
-    ix->ws_bytes = 0;
-    // (one allocation for both: a second one costs the first search of a memory 0.2 ms, most of it when it is freed)
-    const size_t want = round_up(bytes + bytes / 8, 1 << 20);
-    if (want_vals > 0 && hipMalloc(&p, want + want_vals) != hipSuccess) {
-        refuse();
-        want_vals = 0;
-        p = nullptr;
-    }
-    if (!p && hipMalloc(&p, want) != hipSuccess) {
-        (void)hipGetLastError();
-        return PK_ERR_NOMEM;
-    }
-    ix->ws = static_cast<char *>(p);
-    ix->ws_bytes = want;
-    if (want_vals > 0) {
-        ix->vals = ix->ws + want;
-        ix->vals_bytes = want_vals;
-        ix->vals_inside = true;
-    }
-    ix->ws_grows += 1;
+    *place = kInBuffer;
     return PK_OK;
 }
 
@@ -1196,10 +1189,10 @@ int search_impl(pk_index *const *hs, int nh, const int64_t *q_offsets, const flo
             carve(p, fixed_ws, fixed_ws + p.bytes, own);
         } else {
             PK_TRY(plan(false, whole_ok));
-            bool no_vals = false;
-            PK_TRY(ensure_ws(own, p.need, s, p.vbytes, p.vbytes / 4, &no_vals));
-            if (no_vals) PK_TRY(plan(false, false)); // (its workspace is there: p.need)
-            carve(p, own->ws, own->vals, own);
+            Place place = kNoPlace;
+            PK_TRY(ensure_ws(own, p.need, s, p.bytes, p.vbytes, p.vbytes / 4, &place));
+            if (p.dense && place == kNoPlace) PK_TRY(plan(false, false)); // (its workspace is there: p.need)
+            carve(p, own->ws, place == kInBuffer ? own->vals : own->ws + p.bytes, own);
         }
         MultiArgs m;
         fill_multi(m, hs, nh, qlo.data());
@@ -1367,7 +1360,7 @@ void destroy(pk_index *ix)
 {
     if (!ix) return;
     if (ix->ws) (void)hipFree(ix->ws);
-    if (ix->vals && !ix->vals_inside) (void)hipFree(ix->vals);
+    if (ix->vals) (void)hipFree(ix->vals);
     if (ix->ubuf) (void)hipFree(ix->ubuf);
     if (ix->ins_best) (void)hipFree(ix->ins_best);
     if (ix->pin_pages) (void)hipHostFree(ix->pin_pages);
@@ -2538,8 +2531,11 @@ int pk_workspace_reserve(pk_index *const *handles, int32_t n_handles, int64_t nq
     handles[0]->vals_refused = 0;
     size_t whole = p.vbytes;
     if (handles[0]->vals_cap > 0) whole = std::min(whole, (size_t)handles[0]->vals_cap);
-    bool no_vals = false; // (without the buffer for whole values the searches go through sample and gate)
-    return ensure_ws(handles[0], need, s, whole, 0, &no_vals);
+    Plan d = p;
+    d.dense = true; // (what such a plan takes of the workspace: as much or less)
+    carve(d, nullptr, nullptr, handles[0]);
+    Place place; // (without a place for whole values the searches go through sample and gate)
+    return ensure_ws(handles[0], need, s, d.bytes, whole, 0, &place);
 }
 
 int pk_index_set_values_cap(pk_index *ix, int64_t bytes)

@@ -3,7 +3,8 @@
 // (squared L2), Section 2.2's ranking of clusters by centroid distance, for all m, n.
 //
 // gemm_scores_kernel writes the scores: the coarse step of searches.  gemm_split_kernel finds every row's best
-// column: the assignments of large inserts and, of the rows that gemm_first_kernel leaves undecided, of build and k-means.
+// column: the assignments of large inserts, of small sets and, of the rows that gemm_first_kernel leaves undecided, of other builds
+// and k-means iterations.
 //
 // This is a dense contraction, so it runs on the matrix cores with fp32 inputs and fp32
 // accumulation (v_mfma_f32_32x32x2_f32): no down-conversion of queries or centroids, so
@@ -384,23 +385,6 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStr
     return hipGetLastError();
 }
 
-// BM x BN output tile per workgroup of WM x WN waves; K in steps of 32 elements (128 bytes of a split row) through
-// double-buffered LDS, fetched two steps ahead through two register stages (a step is short: 12 MFMAs of 32 cycles per
-// 32 x 32 x 2 blocks, and the operands come from L2).  Every row keeps its best (value key, column) by atomicMin
-// instead of writing scores: top-1 assignment, which then needs no score matrix (268 MB per 16384 rows x 4096) and no
-// selection.  Where a second column is near a row's best (in one tile, or met in memory by the tile's atomic: of two tiles
-// with near best values the later one sees the earlier) its value is kept too; the fp32 kernel then decides for the
-// rows that end up with a near second, so that every assignment is the one that kernel makes.
-// The centroids are the matrix instructions' first operand and the rows the second, so that a lane holds 16 columns of ONE
-// row per block and looks for their best without a word to its neighbours: 6 instructions a value.  (With the rows first a
-// row lay across 32 lanes, and the moves and ballots over them took 75 us of each launch: 658 -> 582 us.)
-// Bound by the chain of short steps: 256 x 256 tiles, eight waves on a CU, keep the matrix cores busy for half of the cycles
-// and LDS for 20 % (no bank conflicts); waves wait for memory and barriers a third of their time.  32768 x 4096 x 768 in
-// 582 us = 354 TFLOP/s of fp32 products, where the fp32 kernel's chunk of 16384 took 962 us = 107 and its
-// selection 194.  (Not for the coarse step of searches, 1024 x 4096 x 768 69 -> 39 us: a query's probes at a near tie would
-// then depend on which kernel its call takes.)  By its own values alone,
-// 28 rows came out on the wrong side of a near tie, against 64 bits, over seven sets of 0.5 - 1 M rows
-// (64 <= d <= 1536), and 46 by the fp32 kernel's.
 // A wave's products (blocks of 32 columns x 32 rows: lane l holds, of row m0 + l % 32 of each block, columns
 // n0 + (l / 32) * 4 + 8 * (r / 4) + r % 4) into the rows' best and near second values.  s_col: of the wave's columns.
 template <int BN, int MI, int NI>
@@ -484,7 +468,26 @@ __device__ __forceinline__ void best_of_split(const SplitGemmArgs &a, const f32x
     }
 }
 
-// LISTED: the rows are listed fp32 rows, which are split on their way into LDS, and the grid walks the tiles there are.
+// BM x BN output tile per workgroup of WM x WN waves; K in steps of 32 elements (128 bytes of a split row) through
+// double-buffered LDS, fetched two steps ahead through two register stages (a step is short: 12 MFMAs of 32 cycles per
+// 32 x 32 x 2 blocks, and the operands come from L2).  Every row keeps its best (value key, column) by atomicMin
+// instead of writing scores: top-1 assignment, which then needs no score matrix (268 MB per 16384 rows x 4096) and no
+// selection.  Where a second column is near a row's best (in one tile, or met in memory by the tile's atomic: of two tiles
+// with near best values the later one sees the earlier) its value is kept too; the fp32 kernel then decides for the
+// rows that end up with a near second, so that every assignment is the one that kernel makes.
+// The centroids are the matrix instructions' first operand and the rows the second, so that a lane holds 16 columns of ONE
+// row per block and looks for their best without a word to its neighbours: 6 instructions a value.  (With the rows first a
+// row lay across 32 lanes, and the moves and ballots over them took 75 us of each launch: 658 -> 582 us.)
+// All rows of large inserts and small sets, in tiles that give every CU one, and LISTED: rows that gemm_first_kernel leaves,
+// listed fp32 rows that are split on their way into LDS; the grid walks the tiles there are.
+// Bound by the chain of short steps: 256 x 256 tiles, eight waves on a CU, keep the matrix cores busy for half of the cycles
+// and LDS for 20 % (no bank conflicts); waves wait for memory and barriers a third of their time.  32768 x 4096 x 768 in
+// 582 us = 354 TFLOP/s of fp32 products (when every assignment took it; such sets begin with gemm_first_kernel now), where the
+// fp32 kernel's chunk of 16384 took 962 us = 107 and its
+// selection 194.  (Not for the coarse step of searches, 1024 x 4096 x 768 69 -> 39 us: a query's probes at a near tie would
+// then depend on which kernel its call takes.)  By its own values alone,
+// 28 rows came out on the wrong side of a near tie, against 64 bits, over seven sets of 0.5 - 1 M rows
+// (64 <= d <= 1536), and 46 by the fp32 kernel's.
 template <int BM, int BN, int WM, int WN, bool LISTED, bool VEC = true>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(SplitGemmArgs a)
 {
@@ -688,13 +691,17 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
         const char *const pa = base_a + at, *const pb = base_b + at;
         const uint32_t to = lds0 + (uint32_t)(ks & 3) * STEP;
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i)
-            asm volatile("s_mov_b32 m0, %0\n\t"
+        for (int i = 0; i < LOADS; ++i) {
+            uint32_t kept; // (m0 is the compiler's: it takes no clobber of it, so it is put back; the load has read it when it is issued)
+            asm volatile("s_mov_b32 %0, m0\n\t"
+                         "s_mov_b32 m0, %1\n\t"
                          "s_nop 0\n\t"
-                         "global_load_lds_dwordx4 %1, %2"
-                         :
+                         "global_load_lds_dwordx4 %2, %3\n\t"
+                         "s_mov_b32 m0, %0"
+                         : "=&s"(kept)
                          : "s"(to + (uint32_t)i * (TH * 16)), "v"(off[i]), "s"(i < ALOADS ? pa : pb)
                          : "memory");
+        }
     };
     f32x16 acc[MI][NI];
 #pragma unroll
