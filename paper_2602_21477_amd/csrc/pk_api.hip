@@ -190,7 +190,7 @@ int ensure_ws(pk_index *ix, size_t bytes, hipStream_t s, size_t before = 0, size
         // One allocation, large enough for the values where that can be had: a larger total or a second allocation makes the first
         // search of a memory, and its end, 0.2 ms longer now and then.
         const size_t least = round_up(bytes + bytes / 8, 1 << 20);
-        size_t want = vals > 0 && !refused ? std::max(least, round_up((before + vals) / 8 * 9, 1 << 20)) : least;
+        size_t want = vals > 0 && !refused ? std::max(least, round_up(before + vals + spare, 1 << 20)) : least;
         void *p = nullptr;
         while (hipMalloc(&p, want) != hipSuccess) {
             (void)hipGetLastError();
