@@ -691,17 +691,12 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
         const char *const pa = base_a + at, *const pb = base_b + at;
         const uint32_t to = lds0 + (uint32_t)(ks & 3) * STEP;
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            uint32_t kept; // (m0 is the compiler's: it takes no clobber of it, so it is put back; the load has read it when it is issued)
-            asm volatile("s_mov_b32 %0, m0\n\t"
-                         "s_mov_b32 m0, %1\n\t"
-                         "s_nop 0\n\t"
-                         "global_load_lds_dwordx4 %2, %3\n\t"
-                         "s_mov_b32 m0, %0"
-                         : "=&s"(kept)
-                         : "s"(to + (uint32_t)i * (TH * 16)), "v"(off[i]), "s"(i < ALOADS ? pa : pb)
+        for (int i = 0; i < LOADS; ++i) // (m0 is where the loads go, and an operand, so that the compiler knows what it holds)
+            asm volatile("s_nop 0\n\t"
+                         "global_load_lds_dwordx4 %1, %2"
+                         :
+                         : "{m0}"(to + (uint32_t)i * (TH * 16)), "v"(off[i]), "s"(i < ALOADS ? pa : pb)
                          : "memory");
-        }
     };
     f32x16 acc[MI][NI];
 #pragma unroll
