@@ -630,7 +630,7 @@ def measure(sc, steps, warmup, recall_queries):
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None, "traffic_source": None,
                      "measured_stream": MEASURED_STREAM_GBS, "frac_of_measured_stream": achieved / MEASURED_STREAM_GBS,
                      "measured_stream_source": MEASURED_STREAM_SOURCE,
-                     "kernel": "pk::scan_kernel + pk::scan_rr_kernel (gated list scan)",
+                     "kernel": "pk::scan_kernel, pk::scan_ks_kernel, pk::scan_rr_kernel (list scan, all launches of a search)",
                      "algorithmic_bytes_per_launch": alg_bytes, "kernel_ms": scan_ms,
                      "kernel_ms_lists_probed_by_many_queries": pr.scan_hot_ms / n},
         "stages_ms": {"coarse": pr.coarse_ms / n, "sample_and_worklist": pr.worklist_ms / n, "scan": scan_ms,
