@@ -1431,6 +1431,7 @@ struct AssignScratch {
     bool halves; // assign_rows begins with the products of the first halfs alone
     char *xh, *ch, *cs; // rows of a chunk (first halfs, or split), centroids (first halfs; split)
     float *xback, *cback, *norm, *left;
+    unsigned long long *next;
     uint32_t *second, *close, *listed, *words;
     // words: [0] rows in listed[], [1] largest squared centroid norm, [2] rows of the first chunk in listed[], [3] rows of the
     // first chunk in close[], [4] rows of the others in close[] behind them, [5] the most that first halfs leave out of a centroid
@@ -1445,6 +1446,7 @@ struct AssignScratch {
         cback = c.take<float>((size_t)nlist_pad);
         norm = c.take<float>((size_t)n);
         left = c.take<float>(halves ? (size_t)n : 0);
+        next = c.take<unsigned long long>(halves ? (size_t)n : 0);
         second = c.take<uint32_t>((size_t)n);
         close = c.take<uint32_t>(halves ? (size_t)n : 0);
         listed = c.take<uint32_t>((size_t)n);
@@ -1536,13 +1538,14 @@ struct InsertScratch {
 // Top-1 assignment of n vectors (Section 3.1: the list of the best centroid): best[i] = (score key << 32 | list), by
 // the scores of the fp32 GEMM, in three rounds, each for the rows that the one before cannot decide:
 //   1. the products of the first halfs alone, two launches per chunk and no score matrix; a row whose best two are
-//      further apart than what the halfs leave out can move them (row_margin) is done,
-//   2. all three products of the split rows (close[]: a few rows in a hundred, or a third of them in early k-means
-//      iterations), again done where the best two are not near,
+//      further apart than what the halfs leave out can move them (first_margin) is done, and one with two candidates is told
+//      by their fp32 scores (launch_pair_ties: a tenth of the rows in early k-means iterations),
+//   2. all three products of the split rows (close[]: rows with more candidates), again done where the best two are not near,
 //   3. the fp32 kernel (listed[]: usually a handful).
 // A last chunk that cannot fill tiles (coarse_tiles) takes the centroid kernel, as an insert of its size does.  What the
-// first chunk leaves undecided says what the others are spared: a round takes a third (1 of 2) or two sevenths (2 of 3)
-// of the next one's time, so that it is the longer way from two rows in three (five in seven) on.
+// first chunk leaves undecided says what the others are spared: a round is the longer way where it decides less than what it takes
+// of the next one's time.  Round 1 takes 0.4 of round 2's for rows of 768 elements and 0.6 for 128 (32768 rows x 4096 and
+// 1024 lists: 235 of 580 us, 29 of 47: a search for the best, and products), round 2 two sevenths of round 3's.
 // Small sets (as.halves false) go without round 1: round 2 is one launch for all rows then.
 int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const AssignScratch &as, int64_t chunk,
                 unsigned long long *best, hipStream_t s)
@@ -1553,7 +1556,8 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
     std::memset(&mm, 0, sizeof(mm));
     PK_HIP(launch_fill_u32(as.words, 0u, 6, s));
     const int64_t head = std::min(chunk, by_gemm);
-    const uint32_t skip1_from = (uint32_t)(head / 3 * 2), skip2_from = (uint32_t)(head / 7 * 5);
+    const double one = 0.68 + 0.00139 * t.ld, all = 0.82 + 0.00453 * t.ld; // ps per row, list: rounds 1 and 2 (128 and 768 elements)
+    const uint32_t skip1_from = (uint32_t)((double)head * (1.0 - one / all)), skip2_from = (uint32_t)(head / 7 * 5);
     SplitGemmArgs g{};
     g.c = as.halves ? as.ch : as.cs;
     g.q_back = as.xback;
@@ -1599,7 +1603,15 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
         nt.nlisted = n_close;
         nt.ld = t.ld;
         nt.metric = t.metric;
-        PK_HIP(launch_near_ties(nt, num_cu, s));
+        nt.next = as.next;
+        nt.x = x;
+        nt.cent = t.cent;
+        nt.cnorm = t.cnorm;
+        nt.d = t.d;
+        nt.redo = as.listed;
+        nt.nredo = as.words;
+        nt.also = start ? as.words + 2 : nullptr;
+        PK_HIP(launch_pair_ties(nt, num_cu, s));
         SplitGemmArgs g2 = g;
         g2.c = as.cs;
         g2.x = x;
@@ -1638,6 +1650,7 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
             sr.ch = as.ch;
             sr.left = as.left + i0;
             sr.cmax_left = as.words + 5;
+            sr.redo = as.next + i0;
         } else {
             sr.xs = as.xh;
         }
@@ -1659,6 +1672,7 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
         if (as.halves) {
             g1.left = as.left + i0;
             g1.cmax_left = as.words + 5;
+            g1.next = as.next + i0;
             g1.skipped = i0 > 0 ? as.words + 3 : nullptr;
             g1.skip_from = skip1_from;
             g1.skipped2 = i0 > 0 ? as.words + 2 : nullptr;

@@ -385,6 +385,17 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStr
     return hipGetLastError();
 }
 
+// What the value of a column that is no list begins with in the search for the best: larger than every list's (whose margins
+// are infinite where it would not be), and finite with a column in its last bits.
+constexpr float kNoList = 3.0e38f;
+// the smaller of two numbers (fminf would first quiet what might be a signalling NaN: one more instruction per value)
+__device__ __forceinline__ float least(float x, float y)
+{
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+
 // A wave's products (blocks of 32 columns x 32 rows: lane l holds, of row m0 + l % 32 of each block, columns
 // n0 + (l / 32) * 4 + 8 * (r / 4) + r % 4) into the rows' best and near second values.  s_col: of the wave's columns.
 template <int BN, int MI, int NI>
@@ -463,7 +474,7 @@ __device__ __forceinline__ void best_of_split(const SplitGemmArgs &a, const f32x
         const float v = a.metric == PK_METRIC_IP ? -next[i] * a.q_back[row[i]] : next[i];
         other = min(other, min(order_bits(v, a.metric), kWorstKey));
         const float gap = fabsf(value_of(other, a.metric) - value_of(min(met[i], key[i]), a.metric));
-        if (gap > row_margin(a.ld, a.metric, a.qnorm[row[i]], a.cmax, a.left ? a.left[row[i]] : 0.f, a.cmax_left)) continue;
+        if (gap > near_margin(a.ld, a.metric, a.qnorm[row[i]], __uint_as_float(*a.cmax))) continue;
         atomicMin(a.second + row[i], gap == gap ? other : kNoOrder);
     }
 }
@@ -635,19 +646,113 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     }
 }
 
+// A wave's products of first halfs into the rows' best, second best and third: as best_of_split, but a value carries its
+// column in its last five bits (the lane's 32 columns; what that moves it by is part of the margin), so that the
+// three smallest and the columns of two cost six instructions a value.  s_col, s_row: of the wave's columns and rows.
+template <int BM, int BN, int MI, int NI>
+__device__ __forceinline__ void best_of_first(const SplitGemmArgs &a, const f32x16 (&acc)[MI][NI], const float *s_col, const float *s_row, int m0,
+                                              int n0, int lane)
+{
+    static_assert(NI <= 2, "five bits of column");
+    const int l32 = lane & 31, kg = lane >> 5;
+    if (n0 >= a.n) return; // no column of the wave's part is a list
+    // t: smaller is nearer (inner product: -dot in the row's scale; L2: |c|^2 - 2 dot, the row's own norm left out)
+    float back[MI], factor[MI], low[MI], next[MI], third[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        back[i] = s_row[i * 32 + l32];
+        factor[i] = a.metric == PK_METRIC_L2 ? -2.f * back[i] : -1.f;
+        low[i] = next[i] = third[i] = kNoList;
+    }
+    const float *const pc = s_col + kg * 4;
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 cb = *reinterpret_cast<const f32x4 *>(pc + j * 32 + g * 8);
+            const f32x4 cn = *reinterpret_cast<const f32x4 *>(pc + BN + j * 32 + g * 8);
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float v = fmaf(acc[i][j][g * 4 + e] * cb[e], factor[i], cn[e]);
+                    const float t = __uint_as_float((__float_as_uint(v) & ~31u) | (uint32_t)(j * 16 + g * 4 + e));
+                    third[i] = __builtin_amdgcn_fmed3f(next[i], third[i], t); // (low <= next <= third)
+                    next[i] = __builtin_amdgcn_fmed3f(low[i], next[i], t);
+                    low[i] = least(low[i], t);
+                }
+        }
+    auto column = [&](float t, int half) { // of the tile
+        const uint32_t at = __float_as_uint(t) & 31u;
+        return (uint32_t)n0 + (at >> 4) * 32u + ((at >> 2) & 3u) * 8u + (at & 3u) + (uint32_t)half * 4u;
+    };
+    // either half wave goes on with every second block: the other's columns of its rows, and the row's best so far
+    unsigned long long mine[MI], met[MI];
+    uint32_t key2[MI], col2[MI], key3[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const float low2 = __shfl_xor(low[i], 32), next2 = __shfl_xor(next[i], 32), third2 = __shfl_xor(third[i], 32);
+        const bool first = low[i] <= low2;
+        const float t1 = first ? low[i] : low2, u = first ? low2 : low[i];
+        const uint32_t c1 = column(t1, first ? kg : kg ^ 1), cu = column(u, first ? kg ^ 1 : kg);
+        const bool own = next[i] <= next2;
+        const float w = own ? next[i] : next2;
+        const uint32_t cw = column(w, own ? kg : kg ^ 1);
+        const float t2 = u <= w ? u : w;
+        col2[i] = u <= w ? cu : cw;
+        const float t3 = fminf(fminf(third[i], third2), fminf(fmaxf(low[i], next2), fmaxf(next[i], low2)));
+        auto key = [&](float t) { return min(order_bits(a.metric == PK_METRIC_IP ? -t * back[i] : t, a.metric), kWorstKey); };
+        mine[i] = ((unsigned long long)key(t1) << 32) | c1;
+        key2[i] = key(t2);
+        key3[i] = key(t3);
+        met[i] = ~0ull;
+        if (((i ^ kg) & 1) == 0 && m0 + i * 32 + l32 < a.m) met[i] = atomicMin(a.best + m0 + i * 32 + l32, mine[i]);
+    }
+    // Whoever comes behind goes on to the next word (every value but a word's last least leaves it once), unless it is too
+    // far from the best so far to matter.  With three near ones in the wave alone the row has more than two candidates, and the
+    // better of those behind the best says so (it stays near a better best as long as any of them does).
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const int m = m0 + i * 32 + l32;
+        if (((i ^ kg) & 1) != 0 || m >= a.m) continue;
+        const float margin = s_row[BM + i * 32 + l32];
+        const unsigned long long lead = mine[i] < met[i] ? mine[i] : met[i], behind = mine[i] < met[i] ? met[i] : mine[i];
+        const float best = value_of((uint32_t)(lead >> 32), a.metric);
+        auto near = [&](uint32_t key) { return key != 0xffffffffu && !(fabsf(value_of(key, a.metric) - best) > margin); };
+        auto enter = [&](unsigned long long k) {
+            const unsigned long long old = atomicMin(a.next + m, k);
+            const uint32_t out = (uint32_t)((old < k ? k : old) >> 32);
+            if (out != 0xffffffffu) atomicMin(a.second + m, out);
+        };
+        const uint32_t key1 = (uint32_t)(behind >> 32);
+        if (near(key3[i])) {
+            atomicMin(a.second + m, min(key1, key2[i]));
+            continue;
+        }
+        if (near(key1)) enter(behind);
+        if (near(key2[i])) enter(((unsigned long long)key2[i] << 32) | col2[i]);
+    }
+}
+
 // The products of the first halfs alone: what decides all but a few rows of an assignment, at a third of the price.
-// Same tiles, order and epilogue as gemm_split_kernel; the operands go from memory into LDS without registers in between
+// Same tiles and order as gemm_split_kernel; the operands go from memory into LDS without registers in between
 // (one instruction per wave moves 16 rows x 64 bytes), three steps of 32 elements ahead of the one being multiplied, in
 // four buffers.  The 16-byte pieces of a row lie in the order piece ^ ((row >> 1) & 3), so that the reads of a piece of 8
 // consecutive rows meet no bank twice.  The loads are counted by hand (the compiler would wait for all of them before the
-// next LDS read): they are the only memory operations of the loop, complete in order, and a
-// step's have arrived when at most those of the two steps behind it are outstanding.  32768 x 4096 x 768 in 252 us =
-// 816 TFLOP/s, where gemm_split_kernel takes 582 for the three products; the rows it leaves undecided (a tenth of them in
-// the first k-means iteration over 4096 clusters, from random rows; fewer where the centroids are trained) cost 83 us more
-// per 32768: one such iteration over 262 144 rows 5710 -> 3729 us, the build of 300 000 x 1024 with 512 lists 2836 -> 2585.
-// Of the 252 us, 150 go to the matrix instructions at the clock they leave (timed alone), 50 to the search for the best;
-// reading the next half step's operands ahead of this one's products (253), two workgroups per CU with tiles of half the
-// size (249) and three buffers (247) change nothing, waves of 128 x 128, one per SIMD, take 289.
+// next LDS read): they are the only memory operations of a tile's steps, complete in order, and a
+// step's have arrived when at most those of the two steps behind it are outstanding (operations between two tiles only make
+// the count stricter).  Workgroups stay and walk the tiles: the last steps of a tile request the first ones of the next, and
+// its rows' and columns' factors are fetched before the search for the best, so that only that search (a fifth of the time)
+// leaves the matrix cores idle.
+// Rows keep their best two columns, and whether a third is near: two candidates are settled by pair_ties_kernel, more by the
+// products of the whole values.
+// 32768 x 4096 x 768 in 235 us = 877 TFLOP/s (252 with a workgroup per tile and eight instructions a value in the search);
+// a large library product of halfs runs at 1390 here.  150 us go to the matrix instructions at the clock they leave (timed
+// alone), and what else is done adds to that as if one after the other: with the two waves of a SIMD taking turns to read and to
+// multiply, a barrier between, and pieces in an order without bank conflicts, 234; two workgroups per CU with tiles of half the size
+// (249 of 252), three buffers (247) and operands read ahead (253) change nothing, waves of 128 x 128, one per SIMD, take 289.
+// A k-means iteration of 262 144 rows over 4096 lists 3400 -> 2920 us (a tenth of its rows have two candidates, for which
+// the products of the whole values took 0.49 ms, pair_ties_kernel takes 0.06), with every list given twice 15.4 -> 4.5 ms.
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_first_kernel(SplitGemmArgs a)
 {
@@ -657,39 +762,50 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     constexpr int LOADS = STEP / 16 / TH;           // loads per wave and step
     constexpr int ALOADS = BM * 64 / 16 / TH;       // ... of them of rows (the others: of centroids)
     static_assert((BM * 4) % TH == 0 && (BN * 4) % TH == 0, "a load is of A or of B for the whole workgroup");
-    extern __shared__ __align__(16) char smem[]; // [4][BM + BN][64], then [2][BN] floats
+    static_assert(TH >= BM + BN, "a thread per column and row of a tile");
+    extern __shared__ __align__(16) char smem[]; // [4][BM + BN][64], then [2][2][BN + BM] floats
     if (a.skipped && *a.skipped > a.skip_from) return; // near ties are the rule: the next kernel takes these rows whole
     if (a.skipped2 && *a.skipped2 > a.skip_from2) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int l32 = lane & 31, kg = lane >> 5;
     const uint32_t tn = (uint32_t)(a.n_pad + BN - 1) / BN, tm = (uint32_t)(a.m + BM - 1) / BM, total = tn * tm;
-    const uint32_t xcd = blockIdx.x & 7u, per = total / 8u, extra = total % 8u;
-    const uint32_t t = xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
-    constexpr uint32_t GM = 8;
-    const uint32_t grp = t / (GM * tn), in = t - grp * GM * tn;
-    const uint32_t gm = tm - grp * GM < GM ? tm - grp * GM : GM;
-    const int m0 = (int)(grp * GM + in % gm) * BM, n0 = (int)(in / gm) * BN;
+    auto place = [&](uint32_t b, int &m0, int &n0) { // (the order of gemm_split_kernel; b % 8 stays a workgroup's XCD)
+        const uint32_t xcd = b & 7u, per = total / 8u, extra = total % 8u;
+        const uint32_t t = xcd * per + (xcd < extra ? xcd : extra) + (b >> 3);
+        constexpr uint32_t GM = 8;
+        const uint32_t grp = t / (GM * tn), in = t - grp * GM * tn;
+        const uint32_t gm = tm - grp * GM < GM ? tm - grp * GM : GM;
+        m0 = (int)(grp * GM + in % gm) * BM;
+        n0 = (int)(in / gm) * BN;
+    };
 
     const int steps = a.ld / 32; // (two at least: rows are padded to 64 elements)
     const uint32_t row_bytes = (uint32_t)a.ld * 2u;
-    const char *const base_a = a.q + (size_t)m0 * row_bytes, *const base_b = a.c + (size_t)n0 * row_bytes;
-    uint32_t off[LOADS];
+    // what is requested next: step rk of tile rb, into buffer rg % 4
+    uint32_t rb = blockIdx.x, rg = 0, off[LOADS];
+    int rk = 0;
+    const char *base_a, *base_b;
+    auto aim = [&]() {
+        int m0, n0;
+        place(rb, m0, n0);
+        base_a = a.q + (size_t)m0 * row_bytes;
+        base_b = a.c + (size_t)n0 * row_bytes;
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-        const int piece = (i < ALOADS ? i : i - ALOADS) * TH + tid; // of the operand's part of the buffer: row piece / 4
-        int r = piece >> 2;
-        const int p = (piece & 3) ^ ((r >> 1) & 3);
-        const int last = i < ALOADS ? a.m - 1 - m0 : a.n_pad - 1 - n0;
-        r = r < last ? r : last; // rows past the end are computed and dropped
-        off[i] = (uint32_t)r * row_bytes + (uint32_t)p * 16u;
-    }
+        for (int i = 0; i < LOADS; ++i) {
+            const int piece = (i < ALOADS ? i : i - ALOADS) * TH + tid; // of the operand's part of the buffer: row piece / 4
+            int r = piece >> 2;
+            const int p = (piece & 3) ^ ((r >> 1) & 3);
+            const int last = i < ALOADS ? a.m - 1 - m0 : a.n_pad - 1 - n0;
+            r = r < last ? r : last; // rows past the end are computed and dropped
+            off[i] = (uint32_t)r * row_bytes + (uint32_t)p * 16u;
+        }
+    };
     // where this wave's loads of a step go: 1024 bytes each, lane by lane
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem + (uint32_t)wave * 1024u;
-    auto request = [&](int ks) { // (past the last step the last one again: the count of loads is the same for every step)
-        const int at = (ks < steps ? ks : steps - 1) * 64;
-        const char *const pa = base_a + at, *const pb = base_b + at;
-        const uint32_t to = lds0 + (uint32_t)(ks & 3) * STEP;
+    auto request = [&]() {
+        const char *const pa = base_a + rk * 64, *const pb = base_b + rk * 64;
+        const uint32_t to = lds0 + (rg & 3u) * STEP;
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) // (m0 is where the loads go, and an operand, so that the compiler knows what it holds)
             asm volatile("s_nop 0\n\t"
@@ -697,65 +813,112 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
                          :
                          : "{m0}"(to + (uint32_t)i * (TH * 16)), "v"(off[i]), "s"(i < ALOADS ? pa : pb)
                          : "memory");
+        ++rg;
+        if (rk + 1 < steps) {
+            ++rk;
+        } else if (rb + gridDim.x < total) {
+            rk = 0;
+            rb += gridDim.x;
+            aim();
+        } // (past the last tile's last step that step again: the count of loads is the same for every step)
     };
-    f32x16 acc[MI][NI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    // per column: what undoes its scale, and what its product is added to (a column that is no list comes behind every list)
-    float *const s_col = reinterpret_cast<float *>(smem + 4 * STEP);
-    for (int i = tid; i < BN; i += TH) {
-        const int n = n0 + i;
-        s_col[i] = n < a.n ? a.c_back[n] : 0.f;
-        s_col[BN + i] = n < a.n ? (a.metric == PK_METRIC_L2 ? a.cnorm[n] : 0.f) : INFINITY;
-    }
+    // Per column: what undoes its scale, and what its product is added to (a column that is no list comes behind every list);
+    // per row: what undoes its scale, and what values may differ by and still change places.  Fetched a tile ahead.
+    const float cmax = __uint_as_float(*a.cmax), cmax_left = __uint_as_float(*a.cmax_left);
+    float f0 = 0.f, f1 = 0.f, f2 = 0.f;
+    auto fetch_factors = [&](uint32_t b) {
+        int m0, n0;
+        place(b, m0, n0);
+        if (tid < BN) {
+            const int n = n0 + tid;
+            const int c = n < a.n ? n : 0;
+            f0 = a.c_back[c];
+            f1 = a.metric == PK_METRIC_L2 ? a.cnorm[c] : 0.f;
+            f2 = n < a.n ? 1.f : 0.f;
+        } else if (tid < BN + BM) {
+            const int m = m0 + tid - BN;
+            const int r = m < a.m ? m : a.m - 1;
+            f0 = a.q_back[r];
+            f1 = a.qnorm[r];
+            f2 = a.left[r];
+        }
+    };
+    float *const s_factors = reinterpret_cast<float *>(smem + 4 * STEP);
+    auto put_factors = [&](int parity) {
+        float *const to = s_factors + parity * 2 * (BN + BM);
+        if (tid < BN) {
+            to[tid] = f2 != 0.f ? f0 : 0.f;
+            to[BN + tid] = f2 != 0.f ? f1 : kNoList;
+        } else if (tid < BN + BM) {
+            to[2 * BN + tid - BN] = f0;
+            to[2 * BN + BM + tid - BN] = first_margin(a.ld, a.metric, f1, cmax, f2, cmax_left);
+        }
+    };
     // byte offsets inside a buffer of the 16 bytes that the lane reads of a block's row, in each half of a step
     const uint32_t sw = (uint32_t)((l32 >> 1) & 3);
     const uint32_t at0 = (uint32_t)l32 * 64u + (((uint32_t)kg) ^ sw) * 16u, at1 = (uint32_t)l32 * 64u + (((uint32_t)kg + 2u) ^ sw) * 16u;
-    request(0);
-    request(1);
-    request(2);
-    for (int ks = 0; ks < steps; ++ks) {
-        // this step's operands are there (this wave's by its count, the others' by the barrier), and every wave has read
-        // what it wanted of the step before, whose buffer the next request fills
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(2 * LOADS) : "memory");
-        request(ks + 3);
-        const char *const buf = smem + (ks & 3) * STEP;
-        const char *const pa = buf + wm * (BM / WM) * 64, *const pb = buf + (BM + wn * (BN / WN)) * 64;
+    fetch_factors(rb); // (the grid has no more workgroups than there are tiles)
+    aim();
+    request();
+    request();
+    request();
+    uint32_t gs = 0; // steps done
+    int parity = 0;
+    for (uint32_t b = blockIdx.x; b < total; b += gridDim.x, parity ^= 1) {
+        put_factors(parity); // (read after this tile's barriers; the other half may still be read by waves a tile behind)
+        f32x16 acc[MI][NI];
 #pragma unroll
-        for (int kc = 0; kc < 2; ++kc) {
-            const uint32_t at = kc ? at1 : at0;
-            half8 ah[MI], bh[NI];
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int i = 0; i < MI; ++i) ah[i] = *reinterpret_cast<const half8 *>(pa + at + i * 32 * 64);
+            for (int j = 0; j < NI; ++j)
 #pragma unroll
-            for (int j = 0; j < NI; ++j) bh[j] = *reinterpret_cast<const half8 *>(pb + at + j * 32 * 64);
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int ks = 0; ks < steps; ++ks, ++gs) {
+            // this step's operands are there (this wave's by its count, the others' by the barrier), and every wave has read
+            // what it wanted of the step before, whose buffer the next request fills
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(2 * LOADS) : "memory");
+            request();
+            const char *const buf = smem + (gs & 3u) * STEP;
+            const char *const pa = buf + wm * (BM / WM) * 64, *const pb = buf + (BM + wn * (BN / WN)) * 64;
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+            for (int kc = 0; kc < 2; ++kc) {
+                const uint32_t at = kc ? at1 : at0;
+                half8 ah[MI], bh[NI];
 #pragma unroll
-                for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[j], ah[i], acc[i][j], 0, 0, 0);
+                for (int i = 0; i < MI; ++i) ah[i] = *reinterpret_cast<const half8 *>(pa + at + i * 32 * 64);
+#pragma unroll
+                for (int j = 0; j < NI; ++j) bh[j] = *reinterpret_cast<const half8 *>(pb + at + j * 32 * 64);
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bh[j], ah[i], acc[i][j], 0, 0, 0);
+            }
         }
+        if (b + gridDim.x < total) fetch_factors(b + gridDim.x);
+        int m0, n0;
+        place(b, m0, n0);
+        const float *const s_col = s_factors + parity * 2 * (BN + BM);
+        best_of_first<BM, BN, MI, NI>(a, acc, s_col + wn * (BN / WN), s_col + 2 * BN + wm * (BM / WM), m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane);
     }
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); // nothing may still be on its way into LDS when the workgroup ends
-    best_of_split<BN, MI, NI>(a, acc, s_col + wn * (BN / WN), m0 + wm * (BM / WM), n0 + wn * (BN / WN), a.m, lane, false);
 }
 
 template <int BM, int BN, int WM, int WN>
-static hipError_t launch_split_one(const SplitGemmArgs &a, hipStream_t s)
+static hipError_t launch_split_one(const SplitGemmArgs &a, [[maybe_unused]] int num_cu, hipStream_t s)
 {
     static LdsCleared cleared, cleared_first;
     const int tiles = (a.n_pad + BN - 1) / BN * ((a.m + BM - 1) / BM);
-    if (a.left)
-        return launch_with_lds(&gemm_first_kernel<BM, BN, WM, WN>, cleared_first, 4 * (BM + BN) * 64 + 2 * BN * 4, a, tiles, WM * WN * 64, s);
+    if (a.left) { // as many workgroups as the CUs hold at a time, whole rounds of the XCDs
+        const int hold = std::max(num_cu / 8 * 8, 8) * (BM == 256 ? 1 : BM == 128 ? 2 : 4);
+        return launch_with_lds(&gemm_first_kernel<BM, BN, WM, WN>, cleared_first, 4 * (BM + BN) * 64 + 4 * (BN + BM) * 4, a, std::min(tiles, hold),
+                               WM * WN * 64, s);
+    }
     return launch_with_lds(&gemm_split_kernel<BM, BN, WM, WN, false>, cleared, 2 * (BM + BN) * 144 + 2 * BN * 4, a, tiles, WM * WN * 64, s);
 }
 
 static bool split_gemm_valid(const SplitGemmArgs &a)
 {
-    return a.ld % 64 == 0 && a.n >= 1 && a.n <= a.n_pad && a.best && !(a.second && !(a.cmax && a.qnorm)) && !a.left == !a.cmax_left;
+    return a.ld % 64 == 0 && a.n >= 1 && a.n <= a.n_pad && a.best && !(a.second && !(a.cmax && a.qnorm)) && !a.left == !a.cmax_left && !a.left == !a.next;
 }
 
 hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
@@ -764,9 +927,9 @@ hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
     if (!split_gemm_valid(a)) return hipErrorInvalidValue;
     auto tiles = [&](int b) { return (int64_t)((a.m + b - 1) / b) * ((a.n_pad + b - 1) / b); };
     // the largest tile that still gives every CU one
-    if (tiles(256) >= num_cu) return launch_split_one<256, 256, 2, 4>(a, s);
-    if (tiles(128) >= num_cu) return launch_split_one<128, 128, 2, 2>(a, s);
-    return launch_split_one<64, 64, 2, 2>(a, s);
+    if (tiles(256) >= num_cu) return launch_split_one<256, 256, 2, 4>(a, num_cu, s);
+    if (tiles(128) >= num_cu) return launch_split_one<128, 128, 2, 2>(a, num_cu, s);
+    return launch_split_one<64, 64, 2, 2>(a, num_cu, s);
 }
 
 hipError_t launch_gemm_split_listed(const SplitGemmArgs &a, int num_cu, hipStream_t s)
@@ -875,7 +1038,7 @@ __global__ __launch_bounds__(256) void near_ties_kernel(NearTiesArgs a)
         for (uint32_t u = 0; u < kEach; ++u) {
             if (!near[u]) continue;
             const uint32_t r = row[u];
-            near[u] = all || near_tie(a.best[r], a.second[r], row_margin(a.ld, a.metric, a.qnorm[r], a.cmax, a.left ? a.left[r] : 0.f, a.cmax_left), a.metric);
+            near[u] = all || near_tie(a.best[r], a.second[r], near_margin(a.ld, a.metric, a.qnorm[r], __uint_as_float(*a.cmax)), a.metric);
             count += near[u];
         }
         uint32_t upto = count; // of this thread and the lanes before it
@@ -902,6 +1065,113 @@ __global__ __launch_bounds__(256) void near_ties_kernel(NearTiesArgs a)
         }
         __syncthreads(); // (s_wave, s_at: read before the next round writes them)
     }
+}
+
+// What the products of the first halfs leave undecided.  Rows with two candidates (most of them): both fp32 scores by 16 lanes,
+// whose sum is closer to the exact one than the fp32 kernel's; further apart than near_margin, or of lists that are
+// the same bit for bit, they settle the row, else the fp32 kernel does.  Rows with more candidates go on to the products of
+// the whole values (a.list), as do all rows where the first halfs were left out.
+// Bound by latency: a pair is 3 rows of 4 ld bytes out of the caches.  229 376 rows x 768 with some 24 000 pairs 45 us; with a
+// wave per pair 77 us instead of 24 where rows are short (200 000 x 128, a third of them pairs).
+template <bool VEC>
+__global__ __launch_bounds__(256) void pair_ties_kernel(NearTiesArgs a)
+{
+    __shared__ uint32_t s_row[256], s_redo[256], s_wave[8], s_at, s_redos;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const bool all = (a.skipped && *a.skipped > a.skip_from) || (a.skipped2 && *a.skipped2 > a.skip_from2);
+    for (uint32_t i0 = a.first + blockIdx.x * 256u; i0 < a.last; i0 += gridDim.x * 256u) {
+        const uint32_t row = i0 + tid;
+        bool many = row < a.last, pair = false;
+        if (many && !all) {
+            const unsigned long long best = a.best[row], next = a.next[row];
+            const uint32_t third = a.second[row];
+            const float margin = first_margin(a.ld, a.metric, a.qnorm[row], __uint_as_float(*a.cmax), a.left[row], __uint_as_float(*a.cmax_left));
+            const float v = value_of((uint32_t)(best >> 32), a.metric);
+            auto near = [&](uint32_t key) { return key != 0xffffffffu && !(fabsf(value_of(key, a.metric) - v) > margin); };
+            const bool told = margin < INFINITY; // (else nothing is known of the row)
+            many = !told || near(third);
+            pair = !many && near((uint32_t)(next >> 32));
+        }
+        const unsigned long long mp = __ballot(pair), mm = __ballot(many), below = (1ull << lane) - 1ull;
+        if (lane == 0u) {
+            s_wave[wave] = (uint32_t)__popcll(mp);
+            s_wave[4 + wave] = (uint32_t)__popcll(mm);
+        }
+        if (tid == 0) s_redos = 0u;
+        __syncthreads();
+        uint32_t pairs = 0, rest = 0, at_pair = (uint32_t)__popcll(mp & below), at_many = (uint32_t)__popcll(mm & below);
+        for (uint32_t w = 0; w < 4; ++w) {
+            at_pair += w < wave ? s_wave[w] : 0u;
+            at_many += w < wave ? s_wave[4 + w] : 0u;
+            pairs += s_wave[w];
+            rest += s_wave[4 + w];
+        }
+        if (pair) s_row[at_pair] = row;
+        if (tid == 0 && rest) s_at = atomicAdd(a.nlisted, rest);
+        __syncthreads();
+        if (many) {
+            a.list[s_at + at_many] = row;
+            a.best[row] = ~0ull;
+            a.second[row] = 0xffffffffu;
+        }
+        const uint32_t sub = tid & 15u;
+        for (uint32_t p0 = wave * 4u; p0 < pairs; p0 += 16u) { // a pair by 16 lanes
+            const uint32_t p = p0 + (lane >> 4), r = s_row[p < pairs ? p : p0];
+            const uint32_t c1 = (uint32_t)a.best[r], c2 = (uint32_t)a.next[r];
+            const float *const x = a.x + (size_t)r * a.d, *const y1 = a.cent + (size_t)c1 * a.ld, *const y2 = a.cent + (size_t)c2 * a.ld;
+            float s1 = 0.f, s2 = 0.f;
+            uint32_t differ = 0;
+#pragma unroll 4
+            for (int i = (int)sub * 4; i < a.ld; i += 64) {
+                const f32x4 w1 = *reinterpret_cast<const f32x4 *>(y1 + i), w2 = *reinterpret_cast<const f32x4 *>(y2 + i);
+                const f32x4 v = dense_zeros(dense_load<VEC>(x, i, a.d), i, a.d);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    s1 = fmaf(v[j], w1[j], s1);
+                    s2 = fmaf(v[j], w2[j], s2);
+                    differ |= __float_as_uint(w1[j]) ^ __float_as_uint(w2[j]);
+                }
+            }
+            for (int off = 8; off > 0; off >>= 1) {
+                s1 += __shfl_xor(s1, off);
+                s2 += __shfl_xor(s2, off);
+                differ |= (uint32_t)__shfl_xor((int)differ, off);
+            }
+            const float qn = a.qnorm[r];
+            if (a.metric == PK_METRIC_L2) {
+                s1 = a.cnorm[c1] - 2.f * s1 + qn;
+                s2 = a.cnorm[c2] - 2.f * s2 + qn;
+            }
+            if (sub == 0u && p < pairs) {
+                const bool same = differ == 0u, first = same ? c1 < c2 : a.metric == PK_METRIC_L2 ? s1 < s2 : s1 > s2;
+                if (same || fabsf(s1 - s2) > near_margin(a.ld, a.metric, qn, __uint_as_float(*a.cmax)))
+                    a.best[r] = ((unsigned long long)order_bits(first ? s1 : s2, a.metric) << 32) | (first ? c1 : c2);
+                else
+                    s_redo[atomicAdd(&s_redos, 1u)] = r;
+            }
+        }
+        __syncthreads();
+        const uint32_t redos = s_redos;
+        if (tid == 0 && redos) {
+            s_at = atomicAdd(a.nredo, redos);
+            if (a.also) atomicAdd(a.also, redos);
+        }
+        __syncthreads();
+        if (tid < redos) {
+            a.redo[s_at + tid] = s_redo[tid];
+            a.best[s_redo[tid]] = ~0ull;
+        }
+        __syncthreads(); // (the lists in LDS: read before the next round writes them)
+    }
+}
+
+hipError_t launch_pair_ties(const NearTiesArgs &a, int num_cu, hipStream_t s)
+{
+    if (a.last <= a.first) return hipSuccess;
+    if (a.ld % 64 != 0 || a.d > a.ld || a.among || !a.next || !a.left || !a.cmax_left || !a.x || !a.cent || !a.redo || !a.nredo) return hipErrorInvalidValue;
+    const dim3 grid(std::min((a.last - a.first + 255u) / 256u, 8u * (uint32_t)num_cu));
+    hipLaunchKernelGGL(whole_pieces(a.x, a.d) ? pair_ties_kernel<true> : pair_ties_kernel<false>, grid, dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_near_ties(const NearTiesArgs &a, int num_cu, hipStream_t s)

@@ -603,8 +603,15 @@ struct NearTiesArgs {
     uint32_t skip_from, skip_from2;
     uint32_t *list, *nlisted, *also; // also (or null): raised as nlisted is
     int ld, metric;
+    // launch_pair_ties (rows [first, last), left and cmax_left given): best, next and second as the products of first halfs
+    // left them; rows of more than two candidates into list, pairs that fp32 sums do not settle into redo (also: raised as nredo is)
+    const unsigned long long *next;
+    const float *x, *cent, *cnorm; // dense fp32 rows [.][d]; the table [.][ld]
+    int d;
+    uint32_t *redo, *nredo;
 };
 hipError_t launch_near_ties(const NearTiesArgs &a, int num_cu, hipStream_t s);
+hipError_t launch_pair_ties(const NearTiesArgs &a, int num_cu, hipStream_t s);
 
 // Two values of a row closer than this are told apart by the fp32 kernel.  The fp32 sum of ld products, two at a time,
 // is off by about 2^-25 sqrt(ld / 2) of |x| |c| in one standard deviation (measured: 1e-6 |x|^2 between two L2 values
@@ -619,17 +626,18 @@ __device__ __forceinline__ float near_margin(int ld, int metric, float qn, float
     return 4.76837158e-7f * sqrtf((float)ld) * (metric == PK_METRIC_L2 ? qn + cmax : sqrtf(qn) * sqrtf(cmax));
 }
 
-// What two values of a row may differ by and still be in the other order for the fp32 kernel.  With `left` (of a row: the
-// length of what its first halfs leave out of it; cmax_left: the most that is of a centroid's) they are sums of the first
+// What two values of a row may differ by and still be in the other order for the fp32 kernel, where they are sums of the first
 // halfs' products alone, <x', c'> where x = x' + x", c = c' + c": off by <x", c> + <x', c">, which is
-// |x"| |c| + |x| |c"| at most (Cauchy-Schwarz; the factor covers the rounding of the lengths themselves).
-__device__ __forceinline__ float row_margin(int ld, int metric, float qn, const uint32_t *cmax, float left, const uint32_t *cmax_left)
+// |x"| |c| + |x| |c"| at most (Cauchy-Schwarz; left: |x"|, cm_left: the most |c"| is; the factor covers the rounding of the
+// lengths themselves), and have a column
+// number in their last five bits, which moves them by 2^-18.  Lengths that are no numbers, or so large that a value might not be one:
+// nothing is further apart than that.
+__device__ __forceinline__ float first_margin(int ld, int metric, float qn, float cm, float left, float cm_left)
 {
-    const float cm = __uint_as_float(*cmax);
-    const float near = near_margin(ld, metric, qn, cm);
-    if (!cmax_left) return near;
-    const float off = 1.001f * (left * sqrtf(cm) + sqrtf(qn) * __uint_as_float(*cmax_left));
-    return near + (metric == PK_METRIC_L2 ? 4.f : 2.f) * off; // (two products, and twice each under L2)
+    if (!(qn + cm < 1.32922800e36f)) return INFINITY; // 2^120
+    const float both = sqrtf(qn) * sqrtf(cm), off = 1.001f * (left * sqrtf(cm) + sqrtf(qn) * cm_left);
+    const float packed = 7.70e-6f * (metric == PK_METRIC_L2 ? cm + 2.f * both : both); // 1.01 * 2^-17
+    return near_margin(ld, metric, qn, cm) + packed + (metric == PK_METRIC_L2 ? 4.f : 2.f) * off; // (two products, and twice each under L2)
 }
 
 // Rows whose values cannot all be compared (a NaN among them: from a NaN or an infinity in the row or in a centroid, or
@@ -680,6 +688,8 @@ struct SplitGemmArgs {
     uint32_t skip_from, skip_from2;
     const float *left;        // [m] or null: the products of the first halfs alone, near by row_margin
     const uint32_t *cmax_left;
+    unsigned long long *next; // with left: [m] the second best (value key << 32 | column), where it is near the best (else all ones, as on
+                              // entry); second[] then has a value key near the best where there are more than two such columns
     // launch_gemm_split_listed: dense fp32 rows [.][d], split on the way; best, second, q_back, qnorm indexed by row like them
     const float *x;
     const uint32_t *list, *nlisted; // rows to score, and how many (on the device)

@@ -410,6 +410,46 @@ def test_inserts_around_the_sizes_where_their_path_changes(gpu_device, metric, s
         ix.close()
 
 
+@pytest.mark.parametrize("n,metric,d,half,copies", [
+    (32768, IP, 600, 40, 2),  # fewer tiles than workgroups; two candidates a row: settled by their fp32 sums, or alike bit for bit
+    (65536 + 3, L2, 603, 200, 3),  # three: the products of the whole values; rows that are not aligned
+    (5 * 32768 + 5, IP, 64, 384, 4),  # more tiles than workgroups, two steps each
+    (2 * 32768, L2, 1536, 300, 2)])  # 256 x 256 tiles, the longest rows
+def test_rows_with_several_lists_alike_go_where_the_fp32_scores_say(gpu_device, n, metric, d, half, copies):
+    """Lists that are given several times: the first copy differs by 2^-11 of its elements (less than first halves can tell), the
+    second is the same bit for bit, in tiles far apart.  The lists are those of the fp32 coarse step, row for row."""
+    assert by_first_halves(n, d, copies * half)
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    c = torch.randn((half, d), device="cuda", generator=g)
+    other = c * (1 + torch.randint(-1, 2, c.shape, device="cuda", generator=g) * 2.0 ** -11)
+    other[::3] = c[::3]
+    cent = torch.cat([c, other, c, other][:copies])
+    x = c[torch.randint(half, (n,), device="cuda", generator=g)] + 0.5 * torch.randn((n, d), device="cuda", generator=g)
+    ix = B.Index(cent, x, metric=metric)
+    try:
+        where = torch.from_numpy(lists_of(ix, n))
+        want = torch.cat([ix.coarse(x[i:i + 16384].contiguous(), 1)[:, 0].cpu() for i in range(0, n, 16384)])
+        assert torch.equal(where, want.long())
+    finally:
+        ix.close()
+
+
+@pytest.mark.parametrize("at", [0, 37, 1500])
+def test_list_whose_products_are_nothing_is_found(gpu_device, at):
+    """Inner product, every list but one on the other side of the rows and that one across them: its product is zero, and the best."""
+    n, d, nlist = 5 * 32768, 64, 1536
+    g = torch.Generator(device="cuda").manual_seed(at)
+    x, cent = torch.rand((n, d), device="cuda", generator=g), -torch.rand((nlist, d), device="cuda", generator=g) - 0.1
+    x[:, d // 2:] = 0
+    cent[at, :d // 2], cent[at, d // 2:] = 0, 1
+    ix = B.Index(cent, x, metric=IP)
+    try:
+        lengths = ix.list_lengths()
+        assert by_first_halves(n, d, nlist) and lengths[at] == n and lengths.sum() == n
+    finally:
+        ix.close()
+
+
 @pytest.mark.parametrize("n,nlist", [(16384, 256), (5 * 32768, 1536)])  # (by all three products; by those of the first halves to begin with)
 @pytest.mark.parametrize("of_rows,of_lists", [(1e-24, 1.0), (1.0, 1e-24), (1e-12, 1e-12), (1e-24, 1e-10), (1e-19, 1.0)])
 def test_assignment_of_rows_whose_squared_length_is_nothing(gpu_device, of_rows, of_lists, n, nlist):
