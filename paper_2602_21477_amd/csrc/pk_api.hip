@@ -272,6 +272,7 @@ struct Plan {
     bool halves_first; // the coarse step's preparation also makes the half-precision copy of the queries
     bool dense;       // every value of the probed rows is written, and the best selected among them: no sample, no gate
     uint32_t cap, width; // dense: slots of each list, values of each query
+    uint32_t tile_rows;  // dense: rows of a tile where there are few tiles (launch_scan_few), else 0
     bool wl_small;    // the second half of the work list is small enough for one workgroup (rides in the threshold launch)
     // buffers
     char *qs32, *qs;
@@ -371,6 +372,7 @@ struct Tunables {
     int wl_aside; // PK_TUNE_WL_ASIDE: large batches build the second half of the work list beside the sample scan
     int fuse_tau; // PK_TUNE_FUSE_TAU: small batches take sample, thresholds and work list in one launch
     int dense;    // PK_TUNE_DENSE: calls of few values write them whole (1), or go through sample and gate (0)
+    int few;      // PK_TUNE_FEW: tenths of the tiles up to which the kernel for few tiles is taken by rule (0: never)
 };
 
 #ifdef PK_DEV_TUNABLES
@@ -401,7 +403,7 @@ const Tunables &tunables()
                         env("PK_TUNE_DENSESEL", 1),  env("PK_TUNE_GRABDIV", 8),   env("PK_TUNE_HIST", 1),
                         env("PK_TUNE_RS_FROM", 0),   env("PK_TUNE_RS_NQ", 512),   env("PK_TUNE_HOT_GRAB", 1),
                         env("PK_TUNE_HOT_CUS", 96),  env("PK_TUNE_WL_ASIDE", 1),  env("PK_TUNE_FUSE_TAU", 1),
-                        env("PK_TUNE_DENSE", 1)};
+                        env("PK_TUNE_DENSE", 1),     env("PK_TUNE_FEW", 10)};
     }();
     return t;
 }
@@ -427,6 +429,7 @@ constexpr double kFoldAny = 5e7;
 // Limits of the calls whose values are written whole (see make_plan).
 constexpr uint64_t kDenseValues = 64u << 20; // values of a call: 256 MB
 constexpr uint64_t kDenseSlots = 2u << 20;   // slots of all lists: two tables of 8 MB
+constexpr uint64_t kFewTiles = 16384;        // room for tiles where they are made smaller because there are few: 512 KB
 
 int grid_for(const pk_index *ix, int row_bytes, int mq)
 {
@@ -483,6 +486,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     p.need_fine = need_fine;
     p.f16 = own->cfg.storage == PK_F16;
     p.mq_f = scan_max_mq(own->row_bytes, own->cfg.storage, own->lds_limit);
+    int want = 16;
     {
         // Query slots per scan tile: the smallest group that holds the expected number of
         // queries per probed list; small groups keep the LDS tile small and the occupancy
@@ -496,7 +500,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         for (int a = 0; a < nh; ++a)
             avg = std::max(avg, (double)(qlo[a + 1] - qlo[a]) * nprobe / hs[a]->cfg.nlist);
         p.avg_per_list = avg;
-        const int want = avg <= 6 ? 16 : (avg <= 20 ? 32 : 64);
+        want = avg <= 6 ? 16 : (avg <= 20 ? 32 : 64);
         p.mq_f = std::min(p.mq_f, tunables().mq > 0 ? tunables().mq : want);
         p.mq_h = own->cfg.storage == PK_F16 ? 64 : 32;
         p.mq_h = std::min(p.mq_h, tunables().mqh);
@@ -535,6 +539,8 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     double distinct = 0; // bytes of rows in lists that some query probes, where the queries spread evenly
     int nlist_hi = 0, pad_hi = 0;
     const int mq_least = worst ? 16 : std::min(p.mq_f, p.mq_h);
+    bool pages_of_64 = true;
+    uint32_t most_P = 32;
     const bool rs_tiles = worst ? (own->row_bytes <= 1536 && own->P % kRrTileRows == 0) : p.hot_rs;
     for (int a = 0; a < nh; ++a) {
         const pk_index *ix = hs[a];
@@ -544,6 +550,8 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         if (nqa == 0) continue;
         const uint64_t w = wq_ub(ix, nprobe, ahead);
         if (w > 0xfffffff0ull) return PK_ERR_UNSUPPORTED; // positions inside a query's range are 32-bit
+        pages_of_64 = pages_of_64 && ix->P % 64 == 0;
+        most_P = std::max(most_P, (uint32_t)ix->P);
         wmax = std::max(wmax, w);
         lmax = std::max(lmax, wq_ub(ix, 1)); // the longest list as it may be now
         bytes += (uint64_t)ix->n_total * (uint64_t)own->row_bytes;
@@ -556,6 +564,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         // list probed by more than kRrSlots queries has one tile per group of that many
         if (rs_tiles) tiles += (uint64_t)(ix->P / kRrTileRows) * pages * ((uint64_t)(nqa + kRrSlots - 1) / kRrSlots);
     }
+    if (worst) tiles += kFewTiles;
     if (tiles > 0xfffffff0ull) return PK_ERR_UNSUPPORTED;
     {
         // Sample pages per query.  The threshold is the k-th best of sp * rows sampled rows, so a list of L rows near the
@@ -663,6 +672,24 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
             p.values = values;
             p.mins = width > kReadOnce ? values / 16 : 0;
             p.slots = slots;
+            // Few tiles: smaller ones, by the kernel that has a tile per workgroup, while these leave CUs idle.  Tiles per CU (of 64
+            // rows, and as many per list as its queries take) up to which it is the faster one, over some four hundred searches of
+            // 1 - 256 queries and 10 000 - 600 000 rows of three slices and more, geometric means of the gain and the extremes: pages of
+            // 128 rows, rows of 3 - 24 slices 1.05 up to 0.8 (0.92 - 1.23), 0.97 from 1 to 2 (0.90 - 1.11), 0.95 beyond; of 256 1.12 up to 2
+            // (0.93 - 1.49), 1.06 up to 4 (0.91 - 1.24); instead of the sliced-query kernel 1.22 up to 1 (1.00 - 1.59), 1.05 up to 3 (0.95 -
+            // 1.62), 1.0 beyond.  Rows of one and two slices 0.8 - 1.04: their tiles are no chain, and twice as many cost more.
+            const uint32_t R = pages_of_64 ? 64u : 32u;
+            const uint64_t cut = tiles * (most_P / R);
+            const int mq = std::min(scan_max_mq(own->row_bytes, own->cfg.storage, own->lds_limit), want);
+            const double per_cu = distinct / own->row_bytes / R * std::max(1.0, p.avg_per_list / std::max(mq, 1)) / own->num_cu;
+            const double up_to = p.hot_from == 0 ? 3.0 : most_P >= 256 ? 4.0 : 0.8;
+            if (mq >= 16 && cut <= kFewTiles && own->row_bytes >= 3 * kIterBytes &&
+                per_cu <= up_to * 0.1 * tunables().few) {
+                p.tile_rows = R;
+                p.mq_f = mq;
+                p.hot_from = 0xffffffffu;
+                tiles = cut;
+            }
         }
     }
     // Other rows (padding, or the norms of L2): the same kernel reads them as they are too and makes the copies and norms on the
@@ -774,6 +801,7 @@ void fill_worklist_args(const Plan &p, const pk_index *own, WorklistArgs &w, Sam
     if (p.dense) {
         w.cap = p.cap;
         w.width = p.width;
+        w.tile_rows = p.tile_rows;
         w.mq = p.hot_from == 0 ? p.mq_h : p.mq_f;
         w.scalars = p.lcnt + 2 * (size_t)p.nh * p.nlist_max;
     }
@@ -947,8 +975,11 @@ int run_dense(const Plan &p, const MultiArgs &m, pk_index *own, int64_t *out_ids
     sa.tile_cap = p.tile_cap;
     sa.grab_div = tunables().grabdiv;
     // (no more workgroups than tiles)
-    const int grid = (int)std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)(sliced ? p.grid_h : p.grid_f), p.tile_cap));
-    if (!sliced) PK_HIP(launch_scan(sa, grid, s));
+    sa.slot_room = (uint32_t)p.slots;
+    const int most = p.tile_rows ? grid_for(own, own->row_bytes, p.mq_f) : sliced ? p.grid_h : p.grid_f;
+    const int grid = (int)std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)most, p.tile_cap));
+    if (p.tile_rows) PK_HIP(launch_scan_few(sa, grid, s));
+    else if (!sliced) PK_HIP(launch_scan(sa, grid, s));
     if (timed) {
         own->prof_beside.push_back(2);
         PK_TRY(mark(own, s));

@@ -278,9 +278,12 @@ struct ScanArgs {
     uint32_t *mins;              // or null: best key of every 16 values, as they lie in `out`
     uint32_t tile_cap;           // more tiles than this: the layout was refused, nothing is scanned
     int grab_div;                // tiles per grab = tiles / (grid * this), 1 .. 8
+    uint32_t slot_room;          // launch_scan_few: entries of slot_query and slot_out
 };
 hipError_t launch_scan(const ScanArgs &a, int grid, hipStream_t s);
 hipError_t launch_scan_ks(const ScanArgs &a, int grid, hipStream_t s);
+constexpr int kFewRows = 64; // most rows of a tile that launch_scan_few takes
+hipError_t launch_scan_few(const ScanArgs &a, int grid, hipStream_t s);
 hipError_t launch_scan_rr(const ScanArgs &a, int grid, hipStream_t s);
 int scan_rr_lds_bytes();
 int scan_lds_bytes(int row_bytes, int mq);
@@ -533,6 +536,7 @@ struct WorklistArgs {
     // whole layout in one go (wl_lay_query), values written whole:
     uint32_t cap;              // slots of each list (the most queries of a handle)
     uint32_t width;            // elements of each query's range
+    uint32_t tile_rows;        // rows of a tile (a divisor of every handle's page size), or 0: a page
     // one handle only: its list lengths, page size and list count, so that the work-list layout of a small batch
     // reads them without first chasing the handle's descriptor (null / 0 otherwise)
     const uint32_t *len1;

@@ -16,13 +16,14 @@
 // the caches hold are fetched that way, straight in operand layout; those of larger ones a whole
 // line at a time and past the caches, and put in that layout by moves between lanes.
 //
-// Two list-scan kernels differ in how the queries reach LDS:
+// Two list-scan kernels differ in how the queries reach LDS,
 //   scan_kernel     the whole query group (up to 64 slots x full rows) sits in LDS and is
 //                   reused over a batch of tiles: least traffic when groups are small;
 //   scan_ks_kernel  the queries are staged 256 bytes of every row at a time (double
 //                   buffered), so LDS use is independent of the row length and up to 128
 //                   slots fit: for lists probed by many queries of the batch and for rows
-//                   too wide for the first kernel to keep several workgroups per CU.
+//                   too wide for the first kernel to keep several workgroups per CU;
+// and where the tiles are few, they are cut smaller and scan_few_kernel takes one per workgroup.
 // What becomes of the values: those that pass a query's gate are emitted (large calls: most of them are never written), or all
 // are written, which needs no gate and hence neither sample nor thresholds (calls whose values are few; launches bound these).
 // sample_tau_kernel is scan_kernel's one-query form for the threshold sample of a small batch,
@@ -313,43 +314,43 @@ __device__ __forceinline__ uint32_t min_of_16(uint32_t x)
     return x;
 }
 
-// The best key of the block's two times 16 rows for every slot: what the final selection of a long range reads first.
-template <int MT>
-__device__ __forceinline__ void write_mins(const ScanArgs &a, const Slots &s, const f32x4 (&acc)[MT][2], int rb, int ln, int lg, int nrows,
+// The best key of each of the block's NB times 16 rows for every slot: what the final selection of a long range reads first.
+template <int MT, int NB>
+__device__ __forceinline__ void write_mins(const ScanArgs &a, const Slots &s, const f32x4 (&acc)[MT][NB], int rb, int ln, int lg, int nrows,
                                            uint32_t qcnt, uint32_t row0, gfloats txn)
 {
-    constexpr int MQ = MT * 16;
-    float xn[2] = {0.f, 0.f};
+    constexpr int MQ = MT * 16, ROWS = NB * 16;
+    float xn[NB] = {};
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-        const int row = rb * kRowBlock + nt * 16 + ln;
+    for (int nt = 0; nt < NB; ++nt) {
+        const int row = rb * ROWS + nt * 16 + ln;
         if (a.metric == PK_METRIC_L2 && row < nrows) xn[nt] = txn[row];
     }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         if ((uint32_t)(mt * 16) >= qcnt) break; // wave-uniform
-        uint32_t mine = 0xffffffffu; // lane ln < 8 of a group: of its slot ln & 3 and 16 rows ln >> 2
+        uint32_t mine = 0xffffffffu; // lane ln < 4 NB of a group: of its slot ln & 3 and 16 rows ln >> 2
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < NB; ++nt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float v = acc[mt][nt][i];
                 if (a.metric == PK_METRIC_L2) v = l2_from_dot(xn[nt], v, s.qn[(mt * 16 + lg * 4 + i) & (MQ - 1)]);
-                const uint32_t best = min_of_16(rb * kRowBlock + nt * 16 + ln < nrows ? order_bits(v, a.metric) : 0xffffffffu);
+                const uint32_t best = min_of_16(rb * ROWS + nt * 16 + ln < nrows ? order_bits(v, a.metric) : 0xffffffffu);
                 mine = ln == nt * 4 + i ? best : mine;
             }
-        const int m = mt * 16 + lg * 4 + (ln & 3), first = rb * kRowBlock + (ln >> 2) * 16;
-        if (ln < 8 && (uint32_t)m < qcnt && first < nrows && s.out[m] != 0xffffffffu) a.mins[(s.out[m] + row0 + (uint32_t)first) >> 4] = mine;
+        const int m = mt * 16 + lg * 4 + (ln & 3), first = rb * ROWS + (ln >> 2) * 16;
+        if (ln < 4 * NB && (uint32_t)m < qcnt && first < nrows && s.out[m] != 0xffffffffu) a.mins[(s.out[m] + row0 + (uint32_t)first) >> 4] = mine;
     }
 }
 
-// Epilogue of one 32-row block: the lane holds rows (rb*32 + nt*16 + ln) for slots
+// Epilogue of one block of NB times 16 rows (32 where gated): the lane holds rows (rb*16*NB + nt*16 + ln) for slots
 // mt*16 + lg*4 + i.  Dense mode writes every value; gated mode emits the survivors.
 // COHERENT (dense mode): the values are written through to where every CU of the device reads them
 // (another workgroup of the same launch goes on to read them).
 // LAID: a query whose values have no place is left out.
-template <int MT, bool GATED, bool COHERENT = false, bool LAID = false>
-__device__ __forceinline__ void finish_block(const ScanArgs &a, const Slots &s, f32x4 (&acc)[MT][2], int rb, int ln, int lg,
+template <int MT, bool GATED, bool COHERENT = false, bool LAID = false, int NB = 2>
+__device__ __forceinline__ void finish_block(const ScanArgs &a, const Slots &s, f32x4 (&acc)[MT][NB], int rb, int ln, int lg,
                                              int nrows, uint32_t qcnt, uint32_t row0, gfloats txn, float *lds_vals = nullptr)
 {
     if constexpr (GATED) {
@@ -359,11 +360,11 @@ __device__ __forceinline__ void finish_block(const ScanArgs &a, const Slots &s, 
         const float worst = a.metric == PK_METRIC_IP ? -INFINITY : INFINITY;
         const int nrows_pad = (nrows + 15) & ~15;
         if constexpr (LAID) {
-            if (a.mins) write_mins<MT>(a, s, acc, rb, ln, lg, nrows, qcnt, row0, txn);
+            if (a.mins) write_mins<MT, NB>(a, s, acc, rb, ln, lg, nrows, qcnt, row0, txn);
         }
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int row = rb * kRowBlock + nt * 16 + ln;
+        for (int nt = 0; nt < NB; ++nt) {
+            const int row = rb * (NB * 16) + nt * 16 + ln;
             const bool live = row < nrows;
             float xn = 0.f;
             if (a.metric == PK_METRIC_L2 && live) xn = txn[row];
@@ -694,6 +695,106 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
         return;
     }
     scan_body<STORAGE, 1, 4, kSample, true, false>(a, smem, blockIdx.x - nq, gridDim.x - nq, &sm, extra_off);
+}
+
+// ------------------------------------------------------------------ scans of few tiles
+
+// wl_lay_query's tiles where the chip holds all of them at once: every workgroup has one, and the call takes as long as it
+// does, a chain of round trips to memory.  So tiles are of 64 rows, 16 a wave, which leaves registers for four slices of them:
+// three are on their way while one is multiplied, and the first are requested together with the slots and queries.  Same
+// instructions per row and query as in scan_kernel, so the same values.  Of what is left, the products of a row are a third: they
+// depend on each other (16 instructions of 32 cycles a slice in fp32).  us, scan_kernel or scan_ks_kernel and this one:
+// 27 311 x 896, 6 queries of 19 of 213 lists 31.4 and 14.5; 14 445 x 640, 5 of 5 of 128 27.6 and 12.7; 78 578 x 1418, one query of 17 of
+// 617 (sliced queries) 54.2 and 19.2; 300 000 x 1024, 4 of 16 of 512 (146 MB: 4.4 TB/s) 38.6 and 32.7.
+template <int STORAGE, int MT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void scan_few_kernel(ScanArgs a)
+{
+    extern __shared__ __align__(16) char smem[];
+    constexpr int MQ = MT * 16;
+    const int row_bytes = a.row_bytes, qstride = row_bytes + kQPadBytes, nit = row_bytes / kIterBytes;
+    Slots s;
+    s.carve(smem + (size_t)MQ * qstride, MQ);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ln = lane & 15, lg = lane >> 4;
+    const uint32_t lane_off = RowLoad<false>::lane_offset(ln, lg, row_bytes);
+    const uint32_t chunks = (uint32_t)row_bytes / 16u, per_chunks = 0xffffffffu / chunks + 1u; // (x / chunks for x below 2^32 / chunks)
+    Tile cur = a.tiles[blockIdx.x];                                                            // (no more workgroups than there is room for tiles)
+    uint32_t nt = *a.ntiles;
+    if (nt > a.tile_cap) nt = 0;
+    for (uint32_t t = blockIdx.x; t < nt; t += gridDim.x) {
+        if (t != blockIdx.x) {
+            __syncthreads(); // the tile before is done with LDS
+            cur = a.tiles[t];
+        }
+        const uint32_t qbeg = __builtin_amdgcn_readfirstlane(cur.qbeg);
+        const int nrows = __builtin_amdgcn_readfirstlane((int)cur.nrows);
+        const bool active = wave * 16 < nrows;
+        // (a wave without rows of its own reads the tile's first ones again)
+        const gbytes rows = uniform(in_global(cur.x)) + (active ? (size_t)(wave * 16) * row_bytes : 0);
+        u32x4 x0[4], x1[4], x2[4], x3[4];
+        auto load = [&](u32x4 (&buf)[4], int it) { // (past the last slice the last one again: no load under a condition)
+            const int at = it < nit ? it : nit - 1;
+#pragma unroll
+            for (int s4 = 0; s4 < 4; ++s4) buf[s4] = RowLoad<false>::load(rows, lane_off, at, s4, row_bytes);
+        };
+        const uint32_t in_list = __builtin_amdgcn_readfirstlane(a.lcnt[cur.list]);
+        uint32_t slot = qbeg + (uint32_t)tid;
+        slot = slot < a.slot_room ? slot : a.slot_room - 1u; // (not looked at where there is no such slot)
+        const uint32_t sq = tid < MQ ? a.slot_query[slot] : 0u, out = tid < MQ ? a.slot_out[slot] : 0u;
+        load(x0, 0);
+        load(x1, 1);
+        load(x2, 2);
+        const uint32_t left = in_list - (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)cur.qcnt) * (uint32_t)MQ;
+        const uint32_t qcnt = left < (uint32_t)MQ ? left : (uint32_t)MQ;
+        const int mt_used = (int)((qcnt + 15u) >> 4);
+        if ((uint32_t)tid < qcnt) {
+            s.q[tid] = sq;
+            s.out[tid] = out;
+            if (a.metric == PK_METRIC_L2) s.qn[tid] = a.qnorm[sq];
+        }
+        __syncthreads();
+        // the slots' queries (what rows without a slot hold meets no value that is written)
+        const uint32_t pieces = qcnt * chunks;
+        for (uint32_t i0 = (uint32_t)tid; i0 < pieces; i0 += 4u * 256u) {
+            u32x4 v[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4u; ++u) {
+                const uint32_t i = i0 + u * 256u < pieces ? i0 + u * 256u : i0, m = __umulhi(i, per_chunks);
+                v[u] = *reinterpret_cast<const u32x4 *>(a.qs + (size_t)s.q[m] * row_bytes + (size_t)(i - m * chunks) * 16);
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < 4u; ++u) {
+                const uint32_t i = i0 + u * 256u, m = __umulhi(i, per_chunks);
+                if (i < pieces) *reinterpret_cast<u32x4 *>(smem + (size_t)m * qstride + (size_t)(i - m * chunks) * 16) = v[u];
+            }
+        }
+        __syncthreads();
+        f32x4 acc[MT][1];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[mt][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const char *const qbase = smem + (size_t)ln * qstride + lg * 16;
+        auto multiply = [&](u32x4 (&buf)[4], int it) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                if (mt < mt_used) {
+                    const char *const qrow = qbase + (size_t)mt * 16 * qstride + (size_t)it * kIterBytes;
+#pragma unroll
+                    for (int s4 = 0; s4 < 4; ++s4) mfma_step<STORAGE>(acc[mt][0], *reinterpret_cast<const u32x4 *>(qrow + s4 * 64), buf[s4]);
+                }
+            }
+        };
+        for (int it = 0; it < nit; it += 4) {
+            load(x3, it + 3);
+            multiply(x0, it);
+            load(x0, it + 4);
+            if (it + 1 < nit) multiply(x1, it + 1);
+            load(x1, it + 5);
+            if (it + 2 < nit) multiply(x2, it + 2);
+            load(x2, it + 6);
+            if (it + 3 < nit) multiply(x3, it + 3);
+        }
+        if (active) finish_block<MT, false, false, true, 1>(a, s, acc, wave, ln, lg, nrows, qcnt, cur.row0, in_global(cur.xn));
+    }
 }
 
 // ------------------------------------------------------------------ sliced-query kernel
@@ -1263,6 +1364,27 @@ hipError_t launch_scan(const ScanArgs &a, int grid, hipStream_t s)
 {
     if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0) return hipErrorInvalidValue;
     return a.storage == PK_F16 ? launch_scan_of<PK_F16>(a, grid, s) : launch_scan_of<PK_F32>(a, grid, s);
+}
+
+template <int STORAGE, int MT>
+static hipError_t launch_few_one(const ScanArgs &a, int grid, hipStream_t s)
+{
+    static LdsCleared cleared;
+    return launch_with_lds(&scan_few_kernel<STORAGE, MT>, cleared, scan_lds_bytes(a.row_bytes, a.mq), a, grid, 256, s);
+}
+
+// wl_lay_query's tiles of at most kFewRows rows (grid: at most as many workgroups as there is room for tiles)
+hipError_t launch_scan_few(const ScanArgs &a, int grid, hipStream_t s)
+{
+    if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || !a.lcnt || a.slot_room == 0 || a.tile_cap == 0 || grid < 1 || (uint32_t)grid > a.tile_cap)
+        return hipErrorInvalidValue;
+    const bool f16 = a.storage == PK_F16;
+    switch (a.mq) {
+    case 16: return f16 ? launch_few_one<PK_F16, 1>(a, grid, s) : launch_few_one<PK_F32, 1>(a, grid, s);
+    case 32: return f16 ? launch_few_one<PK_F16, 2>(a, grid, s) : launch_few_one<PK_F32, 2>(a, grid, s);
+    case 64: return f16 ? launch_few_one<PK_F16, 4>(a, grid, s) : hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+    }
 }
 
 // the sliced-query kernel (fine search only; fp32 rows are held to 32 slots)

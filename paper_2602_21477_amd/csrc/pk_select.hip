@@ -187,13 +187,13 @@ __global__ __launch_bounds__(kSelThreads) void select_probes_kernel(const u64 *p
 // equal to it as are needed, lowest positions first, are collected and sorted.  Positions
 // are list numbers, so ties go to the lower list number.
 // GO_ON: the workgroup goes on to do its query's share of the work-list construction (kCount: pairs per list,
-// candidate layout, sample tiles; kLay: all of it), which saves the launch that would otherwise follow the selection.
-enum GoOn { kStop, kCount, kLay };
+// candidate layout, sample tiles; kLay, kLayCut: all of it), which saves the launch that would otherwise follow the selection.
+enum GoOn { kStop, kCount, kLay, kLayCut };
 // keys that the selection of K probes holds in LDS: 256 within a bound, or K and what rounds them up to a power of two; two of padding
 __device__ __host__ __forceinline__ uint32_t dense_keys(uint32_t K) { return (K <= 256u ? 256u : K <= 512u ? 512u : 1024u) + 2u; }
 static size_t dense_lds(uint32_t K, GoOn go_on)
 {
-    const size_t wl = go_on == kCount ? WlCountLds::bytes(K) : go_on == kLay ? WlLayLds::bytes(K) : 0;
+    const size_t wl = go_on == kCount ? WlCountLds::bytes(K) : go_on == kLay || go_on == kLayCut ? WlLayLds::bytes(K) : 0;
     return 4096 + dense_keys(K) * sizeof(u64) + K * sizeof(int32_t) + wl;
 }
 template <int VPT, GoOn GO_ON>
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, co
     u64 *const sel = reinterpret_cast<u64 *>(s_dyn + 4096);            // [dense_keys(K)]
     constexpr bool COUNT = GO_ON != kStop;
     int32_t *const s_probe = reinterpret_cast<int32_t *>(sel + dense_keys((uint32_t)K)); // [K]
-    [[maybe_unused]] std::conditional_t<GO_ON == kCount, WlCountLds, std::conditional_t<GO_ON == kLay, WlLayLds, uint32_t>> s_wl;
+    [[maybe_unused]] std::conditional_t<GO_ON == kCount, WlCountLds, std::conditional_t<GO_ON == kLay || GO_ON == kLayCut, WlLayLds, uint32_t>> s_wl;
     if constexpr (COUNT) s_wl.carve(reinterpret_cast<uint32_t *>(s_probe + K), (uint32_t)K);
     PK_MARK(sel, 0);
     const uint32_t q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -320,7 +320,8 @@ __global__ __launch_bounds__(256) void select_dense_kernel(const float *vals, co
     if constexpr (COUNT) {
         __syncthreads(); // the probe list is in s_probe
         if constexpr (GO_ON == kCount) wl_count_query(wa, sm, ma, q, s_wl, s_probe, probes + (size_t)q * K, view);
-        if constexpr (GO_ON == kLay) wl_lay_query(wa, ma, q, s_wl, s_probe, probes + (size_t)q * K, view);
+        if constexpr (GO_ON == kLay) wl_lay_query<false>(wa, ma, q, s_wl, s_probe, probes + (size_t)q * K, view);
+        if constexpr (GO_ON == kLayCut) wl_lay_query<true>(wa, ma, q, s_wl, s_probe, probes + (size_t)q * K, view);
         PK_MARK(sel, 7);
     }
 }
@@ -344,7 +345,8 @@ hipError_t launch_select_dense(const float *vals, const uint32_t *qoff, const ui
         };
         if (!wa) run(select_dense_kernel<VPT, kStop>, kStop);
         else if (wa->width == 0) run(select_dense_kernel<VPT, kCount>, kCount);
-        else run(select_dense_kernel<VPT, kLay>, kLay);
+        else if (wa->tile_rows == 0) run(select_dense_kernel<VPT, kLay>, kLay);
+        else run(select_dense_kernel<VPT, kLayCut>, kLayCut);
     };
     if (max_cnt <= 1024) go(std::integral_constant<int, 4>{});
     else if (max_cnt <= 4096) go(std::integral_constant<int, 16>{});

@@ -150,7 +150,7 @@ __device__ __forceinline__ void wl_count_query(const WorklistArgs &a, const Samp
 
 // The whole work list, by the workgroups of the coarse selection (one of 256 threads per query; same arguments as above)
 // and without a word between them.  A pair's slot is the next one of its list, which has room for a.cap; the pair that
-// opens a group of a.mq slots also writes the group's tiles, one per page, in a range taken from the tile counter: how
+// opens a group of a.mq slots also writes the group's tiles, one per page (CUT: per a.tile_rows rows), in a range taken from the tile counter: how
 // many slots the group will have is read from the pair counters by the scan.  Needs no prefix sums over the lists and no
 // sample: for calls whose values are written whole (a.width per query).
 struct WlLayLds {
@@ -175,11 +175,12 @@ struct WlLayLds {
         first = wave + 17;
     }
 };
+template <bool CUT>
 __device__ __forceinline__ void wl_lay_query(const WorklistArgs &a, const MultiArgs &m, uint32_t q, WlLayLds &s,
                                              const int32_t *probes_q, int32_t *probes_out, const WlIndexView &v)
 {
     const DevIndex &ix = *v.ix;
-    const uint32_t P = v.P, np = (uint32_t)a.nprobe, tid = threadIdx.x, mq = (uint32_t)a.mq;
+    const uint32_t P = v.P, np = (uint32_t)a.nprobe, tid = threadIdx.x, mq = (uint32_t)a.mq, R = CUT ? a.tile_rows : P;
     unsigned long long rows = 0; // of the lists that this query is the first to probe
     for (uint32_t r = tid; r < np; r += blockDim.x) {
         const uint32_t l = (uint32_t)probes_q[r];
@@ -191,7 +192,7 @@ __device__ __forceinline__ void wl_lay_query(const WorklistArgs &a, const MultiA
         s.len[r] = len;
         s.slot[r] = slot;
         s.po[r] = (len + 15u) & ~15u; // segments are padded to the 16-row MFMA tile
-        s.to[r] = slot % mq == 0u ? (len + P - 1u) / P : 0u;
+        s.to[r] = slot % mq == 0u ? (len + R - 1u) / R : 0u;
         if (slot == 0u) rows += len;
     }
     __syncthreads();
@@ -258,17 +259,17 @@ __device__ __forceinline__ void wl_lay_query(const WorklistArgs &a, const MultiA
             if (s.to[mid] <= t) lo = mid;
             else hi = mid - 1;
         }
-        const uint32_t l = (uint32_t)probes_q[lo], p = t - s.to[lo];
+        const uint32_t l = (uint32_t)probes_q[lo], unit = t - s.to[lo], row0 = unit * R, p = CUT ? row0 / P : unit;
         const uint32_t pg = p < s.mp[lo] ? s.mb[lo] + p : ix.dtab[(size_t)l * ix.max_dp + (p - s.mp[lo])];
         const Arena &ar = arena_of(ix, pg);
-        const size_t local = (size_t)(pg - ar.first_page) * P;
-        const uint32_t gl = v.ag * (uint32_t)a.nlist_max + l, g = s.slot[lo] / mq, left = s.len[lo] - p * P;
+        const size_t local = (size_t)(pg - ar.first_page) * P + (CUT ? row0 - p * P : 0u);
+        const uint32_t gl = v.ag * (uint32_t)a.nlist_max + l, g = s.slot[lo] / mq, left = s.len[lo] - row0;
         Tile tl;
         tl.x = ar.vec + local * (size_t)ix.row_bytes;
         tl.xn = ar.norm + local;
-        tl.row0 = p * P;
+        tl.row0 = row0;
         tl.qbeg = gl * a.cap + g * mq;
-        tl.nrows = (uint16_t)(left < P ? left : P);
+        tl.nrows = (uint16_t)(left < R ? left : R);
         tl.qcnt = (uint16_t)g;
         tl.list = gl;
         a.tiles[first + t] = tl;

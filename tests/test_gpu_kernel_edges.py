@@ -566,6 +566,57 @@ def test_values_written_whole_give_the_rows_of_the_gated_scan(gpu_device, n, d, 
         other.close()
 
 
+@pytest.mark.parametrize("n,d,nlist,nprobe,k,nq,page,storage,metric", [
+    (9000, 192, 60, 5, 10, 7, 0, F32, L2),  # three slices: the least
+    (9000, 193, 60, 5, 10, 7, 64, F32, IP),  # four: no slice left over
+    (9000, 300, 60, 5, 10, 7, 32, F32, L2),  # five; tiles of a page of 32 rows
+    (9000, 700, 60, 5, 33, 7, 96, F16, IP),  # six; half a wave's rows missing in every other tile
+    (20000, 400, 40, 9, 10, 30, 1024, F32, L2),  # tiles from the middle of pages; groups of 32 slots
+    (12000, 300, 12, 6, 20, 90, 256, F16, L2),  # of 64, several per list
+    (9000, 1536, 50, 6, 5, 3, 0, F32, IP),  # the longest rows, instead of the sliced queries' kernel
+    (9000, 1536, 20, 6, 5, 35, 128, F32, L2),  # ... several groups per list
+    (40000, 1000, 4, 2, 20, 2, 256, F16, IP)])  # ranges of which the bests of 16 are written
+def test_scans_of_few_tiles_give_the_rows_of_the_gated_scan(gpu_device, n, d, nlist, nprobe, k, nq, page, storage, metric):
+    """Searches whose tiles are cut smaller because there are few: the rows of the gated scan, bit for bit, after inserts (delta
+    pages) and deletes too, and for two memories in one call.  The number of tiles says that they were cut."""
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    c = torch.randn((nlist, d), device="cuda", generator=g)
+
+    def around(m):
+        return (c[torch.randint(nlist, (m,), device="cuda", generator=g)] + 0.5 * torch.randn((m, d), device="cuda", generator=g)).half().float()
+
+    x, q = around(n), around(nq)
+    ix, other = (B.Index(c, rows, metric=metric, storage=storage, page_vecs=page, insert_reserve=4096) for rows in (x, x[: n // 3].contiguous()))
+    unit = 64 if page % 64 == 0 else 32  # (0: pages of 128)
+    try:
+        for stage in ("built", "changed"):
+            if stage == "changed":
+                ix.delete(torch.arange(0, n, 11, device="cuda"))
+                ix.insert(around(900))
+            offs = [0, nq - nq // 3, nq]
+            with route(ix, True) as ran:
+                whole = ix.search(q, k, nprobe), B.search_multi([ix, other], offs, q, k, nprobe)
+            tiles = []
+            for one in (lambda: ix.search(q, k, nprobe), lambda: ix.search(q[:1], k, nprobe)):
+                B.pk_profile_begin(ix.handle)
+                one()
+                tiles.append(B.pk_profile_end(ix.handle).tiles)
+            assert ran.whole
+            asked = [torch.bincount(ix.coarse(r, nprobe).flatten().long(), minlength=nlist).cpu().numpy() for r in (q, q[:1])]
+            per_list = nq * nprobe / nlist
+            slots = min(16 if per_list <= 6 else 32 if per_list <= 20 else 64, 16 if d == 1536 else 64)
+            lengths = ix.list_lengths()
+            assert tiles == [int((-(-lengths // unit) * -(-a // s)).sum()) for a, s in zip(asked, (slots, 16))], tiles
+            with route(ix, False):
+                gated = ix.search(q, k, nprobe), B.search_multi([ix, other], offs, q, k, nprobe)
+            for (wi, wv), (gi, gv) in zip(whole, gated):
+                assert torch.equal(wi, gi) and torch.equal(wv, gv), stage
+        assert ix.stats().device_error == 0 and other.stats().device_error == 0
+    finally:
+        ix.close()
+        other.close()
+
+
 @pytest.mark.parametrize("n,kinds,k,nprobe,nq,page,metric,storage", [
     (300000, 50, 100, 16, 1, 0, IP, F32), (300000, 50, 10, 16, 3, 96, L2, F16), (100000, 1, 30, 2, 5, 0, L2, F32),
     (200000, 7, 200, 40, 4, 1024, IP, F16), (300000, 2000, 255, 40, 2, 32, L2, F32), (70000, 3, 1, 40, 9, 0, IP, F32)])
