@@ -676,6 +676,7 @@ __device__ __forceinline__ void final_by_radix(G get, uint32_t cnt_q, uint32_t K
 // parts of it, all ones for a part with none; `all`: every thread has met something.
 __device__ __forceinline__ uint32_t bound_on_kth(u32x4 mn, bool all, uint32_t K, uint32_t (*hist)[256])
 {
+    if (K <= kFewParts) return bound_of_far_parts(min(min(mn[0], mn[1]), min(mn[2], mn[3])), K, hist[0]);
     if (K <= kMostParts) return bound_of_parts(min(min(mn[0], mn[1]), min(mn[2], mn[3])), K, hist[0]);
     if (!all) return 0xffffffffu;
     const uint32_t key[4] = {mn[0], mn[1], mn[2], mn[3]};
@@ -691,8 +692,8 @@ __device__ __forceinline__ uint32_t bound_on_kth(u32x4 mn, bool all, uint32_t K,
 // False: more than fit are within the bound, or K is too large; nothing is selected.  n_surv: how many keys surv holds, every one that is no worse than the K-th best among them (0: none).
 constexpr uint32_t kBlocks = 1024;
 // Keys that surv holds.  Where the query's nearest list has less than K parts' worth of values, all of it is within the
-// bound, and some from other lists: a part is 4 neighbours of ranges that are read once, 16 of others, and four times that
-// where there are 64 parts.
+// bound, and some from other lists: a part is 4 neighbours of ranges that are read once, 16 of others, and four such pieces from
+// afar where there are 64 parts.
 constexpr uint32_t kMostSurvivors = 18u * kSelThreads;
 __device__ __host__ __forceinline__ uint32_t survivors(uint32_t K, uint32_t width)
 {
@@ -825,6 +826,34 @@ __device__ __forceinline__ bool final_of_values(const float *vals, const uint32_
         __syncthreads();
     } else {
         __syncthreads(); // (the selection counts in the same word)
+        // A bound from parts again, now of the collected keys alone: where the nearest list was too short to fill K parts, the
+        // first bound was a value of some other list.  (K = 78 of lists of 370: 2 us of 19, where radix passes took 4.5.)
+        if (K <= kMostParts && n <= 16u * kSelThreads) {
+            uint32_t least = 0xffffffffu;
+            for (uint32_t p = tid; p < n; p += kSelThreads) least = min(least, (uint32_t)(surv[p] >> 32));
+            if (tid == 0) *s_cnt = 0;
+            const uint32_t bound = bound_of_parts(least, K, hist[0]);
+            for (uint32_t p = tid; p < n; p += kSelThreads) {
+                const u64 key = surv[p];
+                if ((uint32_t)(key >> 32) > bound) continue;
+                const uint32_t at = atomicAdd(s_cnt, 1u);
+                if (at < (uint32_t)kSelThreads) keys[at] = key;
+            }
+            __syncthreads();
+            const uint32_t within = *s_cnt;
+            __syncthreads();
+            if (within <= (uint32_t)kSelThreads) { // (the same for the whole workgroup)
+                if (tid < 2) keys[within + tid] = kMaxKey; // padding: the keys are read in pairs
+                __syncthreads();
+                const u64 mine = tid < within ? keys[tid] : kMaxKey;
+                const uint32_t rank = tid < within ? rank_among(keys, within, mine) : K;
+                __syncthreads();
+                if (rank < K) keys[rank] = mine;
+                if (tid == 0) *s_cnt = within < K ? within : K;
+                __syncthreads();
+                return true;
+            }
+        }
         if (n <= 4u * kSelThreads) final_by_radix<4>([=](int, uint32_t p) { return surv[p]; }, n, K, hist, keys, s_cnt);
         else final_by_radix<kMostSurvivors / kSelThreads>([=](int, uint32_t p) { return surv[p]; }, n, K, hist, keys, s_cnt);
     }

@@ -617,6 +617,30 @@ def test_scans_of_few_tiles_give_the_rows_of_the_gated_scan(gpu_device, n, d, nl
         other.close()
 
 
+@pytest.mark.parametrize("nprobe,k", [(30, 20), (30, 23), (30, 24), (30, 100), (30, 127), (30, 128), (10, 23), (10, 24), (10, 100), (10, 127)])
+@pytest.mark.parametrize("metric", [IP, L2])
+def test_bests_of_short_lists_among_many_values(gpu_device, nprobe, k, metric):
+    """Lists of 270 rows that lie apart, 8000 values a query and 2700: the nearest list fills fewer parts of the range than k, and what
+    is within the first bound is far more than k.  The rows of the gated scan, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(k)
+    nlist, d = 300, 40
+    c = torch.randn((nlist, d), device="cuda", generator=g)
+
+    def around(m):
+        return c[torch.randint(nlist, (m,), device="cuda", generator=g)] + 0.3 * torch.randn((m, d), device="cuda", generator=g)
+
+    ix, q = B.Index(c, around(270 * nlist), metric=metric), around(37)
+    try:
+        with route(ix, True) as ran:
+            whole = ix.search(q, k, nprobe)
+        with route(ix, False):
+            gated = ix.search(q, k, nprobe)
+        assert ran.whole and (np.sort(ix.list_lengths())[-nprobe:].sum() > 8192) == (nprobe == 30)
+        assert torch.equal(whole[0], gated[0]) and torch.equal(whole[1], gated[1])
+    finally:
+        ix.close()
+
+
 @pytest.mark.parametrize("n,kinds,k,nprobe,nq,page,metric,storage", [
     (300000, 50, 100, 16, 1, 0, IP, F32), (300000, 50, 10, 16, 3, 96, L2, F16), (100000, 1, 30, 2, 5, 0, L2, F32),
     (200000, 7, 200, 40, 4, 1024, IP, F16), (300000, 2000, 255, 40, 2, 32, L2, F32), (70000, 3, 1, 40, 9, 0, IP, F32)])
