@@ -247,54 +247,65 @@ hipError_t launch_gemm_scores(const GemmArgs &a, hipStream_t s)
 // products of 11-bit numbers that are exact in fp32, at a sixteenth of the fp32 product's price each.
 // Rows in memory: blocks of 32 elements, 64 bytes of hi then 64 bytes of lo; as many bytes as the fp32 row.
 
-// Sum of a wave's row in the order in which prep_row (pk_worklist.hip) adds its squares: part[j] is the sum of the
-// lane's elements 4 * lane + j, + 256, ...: what thread 4 * lane + j of its 256 threads holds.  A query's norm is
-// the same bits whichever kernel prepared it.
-__device__ __forceinline__ float row_sum(float (&part)[4])
+// Sum of a row in the order in which prep_row (pk_worklist.hip) adds its squares, whose thread i of 256 holds elements i, i + 256,
+// ...  A wave's row: part[0][j] is the sum of the lane's elements 4 * lane + j, + 256, ....  A row of at most 256 elements on SUB lanes of a wave:
+// part[u][j] is the lane's element 4 * lane + j + 4 * SUB * u.  (Elements there are none of add zeros, which change nothing.)  A
+// query's norm is the same bits whichever kernel prepared it.
+template <int SUB, int NP>
+__device__ __forceinline__ float row_sum(float (&part)[NP][4])
 {
+    float sum = 0.f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int u = 0; u < NP; ++u) {
 #pragma unroll
-        for (int off = 8; off > 0; off >>= 1) part[j] += __shfl_xor(part[j], off);
-    const float w = (part[0] + part[2]) + (part[1] + part[3]);
-    return __shfl(w, 0) + __shfl(w, 16) + __shfl(w, 32) + __shfl(w, 48);
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) part[u][j] += __shfl_xor(part[u][j], off);
+        const float w = (part[u][0] + part[u][2]) + (part[u][1] + part[u][3]);
+#pragma unroll
+        for (int at = 0; at < SUB; at += 16) {
+            const float x = __shfl(w, at, SUB);
+            sum = u == 0 && at == 0 ? x : sum + x;
+        }
+    }
+    return sum;
 }
 
-// A wave per row, rows [0, m) from `x` (dense, d floats) and then n_c rows of the (padded) centroid table.
-// Bound by memory: 300 000 rows of 4 KB read and written at 4.3 TB/s.
-// T: 256-element parts of a row.
-template <int T>
-__global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiArgs mm)
+// SUB lanes per row, rows [0, m) from `x` (dense, d floats) and then n_c rows of the (padded) centroid table.  A lane has four elements
+// of each of a row's T parts of 4 SUB.
+// Bound by memory (300 000 rows of 4 KB read and written at 4.3 TB/s), and where rows are short by the rate at which workgroups
+// start: with a wave per row, 32768 rows of up to 256 elements take 26 - 31 us, however short they are.  There several rows
+// share a wave, and the workgroups stay and take row after row (long rows: 37 -> 40 us of 32768 x 768): 32768 x 128 27 -> 16 us.
+template <int T, int SUB>
+__device__ __forceinline__ void split_row(const SplitRowsArgs &a, const MultiArgs &mm, uint32_t row, int lane)
 {
-    const int lane = threadIdx.x & 63;
-    const uint32_t row = blockIdx.x * 4u + (threadIdx.x >> 6);
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.meta.nclear; i += gridDim.x * blockDim.x) a.meta.clear[i] = 0u;
-    if (row >= a.m + a.n_c) return;
+    static_assert(SUB == 64 || 4 * SUB * T <= 256, "rows that share a wave have 256 elements at most");
+    constexpr int NP = SUB == 64 ? 1 : T; // sums that are kept apart (see row_sum)
     const bool cent = row >= a.m;
     const uint32_t r = cent ? row - a.m : row;
     const int ld = a.ld, d = cent ? ld : a.d;
     const float *src = cent ? a.c + (size_t)r * ld : a.x + (size_t)r * d;
-    const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0; // (wave-uniform)
+    const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0; // (nearly always the same for the whole wave)
     f32x4 v[T];
-    float big = 0.f, sq[4] = {0.f, 0.f, 0.f, 0.f}, sq16[4] = {0.f, 0.f, 0.f, 0.f}, off[4] = {0.f, 0.f, 0.f, 0.f};
+    float big = 0.f, sq[NP][4] = {}, sq16[NP][4] = {}, off[NP][4] = {};
     if (vec) { // (all of a row's loads in flight at once: none of them under a condition)
 #pragma unroll
-        for (int t = 0; t < T; ++t) v[t] = dense_load<true>(src, lane * 4 + 256 * t, d);
+        for (int t = 0; t < T; ++t) v[t] = dense_load<true>(src, lane * 4 + 4 * SUB * t, d);
     } else {
 #pragma unroll
-        for (int t = 0; t < T; ++t) v[t] = dense_load<false>(src, lane * 4 + 256 * t, d);
+        for (int t = 0; t < T; ++t) v[t] = dense_load<false>(src, lane * 4 + 4 * SUB * t, d);
     }
 #pragma unroll
-    for (int t = 0; t < T; ++t) v[t] = dense_zeros(v[t], lane * 4 + 256 * t, d);
+    for (int t = 0; t < T; ++t) v[t] = dense_zeros(v[t], lane * 4 + 4 * SUB * t, d);
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             big = fmaxf(big, fabsf(v[t][j]));
-            sq[j] += v[t][j] * v[t][j];
+            sq[t % NP][j] += v[t][j] * v[t][j];
         }
-    for (int off = 32; off > 0; off >>= 1) big = fmaxf(big, __shfl_xor(big, off));
-    const float norm = row_sum(sq);
+    for (int o = SUB / 2; o > 0; o >>= 1) big = fmaxf(big, __shfl_xor(big, o));
+    const float norm = row_sum<SUB>(sq);
     // 2^e <= big < 2^(e + 1); the scale stays a normal number (a row of zeros, or one below 2^-112, is scaled by 2^126)
     int s = 14 - ((int)(__float_as_uint(big) >> 23) - 127);
     s = s < -126 ? -126 : (s > 126 ? 126 : s);
@@ -304,7 +315,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     if (first) first += (size_t)r * ld * 2;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-        const int i = lane * 4 + 256 * t;
+        const int i = lane * 4 + 4 * SUB * t;
         if (i >= ld) continue;
         half4 hi, lo;
 #pragma unroll
@@ -313,7 +324,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
             hi[j] = (_Float16)y;
             const float rest = y - (float)hi[j]; // exact
             lo[j] = (_Float16)rest;
-            off[j] += rest * rest;
+            off[t % NP][j] += rest * rest;
         }
         if (first) *reinterpret_cast<half4 *>(first + (size_t)i * 2) = hi;
         if (dst) {
@@ -327,20 +338,20 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
         char *h = a.half_rows + (size_t)r * a.half_bytes;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            const int i = lane * 4 + 256 * t;
+            const int i = lane * 4 + 4 * SUB * t;
             if (i * 2 >= a.half_bytes) continue;
             half4 w;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 w[j] = (_Float16)v[t][j];
                 const float f = (float)w[j];
-                sq16[j] += f * f;
+                sq16[t % NP][j] += f * f;
             }
             *reinterpret_cast<half4 *>(h + (size_t)i * 2) = w;
         }
     }
-    const float norm16 = row_sum(sq16);
-    const float rest = row_sum(off);
+    const float norm16 = row_sum<SUB>(sq16);
+    const float rest = row_sum<SUB>(off);
     if (lane != 0) return;
     const float back = __uint_as_float((uint32_t)(127 - s) << 23);
     const float left = sqrtf(rest) * back; // length of what the first halfs leave out
@@ -371,17 +382,39 @@ __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiA
     }
 }
 
+template <int T, int SUB>
+__global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiArgs mm)
+{
+    const int lane = threadIdx.x & (SUB - 1);
+    constexpr uint32_t kRows = 256 / SUB; // of a workgroup at a time
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.meta.nclear; i += gridDim.x * blockDim.x) a.meta.clear[i] = 0u;
+    uint32_t row = blockIdx.x * kRows + threadIdx.x / SUB;
+    if constexpr (SUB == 64) {
+        if (row < a.m + a.n_c) split_row<T, SUB>(a, mm, row, lane);
+    } else {
+        for (; row < a.m + a.n_c; row += gridDim.x * kRows) split_row<T, SUB>(a, mm, row, lane);
+    }
+}
+
+constexpr uint32_t kSplitRowsGrid = 2048; // workgroups that stay: eight per CU
 hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStream_t s)
 {
     if (a.m + a.n_c == 0) return hipSuccess;
     if (a.ld % 64 != 0 || a.ld > PK_MAX_DIM || a.d > a.ld) return hipErrorInvalidValue;
     if (a.half_rows && (a.half_bytes % 256 != 0 || a.half_bytes > PK_MAX_DIM * 2 || a.half_bytes < a.d * 2)) return hipErrorInvalidValue;
     using Kernel = void (*)(SplitRowsArgs, MultiArgs);
-    static constexpr Kernel by_parts[] = {split_rows_kernel<1>, split_rows_kernel<2>, split_rows_kernel<3>,
-                                          split_rows_kernel<4>, split_rows_kernel<5>, split_rows_kernel<6>};
+    static constexpr Kernel shorter[] = {split_rows_kernel<1, 16>, split_rows_kernel<1, 32>, split_rows_kernel<2, 32>, split_rows_kernel<2, 32>};
+    static constexpr Kernel longer[] = {split_rows_kernel<2, 64>, split_rows_kernel<3, 64>, split_rows_kernel<4, 64>, split_rows_kernel<5, 64>,
+                                        split_rows_kernel<6, 64>};
     static_assert(PK_MAX_DIM <= 6 * 256, "a row has six parts at most");
     const int wide = a.half_rows ? std::max(a.ld, a.half_bytes / 2) : a.ld; // (a half-precision row may be padded further)
-    hipLaunchKernelGGL(by_parts[(wide + 255) / 256 - 1], dim3((a.m + a.n_c + 3) / 4), dim3(256), 0, s, a, mm);
+    const uint32_t rows = a.m + a.n_c;
+    if (wide <= 256) {
+        const uint32_t each = wide <= 64 ? 16u : 8u; // rows of a workgroup at a time
+        hipLaunchKernelGGL(shorter[(wide - 1) / 64], dim3(std::min((rows + each - 1u) / each, kSplitRowsGrid)), dim3(256), 0, s, a, mm);
+    } else {
+        hipLaunchKernelGGL(longer[(wide + 255) / 256 - 2], dim3((rows + 3u) / 4u), dim3(256), 0, s, a, mm);
+    }
     return hipGetLastError();
 }
 

@@ -3,17 +3,17 @@
 // The assignment step is the coarse search with nprobe = 1 under L2 (pk_api.hip); this file
 // turns an assignment and its histogram into new centroids: exclusive scan, scatter of the row
 // numbers into cluster-major order, then the members are summed in fp64, up to 256 of a cluster
-// per workgroup (thread j owns dimensions j, j + 256, ...; rows are read coalesced; the parts of
-// a larger cluster meet by fp64 atomics), and every cluster divides its total.  An empty cluster keeps its
+// per workgroup (rows are read coalesced; the parts of a larger cluster meet by fp64 atomics), and every cluster divides its total.  An empty cluster keeps its
 // centroid.  The objective of the assignment comes out of the same sums:
 // sum_i |x_i - c|^2 = sum |x_i|^2 - 2 <c, sum x_i> + m |c|^2, in fp64.
 #include <algorithm>
+#include <type_traits>
 
 #include "pk_internal.h"
 
 namespace pk {
 
-static_assert(PK_MAX_DIM <= 6 * 256, "a thread owns at most six dimensions");
+static_assert(PK_MAX_DIM <= 2 * 4 * 256, "a lane owns two times four dimensions at most");
 constexpr int kKmChunk = 256;                     // members one workgroup sums
 constexpr int kKmAhead = 8;                       // members in flight
 
@@ -54,16 +54,26 @@ __global__ __launch_bounds__(256) void km_scatter_kernel(KmeansArgs a, bool lds)
     }
 }
 
-// One workgroup per piece: a cluster, or kKmChunk members of a longer one (a.piece0: pieces before each cluster).  Thread j
-// owns dimensions j, j + 256, ... (T of them); kKmAhead members are requested before the first is added, by loads
-// without a condition (with one, the compiler waits for each of them in turn: 262 144 x 768 in 507 us, and 245
-// without).  A cluster of one piece is finished here, without atomics; the pieces of a longer one meet by float64
-// atomics, and km_finalize_kernel divides.
-template <int T>
-__global__ __launch_bounds__(256) void km_accumulate_kernel(KmeansArgs a)
+// One workgroup per piece: a cluster, or kKmChunk members of a longer one (a.piece0: pieces before each cluster).  A lane owns V
+// neighbouring dimensions (T times, `across` lanes apart), `across` lanes a row, and the workgroup's 256 / across groups of
+// lanes take every so manieth member; their sums meet in LDS.  The members' numbers are fetched once, so that the rows are the
+// only memory operations of the loop, and a group's kKmAhead rows are requested before the first is added, by loads
+// without a condition (with one, the compiler waits for each of them in turn).  Rows need no alignment: a lane's 16 bytes are the row's
+// last ones where its dimensions reach past the end, and it keeps those that are its own.  A cluster of one piece is
+// finished here, without atomics; the pieces of a longer one meet by float64 atomics, and km_finalize_kernel divides.
+// With a lane per dimension and one group, 262 144 x 768, 4096 clusters took 247 us, now 180 (4.5 TB/s), 200 000 x 128, 1024 clusters 91
+// and now 25, 100 000 x 1300, 300 clusters 188 and 141.
+struct __attribute__((packed, aligned(4))) AnyFour {
+    f32x4 v;
+};
+// ODD: some lane's dimensions reach past the row's end.
+template <int V, int T, bool ODD>
+__global__ __launch_bounds__(256) void km_accumulate_kernel(KmeansArgs a, uint32_t across)
 {
+    __shared__ double s_sum[256][V];
+    __shared__ uint32_t s_member[kKmChunk];
     __shared__ double s_part[2][4];
-    const uint32_t u = blockIdx.x;
+    const uint32_t u = blockIdx.x, tid = threadIdx.x;
     if (u >= a.piece0[a.nlist]) return;
     uint32_t lo = 0, hi = (uint32_t)a.nlist - 1; // the last cluster whose pieces start at or before u
     while (lo < hi) {
@@ -72,59 +82,89 @@ __global__ __launch_bounds__(256) void km_accumulate_kernel(KmeansArgs a)
         else hi = mid - 1;
     }
     const uint32_t l = lo, cnt = a.cnt[l], first = (u - a.piece0[l]) * (uint32_t)kKmChunk;
-    const uint32_t stop = first + kKmChunk < cnt ? first + kKmChunk : cnt;
-    const uint32_t *members = a.members + a.start[l];
-    double sum[T], sq = 0.0;
+    const uint32_t here = cnt - first < (uint32_t)kKmChunk ? cnt - first : (uint32_t)kKmChunk;
+    s_member[tid] = a.members[a.start[l] + first + (tid < here ? tid : here - 1u)];
+    static_assert(kKmChunk == 256, "a member per thread");
+    __syncthreads();
+    const uint32_t groups = 256u / across, group = tid / across, at = tid - group * across;
+    int from[T]; // the lane's first dimension, and the first that it reads
+    double sum[T][V] = {}, sq = 0.0;
 #pragma unroll
-    for (int t = 0; t < T; ++t) sum[t] = 0.0;
-    for (uint32_t e0 = first; e0 < stop; e0 += kKmAhead) {
-        float v[kKmAhead][T];
+    for (int t = 0; t < T; ++t) {
+        const int j = (int)(at + across * t) * V;
+        from[t] = j < a.d - V ? j : a.d - V;
+    }
+    auto own = [&](int t, int c) { return !ODD || from[t] + c >= (int)(at + across * t) * V; };
+    // kKmAhead members from e0 on (FULL: there are that many; else the last one again where there is none, and not added)
+    auto batch = [&](uint32_t e0, auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        f32x4 v[kKmAhead][T];
 #pragma unroll
         for (int w = 0; w < kKmAhead; ++w) {
-            const uint32_t e = e0 + w < stop ? e0 + w : stop - 1; // past the end the last one again, not added
-            const float *row = a.x + (size_t)members[e] * a.d;
+            const uint32_t e = e0 + (uint32_t)w * groups;
+            const float *const row = a.x + (size_t)s_member[FULL || e < here ? e : here - 1u] * a.d;
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                const int j = (int)threadIdx.x + 256 * t;
-                v[w][t] = row[j < a.d ? j : a.d - 1];
+                if constexpr (V == 4) v[w][t] = reinterpret_cast<const AnyFour *>(row + from[t])->v;
+                else v[w][t][0] = row[from[t]];
             }
         }
 #pragma unroll
         for (int w = 0; w < kKmAhead; ++w) {
-            if (e0 + w >= stop) break;
+            const bool there = FULL || e0 + (uint32_t)w * groups < here; // (no branch: behind one, the load would be, too)
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const double x = (int)threadIdx.x + 256 * t < a.d ? (double)v[w][t] : 0.0;
-                sum[t] += x;
-                sq += x * x;
-            }
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int c = 0; c < V; ++c) {
+                    const double x = (double)(there && own(t, c) ? v[w][t][c] : 0.f);
+                    sum[t][c] += x;
+                    sq += x * x;
+                }
+        }
+    };
+    if (group < groups) {
+        uint32_t e0 = group;
+        for (; e0 + (uint32_t)(kKmAhead - 1) * groups < here; e0 += (uint32_t)kKmAhead * groups) batch(e0, std::true_type{});
+        if (e0 < here) batch(e0, std::false_type{});
+    }
+    if constexpr (T == 1) { // (more than one group only then)
+        if (groups > 1u) {
+#pragma unroll
+            for (int c = 0; c < V; ++c) s_sum[tid][c] = sum[0][c];
+            __syncthreads();
+            if (group == 0u)
+                for (uint32_t g = 1; g < groups; ++g)
+#pragma unroll
+                    for (int c = 0; c < V; ++c) sum[0][c] += s_sum[g * across + at][c];
         }
     }
     const bool whole = cnt <= (uint32_t)kKmChunk;
     double obj = 0.0;
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-        const int j = (int)threadIdx.x + 256 * t;
-        if (j >= a.d) continue;
-        if (whole) {
-            float *c = a.centroids + (size_t)l * a.d + j;
-            const double c0 = (double)*c;
-            obj += (double)cnt * c0 * c0 - 2.0 * c0 * sum[t];
-            *c = (float)(sum[t] / (double)cnt);
-        } else {
-            atomicAdd(&a.sums[(size_t)l * a.d + j], sum[t]);
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int w = 0; w < V; ++w) {
+            const int j = from[t] + w;
+            if (group != 0u || !own(t, w)) continue;
+            if (whole) {
+                float *c = a.centroids + (size_t)l * a.d + j;
+                const double c0 = (double)*c;
+                obj += (double)cnt * c0 * c0 - 2.0 * c0 * sum[t][w];
+                *c = (float)(sum[t][w] / (double)cnt);
+            } else {
+                atomicAdd(&a.sums[(size_t)l * a.d + j], sum[t][w]);
+            }
         }
-    }
     for (int off = 32; off > 0; off >>= 1) {
         sq += __shfl_xor(sq, off);
         obj += __shfl_xor(obj, off);
     }
-    if ((threadIdx.x & 63) == 0) {
-        s_part[0][threadIdx.x >> 6] = sq;
-        s_part[1][threadIdx.x >> 6] = obj;
+    if ((tid & 63) == 0) {
+        s_part[0][tid >> 6] = sq;
+        s_part[1][tid >> 6] = obj;
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
+    if (tid != 0) return;
     sq = (s_part[0][0] + s_part[0][1]) + (s_part[0][2] + s_part[0][3]);
     obj = (s_part[1][0] + s_part[1][1]) + (s_part[1][2] + s_part[1][3]);
     if (whole) atomicAdd(a.inertia, sq + obj);
@@ -168,14 +208,14 @@ hipError_t launch_kmeans_update(const KmeansArgs &a, hipStream_t s)
     e = launch_fill_u32(reinterpret_cast<uint32_t *>(a.sq), 0u, (size_t)a.nlist * 2, s);
     if (e != hipSuccess) return e;
     const dim3 pieces((uint32_t)(a.n / kKmChunk + std::min<int64_t>(a.n, a.nlist) + 1)), threads(256); // at least as many as there are
-    switch ((a.d + 255) / 256) {
-    case 1: hipLaunchKernelGGL(km_accumulate_kernel<1>, pieces, threads, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(km_accumulate_kernel<2>, pieces, threads, 0, s, a); break;
-    case 3: hipLaunchKernelGGL(km_accumulate_kernel<3>, pieces, threads, 0, s, a); break;
-    case 4: hipLaunchKernelGGL(km_accumulate_kernel<4>, pieces, threads, 0, s, a); break;
-    case 5: hipLaunchKernelGGL(km_accumulate_kernel<5>, pieces, threads, 0, s, a); break;
-    default: hipLaunchKernelGGL(km_accumulate_kernel<6>, pieces, threads, 0, s, a); break;
-    }
+    auto go = [&](auto kernel, int v) { // lanes per row: what it takes, or all of the workgroup's
+        const uint32_t across = std::min(256u, (uint32_t)((a.d + v - 1) / v));
+        hipLaunchKernelGGL(kernel, pieces, threads, 0, s, a, across);
+    };
+    if (a.d < 4) go(km_accumulate_kernel<1, 1, false>, 1);
+    else if (a.d > 1024) go(km_accumulate_kernel<4, 2, true>, 4);
+    else if (a.d % 4 == 0) go(km_accumulate_kernel<4, 1, false>, 4);
+    else go(km_accumulate_kernel<4, 1, true>, 4);
     hipLaunchKernelGGL(km_finalize_kernel, dim3(a.nlist), dim3(256), 0, s, a);
     return hipGetLastError();
 }

@@ -617,6 +617,29 @@ def test_scans_of_few_tiles_give_the_rows_of_the_gated_scan(gpu_device, n, d, nl
         other.close()
 
 
+@pytest.mark.parametrize("d", [1, 3, 4, 5, 63, 64, 65, 127, 129, 192, 255, 256, 259, 1021, 1024, 1025, 1536])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_kmeans_update_of_rows_of_any_width(gpu_device, d, shift):
+    """Clusters of no member, of one, of a piece's number of members and one beside it, of several pieces; rows that begin anywhere.
+    Every centroid is the float64 mean of its members, the objective their sum of squared distances, and every row is with
+    the nearest centroid (up to the rounding of fp32 sums of d products)."""
+    sizes = [1, 0, 255, 256, 257, 2, 900, 7, 511, 513]
+    g = torch.Generator(device="cuda").manual_seed(d)
+    c = torch.randn((len(sizes), d), device="cuda", generator=g) + 40 * torch.arange(len(sizes), device="cuda")[:, None]
+    of = torch.repeat_interleave(torch.arange(len(sizes), device="cuda"), torch.tensor(sizes, device="cuda"))
+    of = of[torch.randperm(len(of), device="cuda", generator=g)]
+    room = torch.zeros(len(of) * d + 4, device="cuda")
+    x = room[shift:shift + len(of) * d].view(len(of), d)
+    x[:] = c[of] + torch.randn((len(of), d), device="cuda", generator=g)
+    cent, assign = c.clone(), torch.empty(len(of), dtype=torch.int32, device="cuda")
+    inertia = B.pk_kmeans(x, cent, 1, assign)
+    assert torch.equal(assign.long(), of)
+    means = torch.stack([x[of == l].double().mean(0) if m else c[l].double() for l, m in enumerate(sizes)])
+    assert (cent.double() - means).abs().max() <= 2.0 ** -23 * means.abs().max()
+    want = float((x.double() - c.double()[of]).square().sum())
+    assert abs(inertia[0] - want) <= 1e-9 * (want + float(x.double().square().sum()))
+
+
 @pytest.mark.parametrize("nprobe,k", [(30, 20), (30, 23), (30, 24), (30, 100), (30, 127), (30, 128), (10, 23), (10, 24), (10, 100), (10, 127)])
 @pytest.mark.parametrize("metric", [IP, L2])
 def test_bests_of_short_lists_among_many_values(gpu_device, nprobe, k, metric):
