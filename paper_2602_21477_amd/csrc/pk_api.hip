@@ -975,7 +975,7 @@ int run_dense(const Plan &p, const MultiArgs &m, pk_index *own, int64_t *out_ids
     sa.tile_cap = p.tile_cap;
     sa.grab_div = tunables().grabdiv;
     // (no more workgroups than tiles)
-    sa.slot_room = (uint32_t)p.slots;
+    sa.ecap = (uint32_t)p.slots;
     const int most = p.tile_rows ? grid_for(own, own->row_bytes, p.mq_f) : sliced ? p.grid_h : p.grid_f;
     const int grid = (int)std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)most, p.tile_cap));
     if (p.tile_rows) PK_HIP(launch_scan_few(sa, grid, s));

@@ -263,7 +263,8 @@ struct ScanArgs {
     const float *tinv;           // [nq] bucket scale (see bucket_of)
     uint32_t *hist;              // [nq][kHistBins] emitted candidates per bucket (zero before the launch)
     uint32_t *tcur;              // [nq] running bucket limit shared by all workgroups (starts at kHistBins-1)
-    uint32_t ecap;               // entries of each query's region of cbuf: query q owns [q * ecap, (q + 1) * ecap)
+    uint32_t ecap;               // entries of each query's region of cbuf: query q owns [q * ecap, (q + 1) * ecap); launch_scan_few
+                                 // (which has none): entries of slot_query and slot_out.  (A line more of arguments is 0.3 us.)
     uint32_t *ccnt;              // [nq] candidates that passed the gate so far (zero before the launch); those past
                                  // ecap are counted but not stored, and the query is then selected by rescoring
     unsigned long long *cbuf;
@@ -278,7 +279,6 @@ struct ScanArgs {
     uint32_t *mins;              // or null: best key of every 16 values, as they lie in `out`
     uint32_t tile_cap;           // more tiles than this: the layout was refused, nothing is scanned
     int grab_div;                // tiles per grab = tiles / (grid * this), 1 .. 8
-    uint32_t slot_room;          // launch_scan_few: entries of slot_query and slot_out
 };
 hipError_t launch_scan(const ScanArgs &a, int grid, hipStream_t s);
 hipError_t launch_scan_ks(const ScanArgs &a, int grid, hipStream_t s);
@@ -536,7 +536,6 @@ struct WorklistArgs {
     // whole layout in one go (wl_lay_query), values written whole:
     uint32_t cap;              // slots of each list (the most queries of a handle)
     uint32_t width;            // elements of each query's range
-    uint32_t tile_rows;        // rows of a tile (a divisor of every handle's page size), or 0: a page
     // one handle only: its list lengths, page size and list count, so that the work-list layout of a small batch
     // reads them without first chasing the handle's descriptor (null / 0 otherwise)
     const uint32_t *len1;
@@ -547,6 +546,7 @@ struct WorklistArgs {
 // densely; the k-th best of them bounds the query's k-th best overall.
 struct SampleArgs {
     const int32_t *probes;     // [nq][nprobe]
+    uint32_t tile_rows;        // with width: rows of a tile (a divisor of every handle's page size), or 0: a page
     const uint16_t *qagent;
     int nq;
     int rescued;               // queries whose region overflows may be scored again: slot_out is cleared for that

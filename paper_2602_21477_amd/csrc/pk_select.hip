@@ -673,10 +673,11 @@ __device__ __forceinline__ void final_by_radix(G get, uint32_t cnt_q, uint32_t K
 }
 
 // A bound on the K-th smallest (K up to 256) of what the workgroup's threads met: mn[]: each thread's smallest keys of four
-// parts of it, all ones for a part with none; `all`: every thread has met something.
+// parts of it, all ones for a part with none; `all`: every thread has met something.  FAR: neighbouring threads met neighbours.
+template <bool FAR>
 __device__ __forceinline__ uint32_t bound_on_kth(u32x4 mn, bool all, uint32_t K, uint32_t (*hist)[256])
 {
-    if (K <= kFewParts) return bound_of_far_parts(min(min(mn[0], mn[1]), min(mn[2], mn[3])), K, hist[0]);
+    if (FAR && K <= kFewParts) return bound_of_far_parts(min(min(mn[0], mn[1]), min(mn[2], mn[3])), K, hist[0]);
     if (K <= kMostParts) return bound_of_parts(min(min(mn[0], mn[1]), min(mn[2], mn[3])), K, hist[0]);
     if (!all) return 0xffffffffu;
     const uint32_t key[4] = {mn[0], mn[1], mn[2], mn[3]};
@@ -692,8 +693,8 @@ __device__ __forceinline__ uint32_t bound_on_kth(u32x4 mn, bool all, uint32_t K,
 // False: more than fit are within the bound, or K is too large; nothing is selected.  n_surv: how many keys surv holds, every one that is no worse than the K-th best among them (0: none).
 constexpr uint32_t kBlocks = 1024;
 // Keys that surv holds.  Where the query's nearest list has less than K parts' worth of values, all of it is within the
-// bound, and some from other lists: a part is 4 neighbours of ranges that are read once, 16 of others, and four such pieces from
-// afar where there are 64 parts.
+// bound, and some from other lists: a part is 4 neighbours of ranges that are read once, 16 of others, and four times that
+// (of the others, from afar) where there are 64 parts.
 constexpr uint32_t kMostSurvivors = 18u * kSelThreads;
 __device__ __host__ __forceinline__ uint32_t survivors(uint32_t K, uint32_t width)
 {
@@ -733,7 +734,7 @@ __device__ __forceinline__ bool final_of_values(const float *vals, const uint32_
                 mn[u & 3] = min(mn[u & 3], min(v[u][e], 0xfffffffeu) | (4u * tid + u * kStep < cnt_q ? 0u : 1u));
             }
         PK_MARK(sel, 41);
-        const uint32_t bound = cnt_q > K ? bound_on_kth(mn, cnt_q >= kStep, K, hist) : 0xffffffffu;
+        const uint32_t bound = cnt_q > K ? bound_on_kth<false>(mn, cnt_q >= kStep, K, hist) : 0xffffffffu;
         if (cnt_q <= K) __syncthreads();
         PK_MARK(sel, 42);
 #pragma unroll
@@ -767,7 +768,7 @@ __device__ __forceinline__ bool final_of_values(const float *vals, const uint32_
                 if (r + u * kSelThreads + tid < nb) mn[u & 3] = min(mn[u & 3], min(w[u], 0xfffffffeu));
         }
         PK_MARK(sel, 41);
-        const uint32_t bound = bound_on_kth(mn, nb >= (uint32_t)kSelThreads, K, hist);
+        const uint32_t bound = bound_on_kth<true>(mn, nb >= (uint32_t)kSelThreads, K, hist);
         PK_MARK(sel, 42);
         uint32_t *const blocks = reinterpret_cast<uint32_t *>(keys); // (the kept keys come later)
         for (uint32_t r = 0; r < nb; r += kReadOnce) {

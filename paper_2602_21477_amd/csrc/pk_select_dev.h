@@ -102,7 +102,7 @@ __device__ __forceinline__ uint32_t bound_of_parts(uint32_t least, uint32_t K, u
 // The same for up to kFewParts, where neighbouring threads hold neighbouring keys, most of the best among them: a part is the
 // same lane of the four waves, so that what 64 neighbours hold lies in 64 parts, not in 16 (the bests of 16 of a list of 586 rows
 // filled 10 parts, and K = 21 let hundreds through: final selection 16.5 -> 11.8 us; over ranges of 9 000 rows, 512 queries 19.9 -> 12.8).
-// s: LDS [512].
+// It takes 0.3 us more, which ranges that are read at once do not win back (one query over 2500 values).  s: LDS [512].
 __device__ __forceinline__ uint32_t bound_of_far_parts(uint32_t least, uint32_t K, uint32_t *s)
 {
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
