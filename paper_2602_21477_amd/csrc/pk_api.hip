@@ -696,7 +696,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     // side, unless the GEMM wants them first or the chunked selection, which adds no norm.  A whole search of 1 query with the
     // preparation as launches of its own and without: 100 000 x 130 fp16 L2 33.2 and 29.4 us, 100 000 x 100 fp32 33.7 and 30.6;
     // of 1024 queries 75.6 and 75.1, 81.6 and 80.2.  (Rows of odd widths: kFoldAny.)
-    p.fold = need_coarse && !worst && !p.raw_queries && nlist_hi <= kDenseSelectMax && tunables().densesel;
+    p.fold = need_coarse && !worst && !p.raw_queries && own->cfg.d >= 4 && nlist_hi <= kDenseSelectMax && tunables().densesel;
     for (int a = 0; a < nh && p.fold; ++a)
         if (coarse_by_gemm(qlo[a + 1] - qlo[a], hs[a])) p.fold = false;
     for (int a = 0; a < nh; ++a) p.coarse_products += (double)(qlo[a + 1] - qlo[a]) * hs[a]->cfg.nlist * own->cfg.d;
@@ -1581,6 +1581,11 @@ struct InsertScratch {
 int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const AssignScratch &as, int64_t chunk,
                 unsigned long long *best, hipStream_t s)
 {
+    if (t.d < 4) { // (the kernels that read rows as they are read four floats at a time)
+        for (int64_t i0 = 0; i0 < n; i0 += kFillChunk)
+            PK_TRY(assign_few(x + (size_t)i0 * t.d, std::min<int64_t>(kFillChunk, n - i0), t, num_cu, as.xh, as.norm + i0, best + i0, true, s));
+        return PK_OK;
+    }
     const int64_t tail = n % kFillChunk;
     const int64_t by_gemm = tail > 0 && !coarse_tiles((uint32_t)tail, t.nlist_pad) ? n - tail : n;
     MultiArgs mm;

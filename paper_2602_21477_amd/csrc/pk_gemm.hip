@@ -36,23 +36,19 @@ __device__ __forceinline__ uint32_t listed_tiles(uint32_t rows, int n_pad)
 }
 
 // Four floats of a dense row of d from column `col` on: the load, and zeros past the row's end.  VEC: rows of whole 16-byte
-// pieces (d a multiple of 4, the rows aligned).  The load is unconditional, past the end from the row's last floats, as the
+// pieces (d a multiple of 4, the rows aligned); else of four floats at least.  The load is unconditional, past the end from the row's last floats, as the
 // compiler waits for a load under a condition before it issues the next; the zeros are put in when the floats are used,
 // as putting them in waits for the load.
 template <bool VEC>
 __device__ __forceinline__ f32x4 dense_load(const float *row, int col, int d)
 {
-    f32x4 v;
-    if constexpr (VEC) {
-        v = *reinterpret_cast<const f32x4 *>(row + (col < d ? col : d - 4));
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = row[col + j < d ? col + j : d - 1];
-    }
-    return v;
+    if constexpr (VEC) return *reinterpret_cast<const f32x4 *>(row + (col < d ? col : d - 4));
+    else return __builtin_bit_cast(f32x4, any_load(reinterpret_cast<const uint32_t *>(row), col, d));
 }
+template <bool VEC>
 __device__ __forceinline__ f32x4 dense_zeros(f32x4 v, int col, int d)
 {
+    if constexpr (!VEC) return __builtin_bit_cast(f32x4, any_zeros(__builtin_bit_cast(u32x4, v), col, d));
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = col + j < d ? v[j] : 0.f;
     return v;
@@ -163,7 +159,7 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 #define PK_LSTORE(buf, ks)                                                                               \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                        \
     {                                                                                                    \
-        if constexpr (LISTED) ra4[i] = dense_zeros(ra4[i], (ks) * kGemmBK + scol, a.d);                  \
+        if constexpr (LISTED) ra4[i] = dense_zeros<VEC>(ra4[i], (ks) * kGemmBK + scol, a.d);                  \
         *reinterpret_cast<f32x4 *>(&sA[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = ra4[i];          \
         *reinterpret_cast<f32x4 *>(&sB[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = rb4[i];          \
     }
@@ -291,12 +287,19 @@ __device__ __forceinline__ void split_row(const SplitRowsArgs &a, const MultiArg
     if (vec) { // (all of a row's loads in flight at once: none of them under a condition)
 #pragma unroll
         for (int t = 0; t < T; ++t) v[t] = dense_load<true>(src, lane * 4 + 4 * SUB * t, d);
-    } else {
+#pragma unroll
+        for (int t = 0; t < T; ++t) v[t] = dense_zeros<true>(v[t], lane * 4 + 4 * SUB * t, d);
+    } else if (d >= 4) {
 #pragma unroll
         for (int t = 0; t < T; ++t) v[t] = dense_load<false>(src, lane * 4 + 4 * SUB * t, d);
-    }
 #pragma unroll
-    for (int t = 0; t < T; ++t) v[t] = dense_zeros(v[t], lane * 4 + 4 * SUB * t, d);
+        for (int t = 0; t < T; ++t) v[t] = dense_zeros<false>(v[t], lane * 4 + 4 * SUB * t, d);
+    } else {
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[t][j] = lane * 4 + 4 * SUB * t + j < d ? src[lane * 4 + 4 * SUB * t + j] : 0.f;
+    }
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -606,7 +609,7 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
             if (LISTED && i < ALOADS) { // 4 floats: their first halfs into the row's first 64 bytes, the rest behind
-                const f32x4 v = dense_zeros(__builtin_bit_cast(f32x4, st[i]), ks * 32 + (tid & 7) * 4, a.d);
+                const f32x4 v = dense_zeros<VEC>(__builtin_bit_cast(f32x4, st[i]), ks * 32 + (tid & 7) * 4, a.d);
                 half4 hi, lo;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) { // (the same values as split_rows_kernel's)
@@ -967,7 +970,7 @@ hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 
 hipError_t launch_gemm_split_listed(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 {
-    if (!split_gemm_valid(a) || a.left || !a.list || !a.nlisted || !a.x || a.d > a.ld) return hipErrorInvalidValue;
+    if (!split_gemm_valid(a) || a.left || !a.list || !a.nlisted || !a.x || a.d > a.ld || a.d < 4) return hipErrorInvalidValue;
     static LdsCleared cleared, cleared_any;
     constexpr int lds = 2 * 256 * 144 + 2 * 128 * 4;
     if (whole_pieces(a.x, a.d)) return launch_with_lds(&gemm_split_kernel<128, 128, 2, 2, true, true>, cleared, lds, a, 2 * num_cu, 256, s);
@@ -1015,7 +1018,7 @@ __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
             ra = dense_load<VEC>(ga, at + scol, a.d); // the caller's rows: no padding, any alignment
         };
         auto put = [&](const f32x4 &ra, const f32x4 (&rb)[4], int buf, int ks) {
-            *reinterpret_cast<f32x4 *>(&sA[buf][srow * kGemmLdsStride + scol]) = dense_zeros(ra, ks * kGemmBK + scol, a.d);
+            *reinterpret_cast<f32x4 *>(&sA[buf][srow * kGemmLdsStride + scol]) = dense_zeros<VEC>(ra, ks * kGemmBK + scol, a.d);
 #pragma unroll
             for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4 *>(&sB[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = rb[i];
         };
@@ -1157,7 +1160,7 @@ __global__ __launch_bounds__(256) void pair_ties_kernel(NearTiesArgs a)
 #pragma unroll 4
             for (int i = (int)sub * 4; i < a.ld; i += 64) {
                 const f32x4 w1 = *reinterpret_cast<const f32x4 *>(y1 + i), w2 = *reinterpret_cast<const f32x4 *>(y2 + i);
-                const f32x4 v = dense_zeros(dense_load<VEC>(x, i, a.d), i, a.d);
+                const f32x4 v = dense_zeros<VEC>(dense_load<VEC>(x, i, a.d), i, a.d);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     s1 = fmaf(v[j], w1[j], s1);
@@ -1201,7 +1204,7 @@ __global__ __launch_bounds__(256) void pair_ties_kernel(NearTiesArgs a)
 hipError_t launch_pair_ties(const NearTiesArgs &a, int num_cu, hipStream_t s)
 {
     if (a.last <= a.first) return hipSuccess;
-    if (a.ld % 64 != 0 || a.d > a.ld || a.among || !a.next || !a.left || !a.cmax_left || !a.x || !a.cent || !a.redo || !a.nredo) return hipErrorInvalidValue;
+    if (a.ld % 64 != 0 || a.d > a.ld || a.d < 4 || a.among || !a.next || !a.left || !a.cmax_left || !a.x || !a.cent || !a.redo || !a.nredo) return hipErrorInvalidValue;
     const dim3 grid(std::min((a.last - a.first + 255u) / 256u, 8u * (uint32_t)num_cu));
     hipLaunchKernelGGL(whole_pieces(a.x, a.d) ? pair_ties_kernel<true> : pair_ties_kernel<false>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
@@ -1217,7 +1220,7 @@ hipError_t launch_near_ties(const NearTiesArgs &a, int num_cu, hipStream_t s)
 
 hipError_t launch_gemm_listed(GemmArgs a, int num_cu, hipStream_t s)
 {
-    if (a.ld % 64 != 0 || a.d > a.ld || !a.best || !a.list || !a.nlisted) return hipErrorInvalidValue;
+    if (a.ld % 64 != 0 || a.d > a.ld || a.d < 4 || !a.best || !a.list || !a.nlisted) return hipErrorInvalidValue;
     a.many = 6u * (uint32_t)num_cu;
     const bool vec = whole_pieces(a.q, a.d);
     hipLaunchKernelGGL(vec ? gemm_listed_kernel<true> : gemm_listed_kernel<false>, dim3(3 * num_cu), dim3(256), 0, s, a);

@@ -153,6 +153,27 @@ __device__ __forceinline__ void line_to_operands(u32x4 &a, u32x4 &b)
     }
 }
 
+// Four floats of a dense row of d (four at least) from column `col` on, of a row that begins anywhere: the load, unconditional, from the
+// row's last four floats where fewer are left, and what the columns hold, zeros past the row's end.  In two parts, as
+// arranging them waits for the load.  (A load of 16 bytes wants no more than the alignment of its elements.)
+struct __attribute__((packed, aligned(4))) AnyFour {
+    u32x4 v;
+};
+__device__ __forceinline__ u32x4 any_load(const uint32_t *row, int col, int d)
+{
+    return reinterpret_cast<const AnyFour *>(row + (col + 4 <= d ? col : d - 4))->v;
+}
+__device__ __forceinline__ u32x4 any_zeros(u32x4 v, int col, int d)
+{
+    const int past = col + 4 - d; // how far the load was moved; all of it past the end from 4 on
+    u32x4 r = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int s = 0; s + j < 4; ++s) r[j] = (s == 0 ? past <= 0 : past == s) ? v[j + s] : r[j];
+    return r;
+}
+
 // 16 bytes of a query row (A) against 16 bytes of a stored row (B), fp32 accumulation: one
 // v_mfma_f32_16x16x32_f16, or four v_mfma_f32_16x16x4_f32.  Every kernel that scores a
 // (row, query) pair issues these in the same order over the row, so the value of a pair does
@@ -526,6 +547,7 @@ struct WorklistArgs {
     uint32_t hot_from;         // lists probed by more than this many queries of the batch are hot
     uint32_t *lcnt, *lstart, *lfill, *ltile, *lhtile; // [n_handles * nlist_max]
     bool lcnt_cleared;         // the coarse step of the same search has zeroed lcnt already
+    uint32_t tile_rows;        // with width: rows of a tile (a divisor of every handle's page size), or 0: a page
     uint32_t *pair_off;        // [nq][nprobe+1]
     uint32_t *ccnt;            // [nq] zeroed here (emission counters of the gated scan)
     uint32_t *slot_query, *slot_out; // [nq * nprobe]; slot_out = first position of the pair inside the query's range
@@ -546,7 +568,6 @@ struct WorklistArgs {
 // densely; the k-th best of them bounds the query's k-th best overall.
 struct SampleArgs {
     const int32_t *probes;     // [nq][nprobe]
-    uint32_t tile_rows;        // with width: rows of a tile (a divisor of every handle's page size), or 0: a page
     const uint16_t *qagent;
     int nq;
     int rescued;               // queries whose region overflows may be scored again: slot_out is cleared for that

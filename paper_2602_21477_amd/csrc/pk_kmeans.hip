@@ -63,9 +63,6 @@ __global__ __launch_bounds__(256) void km_scatter_kernel(KmeansArgs a, bool lds)
 // finished here, without atomics; the pieces of a longer one meet by float64 atomics, and km_finalize_kernel divides.
 // With a lane per dimension and one group, 262 144 x 768, 4096 clusters took 247 us, now 180 (4.5 TB/s), 200 000 x 128, 1024 clusters 91
 // and now 25, 100 000 x 1300, 300 clusters 188 and 141.
-struct __attribute__((packed, aligned(4))) AnyFour {
-    f32x4 v;
-};
 // ODD: some lane's dimensions reach past the row's end.
 template <int V, int T, bool ODD>
 __global__ __launch_bounds__(256) void km_accumulate_kernel(KmeansArgs a, uint32_t across)
@@ -98,7 +95,7 @@ __global__ __launch_bounds__(256) void km_accumulate_kernel(KmeansArgs a, uint32
     // kKmAhead members from e0 on (FULL: there are that many; else the last one again where there is none, and not added)
     auto batch = [&](uint32_t e0, auto full) {
         constexpr bool FULL = decltype(full)::value;
-        f32x4 v[kKmAhead][T];
+        u32x4 v[kKmAhead][T];
 #pragma unroll
         for (int w = 0; w < kKmAhead; ++w) {
             const uint32_t e = e0 + (uint32_t)w * groups;
@@ -106,7 +103,7 @@ __global__ __launch_bounds__(256) void km_accumulate_kernel(KmeansArgs a, uint32
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 if constexpr (V == 4) v[w][t] = reinterpret_cast<const AnyFour *>(row + from[t])->v;
-                else v[w][t][0] = row[from[t]];
+                else v[w][t][0] = __float_as_uint(row[from[t]]);
             }
         }
 #pragma unroll
@@ -116,7 +113,7 @@ __global__ __launch_bounds__(256) void km_accumulate_kernel(KmeansArgs a, uint32
             for (int t = 0; t < T; ++t)
 #pragma unroll
                 for (int c = 0; c < V; ++c) {
-                    const double x = (double)(there && own(t, c) ? v[w][t][c] : 0.f);
+                    const double x = (double)__uint_as_float(there && own(t, c) ? v[w][t][c] : 0u);
                     sum[t][c] += x;
                     sq += x * x;
                 }

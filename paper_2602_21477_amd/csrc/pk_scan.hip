@@ -956,20 +956,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 
 // ------------------------------------------------------------------ centroid scoring, small batches
 
-// Four floats of a dense row of d from column `col` on (kRawVec: d a multiple of 4, rows aligned): the load, unconditional and
-// past the row's end from its last floats, and the zeros behind the end, which wait for the load and go in when it is used.
+// Four floats of a dense row of d (four at least) from column `col` on (kRawVec: d a multiple of 4, rows aligned): the load,
+// unconditional and past the row's end from its last floats, and the zeros behind the end, which wait for the load and go in when it is used.
 template <int RAW>
 __device__ __forceinline__ u32x4 raw_load(const char *row, int col, int d)
 {
     const uint32_t *const x = reinterpret_cast<const uint32_t *>(row);
     if constexpr (RAW == kRawVec) return *reinterpret_cast<const u32x4 *>(x + (col < d ? col : d - 4));
-    u32x4 v;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = x[col + j < d ? col + j : d - 1];
-    return v;
+    else return any_load(x, col, d);
 }
+template <int RAW>
 __device__ __forceinline__ u32x4 raw_zeros(u32x4 v, int col, int d)
 {
+    if constexpr (RAW == kRawAny) return any_zeros(v, col, d);
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = col + j < d ? v[j] : 0u;
     return v;
@@ -1088,10 +1087,10 @@ __device__ __forceinline__ void centroid_body(const CentroidArgs &a, const Multi
         _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                         \
         {                                                                                         \
             if constexpr (RAW != kRawNot) {                                                       \
-                if (mt < mt_used) qbuf[mt][s4] = raw_load<RAW>(qp[mt], (it) * 64 + s4 * 16 + lg * 4, a.d); \
+                if (mt == 0 || mt < mt_used) qbuf[mt][s4] = raw_load<RAW>(qp[mt], (it) * 64 + s4 * 16 + lg * 4, a.d); \
             } else {                                                                              \
                 qbuf[mt][s4] = u32x4{0u, 0u, 0u, 0u};                                             \
-                if (mt < mt_used && qp[mt])                                                       \
+                if ((mt == 0 || mt < mt_used) && qp[mt])                                          \
                     qbuf[mt][s4] = *reinterpret_cast<const u32x4 *>(qp[mt] + (size_t)(it) * kIterBytes + s4 * 64); \
             }                                                                                     \
         }                                                                                         \
@@ -1099,10 +1098,10 @@ __device__ __forceinline__ void centroid_body(const CentroidArgs &a, const Multi
 #define PK_CCOMPUTE(xbuf, qbuf, it)                                                               \
     _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                             \
     {                                                                                             \
-        if (mt < mt_used) {                                                                       \
+        if (mt == 0 || mt < mt_used) {                                                            \
             _Pragma("unroll") for (int s4 = 0; s4 < 4; ++s4)                                      \
             {                                                                                     \
-                if constexpr (RAW != kRawNot) qbuf[mt][s4] = raw_zeros(qbuf[mt][s4], (it) * 64 + s4 * 16 + lg * 4, a.d); \
+                if constexpr (RAW != kRawNot) qbuf[mt][s4] = raw_zeros<RAW>(qbuf[mt][s4], (it) * 64 + s4 * 16 + lg * 4, a.d); \
                 mfma_step<PK_F32>(acc[mt], qbuf[mt][s4], xbuf[s4]);                               \
             }                                                                                     \
         }                                                                                         \
@@ -1225,7 +1224,7 @@ hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hip
 {
     if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0) return hipErrorInvalidValue;
     if (a.blk[m.n] == 0) return hipSuccess;
-    if (a.raw != kRawNot && (a.best || !a.meta.cand_off || a.d < 1 || a.d * 4 > a.row_bytes)) return hipErrorInvalidValue;
+    if (a.raw != kRawNot && (a.best || !a.meta.cand_off || a.d < 4 || a.d * 4 > a.row_bytes)) return hipErrorInvalidValue;
     switch (a.raw) {
     case kRawNot: return launch_centroid_raw<kRawNot>(a, m, s);
     case kRawVec: return launch_centroid_raw<kRawVec>(a, m, s);

@@ -640,6 +640,53 @@ def test_kmeans_update_of_rows_of_any_width(gpu_device, d, shift):
     assert abs(inertia[0] - want) <= 1e-9 * (want + float(x.double().square().sum()))
 
 
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 5, 6, 7, 61, 67, 130])
+@pytest.mark.parametrize("shift", [0, 1, 2])
+@pytest.mark.parametrize("metric", [IP, L2])
+def test_rows_of_odd_widths_that_begin_anywhere(gpu_device, d, shift, metric):
+    """Rows and queries whose 16-byte pieces are not aligned or run past the row's end, and such that have none: lists of a build (in tiles
+    and its last rows beyond them), of inserts and of searches of one and many queries are the nearest in 64 bits, up to the
+    rounding of fp32 sums of d products, and so are the rows that are found in them."""
+    g = torch.Generator(device="cuda").manual_seed(d)
+
+    def odd(rows):
+        room = torch.full((rows.numel() + 4,), float("nan"), device="cuda")
+        room[shift:shift + rows.numel()] = rows.flatten()
+        return room[shift:shift + rows.numel()].view(rows.shape)
+
+    n, nlist = 33000, 200
+    cent = torch.randn((nlist, d), device="cuda", generator=g)
+    x, q = torch.randn((n, d), device="cuda", generator=g), torch.randn((300, d), device="cuda", generator=g)
+    ix = B.Index(cent, odd(x), metric=metric, insert_reserve=8192)
+
+    def scores(rows, to):
+        s = rows.double() @ to.double().T
+        return 2 * s - to.double().square().sum(1) - rows.double().square().sum(1)[:, None] if metric == L2 else s
+
+    def bound(rows, to):  # both values of a pair, each 4 sqrt(d) roundings of its terms off
+        size = (rows.double().norm(dim=1)[:, None] + to.double().norm(dim=1).max()) ** 2
+        return 16 * math.sqrt(d) * 2.0 ** -24 * size
+
+    def nearest(rows, lists):
+        s = scores(rows, cent)
+        assert (s.max(1).values[:, None] - s.gather(1, lists) <= bound(rows, cent)).all()
+
+    try:
+        nearest(x, torch.from_numpy(lists_of(ix, n)).cuda()[:, None])
+        nearest(q, ix.coarse(odd(q), 1).long())
+        nearest(q[:1], ix.coarse(odd(q[:1]), 1).long())
+        for m in (3, 5000):
+            nearest(x[:m], ix.insert(odd(x[:m]), want_lists=True).long()[:, None])
+        for m in (1, 300):
+            ids, dist = ix.search(odd(q[:m]), 5, nlist)
+            every = torch.cat([x, x[:3], x[:5000]])
+            s = scores(q[:m], every)
+            off = bound(q[:m], every)
+            assert (s.topk(5, 1).values - s.gather(1, ids) <= off).all() and ((s.gather(1, ids) * (-1 if metric == L2 else 1) - dist).abs() <= off).all()
+    finally:
+        ix.close()
+
+
 @pytest.mark.parametrize("nprobe,k", [(30, 20), (30, 23), (30, 24), (30, 100), (30, 127), (30, 128), (10, 23), (10, 24), (10, 100), (10, 127)])
 @pytest.mark.parametrize("metric", [IP, L2])
 def test_bests_of_short_lists_among_many_values(gpu_device, nprobe, k, metric):
