@@ -1466,6 +1466,8 @@ struct AssignScratch {
     uint32_t *second, *close, *listed, *words;
     // words: [0] rows in listed[], [1] largest squared centroid norm, [2] rows of the first chunk in listed[], [3] rows of the
     // first chunk in close[], [4] rows of the others in close[] behind them, [5] the most that first halfs leave out of a centroid
+    // (all of them zero when assign_rows begins)
+    static constexpr int kWords = 6;
     void lay(Carver &c, int64_t n, int64_t chunk, int nlist_pad, int rb32)
     {
         halves = (double)n * nlist_pad * (rb32 / 4) >= kHalvesFrom || (size_t)chunk * rb32 > kHalvesBytes;
@@ -1481,7 +1483,7 @@ struct AssignScratch {
         second = c.take<uint32_t>((size_t)n);
         close = c.take<uint32_t>(halves ? (size_t)n : 0);
         listed = c.take<uint32_t>((size_t)n);
-        words = c.take<uint32_t>(6);
+        words = c.take<uint32_t>(kWords);
     }
 };
 
@@ -1590,7 +1592,6 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
     const int64_t by_gemm = tail > 0 && !coarse_tiles((uint32_t)tail, t.nlist_pad) ? n - tail : n;
     MultiArgs mm;
     std::memset(&mm, 0, sizeof(mm));
-    PK_HIP(launch_fill_u32(as.words, 0u, 6, s));
     const int64_t head = std::min(chunk, by_gemm);
     const double one = 0.68 + 0.00139 * t.ld, all = 0.82 + 0.00453 * t.ld; // ps per row, list: rounds 1 and 2 (128 and 768 elements)
     const uint32_t skip1_from = (uint32_t)((double)head * (1.0 - one / all)), skip2_from = (uint32_t)(head / 7 * 5);
@@ -1972,9 +1973,6 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
     if (hipMalloc(reinterpret_cast<void **>(&ix->ins_best), (size_t)kInsertFast * 12 + 32) != hipSuccess) return fail(PK_ERR_NOMEM);
     ix->ins_slots = reinterpret_cast<uint32_t *>(ix->ins_best + kInsertFast);
     ix->del_words = ix->ins_slots + kInsertFast;
-    if (launch_fill_u32(reinterpret_cast<uint32_t *>(ix->ins_best), 0xffffffffu, (size_t)kInsertFast * 2, s) != hipSuccess ||
-        launch_fill_u32(ix->del_words, 0u, 8, s) != hipSuccess)
-        return fail(PK_ERR_HIP);
     {
         // set-up for pk_search_noalloc: resolve this device's copy of its workspace array now, so
         // that the call itself finds the address ready (a failure here is reported by that call)
@@ -1988,13 +1986,18 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
     place_header(D, &ix->dev, &ix->pages_total, &cent, &cnorm, cfg, static_cast<char *>(arena), arena_bytes, x);
 
     if (hipMemcpyAsync(ix->dev, &D, sizeof(D), hipMemcpyHostToDevice, s) != hipSuccess) return fail(PK_ERR_HIP);
-    if (launch_fill_u32(D.list_len, 0u, cfg->nlist, s) != hipSuccess ||
-        launch_fill_u32(D.main_base, 0u, cfg->nlist, s) != hipSuccess ||
-        launch_fill_u32(D.main_pages, 0u, cfg->nlist, s) != hipSuccess ||
-        launch_fill_u32(D.dtab, 0xffffffffu, (size_t)cfg->nlist * x.max_dp, s) != hipSuccess ||
-        launch_fill_u32(D.ctr, 0u, 16, s) != hipSuccess ||
-        launch_fill_u32(reinterpret_cast<uint32_t *>(D.stats), 0u, 16, s) != hipSuccess ||
-        launch_fill_u32(D.ctr + 2, ix->pages_total, 1, s) != hipSuccess ||
+    FillRanges fr{};
+    fr.add(ix->ins_best, 0xffffffffu, (size_t)kInsertFast * 2);
+    fr.add(ix->del_words, 0u, 8);
+    fr.add(D.list_len, 0u, (size_t)cfg->nlist);
+    fr.add(D.main_base, 0u, (size_t)cfg->nlist);
+    fr.add(D.main_pages, 0u, (size_t)cfg->nlist);
+    fr.add(D.dtab, 0xffffffffu, (size_t)cfg->nlist * x.max_dp);
+    fr.add(D.ctr, 0u, 2);
+    fr.add(D.ctr + 2, ix->pages_total, 1);
+    fr.add(D.ctr + 3, 0u, 13);
+    fr.add(D.stats, 0u, 16);
+    if (launch_fill_ranges(fr, s) != hipSuccess ||
         launch_store_centroids(centroids, cfg->nlist, cfg->d, x.dpad32, x.nlist_pad, cfg->metric, cent, cnorm, s) !=
             hipSuccess)
         return fail(PK_ERR_HIP);
@@ -2044,33 +2047,27 @@ int pk_index_build(const pk_config *cfg, const float *centroids, const float *ve
         };
         // assignment: a top-1 coarse search per chunk (Section 3.1 rule = rank-1 probe)
         const Table table{ix->dev, cent, cnorm, cfg->nlist, x.nlist_pad, cfg->d, x.dpad32, cfg->metric};
+        FillRanges words{};
+        words.add(as.words, 0u, AssignScratch::kWords);
+        words.add(d_cnt, 0u, (size_t)cfg->nlist);
+        if (launch_fill_ranges(words, s) != hipSuccess) return fail2(PK_ERR_HIP);
         rc = assign_rows(vectors, n, table, ix->num_cu, as, chunk, d_best, s);
         if (rc != PK_OK) return fail2(rc);
-        if (launch_fill_u32(d_cnt, 0u, (size_t)cfg->nlist, s) != hipSuccess ||
-            launch_lists_of_best(d_best, n, cfg->nlist, d_assign, d_cnt, d_slots, s) != hipSuccess ||
-            hipMemcpyAsync(cnt.data(), d_cnt, (size_t)cfg->nlist * sizeof(uint32_t), hipMemcpyDeviceToHost, s) !=
-                hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return fail2(PK_ERR_HIP);
-        std::vector<uint32_t> mbase((size_t)cfg->nlist), mpages((size_t)cfg->nlist);
-        uint64_t used = 0;
-        for (int l = 0; l < cfg->nlist; ++l) {
-            mbase[l] = (uint32_t)used;
-            mpages[l] = (cnt[l] + x.P - 1) / x.P;
-            used += mpages[l];
-        }
-        if (used > ix->pages_total) return fail2(PK_ERR_NOMEM);
-        const uint32_t used32 = (uint32_t)used;
-        if (hipMemcpyAsync(D.main_base, mbase.data(), mbase.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(D.main_pages, mpages.data(), mpages.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(D.list_len, cnt.data(), cnt.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(D.ctr, &used32, 4, hipMemcpyHostToDevice, s) != hipSuccess ||
+        // the lists' extents are laid out on the device (with a wait for the counts and four copies back in
+        // between, and a launch per cleared array, a build of 300 000 x 1024 took 20 us more of 1500); if the
+        // pages do not suffice no row is written
+        if (launch_lists_of_best(d_best, n, cfg->nlist, d_assign, d_cnt, d_slots, s) != hipSuccess ||
+            launch_build_pages(ix->dev, d_cnt, s) != hipSuccess ||
             launch_build_places(ix->dev, d_assign, n, d_slots, s) != hipSuccess ||
             launch_scatter_build(ix->dev, vectors, ids, d_slots, n, 0, x.row_bytes / (cfg->storage == PK_F16 ? 128 : 256), s) != hipSuccess ||
+            hipMemcpyAsync(cnt.data(), d_cnt, (size_t)cfg->nlist * sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             return fail2(PK_ERR_HIP);
+        uint64_t used = 0;
+        for (int l = 0; l < cfg->nlist; ++l) used += (cnt[l] + x.P - 1) / x.P;
+        if (used > ix->pages_total) return fail2(PK_ERR_NOMEM);
         (void)hipFree(scr);
-        ix->pages_known = used32;
+        ix->pages_known = (uint32_t)used;
     }
     if (hipStreamSynchronize(s) != hipSuccess) return fail(PK_ERR_HIP);
     ix->n_total = n;
@@ -2212,10 +2209,17 @@ int pk_kmeans(const float *vectors, int64_t n, int32_t d, int32_t nlist, int32_t
         PK_HIP(hipMemcpyAsync(tdev, &D, sizeof(D), hipMemcpyHostToDevice, s));
         for (int it = 0; it < iters; ++it) {
             PK_HIP(launch_store_centroids(centroids, nlist, d, x.dpad32, x.nlist_pad, PK_METRIC_L2, cent, cnorm, s));
-            PK_TRY(assign_rows(vectors, n, table, cus > 0 ? cus : 256, as, chunk, best, s));
-            PK_HIP(launch_fill_u32(ka.cnt, 0u, (size_t)nlist, s));
-            PK_HIP(launch_lists_of_best(best, n, nlist, assign, ka.cnt, nullptr, s));
             ka.inertia = inertia + it;
+            FillRanges fr{};
+            fr.add(as.words, 0u, AssignScratch::kWords);
+            fr.add(ka.cnt, 0u, (size_t)nlist);
+            fr.add(ka.fill, 0u, (size_t)nlist);
+            fr.add(ka.sums, 0u, (size_t)nlist * d * 2);
+            fr.add(ka.sq, 0u, (size_t)nlist * 2);
+            fr.add(ka.inertia, 0u, 2);
+            PK_HIP(launch_fill_ranges(fr, s));
+            PK_TRY(assign_rows(vectors, n, table, cus > 0 ? cus : 256, as, chunk, best, s));
+            PK_HIP(launch_lists_of_best(best, n, nlist, assign, ka.cnt, nullptr, s));
             PK_HIP(launch_kmeans_update(ka, s));
         }
         if (assign_out) PK_HIP(hipMemcpyAsync(assign_out, assign, (size_t)n * 4, hipMemcpyDeviceToDevice, s));

@@ -267,20 +267,19 @@ __device__ __forceinline__ float row_sum(float (&part)[NP][4])
     return sum;
 }
 
-// SUB lanes per row, rows [0, m) from `x` (dense, d floats) and then n_c rows of the (padded) centroid table.  A lane has four elements
-// of each of a row's T parts of 4 SUB.
+// SUB lanes per row, of rows [0, m) from `x` (dense, d floats) or (CENT) of the n_c of the (padded) centroid table.  A lane has four
+// elements of each of a row's T parts of 4 SUB.  top, top_left (of centroids): raised to the row's squared length and to what its first
+// halfs leave out, as bits (not negative: in the order of the values).
 // Bound by memory (300 000 rows of 4 KB read and written at 4.3 TB/s), and where rows are short by the rate at which workgroups
 // start: with a wave per row, 32768 rows of up to 256 elements take 26 - 31 us, however short they are.  There several rows
 // share a wave, and the workgroups stay and take row after row (long rows: 37 -> 40 us of 32768 x 768): 32768 x 128 27 -> 16 us.
-template <int T, int SUB>
-__device__ __forceinline__ void split_row(const SplitRowsArgs &a, const MultiArgs &mm, uint32_t row, int lane)
+template <int T, int SUB, bool CENT>
+__device__ __forceinline__ void split_row(const SplitRowsArgs &a, const MultiArgs &mm, uint32_t r, int lane, uint32_t &top, uint32_t &top_left)
 {
     static_assert(SUB == 64 || 4 * SUB * T <= 256, "rows that share a wave have 256 elements at most");
     constexpr int NP = SUB == 64 ? 1 : T; // sums that are kept apart (see row_sum)
-    const bool cent = row >= a.m;
-    const uint32_t r = cent ? row - a.m : row;
-    const int ld = a.ld, d = cent ? ld : a.d;
-    const float *src = cent ? a.c + (size_t)r * ld : a.x + (size_t)r * d;
+    const int ld = a.ld, d = CENT ? ld : a.d;
+    const float *src = CENT ? a.c + (size_t)r * ld : a.x + (size_t)r * d;
     const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0; // (nearly always the same for the whole wave)
     f32x4 v[T];
     float big = 0.f, sq[NP][4] = {}, sq16[NP][4] = {}, off[NP][4] = {};
@@ -313,7 +312,7 @@ __device__ __forceinline__ void split_row(const SplitRowsArgs &a, const MultiArg
     int s = 14 - ((int)(__float_as_uint(big) >> 23) - 127);
     s = s < -126 ? -126 : (s > 126 ? 126 : s);
     const float scale = __uint_as_float((uint32_t)(s + 127) << 23);
-    char *dst = cent ? a.cs : a.xs, *first = cent ? a.ch : a.xh;
+    char *dst = CENT ? a.cs : a.xs, *first = CENT ? a.ch : a.xh;
     if (dst) dst += (size_t)r * ld * 4; // (null: the rows are wanted in their other forms only)
     if (first) first += (size_t)r * ld * 2;
 #pragma unroll
@@ -335,9 +334,9 @@ __device__ __forceinline__ void split_row(const SplitRowsArgs &a, const MultiArg
             *reinterpret_cast<half4 *>(p) = hi;
             *reinterpret_cast<half4 *>(p + 64) = lo;
         }
-        if (!cent && a.copy) *reinterpret_cast<f32x4 *>(a.copy + (size_t)r * ld + i) = v[t];
+        if (!CENT && a.copy) *reinterpret_cast<f32x4 *>(a.copy + (size_t)r * ld + i) = v[t];
     }
-    if (!cent && a.half_rows) { // the row as a half-precision index stores it: rounded to nearest even, norm of the rounded values
+    if (!CENT && a.half_rows) { // the row as a half-precision index stores it: rounded to nearest even, norm of the rounded values
         char *h = a.half_rows + (size_t)r * a.half_bytes;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
@@ -355,20 +354,15 @@ __device__ __forceinline__ void split_row(const SplitRowsArgs &a, const MultiArg
     }
     const float norm16 = row_sum<SUB>(sq16);
     const float rest = row_sum<SUB>(off);
-    if (lane != 0) return;
     const float back = __uint_as_float((uint32_t)(127 - s) << 23);
     const float left = sqrtf(rest) * back; // length of what the first halfs leave out
-    if (cent) {
-        a.c_back[r] = back;
-        // (not negative: their bits are in the order of the values; a look first, as every row's atomic meets the others' at one word)
-        auto raise = [](uint32_t *word, float v) {
-            if (word && __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < __float_as_uint(v))
-                atomicMax(word, __float_as_uint(v));
-        };
-        raise(a.cmax, norm);
-        raise(a.cmax_left, left);
+    if constexpr (CENT) {
+        if (lane == 0) a.c_back[r] = back;
+        top = max(top, __float_as_uint(norm));
+        top_left = max(top_left, __float_as_uint(left));
         return;
     }
+    if (lane != 0) return;
     if (a.left) a.left[r] = left;
     if (a.x_back) a.x_back[r] = back;
     if (a.second) a.second[r] = 0xffffffffu;
@@ -385,17 +379,41 @@ __device__ __forceinline__ void split_row(const SplitRowsArgs &a, const MultiArg
     }
 }
 
+// The first workgroups take the centroids, and raise the largest lengths once each: the atomics meet at one word, 7 ns each, and
+// hold up the other rows (one per centroid: the first 32768 rows x 768 with 4096 lists 66 us, with none 31; now 46).
 template <int T, int SUB>
 __global__ __launch_bounds__(256) void split_rows_kernel(SplitRowsArgs a, MultiArgs mm)
 {
     const int lane = threadIdx.x & (SUB - 1);
     constexpr uint32_t kRows = 256 / SUB; // of a workgroup at a time
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < a.meta.nclear; i += gridDim.x * blockDim.x) a.meta.clear[i] = 0u;
-    uint32_t row = blockIdx.x * kRows + threadIdx.x / SUB;
+    const uint32_t group = threadIdx.x / SUB, cents = (a.n_c + kRows - 1) / kRows;
+    uint32_t top = 0, top_left = 0;
+    if (blockIdx.x < cents) {
+        __shared__ uint32_t s_top[2][4];
+        const uint32_t r = blockIdx.x * kRows + group;
+        if (r < a.n_c) split_row<T, SUB, true>(a, mm, r, lane, top, top_left);
+        for (int off = SUB; off < 64; off <<= 1) {
+            top = max(top, (uint32_t)__shfl_xor((int)top, off));
+            top_left = max(top_left, (uint32_t)__shfl_xor((int)top_left, off));
+        }
+        if ((threadIdx.x & 63u) == 0) {
+            s_top[0][threadIdx.x >> 6] = top;
+            s_top[1][threadIdx.x >> 6] = top_left;
+        }
+        __syncthreads();
+        uint32_t *const word = threadIdx.x == 0 ? a.cmax : threadIdx.x == 1 ? a.cmax_left : nullptr;
+        if (!word) return;
+        const uint32_t *const w = s_top[threadIdx.x];
+        const uint32_t v = max(max(w[0], w[1]), max(w[2], w[3]));
+        if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < v) atomicMax(word, v);
+        return;
+    }
+    uint32_t row = (blockIdx.x - cents) * kRows + group;
     if constexpr (SUB == 64) {
-        if (row < a.m + a.n_c) split_row<T, SUB>(a, mm, row, lane);
+        if (row < a.m) split_row<T, SUB, false>(a, mm, row, lane, top, top_left);
     } else {
-        for (; row < a.m + a.n_c; row += gridDim.x * kRows) split_row<T, SUB>(a, mm, row, lane);
+        for (; row < a.m; row += (gridDim.x - cents) * kRows) split_row<T, SUB, false>(a, mm, row, lane, top, top_left);
     }
 }
 
@@ -411,13 +429,10 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStr
                                         split_rows_kernel<6, 64>};
     static_assert(PK_MAX_DIM <= 6 * 256, "a row has six parts at most");
     const int wide = a.half_rows ? std::max(a.ld, a.half_bytes / 2) : a.ld; // (a half-precision row may be padded further)
-    const uint32_t rows = a.m + a.n_c;
-    if (wide <= 256) {
-        const uint32_t each = wide <= 64 ? 16u : 8u; // rows of a workgroup at a time
-        hipLaunchKernelGGL(shorter[(wide - 1) / 64], dim3(std::min((rows + each - 1u) / each, kSplitRowsGrid)), dim3(256), 0, s, a, mm);
-    } else {
-        hipLaunchKernelGGL(longer[(wide + 255) / 256 - 2], dim3((rows + 3u) / 4u), dim3(256), 0, s, a, mm);
-    }
+    const uint32_t each = wide <= 64 ? 16u : wide <= 256 ? 8u : 4u; // rows of a workgroup at a time
+    const uint32_t most = (a.m + each - 1u) / each, cents = (a.n_c + each - 1u) / each;
+    if (wide <= 256) hipLaunchKernelGGL(shorter[(wide - 1) / 64], dim3(cents + std::min(most, kSplitRowsGrid)), dim3(256), 0, s, a, mm);
+    else hipLaunchKernelGGL(longer[(wide + 255) / 256 - 2], dim3(cents + most), dim3(256), 0, s, a, mm);
     return hipGetLastError();
 }
 

@@ -120,6 +120,45 @@ __device__ void write_row(const DevIndex &ix, uint32_t l, uint32_t slot, const f
     }
 }
 
+// Build: the lists' extents from their lengths, one behind the other, and the pages they take together (ctr[0]; more than there
+// are, ctr[2], and no row is placed).  One workgroup, 1024 lists at a time.
+__global__ __launch_bounds__(1024) void build_pages_kernel(const DevIndex *ixp, const uint32_t *cnt)
+{
+    __shared__ uint32_t s_wave[16];
+    const DevIndex &ix = *ixp;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, P = (uint32_t)ix.P, nlist = (uint32_t)ix.nlist;
+    uint64_t before = 0; // pages of the lists before this round's
+    for (uint32_t l0 = 0; l0 < nlist; l0 += 1024u) {
+        const uint32_t l = l0 + tid, len = l < nlist ? cnt[l] : 0u, pages = (len + P - 1u) / P;
+        uint32_t upto = pages; // of this thread's list and the wave's before it
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(upto, off);
+            if (lane >= (uint32_t)off) upto += y;
+        }
+        if (lane == 63u) s_wave[wave] = upto;
+        __syncthreads();
+        uint32_t ahead = 0, all = 0;
+        for (uint32_t w = 0; w < 16u; ++w) {
+            ahead += w < wave ? s_wave[w] : 0u;
+            all += s_wave[w];
+        }
+        if (l < nlist) {
+            ix.main_base[l] = (uint32_t)before + ahead + upto - pages;
+            ix.main_pages[l] = pages;
+            ix.list_len[l] = len;
+        }
+        before += all;
+        __syncthreads(); // (s_wave: read before the next round writes it)
+    }
+    if (tid == 0) ix.ctr[0] = before < 0xffffffffull ? (uint32_t)before : 0xffffffffu;
+}
+
+hipError_t launch_build_pages(const DevIndex *ix, const uint32_t *cnt, hipStream_t s)
+{
+    hipLaunchKernelGGL(build_pages_kernel, dim3(1), dim3(1024), 0, s, ix, cnt);
+    return hipGetLastError();
+}
+
 // From a row's place in its list to its number among all rows of the build-time extents (fewer than 2^32 of at least 256 bytes
 // fit the card), in place: what the scatter needs is then one word per row.  With list and place kept apart the scratch of
 // 300 000 rows passes 2 MB, from where on mapping and unmapping it takes 0.6 ms (build of 300 000 x 1024 2514 and 1896 us).
@@ -127,9 +166,10 @@ constexpr uint32_t kNoRow = 0xffffffffu;
 __global__ __launch_bounds__(256) void build_places_kernel(const DevIndex *ixp, const int32_t *assign, int64_t n, uint32_t *slots)
 {
     const DevIndex &ix = *ixp;
+    const bool fit = ix.ctr[0] <= ix.ctr[2];
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         const uint32_t l = (uint32_t)assign[i]; // (no assignment leaves a number beyond the table, and it is not counted either)
-        slots[i] = l < (uint32_t)ix.nlist ? ix.main_base[l] * (uint32_t)ix.P + slots[i] : kNoRow;
+        slots[i] = fit && l < (uint32_t)ix.nlist ? ix.main_base[l] * (uint32_t)ix.P + slots[i] : kNoRow;
     }
 }
 

@@ -262,6 +262,21 @@ struct MultiArgs {
 // (each enqueues on `s` and returns the HIP status of the launch)
 
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s);
+// several ranges in one launch: a launch that clears a few words takes 2 - 5 us of the stream, and as long of the host
+struct FillRanges {
+    static constexpr int kMost = 10;
+    uint32_t *p[kMost];
+    size_t n[kMost];
+    uint32_t v[kMost];
+    int ranges;
+    void add(void *at, uint32_t value, size_t words)
+    {
+        p[ranges] = static_cast<uint32_t *>(at);
+        n[ranges] = words;
+        v[ranges++] = value;
+    }
+};
+hipError_t launch_fill_ranges(const FillRanges &a, hipStream_t s);
 hipError_t launch_copy_i32(const int32_t *src, int32_t *dst, int64_t n, hipStream_t s);
 
 // queries -> storage type, zero padded rows, squared norms of the converted values
@@ -728,6 +743,7 @@ hipError_t launch_gemm_split_listed(const SplitGemmArgs &a, int num_cu, hipStrea
 // place of its own for every row among those of its list
 hipError_t launch_lists_of_best(const unsigned long long *best, int64_t n, int nlist, int32_t *assign, uint32_t *cnt, uint32_t *slots, hipStream_t s);
 constexpr int kLdsLists = 8192; // most lists that a workgroup counts in LDS (32 KB)
+hipError_t launch_build_pages(const DevIndex *ix, const uint32_t *cnt, hipStream_t s); // main_base, main_pages, list_len and ctr[0]
 hipError_t launch_build_places(const DevIndex *ix, const int32_t *assign, int64_t n, uint32_t *slots, hipStream_t s);
 hipError_t launch_scatter_build(const DevIndex *ix, const float *x, const int64_t *ids, const uint32_t *rows_at, int64_t n, int64_t id0,
                                 int pieces, hipStream_t s); // (pieces: of 64 elements in a stored row)
@@ -793,13 +809,13 @@ struct KmeansArgs {
     int64_t n;
     int d, nlist;
     uint32_t *cnt;         // [nlist] in: members of each cluster
-    uint32_t *start, *fill; // [nlist] each (scratch)
+    uint32_t *start, *fill; // [nlist] each (scratch; fill: zeros)
     uint32_t *piece0;      // [nlist + 1] (scratch) parts of at most 256 members of the clusters before each one
     uint32_t *members;     // [n] row numbers in cluster-major order (scratch)
     float *centroids;      // [nlist][d] in: centroids the assignment used; out: means of the members
-    double *sums;          // [nlist][d] scratch: per-cluster totals
-    double *sq;            // [nlist] scratch: per-cluster totals of |x|^2
-    double *inertia;       // one word: receives the sum of squared distances of the assignment
+    double *sums;          // [nlist][d] scratch, zeros: per-cluster totals
+    double *sq;            // [nlist] scratch, zeros: per-cluster totals of |x|^2
+    double *inertia;       // one word, zero: receives the sum of squared distances of the assignment
 };
 hipError_t launch_kmeans_update(const KmeansArgs &a, hipStream_t s);
 // Insert: slots for the vectors of every handle of the batch (one workgroup per handle; rows [qlo[a], qlo[a+1]) of

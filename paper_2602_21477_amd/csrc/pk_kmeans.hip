@@ -192,18 +192,10 @@ __global__ __launch_bounds__(256) void km_finalize_kernel(KmeansArgs a)
 hipError_t launch_kmeans_update(const KmeansArgs &a, hipStream_t s)
 {
     if (a.n <= 0 || a.nlist <= 0 || a.d <= 0 || a.d > PK_MAX_DIM) return hipErrorInvalidValue;
-    hipError_t e = launch_fill_u32(a.fill, 0u, (size_t)a.nlist, s);
-    if (e != hipSuccess) return e;
-    e = launch_fill_u32(reinterpret_cast<uint32_t *>(a.inertia), 0u, 2, s);
-    if (e != hipSuccess) return e;
     const bool lds = a.nlist <= kLdsLists;
     hipLaunchKernelGGL(km_offsets_kernel, dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(km_scatter_kernel, dim3((uint32_t)((a.n + kKmRun - 1) / kKmRun)), dim3(256),
                        lds ? (size_t)a.nlist * 4 : 0, s, a, lds);
-    e = launch_fill_u32(reinterpret_cast<uint32_t *>(a.sums), 0u, (size_t)a.nlist * a.d * 2, s);
-    if (e != hipSuccess) return e;
-    e = launch_fill_u32(reinterpret_cast<uint32_t *>(a.sq), 0u, (size_t)a.nlist * 2, s);
-    if (e != hipSuccess) return e;
     const dim3 pieces((uint32_t)(a.n / kKmChunk + std::min<int64_t>(a.n, a.nlist) + 1)), threads(256); // at least as many as there are
     auto go = [&](auto kernel, int v) { // lanes per row: what it takes, or all of the workgroup's
         const uint32_t across = std::min(256u, (uint32_t)((a.d + v - 1) / v));

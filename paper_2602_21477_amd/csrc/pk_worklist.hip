@@ -29,6 +29,25 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s)
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void fill_ranges_kernel(FillRanges a)
+{
+    for (int r = 0; r < a.ranges; ++r) {
+        uint32_t *const p = a.p[r];
+        const uint32_t v = a.v[r];
+        const size_t n = a.n[r];
+        for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = v;
+    }
+}
+
+hipError_t launch_fill_ranges(const FillRanges &a, hipStream_t s)
+{
+    if (a.ranges < 1 || a.ranges > FillRanges::kMost) return hipErrorInvalidValue;
+    size_t most = 1;
+    for (int r = 0; r < a.ranges; ++r) most = a.n[r] > most ? a.n[r] : most;
+    hipLaunchKernelGGL(fill_ranges_kernel, dim3((uint32_t)((most + 255) / 256 < 1024 ? (most + 255) / 256 : 1024)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------ query preparation
 
 // one workgroup per query: convert to the storage type, zero pad to row_bytes, squared norm

@@ -903,3 +903,37 @@ def test_queries_copied_beside_the_coarse_step(gpu_device, storage, metric, d, n
     finally:
         ix.close()
         other.close()
+
+
+@pytest.mark.parametrize("nlist", [1, 63, 64, 65, 1023, 1024, 1025, 2500])
+def test_extents_of_built_lists_are_laid_one_behind_the_other(gpu_device, nlist):
+    """Lists of no row, of less than a page, of whole pages and of more, on both sides of what the layout takes at a time: every
+    row in its own list, and as many pages as the lists' lengths need; with a page less the build is refused."""
+    page = 32
+    lens = (torch.arange(nlist) * 37 % 70) * (torch.arange(nlist) % 5 != 3)
+    lens[0] = 3 * page
+    lists = torch.repeat_interleave(torch.arange(nlist), lens)
+    lists = lists[torch.randperm(len(lists), generator=torch.Generator().manual_seed(nlist))]
+    cent = torch.stack([torch.arange(nlist) % 50, torch.arange(nlist) // 50, torch.zeros(nlist), torch.ones(nlist)], 1).float()
+    pages = int(((lens + page - 1) // page).sum())
+    # rows are their list's centroid: under L2 every other list is a unit away at least
+    c = B.pk_config(4, nlist, L2, F32, page, 1)
+    one = B.pk_arena_bytes(c, 0, (nlist + 1) * page) - B.pk_arena_bytes(c, 0, nlist * page)  # a page's bytes
+    room = B.pk_arena_bytes(c, 0, 0)
+    ix = B.Index(cent.cuda(), cent[lists].cuda(), metric=L2, page_vecs=page, max_delta_pages=1, arena_bytes=room + (pages + 1) * one)
+    try:
+        st = ix.stats()
+        assert st.pages_used == pages and st.device_error == 0 and st.n_total == len(lists)
+        assert ix.list_lengths().tolist() == lens.tolist()
+        for l in {0, 1, nlist // 2, nlist - 2, nlist - 1} & set(range(nlist)):
+            assert sorted(ix.list_ids(l).tolist()) == (lists == l).nonzero()[:, 0].tolist()
+        ids, _ = ix.search(cent[lists[:64]].cuda().contiguous(), 1, 1)
+        assert (lists[ids[:, 0].cpu()] == lists[: len(ids)]).all()
+        spare = int(st.pages_total) - pages
+        assert spare >= 0
+    finally:
+        ix.close()
+    with pytest.raises(B.PancakeError) as e:
+        B.Index(cent.cuda(), cent[lists].cuda(), metric=L2, page_vecs=page, max_delta_pages=1,
+                arena_bytes=room + (pages + 1) * one - (spare + 1) * one)
+    assert e.value.status == B.PK_ERR_NOMEM
