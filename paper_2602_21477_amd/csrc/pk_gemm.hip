@@ -550,8 +550,8 @@ __device__ __forceinline__ void best_of_split(const SplitGemmArgs &a, const f32x
 // then depend on which kernel its call takes.)  By its own values alone,
 // 28 rows came out on the wrong side of a near tie, against 64 bits, over seven sets of 0.5 - 1 M rows
 // (64 <= d <= 1536), and 46 by the fp32 kernel's.
-template <int BM, int BN, int WM, int WN, bool LISTED, bool VEC = true>
-__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(SplitGemmArgs a)
+template <int BM, int BN, int WM, int WN, bool LISTED, bool VEC>
+__device__ __forceinline__ void split_tiles(const SplitGemmArgs &a, char *smem, int rows)
 {
     constexpr int TH = WM * WN * 64;
     constexpr int MI = BM / WM / 32, NI = BN / WN / 32; // 32 x 32 blocks per wave
@@ -559,12 +559,9 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     constexpr int LOADS = (BM + BN) * 8 / TH;           // 16-byte pieces per thread and step
     static_assert((BM * 8) % TH == 0 && (BN * 8) % TH == 0, "a thread's piece is of A or of B for the whole workgroup");
     constexpr int ALOADS = BM * 8 / TH;
-    extern __shared__ __align__(16) char smem[]; // [2][BM + BN][LD]
-    if (a.skipped && *a.skipped > a.skip_from) return; // near ties are the rule: the next kernel takes these rows whole
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int l32 = lane & 31, kg = lane >> 5;
-    const int rows = LISTED ? (int)*a.nlisted : a.m;
     const uint32_t tn = (uint32_t)(a.n_pad + BN - 1) / BN, tm = (uint32_t)(rows + BM - 1) / BM, total = tn * tm;
     float *const s_col = reinterpret_cast<float *>(smem + (size_t)2 * (BM + BN) * LD); // [2][BN]
     char *const put = smem + (size_t)(tid >> 3) * LD + (tid & 7) * 16;
@@ -695,6 +692,25 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     best_of_split<BN, MI, NI>(a, acc, s_col + wn * (BN / WN), m0 + wm * (BM / WM), n0 + wn * (BN / WN), rows, lane, LISTED);
     if constexpr (!LISTED) return;
     }
+}
+
+template <int BM, int BN, int WM, int WN, bool LISTED, bool VEC = true>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(SplitGemmArgs a)
+{
+    extern __shared__ __align__(16) char smem[]; // [2][BM + BN][144], then [2][BN] floats
+    if (a.skipped && *a.skipped > a.skip_from) return; // near ties are the rule: the next kernel takes these rows whole
+    const int rows = LISTED ? (int)*a.nlisted : a.m;
+    if constexpr (LISTED) {
+        // Few rows are bound by the steps of one tile (64 x 64: 0.6 us per 32 elements, 128 x 128: 1.0): quarter tiles while the
+        // grid takes them all at once.  300 000 x 1024, what is left of a chunk for 512 lists 32 -> 21 us, 262 144 x 768 for 4096
+        // 29 -> 17; two rounds of them take as long as one of the others.
+        const uint32_t quarters = (uint32_t)((a.n_pad + 63) / 64) * (uint32_t)((rows + 63) / 64);
+        if (quarters <= gridDim.x) {
+            split_tiles<64, 64, 2, 2, true, VEC>(a, smem, rows);
+            return;
+        }
+    }
+    split_tiles<BM, BN, WM, WN, LISTED, VEC>(a, smem, rows);
 }
 
 // A wave's products of first halfs into the rows' best, second best and third: as best_of_split, but a value carries its

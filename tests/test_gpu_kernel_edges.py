@@ -434,6 +434,30 @@ def test_rows_with_several_lists_alike_go_where_the_fp32_scores_say(gpu_device, 
         ix.close()
 
 
+@pytest.mark.parametrize("metric,d", [(IP, 512), (L2, 451)])
+@pytest.mark.parametrize("many", [1, 64, 65, 4096, 4097, 9000])  # (512 lists: quarter tiles up to 4096 rows on 256 CUs)
+def test_few_rows_with_several_near_lists_among_many_clear_ones(gpu_device, metric, d, many):
+    """Rows that the first halves leave to the products of the whole values, `many` of a chunk, beside rows that are clear: the
+    lists are those of the fp32 coarse step, row for row."""
+    n, half = 2 * 32768, 500
+    assert by_first_halves(n, d, 512)
+    g = torch.Generator(device="cuda").manual_seed(d + many)
+    c = torch.randn((half, d), device="cuda", generator=g)
+    near = [c[:4] * (1 + torch.randint(-1, 2, (4, d), device="cuda", generator=g) * 2.0 ** -11) for _ in range(3)]
+    cent = torch.cat([c] + near)
+    lists = torch.randint(4, half, (n,), device="cuda", generator=g)
+    for first in (0, 32768):  # (the chunks after the first are decided together)
+        at = first + torch.randperm(32768, device="cuda", generator=g)[:many]
+        lists[at] = torch.randint(4, (many,), device="cuda", generator=g)
+    x = c[lists] + 0.2 * torch.randn((n, d), device="cuda", generator=g)
+    ix = B.Index(cent, x, metric=metric)
+    try:
+        want = torch.cat([ix.coarse(x[i:i + 16384].contiguous(), 1)[:, 0].cpu() for i in range(0, n, 16384)])
+        assert torch.equal(torch.from_numpy(lists_of(ix, n)), want.long())
+    finally:
+        ix.close()
+
+
 @pytest.mark.parametrize("at", [0, 37, 1500])
 def test_list_whose_products_are_nothing_is_found(gpu_device, at):
     """Inner product, every list but one on the other side of the rows and that one across them: its product is zero, and the best."""
