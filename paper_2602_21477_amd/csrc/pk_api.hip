@@ -536,7 +536,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     p.sp = (k + own->P - 1) / own->P; // sample pages: at least k rows when the first pages are full
     uint64_t tiles = 0, wmax = 0, lmax = 0, bytes = 0;
     double lmean = 0; // rows per list on average (the largest over the handles)
-    double distinct = 0; // bytes of rows in lists that some query probes, where the queries spread evenly
+    double distinct = 0, probed = 0; // bytes of rows in lists that some query probes, and these lists, where the queries spread evenly
     int nlist_hi = 0, pad_hi = 0;
     const int mq_least = worst ? 16 : std::min(p.mq_f, p.mq_h);
     bool pages_of_64 = true;
@@ -556,7 +556,9 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         lmax = std::max(lmax, wq_ub(ix, 1)); // the longest list as it may be now
         bytes += (uint64_t)ix->n_total * (uint64_t)own->row_bytes;
         lmean = std::max(lmean, (double)ix->n_total / ix->cfg.nlist);
-        distinct += (1.0 - std::pow(1.0 - (double)std::min(nprobe, ix->cfg.nlist) / ix->cfg.nlist, (double)nqa)) * (double)ix->n_total * own->row_bytes;
+        const double share = 1.0 - std::pow(1.0 - (double)std::min(nprobe, ix->cfg.nlist) / ix->cfg.nlist, (double)nqa);
+        distinct += share * (double)ix->n_total * own->row_bytes;
+        probed += share * ix->cfg.nlist;
         const uint64_t pp = w / ix->P + nprobe;
         const uint64_t pages = std::min<uint64_t>(pages_used_ub(ix, ahead), nqa * pp);
         tiles += pages + nqa * pp / mq_least + 1;
@@ -673,16 +675,16 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
             p.mins = width > kReadOnce ? values / 16 : 0;
             p.slots = slots;
             // Few tiles: smaller ones, by the kernel that has a tile per workgroup, while these leave CUs idle.  Tiles per CU (of 64
-            // rows, and as many per list as its queries take) up to which it is the faster one, over some four hundred searches of
-            // 1 - 256 queries and 10 000 - 600 000 rows of three slices and more, geometric means of the gain and the extremes: pages of
-            // 128 rows, rows of 3 - 24 slices 1.05 up to 0.8 (0.92 - 1.23), 0.97 from 1 to 2 (0.90 - 1.11), 0.95 beyond; of 256 1.12 up to 2
-            // (0.93 - 1.49), 1.06 up to 4 (0.91 - 1.24); instead of the sliced-query kernel 1.22 up to 1 (1.00 - 1.59), 1.05 up to 3 (0.95 -
-            // 1.62), 1.0 beyond.  Rows of one and two slices 0.8 - 1.04: their tiles are no chain, and twice as many cost more.
+            // rows, three quarters of one over per list, and as many per list as its queries take) up to which it is the faster one, over some
+            // four hundred searches of 1 - 256 queries and 10 000 - 600 000 rows of three slices and more, geometric means of the gain and
+            // the extremes: pages of up to 128 rows 1.05 up to 1 (0.98 - 1.23), 0.99 from 1 to 3 (0.90 - 1.16); of 256 1.12 up to 2 (0.95 -
+            // 1.49), 1.05 up to 4 (0.93 - 1.24); instead of the sliced-query kernel 1.19 up to 2 (1.00 - 1.62), 1.04 up to 3 (1.00 - 1.16).
+            // Rows of one and two slices 0.8 - 1.04: their tiles are no chain, and twice as many cost more.
             const uint32_t R = pages_of_64 ? 64u : 32u;
             const uint64_t cut = tiles * (most_P / R);
             const int mq = std::min(scan_max_mq(own->row_bytes, own->cfg.storage, own->lds_limit), want);
-            const double per_cu = distinct / own->row_bytes / R * std::max(1.0, p.avg_per_list / std::max(mq, 1)) / own->num_cu;
-            const double up_to = p.hot_from == 0 ? 3.0 : most_P >= 256 ? 4.0 : 0.8;
+            const double per_cu = (distinct / own->row_bytes / R + 0.75 * probed) * std::max(1.0, p.avg_per_list / std::max(mq, 1)) / own->num_cu;
+            const double up_to = p.hot_from == 0 ? 3.0 : most_P >= 256 ? 4.0 : 1.0;
             if (mq >= 16 && cut <= kFewTiles && own->row_bytes >= 3 * kIterBytes &&
                 per_cu <= up_to * 0.1 * tunables().few) {
                 p.tile_rows = R;
