@@ -818,7 +818,7 @@ __device__ __forceinline__ void best_of_first(const SplitGemmArgs &a, const f32x
 // alone), and what else is done adds to that as if one after the other: with the two waves of a SIMD taking turns to read and to
 // multiply, a barrier between, and pieces in an order without bank conflicts, 234; two workgroups per CU with tiles of half the size
 // (249 of 252), three buffers (247) and operands read ahead (253) change nothing, waves of 128 x 128, one per SIMD, take 289.
-// A k-means iteration of 262 144 rows over 4096 lists 3400 -> 2920 us (a tenth of its rows have two candidates, for which
+// A k-means iteration of 262 144 rows over 4096 lists 3400 -> 2800 us (a tenth of its rows have two candidates, for which
 // the products of the whole values took 0.49 ms, pair_ties_kernel takes 0.06), with every list given twice 15.4 -> 4.5 ms.
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_first_kernel(SplitGemmArgs a)

@@ -726,7 +726,7 @@ struct SplitGemmArgs {
     const uint32_t *cmax;     // largest squared norm of the centroids (as bits)
     const uint32_t *skipped, *skipped2; // or null: with more than skip_from in it the launch does nothing
     uint32_t skip_from, skip_from2;
-    const float *left;        // [m] or null: the products of the first halfs alone, near by row_margin
+    const float *left;        // [m] or null: the products of the first halfs alone, near by first_margin
     const uint32_t *cmax_left;
     unsigned long long *next; // with left: [m] the second best (value key << 32 | column), where it is near the best (else all ones, as on
                               // entry); second[] then has a value key near the best where there are more than two such columns
