@@ -566,7 +566,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
         // list probed by more than kRrSlots queries has one tile per group of that many
         if (rs_tiles) tiles += (uint64_t)(ix->P / kRrTileRows) * pages * ((uint64_t)(nqa + kRrSlots - 1) / kRrSlots);
     }
-    if (worst) tiles += kFewTiles;
+    if (worst) tiles = std::max(tiles, std::min(kFewTiles, tiles * (most_P / (pages_of_64 ? 64u : 32u)))); // (cut smaller where there are few)
     if (tiles > 0xfffffff0ull) return PK_ERR_UNSUPPORTED;
     {
         // Sample pages per query.  The threshold is the k-th best of sp * rows sampled rows, so a list of L rows near the
