@@ -111,6 +111,10 @@ __device__ __forceinline__ uint32_t bound_of_far_parts(uint32_t least, uint32_t 
     const uint32_t mine = (min(min(s[lane], s[64u + lane]), min(s[128u + lane], s[192u + lane])) & ~255u) | lane;
     uint32_t *const parts = s + 256u + (tid & 192u); // every wave for itself
     parts[lane] = mine;
+    // the other lanes read it: the wave's store before its loads, for the compiler too (no wait of the workgroup)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     uint32_t rank = 0;
 #pragma unroll
     for (int o = 0; o < 64; o += 4) {
