@@ -268,12 +268,15 @@ struct FillRanges {
     uint32_t *p[kMost];
     size_t n[kMost];
     uint32_t v[kMost];
-    int ranges;
+    int ranges; // as many as were added; more than there is room for, and the launch refuses
     void add(void *at, uint32_t value, size_t words)
     {
-        p[ranges] = static_cast<uint32_t *>(at);
-        n[ranges] = words;
-        v[ranges++] = value;
+        if (ranges < kMost) {
+            p[ranges] = static_cast<uint32_t *>(at);
+            n[ranges] = words;
+            v[ranges] = value;
+        }
+        ++ranges;
     }
 };
 hipError_t launch_fill_ranges(const FillRanges &a, hipStream_t s);

@@ -116,3 +116,38 @@ int main()
                     "-I", os.path.join(root, "paper_2602_21477_amd", "csrc"), str(src), "-o", str(exe)], check=True,
                    capture_output=True)
     assert subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout == "0 bad, 128\n"
+
+
+def test_more_ranges_than_a_fill_has_room_for_are_refused_and_nothing_is_overwritten(lib, tmp_path):
+    """The host's list of ranges that one launch fills, compiled by itself: what lies behind it stays as it was, whatever is
+    added, and the launch refuses a list that is too long (before it asks the device for anything)."""
+    root = os.path.dirname(os.path.dirname(HEADER))
+    src = tmp_path / "ranges.hip"
+    src.write_text('''#include "pk_internal.h"
+#include <cstdio>
+#include <cstring>
+int main()
+{
+    struct {
+        pk::FillRanges a;
+        unsigned char behind[512];
+    } s;
+    std::memset(&s, 0, sizeof(s));
+    std::memset(s.behind, 0x5a, sizeof(s.behind));
+    uint32_t words[4];
+    int refused = 0, changed = 0;
+    for (int i = 0; i < pk::FillRanges::kMost + 5; ++i) {
+        s.a.add(words, 7u, 4);
+        if (i >= pk::FillRanges::kMost && pk::launch_fill_ranges(s.a, nullptr) == hipErrorInvalidValue) ++refused;
+    }
+    for (unsigned char c : s.behind) changed += c != 0x5a;
+    for (int i = 0; i < pk::FillRanges::kMost; ++i) changed += s.a.p[i] != words || s.a.n[i] != 4 || s.a.v[i] != 7u;
+    printf("%d refused, %d changed\\n", refused, changed);
+}
+''')
+    exe = tmp_path / "ranges"
+    where = os.path.dirname(B.LIB_PATH)
+    subprocess.run(["hipcc", "-O1", "-std=c++17", "--offload-arch=gfx950", "-I", os.path.join(root, "include"),
+                    "-I", os.path.join(root, "paper_2602_21477_amd", "csrc"), str(src), "-o", str(exe), "-L", where, "-lpancake",
+                    f"-Wl,-rpath,{where}"], check=True, capture_output=True)
+    assert subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout == "5 refused, 0 changed\n"
