@@ -416,9 +416,6 @@ constexpr int64_t kRoomyBatch = 128;
 // largest emission region whose overflow is provided for (see make_plan)
 constexpr uint32_t kRescueFrom = 8192;
 
-// Rows of d floats that can be read in 16-byte pieces.
-bool whole_pieces(const float *rows, int d) { return (d & 3) == 0 && (reinterpret_cast<uintptr_t>(rows) & 15) == 0; }
-
 // Most products of a coarse step whose kernel reads queries of any width and alignment as they are, float by float, for every
 // block of centroids again; a preparation launch is 5 us.  Coarse steps with the launch and without, us: 1030 wide, 333 lists, 64
 // queries (22 M) 20.8 and 18.9, 512 (176 M) 31.2 and 37; 832 lists, 2048 queries (1755 M) 102 and 175; 767 wide, 333 lists, 200
@@ -698,7 +695,7 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
     // side, unless the GEMM wants them first or the chunked selection, which adds no norm.  A whole search of 1 query with the
     // preparation as launches of its own and without: 100 000 x 130 fp16 L2 33.2 and 29.4 us, 100 000 x 100 fp32 33.7 and 30.6;
     // of 1024 queries 75.6 and 75.1, 81.6 and 80.2.  (Rows of odd widths: kFoldAny.)
-    p.fold = need_coarse && !worst && !p.raw_queries && own->cfg.d >= 4 && nlist_hi <= kDenseSelectMax && tunables().densesel;
+    p.fold = need_coarse && !worst && !p.raw_queries && nlist_hi <= kDenseSelectMax && tunables().densesel;
     for (int a = 0; a < nh && p.fold; ++a)
         if (coarse_by_gemm(qlo[a + 1] - qlo[a], hs[a])) p.fold = false;
     for (int a = 0; a < nh; ++a) p.coarse_products += (double)(qlo[a + 1] - qlo[a]) * hs[a]->cfg.nlist * own->cfg.d;
@@ -860,7 +857,7 @@ int run_coarse(const Plan &p, const MultiArgs &m, pk_index *const *hs, const flo
         const bool l2 = own->cfg.metric == PK_METRIC_L2;
         ca.qs = reinterpret_cast<const char *>(q);
         ca.d = own->cfg.d;
-        ca.raw = whole_pieces(q, ca.d) ? kRawVec : kRawAny;
+        ca.raw = raw_kind(q, ca.d);
         ca.meta = qm;
         if (l2) ca.norm = p.qn32;
         if (p.need_fine && !p.f16) ca.rows = p.qs32;
@@ -1204,7 +1201,7 @@ int search_impl(pk_index *const *hs, int nh, const int64_t *q_offsets, const flo
         Plan p;
         auto plan = [&](bool lean, bool dense_ok) -> int {
             PK_TRY(make_plan(p, hs, nh, qlo.data(), nq, k, nprobe, mode != kForced, mode != kCoarseOnly, 0, false, lean, dense_ok));
-            if (!whole_pieces(queries, d) && p.coarse_products > kFoldAny) p.fold = false;
+            if (raw_kind(queries, d) != kRawVec && p.coarse_products > kFoldAny) p.fold = false;
             return PK_OK;
         };
         // (under capture the lists may have grown when the graph runs: by more than the host knows of)
@@ -1585,11 +1582,6 @@ struct InsertScratch {
 int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const AssignScratch &as, int64_t chunk,
                 unsigned long long *best, hipStream_t s)
 {
-    if (t.d < 4) { // (the kernels that read rows as they are read four floats at a time)
-        for (int64_t i0 = 0; i0 < n; i0 += kFillChunk)
-            PK_TRY(assign_few(x + (size_t)i0 * t.d, std::min<int64_t>(kFillChunk, n - i0), t, num_cu, as.xh, as.norm + i0, best + i0, true, s));
-        return PK_OK;
-    }
     const int64_t tail = n % kFillChunk;
     const int64_t by_gemm = tail > 0 && !coarse_tiles((uint32_t)tail, t.nlist_pad) ? n - tail : n;
     MultiArgs mm;

@@ -15,6 +15,7 @@
 // index is permuted identically on both operands so that a lane's four consecutive floats
 // (one ds_read_b128) feed four MFMAs.
 #include <algorithm>
+#include <type_traits>
 
 #include "pk_internal.h"
 
@@ -35,25 +36,29 @@ __device__ __forceinline__ uint32_t listed_tiles(uint32_t rows, int n_pad)
     return (rows + kListRows - 1) / kListRows * ((uint32_t)(n_pad + kListCols - 1) / kListCols);
 }
 
-// Four floats of a dense row of d from column `col` on: the load, and zeros past the row's end.  VEC: rows of whole 16-byte
-// pieces (d a multiple of 4, the rows aligned); else of four floats at least.  The load is unconditional, past the end from the row's last floats, as the
-// compiler waits for a load under a condition before it issues the next; the zeros are put in when the floats are used,
-// as putting them in waits for the load.
-template <bool VEC>
+// Four floats of a dense row of d from column `col` on: the load, and zeros past the row's end, which are put in when the floats
+// are used, as putting them in waits for the load (see raw_load).
+template <int RAW>
 __device__ __forceinline__ f32x4 dense_load(const float *row, int col, int d)
 {
-    if constexpr (VEC) return *reinterpret_cast<const f32x4 *>(row + (col < d ? col : d - 4));
-    else return __builtin_bit_cast(f32x4, any_load(reinterpret_cast<const uint32_t *>(row), col, d));
+    return __builtin_bit_cast(f32x4, raw_load<RAW>(reinterpret_cast<const uint32_t *>(row), col, d));
 }
-template <bool VEC>
+template <int RAW>
 __device__ __forceinline__ f32x4 dense_zeros(f32x4 v, int col, int d)
 {
-    if constexpr (!VEC) return __builtin_bit_cast(f32x4, any_zeros(__builtin_bit_cast(u32x4, v), col, d));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = col + j < d ? v[j] : 0.f;
-    return v;
+    return __builtin_bit_cast(f32x4, raw_zeros<RAW>(__builtin_bit_cast(u32x4, v), col, d));
 }
-static bool whole_pieces(const float *rows, int d) { return (d & 3) == 0 && (reinterpret_cast<uintptr_t>(rows) & 15) == 0; }
+
+// f with the kind as a constant
+template <typename F>
+static auto for_raw(int kind, const F &f)
+{
+    switch (kind) {
+    case kRawVec: return f(std::integral_constant<int, kRawVec>{});
+    case kRawAny: return f(std::integral_constant<int, kRawAny>{});
+    default: return f(std::integral_constant<int, kRawShort>{});
+    }
+}
 
 // A wave's scores of listed rows into their best (value key, column): blocks of 32 columns x 32 rows, lane l holds, of row
 // m0 + l % 32 of each block, columns n0 + (l / 32) * 4 + 8 * (r / 4) + r % 4.  One atomic per row: one per value, behind a
@@ -109,7 +114,7 @@ __device__ __forceinline__ void best_of_listed(const GemmArgs &a, const f32x16 (
 // keeps its best (value key, column) by atomicMin instead of its scores; the grid walks the tiles there are.  For lists
 // that fill tiles (see gemm_listed_kernel): 262 144 listed rows x 4096 x 768
 // in 18.0 ms = 92 TFLOP/s, where the kernel for few of them took 82.
-template <bool LISTED, bool VEC = true>
+template <bool LISTED, int RAW = kRawVec>
 __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
 {
     const int rows = LISTED ? (int)*a.nlisted : a.m;
@@ -153,13 +158,13 @@ __global__ __launch_bounds__(256) void gemm_scores_kernel(GemmArgs a)
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                        \
     {                                                                                    \
         rb4[i] = *reinterpret_cast<const f32x4 *>(gb[i] + (size_t)(ks) * kGemmBK);       \
-        if constexpr (LISTED) ra4[i] = dense_load<VEC>(ga[i], (ks) * kGemmBK + scol, a.d); \
+        if constexpr (LISTED) ra4[i] = dense_load<RAW>(ga[i], (ks) * kGemmBK + scol, a.d); \
         else ra4[i] = *reinterpret_cast<const f32x4 *>(ga[i] + (size_t)(ks) * kGemmBK);  \
     }
 #define PK_LSTORE(buf, ks)                                                                               \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                        \
     {                                                                                                    \
-        if constexpr (LISTED) ra4[i] = dense_zeros<VEC>(ra4[i], (ks) * kGemmBK + scol, a.d);                  \
+        if constexpr (LISTED) ra4[i] = dense_zeros<RAW>(ra4[i], (ks) * kGemmBK + scol, a.d);                  \
         *reinterpret_cast<f32x4 *>(&sA[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = ra4[i];          \
         *reinterpret_cast<f32x4 *>(&sB[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = rb4[i];          \
     }
@@ -285,14 +290,14 @@ __device__ __forceinline__ void split_row(const SplitRowsArgs &a, const MultiArg
     float big = 0.f, sq[NP][4] = {}, sq16[NP][4] = {}, off[NP][4] = {};
     if (vec) { // (all of a row's loads in flight at once: none of them under a condition)
 #pragma unroll
-        for (int t = 0; t < T; ++t) v[t] = dense_load<true>(src, lane * 4 + 4 * SUB * t, d);
+        for (int t = 0; t < T; ++t) v[t] = dense_load<kRawVec>(src, lane * 4 + 4 * SUB * t, d);
 #pragma unroll
-        for (int t = 0; t < T; ++t) v[t] = dense_zeros<true>(v[t], lane * 4 + 4 * SUB * t, d);
+        for (int t = 0; t < T; ++t) v[t] = dense_zeros<kRawVec>(v[t], lane * 4 + 4 * SUB * t, d);
     } else if (d >= 4) {
 #pragma unroll
-        for (int t = 0; t < T; ++t) v[t] = dense_load<false>(src, lane * 4 + 4 * SUB * t, d);
+        for (int t = 0; t < T; ++t) v[t] = dense_load<kRawAny>(src, lane * 4 + 4 * SUB * t, d);
 #pragma unroll
-        for (int t = 0; t < T; ++t) v[t] = dense_zeros<false>(v[t], lane * 4 + 4 * SUB * t, d);
+        for (int t = 0; t < T; ++t) v[t] = dense_zeros<kRawAny>(v[t], lane * 4 + 4 * SUB * t, d);
     } else {
 #pragma unroll
         for (int t = 0; t < T; ++t)
@@ -550,7 +555,7 @@ __device__ __forceinline__ void best_of_split(const SplitGemmArgs &a, const f32x
 // then depend on which kernel its call takes.)  By its own values alone,
 // 28 rows came out on the wrong side of a near tie, against 64 bits, over seven sets of 0.5 - 1 M rows
 // (64 <= d <= 1536), and 46 by the fp32 kernel's.
-template <int BM, int BN, int WM, int WN, bool LISTED, bool VEC>
+template <int BM, int BN, int WM, int WN, bool LISTED, int RAW>
 __device__ __forceinline__ void split_tiles(const SplitGemmArgs &a, char *smem, int rows)
 {
     constexpr int TH = WM * WN * 64;
@@ -611,7 +616,7 @@ __device__ __forceinline__ void split_tiles(const SplitGemmArgs &a, char *smem, 
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
             if (LISTED && i < ALOADS)
-                st[i] = __builtin_bit_cast(u32x4, dense_load<VEC>(reinterpret_cast<const float *>(src[i]), ks * 32 + (tid & 7) * 4, a.d));
+                st[i] = __builtin_bit_cast(u32x4, dense_load<RAW>(reinterpret_cast<const float *>(src[i]), ks * 32 + (tid & 7) * 4, a.d));
             else
                 st[i] = *reinterpret_cast<gvec4>(in_global(src[i]) + at);
         }
@@ -621,7 +626,7 @@ __device__ __forceinline__ void split_tiles(const SplitGemmArgs &a, char *smem, 
 #pragma unroll
         for (int i = 0; i < LOADS; ++i) {
             if (LISTED && i < ALOADS) { // 4 floats: their first halfs into the row's first 64 bytes, the rest behind
-                const f32x4 v = dense_zeros<VEC>(__builtin_bit_cast(f32x4, st[i]), ks * 32 + (tid & 7) * 4, a.d);
+                const f32x4 v = dense_zeros<RAW>(__builtin_bit_cast(f32x4, st[i]), ks * 32 + (tid & 7) * 4, a.d);
                 half4 hi, lo;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) { // (the same values as split_rows_kernel's)
@@ -694,7 +699,7 @@ __device__ __forceinline__ void split_tiles(const SplitGemmArgs &a, char *smem, 
     }
 }
 
-template <int BM, int BN, int WM, int WN, bool LISTED, bool VEC = true>
+template <int BM, int BN, int WM, int WN, bool LISTED, int RAW = kRawVec>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_split_kernel(SplitGemmArgs a)
 {
     extern __shared__ __align__(16) char smem[]; // [2][BM + BN][144], then [2][BN] floats
@@ -706,11 +711,11 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
         // 29 -> 17; two rounds of them take as long as one of the others.
         const uint32_t quarters = (uint32_t)((a.n_pad + 63) / 64) * (uint32_t)((rows + 63) / 64);
         if (quarters <= gridDim.x) {
-            split_tiles<64, 64, 2, 2, true, VEC>(a, smem, rows);
+            split_tiles<64, 64, 2, 2, true, RAW>(a, smem, rows);
             return;
         }
     }
-    split_tiles<BM, BN, WM, WN, LISTED, VEC>(a, smem, rows);
+    split_tiles<BM, BN, WM, WN, LISTED, RAW>(a, smem, rows);
 }
 
 // A wave's products of first halfs into the rows' best, second best and third: as best_of_split, but a value carries its
@@ -1001,11 +1006,12 @@ hipError_t launch_gemm_split(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 
 hipError_t launch_gemm_split_listed(const SplitGemmArgs &a, int num_cu, hipStream_t s)
 {
-    if (!split_gemm_valid(a) || a.left || !a.list || !a.nlisted || !a.x || a.d > a.ld || a.d < 4) return hipErrorInvalidValue;
-    static LdsCleared cleared, cleared_any;
+    if (!split_gemm_valid(a) || a.left || !a.list || !a.nlisted || !a.x || a.d > a.ld || a.d < 1) return hipErrorInvalidValue;
     constexpr int lds = 2 * 256 * 144 + 2 * 128 * 4;
-    if (whole_pieces(a.x, a.d)) return launch_with_lds(&gemm_split_kernel<128, 128, 2, 2, true, true>, cleared, lds, a, 2 * num_cu, 256, s);
-    return launch_with_lds(&gemm_split_kernel<128, 128, 2, 2, true, false>, cleared_any, lds, a, 2 * num_cu, 256, s);
+    return for_raw(raw_kind(a.x, a.d), [&](auto raw) {
+        static LdsCleared cleared;
+        return launch_with_lds(&gemm_split_kernel<128, 128, 2, 2, true, raw()>, cleared, lds, a, 2 * num_cu, 256, s);
+    });
 }
 
 // The fp32 products of a few listed rows (a.list, *a.nlisted of them: dense rows of a.d floats) with every column, in
@@ -1016,7 +1022,7 @@ hipError_t launch_gemm_split_listed(const SplitGemmArgs &a, int num_cu, hipStrea
 // 768 against 4096 columns (140 with zeros put in as the rows were loaded, which waited for each load, and an atomic per value).  Lists of more than a.many tiles (two
 // rounds of the grid, then longer than one round of 128 x 128 tiles) are gemm_scores_kernel<true>'s, and one of the two
 // launches ends at once.
-template <bool VEC>
+template <int RAW>
 __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
 {
     __shared__ __align__(16) float sA[2][kListRows * kGemmLdsStride];
@@ -1046,10 +1052,10 @@ __global__ __launch_bounds__(256) void gemm_listed_kernel(GemmArgs a)
             const int at = (ks < ksteps ? ks : ksteps - 1) * kGemmBK; // (past the last step the last one again)
 #pragma unroll
             for (int i = 0; i < 4; ++i) rb[i] = *reinterpret_cast<const f32x4 *>(gb[i] + at);
-            ra = dense_load<VEC>(ga, at + scol, a.d); // the caller's rows: no padding, any alignment
+            ra = dense_load<RAW>(ga, at + scol, a.d); // the caller's rows: no padding, any alignment
         };
         auto put = [&](const f32x4 &ra, const f32x4 (&rb)[4], int buf, int ks) {
-            *reinterpret_cast<f32x4 *>(&sA[buf][srow * kGemmLdsStride + scol]) = dense_zeros<VEC>(ra, ks * kGemmBK + scol, a.d);
+            *reinterpret_cast<f32x4 *>(&sA[buf][srow * kGemmLdsStride + scol]) = dense_zeros<RAW>(ra, ks * kGemmBK + scol, a.d);
 #pragma unroll
             for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4 *>(&sB[buf][(srow + 32 * i) * kGemmLdsStride + scol]) = rb[i];
         };
@@ -1140,7 +1146,7 @@ __global__ __launch_bounds__(256) void near_ties_kernel(NearTiesArgs a)
 // the whole values (a.list), as do all rows where the first halfs were left out.
 // Bound by latency: a pair is 3 rows of 4 ld bytes out of the caches.  229 376 rows x 768 with some 24 000 pairs 45 us; with a
 // wave per pair 77 us instead of 24 where rows are short (200 000 x 128, a third of them pairs).
-template <bool VEC>
+template <int RAW>
 __global__ __launch_bounds__(256) void pair_ties_kernel(NearTiesArgs a)
 {
     __shared__ uint32_t s_row[256], s_redo[256], s_wave[8], s_at, s_redos;
@@ -1191,7 +1197,7 @@ __global__ __launch_bounds__(256) void pair_ties_kernel(NearTiesArgs a)
 #pragma unroll 4
             for (int i = (int)sub * 4; i < a.ld; i += 64) {
                 const f32x4 w1 = *reinterpret_cast<const f32x4 *>(y1 + i), w2 = *reinterpret_cast<const f32x4 *>(y2 + i);
-                const f32x4 v = dense_zeros<VEC>(dense_load<VEC>(x, i, a.d), i, a.d);
+                const f32x4 v = dense_zeros<RAW>(dense_load<RAW>(x, i, a.d), i, a.d);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     s1 = fmaf(v[j], w1[j], s1);
@@ -1235,9 +1241,9 @@ __global__ __launch_bounds__(256) void pair_ties_kernel(NearTiesArgs a)
 hipError_t launch_pair_ties(const NearTiesArgs &a, int num_cu, hipStream_t s)
 {
     if (a.last <= a.first) return hipSuccess;
-    if (a.ld % 64 != 0 || a.d > a.ld || a.d < 4 || a.among || !a.next || !a.left || !a.cmax_left || !a.x || !a.cent || !a.redo || !a.nredo) return hipErrorInvalidValue;
+    if (a.ld % 64 != 0 || a.d > a.ld || a.d < 1 || a.among || !a.next || !a.left || !a.cmax_left || !a.x || !a.cent || !a.redo || !a.nredo) return hipErrorInvalidValue;
     const dim3 grid(std::min((a.last - a.first + 255u) / 256u, 8u * (uint32_t)num_cu));
-    hipLaunchKernelGGL(whole_pieces(a.x, a.d) ? pair_ties_kernel<true> : pair_ties_kernel<false>, grid, dim3(256), 0, s, a);
+    for_raw(raw_kind(a.x, a.d), [&](auto raw) { hipLaunchKernelGGL(pair_ties_kernel<raw()>, grid, dim3(256), 0, s, a); });
     return hipGetLastError();
 }
 
@@ -1251,11 +1257,12 @@ hipError_t launch_near_ties(const NearTiesArgs &a, int num_cu, hipStream_t s)
 
 hipError_t launch_gemm_listed(GemmArgs a, int num_cu, hipStream_t s)
 {
-    if (a.ld % 64 != 0 || a.d > a.ld || a.d < 4 || !a.best || !a.list || !a.nlisted) return hipErrorInvalidValue;
+    if (a.ld % 64 != 0 || a.d > a.ld || a.d < 1 || !a.best || !a.list || !a.nlisted) return hipErrorInvalidValue;
     a.many = 6u * (uint32_t)num_cu;
-    const bool vec = whole_pieces(a.q, a.d);
-    hipLaunchKernelGGL(vec ? gemm_listed_kernel<true> : gemm_listed_kernel<false>, dim3(3 * num_cu), dim3(256), 0, s, a);
-    hipLaunchKernelGGL((vec ? gemm_scores_kernel<true, true> : gemm_scores_kernel<true, false>), dim3(2 * num_cu), dim3(256), 0, s, a);
+    for_raw(raw_kind(a.q, a.d), [&](auto raw) {
+        hipLaunchKernelGGL(gemm_listed_kernel<raw()>, dim3(3 * num_cu), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((gemm_scores_kernel<true, raw()>), dim3(2 * num_cu), dim3(256), 0, s, a);
+    });
     return hipGetLastError();
 }
 

@@ -153,6 +153,14 @@ __device__ __forceinline__ void line_to_operands(u32x4 &a, u32x4 &b)
     }
 }
 
+// How a kernel reads rows of d floats of the caller's: not at all (padded copies), in aligned 16-byte pieces (kRawVec: d a
+// multiple of 4), in 16-byte pieces that begin anywhere (any_load), or, where a row has less than one of these, float by float.
+enum { kRawNot, kRawVec, kRawAny, kRawShort };
+inline int raw_kind(const float *rows, int d)
+{
+    return d < 4 ? kRawShort : (d & 3) == 0 && (reinterpret_cast<uintptr_t>(rows) & 15) == 0 ? kRawVec : kRawAny;
+}
+
 // Four floats of a dense row of d (four at least) from column `col` on, of a row that begins anywhere: the load, unconditional, from the
 // row's last four floats where fewer are left, and what the columns hold, zeros past the row's end.  In two parts, as
 // arranging them waits for the load.  (A load of 16 bytes wants no more than the alignment of its elements.)
@@ -172,6 +180,31 @@ __device__ __forceinline__ u32x4 any_zeros(u32x4 v, int col, int d)
 #pragma unroll
         for (int s = 0; s + j < 4; ++s) r[j] = (s == 0 ? past <= 0 : past == s) ? v[j + s] : r[j];
     return r;
+}
+
+// The same in each of the three forms.  The loads are unconditional (past the row's end from its last floats): the compiler waits
+// for a load under a condition before it issues the next.  (Nor is the form asked for while reading: a condition that is the same for all
+// lanes splits the loads as well.)
+template <int RAW>
+__device__ __forceinline__ u32x4 raw_load(const uint32_t *row, int col, int d)
+{
+    static_assert(RAW == kRawVec || RAW == kRawAny || RAW == kRawShort, "");
+    if constexpr (RAW == kRawVec) return *reinterpret_cast<const u32x4 *>(row + (col < d ? col : d - 4));
+    else if constexpr (RAW == kRawAny) return any_load(row, col, d);
+    else {
+        u32x4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = row[col + j < d ? col + j : d - 1];
+        return v;
+    }
+}
+template <int RAW>
+__device__ __forceinline__ u32x4 raw_zeros(u32x4 v, int col, int d)
+{
+    if constexpr (RAW == kRawAny) return any_zeros(v, col, d);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = col + j < d ? v[j] : 0u;
+    return v;
 }
 
 // 16 bytes of a query row (A) against 16 bytes of a stored row (B), fp32 accumulation: one
@@ -504,14 +537,13 @@ struct CentroidArgs {
     QueryMeta meta;
     unsigned long long *best;
     //   raw (with meta): qs are the caller's dense rows of d floats; under L2 the scores are written without the query's own
-    //   norm (kRawVec: rows of whole 16-byte pieces);
+    //   norm;
     //   rows, norm: the fp32 rows, zero padded to row_bytes, and their squared norms are written too; halves, half_norm: the
     //   same of the rows rounded to half precision, padded to half_bytes (each of them, or null).
     int raw, d, half_bytes;
     char *rows, *halves;
     float *norm, *half_norm;
 };
-enum { kRawNot, kRawVec, kRawAny };
 hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hipStream_t s);
 // Of the rows (of one handle) whose best two values are near, as the split GEMM left them, the best by the centroid kernel.
 // (Arguments of their own: the other launches' would be a line longer, 0.3 us of a search of one query.)

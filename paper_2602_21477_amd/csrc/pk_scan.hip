@@ -956,24 +956,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 
 // ------------------------------------------------------------------ centroid scoring, small batches
 
-// Four floats of a dense row of d (four at least) from column `col` on (kRawVec: d a multiple of 4, rows aligned): the load,
-// unconditional and past the row's end from its last floats, and the zeros behind the end, which wait for the load and go in when it is used.
-template <int RAW>
-__device__ __forceinline__ u32x4 raw_load(const char *row, int col, int d)
-{
-    const uint32_t *const x = reinterpret_cast<const uint32_t *>(row);
-    if constexpr (RAW == kRawVec) return *reinterpret_cast<const u32x4 *>(x + (col < d ? col : d - 4));
-    else return any_load(x, col, d);
-}
-template <int RAW>
-__device__ __forceinline__ u32x4 raw_zeros(u32x4 v, int col, int d)
-{
-    if constexpr (RAW == kRawAny) return any_zeros(v, col, d);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = col + j < d ? v[j] : 0u;
-    return v;
-}
-
 // The copies of one query that the fine step reads and their norms, by one wave: what prep_row (pk_worklist.hip) makes, in the
 // same order of summation.
 __device__ __forceinline__ void copy_query(const CentroidArgs &a, uint32_t q, int lane)
@@ -1087,7 +1069,7 @@ __device__ __forceinline__ void centroid_body(const CentroidArgs &a, const Multi
         _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                         \
         {                                                                                         \
             if constexpr (RAW != kRawNot) {                                                       \
-                if (mt == 0 || mt < mt_used) qbuf[mt][s4] = raw_load<RAW>(qp[mt], (it) * 64 + s4 * 16 + lg * 4, a.d); \
+                if (mt == 0 || mt < mt_used) qbuf[mt][s4] = raw_load<RAW>(reinterpret_cast<const uint32_t *>(qp[mt]), (it) * 64 + s4 * 16 + lg * 4, a.d); \
             } else {                                                                              \
                 qbuf[mt][s4] = u32x4{0u, 0u, 0u, 0u};                                             \
                 if ((mt == 0 || mt < mt_used) && qp[mt])                                          \
@@ -1224,11 +1206,12 @@ hipError_t launch_centroid_scores(const CentroidArgs &a, const MultiArgs &m, hip
 {
     if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0) return hipErrorInvalidValue;
     if (a.blk[m.n] == 0) return hipSuccess;
-    if (a.raw != kRawNot && (a.best || !a.meta.cand_off || a.d < 4 || a.d * 4 > a.row_bytes)) return hipErrorInvalidValue;
+    if (a.raw != kRawNot && (a.best || !a.meta.cand_off || a.d < 1 || a.d * 4 > a.row_bytes)) return hipErrorInvalidValue;
     switch (a.raw) {
     case kRawNot: return launch_centroid_raw<kRawNot>(a, m, s);
     case kRawVec: return launch_centroid_raw<kRawVec>(a, m, s);
     case kRawAny: return launch_centroid_raw<kRawAny>(a, m, s);
+    case kRawShort: return launch_centroid_raw<kRawShort>(a, m, s);
     default: return hipErrorInvalidValue;
     }
 }

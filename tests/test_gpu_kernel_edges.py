@@ -1,6 +1,7 @@
 """Edges of single kernels and of the rules that choose between them: tile remainders, the smallest and
 largest sizes of a path, and the sizes on both sides of a dispatch."""
 import math
+import time
 
 import numpy as np
 import pytest
@@ -961,3 +962,42 @@ def test_extents_of_built_lists_are_laid_one_behind_the_other(gpu_device, nlist)
         B.Index(cent.cuda(), cent[lists].cuda(), metric=L2, page_vecs=page, max_delta_pages=1,
                 arena_bytes=room + (pages + 1) * one - (spare + 1) * one)
     assert e.value.status == B.PK_ERR_NOMEM
+
+
+@pytest.mark.parametrize("d", [1, 2, 3])
+def test_narrowest_rows_take_the_tiled_products_too(gpu_device, d):
+    """Rows of less than 16 bytes: a build that begins with the products of first halfs, in whole chunks and a rest, finds the lists
+    of the fp32 coarse step, up to the rounding of its sums; and a k-means iteration takes about as long as one of rows of 16 bytes
+    (262 144 rows, 4096 lists: 1.2 to 2.4 times as long; by the small inserts' kernel, row group after row group, 17 times as long)."""
+    n, nlist = 5 * 32768 + 5, 1536
+    assert by_first_halves(n, 64, nlist)
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x, cent = torch.randn((n, d), device="cuda", generator=g), torch.randn((nlist, d), device="cuda", generator=g)
+    for metric in (IP, L2):
+        ix = B.Index(cent, x, metric=metric)
+        try:
+            lists = torch.from_numpy(lists_of(ix, n)).cuda()
+        finally:
+            ix.close()
+        for a in range(0, n, 32768):
+            rows = x[a:a + 32768].double()
+            s = rows @ cent.double().T
+            size = rows.norm(dim=1) * cent.double().norm(dim=1).max()
+            if metric == L2:
+                s = 2 * s - cent.double().square().sum(1)
+                size = (rows.norm(dim=1) + cent.double().norm(dim=1).max()) ** 2
+            # both values of a pair, each 4 sqrt(d) roundings of its terms off
+            assert (s.max(1).values - s.gather(1, lists[a:a + 32768, None])[:, 0] <= 16 * math.sqrt(d) * 2.0 ** -24 * size).all()
+
+    def seconds(width):
+        rows = torch.randn((262144, width), device="cuda", generator=g)
+        taken = []
+        for _ in range(4):
+            c = rows[:4096].clone()
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            B.pk_kmeans(rows, c, 1, None)
+            taken.append(time.perf_counter() - t)
+        return min(taken)
+
+    assert seconds(d) < 4 * seconds(4)
