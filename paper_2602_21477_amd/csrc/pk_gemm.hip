@@ -442,14 +442,22 @@ hipError_t launch_split_rows(const SplitRowsArgs &a, const MultiArgs &mm, hipStr
 }
 
 // What the value of a column that is no list begins with in the search for the best: larger than every list's (whose margins
-// are infinite where it would not be), and finite with a column in its last bits.
+// are infinite where it would not be).
 constexpr float kNoList = 3.0e38f;
-// the smaller of two numbers (fminf would first quiet what might be a signalling NaN: one more instruction per value)
-__device__ __forceinline__ float least(float x, float y)
+
+// One more value for the three smallest (low <= next <= third), and the place of the smallest.  As one statement, since the
+// compiler would put the places off and keep every `low` until then; the two instructions between vcc's write and its read are those that
+// the read has to wait.  (v_min_f32 because fminf would first quiet what might be a signalling NaN.)
+__device__ __forceinline__ void lowest(float t, uint32_t here, float &low, float &next, float &third, uint32_t &at)
 {
-    float r;
-    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
-    return r;
+    asm("v_cmp_nlt_f32 vcc, %4, %0\n\t"
+        "v_med3_f32 %2, %1, %2, %4\n\t"
+        "v_med3_f32 %1, %0, %1, %4\n\t"
+        "v_cndmask_b32 %3, %5, %3, vcc\n\t"
+        "v_min_f32 %0, %0, %4"
+        : "+&v"(low), "+&v"(next), "+&v"(third), "+&v"(at)
+        : "v"(t), "i"(here)
+        : "vcc");
 }
 
 // A wave's products (blocks of 32 columns x 32 rows: lane l holds, of row m0 + l % 32 of each block, columns
@@ -718,23 +726,24 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2)
     split_tiles<BM, BN, WM, WN, LISTED, RAW>(a, smem, rows);
 }
 
-// A wave's products of first halfs into the rows' best, second best and third: as best_of_split, but a value carries its
-// column in its last five bits (the lane's 32 columns; what that moves it by is part of the margin), so that the
-// three smallest and the columns of two cost six instructions a value.  s_col, s_row: of the wave's columns and rows.
+// A wave's products of first halfs into the rows' best, second best and third: as best_of_split, but the three smallest values and
+// the column of the smallest cost seven instructions a value.  The second's column is looked for, by its value, only where the second
+// is near the row's best so far.  (Six with the column in the value's last five bits, which is then no longer the 32-bit sum that
+// it was: gemm_first_kernel 244 us instead of 250.)  s_col, s_row: of the wave's columns and rows.
 template <int BM, int BN, int MI, int NI>
-__device__ __forceinline__ void best_of_first(const SplitGemmArgs &a, const f32x16 (&acc)[MI][NI], const float *s_col, const float *s_row, int m0,
+__device__ __forceinline__ void best_of_first(const SplitGemmArgs &a, f32x16 (&acc)[MI][NI], const float *s_col, const float *s_row, int m0,
                                               int n0, int lane)
 {
-    static_assert(NI <= 2, "five bits of column");
     const int l32 = lane & 31, kg = lane >> 5;
     if (n0 >= a.n) return; // no column of the wave's part is a list
     // t: smaller is nearer (inner product: -dot in the row's scale; L2: |c|^2 - 2 dot, the row's own norm left out)
-    float back[MI], factor[MI], low[MI], next[MI], third[MI];
+    float factor[MI], low[MI], next[MI], third[MI];
+    uint32_t at[MI]; // the smallest one's place among the lane's columns
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        back[i] = s_row[i * 32 + l32];
-        factor[i] = a.metric == PK_METRIC_L2 ? -2.f * back[i] : -1.f;
+        factor[i] = a.metric == PK_METRIC_L2 ? -2.f * s_row[i * 32 + l32] : -1.f;
         low[i] = next[i] = third[i] = kNoList;
+        at[i] = 0;
     }
     const float *const pc = s_col + kg * 4;
 #pragma unroll
@@ -744,39 +753,33 @@ __device__ __forceinline__ void best_of_first(const SplitGemmArgs &a, const f32x
             const f32x4 cb = *reinterpret_cast<const f32x4 *>(pc + j * 32 + g * 8);
             const f32x4 cn = *reinterpret_cast<const f32x4 *>(pc + BN + j * 32 + g * 8);
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float v = fmaf(acc[i][j][g * 4 + e] * cb[e], factor[i], cn[e]);
-                    const float t = __uint_as_float((__float_as_uint(v) & ~31u) | (uint32_t)(j * 16 + g * 4 + e));
-                    third[i] = __builtin_amdgcn_fmed3f(next[i], third[i], t); // (low <= next <= third)
-                    next[i] = __builtin_amdgcn_fmed3f(low[i], next[i], t);
-                    low[i] = least(low[i], t);
+                for (int i = 0; i < MI; ++i) {
+                    const float t = fmaf(acc[i][j][g * 4 + e] * cb[e], factor[i], cn[e]);
+                    lowest(t, j * 16 + g * 4 + e, low[i], next[i], third[i], at[i]);
+                    acc[i][j][g * 4 + e] = t;
                 }
         }
-    auto column = [&](float t, int half) { // of the tile
-        const uint32_t at = __float_as_uint(t) & 31u;
-        return (uint32_t)n0 + (at >> 4) * 32u + ((at >> 2) & 3u) * 8u + (at & 3u) + (uint32_t)half * 4u;
+    auto column = [&](uint32_t place, int half) { // of the tile
+        return (uint32_t)n0 + (place >> 4) * 32u + ((place >> 2) & 3u) * 8u + (place & 3u) + (uint32_t)half * 4u;
     };
+    auto key_of = [&](float t, float back) { return min(order_bits(a.metric == PK_METRIC_IP ? -t * back : t, a.metric), kWorstKey); };
     // either half wave goes on with every second block: the other's columns of its rows, and the row's best so far
+    constexpr uint32_t kLater = 0xffffffffu; // col2: the second best is not the smallest of either half, and where it is not known yet
     unsigned long long mine[MI], met[MI];
-    uint32_t key2[MI], col2[MI], key3[MI];
+    float t2[MI], t3[MI];
+    uint32_t col2[MI];
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
         const float low2 = __shfl_xor(low[i], 32), next2 = __shfl_xor(next[i], 32), third2 = __shfl_xor(third[i], 32);
+        const uint32_t at2 = (uint32_t)__shfl_xor((int)at[i], 32);
         const bool first = low[i] <= low2;
-        const float t1 = first ? low[i] : low2, u = first ? low2 : low[i];
-        const uint32_t c1 = column(t1, first ? kg : kg ^ 1), cu = column(u, first ? kg ^ 1 : kg);
-        const bool own = next[i] <= next2;
-        const float w = own ? next[i] : next2;
-        const uint32_t cw = column(w, own ? kg : kg ^ 1);
-        const float t2 = u <= w ? u : w;
-        col2[i] = u <= w ? cu : cw;
-        const float t3 = fminf(fminf(third[i], third2), fminf(fmaxf(low[i], next2), fmaxf(next[i], low2)));
-        auto key = [&](float t) { return min(order_bits(a.metric == PK_METRIC_IP ? -t * back[i] : t, a.metric), kWorstKey); };
-        mine[i] = ((unsigned long long)key(t1) << 32) | c1;
-        key2[i] = key(t2);
-        key3[i] = key(t3);
+        const float t1 = first ? low[i] : low2, u = first ? low2 : low[i], w = fminf(next[i], next2);
+        t2[i] = u <= w ? u : w;
+        t3[i] = fminf(fminf(third[i], third2), fminf(fmaxf(low[i], next2), fmaxf(next[i], low2)));
+        mine[i] = ((unsigned long long)key_of(t1, s_row[i * 32 + l32]) << 32) | column(first ? at[i] : at2, first ? kg : kg ^ 1);
+        col2[i] = u <= w ? column(first ? at2 : at[i], first ? kg ^ 1 : kg) : kLater;
         met[i] = ~0ull;
         if (((i ^ kg) & 1) == 0 && m0 + i * 32 + l32 < a.m) met[i] = atomicMin(a.best + m0 + i * 32 + l32, mine[i]);
     }
@@ -786,8 +789,8 @@ __device__ __forceinline__ void best_of_first(const SplitGemmArgs &a, const f32x
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
         const int m = m0 + i * 32 + l32;
-        if (((i ^ kg) & 1) != 0 || m >= a.m) continue;
-        const float margin = s_row[BM + i * 32 + l32];
+        const bool own = ((i ^ kg) & 1) == 0 && m < a.m;
+        const float margin = s_row[BM + i * 32 + l32], back = s_row[i * 32 + l32];
         const unsigned long long lead = mine[i] < met[i] ? mine[i] : met[i], behind = mine[i] < met[i] ? met[i] : mine[i];
         const float best = value_of((uint32_t)(lead >> 32), a.metric);
         auto near = [&](uint32_t key) { return key != 0xffffffffu && !(fabsf(value_of(key, a.metric) - best) > margin); };
@@ -796,13 +799,23 @@ __device__ __forceinline__ void best_of_first(const SplitGemmArgs &a, const f32x
             const uint32_t out = (uint32_t)((old < k ? k : old) >> 32);
             if (out != 0xffffffffu) atomicMin(a.second + m, out);
         };
-        const uint32_t key1 = (uint32_t)(behind >> 32);
-        if (near(key3[i])) {
-            atomicMin(a.second + m, min(key1, key2[i]));
-            continue;
+        const uint32_t key1 = (uint32_t)(behind >> 32), key2 = key_of(t2[i], back);
+        const bool many = own && near(key_of(t3[i], back)), two = own && !many && near(key2);
+        if (__any(two && col2[i] == kLater)) {
+            // The second one's place, by its value.  It is in the half of the best, whose place is the first of those with the
+            // smallest value: of several that are as large the last is another one.
+            uint32_t place = kLater;
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) place = acc[i][j][e] == t2[i] ? (uint32_t)(j * 16 + e) : place;
+            const uint32_t place2 = (uint32_t)__shfl_xor((int)place, 32);
+            if (col2[i] == kLater) col2[i] = place != kLater ? column(place, kg) : column(place2, kg ^ 1);
         }
+        if (many) atomicMin(a.second + m, min(key1, key2));
+        if (!own || many) continue;
         if (near(key1)) enter(behind);
-        if (near(key2[i])) enter(((unsigned long long)key2[i] << 32) | col2[i]);
+        if (two) enter(((unsigned long long)key2 << 32) | col2[i]);
     }
 }
 
@@ -818,7 +831,8 @@ __device__ __forceinline__ void best_of_first(const SplitGemmArgs &a, const f32x
 // leaves the matrix cores idle.
 // Rows keep their best two columns, and whether a third is near: two candidates are settled by pair_ties_kernel, more by the
 // products of the whole values.
-// 32768 x 4096 x 768 in 235 us = 877 TFLOP/s (252 with a workgroup per tile and eight instructions a value in the search);
+// 32768 x 4096 x 768 in 235 - 252 us, by the box (some 840 TFLOP/s; a workgroup per tile and eight instructions a value in the search
+// took 252 where six, with less than the whole value, took 235);
 // a large library product of halfs runs at 1390 here.  150 us go to the matrix instructions at the clock they leave (timed
 // alone), and what else is done adds to that as if one after the other: with the two waves of a SIMD taking turns to read and to
 // multiply, a barrier between, and pieces in an order without bank conflicts, 234; two workgroups per CU with tiles of half the size

@@ -704,15 +704,12 @@ __device__ __forceinline__ float near_margin(int ld, int metric, float qn, float
 // What two values of a row may differ by and still be in the other order for the fp32 kernel, where they are sums of the first
 // halfs' products alone, <x', c'> where x = x' + x", c = c' + c": off by <x", c> + <x', c">, which is
 // |x"| |c| + |x| |c"| at most (Cauchy-Schwarz; left: |x"|, cm_left: the most |c"| is; the factor covers the rounding of the
-// lengths themselves), and have a column
-// number in their last five bits, which moves them by 2^-18.  Lengths that are no numbers, or so large that a value might not be one:
-// nothing is further apart than that.
+// lengths themselves).  Lengths that are no numbers, or so large that a value might not be one: nothing is further apart than that.
 __device__ __forceinline__ float first_margin(int ld, int metric, float qn, float cm, float left, float cm_left)
 {
     if (!(qn + cm < 1.32922800e36f)) return INFINITY; // 2^120
-    const float both = sqrtf(qn) * sqrtf(cm), off = 1.001f * (left * sqrtf(cm) + sqrtf(qn) * cm_left);
-    const float packed = 7.70e-6f * (metric == PK_METRIC_L2 ? cm + 2.f * both : both); // 1.01 * 2^-17
-    return near_margin(ld, metric, qn, cm) + packed + (metric == PK_METRIC_L2 ? 4.f : 2.f) * off; // (two products, and twice each under L2)
+    const float off = 1.001f * (left * sqrtf(cm) + sqrtf(qn) * cm_left);
+    return near_margin(ld, metric, qn, cm) + (metric == PK_METRIC_L2 ? 4.f : 2.f) * off; // (two products, and twice each under L2)
 }
 
 // Rows whose values cannot all be compared (a NaN among them: from a NaN or an infinity in the row or in a centroid, or

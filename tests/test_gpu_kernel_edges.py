@@ -1001,3 +1001,27 @@ def test_narrowest_rows_take_the_tiled_products_too(gpu_device, d):
         return min(taken)
 
     assert seconds(d) < 4 * seconds(4)
+
+
+@pytest.mark.parametrize("metric", [IP, L2])
+@pytest.mark.parametrize("apart", [1, 2, 3, 4, 5, 8, 31, 32, 36, 63, 64, 255, 256])
+def test_two_near_lists_at_any_distance_are_told_by_their_fp32_scores(gpu_device, metric, apart):
+    """Pairs of lists as far apart as `apart`: in one lane's columns, in the other half wave's, in other waves' and other tiles'; every third
+    pair the same bit for bit.  The lists are those of the fp32 coarse step, row for row (of two that are the same the lower)."""
+    n, d, nlist = 2 * 32768 + 5, 512, 512
+    assert by_first_halves(n, d, nlist)
+    g = torch.Generator(device="cuda").manual_seed(apart)
+    cent = torch.randn((nlist, d), device="cuda", generator=g)
+    first = torch.tensor([l for l in range(nlist - apart) if l // apart % 2 == 0], device="cuda")
+    other = cent[first] * (1 + torch.randint(-1, 2, (len(first), d), device="cuda", generator=g) * 2.0 ** -11)
+    other[::3] = cent[first[::3]]
+    cent[first + apart] = other
+    x = cent[first[torch.randint(len(first), (n,), device="cuda", generator=g)]] + 0.4 * torch.randn((n, d), device="cuda", generator=g)
+    ix = B.Index(cent, x, metric=metric)
+    try:
+        where = torch.from_numpy(lists_of(ix, n))
+        want = torch.cat([ix.coarse(x[i:i + 16384].contiguous(), 1)[:, 0].cpu() for i in range(0, n, 16384)])
+        assert torch.equal(where, want.long())
+        assert (where % nlist).unique().numel() > len(first)  # (either of a pair is some row's)
+    finally:
+        ix.close()
