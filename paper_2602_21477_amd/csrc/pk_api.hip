@@ -673,15 +673,17 @@ int make_plan(Plan &p, pk_index *const *hs, int nh, const uint32_t *qlo, int64_t
             p.slots = slots;
             // Few tiles: smaller ones, by the kernel that has a tile per workgroup, while these leave CUs idle.  Tiles per CU (of 64
             // rows, three quarters of one over per list, and as many per list as its queries take) up to which it is the faster one, over some
-            // four hundred searches of 1 - 256 queries and 10 000 - 600 000 rows of three slices and more, geometric means of the gain and
-            // the extremes: pages of up to 128 rows 1.05 up to 1 (0.98 - 1.23), 0.99 from 1 to 3 (0.90 - 1.16); of 256 1.12 up to 2 (0.95 -
-            // 1.49), 1.05 up to 4 (0.93 - 1.24); instead of the sliced-query kernel 1.19 up to 2 (1.00 - 1.62), 1.04 up to 3 (1.00 - 1.16).
+            // six hundred searches of 1 - 256 queries and 10 000 - 600 000 rows of three slices and more, geometric means of the gain and
+            // the extremes: pages of up to 128 rows 1.06 up to 1 (0.97 - 1.23), 0.99 from 1 to 3 (0.91 - 1.16); of 256 1.16 up to 2.25 where
+            // lists take half of one and more (0.97 - 1.49), 1.04 from there to 4 (0.88 - 1.30), and where all are shorter 1.03 up to 1
+            // (0.99 - 1.12), 1.00 from 1 to 3 (0.93 - 1.07); instead of the sliced-query kernel 1.19 up to 3 (1.00 - 1.80).
+            // (Skewed memories, whose queries meet longer lists than the mean: 1.15 up to these lines, 0.94 - 1.99.)
             // Rows of one and two slices 0.8 - 1.04: their tiles are no chain, and twice as many cost more.
             const uint32_t R = pages_of_64 ? 64u : 32u;
             const uint64_t cut = tiles * (most_P / R);
             const int mq = std::min(scan_max_mq(own->row_bytes, own->cfg.storage, own->lds_limit), want);
             const double per_cu = (distinct / own->row_bytes / R + 0.75 * probed) * std::max(1.0, p.avg_per_list / std::max(mq, 1)) / own->num_cu;
-            const double up_to = p.hot_from == 0 ? 3.0 : most_P >= 256 ? 4.0 : 1.0;
+            const double up_to = p.hot_from == 0 ? 3.0 : most_P >= 256 && lmax > 128 ? 2.25 : 1.0;
             if (mq >= 16 && cut <= kFewTiles && own->row_bytes >= 3 * kIterBytes &&
                 per_cu <= up_to * 0.1 * tunables().few) {
                 p.tile_rows = R;

@@ -1025,3 +1025,33 @@ def test_two_near_lists_at_any_distance_are_told_by_their_fp32_scores(gpu_device
         assert (where % nlist).unique().numel() > len(first)  # (either of a pair is some row's)
     finally:
         ix.close()
+
+
+@pytest.mark.parametrize("rows,per_cu,cut", [(600, 2.1, True), (600, 2.6, False), (600, 3.6, False), (86, 0.9, True), (86, 1.5, False)])
+def test_tiles_of_large_pages_are_cut_only_while_that_was_measured_to_pay(gpu_device, rows, per_cu, cut):
+    """Pages of 256 rows, lists of several pages and of a third of one, on both sides of the lines (tiles of 64 rows per CU) from which smaller
+    tiles are no gain: the number of tiles says whether they were cut, and the rows are those of the gated scan either way."""
+    d, nprobe, nq, page = 200, 10, 12, 256
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    # share of the lists that are probed: share * nlist * (rows / 64 + 0.75) = per_cu * cus
+    if rows > 128:
+        nlist = next(m for m in range(11, 4000) if (1 - (1 - nprobe / m) ** nq) * m * (rows / 64 + 0.75) >= per_cu * cus)
+    else:
+        nlist = 1000
+        nprobe = next(m for m in range(1, 999) if (1 - (1 - m / nlist) ** nq) * nlist * (rows / 64 + 0.75) >= per_cu * cus)
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    c = torch.randn((nlist, d), device="cuda", generator=g)
+    x = c.repeat(rows, 1) + 0.3 * torch.randn((nlist * rows, d), device="cuda", generator=g)
+    q = c[torch.randperm(nlist, device="cuda", generator=g)[:nq]] + 0.3 * torch.randn((nq, d), device="cuda", generator=g)
+    ix = B.Index(c, x, metric=L2, page_vecs=page)
+    try:
+        assert (ix.list_lengths() == rows).all()
+        with route(ix, True) as ran:
+            whole = ix.search(q, 10, nprobe)
+        with route(ix, False):
+            gated = ix.search(q, 10, nprobe)
+        assert torch.equal(whole[0], gated[0]) and torch.equal(whole[1], gated[1])
+        probed = len(ix.coarse(q, nprobe).unique())
+        assert ran.whole and ran.profile.tiles == probed * -(-rows // (64 if cut else page))
+    finally:
+        ix.close()
