@@ -1658,11 +1658,8 @@ int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const Ass
         nt.last = (uint32_t)(last - first);
         nt.among = close;
         nt.n_among = n_close;
-        nt.cmax_left = nullptr;
-        nt.left = nullptr;
         nt.skipped = nt.skipped2;
         nt.skip_from = skip2_from;
-        nt.skipped2 = nullptr;
         nt.list = as.listed;
         nt.nlisted = as.words;
         nt.also = start ? as.words + 2 : nullptr;

@@ -1110,7 +1110,7 @@ __global__ __launch_bounds__(256) void near_ties_kernel(NearTiesArgs a)
 {
     __shared__ uint32_t s_wave[4], s_at;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, last = a.among ? *a.n_among : a.last;
-    const bool all = (a.skipped && *a.skipped > a.skip_from) || (a.skipped2 && *a.skipped2 > a.skip_from2);
+    const bool all = a.skipped && *a.skipped > a.skip_from;
     for (uint32_t i0 = a.first + blockIdx.x * kNearRows; i0 < last; i0 += gridDim.x * kNearRows) {
         constexpr uint32_t kEach = kNearRows / 256u;
         uint32_t row[kEach], count = 0;

@@ -672,14 +672,18 @@ struct NearTiesArgs {
     const uint32_t *among, *n_among; // or (among not null) the *n_among rows in it, at most last of them; first is 0 then
     unsigned long long *best;    // of the listed rows: back to ~0,
     uint32_t *second;            //   and to all ones
-    const uint32_t *cmax, *cmax_left;
-    const float *qnorm, *left;   // (left: null for values of all three products)
-    const uint32_t *skipped, *skipped2; // or null: more than skip_from in it and the rows are listed all, whatever best and second hold
-    uint32_t skip_from, skip_from2;
+    const uint32_t *cmax;
+    const float *qnorm;
+    const uint32_t *skipped;     // or null: more than skip_from in it and the rows are listed all, whatever best and second hold
+    uint32_t skip_from;
     uint32_t *list, *nlisted, *also; // also (or null): raised as nlisted is
     int ld, metric;
-    // launch_pair_ties (rows [first, last), left and cmax_left given): best, next and second as the products of first halfs
-    // left them; rows of more than two candidates into list, pairs that fp32 sums do not settle into redo (also: raised as nredo is)
+    // launch_pair_ties alone (rows [first, last)): best, next and second as the products of first halfs left them; rows of more
+    // than two candidates into list, pairs that fp32 sums do not settle into redo (also: raised as nredo is)
+    const uint32_t *cmax_left;
+    const float *left;
+    const uint32_t *skipped2;    // as skipped
+    uint32_t skip_from2;
     const unsigned long long *next;
     const float *x, *cent, *cnorm; // dense fp32 rows [.][d]; the table [.][ld]
     int d;
