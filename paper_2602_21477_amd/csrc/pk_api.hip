@@ -976,7 +976,7 @@ int run_dense(const Plan &p, const MultiArgs &m, pk_index *own, int64_t *out_ids
     sa.tile_cap = p.tile_cap;
     sa.grab_div = tunables().grabdiv;
     // (no more workgroups than tiles)
-    sa.ecap = (uint32_t)p.slots;
+    sa.slot_room = (uint32_t)p.slots;
     const int most = p.tile_rows ? grid_for(own, own->row_bytes, p.mq_f) : sliced ? p.grid_h : p.grid_f;
     const int grid = (int)std::max<uint32_t>(1u, std::min<uint32_t>((uint32_t)most, p.tile_cap));
     if (p.tile_rows) PK_HIP(launch_scan_few(sa, grid, s));
@@ -1458,7 +1458,9 @@ int note_inserted(pk_index *ix, int64_t m, hipStream_t s)
 constexpr double kHalvesFrom = 1.5e10;
 constexpr size_t kHalvesBytes = 64u << 20;
 
-// Scratch of assign_rows for n vectors in chunks of `chunk`.
+// Scratch of assign_rows for n vectors in chunks of `chunk`: the operands of a chunk and of the table, and 16 bytes a row, or 32 where
+// it begins with the products of the first halfs (8 of them for the second candidate and its value, by which pairs are settled
+// without the products of the whole values).
 struct AssignScratch {
     bool halves; // assign_rows begins with the products of the first halfs alone
     char *xh, *ch, *cs; // rows of a chunk (first halfs, or split), centroids (first halfs; split)

@@ -272,13 +272,14 @@ __device__ __forceinline__ uint32_t block_exscan(const uint32_t *in, uint32_t *o
     return carry;
 }
 
-// One unit of scan work: one page of rows against one group of query slots.
+// One unit of scan work: the rows of one page, or of a part of it (wl_lay_query's tiles where there are few: 64 or 32 rows from
+// anywhere in the page; the rows-stationary kernels': kRrTileRows), against one group of query slots.
 struct Tile {
-    const char *x;    // first row of the page
-    const float *xn;  // squared norms of the rows (L2), else unused
-    uint32_t row0;    // position of the page's first row in the list
+    const char *x;    // the tile's first row
+    const float *xn;  // squared norms of its rows (L2), else unused
+    uint32_t row0;    // position of its first row in the list
     uint32_t qbeg;    // first slot of the group in slot_query / slot_out
-    uint16_t nrows;   // rows to score (<= rows per page)
+    uint16_t nrows;   // its rows
     uint16_t qcnt;    // slots in the group (<= MQ); of wl_lay_query's tiles: the group's number in its list
     uint32_t list;    // of wl_lay_query's tiles: handle * nlist_max + list
 };
@@ -335,8 +336,10 @@ struct ScanArgs {
     const float *tinv;           // [nq] bucket scale (see bucket_of)
     uint32_t *hist;              // [nq][kHistBins] emitted candidates per bucket (zero before the launch)
     uint32_t *tcur;              // [nq] running bucket limit shared by all workgroups (starts at kHistBins-1)
-    uint32_t ecap;               // entries of each query's region of cbuf: query q owns [q * ecap, (q + 1) * ecap); launch_scan_few
-                                 // (which has none): entries of slot_query and slot_out.  (A line more of arguments is 0.3 us.)
+    union { // (not side by side: a line more of arguments is 0.3 us of a search of one query)
+        uint32_t ecap;           // entries of each query's region of cbuf: query q owns [q * ecap, (q + 1) * ecap)
+        uint32_t slot_room;      // launch_scan_few (no regions): entries of slot_query and slot_out
+    };
     uint32_t *ccnt;              // [nq] candidates that passed the gate so far (zero before the launch); those past
                                  // ecap are counted but not stored, and the query is then selected by rescoring
     unsigned long long *cbuf;

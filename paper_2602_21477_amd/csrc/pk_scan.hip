@@ -739,7 +739,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
         };
         const uint32_t in_list = __builtin_amdgcn_readfirstlane(a.lcnt[cur.list]);
         uint32_t slot = qbeg + (uint32_t)tid;
-        slot = slot < a.ecap ? slot : a.ecap - 1u; // (not looked at where there is no such slot)
+        slot = slot < a.slot_room ? slot : a.slot_room - 1u; // (not looked at where there is no such slot)
         const uint32_t sq = tid < MQ ? a.slot_query[slot] : 0u, out = tid < MQ ? a.slot_out[slot] : 0u;
         load(x0, 0);
         load(x1, 1);
@@ -1358,7 +1358,7 @@ static hipError_t launch_few_one(const ScanArgs &a, int grid, hipStream_t s)
 // wl_lay_query's tiles of at most kFewRows rows (grid: at most as many workgroups as there is room for tiles)
 hipError_t launch_scan_few(const ScanArgs &a, int grid, hipStream_t s)
 {
-    if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || !a.lcnt || a.ecap == 0 || a.tile_cap == 0 || grid < 1 || (uint32_t)grid > a.tile_cap)
+    if (a.row_bytes <= 0 || a.row_bytes % kIterBytes != 0 || !a.lcnt || a.slot_room == 0 || a.tile_cap == 0 || grid < 1 || (uint32_t)grid > a.tile_cap)
         return hipErrorInvalidValue;
     const bool f16 = a.storage == PK_F16;
     switch (a.mq) {
