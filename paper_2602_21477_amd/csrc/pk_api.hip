@@ -1581,7 +1581,7 @@ struct InsertScratch {
 // A last chunk that cannot fill tiles (coarse_tiles) takes the centroid kernel, as an insert of its size does.  What the
 // first chunk leaves undecided says what the others are spared: a round is the longer way where it decides less than what it takes
 // of the next one's time.  Round 1 takes 0.4 of round 2's for rows of 768 elements and 0.6 for 128 (32768 rows x 4096 and
-// 1024 lists: 235 of 580 us, 29 of 47: a search for the best, and products), round 2 two sevenths of round 3's.
+// 1024 lists: 235 of 580 us (by now 250), 29 of 47: a search for the best, and products), round 2 two sevenths of round 3's.
 // Small sets (as.halves false) go without round 1: round 2 is one launch for all rows then.
 int assign_rows(const float *x, int64_t n, const Table &t, int num_cu, const AssignScratch &as, int64_t chunk,
                 unsigned long long *best, hipStream_t s)

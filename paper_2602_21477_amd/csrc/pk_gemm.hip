@@ -831,14 +831,14 @@ __device__ __forceinline__ void best_of_first(const SplitGemmArgs &a, f32x16 (&a
 // leaves the matrix cores idle.
 // Rows keep their best two columns, and whether a third is near: two candidates are settled by pair_ties_kernel, more by the
 // products of the whole values.
-// 32768 x 4096 x 768 in 235 - 252 us, by the box (some 840 TFLOP/s; a workgroup per tile and eight instructions a value in the search
-// took 252 where six, with less than the whole value, took 235);
+// 32768 x 4096 x 768 in 247 - 252 us = 825 TFLOP/s (six instructions a value in the search, with less than the whole value, 242 - 246 on the
+// same boxes; a workgroup per tile and eight instructions 252 where the six took 235);
 // a large library product of halfs runs at 1390 here.  150 us go to the matrix instructions at the clock they leave (timed
 // alone), and what else is done adds to that as if one after the other: with the two waves of a SIMD taking turns to read and to
 // multiply, a barrier between, and pieces in an order without bank conflicts, 234; two workgroups per CU with tiles of half the size
 // (249 of 252), three buffers (247) and operands read ahead (253) change nothing, waves of 128 x 128, one per SIMD, take 289.
-// A k-means iteration of 262 144 rows over 4096 lists 3400 -> 2800 us (a tenth of its rows have two candidates, for which
-// the products of the whole values took 0.49 ms, pair_ties_kernel takes 0.06), with every list given twice 15.4 -> 4.5 ms.
+// A k-means iteration of 262 144 rows over 4096 lists 3560 -> 3000 us (a tenth of its rows have two candidates, for which
+// the products of the whole values took 0.49 ms, pair_ties_kernel takes 0.06), with every list given twice 15.9 -> 4.7 ms.
 template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2))) void gemm_first_kernel(SplitGemmArgs a)
 {

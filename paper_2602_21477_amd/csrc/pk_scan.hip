@@ -703,9 +703,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 // does, a chain of round trips to memory.  So tiles are of 64 rows, 16 a wave, which leaves registers for four slices of them:
 // three are on their way while one is multiplied, and the first are requested together with the slots and queries.  Same
 // instructions per row and query as in scan_kernel, so the same values.  Of what is left, the products of a row are a third: they
-// depend on each other (16 instructions of 32 cycles a slice in fp32).  us, scan_kernel or scan_ks_kernel and this one:
-// 27 311 x 896, 6 queries of 19 of 213 lists 31.4 and 14.5; 14 445 x 640, 5 of 5 of 128 27.6 and 12.7; 78 578 x 1418, one query of 17 of
-// 617 (sliced queries) 54.2 and 19.2; 300 000 x 1024, 4 of 16 of 512 (146 MB: 4.4 TB/s) 38.6 and 32.7.
+// depend on each other (16 instructions of 32 cycles a slice in fp32).  us, scan_kernel or scan_ks_kernel and this one (traced in turn):
+// 27 311 x 896, 6 queries of 19 of 213 lists (41 MB) 19.9 and 13.3; 14 445 x 640, 5 of 5 of 128 15.4 and 10.7; 78 578 x 1418, one query of
+// 17 of 617 (sliced queries) 32.8 and 16.0; 300 000 x 1024, 4 of 16 of 512 (150 MB: 4.6 TB/s) 37.6 and 32.3.
 template <int STORAGE, int MT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void scan_few_kernel(ScanArgs a)
 {
